@@ -74,8 +74,8 @@ def parse():
     return ap.parse_args()
 
 
-TRAVERSAL_SOURCES = ("fs_internal.h", "fs_lds.h", "fs_model.hip", "fs_rank.hip",
-                     "fs_traverse_lds.hip")
+TRAVERSAL_SOURCES = ("fs_internal.h", "fs_lds.h", "fs_model.hip", "fs_rank.hip", "fs_treelet.h",
+                     "fs_treelet.hip", "fs_treelet_pack.hip", "fs_traverse_lds.hip")
 
 
 def source_digest() -> str:
@@ -314,7 +314,7 @@ def evolve_main(args, np, torch, api, W):
                       "seed": args.seed, "scale": args.scale},
            "roofline": {"bound": "hbm", "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS,
                         "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 5), "traffic": None,
-                        "kernel": "traverse_lds_kernel", "kernel_avg_ms": round(trav_avg, 5),
+                        "kernel": "treelet_pair/spread_kernel|traverse_lds_kernel", "kernel_avg_ms": round(trav_avg, 5),
                         "algorithmic_bytes_per_launch": int(alg_bytes)},
            "kernels_ms_per_step": {k: round(v[0] / max(1, args.steps), 5) for k, v in prof.items()
                                    if v[1]},
@@ -390,12 +390,13 @@ def main():
     per_step = sorted(marks[i].elapsed_time(marks[i + 1]) for i in range(args.steps))
     rows_per_s = n_rows / (ms_per_step * 1e-3)
 
-    # ---- roofline of the dominant kernel (LDS-staged traversal) --------------------------------
+    # ---- roofline of the dominant kernel (the traversal) --------------------------------
     # Algorithmic bytes per launch: every feature once (n_features * 4 B per row), one fp32 row
     # score written per row, each family's packed model read once.
-    # The traversal is one of: LDS kernel; rank coding + rank kernel (deep perfect trees);
+    # The traversal is one of: byte-rank treelets or float trees in LDS (one profile group); rank coding +
+    # rank kernel (deep perfect trees);
     # global-memory kernel.  Whichever carried the rows is the dominant kernel (group).
-    cands = {"traverse_lds_kernel": prof["traverse"],
+    cands = {"treelet_pair/spread_kernel|traverse_lds_kernel": prof["traverse"],
              "rank_code_kernel+traverse_rank_kernel":
                  (prof["rank_code"][0] + prof["traverse_rank"][0], prof["traverse_rank"][1]),
              "traverse_global_kernel": prof["traverse_global"]}

@@ -38,8 +38,8 @@
  *     synchronised, the old buffer freed and a larger one allocated.  A caller that has
  *     reserved enough (fs_workspace_bytes, fs_topk_workspace_bytes, fs_workspace_reserve)
  *     never gets here;
- *   - the call's descriptors (232 bytes per family, 56 per top-k workgroup) exceed 16 KB
- *     (about 70 families or 290 top-k workgroups).  Up to that size they travel as kernel
+ *   - the call's descriptors (280 bytes per family, 56 per top-k workgroup) exceed 20 KB
+ *     (about 70 families or 360 top-k workgroups).  Up to that size they travel as kernel
  *     arguments; beyond it they are staged through a ring of 8 pinned slots per device: a
  *     slot grows when it is too small, and the ninth such submission waits until the first
  *     has finished on the device.
@@ -288,7 +288,10 @@ enum {
     FS_TUNE_TRAIN_PACKED = 7,     /* 0: separate 64-bit gradient / curvature sums only              */
     FS_TUNE_LDS_GROUPS = 8,       /* 1..16: tile groups a workgroup of the LDS traversal takes in a
                                      row (automatic: 1..4 by the length of the launch)             */
-    FS_TUNE_OPTIONS = 9
+    FS_TUNE_TREELET = 9,          /* 0: never walk byte-rank treelets, 1: whenever the model fits them */
+    FS_TUNE_TREELET_FORM = 10,    /* 0: two 4-tile workgroups per compute unit, 1 / 2 / 3: 4 / 2 / 1
+                                     tiles shared by 12 wavefronts (read by fs_score_families)     */
+    FS_TUNE_OPTIONS = 11
 };
 int fs_tune_set(int32_t option, int32_t value);
 int32_t fs_tune_get(int32_t option);   /* current override, -1 = automatic */

@@ -11,7 +11,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfamilyseer.so")
 CEILINGS = os.path.join(HERE, "fs_ceilings.bin")   # stand-alone microbenchmarks (csrc/fs_ceilings.hip)
 
-SOURCES = ["fs_api.hip", "fs_model.hip", "fs_traverse_lds.hip", "fs_rank.hip", "fs_traverse_global.hip", "fs_segsum.hip", "fs_topk.hip", "fs_pack.hip", "fs_train.hip", "fs_gather.hip"]
+SOURCES = ["fs_api.hip", "fs_model.hip", "fs_traverse_lds.hip", "fs_rank.hip", "fs_treelet.hip", "fs_treelet_pack.hip", "fs_traverse_global.hip", "fs_segsum.hip", "fs_topk.hip", "fs_pack.hip", "fs_train.hip", "fs_gather.hip"]
 
 FLAGS = [
     "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared",

@@ -51,7 +51,7 @@ enum { kScratchScore = 0, kScratchTopk = 1, kScratchRegions = 2 };
 // a fixed device buffer (one per kind of call), in stream order in front of the kernels that read
 // them.  No pinned staging, no copy, no event and nothing to wait for, so such a call can also be
 // recorded into a HIP graph.  Longer descriptor arrays go through the ring of pinned slots.
-constexpr size_t kInlineBytes = 16384;
+constexpr size_t kInlineBytes = 20480;
 constexpr size_t kBlobBytes = 3968;               // one kernel argument (the limit is 4 KB)
 enum { kDescScore = 0, kDescTopk = 1, kDescKinds = 2 };
 
@@ -207,7 +207,7 @@ static int finish_desc(const DescBuf &db, hipStream_t stream)
 
 // ---- test and tuning overrides -----------------------------------------------------------------
 static std::mutex g_tune_mu;
-static int g_tune[FS_TUNE_OPTIONS] = {-1, -1, -1, -1, -1, -1, -1, -1, -1};
+static int g_tune[FS_TUNE_OPTIONS] = {-1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1};
 
 int tune(int option)
 {
@@ -347,13 +347,33 @@ static int lds_groups_wanted(int64_t groups_in_launch, double group_us, int n_co
     return g;
 }
 
+// Form of the treelet kernel for a call: long launches take two 4-tile workgroups per compute unit;
+// when that leaves compute units idle, fewer tiles per workgroup whose wavefronts share the trees.
+static int treelet_form(int n_families, const fs_family *fams, int n_compute_units)
+{
+    const int forced = tune(FS_TUNE_TREELET_FORM);
+    if (forced >= 0 && forced < kTreeletForms)
+        return forced;
+    int64_t tiles = 0;
+    for (int f = 0; f < n_families; ++f)
+        if (fams[f].model->tl_ok)
+            tiles += (fams[f].n_rows + 63) / 64;
+    if (tiles <= n_compute_units)
+        return kTreeletSpread1;
+    if (tiles <= 2 * n_compute_units)
+        return kTreeletSpread2;
+    if (tiles <= 4 * n_compute_units)
+        return kTreeletSpread4;
+    return kTreeletPair;
+}
+
 // Row-major input needs no pass of its own where the first kernel to touch the features can
 // read it: the rank-coding kernel always can; the LDS kernel transposes tiles on their way
 // into LDS (through the still unused chunk region) when rows are whole 16-byte pieces and at
 // least 8 padded rows fit below the tiles.  Other row-major families are re-tiled into scratch.
 static bool rowmajor_in_kernel(const fs_model *m)
 {
-    if (m->rank_ok)
+    if (m->tl_ok || m->rank_ok)
         return true;
     return m->lds_ok && m->n_features % 4 == 0 && m->lds_tile0 >= 8 * (m->n_features + 1) * 4;
 }
@@ -393,7 +413,7 @@ static int score_scratch_floats(const char *who, int32_t n_families, const fs_fa
             scratch_floats += (size_t)a.n_rows;
         if (a.model->rank_ok)                                // u16 rank tiles, in float units
             scratch_floats += (size_t)((a.n_rows + 63) / 64) * 32 * (size_t)rank_tile_cols(a.model->n_features) + 4;
-        if ((a.model->rank_ok || a.model->lds_ok) && a.layout == FS_ROWMAJOR &&
+        if ((a.model->tl_ok || a.model->rank_ok || a.model->lds_ok) && a.layout == FS_ROWMAJOR &&
             !rowmajor_in_kernel(a.model))                                         // re-tiled copy
             scratch_floats += (size_t)((a.n_rows + 63) / 64) * 64 * (size_t)a.model->n_features + 4;
     }
@@ -470,8 +490,10 @@ extern "C" int fs_score_families(int32_t n_families, const fs_family *fams, void
         return rc;
     FamDesc *h = (FamDesc *)db.host;
     int64_t trav_blocks = 0, seg_blocks = 0, lds_blocks[kLdsModes] = {0, 0};
-    int64_t rk_blocks = 0, bin_blocks = 0, retile_blocks = 0;
-    bool rk_dump = false;
+    int64_t rk_blocks = 0, bin_blocks = 0, retile_blocks = 0, tl_blocks[2] = {0, 0};
+    bool rk_dump = false, tl_dump[2] = {false, false};
+    // treelet launches: 0 takes the form of the call, 1 the models that cannot take that
+    const int tl_form[2] = {treelet_form(n_families, fams, ctx->n_compute_units), kTreeletSpread4};
     bool dump[kLdsModes] = {false, false};
     // tile groups the LDS kernel will see, per workgroup shape (row-major families included:
     // they count towards the length of the launch, though their workgroups take one group each)
@@ -479,7 +501,7 @@ extern "C" int fs_score_families(int32_t n_families, const fs_family *fams, void
     double lds_us[kLdsModes] = {0.0, 0.0};           // all groups of the launch, by the planner's estimate
     for (int f = 0; f < n_families; ++f) {
         const fs_model *m = fams[f].model;
-        if (!m->rank_ok && m->lds_ok) {
+        if (!m->tl_ok && !m->rank_ok && m->lds_ok) {
             const int64_t g = ((fams[f].n_rows + 63) / 64 + m->lds_tiles - 1) / m->lds_tiles;
             lds_groups[m->lds_mode] += g;
             lds_us[m->lds_mode] += (double)g * (double)m->lds_group_us;
@@ -532,7 +554,7 @@ extern "C" int fs_score_families(int32_t n_families, const fs_family *fams, void
         d.rowmajor_src = nullptr;
         d.retile_block0 = (int32_t)retile_blocks;
         d.retile_colblocks = 0;
-        const bool fast = a.model->rank_ok || a.model->lds_ok;
+        const bool fast = a.model->tl_ok || a.model->rank_ok || a.model->lds_ok;
         const bool in_kernel = a.layout == FS_ROWMAJOR && rowmajor_in_kernel(a.model);
         if (fast && a.layout == FS_ROWMAJOR && a.n_rows > 0 && !in_kernel) {
             const int64_t tiles = (a.n_rows + 63) / 64;
@@ -560,11 +582,20 @@ extern "C" int fs_score_families(int32_t n_families, const fs_family *fams, void
         d.bin_feats_per_group = a.model->n_features;
         d.bin_tiles_per_block = kBinTilesPerBlock;
         d.cut_bits = a.model->cut_bits;
-        d.pad = 0;
+        d.tl = a.model->d_tl;
+        d.tl_block0[0] = (int32_t)tl_blocks[0];
+        d.tl_block0[1] = (int32_t)tl_blocks[1];
         // Column-blocked features: deep perfect-tree models are rank-coded first and walked by
         // the rank kernel, other models that fit the LDS format take the LDS kernel; everything
         // else is walked from global memory.
-        if (a.model->rank_ok && (colblock || in_kernel)) {
+        if (a.model->tl_ok) {
+            const int64_t tiles = (a.n_rows + 63) / 64;
+            const int which = tl_form[0] == kTreeletPair && !a.model->tl_pair ? 1 : 0;
+            const int per_wg = kTreeletFormTiles[tl_form[which]];
+            tl_blocks[which] += (tiles + per_wg - 1) / per_wg;
+            if (a.leaf_idx && a.n_rows > 0)
+                tl_dump[which] = true;
+        } else if (a.model->rank_ok && (colblock || in_kernel)) {
             const int64_t tiles = (a.n_rows + 63) / 64;
             scratch_pos = (scratch_pos + 3) & ~(size_t)3;            // 16-byte aligned tiles
             d.ranks = (uint16_t *)(ctx->scratch[kScratchScore] + scratch_pos);
@@ -599,7 +630,7 @@ extern "C" int fs_score_families(int32_t n_families, const fs_family *fams, void
     }
     if (trav_blocks >= ((int64_t)1 << 31) || seg_blocks >= ((int64_t)1 << 31) ||
         lds_blocks[0] >= ((int64_t)1 << 31) || lds_blocks[1] >= ((int64_t)1 << 31) ||
-        rk_blocks >= ((int64_t)1 << 31) || bin_blocks >= ((int64_t)1 << 31) ||
+        tl_blocks[0] >= ((int64_t)1 << 31) || tl_blocks[1] >= ((int64_t)1 << 31) || rk_blocks >= ((int64_t)1 << 31) || bin_blocks >= ((int64_t)1 << 31) ||
         retile_blocks >= ((int64_t)1 << 31))
         return fail(FS_EUNSUPPORTED, "fs_score_families: too much work for one submission");
 
@@ -612,12 +643,15 @@ extern "C" int fs_score_families(int32_t n_families, const fs_family *fams, void
         rc = launch_retile(d_desc, n_families, (int)retile_blocks, stream);
         prof_stop(stream);
     }
-    for (int md = 0; md < kLdsModes && rc == FS_OK; ++md) {
-        if (lds_blocks[md] == 0)
-            continue;
+    if (rc == FS_OK && tl_blocks[0] + tl_blocks[1] + lds_blocks[0] + lds_blocks[1] > 0) {
         prof_start(kKernTraverse, stream);
-        rc = launch_traverse_lds(d_desc, n_families, md, (int)lds_blocks[md], groups_per_wg[md],
-                                 dump[md], stream);
+        for (int i = 0; i < 2 && rc == FS_OK; ++i)
+            if (tl_blocks[i] > 0)
+                rc = launch_treelet(d_desc, n_families, i, tl_form[i], (int)tl_blocks[i], tl_dump[i], stream);
+        for (int md = 0; md < kLdsModes && rc == FS_OK; ++md)
+            if (lds_blocks[md] > 0)
+                rc = launch_traverse_lds(d_desc, n_families, md, (int)lds_blocks[md], groups_per_wg[md],
+                                         dump[md], stream);
         prof_stop(stream);
     }
     if (rc == FS_OK && bin_blocks > 0) {

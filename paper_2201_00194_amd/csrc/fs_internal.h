@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "familyseer.h"
+#include "fs_treelet.h"
 
 namespace fs {
 
@@ -121,6 +122,12 @@ struct fs_model {
     float *d_cuts;             // [n_features][2^cut_bits]: the feature's sorted distinct
                                // thresholds, NaN-padded, as a breadth-first search tree
     int32_t cut_bits;
+    // Byte-rank treelets (fs_treelet.h); null if the model does not fit that format
+    bool tl_ok;
+    bool tl_pair;              // two chunk buffers fit half a compute unit's LDS
+    int32_t tl_cols;
+    void *d_tl_data;           // everything of this format, one allocation
+    fs::TreeletModel *d_tl;    // inside it
 };
 
 namespace fs {
@@ -168,6 +175,8 @@ struct FamDesc {
     int32_t retile_colblocks;        // column blocks per tile (0: family not re-tiled)
     int32_t cut_bits;                // threshold tables are padded to 2^cut_bits entries
     int32_t pad;
+    const TreeletModel *tl;          // byte-rank treelets
+    int32_t tl_block0[2];            // first block of this family in the two treelet launches
 };
 
 // One workgroup of the first top-k stage: the whole request, or one slice of a large one.
@@ -236,6 +245,14 @@ __host__ __device__ inline int lds_groups_per_wg(int layout, int n_features, int
 int launch_rank_code(const FamDesc *d_desc, int n_families, int total_blocks, hipStream_t stream);
 int launch_traverse_rank(const FamDesc *d_desc, int n_families, int total_blocks, bool dump,
                          hipStream_t stream);
+// Forms of the treelet traversal: two 4-tile workgroups per compute unit, or one workgroup of 12
+// wavefronts that share 4, 2 or 1 tiles.
+enum { kTreeletPair = 0, kTreeletSpread4 = 1, kTreeletSpread2 = 2, kTreeletSpread1 = 3, kTreeletForms = 4 };
+constexpr int kTreeletFormTiles[kTreeletForms] = {4, 4, 2, 1};
+// `launch`: which of FamDesc::tl_block0 numbers the blocks (a call makes up to two launches: models whose
+// chunks only fit a whole compute unit's LDS cannot take the first form).
+int launch_treelet(const FamDesc *d_desc, int n_families, int launch, int form, int total_blocks, bool dump,
+                   hipStream_t stream);
 int launch_segsum(const FamDesc *d_desc, int n_families, int total_blocks, hipStream_t stream);
 int launch_topk(const TopkDesc *d_desc, int n_blocks, int max_k, hipStream_t stream);
 // max_padded: largest (slices * k rounded up to a power of two) over the requests

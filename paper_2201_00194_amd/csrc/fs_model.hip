@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "fs_internal.h"
+#include "fs_treelet_pack.h"
 
 using namespace fs;
 
@@ -424,6 +425,7 @@ void free_device(fs_model *m)
     if (m->d_rk_nodes) (void)hipFree(m->d_rk_nodes);
     if (m->d_rk_ids) (void)hipFree(m->d_rk_ids);
     if (m->d_cuts) (void)hipFree(m->d_cuts);
+    if (m->d_tl_data) (void)hipFree(m->d_tl_data);
 }
 
 template <typename T>
@@ -436,6 +438,62 @@ hipError_t upload(T **dst, const std::vector<T> &src)
     if (e != hipSuccess)
         return e;
     return hipMemcpy(*dst, src.data(), src.size() * sizeof(T), hipMemcpyHostToDevice);
+}
+
+// One allocation and one copy: [model][segments][chunks][image][ids][columns and tables per segment],
+// the pointers inside set for where it will lie.
+hipError_t upload_treelets(const TreeletPlan &tl, void **d_data, TreeletModel **d_model)
+{
+    size_t total = 0;
+    auto room = [&](size_t bytes) {
+        const size_t at = total;
+        total = (total + bytes + 255) & ~(size_t)255;
+        return at;
+    };
+    const size_t model_at = room(sizeof(TreeletModel)), seg_at = room(tl.segments.size() * sizeof(TreeletSegment)),
+                 chunk_at = room(tl.chunks.size() * sizeof(TreeletChunk)), image_at = room(tl.image.size()),
+                 id_at = room(tl.ids.size() * sizeof(uint16_t));
+    std::vector<size_t> cols_at, tables_at;
+    for (const TreeletSegmentPlan &sp : tl.segments) {
+        cols_at.push_back(room(sp.cols.size() * sizeof(TreeletCol)));
+        tables_at.push_back(room(sp.tables.size()));
+    }
+    hipError_t e = hipMalloc(d_data, total);
+    if (e != hipSuccess)
+        return e;
+    uint8_t *base = (uint8_t *)*d_data;
+    std::vector<uint8_t> host(total, 0);
+    TreeletModel tm;
+    memset(&tm, 0, sizeof(tm));
+    tm.image = base + image_at;
+    tm.chunks = (const TreeletChunk *)(base + chunk_at);
+    tm.segments = (const TreeletSegment *)(base + seg_at);
+    tm.ids = (const uint16_t *)(base + id_at);
+    tm.n_segments = (int32_t)tl.segments.size();
+    tm.most_cols = tl.most_cols;
+    tm.buf_bytes = tl.buf_bytes;
+    tm.max_trees = tl.max_trees;
+    memcpy(&host[model_at], &tm, sizeof(tm));
+    memcpy(&host[chunk_at], tl.chunks.data(), tl.chunks.size() * sizeof(TreeletChunk));
+    memcpy(&host[image_at], tl.image.data(), tl.image.size());
+    memcpy(&host[id_at], tl.ids.data(), tl.ids.size() * sizeof(uint16_t));
+    for (size_t i = 0; i < tl.segments.size(); ++i) {
+        const TreeletSegmentPlan &sp = tl.segments[i];
+        TreeletSegment g;
+        memset(&g, 0, sizeof(g));
+        g.cols = (const TreeletCol *)(base + cols_at[i]);
+        g.tables = base + tables_at[i];
+        g.n_cols = (int32_t)sp.cols.size();
+        g.buckets = sp.buckets;
+        g.table_stride = sp.table_stride;
+        g.first_chunk = sp.first_chunk;
+        g.n_chunks = sp.n_chunks;
+        memcpy(&host[seg_at + i * sizeof(g)], &g, sizeof(g));
+        memcpy(&host[cols_at[i]], sp.cols.data(), sp.cols.size() * sizeof(TreeletCol));
+        memcpy(&host[tables_at[i]], sp.tables.data(), sp.tables.size());
+    }
+    *d_model = (TreeletModel *)(base + model_at);
+    return hipMemcpy(base, host.data(), total, hipMemcpyHostToDevice);
 }
 
 }  // namespace
@@ -468,8 +526,7 @@ extern "C" int fs_model_create(fs_model **out, int32_t n_features, int32_t n_tre
         return fail(FS_EINVAL, "fs_model_create: a node array is NULL");
 
     try {
-        // ---- validation + flat format ----
-        std::vector<GNode> nodes((size_t)n_nodes);
+        // ---- validation ----
         std::vector<int32_t> depth((size_t)n_nodes, 0);
         int32_t max_depth = 0;
         for (int t = 0; t < n_trees; ++t) {
@@ -477,12 +534,7 @@ extern "C" int fs_model_create(fs_model **out, int32_t n_features, int32_t n_tre
             const int32_t sz = tree_off[t + 1] - o;
             for (int32_t n = 0; n < sz; ++n) {
                 const int32_t g = o + n;
-                GNode nd;
-                if (split_feature[g] < 0) {
-                    memcpy(&nd.x, &value[g], 4);
-                    nd.y = -1;
-                    nd.z = nd.w = g;
-                } else {
+                if (split_feature[g] >= 0) {
                     if (split_feature[g] >= n_features)
                         return fail(FS_EINVAL, "fs_model_create: tree %d node %d splits on feature "
                                     "%d but the model has %d", t, n, split_feature[g], n_features);
@@ -490,17 +542,12 @@ extern "C" int fs_model_create(fs_model **out, int32_t n_features, int32_t n_tre
                         return fail(FS_EINVAL, "fs_model_create: tree %d node %d has child ids "
                                     "(%d, %d); they must lie in (%d, %d)", t, n, left[g], right[g],
                                     n, sz);
-                    memcpy(&nd.x, &threshold[g], 4);
-                    nd.y = split_feature[g];
-                    nd.z = o + left[g];
-                    nd.w = o + right[g];
                     const int32_t dl = depth[g] + 1;   // parents come before their children
                     if (depth[o + left[g]] < dl) depth[o + left[g]] = dl;
                     if (depth[o + right[g]] < dl) depth[o + right[g]] = dl;
                 }
                 if (depth[g] > max_depth)
                     max_depth = depth[g];
-                nodes[(size_t)g] = nd;
             }
         }
 
@@ -514,12 +561,36 @@ extern "C" int fs_model_create(fs_model **out, int32_t n_features, int32_t n_tre
         m->n_nodes = n_nodes;
         m->bias = bias;
 
+        // ---- byte-rank treelets ----
+        TreeletPlan tl;
+        {
+            // overrides of the other forms ask for those forms
+            const bool others = tune(FS_TUNE_LDS_TILES) >= 0 || tune(FS_TUNE_LDS_MODE) >= 0 ||
+                                tune(FS_TUNE_LDS_GROUPS) >= 0 || tune(FS_TUNE_RANK) == 1;
+            const int want = tune(FS_TUNE_TREELET);
+            if (want != 0 && (want == 1 || (!others && n_trees >= kTreeletMinTrees)))
+                m->tl_ok = build_treelets(n_features, n_trees, tree_off, split_feature, threshold, left, right,
+                                          value, want == 1, &tl);
+            // What the LDS kernel takes for a tile: about 13.5 clocks per level it walks and 3 per feature
+            // of the tile (measured on ensembles of 40 to 400 trees).  Models whose chunks do not fit half
+            // a compute unit's LDS only take treelets where there is no other LDS form.
+            if (m->tl_ok && want != 1 && n_features <= 255 &&
+                (!tl.pair_ok || tl.cost > 13.5 * (double)n_trees * (double)max_depth + 3.0 * (double)n_features))
+                m->tl_ok = false;
+            m->tl_pair = tl.pair_ok;
+            m->tl_cols = tl.most_cols;
+            if (m->tl_ok && tune(FS_TUNE_VERBOSE) > 0)
+                fprintf(stderr, "fs_model_create: treelets, %zu segments of up to %d columns, %zu chunks of at most %d "
+                        "trees and %d bytes%s, about %.0f clocks per tile\n", tl.segments.size(), m->tl_cols,
+                        tl.chunks.size(), tl.max_trees, tl.buf_bytes, tl.pair_ok ? "" : " (whole LDS)", tl.cost);
+        }
+
         // ---- LDS-staged format ----
         std::vector<uint8_t> image;
         std::vector<ChunkHdr> chunks;
         std::vector<uint16_t> slot_ids;
         const int tile_bytes = (n_features + 1) * 256;
-        if (n_trees > 0 && n_features <= 255) {
+        if (n_trees > 0 && n_features <= 255 && !m->tl_ok) {
             int common_depth = -1;
             bool compact = true;
             for (int t = 0; t < n_trees && compact; ++t) {
@@ -713,7 +784,7 @@ extern "C" int fs_model_create(fs_model **out, int32_t n_features, int32_t n_tre
         {
             const int want = tune(FS_TUNE_RANK);   // -1 automatic, 0 never, 1 whenever possible
             int depth = -1;
-            bool perfect = n_trees > 0 && n_features <= 511 && want != 0;
+            bool perfect = n_trees > 0 && n_features <= 511 && want != 0 && !m->tl_ok;
             for (int t = 0; t < n_trees && perfect; ++t) {
                 const int32_t o = tree_off[t];
                 perfect = tree_is_perfect(split_feature + o, left + o, right + o, tree_off[t + 1] - o,
@@ -725,8 +796,30 @@ extern "C" int fs_model_create(fs_model **out, int32_t n_features, int32_t n_tre
                                   left, right, value, &rk_nodes, &rk_ids, &cuts);
         }
 
+        // ---- flat format: what the global-memory kernel walks, for models without another form ----
+        std::vector<GNode> nodes;
+        if (!m->tl_ok && !m->lds_ok && !m->rank_ok) {
+            nodes.resize((size_t)n_nodes);
+            for (int t = 0; t < n_trees; ++t) {
+                const int32_t o = tree_off[t];
+                for (int32_t g = o; g < tree_off[t + 1]; ++g) {
+                    GNode &nd = nodes[(size_t)g];
+                    if (split_feature[g] < 0) {
+                        memcpy(&nd.x, &value[g], 4);
+                        nd.y = -1;
+                        nd.z = nd.w = g;
+                    } else {
+                        memcpy(&nd.x, &threshold[g], 4);
+                        nd.y = split_feature[g];
+                        nd.z = o + left[g];
+                        nd.w = o + right[g];
+                    }
+                }
+            }
+        }
+
         hipError_t e = hipGetDevice(&m->device);
-        if (e == hipSuccess) {
+        if (e == hipSuccess && !m->tl_ok && !m->lds_ok && !m->rank_ok) {
             std::vector<int32_t> toff(tree_off, tree_off + n_trees + 1);
             e = upload(&m->d_tree_off, toff);
         }
@@ -739,6 +832,8 @@ extern "C" int fs_model_create(fs_model **out, int32_t n_features, int32_t n_tre
             if (e == hipSuccess) e = upload(&m->d_rk_ids, rk_ids);
             if (e == hipSuccess) e = upload(&m->d_cuts, cuts);
         }
+        if (e == hipSuccess && m->tl_ok)
+            e = upload_treelets(tl, &m->d_tl_data, &m->d_tl);
         if (e != hipSuccess) {
             free_device(m);
             delete m;

@@ -1,0 +1,487 @@
+// Builds the byte-rank treelet format (fs_treelet.h) of a model on the host.
+#include <algorithm>
+#include <cmath>
+#include <cstring>
+#include <utility>
+#include <vector>
+
+#include "fs_internal.h"
+#include "fs_treelet_pack.h"
+
+namespace fs {
+
+namespace {
+
+// Splits by level pair: counts of tree t's split nodes at depth 2*s, summed over the trees before t, at
+// [s][t]; steps[t] = treelet steps to tree t's deepest leaf (>= 1).  False if a node graph is not a tree
+// (a shared child) or deeper than the format is meant for.
+constexpr int kMaxSteps = 32;
+
+struct Shapes {
+    std::vector<int32_t> sum[kMaxSteps];
+    std::vector<uint8_t> steps;
+    int most_steps = 1;
+};
+
+bool tree_shapes(int n_trees, const int32_t *tree_off, const int32_t *sf, const int32_t *left,
+                 const int32_t *right, Shapes *out)
+{
+    out->steps.assign((size_t)n_trees, 1);
+    std::vector<std::vector<int32_t>> cnt;           // [s][t]
+    std::vector<int16_t> depth;
+    for (int t = 0; t < n_trees; ++t) {
+        const int32_t o = tree_off[t], sz = tree_off[t + 1] - o;
+        depth.assign((size_t)sz, -1);
+        depth[0] = 0;
+        int deepest = 0;
+        for (int32_t n = 0; n < sz; ++n) {           // children have larger ids: one forward pass
+            const int dn = depth[(size_t)n];
+            if (dn < 0 || sf[o + n] < 0)
+                continue;
+            const int32_t l = left[o + n], r = right[o + n];
+            if (l == r || depth[(size_t)l] >= 0 || depth[(size_t)r] >= 0 || dn + 1 > 2 * kMaxSteps)
+                return false;
+            depth[(size_t)l] = depth[(size_t)r] = (int16_t)(dn + 1);
+            if (dn + 1 > deepest)
+                deepest = dn + 1;
+            if ((dn & 1) == 0) {
+                while ((int)cnt.size() <= dn / 2)
+                    cnt.emplace_back((size_t)n_trees, 0);
+                ++cnt[(size_t)(dn / 2)][(size_t)t];
+            }
+        }
+        out->steps[(size_t)t] = (uint8_t)(deepest < 2 ? 1 : (deepest + 1) / 2);
+        out->most_steps = std::max(out->most_steps, (int)out->steps[(size_t)t]);
+    }
+    for (int s = 0; s < out->most_steps; ++s) {
+        out->sum[s].assign((size_t)n_trees + 1, 0);
+        if (s < (int)cnt.size())
+            for (int t = 0; t < n_trees; ++t)
+                out->sum[s][(size_t)t + 1] = out->sum[s][(size_t)t] + cnt[(size_t)s][(size_t)t];
+    }
+    return true;
+}
+
+struct Piece { int feature, at, n; };                // thresholds [at, at + n) of the feature
+
+// Columns and tables for B buckets.
+void build_columns(const std::vector<Piece> &pieces, const std::vector<float> &cuts,
+                   const std::vector<int32_t> &cut_at, int B, TreeletSegmentPlan *out)
+{
+    auto values = [&](const Piece &pc) { return cuts.data() + cut_at[(size_t)pc.feature] + pc.at; };
+    auto bucket_of = [B](float x, const TreeletCol &c) -> int {      // as the device truncates and clamps
+        const float t = std::fmaf(x, c.scale, c.offset);
+        return t >= (float)(B - 1) ? B - 1 : (t > 0.0f ? (int)t : 0);
+    };
+    out->cols.clear();
+    int most_cuts = 0, most_steps = 0;
+    std::vector<uint16_t> buckets(pieces.size() * (size_t)kTreeletMaxCuts, 0);
+    uint16_t tried[kTreeletMaxCuts];
+    for (const Piece &pc : pieces) {
+        const float *v = values(pc);
+        // The range the buckets cover: all finite thresholds, or all but the lowest or the highest (an
+        // exact zero far below the rest), a little wider or narrower; the fullest bucket decides.
+        int lo = 0, hi = pc.n - 1;
+        while (lo < hi && std::isinf(v[lo])) ++lo;
+        while (hi > lo && std::isinf(v[hi])) --hi;
+        TreeletCol best = {pc.feature, 0.0f, 0.0f, 0};
+        int best_load = pc.n;                        // one bucket for all
+        for (int trial = 0; trial < 8 && best_load > 3; ++trial) {
+            const int a = std::min(lo + (trial & 1), hi), b = std::max(hi - ((trial >> 1) & 1), a);
+            const double span = (double)v[b] - (double)v[a];
+            if (!(span > 0.0))
+                continue;
+            const double s = (B - 2.0) * (1.0 - 0.07 * (trial >> 2)) / span, o = 1.0 - (double)v[a] * s;
+            if (!(s < 3e38 && s > 1e-37 && std::fabs(o) < 3e38))
+                continue;
+            const TreeletCol c = {pc.feature, (float)s, (float)o, 0};
+            int load = 0, run = 0, prev = -1;
+            for (int i = 0; i < pc.n; ++i) {
+                const int bk = bucket_of(v[i], c);
+                tried[i] = (uint16_t)bk;
+                run = bk == prev ? run + 1 : 1;
+                prev = bk;
+                load = std::max(load, run);
+            }
+            if (load < best_load) {
+                best_load = load;
+                best = c;
+                memcpy(&buckets[out->cols.size() * (size_t)kTreeletMaxCuts], tried, sizeof(tried[0]) * (size_t)pc.n);
+            }
+        }
+        while ((1 << best.steps) - 1 < best_load)
+            ++best.steps;
+        out->cols.push_back(best);
+        most_cuts = std::max(most_cuts, pc.n);
+        most_steps = std::max(most_steps, best.steps);
+    }
+    // probes go up to 2^(steps - 1) - 1 past the number of thresholds
+    const int n_keys = (most_cuts + (1 << std::max(most_steps - 1, 0)) + 3) / 4 * 4;
+    out->buckets = B;
+    out->table_stride = B + 4 * n_keys;
+    out->tables.assign(pieces.size() * (size_t)out->table_stride + kTreeletTablePad, 0);
+    for (size_t c = 0; c < pieces.size(); ++c) {
+        const float *v = values(pieces[c]);
+        const uint16_t *bucket = &buckets[c * (size_t)kTreeletMaxCuts];
+        uint8_t *tab = out->tables.data() + c * (size_t)out->table_stride;
+        float *key = (float *)(tab + B);
+        for (int i = 0; i < n_keys; ++i)
+            key[i] = i < pieces[c].n ? v[i] : __builtin_nanf("");
+        for (int b = 0, i = 0; b < B; ++b) {
+            tab[b] = (uint8_t)i;                     // thresholds in lower buckets
+            while (i < pieces[c].n && bucket[i] == b)
+                ++i;
+        }
+    }
+}
+
+// Thresholds and columns of a segment's trees.
+struct SegmentCuts {
+    std::vector<float> cuts;                         // sorted and distinct, per feature
+    std::vector<int32_t> cut_at;
+    std::vector<Piece> pieces;
+};
+
+// Order of floats as unsigned integers (-0 joins +0).
+inline uint32_t ordered(float v)
+{
+    uint32_t b;
+    v = v + 0.0f;
+    memcpy(&b, &v, 4);
+    return (b & 0x80000000u) ? ~b : b | 0x80000000u;
+}
+
+// Sorts the thresholds of nodes [node0, node1), lists the columns and sets word[node] = column << 8 | rank of
+// every split (rank 0 for a NaN threshold: it sends nothing left).  False if the trees need more
+// columns than a byte names.
+bool segment_cuts(int n_features, int32_t node0, int32_t node1, const int32_t *sf, const float *thr,
+                  std::vector<uint64_t> &keys, uint16_t *word, SegmentCuts *out)
+{
+    std::vector<int32_t> at((size_t)n_features + 1, 0);
+    std::vector<uint8_t> used((size_t)n_features, 0);
+    std::vector<int32_t> nan_nodes;
+    keys.resize(2 * (size_t)(node1 - node0) + 1);
+    uint64_t *from = keys.data();
+    size_t n_keys = 0;                               // (the loop has no branch that a leaf would upset)
+    for (int32_t g = node0; g < node1; ++g) {
+        from[n_keys] = ((uint64_t)ordered(thr[g]) << 32) | (uint32_t)g;
+        n_keys += sf[g] >= 0;
+    }
+    uint32_t count[3][2048] = {};
+    {
+        size_t n = 0;
+        for (size_t i = 0; i < n_keys; ++i) {
+            const uint32_t g = (uint32_t)from[i], k = (uint32_t)(from[i] >> 32);
+            used[(size_t)sf[g]] = 1;
+            if (!(thr[g] == thr[g])) {
+                nan_nodes.push_back((int32_t)g);
+                continue;
+            }
+            from[n++] = from[i];
+            ++at[(size_t)sf[g] + 1];
+            ++count[0][k & 2047];
+            ++count[1][(k >> 11) & 2047];
+            ++count[2][k >> 22];
+        }
+        n_keys = n;
+    }
+    for (int f = 0; f < n_features; ++f)
+        at[(size_t)f + 1] += at[(size_t)f];
+    // by threshold (three digits, least first), then stably by feature
+    uint64_t *to = from + n_keys;
+    for (int pass = 0; pass < 3; ++pass) {
+        uint32_t before = 0;
+        for (uint32_t &c : count[pass]) {
+            const uint32_t here = c;
+            c = before;
+            before += here;
+        }
+        for (size_t i = 0; i < n_keys; ++i)
+            to[count[pass][(size_t)((from[i] >> (32 + 11 * pass)) & 2047)]++] = from[i];
+        std::swap(from, to);
+    }
+    std::vector<int32_t> fill(at.begin(), at.end() - 1);
+    for (size_t i = 0; i < n_keys; ++i)
+        to[(size_t)fill[(size_t)sf[(uint32_t)from[i]]]++] = from[i];
+    out->cuts.resize(n_keys);
+    out->cut_at.assign((size_t)n_features + 1, 0);
+    out->pieces.clear();
+    std::vector<int32_t> first_col((size_t)n_features, 0);
+    for (int f = 0; f < n_features; ++f) {
+        if (!used[(size_t)f])
+            continue;
+        const int first = (int)out->pieces.size();
+        first_col[(size_t)f] = first;
+        const uint64_t *k = to + at[(size_t)f];
+        const int m = at[(size_t)f + 1] - at[(size_t)f];
+        float *v = out->cuts.data() + at[(size_t)f];
+        int n = 0;
+        for (int i = 0; i < m; ++i) {
+            n += i == 0 || (k[i] >> 32) != (k[i - 1] >> 32);
+            v[n - 1] = thr[(uint32_t)k[i]] + 0.0f;
+            word[(uint32_t)k[i]] = (uint16_t)(((first + (n - 1) / kTreeletMaxCuts) << 8) | ((n - 1) % kTreeletMaxCuts + 1));
+        }
+        out->cut_at[(size_t)f] = at[(size_t)f];
+        int from = 0;
+        do {
+            out->pieces.push_back({f, from, std::min(kTreeletMaxCuts, n - from)});
+            from += kTreeletMaxCuts;
+        } while (from < n);
+        if (out->pieces.size() > (size_t)kTreeletMaxCols)
+            return false;
+    }
+    for (int32_t g : nan_nodes)
+        word[g] = (uint16_t)(first_col[(size_t)sf[g]] << 8);
+    if (out->pieces.empty())                         // single leaves only: one column nobody asks
+        out->pieces.push_back({0, 0, 0});
+    return true;
+}
+
+}  // namespace
+
+bool build_treelets(int n_features, int n_trees, const int32_t *tree_off, const int32_t *sf,
+                    const float *thr, const int32_t *left, const int32_t *right, const float *val,
+                    bool any_size, TreeletPlan *out)
+{
+    if (n_trees < 1)
+        return false;
+    Shapes shape;
+    if (!tree_shapes(n_trees, tree_off, sf, left, right, &shape))
+        return false;
+    // bytes of a chunk of trees [a, b) (padded to units) and its step count
+    auto chunk_size = [&](int a, int b, int *steps, int *entries, int *values) -> size_t {
+        int s = 1;
+        for (int t = a; t < b; ++t)
+            s = std::max(s, (int)shape.steps[(size_t)t]);
+        int64_t e = (b - a + kTreeletUnit - 1) / kTreeletUnit * kTreeletUnit;
+        for (int i = 0; i + 1 < s; ++i)
+            e += 4 * (int64_t)(shape.sum[i][(size_t)b] - shape.sum[i][(size_t)a]);
+        const int64_t v = 4 * (int64_t)(shape.sum[s - 1][(size_t)b] - shape.sum[s - 1][(size_t)a]);
+        *steps = s;
+        *entries = (int)e;
+        *values = (int)(e + v);
+        return ((size_t)(8 * e + 4 * (e + v)) + 1023) & ~(size_t)1023;
+    };
+    int s_, e_, v_;
+    // Trees so large that a chunk holds a handful walk no faster here than in the other forms.
+    if (!any_size && chunk_size(0, n_trees, &s_, &e_, &v_) / (size_t)n_trees * kTreeletFewTrees > (size_t)kTreeletPairBuf)
+        return false;
+
+    // ---- segments: as few as their columns allow, equally long ----
+    std::vector<SegmentCuts> seg_cuts;
+    std::vector<uint16_t> word((size_t)tree_off[n_trees]);           // column << 8 | rank of the splits
+    {
+        // (an ensemble whose splits are many times what the columns hold starts with several segments: no
+        // sort of a million thresholds only to see that)
+        std::vector<int32_t> n_splits((size_t)n_features, 0);
+        for (int32_t g = 0; g < tree_off[n_trees]; ++g)
+            if (sf[g] >= 0)
+                ++n_splits[(size_t)sf[g]];
+        int m = 1;
+        for (;; ++m) {                               // assumes that half of the splits are distinct
+            int64_t cols = 0;
+            for (int f = 0; f < n_features; ++f)
+                if (n_splits[(size_t)f])
+                    cols += std::max<int64_t>(1, n_splits[(size_t)f] / (2 * (int64_t)m * kTreeletMaxCuts));
+            if (cols <= kTreeletMaxCols)
+                break;
+            if (m >= kTreeletMaxSegments)
+                return false;
+        }
+        std::vector<uint64_t> keys;
+        for (;; ++m) {
+            if (m > kTreeletMaxSegments)
+                return false;
+            const int per = ((n_trees + m - 1) / m + 7) / 8 * 8;
+            out->segments.clear();
+            seg_cuts.clear();
+            bool ok = true;
+            for (int t = 0; t < n_trees && ok; t += per) {
+                out->segments.emplace_back();
+                seg_cuts.emplace_back();
+                TreeletSegmentPlan &sp = out->segments.back();
+                sp.first_tree = t;
+                sp.n_trees = std::min(per, n_trees - t);
+                ok = segment_cuts(n_features, tree_off[t], tree_off[t + sp.n_trees], sf, thr, keys, word.data(),
+                                  &seg_cuts.back());
+            }
+            if (ok)
+                break;
+            if (per <= 8)
+                return false;
+        }
+    }
+    out->most_cols = 0;
+    for (const SegmentCuts &c : seg_cuts)
+        out->most_cols = std::max(out->most_cols, (int)c.pieces.size());
+
+    // ---- columns ----
+    // Buckets of every column: five or more per threshold, so that a bucket of evenly spread thresholds
+    // holds three at most (two bisection steps), with few exceptions; less where the tables of the
+    // wavefronts would not fit beside the columns.
+    const long beside = (long)out->most_cols * 256;
+    auto kb = [](long bytes) { return (bytes + 1023) / 1024 * 1024; };
+    // (the coder's layouts in fs_treelet.hip: a double-buffered table for each of 8 wavefronts; four
+    // tables for each of 12)
+    auto pair_fits = [&](int stride) { return 16 * kb(stride) <= (long)kTreeletLds - kTreeletSumBytes - beside; };
+    auto spread_fits = [&](int stride) { return 12 * kb(4 * stride) <= (long)kTreeletLdsWhole - beside; };
+    bool pair_coder = true;
+    for (size_t i = 0; i < out->segments.size();) {
+        TreeletSegmentPlan *sp = &out->segments[i];
+        int most_cuts = 0, want = 64;
+        for (const Piece &pc : seg_cuts[i].pieces)
+            most_cuts = std::max(most_cuts, pc.n);
+        while (want < 5 * most_cuts && want < 1024)
+            want *= 2;
+        bool fits = false;
+        for (int B = want; B >= 64 && !fits; B /= 2) {
+            build_columns(seg_cuts[i].pieces, seg_cuts[i].cuts, seg_cuts[i].cut_at, B, sp);
+            fits = spread_fits(sp->table_stride) && (pair_fits(sp->table_stride) || !pair_coder);
+        }
+        if (fits) {
+            ++i;
+        } else if (pair_coder) {                     // give the two-per-compute-unit form up and start over
+            pair_coder = false;
+            i = 0;
+        } else {
+            return false;
+        }
+    }
+
+    // ---- chunks ----
+    // Bounds of the chunks of trees [t0, t1) in buffers of `buf` bytes.  Two wavefronts take a chunk's
+    // halves in rounds of kTreeletRound: full rounds if the trees fit, else eights, else fours.
+    auto plan = [&](int t0, int t1, size_t buf, std::vector<int> *bounds) -> bool {
+        bounds->assign(1, t0);
+        int s, e, v;
+        auto fits = [&](int t, int cnt) { return chunk_size(t, std::min(t1, t + cnt), &s, &e, &v) <= buf; };
+        while (bounds->back() < t1) {
+            const int t = bounds->back();
+            int cnt = kTreeletMaxTrees;
+            while (cnt > 2 * kTreeletRound && !fits(t, cnt))
+                cnt -= 2 * kTreeletRound;
+            while (cnt > 2 * kTreeletUnit && !fits(t, cnt))
+                cnt -= 2 * kTreeletUnit;
+            if (!fits(t, cnt))
+                cnt = kTreeletUnit;
+            if (!fits(t, cnt))
+                return false;
+            bounds->push_back(std::min(t1, t + cnt));
+        }
+        return true;
+    };
+    auto plan_all = [&](size_t buf, std::vector<std::vector<int>> *all) -> bool {
+        all->resize(out->segments.size());
+        for (size_t i = 0; i < out->segments.size(); ++i)
+            if (!plan(out->segments[i].first_tree, out->segments[i].first_tree + out->segments[i].n_trees, buf, &(*all)[i]))
+                return false;
+        return true;
+    };
+    std::vector<std::vector<int>> all;
+    const long room = (long)kTreeletLds - kTreeletSumBytes - (long)out->most_cols * 256;
+    out->pair_ok = pair_coder && plan_all(std::min((size_t)room / 1024 * 1024, (size_t)kTreeletPairBuf), &all);
+    if (!out->pair_ok && !plan_all(kTreeletWholeBuf, &all))
+        return false;
+    size_t largest = 0;
+    out->max_trees = 0;
+    out->image.clear();
+    out->chunks.clear();
+    out->ids.clear();
+    struct Item { int32_t node, entry, step; };
+    std::vector<Item> work;
+    out->cost = 0.0;
+    for (size_t si = 0; si < out->segments.size(); ++si) {
+      TreeletSegmentPlan &sp = out->segments[si];
+      sp.first_chunk = (int)out->chunks.size();
+      sp.n_chunks = (int)all[si].size() - 1;
+      out->cost += kTreeletColClk * (double)sp.cols.size();
+      for (size_t ci = 0; ci + 1 < all[si].size(); ++ci) {
+        const int a = all[si][ci], b = all[si][ci + 1];
+        TreeletChunk h;
+        int steps, entries, values;
+        const size_t bytes = chunk_size(a, b, &steps, &entries, &values);
+        const int n = (b - a + kTreeletUnit - 1) / kTreeletUnit * kTreeletUnit;
+        h.byte_off = (uint32_t)out->image.size();
+        h.bytes = (uint32_t)bytes;
+        h.n_trees = (uint32_t)n;
+        h.first_tree = (uint32_t)a;
+        h.n_real = (uint32_t)(b - a);
+        h.val_off = (uint32_t)entries * 8u;
+        h.steps = (uint32_t)steps;
+        h.id_off = (uint32_t)out->ids.size();
+        out->image.resize(out->image.size() + bytes, 0);
+        out->ids.resize(out->ids.size() + (size_t)values, 0);
+        uint32_t *ent = (uint32_t *)(out->image.data() + h.byte_off);
+        uint32_t *valtab = ent + 2 * (size_t)entries;
+        uint16_t *ids = out->ids.data() + h.id_off;
+        auto forced = [](int bit) -> uint32_t { return bit ? 0u : 255u; };
+        auto absorb = [&](int32_t e) {               // an entry that steps onto itself
+            const uint32_t t0 = forced((e >> 1) & 1), t1 = forced(e & 1);
+            ent[2 * e] = t0 | ((uint32_t)(e >> 2) << 16);
+            ent[2 * e + 1] = t1 | (t1 << 16);
+        };
+        int32_t next_entry = n, next_value = entries;
+        for (int j = 0; j < n; ++j) {
+            if (a + j >= b) {                        // padding
+                absorb(j);
+                const float minus_zero = -0.0f;
+                memcpy(&valtab[j], &minus_zero, 4);
+                continue;
+            }
+            const int32_t o = tree_off[a + j];
+            work.clear();
+            work.push_back({0, j, 0});
+            for (size_t i = 0; i < work.size(); ++i) {
+                const Item it = work[i];
+                const int64_t g = (int64_t)o + it.node;
+                if (sf[g] < 0) {
+                    absorb(it.entry);
+                    memcpy(&valtab[it.entry], &val[g], 4);
+                    ids[it.entry] = (uint16_t)it.node;
+                    continue;
+                }
+                const bool last = it.step + 1 == steps;
+                int32_t &next = last ? next_value : next_entry;
+                const int32_t block = next;
+                next += 4;
+                uint32_t half[2];
+                const int32_t child[2] = {left[g], right[g]};
+                for (int c = 0; c < 2; ++c) {
+                    const int64_t gc = (int64_t)o + child[c];
+                    int32_t to[2];                   // node of outcome (c, 0) and (c, 1), -1: never reached
+                    if (sf[gc] < 0) {
+                        half[c] = forced(1);
+                        to[0] = -1;
+                        to[1] = child[c];
+                    } else {
+                        half[c] = word[(size_t)gc];
+                        to[0] = left[gc];
+                        to[1] = right[gc];
+                    }
+                    for (int k = 0; k < 2; ++k) {
+                        if (to[k] < 0)
+                            continue;
+                        const int32_t at = block + 2 * c + k;
+                        if (last) {                  // the chunk's steps reach every leaf
+                            memcpy(&valtab[at], &val[(int64_t)o + to[k]], 4);
+                            ids[at] = (uint16_t)to[k];
+                        } else {
+                            work.push_back({to[k], at, it.step + 1});
+                        }
+                    }
+                }
+                ent[2 * it.entry] = word[(size_t)g] | ((uint32_t)(block >> 2) << 16);
+                ent[2 * it.entry + 1] = half[0] | (half[1] << 16);
+            }
+        }
+        largest = std::max(largest, bytes);
+        out->max_trees = std::max(out->max_trees, n);
+        out->chunks.push_back(h);
+        out->cost += kTreeletStepClk * (double)n * steps + kTreeletChunkClk;
+      }
+    }
+    out->buf_bytes = (int)largest;
+    return true;
+}
+
+}  // namespace fs

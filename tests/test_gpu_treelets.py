@@ -1,0 +1,84 @@
+"""The byte-rank treelet traversal (fs_treelet.hip) against the oracle: every output of every form of
+the kernel, at the edges of its format -- tiles and rounds that are not full, features with more
+thresholds than one column holds, ensembles cut into segments, leaves at every depth, special
+values, both layouts."""
+import numpy as np
+import pytest
+
+from paper_2201_00194_amd import workloads as W
+from test_gpu_parity import check_family, run_families
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def api():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    from paper_2201_00194_amd import api as A
+    return A
+
+
+def family(seed, n_programs, stmts, n_trees, depth, q, n_features=164, special=False, steps=0):
+    fam = W.make_small_family(seed=seed, n_programs=n_programs, stmts=stmts, n_trees=n_trees, depth=depth,
+                              early_leaf_q=q, n_features=n_features, k=min(50, n_programs), bias=0.5)
+    rng = np.random.default_rng(seed)
+    if steps:                                   # few distinct values: thresholds and features tie
+        fam.features[:] = np.floor(fam.features * steps) / steps
+        fam.model.threshold[:] = np.where(fam.model.split_feature >= 0,
+                                          np.floor(fam.model.threshold * steps) / steps, 0)
+    if special:
+        X = fam.features
+        inner = np.flatnonzero(fam.model.split_feature >= 0)
+        for val in (np.nan, np.inf, -np.inf, -0.0, 1e-42, -1e-42, 3e38, -3e38):
+            X[rng.integers(0, X.shape[0], 60), rng.integers(0, X.shape[1], 60)] = val
+            fam.model.threshold[rng.choice(inner, min(5, inner.size), replace=False)] = val
+    return fam
+
+
+CASES = [
+    # one row; a tile and a row; four tiles and a row; trees that fill no unit, one unit, a round and one
+    dict(n_programs=1, stmts=(1, 1), n_trees=33, depth=5, q=0.2),
+    dict(n_programs=65, stmts=(1, 1), n_trees=4, depth=3, q=0.0),
+    dict(n_programs=257, stmts=(1, 1), n_trees=49, depth=7, q=0.25, special=True),
+    # single leaves, stumps, an odd depth; the narrowest and the widest feature matrix
+    dict(n_programs=150, stmts=(1, 3), n_trees=35, depth=0, q=0.0),
+    dict(n_programs=90, stmts=(2, 2), n_trees=97, depth=1, q=0.0, n_features=1, special=True),
+    dict(n_programs=120, stmts=(1, 4), n_trees=60, depth=5, q=0.1, n_features=255),
+    dict(n_programs=130, stmts=(1, 4), n_trees=70, depth=6, q=0.3, n_features=131, steps=3),
+    # more thresholds per feature than a column holds; two segments; deep irregular trees
+    dict(n_programs=300, stmts=(3, 5), n_trees=50, depth=8, q=0.0, n_features=30, special=True),
+    dict(n_programs=500, stmts=(4, 8), n_trees=280, depth=8, q=0.0),
+    dict(n_programs=200, stmts=(1, 9), n_trees=90, depth=12, q=0.3, special=True),
+]
+
+
+@pytest.mark.parametrize("form", [-1, 0, 1, 2, 3])
+@pytest.mark.parametrize("layout", [0, 1])
+def test_treelet_forms_all_outputs(api, oracle, tune, form, layout):
+    tune(api.FS_TUNE_TREELET, 1)
+    tune(api.FS_TUNE_TREELET_FORM, form)
+    fams = [family(9000 + i, **c) for i, c in enumerate(CASES)]
+    devs = run_families(api, fams, layout)
+    for f, d in zip(fams, devs):
+        check_family(oracle, f, d)
+    devs = run_families(api, fams, layout, want_rows=False, want_leaves=False)
+    for f, d in zip(fams, devs):
+        check_family(oracle, f, d)
+
+
+@pytest.mark.parametrize("seed", range(12))
+def test_treelets_random_shapes(api, oracle, tune, seed):
+    rng = np.random.default_rng([seed, 424])
+    tune(api.FS_TUNE_TREELET, 1)
+    tune(api.FS_TUNE_TREELET_FORM, int(rng.integers(-1, 4)))
+    fams = []
+    for i in range(4):
+        depth = int(rng.integers(0, 11))
+        fams.append(family(7000 + 10 * seed + i, int(rng.integers(1, 300)), (1, int(rng.integers(1, 12))),
+                           int(rng.integers(1, 30 if depth > 8 else 120)), depth,
+                           float(rng.choice([0.0, 0.15, 0.35])), n_features=int(rng.choice([2, 33, 64, 164, 255, 300])),
+                           special=bool(rng.integers(0, 2)), steps=int(rng.choice([0, 0, 2, 40]))))
+    devs = run_families(api, fams, int(rng.integers(0, 2)))
+    for f, d in zip(fams, devs):
+        check_family(oracle, f, d)
