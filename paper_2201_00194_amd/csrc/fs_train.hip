@@ -9,19 +9,16 @@
 //
 // Per round and family (all families of a batch share every launch; nothing returns to the
 // host between rounds):
-//   begin_tree   clear the heap of the tree to grow
-//   grad         per program: s_p (row order), g_p, q_p; rows get (q_p, rows of p) and go
-//                back to the root; the root's (G, H) are added up on the way
-//   per level:   hist (LDS histograms per family, four features and up to 16 nodes; a
-//                feature's most frequent bin is never counted, it is the node's total minus
-//                the rest; with one slab of rows per family the same workgroup then finds the
-//                best cut of each (node, feature), else the slabs add into a global buffer and
-//                `split` searches there), pick (per node: best feature, split or leaf, child
-//                ids in breadth-first order), part (rows of split nodes move to a child)
-//   deep trees:  before level 5 the rows are regrouped once by their node (seg_*), so that
-//                deeper histogram passes read only the segments of their nodes' ancestors
-//   pick         once more at max_depth: what is left becomes leaves
-//   update       row output += value of the row's leaf;  emit: heap -> flat model arrays
+//   grad         per program: s_p (row order), g_p, q_p; its rows' records (row, q_p, rows of p)
+//                go back to the root; the root's (G, H) are added up on the way
+//   per level:   hist (LDS histograms of the smaller child of every split node, sixteen features
+//                per workgroup; the larger child is the parent minus the smaller, exactly; a
+//                feature's most frequent bin is never counted, it is the node's total minus the
+//                rest; the workgroup goes on to search the cuts of both children), split (the same
+//                search where a node's rows were dealt to several workgroups), pick (per node: best
+//                feature, split or leaf, child ids in breadth-first order), part (records of split
+//                nodes move to their child's segment, rows of leaves take the leaf's value)
+//   emit         heap -> flat model arrays; clears the heap for the next tree
 #include <math.h>
 #include <stdlib.h>
 #include <algorithm>
@@ -37,24 +34,25 @@ namespace fs {
 
 constexpr int kHeapNodes = (1 << (FS_TRAIN_MAX_DEPTH + 1)) - 1;   // 2047
 constexpr int kBins = FS_TRAIN_MAX_CUTS + 1;                      // 256
-constexpr int kHistThreads = 1024;
-constexpr int kHistRowsPerSlab = 65536;
-
-// Deep trees: from this level on a histogram pass covers a small share of the nodes, and
-// streaming all rows for every pass is what the time goes into.  Before that level's histograms
-// the rows are regrouped once by their node of the level; the rows of a node's descendants stay
-// inside its segment, so a pass over some nodes of a deeper level reads only the segments of
-// their ancestors on this level.
-constexpr int kSortLevel = 5;
-constexpr int kSortSegs = 1 << kSortLevel;             // 32 nodes, heap indices 31..62
-constexpr int kSortMinDepth = 7;                       // worth it when at least two levels use it
+constexpr int kHistFeats = 16;          // features per workgroup: 16 bytes of bins per row
+constexpr int kHistWords = kHistFeats * kBins;
+constexpr int kChunkShiftMin = 10;      // at least 1024 rows to a histogram workgroup: zeroing and storing its LDS
+                                        // costs as much as 256 rows
+constexpr int kChunkPieces = 96;
 
 // heap node states
 enum { kAbsent = 0, kOpen = 1, kInternal = 2, kLeaf = 3 };
 
+// A (node, feature)'s best cut; cut 0 = none is admissible.
+struct __align__(32) Best {
+    double gain;
+    long long GL, HL;
+    int32_t cut, pad;
+};
+
 struct TrainDesc {
-    const uint8_t *bins;       // [feature / 4][r_pad][4]: the bins of four consecutive features
-                               // of a row share one 32-bit word
+    const uint8_t *bins;       // [feature / 16][r_pad][16]: a row's bins of sixteen consecutive
+                               // features are one 16-byte load
     const int32_t *prog_off;
     const float *target;
     const int32_t *cut_off;    // device copies of the cut lists
@@ -63,27 +61,24 @@ struct TrainDesc {
                                // (it is the node's total minus the other bins)
     float *row_pred;
     float *prog_pred;
-    int2 *qh;                  // per row: (gradient in fixed point, curvature)
-    uint16_t *node_of_row;     // heap index of the node that holds the row
-    unsigned long long *hist;  // [slot][feature][bin][2]: (G, H) of the level in work
-    int32_t *h_state, *h_feat, *h_cut, *h_id;
+    int4 *rec[2];              // {row, gradient in fixed point, curvature, node} of every row, grouped
+                               // by the node of a level; levels alternate between the two
+    int4 *seg;                 // per split node of the heap: {rows gone left, rows gone right, first
+                               // position, end}; zero if the node is not split.  The left child's
+                               // records fill the segment from its front, the right child's from its back
+    int32_t *h_slot;           // where in `hist` the node's histograms are
+    unsigned long long *hist;  // [slot][feature][bin]: complete histograms, what the next level subtracts from
+    unsigned long long *part;  // the same of parts of a node, see part_slot
+    int64_t hist_plane, part_plane;   // words to the curvature sums (wide form)
+    int32_t *h_state, *h_feat, *h_id;
     float *h_thr, *h_val;
     long long *h_G, *h_H;
-    double *best_gain;         // [slot][feature]
-    int32_t *best_cut;
-    long long *best_GL, *best_HL;
+    Best *best;                // [node of the level][feature]
+    int4 *decision;            // per node of the heap: {state, feature, cut, leaf value (bits)}
     int32_t *counters;         // [0] next node id of the tree in work, [1] trees, [2] nodes
     unsigned long long *abs_q; // sum over the rows of |gradient| (fixed point) of the round in work
     int32_t *pk_feat, *pk_cut; // per node of a level: its best feature and cut (levels with many nodes)
     double *pk_gain;
-    // Rows regrouped by their node of level kSortLevel (deep trees only, see train_seg_* below):
-    uint8_t *s_bins;           // bins in that order, same layout as `bins`
-    int2 *s_qh;
-    int32_t *s_rowid;          // original row of a regrouped position
-    uint16_t *s_node;          // node that holds it (kept up to date below kSortLevel)
-    int32_t *s_dest;           // scratch: regrouped position of an original row, -1 if it stayed behind
-    int32_t *seg_start;        // kSortSegs + 1: first position of every node of level kSortLevel
-    int32_t *seg_cursor;       // kSortSegs: counts, then fill positions
     int32_t *m_tree_off, *m_feat, *m_left, *m_right;
     float *m_thr, *m_val;
     int64_t r_pad;
@@ -100,52 +95,77 @@ struct Params {
 
 // ---- set-up kernels ----------------------------------------------------------------------
 
-// bin = number of cuts <= x; NaN takes the last bin.  One block column per feature.
+// bin = number of cuts <= x; NaN takes the last bin.  A workgroup takes 256 rows of sixteen features,
+// whose cut lists fit LDS together, so that a row's sixteen bins leave in one store.
 __global__ void __launch_bounds__(256)
 train_bin_kernel(const float *__restrict__ x, int layout, int n_features, int n_rows,
                  int64_t r_pad, const int32_t *__restrict__ cut_off,
                  const float *__restrict__ cuts, uint8_t *__restrict__ bins)
 {
-    __shared__ float c[kBins];
-    const int f = blockIdx.y;
-    const int m = cut_off[f + 1] - cut_off[f];
-    for (int i = threadIdx.x; i < m; i += blockDim.x)
-        c[i] = cuts[cut_off[f] + i];
+    __shared__ float c[kHistFeats][kBins];
+    const int f0 = blockIdx.y * kHistFeats;
+    const int nf = min(kHistFeats, n_features - f0);
+    for (int i = threadIdx.x; i < kHistWords; i += blockDim.x) {
+        const int f = min(f0 + i / kBins, n_features - 1), j = i % kBins;
+        c[i / kBins][j] = j < cut_off[f + 1] - cut_off[f] ? cuts[cut_off[f] + j] : __builtin_inff();
+    }
     __syncthreads();
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (r >= n_rows)
         return;
-    const float v = layout == FS_COLBLOCK64
-                        ? x[(int64_t)(r >> 6) * n_features * 64 + (int64_t)f * 64 + (r & 63)]
-                        : x[(int64_t)r * n_features + f];
-    int lo = 0, hi = m;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (c[mid] <= v)
-            lo = mid + 1;
-        else
-            hi = mid;
+    uint32_t w[kHistFeats / 4] = {};
+#pragma unroll
+    for (int k = 0; k < kHistFeats; ++k) {
+        const int f = min(f0 + k, n_features - 1), m = cut_off[f + 1] - cut_off[f];   // (one load pattern for all)
+        const float v = layout == FS_COLBLOCK64 ? x[(r >> 6) * n_features * 64 + (int64_t)f * 64 + (r & 63)]
+                                                : x[r * n_features + f];
+        int lo = 0;                              // cuts known to be <= v; entries past the list never are
+#pragma unroll
+        for (int step = kBins / 2; step > 0; step >>= 1)
+            if (c[k][lo + step - 1] <= v)
+                lo += step;
+        lo = v != v ? m : min(lo, m);            // (+inf passes the padding too)
+        w[k >> 2] |= (uint32_t)(k < nf ? lo : 0) << (8 * (k & 3));
     }
-    if (v != v)
-        lo = m;
-    bins[((int64_t)(f >> 2) * r_pad + r) * 4 + (f & 3)] = (uint8_t)lo;
+    ((uint4 *)bins)[(int64_t)blockIdx.y * r_pad + r] = make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+// Rows per (feature, bin): 4096 rows of sixteen features per workgroup, counted in LDS.
+constexpr int kCountRows = 4096;
+
+__global__ void __launch_bounds__(512)
+train_count_kernel(const uint8_t *__restrict__ bins, int n_features, int n_rows, int64_t r_pad,
+                   uint32_t *__restrict__ count)
+{
+    __shared__ uint32_t cnt[kHistWords];
+    const int f0 = blockIdx.y * kHistFeats;
+    const int nf = min(kHistFeats, n_features - f0);
+    for (int i = threadIdx.x; i < kHistWords; i += blockDim.x)
+        cnt[i] = 0u;
+    __syncthreads();
+    const int64_t first = blockIdx.x * (int64_t)kCountRows;
+    const int n = (int)min((int64_t)kCountRows, n_rows - first);
+    for (int i = threadIdx.x; i < n; i += blockDim.x) {
+        const uint4 v = ((const uint4 *)bins)[(int64_t)blockIdx.y * r_pad + first + i];
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int k = 0; k < kHistFeats; ++k)
+            atomicAdd(&cnt[k * kBins + ((w[k >> 2] >> (8 * (k & 3))) & 255)], 1u);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < nf * kBins; i += blockDim.x)
+        if (cnt[i] != 0u)
+            atomicAdd(&count[f0 * kBins + i], cnt[i]);
 }
 
 // The most frequent bin of every feature over the whole training set (lowest on ties).
-__global__ void __launch_bounds__(256)
-train_hot_bin_kernel(const uint8_t *__restrict__ bins, int n_rows, int64_t r_pad,
-                     int32_t *__restrict__ hot_bin)
+__global__ void __launch_bounds__(kBins)
+train_hot_bin_kernel(const uint32_t *__restrict__ count, int32_t *__restrict__ hot_bin)
 {
-    __shared__ unsigned int cnt[kBins];
     __shared__ unsigned int s_best[kBins];
     __shared__ int s_arg[kBins];
     const int f = blockIdx.x, t = threadIdx.x;
-    cnt[t] = 0u;
-    __syncthreads();
-    for (int r = t; r < n_rows; r += blockDim.x)
-        atomicAdd(&cnt[bins[((int64_t)(f >> 2) * r_pad + r) * 4 + (f & 3)]], 1u);
-    __syncthreads();
-    s_best[t] = cnt[t];
+    s_best[t] = count[f * kBins + t];
     s_arg[t] = t;
     __syncthreads();
     for (int off = kBins / 2; off > 0; off >>= 1) {
@@ -184,10 +204,9 @@ __global__ void train_fill_kernel(float *p, int64_t n, float v)
 
 // ---- per-round kernels -------------------------------------------------------------------
 
-__global__ void __launch_bounds__(512)
-train_begin_tree_kernel(const TrainDesc *__restrict__ descs)
+// The heap of the tree to grow (one workgroup per trainer).
+__device__ __forceinline__ void begin_tree(const TrainDesc &d)
 {
-    const TrainDesc &d = descs[blockIdx.x];
     for (int i = threadIdx.x; i < kHeapNodes; i += blockDim.x) {
         d.h_state[i] = i == 0 ? kOpen : kAbsent;
         d.h_G[i] = 0;
@@ -197,10 +216,15 @@ train_begin_tree_kernel(const TrainDesc *__restrict__ descs)
     }
     if (threadIdx.x == 0) {
         d.counters[0] = 1;
+        d.h_slot[0] = 0;
         *d.abs_q = 0ull;
     }
-    if (d.seg_cursor && threadIdx.x < kSortSegs)
-        d.seg_cursor[threadIdx.x] = 0;
+}
+
+__global__ void __launch_bounds__(512)
+train_begin_kernel(const TrainDesc *__restrict__ descs)
+{
+    begin_tree(descs[blockIdx.x]);
 }
 
 __device__ __forceinline__ int quantize(float g, float grad_scale)
@@ -228,10 +252,8 @@ train_grad_kernel(const TrainDesc *__restrict__ descs, float grad_scale, int wit
         if (with_grad) {
             const int q = quantize(s - d.target[p], grad_scale);
             const int len = e - b;
-            for (int r = b; r < e; ++r) {
-                d.qh[r] = make_int2(q, len);
-                d.node_of_row[r] = 0;
-            }
+            for (int r = b; r < e; ++r)
+                d.rec[0][r] = make_int4(r, q, len, 0);
             G = (long long)q * len;
             H = (long long)len * len;
             A = (unsigned long long)(G < 0 ? -G : G);
@@ -445,241 +467,449 @@ __device__ __forceinline__ void wave_best_cut(const TrainDesc &d, const Params &
     best_step<0x143, 0xc>(best, best_cut);
     best_cut = __builtin_amdgcn_readlane(best_cut, 63);
     if (best_cut == 0) {
-        if (lane == 0) {
-            d.best_gain[pair] = 0.0;
-            d.best_cut[pair] = 0;
-            d.best_GL[pair] = 0;
-            d.best_HL[pair] = 0;
-        }
+        if (lane == 0)
+            d.best[pair].cut = 0;
     } else if (cut == best_cut) {                                // exactly one lane holds the winner
-        d.best_gain[pair] = gain;
-        d.best_cut[pair] = cut;
-        d.best_GL[pair] = bGL;
-        d.best_HL[pair] = bHL;
+        d.best[pair] = {gain, bGL, bHL, cut, 0};
     }
 }
 
-// Histograms of one level.  A workgroup takes a slab of rows, four consecutive features (one
-// 32-bit word of bins per row) and a run of nodes of the level, and keeps their (G, H)
-// histograms in LDS.  blockIdx = (slab, feature group, trainer * passes + pass); a pass covers
-// consecutive nodes.  With one slab per family the workgroup holds the complete histograms and
-// searches the cuts itself; with more slabs the partial histograms are added to the global
-// buffer (which is all zero: the split kernel clears what it reads) and train_split_kernel
-// does the search.
-//
-// Two forms of a bin in LDS.  Packed: one 64-bit word G * 2^hb + H, fed by one atomic per
-// (row, feature); hb bits hold any curvature sum of the slab (the host knows rows x longest
-// program) and the rest holds G as long as the sum of |gradient| over the trainer's rows,
-// which train_grad_kernel leaves in abs_q, stays below 2^(63-hb).  Wide: G and H in 64 bits
-// each, always safe; a workgroup launched for the packed form falls back to it, its nodes in
-// two halves, when the gradients of its trainer are too large.  Both are exact integer sums.
-constexpr int kHistFeats = 4;           // features per workgroup: one 32-bit word of bins per row
-constexpr int kHistSlotsWide = 8;       // 8 nodes x 4 features x 256 bins x 16 B = 128 KB
-constexpr int kHistSlotsPacked = 16;    // 16 nodes x 4 features x 256 bins x 8 B = 128 KB
-// Behind the histograms: where the adds of rows that do not count land (rows past the end, of
-// other nodes, or in the feature's most frequent bin), one word per lane and feature, so that
-// the row loop has no branches.
-constexpr int kHistTrashWords = (kHistFeats - 1) * kBins + 64;
-static_assert(kBins * 8 >= kCutScratchBytes, "the cut search borrows its pair's own histogram");
-
-// One run of `slots` nodes, the first being number `abs0` of its level (heap index node0).
-template <bool PACKED>
-__device__ __forceinline__ void hist_run(const TrainDesc &d, const Params &prm,
-                                         unsigned long long *lds_hist, int node0, int abs0, int slots,
-                                         int row0, int row1, int f0, int nf, const int (&hot)[kHistFeats],
-                                         const uint32_t *__restrict__ words,
-                                         const uint16_t *__restrict__ node_of,
-                                         const int2 *__restrict__ qh_of, int n_slabs, int hb)
+// Shared by the packed search below: largest value of a non-negative float over the wavefront.
+__device__ __forceinline__ float wave_max_f(float v)
 {
-    const int pairs = slots * kHistFeats;
-    unsigned long long *lds_h = lds_hist + pairs * kBins;       // wide form only
-    for (int i = threadIdx.x; i < pairs * kBins * (PACKED ? 1 : 2); i += kHistThreads)
-        lds_hist[i] = 0ull;
-    __syncthreads();
-    // Rows in batches of kUnroll per thread.  The loads of the next batch are issued before the
-    // atomics of the current one, so that their latency passes while the LDS works.  (Indices
-    // are clamped to the last row: a batch past the end loads that row again and counts nothing.)
-    // The loop is bound by instruction issue, so it is kept free of branches: an add that does
-    // not count goes to the lane's own trash word instead.
-    constexpr int kUnroll = 4;
-    const int trash = pairs * kBins * (PACKED ? 1 : 2) + (threadIdx.x & 63);
-    int slot[kUnroll];
-    uint32_t w[kUnroll];                                         // the row's bins of the four features
-    int2 qh[kUnroll];
-    // (global address space stated: plain pointers make flat loads, which also count as LDS
-    // traffic and would make every wait for them a wait for the atomics too)
-    auto g_node = FS_GLOBAL(const uint16_t, node_of);
-    auto g_words = FS_GLOBAL(const uint32_t, words);
-    auto g_qh = FS_GLOBAL(const int2, qh_of);
-    auto fetch = [&](int base, int (&sl)[kUnroll], uint32_t (&ww)[kUnroll], int2 (&q)[kUnroll]) {
+    v = fmaxf(v, __int_as_float(dpp_i<0x111, 0xf>(__float_as_int(v))));
+    v = fmaxf(v, __int_as_float(dpp_i<0x112, 0xf>(__float_as_int(v))));
+    v = fmaxf(v, __int_as_float(dpp_i<0x114, 0xf>(__float_as_int(v))));
+    v = fmaxf(v, __int_as_float(dpp_i<0x118, 0xf>(__float_as_int(v))));
+    v = fmaxf(v, __int_as_float(dpp_i<0x142, 0xa>(__float_as_int(v))));
+    v = fmaxf(v, __int_as_float(dpp_i<0x143, 0xc>(__float_as_int(v))));
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+
+// The same for packed bins (G * 2^hb + H, hb <= 31).  The search is bound by instruction issue, most
+// of it double-precision divisions, so:
+//  - G and H go through one prefix sum, still packed.
+//  - GL^2/(HL+lambda) + GR^2/(HR+lambda) is formed in float first, and only cuts within 2^-18 of
+//    the largest are evaluated as the definition says, usually one.  The float value is within
+//    10 * 2^-24 of the true one (G in units of 2^-hb is below 2^63 and its square is taken times the
+//    reciprocal, so nothing overflows; a reciprocal that underflows leaves 0 for every cut, and
+//    all are evaluated).  The gain itself is that sum minus a term that is the same for all cuts
+//    and at most twice the sum, so a cut that wins after the rounding of double arithmetic is
+//    within 2^-50 of the largest and never dropped.
+__device__ __forceinline__ void wave_best_cut_packed(const TrainDesc &d, const Params &prm, int node, int f,
+                                                     int pair, int lane, unsigned long long (&v)[4], int hb)
+{
+    const long long G = d.h_G[node], H = d.h_H[node];
+    const int hot = d.hot_bin[f];
+    const int m = d.cut_off[f + 1] - d.cut_off[f];
+    const unsigned mask = (1u << hb) - 1u;
+    const unsigned long long total = (unsigned long long)(G * ((long long)1 << hb) + H);
+    const unsigned long long mine = v[0] + v[1] + v[2] + v[3];
+    const unsigned long long incl = (unsigned long long)wave_prefix_ll((long long)mine);
+    // what the counted bins lack of the node's totals sits in the hot bin
+    const unsigned long long rest = total - (unsigned long long)lane63_ll((long long)incl);
+    unsigned long long before = incl - mine;
+    if ((hot >> 2) < lane)
+        before += rest;
+    if ((hot >> 2) == lane) {
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            const uint32_t r = (uint32_t)min(base + u * kHistThreads, row1 - 1);   // 32-bit offsets from uniform bases
-            sl[u] = (int)g_node[r] - node0;
-            ww[u] = g_words[r];
-            q[u] = g_qh[r];
-        }
-    };
-    if (row0 < row1)
-        fetch(row0 + threadIdx.x, slot, w, qh);
-    for (int base = row0 + threadIdx.x; base < row1; base += kHistThreads * kUnroll) {
-        int n_slot[kUnroll];
-        uint32_t n_w[kUnroll];
-        int2 n_qh[kUnroll];
-        fetch(base + kHistThreads * kUnroll, n_slot, n_w, n_qh);
+        for (int k = 0; k < 4; ++k)
+            if ((hot & 3) == k)
+                v[k] = rest;
+    }
+    const int mcw = (int)min(prm.mcw, 0x7fffffffll), H_all = (int)H;
+    const float lambda = (float)prm.lambda;
+    float t[4], most = 0.0f;
+    bool cand[4];
+    int n_cand = 0;
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            const bool counts = base + u * kHistThreads < row1 && (unsigned)slot[u] < (unsigned)slots;
-            const unsigned long long both =
-                (unsigned long long)((long long)qh[u].x * ((long long)1 << hb) + (long long)qh[u].y);
-            const int row_at = slot[u] * (kHistFeats * kBins);
+    for (int k = 0; k < 4; ++k) {
+        const bool filled = ((unsigned)v[k] & mask) != 0u;
+        before += v[k];
+        v[k] = before;                                           // left sums of cut 4 * lane + k + 1
+        const int HL = (int)((unsigned)before & mask), HR = H_all - HL;
+        cand[k] = 4 * lane + k + 1 <= m && filled && HL >= mcw && HR >= mcw;
+        const unsigned long long GL = before - (unsigned)HL;     // times 2^hb
+        const float gl = (float)(double)(long long)GL;
+        const float gr = (float)(double)(long long)(total - (unsigned long long)H - GL);
+        const float l = gl * __builtin_amdgcn_rcpf((float)HL + lambda), r = gr * __builtin_amdgcn_rcpf((float)HR + lambda);
+        t[k] = gl * l + gr * r;
+        most = cand[k] ? fmaxf(most, t[k]) : most;
+    }
+    most = wave_max_f(most);
+    const float least = most * (1.0f - 0x1p-18f);
+    int cut = 0;
+    double best = 0.0;
+    long long bGL = 0, bHL = 0;
+    const double t3 = parent_term(G, H, prm.inv_scale, prm.lambda);
 #pragma unroll
-            for (int fi = 0; fi < kHistFeats; ++fi) {
-                const int b = (w[u] >> (8 * fi)) & 255;
-                // (a feature past the family's last has hot = 256 and its bins are 0: harmless)
-                // (mask arithmetic, not a conditional: the compiler turns that into a branch)
-                const int take = -(int)(counts & (b != hot[fi]));
-                const int at = trash + ((row_at + b - trash) & take) + fi * kBins;
-                if (PACKED) {
-                    atomicAdd(&lds_hist[at], both);
-                } else {
-                    atomicAdd(&lds_hist[at], (unsigned long long)(long long)qh[u].x);
-                    atomicAdd(&lds_hist[at + (at >= trash ? 0 : pairs * kBins)], (unsigned long long)qh[u].y);
-                }
+    for (int k = 0; k < 4; ++k) {
+        const bool eval = cand[k] && !(t[k] < least);
+        const unsigned long long votes = __ballot(eval);
+        if (votes == 0)
+            continue;
+        n_cand += __popcll(votes);
+        if (eval) {
+            const long long HL = (long long)((unsigned)v[k] & mask);
+            const long long GL = ((long long)v[k] - HL) >> hb;   // the difference is a multiple of 2^hb
+            const double gn = split_gain(GL, HL, G, H, prm.inv_scale, prm.lambda, t3);
+            if (cut == 0 || gn > best) {                         // ascending cuts: first of equals stays
+                best = gn;
+                cut = 4 * lane + k + 1;
+                bGL = GL;
+                bHL = HL;
             }
         }
+    }
+    if (n_cand == 0) {
+        if (lane == 0)
+            d.best[pair].cut = 0;
+        return;
+    }
+    const double gain = best;
+    int best_cut = cut;
+    if (n_cand > 1) {
+        // largest gain, lowest cut on ties: the same steps as the prefix sum leave the best of all
+        // lanes in lane 63
+        best_step<0x111, 0xf>(best, best_cut);
+        best_step<0x112, 0xf>(best, best_cut);
+        best_step<0x114, 0xf>(best, best_cut);
+        best_step<0x118, 0xf>(best, best_cut);
+        best_step<0x142, 0xa>(best, best_cut);
+        best_step<0x143, 0xc>(best, best_cut);
+        best_cut = __builtin_amdgcn_readlane(best_cut, 63);
+    }
+    if (cut != 0 && cut == best_cut)                             // exactly one lane holds the winner
+        d.best[pair] = {gain, bGL, bHL, cut, 0};
+}
+
+// Histograms of one level.
+//
+// Of two siblings only the one with fewer rows is counted; the other is the parent's histogram
+// minus it.  All sums are integer sums, so that is exact.  A work item is up to 2^shift rows of
+// one such node; a workgroup takes one item and sixteen features, walks the item's records (grouped by
+// node) and gathers each row's bins, 16 bytes at a time.  Over a tree of depth 8 rows are visited 4.5
+// times instead of 8 and no level streams the rows of other nodes.
+//
+// A node of a single item is finished here: one wavefront per feature reads the parent's bins,
+// searches the cuts of both children and, unless the level is the last that splits, leaves both
+// histograms for the next level, the larger child's in the parent's place.  The items of larger
+// nodes write their part and train_split_kernel adds the parts up.  (Parts are stored and not added
+// atomically: nothing has to be cleared, and the memory-side atomics of eight XCDs are slower
+// than the extra read.)
+//
+// Two forms of a bin.  Packed: one 64-bit word G * 2^hb + H, fed by one atomic per (row, feature);
+// hb bits hold any curvature sum (the host knows rows x longest program) and the rest holds G as
+// long as the sum of |gradient| over the trainer's rows, which train_grad_kernel leaves in abs_q,
+// stays below 2^(63-hb).  Wide: G and H in 64 bits each, always safe, eight features at a time in
+// the same LDS; H has a plane of its own in the buffers.  Every kernel of a round decides alike.
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+constexpr int kHistThreads = 512;
+constexpr int kHistWaves = kHistThreads / 64;
+static_assert(kBins * 8 >= kCutScratchBytes, "the cut search borrows its own histogram's LDS");
+
+__device__ __forceinline__ bool is_packed(const TrainDesc &d, int hb)
+{
+    return hb > 0 && *d.abs_q < (1ull << (63 - hb));
+}
+
+// A node to count (`small`), its sibling, and the part of the node's records an item covers.
+struct Item {
+    int small, large;         // heap indices; large < 0 at the root
+    int pair;                 // number of the parent within its level
+    int first, count;         // records of the whole node
+    int piece;
+};
+
+__device__ __forceinline__ int wave_prefix_i(int v)
+{
+    v += dpp_i<0x111, 0xf>(v);
+    v += dpp_i<0x112, 0xf>(v);
+    v += dpp_i<0x114, 0xf>(v);
+    v += dpp_i<0x118, 0xf>(v);
+    v += dpp_i<0x142, 0xa>(v);
+    v += dpp_i<0x143, 0xc>(v);
+    return v;
+}
+
+// Item number `index` of the level (every wavefront finds it for itself: one 16-byte load per parent
+// and a scan).  `nodes`: number nodes of several items instead, each once.
+__device__ __forceinline__ bool find_item(const TrainDesc &d, int level, int shift, int index, bool nodes,
+                                          int lane, Item &it)
+{
+    if (level == 0) {
+        const int pieces = (int)(((int64_t)d.n_rows + (1ll << shift) - 1) >> shift);
+        it = {0, -1, 0, 0, d.n_rows, index};
+        return nodes ? index == 0 && pieces > 1 : index < pieces;
+    }
+    constexpr int kMost = (1 << (FS_TRAIN_MAX_DEPTH - 2)) / 64;   // parents per lane
+    const int n_pairs = 1 << (level - 1);
+    const int per = n_pairs > 64 ? n_pairs / 64 : 1;
+    int items[kMost], sum = 0;
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            slot[u] = n_slot[u];
-            w[u] = n_w[u];
-            qh[u] = n_qh[u];
+    for (int i = 0; i < kMost; ++i) {
+        items[i] = 0;
+        const int pair = lane * per + i;
+        if (i < per && pair < n_pairs) {
+            const int4 s = d.seg[n_pairs - 1 + pair];
+            const int pieces = (int)(((int64_t)min(s.x, s.y) + (1ll << shift) - 1) >> shift);
+            items[i] = nodes ? (pieces > 1 ? 1 : 0) : pieces;
+        }
+        sum += items[i];
+    }
+    const int incl = wave_prefix_i(sum);
+    const unsigned long long past = __ballot(incl > index);
+    if (past == 0)
+        return false;
+    const int owner = __builtin_amdgcn_readfirstlane(__ffsll((long long)past) - 1);
+    int rest = index - (incl - sum), pick = -1, piece = 0;
+#pragma unroll
+    for (int i = 0; i < kMost; ++i) {
+        if (pick < 0 && rest < items[i]) {
+            pick = lane * per + i;
+            piece = rest;
+        }
+        rest -= items[i];
+    }
+    const int pair = __builtin_amdgcn_readlane(pick, owner);
+    const int4 s = d.seg[n_pairs - 1 + pair];
+    const int left = 2 * (n_pairs - 1 + pair) + 1;
+    if (s.x <= s.y)
+        it = {left, left + 1, pair, s.z, s.x, 0};
+    else
+        it = {left + 1, left, pair, s.z + s.x, s.y, 0};
+    it.piece = __builtin_amdgcn_readlane(piece, owner);
+    return true;
+}
+
+// Where the parts of a node of several items start in `part`.  Two nodes never overlap: one of
+// c > 2^shift rows has at most ceil(c / 2^shift) <= floor(2c / 2^shift) parts.
+__device__ __forceinline__ int64_t part_slot(int first, int shift)
+{
+    return (2 * (int64_t)first) >> shift;
+}
+
+template <bool PACKED>
+struct Bins4 {                // four consecutive bins of a lane
+    unsigned long long a[4], b[PACKED ? 1 : 4];
+    __device__ __forceinline__ void load(const unsigned long long *p, int64_t plane)
+    {
+        typedef unsigned long long u64x2 __attribute__((ext_vector_type(2)));
+        const u64x2 u = ((const u64x2 *)p)[0], v = ((const u64x2 *)p)[1];
+        a[0] = u.x, a[1] = u.y, a[2] = v.x, a[3] = v.y;
+        if (!PACKED) {
+            const u64x2 x = ((const u64x2 *)(p + plane))[0], y = ((const u64x2 *)(p + plane))[1];
+            b[0] = x.x, b[PACKED ? 0 : 1] = x.y, b[PACKED ? 0 : 2] = y.x, b[PACKED ? 0 : 3] = y.y;
+        }
+    }
+    __device__ __forceinline__ void store(unsigned long long *p, int64_t plane) const
+    {
+        typedef unsigned long long u64x2 __attribute__((ext_vector_type(2)));
+        ((u64x2 *)p)[0] = (u64x2){a[0], a[1]};
+        ((u64x2 *)p)[1] = (u64x2){a[2], a[3]};
+        if (!PACKED) {
+            ((u64x2 *)(p + plane))[0] = (u64x2){b[0], b[PACKED ? 0 : 1]};
+            ((u64x2 *)(p + plane))[1] = (u64x2){b[PACKED ? 0 : 2], b[PACKED ? 0 : 3]};
+        }
+    }
+    __device__ __forceinline__ void add(const Bins4 &o, bool minus)
+    {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            a[k] = minus ? o.a[k] - a[k] : a[k] + o.a[k];
+        if (!PACKED)
+#pragma unroll
+            for (int k = 0; k < (PACKED ? 1 : 4); ++k)
+                b[k] = minus ? o.b[k] - b[k] : b[k] + o.b[k];
+    }
+};
+
+// Cuts of one child: `which` = 0 the counted node, 1 its sibling.  `own` holds the counted node's bins
+// and is the other child's when this returns.
+template <bool PACKED>
+__device__ __forceinline__ void search_child(const TrainDesc &d, const Params &prm, int level, const Item &it,
+                                             int which, int f, int lane, Bins4<PACKED> &own, int hb,
+                                             unsigned char *scratch)
+{
+    const int n_pairs = level > 0 ? 1 << (level - 1) : 0;
+    const int parent_slot = level > 0 ? d.h_slot[n_pairs - 1 + it.pair] : 0;
+    const int slot = which || level == 0 ? parent_slot : n_pairs + it.pair;
+    const int node = which ? it.large : it.small;
+    unsigned long long *place = d.hist + ((int64_t)slot * d.n_features + f) * kBins + 4 * lane;
+    if (which) {
+        Bins4<PACKED> parent;
+        parent.load(place, d.hist_plane);
+        own.add(parent, true);
+    }
+    if (level + 1 < prm.max_depth)
+        own.store(place, d.hist_plane);
+    const int pair = (node - ((1 << level) - 1)) * d.n_features + f;
+    if constexpr (PACKED) {
+        unsigned long long v[4] = {own.a[0], own.a[1], own.a[2], own.a[3]};
+        wave_best_cut_packed(d, prm, node, f, pair, lane, v, hb);
+    } else {
+        long long g[4] = {(long long)own.a[0], (long long)own.a[1], (long long)own.a[2], (long long)own.a[3]};
+        long long h[4] = {(long long)own.b[0], (long long)own.b[1], (long long)own.b[2], (long long)own.b[3]};
+        wave_best_cut(d, prm, node, f, pair, lane, g, h, scratch);
+    }
+}
+
+// The children's places in `hist`, for the next level.
+__device__ __forceinline__ void note_slots(const TrainDesc &d, int level, const Item &it)
+{
+    const int n_pairs = 1 << (level - 1);
+    d.h_slot[it.small] = n_pairs + it.pair;
+    d.h_slot[it.large] = d.h_slot[n_pairs - 1 + it.pair];
+}
+
+// Features f0 + base .. + NF of the item.
+template <bool PACKED>
+__device__ __forceinline__ void hist_run(const TrainDesc &d, const Params &prm, unsigned long long *lds,
+                                         const Item &it, int level, int shift, int group, int base, int hb)
+{
+    constexpr int NF = PACKED ? kHistFeats : kHistFeats / 2;
+    constexpr int NW = NF / 4;
+    const int f0 = group * kHistFeats + base;
+    const int nf = min(NF, d.n_features - f0);
+    for (int i = threadIdx.x; i < kHistWords; i += kHistThreads)
+        lds[i] = 0ull;
+    int hot[NF];
+#pragma unroll
+    for (int k = 0; k < NF; ++k)
+        hot[k] = k < nf ? d.hot_bin[f0 + k] : 256;               // 256: no bin, nothing is skipped
+    __syncthreads();
+    const int n = min(it.count - (int)((int64_t)it.piece << shift), 1 << shift);
+    auto recs = FS_GLOBAL(const i32x4, d.rec[level & 1] + it.first + ((int64_t)it.piece << shift));
+    typedef uint32_t words __attribute__((ext_vector_type(NW)));
+    auto bins = FS_GLOBAL(const words, d.bins + (int64_t)group * d.r_pad * kHistFeats + base);
+    // (the records of a group are read in order, its bins gathered: the loads of the next step are
+    // issued before the atomics of this one)
+    // An add that does not count goes to the lane's own word behind the histograms, without a branch:
+    // the hot bin would otherwise take a third of a wavefront's adds, one after the other.
+    const int trash = kHistWords + (threadIdx.x & 63);
+    int i = threadIdx.x;
+    if (i < n) {
+        i32x4 r = recs[i];
+        words w = bins[(int64_t)r.x * (PACKED ? 1 : 2)];
+        i32x4 r_next = recs[min(i + kHistThreads, n - 1)];
+        for (; i < n; i += kHistThreads) {
+            const words w_next = bins[(int64_t)r_next.x * (PACKED ? 1 : 2)];
+            const i32x4 r_after = recs[min(i + 2 * kHistThreads, n - 1)];
+            const unsigned long long both =
+                (unsigned long long)((long long)r.y * ((long long)1 << hb) + (long long)r.z);
+#pragma unroll
+            for (int k = 0; k < NF; ++k) {
+                if ((k & 3) == 0 && k >= nf)
+                    break;
+                const int b = (w[k >> 2] >> (8 * (k & 3))) & 255;
+                const int at = (b == hot[k] ? trash - k * kBins : b) + k * kBins;
+                if (PACKED) {
+                    atomicAdd(&lds[at], both);
+                } else {
+                    atomicAdd(&lds[at], (unsigned long long)(long long)r.y);
+                    atomicAdd(&lds[at + (b == hot[k] ? 0 : kHistWords / 2)], (unsigned long long)r.z);
+                }
+            }
+            r = r_next;
+            w = w_next;
+            r_next = r_after;
         }
     }
     __syncthreads();
-    const long long h_mask = ((long long)1 << hb) - 1;
-    auto bin_at = [&](int i, long long &g, long long &h) {
-        if (PACKED) {
-            const long long v = (long long)lds_hist[i];
-            h = v & h_mask;
-            g = (v - h) >> hb;                                   // v - h is a multiple of 2^hb
-        } else {
-            g = (long long)lds_hist[i];
-            h = (long long)lds_h[i];
-        }
-    };
-    if (n_slabs == 1) {
-        // The whole histogram of these nodes and features is here: search the cuts right away
-        // (one wavefront per (node, feature)); nothing goes through the global buffer.
-        const int lane = threadIdx.x & 63;
-        for (int pair = threadIdx.x >> 6; pair < pairs; pair += kHistThreads / 64) {
-            const int slot = pair / kHistFeats, fi = pair % kHistFeats;
-            const int node = node0 + slot;
-            if (fi >= nf || d.h_state[node] != kOpen)
-                continue;
-            long long g[4], h[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                bin_at(pair * kBins + 4 * lane + k, g[k], h[k]);
-            // The pair's bins are in registers now and no other wavefront reads them: their LDS
-            // serves as the search's scratch (a wavefront's LDS accesses complete in order).
-            wave_best_cut(d, prm, node, f0 + fi, (abs0 + slot) * d.n_features + f0 + fi, lane, g, h,
-                          (unsigned char *)(lds_hist + pair * kBins));
+    if (it.count > 1 << shift) {
+        const int64_t at = ((part_slot(it.first, shift) + it.piece) * d.n_features + f0) * kBins;
+        for (int j = threadIdx.x; j < nf * kBins; j += kHistThreads) {
+            d.part[at + j] = lds[j];
+            if (!PACKED)
+                d.part[at + d.part_plane + j] = lds[kHistWords / 2 + j];
         }
     } else {
-        for (int i = threadIdx.x; i < pairs * kBins; i += kHistThreads) {
-            const int pair = i / kBins, b = i - pair * kBins;
-            const int slot = pair / kHistFeats, fi = pair % kHistFeats;
-            long long g, h;
-            bin_at(i, g, h);
-            if (fi >= nf || h == 0)
-                continue;
-            const int64_t at = (((int64_t)(abs0 + slot) * d.n_features + (f0 + fi)) * kBins + b) * 2;
-            atomicAdd(&d.hist[at], (unsigned long long)g);
-            atomicAdd(&d.hist[at + 1], (unsigned long long)h);
+        const int lane = threadIdx.x & 63;
+        const int children = level > 0 ? 2 : 1;
+        for (int k = threadIdx.x >> 6; k < nf; k += kHistWaves) {
+            // The feature's bins are in registers once read and no other wavefront reads them: their LDS
+            // serves as the search's scratch (a wavefront's LDS accesses complete in order).
+            Bins4<PACKED> own;
+            own.load(lds + k * kBins + 4 * lane, kHistWords / 2);
+#pragma unroll 1
+            for (int which = 0; which < children; ++which)
+                search_child<PACKED>(d, prm, level, it, which, f0 + k, lane, own, hb,
+                                     (unsigned char *)(lds + k * kBins));
         }
+        if (f0 == 0 && threadIdx.x == 0 && level > 0 && level + 1 < prm.max_depth)
+            note_slots(d, level, it);
     }
     __syncthreads();                                             // LDS may be reused by the next run
 }
 
-template <bool PACKED>
-__global__ void __launch_bounds__(kHistThreads)
-train_hist_kernel(const TrainDesc *__restrict__ descs, int level, int passes, int rows_per_slab,
-                  int n_slabs, int hb, int sorted, Params prm)
+// blockIdx = (item, feature group, trainer)
+__global__ void __launch_bounds__(kHistThreads, 6)
+train_hist_kernel(const TrainDesc *__restrict__ descs, int level, int shift, int hb, Params prm)
 {
-    extern __shared__ unsigned long long lds_hist[];
-    const TrainDesc &d = descs[blockIdx.z / passes];
-    const int pass = blockIdx.z % passes;
-    int row0 = blockIdx.x * rows_per_slab;
-    const int f0 = blockIdx.y * kHistFeats;
-    if (row0 >= d.n_rows || f0 >= d.n_features)
+    __shared__ __align__(16) unsigned long long lds[kHistWords + 64];
+    const TrainDesc &d = descs[blockIdx.z];
+    Item it;
+    if ((int)blockIdx.y * kHistFeats >= d.n_features ||
+        !find_item(d, level, shift, (int)blockIdx.x, false, threadIdx.x & 63, it))
         return;
-    int row1 = min(row0 + rows_per_slab, d.n_rows);
-    const int nf = min(kHistFeats, d.n_features - f0);
-    const int n_slots = 1 << level;
-    const int slots = min(PACKED ? kHistSlotsPacked : kHistSlotsWide, n_slots);
-    const int abs0 = pass * slots;                               // first node of the pass, within the level
-    const int node0 = n_slots - 1 + abs0;                        // its heap index
-    if (sorted) {
-        // regrouped rows (one slab): the segments of this pass's ancestors on level kSortLevel
-        const int up = level - kSortLevel;
-        row0 = d.seg_start[abs0 >> up];
-        row1 = d.seg_start[((abs0 + slots - 1) >> up) + 1];
-    }
-    int hot[kHistFeats];
-#pragma unroll
-    for (int fi = 0; fi < kHistFeats; ++fi)
-        hot[fi] = fi < nf ? d.hot_bin[f0 + fi] : 256;           // 256: no bin, nothing is skipped
-    const uint32_t *__restrict__ words =
-        (const uint32_t *)(sorted ? d.s_bins : d.bins) + (int64_t)blockIdx.y * d.r_pad;
-    const uint16_t *__restrict__ node_of = sorted ? d.s_node : d.node_of_row;
-    const int2 *__restrict__ qh_of = sorted ? d.s_qh : d.qh;
-    if (PACKED) {
-        if (*d.abs_q < (1ull << (63 - hb))) {
-            hist_run<true>(d, prm, lds_hist, node0, abs0, slots, row0, row1, f0, nf, hot, words, node_of, qh_of,
-                           n_slabs, hb);
-        } else {
-            const int half = slots > 1 ? slots / 2 : 1;          // the wide form takes twice the LDS per node
-            for (int s = 0; s < slots; s += half)
-                hist_run<false>(d, prm, lds_hist, node0 + s, abs0 + s, half, row0, row1, f0, nf, hot, words,
-                                node_of, qh_of, n_slabs, 0);
-        }
+    if (is_packed(d, hb)) {
+        hist_run<true>(d, prm, lds, it, level, shift, blockIdx.y, 0, hb);
     } else {
-        hist_run<false>(d, prm, lds_hist, node0, abs0, slots, row0, row1, f0, nf, hot, words, node_of, qh_of,
-                        n_slabs, 0);
+        hist_run<false>(d, prm, lds, it, level, shift, blockIdx.y, 0, 0);
+        if ((int)blockIdx.y * kHistFeats + kHistFeats / 2 < d.n_features)
+            hist_run<false>(d, prm, lds, it, level, shift, blockIdx.y, kHistFeats / 2, 0);
     }
 }
 
-// Best cut of one feature for one open node.  One wavefront per (node, feature); lane l owns
-// bins 4l..4l+3 and the cuts 4l+1..4l+4.  The histogram entries are zeroed once read, so that
-// the buffer is all zero again for the next level.  Only used when a family's rows span
-// several slabs.
+// Nodes of several items: one workgroup per (node, feature) adds the parts up, every wavefront some of
+// them, then one wavefront searches the node's cuts and another its sibling's.
 constexpr int kSplitWaves = 4;
 
-__global__ void __launch_bounds__(64 * kSplitWaves)
-train_split_kernel(const TrainDesc *__restrict__ descs, int level, Params prm)
+template <bool PACKED>
+__device__ __forceinline__ void split_run(const TrainDesc &d, const Params &prm, unsigned long long *lds,
+                                          const Item &it, int level, int shift, int f, int hb)
 {
-    __shared__ __align__(8) unsigned char s_cut_scratch[kSplitWaves][kCutScratchBytes];
-    const TrainDesc &d = descs[blockIdx.z];
-    const int lane = threadIdx.x & 63;
-    const int pair = blockIdx.x * kSplitWaves + (threadIdx.x >> 6);
-    const int n_slots = 1 << level;
-    if (pair >= n_slots * d.n_features)
-        return;
-    const int slot = pair / d.n_features, f = pair - slot * d.n_features;
-    const int node = n_slots - 1 + slot;
-    if (d.h_state[node] != kOpen)
-        return;
-    typedef unsigned long long u64x2 __attribute__((ext_vector_type(2)));
-    u64x2 *hp = (u64x2 *)(d.hist + ((int64_t)pair * kBins + 4 * lane) * 2);
-    long long g[4], h[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const u64x2 v = hp[k];
-        g[k] = (long long)v.x;
-        h[k] = (long long)v.y;
-        hp[k] = (u64x2){0ull, 0ull};
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int pieces = (int)(((int64_t)it.count + (1ll << shift) - 1) >> shift);
+    const unsigned long long *part = d.part + (part_slot(it.first, shift) * d.n_features + f) * kBins + 4 * lane;
+    const int64_t stride = (int64_t)d.n_features * kBins;
+    Bins4<PACKED> own = {};
+#pragma unroll 4
+    for (int j = wave; j < pieces; j += kSplitWaves) {
+        Bins4<PACKED> one;
+        one.load(part + j * stride, d.part_plane);
+        own.add(one, false);
     }
-    wave_best_cut(d, prm, node, f, pair, lane, g, h, s_cut_scratch[threadIdx.x >> 6]);
+    own.store(lds + wave * kBins + 4 * lane, kSplitWaves * kBins);
+    __syncthreads();
+    if (wave >= (level > 0 ? 2 : 1))
+        return;
+    own = {};
+#pragma unroll
+    for (int j = 0; j < kSplitWaves; ++j) {
+        Bins4<PACKED> one;
+        one.load(lds + j * kBins + 4 * lane, kSplitWaves * kBins);
+        own.add(one, false);
+    }
+    search_child<PACKED>(d, prm, level, it, wave, f, lane, own, hb,
+                         (unsigned char *)(lds + 2 * kSplitWaves * kBins) + wave * kBins * 8);
+    if (f == 0 && wave == 0 && lane == 0 && level > 0 && level + 1 < prm.max_depth)
+        note_slots(d, level, it);
+}
+
+__global__ void __launch_bounds__(64 * kSplitWaves)
+train_split_kernel(const TrainDesc *__restrict__ descs, int level, int shift, int hb, Params prm)
+{
+    __shared__ __align__(16) unsigned long long lds[(2 * kSplitWaves + 2) * kBins];
+    const TrainDesc &d = descs[blockIdx.z];
+    const int f = blockIdx.x;
+    Item it;
+    if (f >= d.n_features || !find_item(d, level, shift, (int)blockIdx.y, true, threadIdx.x & 63, it))
+        return;
+    if (is_packed(d, hb))
+        split_run<true>(d, prm, lds, it, level, shift, f, hb);
+    else
+        split_run<false>(d, prm, lds, it, level, shift, f, 0);
 }
 
 // Per open node of the level: best feature, split or leaf; children get consecutive ids in
@@ -702,12 +932,10 @@ __device__ __forceinline__ void wave_best_feature(const TrainDesc &d, int level,
     bg = 0.0;
     if (level < prm.max_depth && d.h_state[n_slots - 1 + sl] == kOpen) {
         for (int f = lane; f < d.n_features; f += 64) {          // ascending: first of equals stays
-            const int64_t o = (int64_t)sl * d.n_features + f;
-            const int c = d.best_cut[o];
-            if (c == 0)
-                continue;
-            const double g = d.best_gain[o];
-            if (bf < 0 || g > bg) {
+            const Best &o = d.best[(int64_t)sl * d.n_features + f];
+            const int c = o.cut;
+            const double g = o.gain;                             // (not read as a gain where cut is 0)
+            if (c != 0 && (bf < 0 || g > bg)) {
                 bg = g;
                 bf = f;
                 bc = c;
@@ -745,10 +973,16 @@ train_pick_reduce_kernel(const TrainDesc *__restrict__ descs, int level, Params 
     }
 }
 
+__device__ __forceinline__ float leaf_value(long long G, long long H, const Params &prm)
+{
+    const double g = (double)G * prm.inv_scale;
+    return (float)(-prm.eta * g / ((double)H + prm.lambda));
+}
+
 __global__ void __launch_bounds__(kPickThreads)
 train_pick_kernel(const TrainDesc *__restrict__ descs, int level, int reduced, Params prm)
 {
-    __shared__ int s_scan[kMaxSlots];
+    __shared__ int s_count[kPickThreads / 64];
     __shared__ int s_bf[kMaxSlots], s_bc[kMaxSlots];
     __shared__ double s_bg[kMaxSlots];
     const TrainDesc &d = descs[blockIdx.x];
@@ -779,33 +1013,47 @@ train_pick_kernel(const TrainDesc *__restrict__ descs, int level, int reduced, P
     const int bf = open ? s_bf[slot] : -1, bc = open ? s_bc[slot] : 0;
     const double bg = open ? s_bg[slot] : 0.0;
     const bool split = open && bf >= 0 && bg > prm.min_gain;
-    if (threadIdx.x < kMaxSlots)
-        s_scan[threadIdx.x] = split ? 1 : 0;
+    const unsigned long long votes = __ballot(split);
+    if (lane == 0)
+        s_count[wave] = __popcll(votes);
     __syncthreads();
-    for (int off = 1; off < kMaxSlots; off <<= 1) {
-        int v = 0;
-        if (threadIdx.x < kMaxSlots && (int)threadIdx.x >= off)
-            v = s_scan[threadIdx.x - off];
-        __syncthreads();
-        if (threadIdx.x < kMaxSlots)
-            s_scan[threadIdx.x] += v;
-        __syncthreads();
+    int before = __popcll(votes & ((1ull << lane) - 1ull)), total = 0;
+    for (int w = 0; w < kPickThreads / 64; ++w) {
+        before += w < wave ? s_count[w] : 0;
+        total += s_count[w];
     }
-    const int before = threadIdx.x < kMaxSlots ? s_scan[threadIdx.x] - (split ? 1 : 0) : 0;
-    const int total = s_scan[kMaxSlots - 1];
     const int next_id = d.counters[0];
+    if (slot < n_slots) {
+        int4 own = make_int4(0, 0, 0, 0);
+        if (split) {
+            own.w = d.n_rows;
+            if (level > 0) {
+                const int4 up = d.seg[(node - 1) >> 1];
+                own.z = up.z + (node & 1 ? 0 : up.x);
+                own.w = node & 1 ? up.z + up.x : up.w;
+            }
+        }
+        d.seg[node] = own;
+        if (!open)
+            d.decision[node] = make_int4(kAbsent, 0, 0, 0);
+    }
     if (open) {
         const long long G = d.h_G[node], H = d.h_H[node];
         if (split) {
-            const int64_t o = (int64_t)slot * d.n_features + bf;
-            const long long GL = d.best_GL[o], HL = d.best_HL[o];
+            const Best &o = d.best[(int64_t)slot * d.n_features + bf];
+            const long long GL = o.GL, HL = o.HL;
             const int lc = 2 * node + 1, rc = lc + 1;
             d.h_state[node] = kInternal;
+            d.decision[node] = make_int4(kInternal, bf, bc, 0);
             d.h_feat[node] = bf;
-            d.h_cut[node] = bc;
             d.h_thr[node] = d.cuts[d.cut_off[bf] + bc - 1];
-            d.h_state[lc] = kOpen;
-            d.h_state[rc] = kOpen;
+            const bool deepest = level + 1 == prm.max_depth;     // what is left becomes leaves
+            d.h_state[lc] = deepest ? kLeaf : kOpen;
+            d.h_state[rc] = deepest ? kLeaf : kOpen;
+            if (deepest) {
+                d.h_val[lc] = leaf_value(GL, HL, prm);
+                d.h_val[rc] = leaf_value(G - GL, H - HL, prm);
+            }
             d.h_G[lc] = GL;
             d.h_H[lc] = HL;
             d.h_G[rc] = G - GL;
@@ -813,9 +1061,9 @@ train_pick_kernel(const TrainDesc *__restrict__ descs, int level, int reduced, P
             d.h_id[lc] = next_id + 2 * before;
             d.h_id[rc] = next_id + 2 * before + 1;
         } else {
-            const double g = (double)G * prm.inv_scale;
             d.h_state[node] = kLeaf;
-            d.h_val[node] = (float)(-prm.eta * g / ((double)H + prm.lambda));
+            d.h_val[node] = leaf_value(G, H, prm);
+            d.decision[node] = make_int4(kLeaf, 0, 0, __float_as_int(leaf_value(G, H, prm)));
         }
     }
     __syncthreads();
@@ -823,160 +1071,104 @@ train_pick_kernel(const TrainDesc *__restrict__ descs, int level, int reduced, P
         d.counters[0] = next_id + 2 * total;
 }
 
-// Rows of the nodes that were split move to the left child if their bin is below the cut.
-__global__ void __launch_bounds__(256)
-train_part_kernel(const TrainDesc *__restrict__ descs, int level)
-{
-    const TrainDesc &d = descs[blockIdx.y];
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= d.n_rows)
-        return;
-    const int node = d.node_of_row[r];
-    if (node < (1 << level) - 1 || d.h_state[node] != kInternal)
-        return;
-    const int f = d.h_feat[node];
-    const int b = d.bins[((int64_t)(f >> 2) * d.r_pad + r) * 4 + (f & 3)];
-    d.node_of_row[r] = (uint16_t)(2 * node + (b < d.h_cut[node] ? 1 : 2));
-}
+// Records of the nodes that were split move to their child's segment in the other buffer (the order
+// inside a segment is free: all sums over rows are integer sums); rows of leaves take the leaf's
+// value.  A record of an earlier level that was not overwritten since belongs to a node above the
+// level and is passed over.  (At level 1 every position is fresh: either all rows moved there, or
+// the tree is one leaf and no node of the heap is open or split.)
+constexpr int kPartThreads = 1024;
 
-// The same for regrouped rows (levels from kSortLevel on): positions instead of rows.
-__global__ void __launch_bounds__(256)
-train_part_sorted_kernel(const TrainDesc *__restrict__ descs, int level)
+__global__ void __launch_bounds__(kPartThreads)
+train_part_kernel(const TrainDesc *__restrict__ descs, int level, int max_depth)
 {
+    __shared__ int s_left[kPartThreads / 64], s_right[kPartThreads / 64];
+    __shared__ unsigned long long s_base;
     const TrainDesc &d = descs[blockIdx.y];
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= d.seg_start[kSortSegs])
+    const int64_t p = blockIdx.x * (int64_t)kPartThreads + threadIdx.x;
+    if (blockIdx.x * (int64_t)kPartThreads >= d.n_rows)
         return;
-    const int node = d.s_node[p];
-    if (node < (1 << level) - 1 || d.h_state[node] != kInternal)
-        return;
-    const int f = d.h_feat[node];
-    const int b = d.s_bins[((int64_t)(f >> 2) * d.r_pad + p) * 4 + (f & 3)];
-    d.s_node[p] = (uint16_t)(2 * node + (b < d.h_cut[node] ? 1 : 2));
-}
-
-// Regrouping, step 1: rows per node of level kSortLevel (rows that stopped in a leaf above
-// that level stay behind).  seg_cursor is zero when the tree begins.
-__global__ void __launch_bounds__(256)
-train_seg_count_kernel(const TrainDesc *__restrict__ descs)
-{
-    __shared__ int s_cnt[kSortSegs];
-    const TrainDesc &d = descs[blockIdx.y];
-    if (blockIdx.x * blockDim.x >= (unsigned)d.n_rows)
-        return;
-    if (threadIdx.x < kSortSegs)
-        s_cnt[threadIdx.x] = 0;
-    __syncthreads();
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r < d.n_rows) {
-        const int seg = (int)d.node_of_row[r] - (kSortSegs - 1);
-        if (seg >= 0 && seg < kSortSegs)
-            atomicAdd(&s_cnt[seg], 1);
-    }
-    __syncthreads();
-    if (threadIdx.x < kSortSegs && s_cnt[threadIdx.x] != 0)
-        atomicAdd(&d.seg_cursor[threadIdx.x], s_cnt[threadIdx.x]);
-}
-
-// Step 2: seg_start = exclusive scan of the counts; seg_cursor = the same (fill positions).
-__global__ void __launch_bounds__(64)
-train_seg_scan_kernel(const TrainDesc *__restrict__ descs)
-{
-    static_assert(kSortSegs <= 64, "one wavefront scans the segments");
-    const TrainDesc &d = descs[blockIdx.x];
-    const int t = threadIdx.x;
-    const int mine = t < kSortSegs ? d.seg_cursor[t] : 0;
-    int incl = mine;
-    for (int off = 1; off < 64; off <<= 1) {
-        const int u = __shfl_up(incl, off);
-        if (t >= off)
-            incl += u;
-    }
-    if (t < kSortSegs) {
-        d.seg_start[t] = incl - mine;
-        d.seg_cursor[t] = incl - mine;
-    }
-    if (t == kSortSegs - 1)
-        d.seg_start[kSortSegs] = incl;
-}
-
-// Step 3: a position for every row that goes on (order inside a segment is free: all sums over
-// rows are integer sums); its node, gradient pair and row number move there.
-__global__ void __launch_bounds__(256)
-train_seg_place_kernel(const TrainDesc *__restrict__ descs)
-{
-    __shared__ int s_cnt[kSortSegs], s_base[kSortSegs];
-    const TrainDesc &d = descs[blockIdx.y];
-    if (blockIdx.x * blockDim.x >= (unsigned)d.n_rows)
-        return;
-    if (threadIdx.x < kSortSegs)
-        s_cnt[threadIdx.x] = 0;
-    __syncthreads();
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    int seg = -1, rank = 0, node = 0;
-    if (r < d.n_rows) {
-        node = d.node_of_row[r];
-        seg = node - (kSortSegs - 1);
-        if (seg >= kSortSegs)
-            seg = -1;                                            // cannot happen: no row is below this level yet
-        if (seg >= 0)
-            rank = atomicAdd(&s_cnt[seg], 1);
-    }
-    __syncthreads();
-    if (threadIdx.x < kSortSegs && s_cnt[threadIdx.x] != 0)
-        s_base[threadIdx.x] = atomicAdd(&d.seg_cursor[threadIdx.x], s_cnt[threadIdx.x]);
-    __syncthreads();
-    if (r < d.n_rows) {
-        int p = -1;
-        if (seg >= 0) {
-            p = s_base[seg] + rank;
-            d.s_rowid[p] = r;
-            d.s_node[p] = (uint16_t)node;
-            d.s_qh[p] = d.qh[r];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int4 r = make_int4(0, 0, 0, -1), todo_of = make_int4(kAbsent, 0, 0, 0);
+    int2 ends = make_int2(0, 0);
+    if (p < d.n_rows) {
+        r = d.rec[level & 1][p];
+        if (r.w >= (1 << level) - 1 && r.w < (2 << level) - 1) {
+            todo_of = d.decision[r.w];
+            ends = ((const int2 *)&d.seg[r.w])[1];               // (the other half is being counted up)
         }
-        d.s_dest[r] = p;
     }
-}
-
-// Step 4: the bins follow, one 32-bit word (four features) per thread.
-__global__ void __launch_bounds__(256)
-train_seg_bins_kernel(const TrainDesc *__restrict__ descs)
-{
-    const TrainDesc &d = descs[blockIdx.z];
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= d.n_rows || (int)blockIdx.y * 4 >= d.n_features)
-        return;
-    const int p = d.s_dest[r];
-    if (p < 0)
-        return;
-    const int64_t g = (int64_t)blockIdx.y * d.r_pad;
-    ((uint32_t *)d.s_bins)[g + p] = ((const uint32_t *)d.bins)[g + r];
-}
-
-// Row outputs += value of the leaf that holds the row.  With regrouped rows (`sorted`), the
-// rows that went on below kSortLevel are updated through their regrouped record, the others
-// (in a leaf above that level) through node_of_row.
-__global__ void __launch_bounds__(256)
-train_update_kernel(const TrainDesc *__restrict__ descs, int sorted)
-{
-    const TrainDesc &d = descs[blockIdx.y];
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= d.n_rows)
-        return;
-    if (sorted) {
-        if (r < d.seg_start[kSortSegs]) {
-            const int row = d.s_rowid[r];
-            d.row_pred[row] = d.row_pred[row] + d.h_val[d.s_node[r]];
+    const int state = todo_of.x;
+    bool left = false;
+    if (state == kInternal) {
+        const int f = todo_of.y;
+        const int b = d.bins[((int64_t)(f / kHistFeats) * d.r_pad + r.x) * kHistFeats + f % kHistFeats];
+        left = b < todo_of.z;
+        if (level + 1 == max_depth) {
+            const float v = d.h_val[2 * r.w + (left ? 1 : 2)];
+            d.row_pred[r.x] = d.row_pred[r.x] + v;
         }
-        const int node = d.node_of_row[r];
-        if (node < kSortSegs - 1)
-            d.row_pred[r] = d.row_pred[r] + d.h_val[node];
-        return;
+    } else if (state == kLeaf) {
+        d.row_pred[r.x] = d.row_pred[r.x] + __int_as_float(todo_of.w);
     }
-    d.row_pred[r] = d.row_pred[r] + d.h_val[d.node_of_row[r]];
+    if (level + 1 >= max_depth)
+        return;
+    const bool moves = state == kInternal;
+    const unsigned long long below = (1ull << lane) - 1ull;
+    int at = 0;
+    // One node holds most positions of a workgroup high up in the tree: one atomic for all of them.
+    const int node0 = __builtin_amdgcn_readfirstlane(r.w);
+    __shared__ int s_node;
+    if (threadIdx.x == 0)
+        s_node = r.w;
+    __syncthreads();
+    if (__syncthreads_and(!moves ? p >= d.n_rows : r.w == s_node)) {
+        const unsigned long long lm = __ballot(moves && left), rm = __ballot(moves && !left);
+        if (lane == 0) {
+            s_left[wave] = __popcll(lm);
+            s_right[wave] = __popcll(rm);
+        }
+        __syncthreads();
+        int l = 0, rt = 0, l_all = 0, r_all = 0;
+        for (int w = 0; w < kPartThreads / 64; ++w) {
+            if (w == wave) {
+                l = l_all;
+                rt = r_all;
+            }
+            l_all += s_left[w];
+            r_all += s_right[w];
+        }
+        if (threadIdx.x == 0)
+            s_base = atomicAdd((unsigned long long *)&d.seg[s_node],
+                               (unsigned long long)(unsigned)l_all | (unsigned long long)(unsigned)r_all << 32);
+        __syncthreads();
+        const unsigned long long base = s_base;
+        at = left ? (int)(unsigned)base + l + __popcll(lm & below) : (int)(base >> 32) + rt + __popcll(rm & below);
+    } else {
+        unsigned long long todo = __ballot(moves);
+        int node = node0;
+        while (todo) {
+            const int lead = __ffsll((long long)todo) - 1;
+            node = __builtin_amdgcn_readlane(r.w, lead);
+            const bool mine = moves && r.w == node;
+            const unsigned long long lm = __ballot(mine && left), rm = __ballot(mine && !left);
+            unsigned long long base = 0;
+            if (lane == lead)
+                base = atomicAdd((unsigned long long *)&d.seg[node],
+                                 (unsigned long long)__popcll(lm) | (unsigned long long)__popcll(rm) << 32);
+            const int bl = __builtin_amdgcn_readlane((int)(unsigned)base, lead);
+            const int br = __builtin_amdgcn_readlane((int)(base >> 32), lead);
+            if (mine)
+                at = left ? bl + __popcll(lm & below) : br + __popcll(rm & below);
+            todo &= ~(lm | rm);
+        }
+    }
+    if (moves) {
+        const int to = left ? ends.x + at : ends.y - 1 - at;
+        d.rec[(level + 1) & 1][to] = make_int4(r.x, r.y, r.z, 2 * r.w + (left ? 1 : 2));
+    }
 }
 
-// Heap -> flat arrays, appended to the model.
+// Heap -> flat arrays, appended to the model; then the heap is the next tree's.
 __global__ void __launch_bounds__(512)
 train_emit_kernel(const TrainDesc *__restrict__ descs)
 {
@@ -1007,6 +1199,8 @@ train_emit_kernel(const TrainDesc *__restrict__ descs)
         d.counters[2] = base + n_new;
         d.m_tree_off[n_trees + 1] = base + n_new;
     }
+    __syncthreads();
+    begin_tree(d);
 }
 
 }  // namespace fs
@@ -1019,6 +1213,8 @@ struct fs_trainer {
     int max_depth, max_trees;
     int trees_enqueued;
     int max_len;              // rows of the longest program
+    void *own_work;           // its histograms where a batch's do not fit the shared buffer
+    size_t own_work_bytes;
     std::vector<void *> allocs;
 };
 
@@ -1029,6 +1225,8 @@ struct BatchBuf {
     TrainDesc *d_desc = nullptr;
     TrainDesc *h_desc = nullptr;   // pinned
     int cap = 0;
+    void *work = nullptr;          // histograms of the batch in work, at most kKeptWork bytes
+    size_t work_bytes = 0;
     hipEvent_t copied = nullptr;
     bool pending = false;
 };
@@ -1069,6 +1267,8 @@ extern "C" void fs_trainer_destroy(fs_trainer *t)
         return;
     for (void *p : t->allocs)
         (void)hipFree(p);
+    if (t->own_work)
+        (void)hipFree(t->own_work);
     delete t;
 }
 
@@ -1140,32 +1340,32 @@ extern "C" int fs_trainer_create(fs_trainer **out, int32_t n_features, const flo
     int32_t *d_prog_off = nullptr, *d_cut_off = nullptr;
     float *d_target = nullptr, *d_cuts = nullptr;
     int32_t *d_hot = nullptr;
+    uint32_t *d_count = nullptr;
 #define TRY(x)            \
     if (rc == FS_OK)      \
     rc = (x)
-    TRY(dev_alloc(t, &bins, (size_t)h.r_pad * 4 * (size_t)((n_features + 3) / 4)));
+    TRY(dev_alloc(t, &bins, (size_t)h.r_pad * kHistFeats * (size_t)((n_features + kHistFeats - 1) / kHistFeats)));
     TRY(dev_alloc(t, &d_prog_off, (size_t)n_programs + 1));
     TRY(dev_alloc(t, &d_target, (size_t)n_programs));
     TRY(dev_alloc(t, &d_cut_off, (size_t)n_features + 1));
     TRY(dev_alloc(t, &d_cuts, (size_t)n_cuts));
     TRY(dev_alloc(t, &d_hot, (size_t)n_features));
+    TRY(dev_alloc(t, &d_count, (size_t)n_features * kBins));
     TRY(dev_alloc(t, &h.row_pred, (size_t)n_rows));
     TRY(dev_alloc(t, &h.prog_pred, (size_t)n_programs));
-    TRY(dev_alloc(t, &h.qh, (size_t)n_rows));
-    TRY(dev_alloc(t, &h.node_of_row, (size_t)n_rows));
-    h.hist = nullptr;       // only families that span several slabs need it: see ensure_hist
+    TRY(dev_alloc(t, &h.rec[0], (size_t)n_rows));
+    TRY(dev_alloc(t, &h.rec[1], (size_t)n_rows));
+    TRY(dev_alloc(t, &h.seg, (size_t)kHeapNodes));
+    TRY(dev_alloc(t, &h.h_slot, (size_t)kHeapNodes));
     TRY(dev_alloc(t, &h.h_state, (size_t)kHeapNodes));
     TRY(dev_alloc(t, &h.h_feat, (size_t)kHeapNodes));
-    TRY(dev_alloc(t, &h.h_cut, (size_t)kHeapNodes));
     TRY(dev_alloc(t, &h.h_id, (size_t)kHeapNodes));
     TRY(dev_alloc(t, &h.h_thr, (size_t)kHeapNodes));
     TRY(dev_alloc(t, &h.h_val, (size_t)kHeapNodes));
     TRY(dev_alloc(t, &h.h_G, (size_t)kHeapNodes));
     TRY(dev_alloc(t, &h.h_H, (size_t)kHeapNodes));
-    TRY(dev_alloc(t, &h.best_gain, (size_t)hist_slots * n_features));
-    TRY(dev_alloc(t, &h.best_cut, (size_t)hist_slots * n_features));
-    TRY(dev_alloc(t, &h.best_GL, (size_t)hist_slots * n_features));
-    TRY(dev_alloc(t, &h.best_HL, (size_t)hist_slots * n_features));
+    TRY(dev_alloc(t, &h.best, (size_t)hist_slots * n_features));
+    TRY(dev_alloc(t, &h.decision, (size_t)kHeapNodes));
     TRY(dev_alloc(t, &h.counters, (size_t)4));
     TRY(dev_alloc(t, &h.abs_q, (size_t)1));
     TRY(dev_alloc(t, &h.pk_feat, (size_t)kMaxSlots));
@@ -1207,13 +1407,19 @@ extern "C" int fs_trainer_create(fs_trainer **out, int32_t n_features, const flo
         fs_trainer_destroy(t);
         return fail_hip(e, "fs_trainer_create: copies");
     }
-    hipLaunchKernelGGL(train_bin_kernel, dim3((unsigned)((n_rows + 255) / 256), (unsigned)n_features),
+    hipLaunchKernelGGL(train_bin_kernel, dim3((unsigned)((n_rows + 255) / 256), (unsigned)((n_features + kHistFeats - 1) / kHistFeats)),
                        dim3(256), 0, stream, features, layout, n_features, (int)n_rows, h.r_pad,
                        (const int32_t *)d_cut_off, (const float *)d_cuts, bins);
     rc = check_launch("train_bin_kernel launch");
     if (rc == FS_OK) {
-        hipLaunchKernelGGL(train_hot_bin_kernel, dim3((unsigned)n_features), dim3(256), 0, stream,
-                           (const uint8_t *)bins, (int)n_rows, h.r_pad, d_hot);
+        hipLaunchKernelGGL(train_fill_kernel, dim3(64), dim3(256), 0, stream, (float *)d_count,
+                           (int64_t)n_features * kBins, 0.0f);
+        hipLaunchKernelGGL(train_count_kernel,
+                           dim3((unsigned)((n_rows + kCountRows - 1) / kCountRows),
+                                (unsigned)((n_features + kHistFeats - 1) / kHistFeats)),
+                           dim3(512), 0, stream, (const uint8_t *)bins, n_features, (int)n_rows, h.r_pad, d_count);
+        hipLaunchKernelGGL(train_hot_bin_kernel, dim3((unsigned)n_features), dim3(kBins), 0, stream,
+                           (const uint32_t *)d_count, d_hot);
         hipLaunchKernelGGL(train_fill_kernel, dim3(1024), dim3(256), 0, stream, h.row_pred,
                            (int64_t)n_rows, bias);
         rc = check_launch("trainer set-up kernels launch");
@@ -1239,37 +1445,73 @@ extern "C" int fs_trainer_create(fs_trainer **out, int32_t n_features, const flo
     return FS_OK;
 }
 
-// The global histogram buffer of a trainer whose rows span several slabs, all zero at first
-// (the split kernel clears what it reads).
-static int ensure_hist(fs_trainer *t, hipStream_t stream)
+// Histograms live for one fs_train_boost only, and training calls on one device are ordered by the
+// caller, as its descriptors need already: all trainers share a buffer of the device.  It is kept between
+// calls (mapping and clearing 20 MB of fresh memory per trainer took 0.7 ms, a twentieth of a job's
+// retraining) up to this size; a batch that needs more has buffers of its trainers' own, freed with them.
+constexpr size_t kKeptWork = (size_t)256 << 20;
+
+// Replaces a buffer by a larger one; earlier batches may still be at work in it.
+static int grow(void **buf, size_t *have, size_t need)
 {
-    if (t->h.hist)
+    if (need <= *have)
         return FS_OK;
-    const size_t slots = t->max_depth > 0 ? (size_t)1 << (t->max_depth - 1) : 1;
-    const size_t words = slots * (size_t)t->h.n_features * kBins * 2;
-    int rc = dev_alloc(t, &t->h.hist, words);
-    if (rc != FS_OK)
-        return rc;
-    hipLaunchKernelGGL(train_fill_kernel, dim3(1024), dim3(256), 0, stream, (float *)t->h.hist,
-                       (int64_t)words * 2, 0.0f);
-    return check_launch("train_fill_kernel launch");
+    FS_HIP(hipDeviceSynchronize());
+    if (*buf)
+        (void)hipFree(*buf);
+    *buf = nullptr;
+    *have = 0;
+    const hipError_t e = hipMalloc(buf, need);
+    if (e != hipSuccess) {
+        *buf = nullptr;
+        return e == hipErrorOutOfMemory ? fail(FS_ENOMEM, "hipMalloc of %zu bytes failed", need)
+                                        : fail_hip(e, "hipMalloc");
+    }
+    *have = need;
+    return FS_OK;
 }
 
-// Buffers for the rows regrouped by node (deep trees).
-static int ensure_sort(fs_trainer *t)
+// Gives every trainer room for the histograms that trees of `depth` levels keep and for the parts of
+// its nodes of several items.
+static int place_hist(int n, fs_trainer *const *trainers, int depth, int shift)
 {
-    if (t->h.s_bins)
-        return FS_OK;
-    TrainDesc &h = t->h;
-    const size_t groups = ((size_t)h.n_features + 3) / 4;
-    int rc = dev_alloc(t, &h.s_qh, (size_t)h.n_rows);
-    if (rc == FS_OK) rc = dev_alloc(t, &h.s_rowid, (size_t)h.n_rows);
-    if (rc == FS_OK) rc = dev_alloc(t, &h.s_node, (size_t)h.n_rows);
-    if (rc == FS_OK) rc = dev_alloc(t, &h.s_dest, (size_t)h.n_rows);
-    if (rc == FS_OK) rc = dev_alloc(t, &h.seg_start, (size_t)kSortSegs + 1);
-    if (rc == FS_OK) rc = dev_alloc(t, &h.seg_cursor, (size_t)kSortSegs);
-    if (rc == FS_OK) rc = dev_alloc(t, &h.s_bins, groups * (size_t)h.r_pad * 4);   // last: marks the set complete
-    return rc;
+    auto words = [&](const fs_trainer *t, size_t *hist, size_t *part) {
+        const size_t row = (size_t)t->h.n_features * kBins;
+        const int64_t rows = t->h.n_rows;
+        *hist = (depth > 1 ? (size_t)1 << (depth - 2) : 1) * row;
+        *part = rows >> shift ? ((size_t)((2 * rows) >> shift) + 1) * row : 0;
+        return (*hist + *part) * 2 * sizeof(unsigned long long);
+    };
+    size_t all = 0, hist, part;
+    for (int i = 0; i < n; ++i)
+        all += words(trainers[i], &hist, &part);
+    int dev = 0;
+    FS_HIP(hipGetDevice(&dev));
+    if (dev < 0 || dev >= 16)
+        return fail(FS_EUNSUPPORTED, "device ordinal %d not supported", dev);
+    const bool shared = all <= kKeptWork;
+    if (shared) {
+        const int rc = grow(&g_batch[dev].work, &g_batch[dev].work_bytes, all);
+        if (rc != FS_OK)
+            return rc;
+    }
+    char *at = (char *)g_batch[dev].work;
+    for (int i = 0; i < n; ++i) {
+        fs_trainer *t = trainers[i];
+        const size_t bytes = words(t, &hist, &part);
+        if (!shared) {
+            const int rc = grow(&t->own_work, &t->own_work_bytes, bytes);
+            if (rc != FS_OK)
+                return rc;
+            at = (char *)t->own_work;
+        }
+        t->h.hist = (unsigned long long *)at;
+        t->h.hist_plane = (int64_t)hist;
+        t->h.part = t->h.hist + 2 * hist;
+        t->h.part_plane = (int64_t)part;
+        at += bytes;
+    }
+    return FS_OK;
 }
 
 // Uploads the batch's descriptors; returns the device array.
@@ -1366,6 +1608,7 @@ extern "C" int fs_train_boost(int32_t n_trainers, fs_trainer *const *trainers, i
     if (n_trainers == 0 || n_rounds == 0)
         return FS_OK;
     int max_rows = 0, max_prog = 0, max_feat = 0, max_len = 0;
+    int64_t total_rows = 0;
     for (int i = 0; i < n_trainers; ++i) {
         const fs_trainer *t = trainers[i];
         if (p->max_depth > t->max_depth)
@@ -1373,31 +1616,25 @@ extern "C" int fs_train_boost(int32_t n_trainers, fs_trainer *const *trainers, i
         if (t->trees_enqueued + n_rounds > t->max_trees)
             return fail(FS_EUNSUPPORTED, "fs_train_boost: trainer %d holds %d trees of at most %d", i,
                         t->trees_enqueued, t->max_trees);
+        total_rows += t->h.n_rows;
         if (t->h.n_rows > max_rows) max_rows = t->h.n_rows;
         if (t->h.n_programs > max_prog) max_prog = t->h.n_programs;
         if (t->h.n_features > max_feat) max_feat = t->h.n_features;
         if (t->max_len > max_len) max_len = t->max_len;
     }
     std::lock_guard<std::mutex> lock(g_train_mu);
-    int slab_rows = kHistRowsPerSlab;
+    // A histogram workgroup takes up to 2^shift rows of a node: 48 to 96 pieces of all the batch's rows
+    // at the root, which with ten feature groups are two to four workgroups per compute unit.
+    int shift = kChunkShiftMin;
+    while (shift < 30 && ((int64_t)1 << shift) * kChunkPieces < total_rows)
+        ++shift;
     {
         const int v = tune(FS_TUNE_TRAIN_SLAB_ROWS);             // test / tuning override
-        if (v >= 64 && v <= kHistRowsPerSlab)
-            slab_rows = v;
+        if (v >= 64 && v <= 65536)
+            for (shift = 6; (1 << shift) < v;)
+                ++shift;
     }
-    // one slab per family up to slab_rows rows: the histogram workgroup then searches the cuts
-    // itself and nothing is added up in global memory
-    const int n_slabs = (max_rows + slab_rows - 1) / slab_rows;
-    if (n_slabs > 1)
-        for (int i = 0; i < n_trainers && rc == FS_OK; ++i)
-            rc = ensure_hist(trainers[i], stream);
-    // deep trees of one-slab families: rows regrouped by node before level kSortLevel
-    bool use_sort = n_slabs == 1 && p->max_depth >= kSortMinDepth;
-    if (tune(FS_TUNE_TRAIN_SORT) >= 0)                           // override: 0 never, 1 whenever possible
-        use_sort = n_slabs == 1 && tune(FS_TUNE_TRAIN_SORT) != 0 && p->max_depth > kSortLevel;
-    if (use_sort)
-        for (int i = 0; i < n_trainers && rc == FS_OK; ++i)
-            rc = ensure_sort(trainers[i]);
+    rc = place_hist(n_trainers, trainers, p->max_depth, shift);
     if (rc != FS_OK)
         return rc;
     const TrainDesc *d = nullptr;
@@ -1414,67 +1651,43 @@ extern "C" int fs_train_boost(int32_t n_trainers, fs_trainer *const *trainers, i
     prm.grad_scale = p->grad_scale;
     prm.max_depth = p->max_depth;
 
-    static bool hist_configured[16] = {};
-    {
-        int dev = 0;
-        FS_HIP(hipGetDevice(&dev));
-        if (!hist_configured[dev]) {
-            FS_HIP(hipFuncSetAttribute((const void *)train_hist_kernel<true>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       kHistSlotsPacked * kHistFeats * kBins * 8 + kHistTrashWords * 8));
-            FS_HIP(hipFuncSetAttribute((const void *)train_hist_kernel<false>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       kHistSlotsWide * kHistFeats * kBins * 16 + kHistTrashWords * 8));
-            hist_configured[dev] = true;
-        }
-    }
     const unsigned nt = (unsigned)n_trainers;
-    const unsigned row_blocks = (unsigned)((max_rows + 255) / 256);
-    const int rows_per_slab = (((max_rows + n_slabs - 1) / n_slabs) + 63) & ~63;
-    // Bits that hold any curvature sum of a slab (rows x longest program bounds it).  The packed
-    // form of the histograms needs room for the gradient sums beside them; beyond 31 bits the
-    // wide form is launched right away.
+    const unsigned groups = (unsigned)((max_feat + kHistFeats - 1) / kHistFeats);
+    // Bits that hold any curvature sum (rows x longest program bounds it).  The packed form of the
+    // histograms needs room for the gradient sums beside them; beyond 31 bits the wide form is
+    // taken right away.
     int hb = 1;
-    {
-        const long long bound = (long long)max_len * (long long)(rows_per_slab < max_rows ? rows_per_slab : max_rows);
-        while (hb < 63 && ((long long)1 << hb) <= bound)
-            ++hb;
-    }
-    bool packed = hb <= 31;
-    if (tune(FS_TUNE_TRAIN_PACKED) == 0)                         // override: wide form only
-        packed = false;
+    while (hb < 63 && ((long long)1 << hb) <= (long long)max_len * (long long)max_rows)
+        ++hb;
+    if (hb > 31 || tune(FS_TUNE_TRAIN_PACKED) == 0)              // override: wide form only
+        hb = 0;
+    prof_start(kKernTrainOther, stream);
+    hipLaunchKernelGGL(train_begin_kernel, dim3(nt), dim3(512), 0, stream, d);
+    prof_stop(stream);
     for (int round = 0; round < n_rounds; ++round) {
         prof_start(kKernTrainOther, stream);
-        hipLaunchKernelGGL(train_begin_tree_kernel, dim3(nt), dim3(512), 0, stream, d);
         hipLaunchKernelGGL(train_grad_kernel, dim3((unsigned)((max_prog + 255) / 256), nt), dim3(256), 0,
                            stream, d, prm.grad_scale, 1);
         prof_stop(stream);
-        for (int level = 0; level < prm.max_depth; ++level) {
+        for (int level = 0; level < std::max(1, prm.max_depth); ++level) {
             const int n_slots = 1 << level;
-            const int sorted = use_sort && level >= kSortLevel ? 1 : 0;
-            const int per_pass = packed ? kHistSlotsPacked : kHistSlotsWide;
-            const int slots = n_slots < per_pass ? n_slots : per_pass;
-            const int passes = n_slots / slots;
-            const dim3 hgrid((unsigned)n_slabs, (unsigned)((max_feat + kHistFeats - 1) / kHistFeats), nt * passes);
-            prof_start(kKernTrainHist, stream);
-            if (packed) {
-                // a lone node still needs the 8 KB of its wide form for the fall-back
-                size_t lds = (size_t)slots * kHistFeats * kBins * 8;
-                if (lds < (size_t)kHistFeats * kBins * 16)
-                    lds = (size_t)kHistFeats * kBins * 16;
-                hipLaunchKernelGGL(train_hist_kernel<true>, hgrid, dim3(kHistThreads), lds + kHistTrashWords * 8,
-                                   stream, d, level, passes, rows_per_slab, n_slabs, hb, sorted, prm);
+            if (level < prm.max_depth) {
+                // at most this many items and, of those, nodes of several: the counted children hold at
+                // most half the rows, each at least one
+                const int64_t rows = level ? max_rows / 2 : max_rows, n_counted = level ? n_slots / 2 : 1;
+                const int64_t items = std::max<int64_t>(1, std::min(rows, (rows >> shift) + n_counted));
+                const int64_t several = std::min(rows >> shift, n_counted);
+                prof_start(kKernTrainHist, stream);
+                hipLaunchKernelGGL(train_hist_kernel, dim3((unsigned)items, groups, nt), dim3(kHistThreads), 0,
+                                   stream, d, level, shift, hb, prm);
+                prof_stop(stream);
+                prof_start(kKernTrainSplit, stream);
+                if (several > 0)
+                    hipLaunchKernelGGL(train_split_kernel, dim3((unsigned)max_feat, (unsigned)several, nt),
+                                       dim3(64 * kSplitWaves), 0, stream, d, level, shift, hb, prm);
             } else {
-                hipLaunchKernelGGL(train_hist_kernel<false>, hgrid, dim3(kHistThreads),
-                                   (size_t)slots * kHistFeats * kBins * 16 + kHistTrashWords * 8, stream, d, level, passes,
-                                   rows_per_slab, n_slabs, 0, sorted, prm);
+                prof_start(kKernTrainSplit, stream);
             }
-            prof_stop(stream);
-            prof_start(kKernTrainSplit, stream);
-            if (n_slabs > 1)
-                hipLaunchKernelGGL(train_split_kernel,
-                                   dim3((unsigned)((n_slots * max_feat + kSplitWaves - 1) / kSplitWaves), 1u, nt),
-                                   dim3(64 * kSplitWaves), 0, stream, d, level, prm);
             // from 64 nodes on the per-node reduction over the features gets the whole chip
             const int reduced = n_slots >= kPickSpreadSlots ? 1 : 0;
             if (reduced)
@@ -1485,24 +1698,11 @@ extern "C" int fs_train_boost(int32_t n_trainers, fs_trainer *const *trainers, i
                                prm);
             prof_stop(stream);
             prof_start(kKernTrainOther, stream);
-            if (sorted)
-                hipLaunchKernelGGL(train_part_sorted_kernel, dim3(row_blocks, nt), dim3(256), 0, stream, d, level);
-            else
-                hipLaunchKernelGGL(train_part_kernel, dim3(row_blocks, nt), dim3(256), 0, stream, d, level);
-            if (use_sort && level == kSortLevel - 1) {
-                hipLaunchKernelGGL(train_seg_count_kernel, dim3(row_blocks, nt), dim3(256), 0, stream, d);
-                hipLaunchKernelGGL(train_seg_scan_kernel, dim3(nt), dim3(64), 0, stream, d);
-                hipLaunchKernelGGL(train_seg_place_kernel, dim3(row_blocks, nt), dim3(256), 0, stream, d);
-                hipLaunchKernelGGL(train_seg_bins_kernel, dim3(row_blocks, (unsigned)((max_feat + 3) / 4), nt),
-                                   dim3(256), 0, stream, d);
-            }
+            hipLaunchKernelGGL(train_part_kernel, dim3((unsigned)((max_rows + (int64_t)kPartThreads - 1) / kPartThreads), nt),
+                               dim3(kPartThreads), 0, stream, d, level, prm.max_depth);
             prof_stop(stream);
         }
         prof_start(kKernTrainOther, stream);
-        hipLaunchKernelGGL(train_pick_kernel, dim3(nt), dim3(kPickThreads), 0, stream, d,
-                           prm.max_depth, 0, prm);
-        hipLaunchKernelGGL(train_update_kernel, dim3(row_blocks, nt), dim3(256), 0, stream, d,
-                           use_sort ? 1 : 0);
         hipLaunchKernelGGL(train_emit_kernel, dim3(nt), dim3(512), 0, stream, d);
         prof_stop(stream);
         rc = check_launch("training kernels launch");
