@@ -14,8 +14,8 @@
 //   per level:   hist (LDS histograms of the smaller child of every split node, sixteen features
 //                per workgroup; the larger child is the parent minus the smaller, exactly; a
 //                feature's most frequent bin is never counted, it is the node's total minus the
-//                rest; the workgroup goes on to search the cuts of both children), split (the same
-//                search where a node's rows were dealt to several workgroups), pick (per node: best
+//                rest), split (adds up the parts of nodes whose rows were dealt to several workgroups,
+//                subtracts, searches the cuts of both children), pick (per node: best
 //                feature, split or leaf, child ids in breadth-first order), part (records of split
 //                nodes move to their child's segment, rows of leaves take the leaf's value)
 //   emit         heap -> flat model arrays; clears the heap for the next tree
@@ -130,8 +130,8 @@ train_bin_kernel(const float *__restrict__ x, int layout, int n_features, int n_
     ((uint4 *)bins)[(int64_t)blockIdx.y * r_pad + r] = make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-// Rows per (feature, bin): 4096 rows of sixteen features per workgroup, counted in LDS.
-constexpr int kCountRows = 4096;
+// Rows per (feature, bin): 1024 rows of sixteen features per workgroup, counted in LDS.
+constexpr int kCountRows = 1024;
 
 __global__ void __launch_bounds__(512)
 train_count_kernel(const uint8_t *__restrict__ bins, int n_features, int n_rows, int64_t r_pad,
@@ -591,12 +591,12 @@ __device__ __forceinline__ void wave_best_cut_packed(const TrainDesc &d, const P
 // node) and gathers each row's bins, 16 bytes at a time.  Over a tree of depth 8 rows are visited 4.5
 // times instead of 8 and no level streams the rows of other nodes.
 //
-// A node of a single item is finished here: one wavefront per feature reads the parent's bins,
-// searches the cuts of both children and, unless the level is the last that splits, leaves both
-// histograms for the next level, the larger child's in the parent's place.  The items of larger
-// nodes write their part and train_split_kernel adds the parts up.  (Parts are stored and not added
-// atomically: nothing has to be cleared, and the memory-side atomics of eight XCDs are slower
-// than the extra read.)
+// A node of a single item leaves its histogram in its place of `hist`; the items of larger nodes write
+// their part and train_split_kernel adds the parts up.  (Parts are stored and not added atomically:
+// nothing has to be cleared, and the memory-side atomics of eight XCDs are slower than the extra
+// read.)  The cut search is a kernel of its own: in here it held the row loop to 6 wavefronts a
+// SIMD and a node's sixteen features to eight wavefronts; depth 6, 25 500 rows: 15 us for the
+// histograms and cuts of 8 nodes.
 //
 // Two forms of a bin.  Packed: one 64-bit word G * 2^hb + H, fed by one atomic per (row, feature);
 // hb bits hold any curvature sum (the host knows rows x longest program) and the rest holds G as
@@ -606,7 +606,7 @@ __device__ __forceinline__ void wave_best_cut_packed(const TrainDesc &d, const P
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 constexpr int kHistThreads = 512;
 constexpr int kHistWaves = kHistThreads / 64;
-static_assert(kBins * 8 >= kCutScratchBytes, "the cut search borrows its own histogram's LDS");
+static_assert(kBins * 8 >= kCutScratchBytes, "room for the cut search's scratch");
 
 __device__ __forceinline__ bool is_packed(const TrainDesc &d, int hb)
 {
@@ -633,14 +633,14 @@ __device__ __forceinline__ int wave_prefix_i(int v)
 }
 
 // Item number `index` of the level (every wavefront finds it for itself: one 16-byte load per parent
-// and a scan).  `nodes`: number nodes of several items instead, each once.
+// and a scan).  `nodes`: number the counted nodes instead.
 __device__ __forceinline__ bool find_item(const TrainDesc &d, int level, int shift, int index, bool nodes,
                                           int lane, Item &it)
 {
     if (level == 0) {
         const int pieces = (int)(((int64_t)d.n_rows + (1ll << shift) - 1) >> shift);
         it = {0, -1, 0, 0, d.n_rows, index};
-        return nodes ? index == 0 && pieces > 1 : index < pieces;
+        return index < (nodes ? 1 : pieces);
     }
     constexpr int kMost = (1 << (FS_TRAIN_MAX_DEPTH - 2)) / 64;   // parents per lane
     const int n_pairs = 1 << (level - 1);
@@ -653,7 +653,7 @@ __device__ __forceinline__ bool find_item(const TrainDesc &d, int level, int shi
         if (i < per && pair < n_pairs) {
             const int4 s = d.seg[n_pairs - 1 + pair];
             const int pieces = (int)(((int64_t)min(s.x, s.y) + (1ll << shift) - 1) >> shift);
-            items[i] = nodes ? (pieces > 1 ? 1 : 0) : pieces;
+            items[i] = nodes ? min(pieces, 1) : pieces;
         }
         sum += items[i];
     }
@@ -724,24 +724,29 @@ struct Bins4 {                // four consecutive bins of a lane
     }
 };
 
-// Cuts of one child: `which` = 0 the counted node, 1 its sibling.  `own` holds the counted node's bins
-// and is the other child's when this returns.
-template <bool PACKED>
-__device__ __forceinline__ void search_child(const TrainDesc &d, const Params &prm, int level, const Item &it,
-                                             int which, int f, int lane, Bins4<PACKED> &own, int hb,
-                                             unsigned char *scratch)
+// Words of a node's histogram of feature f; at the root and for counted children a place of their own,
+// for the larger child its parent's.
+__device__ __forceinline__ int64_t hist_at(const TrainDesc &d, int level, const Item &it, int which, int f)
 {
     const int n_pairs = level > 0 ? 1 << (level - 1) : 0;
-    const int parent_slot = level > 0 ? d.h_slot[n_pairs - 1 + it.pair] : 0;
-    const int slot = which || level == 0 ? parent_slot : n_pairs + it.pair;
+    const int slot = level == 0 ? 0 : which ? d.h_slot[n_pairs - 1 + it.pair] : n_pairs + it.pair;
+    return ((int64_t)slot * d.n_features + f) * kBins;
+}
+
+// Cuts of one child: `which` = 0 the counted node, 1 its sibling; `own`: the counted node's bins.
+template <bool PACKED>
+__device__ __forceinline__ void search_child(const TrainDesc &d, const Params &prm, int level, const Item &it,
+                                             int which, bool store, int f, int lane, Bins4<PACKED> &own, int hb,
+                                             unsigned char *scratch)
+{
     const int node = which ? it.large : it.small;
-    unsigned long long *place = d.hist + ((int64_t)slot * d.n_features + f) * kBins + 4 * lane;
+    unsigned long long *place = d.hist + hist_at(d, level, it, which, f) + 4 * lane;
     if (which) {
         Bins4<PACKED> parent;
         parent.load(place, d.hist_plane);
         own.add(parent, true);
     }
-    if (level + 1 < prm.max_depth)
+    if (store && level + 1 < prm.max_depth)
         own.store(place, d.hist_plane);
     const int pair = (node - ((1 << level) - 1)) * d.n_features + f;
     if constexpr (PACKED) {
@@ -764,8 +769,7 @@ __device__ __forceinline__ void note_slots(const TrainDesc &d, int level, const 
 
 // Features f0 + base .. + NF of the item.
 template <bool PACKED>
-__device__ __forceinline__ void hist_run(const TrainDesc &d, const Params &prm, unsigned long long *lds,
-                                         const Item &it, int level, int shift, int group, int base, int hb)
+__device__ __forceinline__ void hist_run(const TrainDesc &d, unsigned long long *lds, const Item &it, int level, int shift, int group, int base, int hb)
 {
     constexpr int NF = PACKED ? kHistFeats : kHistFeats / 2;
     constexpr int NW = NF / 4;
@@ -816,35 +820,22 @@ __device__ __forceinline__ void hist_run(const TrainDesc &d, const Params &prm, 
         }
     }
     __syncthreads();
-    if (it.count > 1 << shift) {
-        const int64_t at = ((part_slot(it.first, shift) + it.piece) * d.n_features + f0) * kBins;
-        for (int j = threadIdx.x; j < nf * kBins; j += kHistThreads) {
-            d.part[at + j] = lds[j];
-            if (!PACKED)
-                d.part[at + d.part_plane + j] = lds[kHistWords / 2 + j];
-        }
-    } else {
-        const int lane = threadIdx.x & 63;
-        const int children = level > 0 ? 2 : 1;
-        for (int k = threadIdx.x >> 6; k < nf; k += kHistWaves) {
-            // The feature's bins are in registers once read and no other wavefront reads them: their LDS
-            // serves as the search's scratch (a wavefront's LDS accesses complete in order).
-            Bins4<PACKED> own;
-            own.load(lds + k * kBins + 4 * lane, kHistWords / 2);
-#pragma unroll 1
-            for (int which = 0; which < children; ++which)
-                search_child<PACKED>(d, prm, level, it, which, f0 + k, lane, own, hb,
-                                     (unsigned char *)(lds + k * kBins));
-        }
-        if (f0 == 0 && threadIdx.x == 0 && level > 0 && level + 1 < prm.max_depth)
-            note_slots(d, level, it);
+    const bool whole = it.count <= 1 << shift;
+    const int64_t plane = whole ? d.hist_plane : d.part_plane;
+    unsigned long long *out =
+        whole ? d.hist + hist_at(d, level, it, 0, f0)
+              : d.part + ((part_slot(it.first, shift) + it.piece) * d.n_features + f0) * kBins;
+    for (int j = 2 * threadIdx.x; j < nf * kBins; j += 2 * kHistThreads) {
+        *(ulonglong2 *)(out + j) = *(ulonglong2 *)(lds + j);
+        if (!PACKED)
+            *(ulonglong2 *)(out + plane + j) = *(ulonglong2 *)(lds + kHistWords / 2 + j);
     }
     __syncthreads();                                             // LDS may be reused by the next run
 }
 
 // blockIdx = (item, feature group, trainer)
-__global__ void __launch_bounds__(kHistThreads, 6)
-train_hist_kernel(const TrainDesc *__restrict__ descs, int level, int shift, int hb, Params prm)
+__global__ void __launch_bounds__(kHistThreads)
+train_hist_kernel(const TrainDesc *__restrict__ descs, int level, int shift, int hb)
 {
     __shared__ __align__(16) unsigned long long lds[kHistWords + 64];
     const TrainDesc &d = descs[blockIdx.z];
@@ -853,45 +844,52 @@ train_hist_kernel(const TrainDesc *__restrict__ descs, int level, int shift, int
         !find_item(d, level, shift, (int)blockIdx.x, false, threadIdx.x & 63, it))
         return;
     if (is_packed(d, hb)) {
-        hist_run<true>(d, prm, lds, it, level, shift, blockIdx.y, 0, hb);
+        hist_run<true>(d, lds, it, level, shift, blockIdx.y, 0, hb);
     } else {
-        hist_run<false>(d, prm, lds, it, level, shift, blockIdx.y, 0, 0);
+        hist_run<false>(d, lds, it, level, shift, blockIdx.y, 0, 0);
         if ((int)blockIdx.y * kHistFeats + kHistFeats / 2 < d.n_features)
-            hist_run<false>(d, prm, lds, it, level, shift, blockIdx.y, kHistFeats / 2, 0);
+            hist_run<false>(d, lds, it, level, shift, blockIdx.y, kHistFeats / 2, 0);
     }
 }
 
-// Nodes of several items: one workgroup per (node, feature) adds the parts up, every wavefront some of
-// them, then one wavefront searches the node's cuts and another its sibling's.
+// One workgroup per (counted node, feature): the wavefronts add up the node's parts if it has several,
+// then one searches the node's cuts and another its sibling's, whose histogram takes the parent's place.
+// Four wavefronts where a node may have many parts, else two.
 constexpr int kSplitWaves = 4;
 
 template <bool PACKED>
 __device__ __forceinline__ void split_run(const TrainDesc &d, const Params &prm, unsigned long long *lds,
                                           const Item &it, int level, int shift, int f, int hb)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+    const int children = level > 0 ? 2 : 1;
     const int pieces = (int)(((int64_t)it.count + (1ll << shift) - 1) >> shift);
-    const unsigned long long *part = d.part + (part_slot(it.first, shift) * d.n_features + f) * kBins + 4 * lane;
-    const int64_t stride = (int64_t)d.n_features * kBins;
     Bins4<PACKED> own = {};
+    if (pieces > 1) {
+        const unsigned long long *part = d.part + (part_slot(it.first, shift) * d.n_features + f) * kBins + 4 * lane;
+        const int64_t stride = (int64_t)d.n_features * kBins;
 #pragma unroll 4
-    for (int j = wave; j < pieces; j += kSplitWaves) {
-        Bins4<PACKED> one;
-        one.load(part + j * stride, d.part_plane);
-        own.add(one, false);
+        for (int j = wave; j < pieces; j += waves) {
+            Bins4<PACKED> one;
+            one.load(part + j * stride, d.part_plane);
+            own.add(one, false);
+        }
+        own.store(lds + wave * kBins + 4 * lane, kSplitWaves * kBins);
+        __syncthreads();
+        if (wave >= children)
+            return;
+        own = {};
+        for (int j = 0; j < waves; ++j) {
+            Bins4<PACKED> one;
+            one.load(lds + j * kBins + 4 * lane, kSplitWaves * kBins);
+            own.add(one, false);
+        }
+    } else {
+        if (wave >= children)
+            return;
+        own.load(d.hist + hist_at(d, level, it, 0, f) + 4 * lane, d.hist_plane);
     }
-    own.store(lds + wave * kBins + 4 * lane, kSplitWaves * kBins);
-    __syncthreads();
-    if (wave >= (level > 0 ? 2 : 1))
-        return;
-    own = {};
-#pragma unroll
-    for (int j = 0; j < kSplitWaves; ++j) {
-        Bins4<PACKED> one;
-        one.load(lds + j * kBins + 4 * lane, kSplitWaves * kBins);
-        own.add(one, false);
-    }
-    search_child<PACKED>(d, prm, level, it, wave, f, lane, own, hb,
+    search_child<PACKED>(d, prm, level, it, wave, wave || pieces > 1, f, lane, own, hb,
                          (unsigned char *)(lds + 2 * kSplitWaves * kBins) + wave * kBins * 8);
     if (f == 0 && wave == 0 && lane == 0 && level > 0 && level + 1 < prm.max_depth)
         note_slots(d, level, it);
@@ -1426,7 +1424,7 @@ extern "C" int fs_trainer_create(fs_trainer **out, int32_t n_features, const flo
     }
     if (rc == FS_OK) {
         // counters[3] is free until training starts: longest program, read back here
-        hipLaunchKernelGGL(train_max_len_kernel, dim3(256), dim3(256), 0, stream,
+        hipLaunchKernelGGL(train_max_len_kernel, dim3((unsigned)std::min(256, (n_programs + 255) / 256)), dim3(256), 0, stream,
                            (const int32_t *)d_prog_off, n_programs, h.counters + 3);
         rc = check_launch("train_max_len_kernel launch");
         if (rc == FS_OK) {
@@ -1449,7 +1447,7 @@ extern "C" int fs_trainer_create(fs_trainer **out, int32_t n_features, const flo
 // caller, as its descriptors need already: all trainers share a buffer of the device.  It is kept between
 // calls (mapping and clearing 20 MB of fresh memory per trainer took 0.7 ms, a twentieth of a job's
 // retraining) up to this size; a batch that needs more has buffers of its trainers' own, freed with them.
-constexpr size_t kKeptWork = (size_t)256 << 20;
+constexpr size_t kKeptWork = (size_t)512 << 20;
 
 // Replaces a buffer by a larger one; earlier batches may still be at work in it.
 static int grow(void **buf, size_t *have, size_t need)
@@ -1478,7 +1476,7 @@ static int place_hist(int n, fs_trainer *const *trainers, int depth, int shift)
     auto words = [&](const fs_trainer *t, size_t *hist, size_t *part) {
         const size_t row = (size_t)t->h.n_features * kBins;
         const int64_t rows = t->h.n_rows;
-        *hist = (depth > 1 ? (size_t)1 << (depth - 2) : 1) * row;
+        *hist = (depth > 0 ? (size_t)1 << (depth - 1) : 1) * row;
         *part = rows >> shift ? ((size_t)((2 * rows) >> shift) + 1) * row : 0;
         return (*hist + *part) * 2 * sizeof(unsigned long long);
     };
@@ -1672,19 +1670,17 @@ extern "C" int fs_train_boost(int32_t n_trainers, fs_trainer *const *trainers, i
         for (int level = 0; level < std::max(1, prm.max_depth); ++level) {
             const int n_slots = 1 << level;
             if (level < prm.max_depth) {
-                // at most this many items and, of those, nodes of several: the counted children hold at
-                // most half the rows, each at least one
+                // at most this many items: the counted children hold at most half the rows, each at least one
                 const int64_t rows = level ? max_rows / 2 : max_rows, n_counted = level ? n_slots / 2 : 1;
                 const int64_t items = std::max<int64_t>(1, std::min(rows, (rows >> shift) + n_counted));
-                const int64_t several = std::min(rows >> shift, n_counted);
                 prof_start(kKernTrainHist, stream);
                 hipLaunchKernelGGL(train_hist_kernel, dim3((unsigned)items, groups, nt), dim3(kHistThreads), 0,
-                                   stream, d, level, shift, hb, prm);
+                                   stream, d, level, shift, hb);
                 prof_stop(stream);
                 prof_start(kKernTrainSplit, stream);
-                if (several > 0)
-                    hipLaunchKernelGGL(train_split_kernel, dim3((unsigned)max_feat, (unsigned)several, nt),
-                                       dim3(64 * kSplitWaves), 0, stream, d, level, shift, hb, prm);
+                hipLaunchKernelGGL(train_split_kernel, dim3((unsigned)max_feat, (unsigned)std::min(std::max<int64_t>(1, rows), n_counted), nt),
+                                   dim3(64 * (n_counted <= 4 ? kSplitWaves : 2)), 0, stream, d, level, shift, hb,
+                                   prm);
             } else {
                 prof_start(kKernTrainSplit, stream);
             }
