@@ -18,10 +18,12 @@
 //                subtracts, searches the cuts of both children), pick (per node: best
 //                feature, split or leaf, child ids in breadth-first order), part (records of split
 //                nodes move to their child's segment, rows of leaves take the leaf's value)
-//   emit         heap -> flat model arrays; clears the heap for the next tree
+//                (after the last level: heap -> flat model arrays, heap cleared for the next tree)
 #include <math.h>
 #include <stdlib.h>
+#include <string.h>
 #include <algorithm>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -50,6 +52,13 @@ struct __align__(32) Best {
     int32_t cut, pad;
 };
 
+// Best feature of a node, and its cut.
+struct Winner {
+    double gain;
+    long long GL, HL;
+    int32_t feature, cut;     // feature -1: no candidate
+};
+
 struct TrainDesc {
     const uint8_t *bins;       // [feature / 16][r_pad][16]: a row's bins of sixteen consecutive
                                // features are one 16-byte load
@@ -70,15 +79,15 @@ struct TrainDesc {
     unsigned long long *hist;  // [slot][feature][bin]: complete histograms, what the next level subtracts from
     unsigned long long *part;  // the same of parts of a node, see part_slot
     int64_t hist_plane, part_plane;   // words to the curvature sums (wide form)
-    int32_t *h_state, *h_feat, *h_id;
-    float *h_thr, *h_val;
+    int32_t *h_state, *h_id;
+    float *h_val;
     long long *h_G, *h_H;
+    double *h_own;             // the node's own term of the gain
     Best *best;                // [node of the level][feature]
     int4 *decision;            // per node of the heap: {state, feature, cut, leaf value (bits)}
     int32_t *counters;         // [0] next node id of the tree in work, [1] trees, [2] nodes
     unsigned long long *abs_q; // sum over the rows of |gradient| (fixed point) of the round in work
-    int32_t *pk_feat, *pk_cut; // per node of a level: its best feature and cut (levels with many nodes)
-    double *pk_gain;
+    Winner *winner;            // per node of a level (levels with many nodes)
     int32_t *m_tree_off, *m_feat, *m_left, *m_right;
     float *m_thr, *m_val;
     int64_t r_pad;
@@ -202,19 +211,28 @@ __global__ void train_fill_kernel(float *p, int64_t n, float v)
         p[i] = v;
 }
 
+__global__ void train_clear_kernel(uint32_t *count, int n, int32_t *counters, int32_t *tree_off)
+{
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
+        count[i] = 0u;
+    if (blockIdx.x == 0 && threadIdx.x < 4)
+        counters[threadIdx.x] = 0;
+    if (blockIdx.x == 0 && threadIdx.x == 4)
+        tree_off[0] = 0;
+}
+
 // ---- per-round kernels -------------------------------------------------------------------
 
-// The heap of the tree to grow (one workgroup per trainer).
+// The heap of the tree to grow (one workgroup per trainer).  What belongs to a node below the root is
+// written when its parent is split.
 __device__ __forceinline__ void begin_tree(const TrainDesc &d)
 {
-    for (int i = threadIdx.x; i < kHeapNodes; i += blockDim.x) {
+    for (int i = threadIdx.x; i < kHeapNodes; i += blockDim.x)
         d.h_state[i] = i == 0 ? kOpen : kAbsent;
-        d.h_G[i] = 0;
-        d.h_H[i] = 0;
-        d.h_id[i] = 0;
-        d.h_val[i] = 0.0f;
-    }
     if (threadIdx.x == 0) {
+        d.h_G[0] = 0;
+        d.h_H[0] = 0;
+        d.h_id[0] = 0;
         d.counters[0] = 1;
         d.h_slot[0] = 0;
         *d.abs_q = 0ull;
@@ -491,7 +509,9 @@ __device__ __forceinline__ float wave_max_f(float v)
 //  - G and H go through one prefix sum, still packed.
 //  - GL^2/(HL+lambda) + GR^2/(HR+lambda) is formed in float first, and only cuts within 2^-18 of
 //    the largest are evaluated as the definition says, usually one.  The float value is within
-//    10 * 2^-24 of the true one (G in units of 2^-hb is below 2^63 and its square is taken times the
+//    10 * 2^-24 of the true one (G and GL times 2^hb are multiples of 2^hb below 2^63, and below
+//    2^(31+2hb) since there are fewer than 2^hb rows: at most 53 bits, so their difference in double is
+//    exact; G in units of 2^-hb is below 2^63 and its square is taken times the
 //    reciprocal, so nothing overflows; a reciprocal that underflows leaves 0 for every cut, and
 //    all are evaluated).  The gain itself is that sum minus a term that is the same for all cuts
 //    and at most twice the sum, so a cut that wins after the rounding of double arithmetic is
@@ -519,6 +539,7 @@ __device__ __forceinline__ void wave_best_cut_packed(const TrainDesc &d, const P
     }
     const int mcw = (int)min(prm.mcw, 0x7fffffffll), H_all = (int)H;
     const float lambda = (float)prm.lambda;
+    const double G_all = (double)(long long)(total - (unsigned long long)H);
     float t[4], most = 0.0f;
     bool cand[4];
     int n_cand = 0;
@@ -529,9 +550,8 @@ __device__ __forceinline__ void wave_best_cut_packed(const TrainDesc &d, const P
         v[k] = before;                                           // left sums of cut 4 * lane + k + 1
         const int HL = (int)((unsigned)before & mask), HR = H_all - HL;
         cand[k] = 4 * lane + k + 1 <= m && filled && HL >= mcw && HR >= mcw;
-        const unsigned long long GL = before - (unsigned)HL;     // times 2^hb
-        const float gl = (float)(double)(long long)GL;
-        const float gr = (float)(double)(long long)(total - (unsigned long long)H - GL);
+        const double GL = (double)(long long)(before - (unsigned)HL);   // times 2^hb
+        const float gl = (float)GL, gr = (float)(G_all - GL);
         const float l = gl * __builtin_amdgcn_rcpf((float)HL + lambda), r = gr * __builtin_amdgcn_rcpf((float)HR + lambda);
         t[k] = gl * l + gr * r;
         most = cand[k] ? fmaxf(most, t[k]) : most;
@@ -541,7 +561,7 @@ __device__ __forceinline__ void wave_best_cut_packed(const TrainDesc &d, const P
     int cut = 0;
     double best = 0.0;
     long long bGL = 0, bHL = 0;
-    const double t3 = parent_term(G, H, prm.inv_scale, prm.lambda);
+    const double t3 = node == 0 ? parent_term(G, H, prm.inv_scale, prm.lambda) : d.h_own[node];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const bool eval = cand[k] && !(t[k] < least);
@@ -605,7 +625,6 @@ __device__ __forceinline__ void wave_best_cut_packed(const TrainDesc &d, const P
 // the same LDS; H has a plane of its own in the buffers.  Every kernel of a round decides alike.
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 constexpr int kHistThreads = 512;
-constexpr int kHistWaves = kHistThreads / 64;
 static_assert(kBins * 8 >= kCutScratchBytes, "room for the cut search's scratch");
 
 __device__ __forceinline__ bool is_packed(const TrainDesc &d, int hb)
@@ -632,15 +651,22 @@ __device__ __forceinline__ int wave_prefix_i(int v)
     return v;
 }
 
+// The counted node of a pair, given the parent's segment.
+__device__ __forceinline__ Item counted_node(int parent, int pair, const int4 &s)
+{
+    const int left = 2 * parent + 1;
+    if (s.x <= s.y)
+        return {left, left + 1, pair, s.z, s.x, 0};
+    return {left + 1, left, pair, s.z + s.x, s.y, 0};
+}
+
 // Item number `index` of the level (every wavefront finds it for itself: one 16-byte load per parent
-// and a scan).  `nodes`: number the counted nodes instead.
-__device__ __forceinline__ bool find_item(const TrainDesc &d, int level, int shift, int index, bool nodes,
-                                          int lane, Item &it)
+// and a scan).
+__device__ __forceinline__ bool find_item(const TrainDesc &d, int level, int shift, int index, int lane, Item &it)
 {
     if (level == 0) {
-        const int pieces = (int)(((int64_t)d.n_rows + (1ll << shift) - 1) >> shift);
         it = {0, -1, 0, 0, d.n_rows, index};
-        return index < (nodes ? 1 : pieces);
+        return index < (int)(((int64_t)d.n_rows + (1ll << shift) - 1) >> shift);
     }
     constexpr int kMost = (1 << (FS_TRAIN_MAX_DEPTH - 2)) / 64;   // parents per lane
     const int n_pairs = 1 << (level - 1);
@@ -652,8 +678,7 @@ __device__ __forceinline__ bool find_item(const TrainDesc &d, int level, int shi
         const int pair = lane * per + i;
         if (i < per && pair < n_pairs) {
             const int4 s = d.seg[n_pairs - 1 + pair];
-            const int pieces = (int)(((int64_t)min(s.x, s.y) + (1ll << shift) - 1) >> shift);
-            items[i] = nodes ? min(pieces, 1) : pieces;
+            items[i] = (int)(((int64_t)min(s.x, s.y) + (1ll << shift) - 1) >> shift);
         }
         sum += items[i];
     }
@@ -672,12 +697,7 @@ __device__ __forceinline__ bool find_item(const TrainDesc &d, int level, int shi
         rest -= items[i];
     }
     const int pair = __builtin_amdgcn_readlane(pick, owner);
-    const int4 s = d.seg[n_pairs - 1 + pair];
-    const int left = 2 * (n_pairs - 1 + pair) + 1;
-    if (s.x <= s.y)
-        it = {left, left + 1, pair, s.z, s.x, 0};
-    else
-        it = {left + 1, left, pair, s.z + s.x, s.y, 0};
+    it = counted_node(n_pairs - 1 + pair, pair, d.seg[n_pairs - 1 + pair]);
     it.piece = __builtin_amdgcn_readlane(piece, owner);
     return true;
 }
@@ -841,7 +861,7 @@ train_hist_kernel(const TrainDesc *__restrict__ descs, int level, int shift, int
     const TrainDesc &d = descs[blockIdx.z];
     Item it;
     if ((int)blockIdx.y * kHistFeats >= d.n_features ||
-        !find_item(d, level, shift, (int)blockIdx.x, false, threadIdx.x & 63, it))
+        !find_item(d, level, shift, (int)blockIdx.x, threadIdx.x & 63, it))
         return;
     if (is_packed(d, hb)) {
         hist_run<true>(d, lds, it, level, shift, blockIdx.y, 0, hb);
@@ -874,23 +894,24 @@ __device__ __forceinline__ void split_run(const TrainDesc &d, const Params &prm,
             one.load(part + j * stride, d.part_plane);
             own.add(one, false);
         }
-        own.store(lds + wave * kBins + 4 * lane, kSplitWaves * kBins);
+        own.store(lds + wave * kBins + 4 * lane, waves * kBins);
         __syncthreads();
-        if (wave >= children)
-            return;
         own = {};
         for (int j = 0; j < waves; ++j) {
             Bins4<PACKED> one;
-            one.load(lds + j * kBins + 4 * lane, kSplitWaves * kBins);
+            one.load(lds + j * kBins + 4 * lane, waves * kBins);
             own.add(one, false);
         }
+        __syncthreads();                                         // the sums' LDS is the search's scratch now
+        if (wave >= children)
+            return;
     } else {
         if (wave >= children)
             return;
         own.load(d.hist + hist_at(d, level, it, 0, f) + 4 * lane, d.hist_plane);
     }
     search_child<PACKED>(d, prm, level, it, wave, wave || pieces > 1, f, lane, own, hb,
-                         (unsigned char *)(lds + 2 * kSplitWaves * kBins) + wave * kBins * 8);
+                         (unsigned char *)(lds + wave * kBins));
     if (f == 0 && wave == 0 && lane == 0 && level > 0 && level + 1 < prm.max_depth)
         note_slots(d, level, it);
 }
@@ -898,12 +919,19 @@ __device__ __forceinline__ void split_run(const TrainDesc &d, const Params &prm,
 __global__ void __launch_bounds__(64 * kSplitWaves)
 train_split_kernel(const TrainDesc *__restrict__ descs, int level, int shift, int hb, Params prm)
 {
-    __shared__ __align__(16) unsigned long long lds[(2 * kSplitWaves + 2) * kBins];
+    extern __shared__ __align__(16) unsigned long long lds[];
     const TrainDesc &d = descs[blockIdx.z];
-    const int f = blockIdx.x;
-    Item it;
-    if (f >= d.n_features || !find_item(d, level, shift, (int)blockIdx.y, true, threadIdx.x & 63, it))
+    const int f = blockIdx.x, pair = blockIdx.y;
+    if (f >= d.n_features)
         return;
+    Item it = {0, -1, 0, 0, d.n_rows, 0};
+    if (level > 0) {
+        const int parent = (1 << (level - 1)) - 1 + pair;
+        const int4 s = d.seg[parent];
+        if (s.x == 0)                                            // not split
+            return;
+        it = counted_node(parent, pair, s);
+    }
     if (is_packed(d, hb))
         split_run<true>(d, prm, lds, it, level, shift, f, hb);
     else
@@ -920,35 +948,43 @@ static_assert(kMaxSlots <= kPickThreads, "one thread per node of the deepest lev
 constexpr int kPickSpreadSlots = 64;     // levels with at least this many nodes reduce in a kernel of their own
 
 // Best feature of node number `sl` of the level, by one wavefront (lanes over the features):
-// largest gain, lowest feature on ties.  No candidate: feature -1.
+// largest gain, lowest feature on ties.  `out` is written by the lane that holds it.
 __device__ __forceinline__ void wave_best_feature(const TrainDesc &d, int level, const Params &prm, int sl,
-                                                  int lane, int &bf, int &bc, double &bg)
+                                                  int lane, Winner *out)
 {
     const int n_slots = 1 << level;
-    bf = -1;
-    bc = 0;
-    bg = 0.0;
+    Winner mine = {0.0, 0, 0, -1, 0};
     if (level < prm.max_depth && d.h_state[n_slots - 1 + sl] == kOpen) {
-        for (int f = lane; f < d.n_features; f += 64) {          // ascending: first of equals stays
-            const Best &o = d.best[(int64_t)sl * d.n_features + f];
-            const int c = o.cut;
-            const double g = o.gain;                             // (not read as a gain where cut is 0)
-            if (c != 0 && (bf < 0 || g > bg)) {
-                bg = g;
-                bf = f;
-                bc = c;
-            }
-        }
-        for (int off = 32; off > 0; off >>= 1) {                 // largest gain, lowest feature on ties
-            const double og = __shfl_xor(bg, off);
-            const int of = __shfl_xor(bf, off), oc = __shfl_xor(bc, off);
-            if (of >= 0 && (bf < 0 || og > bg || (og == bg && of < bf))) {
-                bg = og;
-                bf = of;
-                bc = oc;
+        constexpr int kPerLane = 3;                              // loads at a time: this is a chain of latencies
+        for (int f0 = lane; f0 < d.n_features; f0 += 64 * kPerLane) {
+            Best o[kPerLane];
+#pragma unroll
+            for (int i = 0; i < kPerLane; ++i)
+                o[i] = d.best[(int64_t)sl * d.n_features + min(f0 + 64 * i, d.n_features - 1)];
+#pragma unroll
+            for (int i = 0; i < kPerLane; ++i) {                 // ascending: first of equals stays
+                const int f = f0 + 64 * i;
+                if (f < d.n_features && o[i].cut != 0 && (mine.feature < 0 || o[i].gain > mine.gain)) {
+                    mine.gain = o[i].gain;
+                    mine.GL = o[i].GL;
+                    mine.HL = o[i].HL;
+                    mine.feature = f;
+                    mine.cut = o[i].cut;
+                }
             }
         }
     }
+    double best = mine.gain;
+    int id = mine.feature + 1;                                   // as in the cut search: 0 = nothing
+    best_step<0x111, 0xf>(best, id);
+    best_step<0x112, 0xf>(best, id);
+    best_step<0x114, 0xf>(best, id);
+    best_step<0x118, 0xf>(best, id);
+    best_step<0x142, 0xa>(best, id);
+    best_step<0x143, 0xc>(best, id);
+    id = __builtin_amdgcn_readlane(id, 63);
+    if (id == 0 ? lane == 0 : mine.feature + 1 == id)
+        *out = mine;
 }
 
 // Levels with many nodes: the best feature of every node, one wavefront each, over the whole
@@ -957,18 +993,9 @@ __global__ void __launch_bounds__(kPickThreads)
 train_pick_reduce_kernel(const TrainDesc *__restrict__ descs, int level, Params prm)
 {
     const TrainDesc &d = descs[blockIdx.y];
-    const int lane = threadIdx.x & 63;
     const int sl = blockIdx.x * (kPickThreads / 64) + (threadIdx.x >> 6);
-    if (sl >= (1 << level))
-        return;
-    int bf, bc;
-    double bg;
-    wave_best_feature(d, level, prm, sl, lane, bf, bc, bg);
-    if (lane == 0) {
-        d.pk_feat[sl] = bf;
-        d.pk_cut[sl] = bc;
-        d.pk_gain[sl] = bg;
-    }
+    if (sl < (1 << level))
+        wave_best_feature(d, level, prm, sl, threadIdx.x & 63, &d.winner[sl]);
 }
 
 __device__ __forceinline__ float leaf_value(long long G, long long H, const Params &prm)
@@ -981,36 +1008,27 @@ __global__ void __launch_bounds__(kPickThreads)
 train_pick_kernel(const TrainDesc *__restrict__ descs, int level, int reduced, Params prm)
 {
     __shared__ int s_count[kPickThreads / 64];
-    __shared__ int s_bf[kMaxSlots], s_bc[kMaxSlots];
-    __shared__ double s_bg[kMaxSlots];
+    __shared__ Winner s_win[kPickSpreadSlots];
     const TrainDesc &d = descs[blockIdx.x];
     const int n_slots = 1 << level;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (reduced) {
-        if ((int)threadIdx.x < n_slots) {
-            s_bf[threadIdx.x] = d.pk_feat[threadIdx.x];
-            s_bc[threadIdx.x] = d.pk_cut[threadIdx.x];
-            s_bg[threadIdx.x] = d.pk_gain[threadIdx.x];
-        }
-    } else {
-        for (int sl = wave; sl < n_slots; sl += kPickThreads / 64) {
-            int bf, bc;
-            double bg;
-            wave_best_feature(d, level, prm, sl, lane, bf, bc, bg);
-            if (lane == 0) {
-                s_bf[sl] = bf;
-                s_bc[sl] = bc;
-                s_bg[sl] = bg;
-            }
-        }
-    }
-    __syncthreads();
     const int slot = threadIdx.x;
     const int node = n_slots - 1 + slot;
     const bool open = slot < n_slots && d.h_state[node] == kOpen;
-    const int bf = open ? s_bf[slot] : -1, bc = open ? s_bc[slot] : 0;
-    const double bg = open ? s_bg[slot] : 0.0;
-    const bool split = open && bf >= 0 && bg > prm.min_gain;
+    // (what the decision needs is loaded before the barrier)
+    const long long G = open ? d.h_G[node] : 0, H = open ? d.h_H[node] : 0;
+    const int4 up = open && level > 0 ? d.seg[(node - 1) >> 1] : make_int4(0, 0, 0, 0);
+    const int next_id = d.counters[0];
+    if (!reduced) {
+        for (int sl = wave; sl < n_slots; sl += kPickThreads / 64)
+            wave_best_feature(d, level, prm, sl, lane, &s_win[sl]);
+        __syncthreads();
+    }
+    Winner win = {0.0, 0, 0, -1, 0};
+    if (open)
+        win = reduced ? d.winner[slot] : s_win[slot];
+    const int bf = win.feature, bc = win.cut;
+    const bool split = open && bf >= 0 && win.gain > prm.min_gain;
     const unsigned long long votes = __ballot(split);
     if (lane == 0)
         s_count[wave] = __popcll(votes);
@@ -1020,13 +1038,11 @@ train_pick_kernel(const TrainDesc *__restrict__ descs, int level, int reduced, P
         before += w < wave ? s_count[w] : 0;
         total += s_count[w];
     }
-    const int next_id = d.counters[0];
     if (slot < n_slots) {
         int4 own = make_int4(0, 0, 0, 0);
         if (split) {
             own.w = d.n_rows;
             if (level > 0) {
-                const int4 up = d.seg[(node - 1) >> 1];
                 own.z = up.z + (node & 1 ? 0 : up.x);
                 own.w = node & 1 ? up.z + up.x : up.w;
             }
@@ -1036,15 +1052,11 @@ train_pick_kernel(const TrainDesc *__restrict__ descs, int level, int reduced, P
             d.decision[node] = make_int4(kAbsent, 0, 0, 0);
     }
     if (open) {
-        const long long G = d.h_G[node], H = d.h_H[node];
         if (split) {
-            const Best &o = d.best[(int64_t)slot * d.n_features + bf];
-            const long long GL = o.GL, HL = o.HL;
+            const long long GL = win.GL, HL = win.HL;
             const int lc = 2 * node + 1, rc = lc + 1;
             d.h_state[node] = kInternal;
             d.decision[node] = make_int4(kInternal, bf, bc, 0);
-            d.h_feat[node] = bf;
-            d.h_thr[node] = d.cuts[d.cut_off[bf] + bc - 1];
             const bool deepest = level + 1 == prm.max_depth;     // what is left becomes leaves
             d.h_state[lc] = deepest ? kLeaf : kOpen;
             d.h_state[rc] = deepest ? kLeaf : kOpen;
@@ -1056,6 +1068,8 @@ train_pick_kernel(const TrainDesc *__restrict__ descs, int level, int reduced, P
             d.h_H[lc] = HL;
             d.h_G[rc] = G - GL;
             d.h_H[rc] = H - HL;
+            d.h_own[lc] = parent_term(GL, HL, prm.inv_scale, prm.lambda);
+            d.h_own[rc] = parent_term(G - GL, H - HL, prm.inv_scale, prm.lambda);
             d.h_id[lc] = next_id + 2 * before;
             d.h_id[rc] = next_id + 2 * before + 1;
         } else {
@@ -1069,6 +1083,40 @@ train_pick_kernel(const TrainDesc *__restrict__ descs, int level, int reduced, P
         d.counters[0] = next_id + 2 * total;
 }
 
+// Heap -> flat arrays, appended to the model; then the heap is the next tree's (one workgroup).
+__device__ __forceinline__ void emit_tree(const TrainDesc &d)
+{
+    const int n_trees = d.counters[1], base = d.counters[2], n_new = d.counters[0];
+    for (int i = threadIdx.x; i < kHeapNodes; i += blockDim.x) {
+        const int st = d.h_state[i];
+        if (st != kInternal && st != kLeaf)
+            continue;
+        const int at = base + d.h_id[i];
+        if (st == kInternal) {
+            const int4 c = d.decision[i];
+            d.m_feat[at] = c.y;
+            d.m_thr[at] = d.cuts[d.cut_off[c.y] + c.z - 1];
+            d.m_left[at] = d.h_id[2 * i + 1];
+            d.m_right[at] = d.h_id[2 * i + 2];
+            d.m_val[at] = 0.0f;
+        } else {
+            d.m_feat[at] = -1;
+            d.m_thr[at] = 0.0f;
+            d.m_left[at] = -1;
+            d.m_right[at] = -1;
+            d.m_val[at] = d.h_val[i];
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        d.counters[1] = n_trees + 1;
+        d.counters[2] = base + n_new;
+        d.m_tree_off[n_trees + 1] = base + n_new;
+    }
+    __syncthreads();
+    begin_tree(d);
+}
+
 // Records of the nodes that were split move to their child's segment in the other buffer (the order
 // inside a segment is free: all sums over rows are integer sums); rows of leaves take the leaf's
 // value.  A record of an earlier level that was not overwritten since belongs to a node above the
@@ -1077,11 +1125,15 @@ train_pick_kernel(const TrainDesc *__restrict__ descs, int level, int reduced, P
 constexpr int kPartThreads = 1024;
 
 __global__ void __launch_bounds__(kPartThreads)
-train_part_kernel(const TrainDesc *__restrict__ descs, int level, int max_depth)
+train_part_kernel(const TrainDesc *__restrict__ descs, int level, int max_depth, int row_blocks)
 {
     __shared__ int s_left[kPartThreads / 64], s_right[kPartThreads / 64];
     __shared__ unsigned long long s_base;
     const TrainDesc &d = descs[blockIdx.y];
+    if ((int)blockIdx.x == row_blocks) {                         // last level only; clears nothing that the rows read
+        emit_tree(d);
+        return;
+    }
     const int64_t p = blockIdx.x * (int64_t)kPartThreads + threadIdx.x;
     if (blockIdx.x * (int64_t)kPartThreads >= d.n_rows)
         return;
@@ -1166,41 +1218,6 @@ train_part_kernel(const TrainDesc *__restrict__ descs, int level, int max_depth)
     }
 }
 
-// Heap -> flat arrays, appended to the model; then the heap is the next tree's.
-__global__ void __launch_bounds__(512)
-train_emit_kernel(const TrainDesc *__restrict__ descs)
-{
-    const TrainDesc &d = descs[blockIdx.x];
-    const int n_trees = d.counters[1], base = d.counters[2], n_new = d.counters[0];
-    for (int i = threadIdx.x; i < kHeapNodes; i += blockDim.x) {
-        const int st = d.h_state[i];
-        if (st != kInternal && st != kLeaf)
-            continue;
-        const int at = base + d.h_id[i];
-        if (st == kInternal) {
-            d.m_feat[at] = d.h_feat[i];
-            d.m_thr[at] = d.h_thr[i];
-            d.m_left[at] = d.h_id[2 * i + 1];
-            d.m_right[at] = d.h_id[2 * i + 2];
-            d.m_val[at] = 0.0f;
-        } else {
-            d.m_feat[at] = -1;
-            d.m_thr[at] = 0.0f;
-            d.m_left[at] = -1;
-            d.m_right[at] = -1;
-            d.m_val[at] = d.h_val[i];
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        d.counters[1] = n_trees + 1;
-        d.counters[2] = base + n_new;
-        d.m_tree_off[n_trees + 1] = base + n_new;
-    }
-    __syncthreads();
-    begin_tree(d);
-}
-
 }  // namespace fs
 
 // ---- host side ----------------------------------------------------------------------------
@@ -1213,7 +1230,7 @@ struct fs_trainer {
     int max_len;              // rows of the longest program
     void *own_work;           // its histograms where a batch's do not fit the shared buffer
     size_t own_work_bytes;
-    std::vector<void *> allocs;
+    void *memory;             // everything the descriptor points to
 };
 
 namespace fs {
@@ -1230,22 +1247,31 @@ struct BatchBuf {
 };
 static BatchBuf g_batch[16];
 
-template <class T>
-static int dev_alloc(fs_trainer *t, T **out, size_t count)
-{
-    void *p = nullptr;
-    hipError_t e = hipMalloc(&p, (count ? count : 1) * sizeof(T));
-    if (e != hipSuccess)
-        return e == hipErrorOutOfMemory ? fail(FS_ENOMEM, "hipMalloc of %zu bytes failed", count * sizeof(T))
-                                        : fail_hip(e, "hipMalloc");
-    if (t->allocs.size() == t->allocs.capacity()) {       // cannot happen with the reserve at creation
-        (void)hipFree(p);
-        return fail(FS_ENOMEM, "allocation table full");
+// The arrays of a trainer lie in one device allocation: noted first, placed when all are known.
+struct Arena {
+    struct Part { void **out; size_t at; };
+    Part part[48];
+    int n = 0;
+    size_t bytes = 0;
+    template <class T>
+    void add(T **out, size_t count)
+    {
+        part[n++] = {(void **)out, bytes};
+        bytes += ((count ? count : 1) * sizeof(T) + 255) & ~(size_t)255;
     }
-    t->allocs.push_back(p);
-    *out = (T *)p;
-    return FS_OK;
-}
+    int place(void **base)
+    {
+        const hipError_t e = hipMalloc(base, bytes);
+        if (e != hipSuccess) {
+            *base = nullptr;
+            return e == hipErrorOutOfMemory ? fail(FS_ENOMEM, "hipMalloc of %zu bytes failed", bytes)
+                                            : fail_hip(e, "hipMalloc");
+        }
+        for (int i = 0; i < n; ++i)
+            *part[i].out = (char *)*base + part[i].at;
+        return FS_OK;
+    }
+};
 
 static int check_launch(const char *what)
 {
@@ -1263,8 +1289,8 @@ extern "C" void fs_trainer_destroy(fs_trainer *t)
 {
     if (!t)
         return;
-    for (void *p : t->allocs)
-        (void)hipFree(p);
+    if (t->memory)
+        (void)hipFree(t->memory);
     if (t->own_work)
         (void)hipFree(t->own_work);
     delete t;
@@ -1310,12 +1336,6 @@ extern "C" int fs_trainer_create(fs_trainer **out, int32_t n_features, const flo
     fs_trainer *t = new (std::nothrow) fs_trainer();
     if (!t)
         return fail(FS_ENOMEM, "out of host memory");
-    try {
-        t->allocs.reserve(64);      // every later push_back stays within this (no throw past the C ABI)
-    } catch (const std::bad_alloc &) {
-        delete t;
-        return fail(FS_ENOMEM, "out of host memory");
-    }
     int rc = FS_OK;
     hipError_t e = hipGetDevice(&t->device);
     if (e != hipSuccess) {
@@ -1339,68 +1359,66 @@ extern "C" int fs_trainer_create(fs_trainer **out, int32_t n_features, const flo
     float *d_target = nullptr, *d_cuts = nullptr;
     int32_t *d_hot = nullptr;
     uint32_t *d_count = nullptr;
-#define TRY(x)            \
-    if (rc == FS_OK)      \
-    rc = (x)
-    TRY(dev_alloc(t, &bins, (size_t)h.r_pad * kHistFeats * (size_t)((n_features + kHistFeats - 1) / kHistFeats)));
-    TRY(dev_alloc(t, &d_prog_off, (size_t)n_programs + 1));
-    TRY(dev_alloc(t, &d_target, (size_t)n_programs));
-    TRY(dev_alloc(t, &d_cut_off, (size_t)n_features + 1));
-    TRY(dev_alloc(t, &d_cuts, (size_t)n_cuts));
-    TRY(dev_alloc(t, &d_hot, (size_t)n_features));
-    TRY(dev_alloc(t, &d_count, (size_t)n_features * kBins));
-    TRY(dev_alloc(t, &h.row_pred, (size_t)n_rows));
-    TRY(dev_alloc(t, &h.prog_pred, (size_t)n_programs));
-    TRY(dev_alloc(t, &h.rec[0], (size_t)n_rows));
-    TRY(dev_alloc(t, &h.rec[1], (size_t)n_rows));
-    TRY(dev_alloc(t, &h.seg, (size_t)kHeapNodes));
-    TRY(dev_alloc(t, &h.h_slot, (size_t)kHeapNodes));
-    TRY(dev_alloc(t, &h.h_state, (size_t)kHeapNodes));
-    TRY(dev_alloc(t, &h.h_feat, (size_t)kHeapNodes));
-    TRY(dev_alloc(t, &h.h_id, (size_t)kHeapNodes));
-    TRY(dev_alloc(t, &h.h_thr, (size_t)kHeapNodes));
-    TRY(dev_alloc(t, &h.h_val, (size_t)kHeapNodes));
-    TRY(dev_alloc(t, &h.h_G, (size_t)kHeapNodes));
-    TRY(dev_alloc(t, &h.h_H, (size_t)kHeapNodes));
-    TRY(dev_alloc(t, &h.best, (size_t)hist_slots * n_features));
-    TRY(dev_alloc(t, &h.decision, (size_t)kHeapNodes));
-    TRY(dev_alloc(t, &h.counters, (size_t)4));
-    TRY(dev_alloc(t, &h.abs_q, (size_t)1));
-    TRY(dev_alloc(t, &h.pk_feat, (size_t)kMaxSlots));
-    TRY(dev_alloc(t, &h.pk_cut, (size_t)kMaxSlots));
-    TRY(dev_alloc(t, &h.pk_gain, (size_t)kMaxSlots));
-    TRY(dev_alloc(t, &h.m_tree_off, (size_t)max_trees + 1));
-    TRY(dev_alloc(t, &h.m_feat, (size_t)node_cap));
-    TRY(dev_alloc(t, &h.m_left, (size_t)node_cap));
-    TRY(dev_alloc(t, &h.m_right, (size_t)node_cap));
-    TRY(dev_alloc(t, &h.m_thr, (size_t)node_cap));
-    TRY(dev_alloc(t, &h.m_val, (size_t)node_cap));
-#undef TRY
+    Arena arena;
+    arena.add(&bins, (size_t)h.r_pad * kHistFeats * (size_t)((n_features + kHistFeats - 1) / kHistFeats));
+    arena.add(&d_prog_off, (size_t)n_programs + 1);
+    arena.add(&d_target, (size_t)n_programs);
+    arena.add(&d_cut_off, (size_t)n_features + 1 + (size_t)n_cuts);   // the cuts lie behind
+    arena.add(&d_hot, (size_t)n_features);
+    arena.add(&d_count, (size_t)n_features * kBins);
+    arena.add(&h.row_pred, (size_t)n_rows);
+    arena.add(&h.prog_pred, (size_t)n_programs);
+    arena.add(&h.rec[0], (size_t)n_rows);
+    arena.add(&h.rec[1], (size_t)n_rows);
+    arena.add(&h.seg, (size_t)kHeapNodes);
+    arena.add(&h.h_slot, (size_t)kHeapNodes);
+    arena.add(&h.h_state, (size_t)kHeapNodes);
+    arena.add(&h.h_own, (size_t)kHeapNodes);
+    arena.add(&h.h_id, (size_t)kHeapNodes);
+    arena.add(&h.h_val, (size_t)kHeapNodes);
+    arena.add(&h.h_G, (size_t)kHeapNodes);
+    arena.add(&h.h_H, (size_t)kHeapNodes);
+    arena.add(&h.best, (size_t)hist_slots * n_features);
+    arena.add(&h.decision, (size_t)kHeapNodes);
+    arena.add(&h.counters, (size_t)4);
+    arena.add(&h.abs_q, (size_t)1);
+    arena.add(&h.winner, (size_t)kMaxSlots);
+    arena.add(&h.m_tree_off, (size_t)max_trees + 1);
+    arena.add(&h.m_feat, (size_t)node_cap);
+    arena.add(&h.m_left, (size_t)node_cap);
+    arena.add(&h.m_right, (size_t)node_cap);
+    arena.add(&h.m_thr, (size_t)node_cap);
+    arena.add(&h.m_val, (size_t)node_cap);
+    rc = arena.place(&t->memory);
     if (rc != FS_OK) {
         fs_trainer_destroy(t);
         return rc;
     }
+    d_cuts = (float *)(d_cut_off + n_features + 1);
     h.bins = bins;
     h.prog_off = d_prog_off;
     h.target = d_target;
     h.cut_off = d_cut_off;
     h.cuts = d_cuts;
     h.hot_bin = d_hot;
-    const int32_t zeros[4] = {0, 0, 0, 0};
     e = hipMemcpyAsync(d_prog_off, prog_off, sizeof(int32_t) * ((size_t)n_programs + 1),
                        hipMemcpyDeviceToDevice, stream);
     if (e == hipSuccess)
         e = hipMemcpyAsync(d_target, target, sizeof(float) * (size_t)n_programs,
                            hipMemcpyDeviceToDevice, stream);
-    // small host arrays: plain copies (these wait for the device)
-    if (e == hipSuccess)
-        e = hipMemcpy(d_cut_off, cut_off, sizeof(int32_t) * ((size_t)n_features + 1), hipMemcpyHostToDevice);
-    if (e == hipSuccess && n_cuts > 0)
-        e = hipMemcpy(d_cuts, cuts, sizeof(float) * (size_t)n_cuts, hipMemcpyHostToDevice);
-    if (e == hipSuccess)
-        e = hipMemcpy(h.counters, zeros, sizeof(zeros), hipMemcpyHostToDevice);
-    if (e == hipSuccess)
-        e = hipMemcpy(h.m_tree_off, zeros, sizeof(int32_t), hipMemcpyHostToDevice);
+    // the small host arrays in one plain copy (it waits for the device)
+    if (e == hipSuccess) {
+        const size_t head = (size_t)n_features + 1;
+        std::unique_ptr<int32_t[]> both(new (std::nothrow) int32_t[head + (size_t)n_cuts]);
+        if (!both) {
+            fs_trainer_destroy(t);
+            return fail(FS_ENOMEM, "out of host memory");
+        }
+        memcpy(both.get(), cut_off, sizeof(int32_t) * head);
+        if (n_cuts > 0)
+            memcpy(both.get() + head, cuts, sizeof(float) * (size_t)n_cuts);
+        e = hipMemcpy(d_cut_off, both.get(), sizeof(int32_t) * (head + (size_t)n_cuts), hipMemcpyHostToDevice);
+    }
     if (e != hipSuccess) {
         fs_trainer_destroy(t);
         return fail_hip(e, "fs_trainer_create: copies");
@@ -1410,8 +1428,8 @@ extern "C" int fs_trainer_create(fs_trainer **out, int32_t n_features, const flo
                        (const int32_t *)d_cut_off, (const float *)d_cuts, bins);
     rc = check_launch("train_bin_kernel launch");
     if (rc == FS_OK) {
-        hipLaunchKernelGGL(train_fill_kernel, dim3(64), dim3(256), 0, stream, (float *)d_count,
-                           (int64_t)n_features * kBins, 0.0f);
+        hipLaunchKernelGGL(train_clear_kernel, dim3(64), dim3(256), 0, stream, d_count, n_features * kBins,
+                           h.counters, h.m_tree_off);
         hipLaunchKernelGGL(train_count_kernel,
                            dim3((unsigned)((n_rows + kCountRows - 1) / kCountRows),
                                 (unsigned)((n_features + kHistFeats - 1) / kHistFeats)),
@@ -1678,9 +1696,10 @@ extern "C" int fs_train_boost(int32_t n_trainers, fs_trainer *const *trainers, i
                                    stream, d, level, shift, hb);
                 prof_stop(stream);
                 prof_start(kKernTrainSplit, stream);
-                hipLaunchKernelGGL(train_split_kernel, dim3((unsigned)max_feat, (unsigned)std::min(std::max<int64_t>(1, rows), n_counted), nt),
-                                   dim3(64 * (n_counted <= 4 ? kSplitWaves : 2)), 0, stream, d, level, shift, hb,
-                                   prm);
+                const unsigned waves = n_counted <= 4 ? kSplitWaves : 2;
+                hipLaunchKernelGGL(train_split_kernel, dim3((unsigned)max_feat, (unsigned)n_counted, nt),
+                                   dim3(64 * waves), 2 * waves * kBins * 8,
+                                   stream, d, level, shift, hb, prm);
             } else {
                 prof_start(kKernTrainSplit, stream);
             }
@@ -1694,13 +1713,12 @@ extern "C" int fs_train_boost(int32_t n_trainers, fs_trainer *const *trainers, i
                                prm);
             prof_stop(stream);
             prof_start(kKernTrainOther, stream);
-            hipLaunchKernelGGL(train_part_kernel, dim3((unsigned)((max_rows + (int64_t)kPartThreads - 1) / kPartThreads), nt),
-                               dim3(kPartThreads), 0, stream, d, level, prm.max_depth);
+            const int row_blocks = (int)((max_rows + (int64_t)kPartThreads - 1) / kPartThreads);
+            const int last = level + 1 >= prm.max_depth ? 1 : 0;   // one more workgroup puts the tree into the model
+            hipLaunchKernelGGL(train_part_kernel, dim3((unsigned)(row_blocks + last), nt), dim3(kPartThreads), 0,
+                               stream, d, level, prm.max_depth, row_blocks);
             prof_stop(stream);
         }
-        prof_start(kKernTrainOther, stream);
-        hipLaunchKernelGGL(train_emit_kernel, dim3(nt), dim3(512), 0, stream, d);
-        prof_stop(stream);
         rc = check_launch("training kernels launch");
         if (rc != FS_OK)
             return rc;
