@@ -808,9 +808,6 @@ __device__ __forceinline__ void hist_run(const TrainDesc &d, unsigned long long 
     auto bins = FS_GLOBAL(const words, d.bins + (int64_t)group * d.r_pad * kHistFeats + base);
     // (the records of a group are read in order, its bins gathered: the loads of the next step are
     // issued before the atomics of this one)
-    // An add that does not count goes to the lane's own word behind the histograms, without a branch:
-    // the hot bin would otherwise take a third of a wavefront's adds, one after the other.
-    const int trash = kHistWords + (threadIdx.x & 63);
     int i = threadIdx.x;
     if (i < n) {
         i32x4 r = recs[i];
@@ -826,12 +823,10 @@ __device__ __forceinline__ void hist_run(const TrainDesc &d, unsigned long long 
                 if ((k & 3) == 0 && k >= nf)
                     break;
                 const int b = (w[k >> 2] >> (8 * (k & 3))) & 255;
-                const int at = (b == hot[k] ? trash - k * kBins : b) + k * kBins;
-                if (PACKED) {
-                    atomicAdd(&lds[at], both);
-                } else {
-                    atomicAdd(&lds[at], (unsigned long long)(long long)r.y);
-                    atomicAdd(&lds[at + (b == hot[k] ? 0 : kHistWords / 2)], (unsigned long long)r.z);
+                if (b != hot[k]) {
+                    atomicAdd(&lds[k * kBins + b], PACKED ? both : (unsigned long long)(long long)r.y);
+                    if (!PACKED)
+                        atomicAdd(&lds[kHistWords / 2 + k * kBins + b], (unsigned long long)r.z);
                 }
             }
             r = r_next;
@@ -857,7 +852,7 @@ __device__ __forceinline__ void hist_run(const TrainDesc &d, unsigned long long 
 __global__ void __launch_bounds__(kHistThreads)
 train_hist_kernel(const TrainDesc *__restrict__ descs, int level, int shift, int hb)
 {
-    __shared__ __align__(16) unsigned long long lds[kHistWords + 64];
+    __shared__ __align__(16) unsigned long long lds[kHistWords];
     const TrainDesc &d = descs[blockIdx.z];
     Item it;
     if ((int)blockIdx.y * kHistFeats >= d.n_features ||
@@ -916,7 +911,7 @@ __device__ __forceinline__ void split_run(const TrainDesc &d, const Params &prm,
         note_slots(d, level, it);
 }
 
-__global__ void __launch_bounds__(64 * kSplitWaves)
+__global__ void __launch_bounds__(64 * kSplitWaves, 6)
 train_split_kernel(const TrainDesc *__restrict__ descs, int level, int shift, int hb, Params prm)
 {
     extern __shared__ __align__(16) unsigned long long lds[];
