@@ -60,8 +60,10 @@ struct Winner {
 };
 
 struct TrainDesc {
-    const uint8_t *bins;       // [feature / 16][r_pad][16]: a row's bins of sixteen consecutive
-                               // features are one 16-byte load
+    const uint8_t *bins;       // [row][row_bytes]: what a histogram workgroup gathers.  A row's features lie
+                               // together so that the sixteen-byte pieces of all feature groups, taken by
+                               // workgroups of one XCD, are a line or two of its L2 and not one line each
+    const uint8_t *cols;       // [feature][r_pad]: the same by feature, for moving rows to a child
     const int32_t *prog_off;
     const float *target;
     const int32_t *cut_off;    // device copies of the cut lists
@@ -91,6 +93,7 @@ struct TrainDesc {
     int32_t *m_tree_off, *m_feat, *m_left, *m_right;
     float *m_thr, *m_val;
     int64_t r_pad;
+    int32_t row_bytes;
     int32_t n_features, n_rows, n_programs;
     float bias;
 };
@@ -104,22 +107,42 @@ struct Params {
 
 // ---- set-up kernels ----------------------------------------------------------------------
 
+// Workgroups go to the eight XCDs in turn: takes the workgroups of piece i of a launch, one per
+// feature group, to one XCD, one after the other, so that they share its L2.  `turn` (a trainer's number)
+// moves the first piece to another XCD: families of five pieces would leave three XCDs idle.
+__device__ __forceinline__ void xcd_piece(unsigned w, unsigned groups, unsigned turn, int &piece, int &group)
+{
+    const unsigned k = w >> 3, q = k / groups;
+    group = (int)(k - q * groups);
+    piece = (int)(q * 8 + ((w + 5 * turn) & 7));
+}
+
+static unsigned xcd_grid(int64_t pieces, unsigned groups)
+{
+    return (unsigned)((pieces + 7) / 8 * 8) * groups;
+}
+
 // bin = number of cuts <= x; NaN takes the last bin.  A workgroup takes 256 rows of sixteen features,
 // whose cut lists fit LDS together, so that a row's sixteen bins leave in one store.
 __global__ void __launch_bounds__(256)
 train_bin_kernel(const float *__restrict__ x, int layout, int n_features, int n_rows,
                  int64_t r_pad, const int32_t *__restrict__ cut_off,
-                 const float *__restrict__ cuts, uint8_t *__restrict__ bins)
+                 const float *__restrict__ cuts, uint8_t *__restrict__ bins, int row_bytes,
+                 uint8_t *__restrict__ cols)
 {
     __shared__ float c[kHistFeats][kBins];
-    const int f0 = blockIdx.y * kHistFeats;
+    int block, group;
+    xcd_piece(blockIdx.x, (n_features + kHistFeats - 1) / kHistFeats, 0, block, group);
+    if (block * (int64_t)blockDim.x >= n_rows)
+        return;
+    const int f0 = group * kHistFeats;
     const int nf = min(kHistFeats, n_features - f0);
     for (int i = threadIdx.x; i < kHistWords; i += blockDim.x) {
         const int f = min(f0 + i / kBins, n_features - 1), j = i % kBins;
         c[i / kBins][j] = j < cut_off[f + 1] - cut_off[f] ? cuts[cut_off[f] + j] : __builtin_inff();
     }
     __syncthreads();
-    const int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    const int64_t r = block * (int64_t)blockDim.x + threadIdx.x;
     if (r >= n_rows)
         return;
     uint32_t w[kHistFeats / 4] = {};
@@ -134,37 +157,40 @@ train_bin_kernel(const float *__restrict__ x, int layout, int n_features, int n_
             if (c[k][lo + step - 1] <= v)
                 lo += step;
         lo = v != v ? m : min(lo, m);            // (+inf passes the padding too)
-        w[k >> 2] |= (uint32_t)(k < nf ? lo : 0) << (8 * (k & 3));
+        if (k < nf) {
+            w[k >> 2] |= (uint32_t)lo << (8 * (k & 3));
+            cols[f * r_pad + r] = (uint8_t)lo;
+        }
     }
-    ((uint4 *)bins)[(int64_t)blockIdx.y * r_pad + r] = make_uint4(w[0], w[1], w[2], w[3]);
+    *(uint4 *)(bins + r * row_bytes + f0) = make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-// Rows per (feature, bin): 1024 rows of sixteen features per workgroup, counted in LDS.
-constexpr int kCountRows = 1024;
+// Rows per (feature, bin): 8192 rows of a feature per workgroup, counted in LDS by each wavefront for itself.
+constexpr int kCountRows = 8192;
 
-__global__ void __launch_bounds__(512)
-train_count_kernel(const uint8_t *__restrict__ bins, int n_features, int n_rows, int64_t r_pad,
-                   uint32_t *__restrict__ count)
+__global__ void __launch_bounds__(256)
+train_count_kernel(const uint8_t *__restrict__ cols, int n_rows, int64_t r_pad, uint32_t *__restrict__ count)
 {
-    __shared__ uint32_t cnt[kHistWords];
-    const int f0 = blockIdx.y * kHistFeats;
-    const int nf = min(kHistFeats, n_features - f0);
-    for (int i = threadIdx.x; i < kHistWords; i += blockDim.x)
-        cnt[i] = 0u;
+    __shared__ uint32_t cnt[4][kBins];
+    const int t = threadIdx.x, f = blockIdx.y;
+    for (int w = 0; w < 4; ++w)
+        cnt[w][t] = 0u;
     __syncthreads();
     const int64_t first = blockIdx.x * (int64_t)kCountRows;
     const int n = (int)min((int64_t)kCountRows, n_rows - first);
-    for (int i = threadIdx.x; i < n; i += blockDim.x) {
-        const uint4 v = ((const uint4 *)bins)[(int64_t)blockIdx.y * r_pad + first + i];
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+    const uint32_t *words = (const uint32_t *)(cols + f * r_pad + first);   // r_pad and first are multiples of 256
+#pragma unroll 4
+    for (int i = 4 * t; i < n; i += 4 * 256) {
+        const uint32_t v = words[i >> 2];
 #pragma unroll
-        for (int k = 0; k < kHistFeats; ++k)
-            atomicAdd(&cnt[k * kBins + ((w[k >> 2] >> (8 * (k & 3))) & 255)], 1u);
+        for (int k = 0; k < 4; ++k)
+            if (i + k < n)
+                atomicAdd(&cnt[t >> 6][(v >> (8 * k)) & 255], 1u);
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < nf * kBins; i += blockDim.x)
-        if (cnt[i] != 0u)
-            atomicAdd(&count[f0 * kBins + i], cnt[i]);
+    const uint32_t all = cnt[0][t] + cnt[1][t] + cnt[2][t] + cnt[3][t];
+    if (all != 0u)
+        atomicAdd(&count[f * kBins + t], all);
 }
 
 // The most frequent bin of every feature over the whole training set (lowest on ties).
@@ -805,16 +831,18 @@ __device__ __forceinline__ void hist_run(const TrainDesc &d, unsigned long long 
     const int n = min(it.count - (int)((int64_t)it.piece << shift), 1 << shift);
     auto recs = FS_GLOBAL(const i32x4, d.rec[level & 1] + it.first + ((int64_t)it.piece << shift));
     typedef uint32_t words __attribute__((ext_vector_type(NW)));
-    auto bins = FS_GLOBAL(const words, d.bins + (int64_t)group * d.r_pad * kHistFeats + base);
+    auto bins = FS_GLOBAL(const uint8_t, d.bins + f0);
+    const int64_t row_bytes = d.row_bytes;
+    typedef __attribute__((address_space(1))) const words *words_at;
     // (the records of a group are read in order, its bins gathered: the loads of the next step are
     // issued before the atomics of this one)
     int i = threadIdx.x;
     if (i < n) {
         i32x4 r = recs[i];
-        words w = bins[(int64_t)r.x * (PACKED ? 1 : 2)];
+        words w = *(words_at)(bins + r.x * row_bytes);
         i32x4 r_next = recs[min(i + kHistThreads, n - 1)];
         for (; i < n; i += kHistThreads) {
-            const words w_next = bins[(int64_t)r_next.x * (PACKED ? 1 : 2)];
+            const words w_next = *(words_at)(bins + r_next.x * row_bytes);
             const i32x4 r_after = recs[min(i + 2 * kHistThreads, n - 1)];
             const unsigned long long both =
                 (unsigned long long)((long long)r.y * ((long long)1 << hb) + (long long)r.z);
@@ -848,22 +876,23 @@ __device__ __forceinline__ void hist_run(const TrainDesc &d, unsigned long long 
     __syncthreads();                                             // LDS may be reused by the next run
 }
 
-// blockIdx = (item, feature group, trainer)
+// blockIdx = (item and feature group, -, trainer)
 __global__ void __launch_bounds__(kHistThreads)
-train_hist_kernel(const TrainDesc *__restrict__ descs, int level, int shift, int hb)
+train_hist_kernel(const TrainDesc *__restrict__ descs, int level, int shift, int hb, int groups)
 {
     __shared__ __align__(16) unsigned long long lds[kHistWords];
     const TrainDesc &d = descs[blockIdx.z];
     Item it;
-    if ((int)blockIdx.y * kHistFeats >= d.n_features ||
-        !find_item(d, level, shift, (int)blockIdx.x, threadIdx.x & 63, it))
+    int item, group;
+    xcd_piece(blockIdx.x, groups, blockIdx.z, item, group);
+    if (group * kHistFeats >= d.n_features || !find_item(d, level, shift, item, threadIdx.x & 63, it))
         return;
     if (is_packed(d, hb)) {
-        hist_run<true>(d, lds, it, level, shift, blockIdx.y, 0, hb);
+        hist_run<true>(d, lds, it, level, shift, group, 0, hb);
     } else {
-        hist_run<false>(d, lds, it, level, shift, blockIdx.y, 0, 0);
-        if ((int)blockIdx.y * kHistFeats + kHistFeats / 2 < d.n_features)
-            hist_run<false>(d, lds, it, level, shift, blockIdx.y, kHistFeats / 2, 0);
+        hist_run<false>(d, lds, it, level, shift, group, 0, 0);
+        if (group * kHistFeats + kHistFeats / 2 < d.n_features)
+            hist_run<false>(d, lds, it, level, shift, group, kHistFeats / 2, 0);
     }
 }
 
@@ -1146,7 +1175,7 @@ train_part_kernel(const TrainDesc *__restrict__ descs, int level, int max_depth,
     bool left = false;
     if (state == kInternal) {
         const int f = todo_of.y;
-        const int b = d.bins[((int64_t)(f / kHistFeats) * d.r_pad + r.x) * kHistFeats + f % kHistFeats];
+        const int b = d.cols[f * d.r_pad + r.x];
         left = b < todo_of.z;
         if (level + 1 == max_depth) {
             const float v = d.h_val[2 * r.w + (left ? 1 : 2)];
@@ -1349,13 +1378,17 @@ extern "C" int fs_trainer_create(fs_trainer **out, int32_t n_features, const flo
     const int n_cuts = cut_off[n_features];
     const int hist_slots = max_depth > 0 ? 1 << (max_depth - 1) : 1;
     const int64_t node_cap = (int64_t)max_trees * ((1 << (max_depth + 1)) - 1);
-    uint8_t *bins = nullptr;
+    uint8_t *bins = nullptr, *cols = nullptr;
     int32_t *d_prog_off = nullptr, *d_cut_off = nullptr;
     float *d_target = nullptr, *d_cuts = nullptr;
     int32_t *d_hot = nullptr;
     uint32_t *d_count = nullptr;
     Arena arena;
-    arena.add(&bins, (size_t)h.r_pad * kHistFeats * (size_t)((n_features + kHistFeats - 1) / kHistFeats));
+    // whole pieces of a row, and of a 64-byte sector from four pieces on
+    h.row_bytes = (n_features + kHistFeats - 1) / kHistFeats * kHistFeats;
+    h.row_bytes = h.row_bytes > 2 * kHistFeats ? (h.row_bytes + 63) & ~63 : h.row_bytes;
+    arena.add(&bins, (size_t)n_rows * (size_t)h.row_bytes);
+    arena.add(&cols, (size_t)h.r_pad * (size_t)n_features);
     arena.add(&d_prog_off, (size_t)n_programs + 1);
     arena.add(&d_target, (size_t)n_programs);
     arena.add(&d_cut_off, (size_t)n_features + 1 + (size_t)n_cuts);   // the cuts lie behind
@@ -1391,6 +1424,7 @@ extern "C" int fs_trainer_create(fs_trainer **out, int32_t n_features, const flo
     }
     d_cuts = (float *)(d_cut_off + n_features + 1);
     h.bins = bins;
+    h.cols = cols;
     h.prog_off = d_prog_off;
     h.target = d_target;
     h.cut_off = d_cut_off;
@@ -1418,17 +1452,17 @@ extern "C" int fs_trainer_create(fs_trainer **out, int32_t n_features, const flo
         fs_trainer_destroy(t);
         return fail_hip(e, "fs_trainer_create: copies");
     }
-    hipLaunchKernelGGL(train_bin_kernel, dim3((unsigned)((n_rows + 255) / 256), (unsigned)((n_features + kHistFeats - 1) / kHistFeats)),
+    hipLaunchKernelGGL(train_bin_kernel,
+                       dim3(xcd_grid((n_rows + 255) / 256, (unsigned)((n_features + kHistFeats - 1) / kHistFeats))),
                        dim3(256), 0, stream, features, layout, n_features, (int)n_rows, h.r_pad,
-                       (const int32_t *)d_cut_off, (const float *)d_cuts, bins);
+                       (const int32_t *)d_cut_off, (const float *)d_cuts, bins, h.row_bytes, cols);
     rc = check_launch("train_bin_kernel launch");
     if (rc == FS_OK) {
         hipLaunchKernelGGL(train_clear_kernel, dim3(64), dim3(256), 0, stream, d_count, n_features * kBins,
                            h.counters, h.m_tree_off);
         hipLaunchKernelGGL(train_count_kernel,
-                           dim3((unsigned)((n_rows + kCountRows - 1) / kCountRows),
-                                (unsigned)((n_features + kHistFeats - 1) / kHistFeats)),
-                           dim3(512), 0, stream, (const uint8_t *)bins, n_features, (int)n_rows, h.r_pad, d_count);
+                           dim3((unsigned)((n_rows + kCountRows - 1) / kCountRows), (unsigned)n_features), dim3(256),
+                           0, stream, (const uint8_t *)cols, (int)n_rows, h.r_pad, d_count);
         hipLaunchKernelGGL(train_hot_bin_kernel, dim3((unsigned)n_features), dim3(kBins), 0, stream,
                            (const uint32_t *)d_count, d_hot);
         hipLaunchKernelGGL(train_fill_kernel, dim3(1024), dim3(256), 0, stream, h.row_pred,
@@ -1687,8 +1721,8 @@ extern "C" int fs_train_boost(int32_t n_trainers, fs_trainer *const *trainers, i
                 const int64_t rows = level ? max_rows / 2 : max_rows, n_counted = level ? n_slots / 2 : 1;
                 const int64_t items = std::max<int64_t>(1, std::min(rows, (rows >> shift) + n_counted));
                 prof_start(kKernTrainHist, stream);
-                hipLaunchKernelGGL(train_hist_kernel, dim3((unsigned)items, groups, nt), dim3(kHistThreads), 0,
-                                   stream, d, level, shift, hb);
+                hipLaunchKernelGGL(train_hist_kernel, dim3(xcd_grid(items, groups), 1u, nt), dim3(kHistThreads), 0,
+                                   stream, d, level, shift, hb, (int)groups);
                 prof_stop(stream);
                 prof_start(kKernTrainSplit, stream);
                 const unsigned waves = n_counted <= 4 ? kSplitWaves : 2;
