@@ -283,8 +283,8 @@ enum {
     FS_TUNE_RANK = 2,             /* 0: never rank-code a model, 1: whenever its trees allow        */
     FS_TUNE_RANK_TILES = 3,       /* 1, 2, 3, 4 or 6: tiles per workgroup of the rank traversal     */
     FS_TUNE_VERBOSE = 4,          /* 1: fs_model_create reports its plan on stderr                  */
-    FS_TUNE_TRAIN_SLAB_ROWS = 5,  /* 64..65536: rows per histogram slab                             */
-    FS_TUNE_TRAIN_SORT = 6,       /* 0: never regroup rows by node, 1: whenever possible            */
+    FS_TUNE_TRAIN_SLAB_ROWS = 5,  /* 64..65536: rows per histogram workgroup, up to a power of two  */
+    FS_TUNE_TRAIN_SORT = 6,       /* accepted, no effect: rows are always grouped by node           */
     FS_TUNE_TRAIN_PACKED = 7,     /* 0: separate 64-bit gradient / curvature sums only              */
     FS_TUNE_LDS_GROUPS = 8,       /* 1..16: tile groups a workgroup of the LDS traversal takes in a
                                      row (automatic: 1..4 by the length of the launch)             */
