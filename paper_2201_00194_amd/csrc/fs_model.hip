@@ -570,12 +570,12 @@ extern "C" int fs_model_create(fs_model **out, int32_t n_features, int32_t n_tre
             const int want = tune(FS_TUNE_TREELET);
             if (want != 0 && (want == 1 || (!others && n_trees >= kTreeletMinTrees)))
                 m->tl_ok = build_treelets(n_features, n_trees, tree_off, split_feature, threshold, left, right,
-                                          value, want == 1, &tl);
+                                          value, want == 1, want != 1 && n_features <= 255, &tl);
             // What the LDS kernel takes for a tile: about 13.5 clocks per level it walks and 3 per feature
             // of the tile (measured on ensembles of 40 to 400 trees).  Models whose chunks do not fit half
             // a compute unit's LDS only take treelets where there is no other LDS form.
             if (m->tl_ok && want != 1 && n_features <= 255 &&
-                (!tl.pair_ok || tl.cost > 13.5 * (double)n_trees * (double)max_depth + 3.0 * (double)n_features))
+                (tl.cost > 13.5 * (double)n_trees * (double)max_depth + 3.0 * (double)n_features))
                 m->tl_ok = false;
             m->tl_pair = tl.pair_ok;
             m->tl_cols = tl.most_cols;

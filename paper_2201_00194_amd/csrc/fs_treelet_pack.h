@@ -27,10 +27,10 @@ struct TreeletPlan {
 
 // False if the model does not fit the format (more columns than a byte names, a node graph that
 // is not a tree, trees too large for a chunk -- or, unless `any_size`, so large that the other forms are
-// as good).
+// as good; or with `pair_only`, where no two workgroups fit a compute unit).
 bool build_treelets(int n_features, int n_trees, const int32_t *tree_off, const int32_t *sf,
                     const float *thr, const int32_t *left, const int32_t *right, const float *val,
-                    bool any_size, TreeletPlan *out);
+                    bool any_size, bool pair_only, TreeletPlan *out);
 
 }  // namespace fs
 #endif

@@ -241,7 +241,7 @@ bool segment_cuts(int n_features, int32_t node0, int32_t node1, const int32_t *s
 
 bool build_treelets(int n_features, int n_trees, const int32_t *tree_off, const int32_t *sf,
                     const float *thr, const int32_t *left, const int32_t *right, const float *val,
-                    bool any_size, TreeletPlan *out)
+                    bool any_size, bool pair_only, TreeletPlan *out)
 {
     if (n_trees < 1)
         return false;
@@ -315,40 +315,7 @@ bool build_treelets(int n_features, int n_trees, const int32_t *tree_off, const 
     for (const SegmentCuts &c : seg_cuts)
         out->most_cols = std::max(out->most_cols, (int)c.pieces.size());
 
-    // ---- columns ----
-    // Buckets of every column: five or more per threshold, so that a bucket of evenly spread thresholds
-    // holds three at most (two bisection steps), with few exceptions; less where the tables of the
-    // wavefronts would not fit beside the columns.
-    const long beside = (long)out->most_cols * 256;
-    auto kb = [](long bytes) { return (bytes + 1023) / 1024 * 1024; };
-    // (the coder's layouts in fs_treelet.hip: a double-buffered table for each of 8 wavefronts; four
-    // tables for each of 12)
-    auto pair_fits = [&](int stride) { return 16 * kb(stride) <= (long)kTreeletLds - kTreeletSumBytes - beside; };
-    auto spread_fits = [&](int stride) { return 12 * kb(4 * stride) <= (long)kTreeletLdsWhole - beside; };
-    bool pair_coder = true;
-    for (size_t i = 0; i < out->segments.size();) {
-        TreeletSegmentPlan *sp = &out->segments[i];
-        int most_cuts = 0, want = 64;
-        for (const Piece &pc : seg_cuts[i].pieces)
-            most_cuts = std::max(most_cuts, pc.n);
-        while (want < 5 * most_cuts && want < 1024)
-            want *= 2;
-        bool fits = false;
-        for (int B = want; B >= 64 && !fits; B /= 2) {
-            build_columns(seg_cuts[i].pieces, seg_cuts[i].cuts, seg_cuts[i].cut_at, B, sp);
-            fits = spread_fits(sp->table_stride) && (pair_fits(sp->table_stride) || !pair_coder);
-        }
-        if (fits) {
-            ++i;
-        } else if (pair_coder) {                     // give the two-per-compute-unit form up and start over
-            pair_coder = false;
-            i = 0;
-        } else {
-            return false;
-        }
-    }
-
-    // ---- chunks ----
+    // ---- bounds of the chunks ----
     // Bounds of the chunks of trees [t0, t1) in buffers of `buf` bytes.  Two wavefronts take a chunk's
     // halves in rounds of kTreeletRound: full rounds if the trees fit, else eights, else fours.
     auto plan = [&](int t0, int t1, size_t buf, std::vector<int> *bounds) -> bool {
@@ -377,9 +344,54 @@ bool build_treelets(int n_features, int n_trees, const int32_t *tree_off, const 
                 return false;
         return true;
     };
+    // (before the columns' tables, which are most of what is left to do: a model that would be turned down
+    // for this costs its sort of the thresholds and no more)
     std::vector<std::vector<int>> all;
     const long room = (long)kTreeletLds - kTreeletSumBytes - (long)out->most_cols * 256;
-    out->pair_ok = pair_coder && plan_all(std::min((size_t)room / 1024 * 1024, (size_t)kTreeletPairBuf), &all);
+    out->pair_ok = plan_all(std::min((size_t)room / 1024 * 1024, (size_t)kTreeletPairBuf), &all);
+    if (pair_only && !out->pair_ok)
+        return false;
+
+    // ---- columns ----
+    // Buckets of every column: five or more per threshold, so that a bucket of evenly spread thresholds
+    // holds three at most (two bisection steps), with few exceptions; less where the tables of the
+    // wavefronts would not fit beside the columns.
+    const long beside = (long)out->most_cols * 256;
+    auto kb = [](long bytes) { return (bytes + 1023) / 1024 * 1024; };
+    // (the coder's layouts in fs_treelet.hip: a double-buffered table for each of 8 wavefronts; four
+    // tables for each of 12)
+    auto pair_fits = [&](int stride) { return 16 * kb(stride) <= (long)kTreeletLds - kTreeletSumBytes - beside; };
+    auto spread_fits = [&](int stride) { return 12 * kb(4 * stride) <= (long)kTreeletLdsWhole - beside; };
+    bool pair_coder = true;
+    for (size_t i = 0; i < out->segments.size();) {
+        TreeletSegmentPlan *sp = &out->segments[i];
+        int most_cuts = 0, want = 64;
+        for (const Piece &pc : seg_cuts[i].pieces)
+            most_cuts = std::max(most_cuts, pc.n);
+        while (want < 5 * most_cuts && want < 1024)
+            want *= 2;
+        bool fits = false;
+        for (int B = want; B >= 64 && !fits; B /= 2) {
+            const int least = B + 4 * ((most_cuts + 1 + 3) / 4 * 4);   // of what build_columns makes the stride
+            if (!spread_fits(least) || (pair_coder && !pair_fits(least)))
+                continue;
+            build_columns(seg_cuts[i].pieces, seg_cuts[i].cuts, seg_cuts[i].cut_at, B, sp);
+            fits = spread_fits(sp->table_stride) && (pair_fits(sp->table_stride) || !pair_coder);
+        }
+        if (fits) {
+            ++i;
+        } else if (pair_only) {
+            return false;
+        } else if (pair_coder) {                     // give the two-per-compute-unit form up and start over
+            pair_coder = false;
+            i = 0;
+        } else {
+            return false;
+        }
+    }
+
+    // ---- chunks ----
+    out->pair_ok = out->pair_ok && pair_coder;
     if (!out->pair_ok && !plan_all(kTreeletWholeBuf, &all))
         return false;
     size_t largest = 0;
