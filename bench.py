@@ -203,10 +203,11 @@ def train_main(args, np, torch, api, W):
     wall_ms = (time.perf_counter() - w0) * 1e3
     prof = api.fs_profile_end()
     ms_per_step = e0.elapsed_time(e1) / args.steps
-    # dominant kernel: the histogram build.  Algorithmic bytes per launch (one level): every
-    # bin once (1 B per row and feature) plus gradient, curvature and node of every row once.
+    # dominant kernel: the histogram build.  Algorithmic bytes per launch (one level): the bins of every
+    # row counted (1 B per row and feature) and its record of 16 B; all rows at the root, at most
+    # half of them (the smaller children's) on the levels below.
     hist_ms, hist_n = prof["train_hist"]
-    alg_bytes = n_rows * (n_feat + 10)
+    alg_bytes = n_rows * (n_feat + 16) * (args.depth + 1) / (2 * max(1, args.depth))
     hist_avg = hist_ms / max(1, hist_n)
     achieved = alg_bytes / (hist_avg * 1e-3) / 1e9 if hist_avg > 0 else 0.0
     out = {
