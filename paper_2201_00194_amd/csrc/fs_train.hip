@@ -1267,8 +1267,7 @@ struct fs_trainer {
     int max_depth, max_trees;
     int trees_enqueued;
     int max_len;              // rows of the longest program
-    void *own_work;           // its histograms where a batch's do not fit the shared buffer
-    size_t own_work_bytes;
+    bool counted;             // among the device's trainers
     void *memory;             // everything the descriptor points to
 };
 
@@ -1279,12 +1278,30 @@ struct BatchBuf {
     TrainDesc *d_desc = nullptr;
     TrainDesc *h_desc = nullptr;   // pinned
     int cap = 0;
-    void *work = nullptr;          // histograms of the batch in work, at most kKeptWork bytes
+    void *work = nullptr;          // histograms of the batch in work
     size_t work_bytes = 0;
+    int trainers = 0;              // alive; without any `work` is kept up to kKeptWork
     hipEvent_t copied = nullptr;
     bool pending = false;
 };
 static BatchBuf g_batch[16];
+
+// The histograms' buffer stays between the trainers of one tuning step and the next up to this size:
+// mapping and freeing it for every retraining took 0.7 to 1.3 ms of 6.5 to 17 (what a batch needs beyond
+// goes with the device's last trainer, all of it where device memory runs out for a new one).
+constexpr size_t kKeptWork = (size_t)512 << 20;
+
+// Frees the histograms' buffer of a device without trainers (g_train_mu held).
+static bool give_back(int dev)
+{
+    BatchBuf &b = g_batch[dev];
+    if (b.trainers != 0 || !b.work)
+        return false;
+    (void)hipFree(b.work);
+    b.work = nullptr;
+    b.work_bytes = 0;
+    return true;
+}
 
 // The arrays of a trainer lie in one device allocation: noted first, placed when all are known.
 struct Arena {
@@ -1303,6 +1320,7 @@ struct Arena {
         const hipError_t e = hipMalloc(base, bytes);
         if (e != hipSuccess) {
             *base = nullptr;
+            (void)hipGetLastError();                             // not the next launch's error
             return e == hipErrorOutOfMemory ? fail(FS_ENOMEM, "hipMalloc of %zu bytes failed", bytes)
                                             : fail_hip(e, "hipMalloc");
         }
@@ -1330,8 +1348,11 @@ extern "C" void fs_trainer_destroy(fs_trainer *t)
         return;
     if (t->memory)
         (void)hipFree(t->memory);
-    if (t->own_work)
-        (void)hipFree(t->own_work);
+    if (t->counted) {
+        std::lock_guard<std::mutex> lock(g_train_mu);
+        if (--g_batch[t->device].trainers == 0 && g_batch[t->device].work_bytes > kKeptWork)
+            give_back(t->device);
+    }
     delete t;
 }
 
@@ -1433,6 +1454,13 @@ extern "C" int fs_trainer_create(fs_trainer **out, int32_t n_features, const flo
     arena.add(&h.m_thr, (size_t)node_cap);
     arena.add(&h.m_val, (size_t)node_cap);
     rc = arena.place(&t->memory);
+    if (rc == FS_ENOMEM && t->device < 16) {
+        std::unique_lock<std::mutex> lock(g_train_mu);
+        const bool freed = give_back(t->device);
+        lock.unlock();
+        if (freed)
+            rc = arena.place(&t->memory);
+    }
     if (rc != FS_OK) {
         fs_trainer_destroy(t);
         return rc;
@@ -1501,74 +1529,61 @@ extern "C" int fs_trainer_create(fs_trainer **out, int32_t n_features, const flo
         fs_trainer_destroy(t);
         return rc;
     }
+    if (t->device < 16) {
+        std::lock_guard<std::mutex> lock(g_train_mu);
+        ++g_batch[t->device].trainers;
+        t->counted = true;
+    }
     *out = t;
     return FS_OK;
 }
 
 // Histograms live for one fs_train_boost only, and training calls on one device are ordered by the
-// caller, as its descriptors need already: all trainers share a buffer of the device.  It is kept between
-// calls (mapping and clearing 20 MB of fresh memory per trainer took 0.7 ms, a twentieth of a job's
-// retraining) up to this size; a batch that needs more has buffers of its trainers' own, freed with them.
-constexpr size_t kKeptWork = (size_t)512 << 20;
+// caller, as its descriptors need already: all trainers share a buffer of the device (fresh memory of
+// 20 MB for each of eight trainers took 5 ms of a job's retraining).  A batch that needs more than this is trained in parts, one after the other.
+constexpr size_t kMostWork = (size_t)16 << 30;
 
-// Replaces a buffer by a larger one; earlier batches may still be at work in it.
-static int grow(void **buf, size_t *have, size_t need)
+// Bytes for the histograms that trees of `depth` levels keep and for the parts of nodes of several items.
+static size_t hist_bytes(const fs_trainer *t, int depth, int shift, size_t *hist, size_t *part)
 {
-    if (need <= *have)
-        return FS_OK;
-    FS_HIP(hipDeviceSynchronize());
-    if (*buf)
-        (void)hipFree(*buf);
-    *buf = nullptr;
-    *have = 0;
-    const hipError_t e = hipMalloc(buf, need);
-    if (e != hipSuccess) {
-        *buf = nullptr;
-        return e == hipErrorOutOfMemory ? fail(FS_ENOMEM, "hipMalloc of %zu bytes failed", need)
-                                        : fail_hip(e, "hipMalloc");
-    }
-    *have = need;
-    return FS_OK;
+    const size_t row = (size_t)t->h.n_features * kBins;
+    const int64_t rows = t->h.n_rows;
+    *hist = (depth > 0 ? (size_t)1 << (depth - 1) : 1) * row;
+    *part = rows >> shift ? ((size_t)((2 * rows) >> shift) + 1) * row : 0;
+    return (*hist + *part) * 2 * sizeof(unsigned long long);
 }
 
-// Gives every trainer room for the histograms that trees of `depth` levels keep and for the parts of
-// its nodes of several items.
-static int place_hist(int n, fs_trainer *const *trainers, int depth, int shift)
+// Gives every trainer its place in the device's buffer, which grows to `all` bytes.
+static int place_hist(int n, fs_trainer *const *trainers, int depth, int shift, size_t all)
 {
-    auto words = [&](const fs_trainer *t, size_t *hist, size_t *part) {
-        const size_t row = (size_t)t->h.n_features * kBins;
-        const int64_t rows = t->h.n_rows;
-        *hist = (depth > 0 ? (size_t)1 << (depth - 1) : 1) * row;
-        *part = rows >> shift ? ((size_t)((2 * rows) >> shift) + 1) * row : 0;
-        return (*hist + *part) * 2 * sizeof(unsigned long long);
-    };
-    size_t all = 0, hist, part;
-    for (int i = 0; i < n; ++i)
-        all += words(trainers[i], &hist, &part);
     int dev = 0;
     FS_HIP(hipGetDevice(&dev));
     if (dev < 0 || dev >= 16)
         return fail(FS_EUNSUPPORTED, "device ordinal %d not supported", dev);
-    const bool shared = all <= kKeptWork;
-    if (shared) {
-        const int rc = grow(&g_batch[dev].work, &g_batch[dev].work_bytes, all);
-        if (rc != FS_OK)
-            return rc;
-    }
-    char *at = (char *)g_batch[dev].work;
-    for (int i = 0; i < n; ++i) {
-        fs_trainer *t = trainers[i];
-        const size_t bytes = words(t, &hist, &part);
-        if (!shared) {
-            const int rc = grow(&t->own_work, &t->own_work_bytes, bytes);
-            if (rc != FS_OK)
-                return rc;
-            at = (char *)t->own_work;
+    BatchBuf &b = g_batch[dev];
+    if (b.work_bytes < all) {
+        FS_HIP(hipDeviceSynchronize());                          // earlier batches may still be at work in it
+        if (b.work)
+            (void)hipFree(b.work);
+        b.work_bytes = 0;
+        const hipError_t e = hipMalloc(&b.work, all);
+        if (e != hipSuccess) {
+            b.work = nullptr;
+            (void)hipGetLastError();
+            return e == hipErrorOutOfMemory ? fail(FS_ENOMEM, "hipMalloc of %zu bytes failed", all)
+                                            : fail_hip(e, "hipMalloc");
         }
-        t->h.hist = (unsigned long long *)at;
-        t->h.hist_plane = (int64_t)hist;
-        t->h.part = t->h.hist + 2 * hist;
-        t->h.part_plane = (int64_t)part;
+        b.work_bytes = all;
+    }
+    char *at = (char *)b.work;
+    for (int i = 0; i < n; ++i) {
+        TrainDesc &h = trainers[i]->h;
+        size_t hist, part;
+        const size_t bytes = hist_bytes(trainers[i], depth, shift, &hist, &part);
+        h.hist = (unsigned long long *)at;
+        h.hist_plane = (int64_t)hist;
+        h.part = h.hist + 2 * hist;
+        h.part_plane = (int64_t)part;
         at += bytes;
     }
     return FS_OK;
@@ -1682,7 +1697,6 @@ extern "C" int fs_train_boost(int32_t n_trainers, fs_trainer *const *trainers, i
         if (t->h.n_features > max_feat) max_feat = t->h.n_features;
         if (t->max_len > max_len) max_len = t->max_len;
     }
-    std::lock_guard<std::mutex> lock(g_train_mu);
     // A histogram workgroup takes up to 2^shift rows of a node: 48 to 96 pieces of all the batch's rows
     // at the root, which with ten feature groups are two to four workgroups per compute unit.
     int shift = kChunkShiftMin;
@@ -1694,7 +1708,16 @@ extern "C" int fs_train_boost(int32_t n_trainers, fs_trainer *const *trainers, i
             for (shift = 6; (1 << shift) < v;)
                 ++shift;
     }
-    rc = place_hist(n_trainers, trainers, p->max_depth, shift);
+    size_t work = 0, hist = 0, part = 0;
+    for (int i = 0; i < n_trainers; ++i)
+        work += hist_bytes(trainers[i], p->max_depth, shift, &hist, &part);
+    if (work > kMostWork && n_trainers > 1) {                    // (all trainers were found good above)
+        rc = fs_train_boost(n_trainers / 2, trainers, n_rounds, p, stream_);
+        return rc != FS_OK ? rc
+                           : fs_train_boost(n_trainers - n_trainers / 2, trainers + n_trainers / 2, n_rounds, p, stream_);
+    }
+    std::lock_guard<std::mutex> lock(g_train_mu);
+    rc = place_hist(n_trainers, trainers, p->max_depth, shift, work);
     if (rc != FS_OK)
         return rc;
     const TrainDesc *d = nullptr;
