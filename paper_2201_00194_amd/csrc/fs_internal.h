@@ -91,7 +91,6 @@ constexpr int kPrefetchRegs = 6;        // 16-byte registers per thread for the 
 struct fs_model {
     int32_t n_features;
     int32_t n_trees;
-    int32_t max_depth;     // longest root-to-leaf path (in splits) over all trees
     int64_t n_nodes;
     float bias;
     int device;

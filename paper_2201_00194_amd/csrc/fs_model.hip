@@ -1,10 +1,12 @@
 // fs_model_create / fs_model_destroy: validation of the caller's ensemble and packing into
 // the two device formats (flat global-memory nodes; LDS-staged chunk images).
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <new>
+#include <utility>
 #include <vector>
 
 #include "fs_internal.h"
@@ -14,129 +16,68 @@ using namespace fs;
 
 namespace {
 
-struct PackedTree {
-    std::vector<uint32_t> words;     // tree image; child offsets relative to the tree start
-    std::vector<uint16_t> slot_ids;  // caller's local id per 4-byte slot
-    std::vector<uint32_t> fix;       // word indices whose low 16 bits need + tree base
-    int depth = 0;
+// What the LDS-staged format needs to know of a tree before its nodes are written.
+struct TreeSize {
+    int32_t nodes;                   // on the paths from the root
+    int32_t bytes;
+    int32_t depth;
 };
 
-// Breadth-first relabelling that puts the two children of a node next to each other.
-// Returns false if the node graph is not a tree (a shared child), or if compact is asked for
-// and the tree is not perfect of `depth`.
-bool pack_tree(const int32_t *sf, const float *thr, const int32_t *left, const int32_t *right,
-               const float *val, int32_t sz, int n_features, bool compact, int depth,
-               PackedTree *out)
+// Size of a tree whose nodes share children: every path to a node counts.  False if it has more nodes
+// than the caller's array, as it may unfold without bound.
+bool unfolded_size(const int32_t *sf, const int32_t *left, const int32_t *right, int32_t sz, TreeSize *out)
 {
-    std::vector<int32_t> order;
-    std::vector<int32_t> level;
-    order.push_back(0);
-    level.push_back(0);
-    int max_level = 0;
-    for (size_t i = 0; i < order.size(); ++i) {
-        const int32_t n = order[i];
-        if (sf[n] >= 0) {
-            order.push_back(left[n]);
-            level.push_back(level[i] + 1);
-            order.push_back(right[n]);
-            level.push_back(level[i] + 1);
-            if (level[i] + 1 > max_level)
-                max_level = level[i] + 1;
-            if (order.size() > (size_t)sz)
-                return false;   // some node has two parents: not a tree, would unfold without bound
-        }
-    }
-    out->depth = max_level;
-    const size_t n = order.size();
-    // position of the first child of order[i] in `order`: children are appended in visit order
-    std::vector<uint32_t> first_child(n, 0);
-    {
-        uint32_t next = 1;
-        for (size_t i = 0; i < n; ++i)
-            if (sf[order[i]] >= 0) {
-                first_child[i] = next;
-                next += 2;
-            }
-    }
-    const uint32_t nan_col = (uint32_t)n_features * 256u;
-    if (!compact) {
-        out->words.assign(2 * n, 0);
-        out->slot_ids.assign(2 * n, 0);
-        for (size_t i = 0; i < n; ++i) {
-            const int32_t o = order[i];
-            uint32_t w0, w1;
-            if (sf[o] >= 0) {
-                memcpy(&w0, &thr[o], 4);
-                w1 = (((uint32_t)sf[o] * 256u) << 16) | (8u * first_child[i]);
-            } else {
-                memcpy(&w0, &val[o], 4);
-                // own offset - 8; the tree base is at least 8, so this never underflows
-                w1 = (nan_col << 16) | ((8u * (uint32_t)i - 8u) & 0xFFFFu);
-            }
-            out->words[2 * i] = w0;
-            out->words[2 * i + 1] = w1;
-            out->fix.push_back((uint32_t)(2 * i + 1));
-            out->slot_ids[2 * i] = (uint16_t)o;
-            out->slot_ids[2 * i + 1] = (uint16_t)o;
-        }
-        return true;
-    }
-    // compact: internal nodes first (8 bytes), then leaves (4 bytes), both in visit order
-    const size_t n_int = ((size_t)1 << depth) - 1, n_leaf = (size_t)1 << depth;
-    if (n != n_int + n_leaf)
-        return false;
-    for (size_t i = 0; i < n; ++i)
-        if ((sf[order[i]] >= 0) != (i < n_int) || level[i] != (i < n_int ? level[i] : depth))
+    std::vector<std::pair<int32_t, int32_t>> todo(1, {0, 0});    // node, level; breadth first
+    out->depth = 0;
+    for (size_t i = 0; i < todo.size(); ++i) {
+        const int32_t n = todo[i].first, level = todo[i].second;
+        if (sf[n] < 0)
+            continue;
+        todo.push_back({left[n], level + 1});
+        todo.push_back({right[n], level + 1});
+        out->depth = std::max(out->depth, level + 1);
+        if (todo.size() > (size_t)sz)
             return false;
-    out->words.assign(2 * n_int + n_leaf, 0);
-    out->slot_ids.assign(2 * n_int + n_leaf, 0);
-    for (size_t i = 0; i < n_int; ++i) {
-        const int32_t o = order[i];
-        uint32_t w0;
-        memcpy(&w0, &thr[o], 4);
-        const uint32_t c = first_child[i];
-        const uint32_t child_off = (c < n_int) ? 8u * c : (uint32_t)(8u * n_int + 4u * (c - n_int));
-        out->words[2 * i] = w0;
-        out->words[2 * i + 1] = (((uint32_t)sf[o] * 256u) << 16) | child_off;
-        out->fix.push_back((uint32_t)(2 * i + 1));
-        out->slot_ids[2 * i] = out->slot_ids[2 * i + 1] = (uint16_t)o;
     }
-    for (size_t j = 0; j < n_leaf; ++j) {
-        const int32_t o = order[n_int + j];
-        memcpy(&out->words[2 * n_int + j], &val[o], 4);
-        out->slot_ids[2 * n_int + j] = (uint16_t)o;
-    }
+    out->nodes = (int32_t)todo.size();
     return true;
 }
 
-// Depth of every leaf equal to `*depth` (set from the first leaf) and the tree perfect?
-bool tree_is_perfect(const int32_t *sf, const int32_t *left, const int32_t *right, int32_t sz,
-                     int *depth)
+// A tree of the LDS-staged format at byte `base` of a chunk image, breadth first, so that the two children of
+// a node are next to each other; `ids` = the caller's local id per 4-byte slot of the chunk.  In compact
+// chunks the splits (8 bytes) come first, then the leaves (4 bytes); the tree is perfect, so breadth
+// first has them in that order.  `order`: room for the tree's nodes.
+void write_tree(const int32_t *sf, const float *thr, const int32_t *left, const int32_t *right,
+                const float *val, const TreeSize &ts, int n_features, bool compact, uint32_t base,
+                uint8_t *image, uint16_t *ids, int32_t *order)
 {
-    std::vector<int32_t> lev((size_t)sz, -1);
-    lev[0] = 0;
-    int64_t reach = 0;
-    int d = -1;
-    for (int32_t n = 0; n < sz; ++n) {       // children have larger ids: one forward pass
-        if (lev[n] < 0)
-            continue;
-        ++reach;
-        if (sf[n] >= 0) {
-            if (lev[left[n]] >= 0 || lev[right[n]] >= 0 || left[n] == right[n])
-                return false;                // shared child: not a tree
-            lev[left[n]] = lev[right[n]] = lev[n] + 1;
+    const uint32_t n = (uint32_t)ts.nodes, n_int = compact ? n / 2 : n;
+    const uint32_t nan_col = (uint32_t)n_features * 256u;
+    uint32_t *words = (uint32_t *)(image + base);
+    uint16_t *slots = ids + base / 4;
+    uint32_t next = 1;                               // position of the next split's left child
+    order[0] = 0;
+    for (uint32_t i = 0; i < n; ++i) {
+        const int32_t o = order[i];
+        const uint16_t id = (uint16_t)o;
+        if (sf[o] >= 0) {
+            order[next] = left[o];
+            order[next + 1] = right[o];
+            const uint32_t child = next < n_int ? 8u * next : 8u * n_int + 4u * (next - n_int);
+            next += 2;
+            memcpy(&words[2 * i], &thr[o], 4);
+            words[2 * i + 1] = (((uint32_t)sf[o] * 256u) << 16) | ((child + base) & 0xFFFFu);
+            slots[2 * i] = slots[2 * i + 1] = id;
+        } else if (compact) {
+            memcpy(&words[n_int + i], &val[o], 4);
+            slots[n_int + i] = id;
         } else {
-            if (d < 0)
-                d = lev[n];
-            else if (d != lev[n])
-                return false;
+            memcpy(&words[2 * i], &val[o], 4);
+            // own offset - 8; the tree base is at least 8, so this never underflows
+            words[2 * i + 1] = (nan_col << 16) | ((8u * i - 8u + base) & 0xFFFFu);
+            slots[2 * i] = slots[2 * i + 1] = id;
         }
     }
-    if (d < 1 || d > 14 || reach != ((int64_t)2 << d) - 1)
-        return false;
-    if (*depth < 0)
-        *depth = d;
-    return *depth == d;
 }
 
 // Largest chunk image: node offsets are 16 bits, and the kernel stages the next chunk in
@@ -305,6 +246,213 @@ size_t chunk_image_limit(int mode)
 {
     const size_t by_regs = (size_t)kLdsModeWaves[mode] * 64 * kPrefetchRegs * 16;
     return by_regs < (size_t)kMaxChunkBytes ? by_regs : (size_t)kMaxChunkBytes;
+}
+
+// ---- LDS-staged format: which trees go into which chunk --------------------------------------------
+struct LdsPlan {
+    int mode = 0, tiles = 0;
+    bool compact = false;
+    std::vector<TreeSize> trees;
+    std::vector<int> bounds;         // chunk i holds trees [bounds[i], bounds[i + 1])
+    std::vector<SlotPlan> slots;     // per chunk
+    float group_us = 0.0f;           // one tile group, estimated
+};
+
+// False if the model does not fit the format.
+bool plan_lds(int n_features, int n_trees, const TreeShapes &shapes, const int32_t *tree_off, const int32_t *sf,
+              const int32_t *left, const int32_t *right, LdsPlan *out)
+{
+    const int tile_bytes = (n_features + 1) * 256;
+    const bool compact = shapes.perfect_depth() >= 0;
+    out->compact = compact;
+    out->trees.resize((size_t)n_trees);
+    size_t max_tree = 0, sum_tree = 0;
+    for (int t = 0; t < n_trees; ++t) {
+        TreeSize &ts = out->trees[(size_t)t];
+        const TreeShapes::Tree &shape = shapes.trees[(size_t)t];
+        ts = {shape.n_split + shape.n_leaf, 0, shape.depth};
+        const int32_t o = tree_off[t];
+        if (!shape.tree && !unfolded_size(sf + o, left + o, right + o, tree_off[t + 1] - o, &ts))
+            return false;
+        ts.bytes = compact ? 8 * shape.n_split + 4 * shape.n_leaf : 8 * ts.nodes;
+        max_tree = std::max(max_tree, (size_t)ts.bytes);
+        sum_tree += (size_t)ts.bytes;
+    }
+    const size_t avg_tree = sum_tree / (size_t)n_trees;
+    // Pick the workgroup shape and the number of row tiles per workgroup.  More tiles
+    // mean fewer passes of the model through LDS, but less room for trees; what hides
+    // LDS latency is the number of independent walks in flight (tiles x trees
+    // resident), so that comes first.  The small shape is taken when it still gets 8
+    // or more trees into a chunk.
+    int best_t = 0, best_score = -1, best_mode = 0;
+    size_t best_avail = 0;
+    const int forced_tiles = tune(FS_TUNE_LDS_TILES), forced_mode = tune(FS_TUNE_LDS_MODE);
+    for (int mode = kLdsModes - 1; mode >= 0 && best_t == 0; --mode) {
+        // The half-LDS shape (two workgroups per compute unit) measured no faster on
+        // any workload and doubles the model traffic from L2: tuning aid only.
+        if (mode == 0 && forced_mode != 1)
+            continue;
+        if (forced_mode >= 1 && forced_mode <= kLdsModes && mode != forced_mode - 1)
+            continue;
+        const int max_tiles = mode == 0 ? 1 : kLdsMaxTiles;
+        for (int nt = max_tiles; nt >= 1; --nt) {
+            if (mode == 1 && forced_tiles >= 1 && forced_tiles <= kLdsMaxTiles && nt != forced_tiles)
+                continue;
+            const long avail = (long)kLdsModeBytes[mode] - (long)nt * tile_bytes - 64;
+            const size_t per_tree_val = (size_t)nt * 256;
+            const size_t per_tree_tab = 4;   // a tree word of a run record
+            const size_t head = (size_t)(kLdsMaxWaves + 12) * kRunBytes + 16;   // records + padding
+            if (avail < (long)(max_tree + head + per_tree_val))
+                continue;
+            const size_t max_img = chunk_image_limit(mode);
+            if (max_img < max_tree + head)
+                continue;
+            size_t by_chunk = (max_img - head) / (avg_tree + per_tree_tab);
+            size_t by_avail = ((size_t)avail - head) / (avg_tree + per_tree_tab + per_tree_val);
+            size_t per = by_chunk < by_avail ? by_chunk : by_avail;
+            if (per < 1) per = 1;
+            if (per > (size_t)kMaxChunkTrees) per = kMaxChunkTrees;
+            if (mode == 0 && per < 8 && forced_mode != 1)
+                continue;
+            int score = nt * (int)per;
+            if (score > 64) score = 64;   // measured: beyond ~5 trees per wavefront more
+                                          // tiles win, below it more trees per chunk do
+            if (score > best_score) {
+                best_score = score;
+                best_t = nt;
+                best_mode = mode;
+                best_avail = (size_t)avail;
+            }
+        }
+    }
+    if (best_t == 0)
+        return false;
+    if (tune(FS_TUNE_VERBOSE) > 0)
+        fprintf(stderr, "fs_model_create: mode=%d tiles=%d avail=%zu avg_tree=%zu max_tree=%zu compact=%d\n",
+                best_mode, best_t, best_avail, avg_tree, max_tree, (int)compact);
+    const size_t per_tree_val = (size_t)best_t * 256;
+    out->tiles = best_t;
+    out->mode = best_mode;
+    // Trees per chunk: estimated from the average tree, then balanced over the
+    // wavefronts that share a tile (chunk_tree_target); a chunk ends early if its
+    // trees are larger than average and the next one does not fit.
+    const int share = kLdsModeWaves[best_mode] / best_t;
+    const size_t img_limit = chunk_image_limit(best_mode);
+    std::vector<int> tdepth((size_t)n_trees);
+    for (int t = 0; t < n_trees; ++t)
+        tdepth[(size_t)t] = out->trees[(size_t)t].depth;
+    // (every tree may need a run record of its own on top of the slots' first records)
+    const size_t head0 = (size_t)kLdsMaxWaves * kRunBytes + 16;
+    size_t est_per = (best_avail - head0) / (avg_tree + kRunBytes + per_tree_val);
+    const size_t est_img = (img_limit - head0) / (avg_tree + kRunBytes);
+    if (est_per > est_img) est_per = est_img;
+    if (est_per > (size_t)kMaxChunkTrees) est_per = kMaxChunkTrees;
+    if (est_per < 1) est_per = 1;
+    const int even_cap = chunk_tree_target(n_trees, (int)est_per, share);
+    out->bounds.assign(1, 0);
+    for (int t = 0; t < n_trees;) {
+        int cnt = 0;
+        size_t body = 0;
+        while (t + cnt < n_trees && cnt < kMaxChunkTrees && cnt < even_cap) {
+            const size_t bt = (size_t)out->trees[(size_t)(t + cnt)].bytes;
+            // run records in front of the nodes: at most one per slot and one per tree
+            const size_t img = ((size_t)(kLdsMaxWaves + cnt + 1) * kRunBytes + body + bt + 15) & ~(size_t)15;
+            if (img > img_limit || img + (size_t)(cnt + 1) * per_tree_val > best_avail)
+                break;
+            body += bt;
+            ++cnt;
+        }
+        t += cnt;                                 // cnt >= 1 by the choice of best_t
+        out->bounds.push_back(t);
+    }
+    out->slots.resize(out->bounds.size() - 1);
+    std::vector<int> by_depth;
+    for (size_t ci = 0; ci + 1 < out->bounds.size(); ++ci) {
+        const int t = out->bounds[ci], cnt = out->bounds[ci + 1] - t;
+        by_depth.resize((size_t)cnt);
+        for (int j = 0; j < cnt; ++j)
+            by_depth[(size_t)j] = j;
+        std::stable_sort(by_depth.begin(), by_depth.end(), [&](int x, int y) {
+            return tdepth[(size_t)(t + x)] > tdepth[(size_t)(t + y)];
+        });
+        deal_trees(by_depth, tdepth.data() + t, share, &out->slots[ci]);
+        // (the plan's cost is in units of about 1.5 us: 12.1 for 18 us a group of 200 trees of depth 8)
+        out->group_us += 1.5f * (float)out->slots[ci].cost;
+    }
+    return true;
+}
+
+void write_lds(const LdsPlan &plan, int n_features, const int32_t *tree_off, const int32_t *sf, const float *thr,
+               const int32_t *left, const int32_t *right, const float *val, std::vector<uint8_t> *image,
+               std::vector<ChunkHdr> *chunks, std::vector<uint16_t> *slot_ids)
+{
+    const int share = kLdsModeWaves[plan.mode] / plan.tiles;
+    size_t most_nodes = 0;
+    for (const TreeSize &ts : plan.trees)
+        most_nodes = std::max(most_nodes, (size_t)ts.nodes);
+    std::vector<int32_t> order(most_nodes);
+    std::vector<int> rec_of;                             // record index of every run
+    std::vector<uint32_t> root_at;
+    // the images' sizes, so that they are allocated once
+    std::vector<size_t> table(plan.slots.size());
+    size_t total = 0;
+    for (size_t ci = 0; ci < plan.slots.size(); ++ci) {
+        const SlotPlan &sp = plan.slots[ci];
+        size_t n_rec = kLdsMaxWaves;                     // one per slot first (its first run, or an empty one), then the rest
+        for (int b = 0; b < share; ++b)
+            if (sp.slot_start[b + 1] > sp.slot_start[b])
+                n_rec += (size_t)(sp.slot_start[b + 1] - sp.slot_start[b] - 1);
+        table[ci] = (n_rec * kRunBytes + 7) & ~(size_t)7;
+        size_t body = 0;
+        for (int t = plan.bounds[ci]; t < plan.bounds[ci + 1]; ++t)
+            body += (size_t)plan.trees[(size_t)t].bytes;
+        ChunkHdr h;
+        memset(&h, 0, sizeof(h));
+        h.byte_off = (uint32_t)total;
+        h.bytes = (uint32_t)((table[ci] + body + 15) & ~(size_t)15);
+        h.n_trees = (uint32_t)(plan.bounds[ci + 1] - plan.bounds[ci]);
+        h.first_tree = (uint32_t)plan.bounds[ci];
+        h.slot_off = (uint32_t)(total / 4);
+        chunks->push_back(h);
+        total += h.bytes;
+    }
+    image->assign(total, 0);
+    slot_ids->assign(total / 4, 0);
+    for (size_t ci = 0; ci < plan.slots.size(); ++ci) {
+        const SlotPlan &sp = plan.slots[ci];
+        ChunkHdr &h = (*chunks)[ci];
+        uint8_t *img = image->data() + h.byte_off;
+        uint16_t *ids = slot_ids->data() + h.slot_off;
+        size_t pos = table[ci];
+        root_at.resize(h.n_trees);
+        for (uint32_t j = 0; j < h.n_trees; ++j) {
+            const size_t t = h.first_tree + j;
+            const TreeSize &ts = plan.trees[t];
+            const int32_t o = tree_off[t];
+            root_at[j] = (uint32_t)pos;
+            write_tree(sf + o, thr + o, left + o, right + o, val + o, ts, n_features, plan.compact, (uint32_t)pos, img,
+                       ids, order.data());
+            pos += (size_t)ts.bytes;
+            h.depth = std::max(h.depth, (uint32_t)ts.depth);
+        }
+        rec_of.assign(sp.runs.size(), -1);
+        int n_rec = kLdsMaxWaves;
+        for (int b = 0; b < share; ++b)
+            for (int r = sp.slot_start[b]; r < sp.slot_start[b + 1]; ++r)
+                rec_of[(size_t)r] = r == sp.slot_start[b] ? b : n_rec++;
+        for (int b = 0; b < share; ++b)
+            for (int r = sp.slot_start[b]; r < sp.slot_start[b + 1]; ++r) {
+                const RunPlan &rp = sp.runs[(size_t)r];
+                const int next = r + 1 < sp.slot_start[b + 1] ? rec_of[(size_t)(r + 1)] + 1 : 0;
+                uint32_t rec[kRunWords];
+                rec[0] = (uint32_t)rp.count | ((uint32_t)next << 4) | ((uint32_t)rp.depth << 16);
+                for (int k = 0; k < 8; ++k) {
+                    const int j = sp.order[(size_t)(rp.first + (k < rp.count ? k : 0))];
+                    rec[1 + k] = root_at[(size_t)j] | ((uint32_t)j << 16);
+                }
+                memcpy(img + (size_t)rec_of[(size_t)r] * kRunBytes, rec, sizeof(rec));
+            }
+    }
 }
 
 // Rank-coded image of a model of perfect trees of one depth (see fs_rank.hip): per feature the
@@ -526,30 +674,50 @@ extern "C" int fs_model_create(fs_model **out, int32_t n_features, int32_t n_tre
         return fail(FS_EINVAL, "fs_model_create: a node array is NULL");
 
     try {
-        // ---- validation ----
-        std::vector<int32_t> depth((size_t)n_nodes, 0);
-        int32_t max_depth = 0;
-        for (int t = 0; t < n_trees; ++t) {
-            const int32_t o = tree_off[t];
-            const int32_t sz = tree_off[t + 1] - o;
-            for (int32_t n = 0; n < sz; ++n) {
-                const int32_t g = o + n;
-                if (split_feature[g] >= 0) {
-                    if (split_feature[g] >= n_features)
-                        return fail(FS_EINVAL, "fs_model_create: tree %d node %d splits on feature "
-                                    "%d but the model has %d", t, n, split_feature[g], n_features);
-                    if (left[g] <= n || left[g] >= sz || right[g] <= n || right[g] >= sz)
-                        return fail(FS_EINVAL, "fs_model_create: tree %d node %d has child ids "
-                                    "(%d, %d); they must lie in (%d, %d)", t, n, left[g], right[g],
-                                    n, sz);
-                    const int32_t dl = depth[g] + 1;   // parents come before their children
-                    if (depth[o + left[g]] < dl) depth[o + left[g]] = dl;
-                    if (depth[o + right[g]] < dl) depth[o + right[g]] = dl;
+        // ---- validation, and the shapes of the trees on the way ----
+        TreeShapes shapes;
+        {
+            std::vector<int32_t> level((size_t)n_nodes, -1);     // -1: not on a path from the root
+            shapes.trees.resize((size_t)n_trees);
+            for (int t = 0; t < n_trees; ++t) {
+                const int32_t o = tree_off[t];
+                const int32_t sz = tree_off[t + 1] - o;
+                const int32_t *sf = split_feature + o, *le = left + o, *ri = right + o;
+                int32_t *lev = level.data() + o;
+                TreeShapes::Tree ts = {0, 0, 0, true, false};
+                int32_t shallowest = sz;
+                shapes.begin_tree();
+                lev[0] = 0;
+                for (int32_t n = 0; n < sz; ++n) {
+                    const int32_t l = lev[n];
+                    if (sf[n] >= 0) {
+                        if (sf[n] >= n_features)
+                            return fail(FS_EINVAL, "fs_model_create: tree %d node %d splits on feature "
+                                        "%d but the model has %d", t, n, sf[n], n_features);
+                        if (le[n] <= n || le[n] >= sz || ri[n] <= n || ri[n] >= sz)
+                            return fail(FS_EINVAL, "fs_model_create: tree %d node %d has child ids "
+                                        "(%d, %d); they must lie in (%d, %d)", t, n, le[n], ri[n],
+                                        n, sz);
+                        if (l < 0)
+                            continue;
+                        if (le[n] == ri[n] || lev[le[n]] >= 0 || lev[ri[n]] >= 0)
+                            ts.tree = false;             // a shared child
+                        ++ts.n_split;
+                        shapes.add_split(l);
+                        lev[le[n]] = lev[ri[n]] = l + 1;
+                    } else if (l >= 0) {
+                        ++ts.n_leaf;
+                        ts.depth = std::max(ts.depth, l);
+                        shallowest = std::min(shallowest, l);
+                    }
                 }
-                if (depth[g] > max_depth)
-                    max_depth = depth[g];
+                ts.perfect = ts.tree && ts.depth == shallowest && ts.depth >= 1 && ts.depth <= 14;
+                shapes.trees[(size_t)t] = ts;
+                shapes.end_tree(t, n_trees);
             }
         }
+        // depth of the trees if all are perfect and of one depth, else -1
+        const int perfect_depth = shapes.perfect_depth();
 
         fs_model *m = new (std::nothrow) fs_model();
         if (!m)
@@ -557,7 +725,6 @@ extern "C" int fs_model_create(fs_model **out, int32_t n_features, int32_t n_tre
         memset(m, 0, sizeof(*m));
         m->n_features = n_features;
         m->n_trees = n_trees;
-        m->max_depth = max_depth;
         m->n_nodes = n_nodes;
         m->bias = bias;
 
@@ -568,15 +735,15 @@ extern "C" int fs_model_create(fs_model **out, int32_t n_features, int32_t n_tre
             const bool others = tune(FS_TUNE_LDS_TILES) >= 0 || tune(FS_TUNE_LDS_MODE) >= 0 ||
                                 tune(FS_TUNE_LDS_GROUPS) >= 0 || tune(FS_TUNE_RANK) == 1;
             const int want = tune(FS_TUNE_TREELET);
-            if (want != 0 && (want == 1 || (!others && n_trees >= kTreeletMinTrees)))
-                m->tl_ok = build_treelets(n_features, n_trees, tree_off, split_feature, threshold, left, right,
-                                          value, want == 1, want != 1 && n_features <= 255, &tl);
             // What the LDS kernel takes for a tile: about 13.5 clocks per level it walks and 3 per feature
             // of the tile (measured on ensembles of 40 to 400 trees).  Models whose chunks do not fit half
             // a compute unit's LDS only take treelets where there is no other LDS form.
-            if (m->tl_ok && want != 1 && n_features <= 255 &&
-                (tl.cost > 13.5 * (double)n_trees * (double)max_depth + 3.0 * (double)n_features))
-                m->tl_ok = false;
+            const double most = want == 1 || n_features > 255
+                                    ? HUGE_VAL
+                                    : 13.5 * (double)n_trees * (double)shapes.max_depth() + 3.0 * (double)n_features;
+            if (want != 0 && (want == 1 || (!others && n_trees >= kTreeletMinTrees)))
+                m->tl_ok = build_treelets(n_features, n_trees, shapes, tree_off, split_feature, threshold, left,
+                                          right, value, want == 1, want != 1 && n_features <= 255, most, &tl);
             m->tl_pair = tl.pair_ok;
             m->tl_cols = tl.most_cols;
             if (m->tl_ok && tune(FS_TUNE_VERBOSE) > 0)
@@ -589,182 +756,16 @@ extern "C" int fs_model_create(fs_model **out, int32_t n_features, int32_t n_tre
         std::vector<uint8_t> image;
         std::vector<ChunkHdr> chunks;
         std::vector<uint16_t> slot_ids;
-        const int tile_bytes = (n_features + 1) * 256;
         if (n_trees > 0 && n_features <= 255 && !m->tl_ok) {
-            int common_depth = -1;
-            bool compact = true;
-            for (int t = 0; t < n_trees && compact; ++t) {
-                const int32_t o = tree_off[t];
-                compact = tree_is_perfect(split_feature + o, left + o, right + o,
-                                          tree_off[t + 1] - o, &common_depth);
-            }
-            std::vector<PackedTree> trees((size_t)n_trees);
-            size_t max_tree = 0, sum_tree = 0;
-            bool all_trees = true;
-            for (int t = 0; t < n_trees && all_trees; ++t) {
-                const int32_t o = tree_off[t];
-                all_trees = pack_tree(split_feature + o, threshold + o, left + o, right + o,
-                                      value + o, tree_off[t + 1] - o, n_features, compact,
-                                      common_depth, &trees[(size_t)t]);
-                const size_t b = trees[(size_t)t].words.size() * 4;
-                max_tree = b > max_tree ? b : max_tree;
-                sum_tree += b;
-            }
-            const size_t avg_tree = sum_tree / (size_t)n_trees;
-            // Pick the workgroup shape and the number of row tiles per workgroup.  More tiles
-            // mean fewer passes of the model through LDS, but less room for trees; what hides
-            // LDS latency is the number of independent walks in flight (tiles x trees
-            // resident), so that comes first.  The small shape is taken when it still gets 8
-            // or more trees into a chunk.
-            int best_t = 0, best_score = -1, best_mode = 0;
-            size_t best_avail = 0;
-            const int forced_tiles = tune(FS_TUNE_LDS_TILES), forced_mode = tune(FS_TUNE_LDS_MODE);
-            for (int mode = kLdsModes - 1; mode >= 0 && all_trees && best_t == 0; --mode) {
-                // The half-LDS shape (two workgroups per compute unit) measured no faster on
-                // any workload and doubles the model traffic from L2: tuning aid only.
-                if (mode == 0 && forced_mode != 1)
-                    continue;
-                if (forced_mode >= 1 && forced_mode <= kLdsModes && mode != forced_mode - 1)
-                    continue;
-                const int max_tiles = mode == 0 ? 1 : kLdsMaxTiles;
-                for (int nt = max_tiles; nt >= 1; --nt) {
-                    if (mode == 1 && forced_tiles >= 1 && forced_tiles <= kLdsMaxTiles &&
-                        nt != forced_tiles)
-                        continue;
-                    const long avail = (long)kLdsModeBytes[mode] - (long)nt * tile_bytes - 64;
-                    const size_t per_tree_val = (size_t)nt * 256;
-                    const size_t per_tree_tab = 4;   // a tree word of a run record
-                    const size_t head = (size_t)(kLdsMaxWaves + 12) * kRunBytes + 16;   // records + padding
-                    if (avail < (long)(max_tree + head + per_tree_val))
-                        continue;
-                    const size_t max_img = chunk_image_limit(mode);
-                    if (max_img < max_tree + head)
-                        continue;
-                    size_t by_chunk = (max_img - head) / (avg_tree + per_tree_tab);
-                    size_t by_avail = ((size_t)avail - head) / (avg_tree + per_tree_tab + per_tree_val);
-                    size_t per = by_chunk < by_avail ? by_chunk : by_avail;
-                    if (per < 1) per = 1;
-                    if (per > (size_t)kMaxChunkTrees) per = kMaxChunkTrees;
-                    if (mode == 0 && per < 8 && forced_mode != 1)
-                        continue;
-                    int score = nt * (int)per;
-                    if (score > 64) score = 64;   // measured: beyond ~5 trees per wavefront more
-                                                  // tiles win, below it more trees per chunk do
-                    if (score > best_score) {
-                        best_score = score;
-                        best_t = nt;
-                        best_mode = mode;
-                        best_avail = (size_t)avail;
-                    }
-                }
-            }
-            if (best_t > 0 && tune(FS_TUNE_VERBOSE) > 0)
-                fprintf(stderr, "fs_model_create: mode=%d tiles=%d avail=%zu avg_tree=%zu "
-                        "max_tree=%zu compact=%d\n", best_mode, best_t, best_avail, avg_tree,
-                        max_tree, (int)compact);
-            if (best_t > 0) {
-                const size_t per_tree_val = (size_t)best_t * 256;
+            LdsPlan plan;
+            if (plan_lds(n_features, n_trees, shapes, tree_off, split_feature, left, right, &plan)) {
                 m->lds_ok = true;
-                m->compact = compact;
-                m->lds_tiles = best_t;
-                m->lds_mode = best_mode;
-                // Trees per chunk: estimated from the average tree, then balanced over the
-                // wavefronts that share a tile (chunk_tree_target); a chunk ends early if its
-                // trees are larger than average and the next one does not fit.
-                const int share = kLdsModeWaves[best_mode] / best_t;
-                const size_t img_limit = chunk_image_limit(best_mode);
-                std::vector<int> tdepth((size_t)n_trees);
-                for (int t = 0; t < n_trees; ++t)
-                    tdepth[(size_t)t] = trees[(size_t)t].depth;
-                // (every tree may need a run record of its own on top of the slots' first records)
-                const size_t head0 = (size_t)kLdsMaxWaves * kRunBytes + 16;
-                size_t est_per = (best_avail - head0) / (avg_tree + kRunBytes + per_tree_val);
-                const size_t est_img = (img_limit - head0) / (avg_tree + kRunBytes);
-                if (est_per > est_img) est_per = est_img;
-                if (est_per > (size_t)kMaxChunkTrees) est_per = kMaxChunkTrees;
-                if (est_per < 1) est_per = 1;
-                const int even_cap = chunk_tree_target(n_trees, (int)est_per, share);
-                std::vector<int> bounds(1, 0);
-                for (int t = 0; t < n_trees;) {
-                    int cnt = 0;
-                    size_t body = 0;
-                    while (t + cnt < n_trees && cnt < kMaxChunkTrees && cnt < even_cap) {
-                        const size_t bt = trees[(size_t)(t + cnt)].words.size() * 4;
-                        // run records in front of the nodes: at most one per slot and one per tree
-                        const size_t img = ((size_t)(kLdsMaxWaves + cnt + 1) * kRunBytes + body + bt + 15) & ~(size_t)15;
-                        if (img > img_limit || img + (size_t)(cnt + 1) * per_tree_val > best_avail)
-                            break;
-                        body += bt;
-                        ++cnt;
-                    }
-                    t += cnt;                                 // cnt >= 1 by the choice of best_t
-                    bounds.push_back(t);
-                }
-                for (size_t ci = 0; ci + 1 < bounds.size(); ++ci) {
-                    const int t = bounds[ci], cnt = bounds[ci + 1] - bounds[ci];
-                    size_t body = 0;
-                    for (int j = 0; j < cnt; ++j)
-                        body += trees[(size_t)(t + j)].words.size() * 4;
-                    std::vector<int> by_depth((size_t)cnt);
-                    for (int j = 0; j < cnt; ++j)
-                        by_depth[(size_t)j] = j;
-                    std::stable_sort(by_depth.begin(), by_depth.end(), [&](int x, int y) {
-                        return tdepth[(size_t)(t + x)] > tdepth[(size_t)(t + y)];
-                    });
-                    SlotPlan sp;
-                    deal_trees(by_depth, tdepth.data() + t, share, &sp);
-                    // (the plan's cost is in units of about 1.5 us: configs[3] 12.1 for 18 us a group)
-                    m->lds_group_us += 1.5f * (float)sp.cost;
-                    // records: one per slot first (its first run, or an empty one), then the rest
-                    std::vector<int> rec_of(sp.runs.size(), -1);     // record index of every run
-                    int n_rec = kLdsMaxWaves;
-                    for (int b = 0; b < share; ++b)
-                        for (int r = sp.slot_start[b]; r < sp.slot_start[b + 1]; ++r)
-                            rec_of[(size_t)r] = r == sp.slot_start[b] ? b : n_rec++;
-                    const size_t table = ((size_t)n_rec * kRunBytes + 7) & ~(size_t)7;
-                    const size_t bytes = (table + body + 15) & ~(size_t)15;
-                    ChunkHdr h;
-                    memset(&h, 0, sizeof(h));
-                    h.byte_off = (uint32_t)image.size();
-                    h.bytes = (uint32_t)bytes;
-                    h.n_trees = (uint32_t)cnt;
-                    h.first_tree = (uint32_t)t;
-                    h.slot_off = (uint32_t)slot_ids.size();
-                    image.resize(image.size() + bytes, 0);
-                    slot_ids.resize(slot_ids.size() + bytes / 4, 0);
-                    uint8_t *img = image.data() + h.byte_off;
-                    uint16_t *ids = slot_ids.data() + h.slot_off;
-                    size_t pos = table;
-                    uint32_t dmax = 0;
-                    std::vector<uint32_t> root_at((size_t)cnt);
-                    for (int j = 0; j < cnt; ++j) {
-                        PackedTree &pt = trees[(size_t)(t + j)];
-                        const uint32_t base = (uint32_t)pos;
-                        root_at[(size_t)j] = base;
-                        for (uint32_t wi : pt.fix) {
-                            const uint32_t w = pt.words[wi];
-                            pt.words[wi] = (w & 0xFFFF0000u) | (((w & 0xFFFFu) + base) & 0xFFFFu);
-                        }
-                        memcpy(img + pos, pt.words.data(), pt.words.size() * 4);
-                        memcpy(ids + pos / 4, pt.slot_ids.data(), pt.slot_ids.size() * 2);
-                        pos += pt.words.size() * 4;
-                        if ((uint32_t)pt.depth > dmax) dmax = (uint32_t)pt.depth;
-                    }
-                    h.depth = dmax;
-                    for (int b = 0; b < share; ++b)
-                        for (int r = sp.slot_start[b]; r < sp.slot_start[b + 1]; ++r) {
-                            const RunPlan &rp = sp.runs[(size_t)r];
-                            const int next = r + 1 < sp.slot_start[b + 1] ? rec_of[(size_t)(r + 1)] + 1 : 0;
-                            uint32_t rec[kRunWords];
-                            rec[0] = (uint32_t)rp.count | ((uint32_t)next << 4) | ((uint32_t)rp.depth << 16);
-                            for (int k = 0; k < 8; ++k) {
-                                const int j = sp.order[(size_t)(rp.first + (k < rp.count ? k : 0))];
-                                rec[1 + k] = root_at[(size_t)j] | ((uint32_t)j << 16);
-                            }
-                            memcpy(img + (size_t)rec_of[(size_t)r] * kRunBytes, rec, sizeof(rec));
-                        }
-                    chunks.push_back(h);
-                }
+                m->compact = plan.compact;
+                m->lds_tiles = plan.tiles;
+                m->lds_mode = plan.mode;
+                m->lds_group_us = plan.group_us;
+                write_lds(plan, n_features, tree_off, split_feature, threshold, left, right, value, &image, &chunks,
+                          &slot_ids);
                 if (tune(FS_TUNE_VERBOSE) > 0) {
                     fprintf(stderr, "fs_model_create: %zu chunks, trees per chunk:", chunks.size());
                     for (const ChunkHdr &c : chunks)
@@ -773,7 +774,7 @@ extern "C" int fs_model_create(fs_model **out, int32_t n_features, int32_t n_tre
                 }
                 m->n_chunks = (int32_t)chunks.size();
                 m->image_bytes = image.size();
-                m->lds_tile0 = kLdsModeBytes[best_mode] - best_t * tile_bytes;
+                m->lds_tile0 = kLdsModeBytes[plan.mode] - plan.tiles * (n_features + 1) * 256;
             }
         }
 
@@ -783,16 +784,10 @@ extern "C" int fs_model_create(fs_model **out, int32_t n_features, int32_t n_tre
         std::vector<float> cuts;
         {
             const int want = tune(FS_TUNE_RANK);   // -1 automatic, 0 never, 1 whenever possible
-            int depth = -1;
-            bool perfect = n_trees > 0 && n_features <= 511 && want != 0 && !m->tl_ok;
-            for (int t = 0; t < n_trees && perfect; ++t) {
-                const int32_t o = tree_off[t];
-                perfect = tree_is_perfect(split_feature + o, left + o, right + o, tree_off[t + 1] - o,
-                                          &depth);
-            }
             // measured: pays from depth 8 on (3 KB per tree in the 8-byte-node format)
-            if (perfect && (want == 1 || depth >= 8) && depth <= 12)
-                build_rank_format(m, n_features, n_trees, depth, tree_off, split_feature, threshold,
+            if (n_features <= 511 && want != 0 && !m->tl_ok && perfect_depth >= (want == 1 ? 1 : 8) &&
+                perfect_depth <= 12)
+                build_rank_format(m, n_features, n_trees, perfect_depth, tree_off, split_feature, threshold,
                                   left, right, value, &rk_nodes, &rk_ids, &cuts);
         }
 

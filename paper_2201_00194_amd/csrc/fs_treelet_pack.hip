@@ -12,56 +12,6 @@ namespace fs {
 
 namespace {
 
-// Splits by level pair: counts of tree t's split nodes at depth 2*s, summed over the trees before t, at
-// [s][t]; steps[t] = treelet steps to tree t's deepest leaf (>= 1).  False if a node graph is not a tree
-// (a shared child) or deeper than the format is meant for.
-constexpr int kMaxSteps = 32;
-
-struct Shapes {
-    std::vector<int32_t> sum[kMaxSteps];
-    std::vector<uint8_t> steps;
-    int most_steps = 1;
-};
-
-bool tree_shapes(int n_trees, const int32_t *tree_off, const int32_t *sf, const int32_t *left,
-                 const int32_t *right, Shapes *out)
-{
-    out->steps.assign((size_t)n_trees, 1);
-    std::vector<std::vector<int32_t>> cnt;           // [s][t]
-    std::vector<int16_t> depth;
-    for (int t = 0; t < n_trees; ++t) {
-        const int32_t o = tree_off[t], sz = tree_off[t + 1] - o;
-        depth.assign((size_t)sz, -1);
-        depth[0] = 0;
-        int deepest = 0;
-        for (int32_t n = 0; n < sz; ++n) {           // children have larger ids: one forward pass
-            const int dn = depth[(size_t)n];
-            if (dn < 0 || sf[o + n] < 0)
-                continue;
-            const int32_t l = left[o + n], r = right[o + n];
-            if (l == r || depth[(size_t)l] >= 0 || depth[(size_t)r] >= 0 || dn + 1 > 2 * kMaxSteps)
-                return false;
-            depth[(size_t)l] = depth[(size_t)r] = (int16_t)(dn + 1);
-            if (dn + 1 > deepest)
-                deepest = dn + 1;
-            if ((dn & 1) == 0) {
-                while ((int)cnt.size() <= dn / 2)
-                    cnt.emplace_back((size_t)n_trees, 0);
-                ++cnt[(size_t)(dn / 2)][(size_t)t];
-            }
-        }
-        out->steps[(size_t)t] = (uint8_t)(deepest < 2 ? 1 : (deepest + 1) / 2);
-        out->most_steps = std::max(out->most_steps, (int)out->steps[(size_t)t]);
-    }
-    for (int s = 0; s < out->most_steps; ++s) {
-        out->sum[s].assign((size_t)n_trees + 1, 0);
-        if (s < (int)cnt.size())
-            for (int t = 0; t < n_trees; ++t)
-                out->sum[s][(size_t)t + 1] = out->sum[s][(size_t)t] + cnt[(size_t)s][(size_t)t];
-    }
-    return true;
-}
-
 struct Piece { int feature, at, n; };                // thresholds [at, at + n) of the feature
 
 // Columns and tables for B buckets.
@@ -69,8 +19,15 @@ void build_columns(const std::vector<Piece> &pieces, const std::vector<float> &c
                    const std::vector<int32_t> &cut_at, int B, TreeletSegmentPlan *out)
 {
     auto values = [&](const Piece &pc) { return cuts.data() + cut_at[(size_t)pc.feature] + pc.at; };
-    auto bucket_of = [B](float x, const TreeletCol &c) -> int {      // as the device truncates and clamps
-        const float t = std::fmaf(x, c.scale, c.offset);
+    // As the device rounds, truncates and clamps.  x * scale is exact in double, so the sum in double rounded
+    // to float is the fused result unless the rounding to double has made it a tie between two floats.
+    auto bucket_of = [B](float x, const TreeletCol &c) -> int {
+        const double sum = (double)x * (double)c.scale + (double)c.offset;
+        uint64_t bits;
+        memcpy(&bits, &sum, 8);
+        float t = (float)sum;
+        if ((bits & 0x1FFFFFFFu) == 0x10000000u)
+            t = std::fmaf(x, c.scale, c.offset);
         return t >= (float)(B - 1) ? B - 1 : (t > 0.0f ? (int)t : 0);
     };
     out->cols.clear();
@@ -96,7 +53,7 @@ void build_columns(const std::vector<Piece> &pieces, const std::vector<float> &c
                 continue;
             const TreeletCol c = {pc.feature, (float)s, (float)o, 0};
             int load = 0, run = 0, prev = -1;
-            for (int i = 0; i < pc.n; ++i) {
+            for (int i = 0; i < pc.n && load < best_load; ++i) {
                 const int bk = bucket_of(v[i], c);
                 tried[i] = (uint16_t)bk;
                 run = bk == prev ? run + 1 : 1;
@@ -124,14 +81,19 @@ void build_columns(const std::vector<Piece> &pieces, const std::vector<float> &c
         const float *v = values(pieces[c]);
         const uint16_t *bucket = &buckets[c * (size_t)kTreeletMaxCuts];
         uint8_t *tab = out->tables.data() + c * (size_t)out->table_stride;
+        // thresholds in lower buckets, for every bucket: eight at a time (the last writes run into the keys'
+        // place, or the next column's, which are written after)
+        int b = 0;
+        for (int i = 0; i <= pieces[c].n; ++i) {
+            const int end = i < pieces[c].n ? bucket[i] + 1 : B;
+            const uint64_t eight = 0x0101010101010101ull * (uint64_t)i;
+            for (; b < end; b += 8)
+                memcpy(tab + b, &eight, 8);
+            b = end;
+        }
         float *key = (float *)(tab + B);
         for (int i = 0; i < n_keys; ++i)
             key[i] = i < pieces[c].n ? v[i] : __builtin_nanf("");
-        for (int b = 0, i = 0; b < B; ++b) {
-            tab[b] = (uint8_t)i;                     // thresholds in lower buckets
-            while (i < pieces[c].n && bucket[i] == b)
-                ++i;
-        }
     }
 }
 
@@ -151,75 +113,122 @@ inline uint32_t ordered(float v)
     return (b & 0x80000000u) ? ~b : b | 0x80000000u;
 }
 
-// Sorts the thresholds of nodes [node0, node1), lists the columns and sets word[node] = column << 8 | rank of
-// every split (rank 0 for a NaN threshold: it sends nothing left).  False if the trees need more
+// The float of an ordered() value.
+inline float unordered(uint32_t k)
+{
+    k = (k & 0x80000000u) ? k & 0x7FFFFFFFu : ~k;
+    float v;
+    memcpy(&v, &k, 4);
+    return v;
+}
+
+// Sorts n keys by their upper halves; `spare` has room for as many.  Returns where they are, keys or spare.
+// First into about n buckets of equal width, as the thresholds of a feature are mostly spread over its
+// values, then each bucket (whatever the values are, this is no slower than its sort).
+uint64_t *sort_keys(uint64_t *keys, uint64_t *spare, int n)
+{
+    constexpr int kMost = 1024;
+    uint32_t lo = 0xFFFFFFFFu, hi = 0;
+    for (int i = 0; i < n; ++i) {
+        const uint32_t k = (uint32_t)(keys[i] >> 32);
+        lo = std::min(lo, k);
+        hi = std::max(hi, k);
+    }
+    const int buckets = std::min(n, kMost);
+    const float low = unordered(lo), scale = (float)buckets / (unordered(hi) - low);
+    if (n < 16 || !(scale > 0.0f && scale < 3e38f) || std::isinf(low)) {
+        std::sort(keys, keys + n);
+        return keys;
+    }
+    uint32_t at[kMost + 1];
+    std::fill(at, at + buckets + 1, 0u);
+    // (never decreases with the key: subtraction, product and truncation round monotonically)
+    auto bucket_of = [&](uint64_t k) {
+        return std::min((int)((unordered((uint32_t)(k >> 32)) - low) * scale), buckets - 1);
+    };
+    for (int i = 0; i < n; ++i)
+        ++at[bucket_of(keys[i]) + 1];
+    uint32_t fullest = 0;
+    for (int b = 0; b < buckets; ++b) {
+        fullest = std::max(fullest, at[b + 1]);
+        at[b + 1] += at[b];
+    }
+    for (int i = 0; i < n; ++i)
+        spare[at[bucket_of(keys[i])]++] = keys[i];
+    if (fullest > 16)
+        for (int b = 0; b < buckets; ++b) {          // at[b] is where bucket b ends now
+            const uint32_t from = b ? at[b - 1] : 0;
+            if (at[b] - from > 16)
+                std::sort(spare + from, spare + at[b]);
+        }
+    for (int i = 1; i < n; ++i) {                    // what is left to move stays inside its bucket
+        const uint64_t k = spare[i];
+        int j = i;
+        for (; j > 0 && spare[j - 1] > k; --j)
+            spare[j] = spare[j - 1];
+        spare[j] = k;
+    }
+    return spare;
+}
+
+// Sorts the thresholds of nodes [node0, node1) by feature, lists the columns and sets word[node] = column << 8 |
+// rank of every split (rank 0 for a NaN threshold: it sends nothing left).  False if the trees need more
 // columns than a byte names.
 bool segment_cuts(int n_features, int32_t node0, int32_t node1, const int32_t *sf, const float *thr,
                   std::vector<uint64_t> &keys, uint16_t *word, SegmentCuts *out)
 {
-    std::vector<int32_t> at((size_t)n_features + 1, 0);
-    std::vector<uint8_t> used((size_t)n_features, 0);
-    std::vector<int32_t> nan_nodes;
-    keys.resize(2 * (size_t)(node1 - node0) + 1);
-    uint64_t *from = keys.data();
-    size_t n_keys = 0;                               // (the loop has no branch that a leaf would upset)
+    // The splits, and how many each feature has (at [feature + 2]; leaves count at [1]: no branch that a leaf
+    // would upset), then where its keys start.
+    std::vector<int32_t> at((size_t)n_features + 2, 0), fill((size_t)n_features, 0), nan_nodes;
+    std::vector<int32_t> nodes((size_t)(node1 - node0));
+    size_t n_splits = 0;
     for (int32_t g = node0; g < node1; ++g) {
-        from[n_keys] = ((uint64_t)ordered(thr[g]) << 32) | (uint32_t)g;
-        n_keys += sf[g] >= 0;
+        nodes[n_splits] = g;
+        n_splits += sf[g] >= 0;
+        ++at[(size_t)(std::max(sf[g], -1) + 2)];
     }
-    uint32_t count[3][2048] = {};
-    {
-        size_t n = 0;
-        for (size_t i = 0; i < n_keys; ++i) {
-            const uint32_t g = (uint32_t)from[i], k = (uint32_t)(from[i] >> 32);
-            used[(size_t)sf[g]] = 1;
-            if (!(thr[g] == thr[g])) {
-                nan_nodes.push_back((int32_t)g);
-                continue;
-            }
-            from[n++] = from[i];
-            ++at[(size_t)sf[g] + 1];
-            ++count[0][k & 2047];
-            ++count[1][(k >> 11) & 2047];
-            ++count[2][k >> 22];
-        }
-        n_keys = n;
+    at[1] = 0;
+    int32_t most = 0;
+    for (int f = 0; f < n_features; ++f) {
+        most = std::max(most, at[(size_t)f + 2]);
+        at[(size_t)f + 2] += at[(size_t)f + 1];
+        fill[(size_t)f] = at[(size_t)f + 1];
     }
-    for (int f = 0; f < n_features; ++f)
-        at[(size_t)f + 1] += at[(size_t)f];
-    // by threshold (three digits, least first), then stably by feature
-    uint64_t *to = from + n_keys;
-    for (int pass = 0; pass < 3; ++pass) {
-        uint32_t before = 0;
-        for (uint32_t &c : count[pass]) {
-            const uint32_t here = c;
-            c = before;
-            before += here;
-        }
-        for (size_t i = 0; i < n_keys; ++i)
-            to[count[pass][(size_t)((from[i] >> (32 + 11 * pass)) & 2047)]++] = from[i];
-        std::swap(from, to);
+    at.erase(at.begin());                            // feature f's keys are [at[f], at[f + 1])
+    keys.resize(n_splits + (size_t)most);
+    for (size_t i = 0; i < n_splits; ++i) {
+        const int32_t g = nodes[i];
+        if (thr[g] == thr[g])
+            keys[(size_t)fill[(size_t)sf[g]]++] = ((uint64_t)ordered(thr[g]) << 32) | (uint32_t)g;
+        else
+            nan_nodes.push_back(g);
     }
-    std::vector<int32_t> fill(at.begin(), at.end() - 1);
-    for (size_t i = 0; i < n_keys; ++i)
-        to[(size_t)fill[(size_t)sf[(uint32_t)from[i]]]++] = from[i];
-    out->cuts.resize(n_keys);
+    uint64_t *spare = keys.data() + n_splits;
+    out->cuts.resize(n_splits);
     out->cut_at.assign((size_t)n_features + 1, 0);
     out->pieces.clear();
     std::vector<int32_t> first_col((size_t)n_features, 0);
     for (int f = 0; f < n_features; ++f) {
-        if (!used[(size_t)f])
+        if (at[(size_t)f + 1] == at[(size_t)f])
             continue;
         const int first = (int)out->pieces.size();
         first_col[(size_t)f] = first;
-        const uint64_t *k = to + at[(size_t)f];
-        const int m = at[(size_t)f + 1] - at[(size_t)f];
+        const int m = fill[(size_t)f] - at[(size_t)f];
+        const uint64_t *k = sort_keys(keys.data() + at[(size_t)f], spare, m);
         float *v = out->cuts.data() + at[(size_t)f];
-        int n = 0;
+        int n = 0, rank = 0;                         // rank inside the piece
+        uint32_t piece = (uint32_t)first - 1, last = 0;
         for (int i = 0; i < m; ++i) {
-            n += i == 0 || (k[i] >> 32) != (k[i - 1] >> 32);
-            v[n - 1] = thr[(uint32_t)k[i]] + 0.0f;
-            word[(uint32_t)k[i]] = (uint16_t)(((first + (n - 1) / kTreeletMaxCuts) << 8) | ((n - 1) % kTreeletMaxCuts + 1));
+            const uint32_t key = (uint32_t)(k[i] >> 32);
+            if (i == 0 || key != last) {
+                last = key;
+                v[n++] = unordered(key);
+                if (++rank > kTreeletMaxCuts || i == 0) {
+                    rank = 1;
+                    ++piece;
+                }
+            }
+            word[(uint32_t)k[i]] = (uint16_t)((piece << 8) | (uint32_t)rank);
         }
         out->cut_at[(size_t)f] = at[(size_t)f];
         int from = 0;
@@ -239,24 +248,31 @@ bool segment_cuts(int n_features, int32_t node0, int32_t node1, const int32_t *s
 
 }  // namespace
 
-bool build_treelets(int n_features, int n_trees, const int32_t *tree_off, const int32_t *sf,
-                    const float *thr, const int32_t *left, const int32_t *right, const float *val,
-                    bool any_size, bool pair_only, TreeletPlan *out)
+bool build_treelets(int n_features, int n_trees, const TreeShapes &shape, const int32_t *tree_off,
+                    const int32_t *sf, const float *thr, const int32_t *left, const int32_t *right, const float *val,
+                    bool any_size, bool pair_only, double most_cost, TreeletPlan *out)
 {
     if (n_trees < 1)
         return false;
-    Shapes shape;
-    if (!tree_shapes(n_trees, tree_off, sf, left, right, &shape))
-        return false;
+    std::vector<uint8_t> tree_steps((size_t)n_trees);
+    for (int t = 0; t < n_trees; ++t) {
+        if (!shape.trees[(size_t)t].tree || shape.deep)
+            return false;
+        tree_steps[(size_t)t] = (uint8_t)shape.steps(t);
+    }
+    // splits at depth 2*s of trees [a, b)
+    auto splits = [&](int s, int a, int b) -> int64_t {
+        return shape.sum[s].empty() ? 0 : shape.sum[s][(size_t)b] - shape.sum[s][(size_t)a];
+    };
     // bytes of a chunk of trees [a, b) (padded to units) and its step count
     auto chunk_size = [&](int a, int b, int *steps, int *entries, int *values) -> size_t {
         int s = 1;
         for (int t = a; t < b; ++t)
-            s = std::max(s, (int)shape.steps[(size_t)t]);
+            s = std::max(s, (int)tree_steps[(size_t)t]);
         int64_t e = (b - a + kTreeletUnit - 1) / kTreeletUnit * kTreeletUnit;
         for (int i = 0; i + 1 < s; ++i)
-            e += 4 * (int64_t)(shape.sum[i][(size_t)b] - shape.sum[i][(size_t)a]);
-        const int64_t v = 4 * (int64_t)(shape.sum[s - 1][(size_t)b] - shape.sum[s - 1][(size_t)a]);
+            e += 4 * splits(i, a, b);
+        const int64_t v = 4 * splits(s - 1, a, b);
         *steps = s;
         *entries = (int)e;
         *values = (int)(e + v);
@@ -277,6 +293,14 @@ bool build_treelets(int n_features, int n_trees, const int32_t *tree_off, const 
         for (int32_t g = 0; g < tree_off[n_trees]; ++g)
             if (sf[g] >= 0)
                 ++n_splits[(size_t)sf[g]];
+        // what the walk costs at least: every used feature one column, every tree its own steps
+        double least = 0.0;
+        for (int32_t n : n_splits)
+            least += n ? kTreeletColClk : 0.0;
+        for (uint8_t n : tree_steps)
+            least += kTreeletStepClk * n;
+        if (least > most_cost)
+            return false;
         int m = 1;
         for (;; ++m) {                               // assumes that half of the splits are distinct
             int64_t cols = 0;
@@ -344,12 +368,27 @@ bool build_treelets(int n_features, int n_trees, const int32_t *tree_off, const 
                 return false;
         return true;
     };
+    auto cost_of = [&](const std::vector<std::vector<int>> &all) {
+        int steps, e, v;
+        double cost = 0.0;
+        for (size_t i = 0; i < all.size(); ++i) {
+            cost += kTreeletColClk * (double)seg_cuts[i].pieces.size();
+            for (size_t c = 0; c + 1 < all[i].size(); ++c) {
+                const int n = (all[i][c + 1] - all[i][c] + kTreeletUnit - 1) / kTreeletUnit * kTreeletUnit;
+                (void)chunk_size(all[i][c], all[i][c + 1], &steps, &e, &v);
+                cost += kTreeletStepClk * (double)n * steps + kTreeletChunkClk;
+            }
+        }
+        return cost;
+    };
     // (before the columns' tables, which are most of what is left to do: a model that would be turned down
     // for this costs its sort of the thresholds and no more)
     std::vector<std::vector<int>> all;
     const long room = (long)kTreeletLds - kTreeletSumBytes - (long)out->most_cols * 256;
     out->pair_ok = plan_all(std::min((size_t)room / 1024 * 1024, (size_t)kTreeletPairBuf), &all);
     if (pair_only && !out->pair_ok)
+        return false;
+    if (out->pair_ok && cost_of(all) > most_cost)
         return false;
 
     // ---- columns ----
@@ -394,35 +433,46 @@ bool build_treelets(int n_features, int n_trees, const int32_t *tree_off, const 
     out->pair_ok = out->pair_ok && pair_coder;
     if (!out->pair_ok && !plan_all(kTreeletWholeBuf, &all))
         return false;
+    out->cost = cost_of(all);
+    if (out->cost > most_cost)
+        return false;
     size_t largest = 0;
     out->max_trees = 0;
-    out->image.clear();
     out->chunks.clear();
-    out->ids.clear();
+    {
+        size_t image_bytes = 0, n_ids = 0;
+        int steps, entries, values;
+        for (const std::vector<int> &b : all)
+            for (size_t c = 0; c + 1 < b.size(); ++c) {
+                image_bytes += chunk_size(b[c], b[c + 1], &steps, &entries, &values);
+                n_ids += (size_t)values;
+            }
+        out->image.assign(image_bytes, 0);
+        out->ids.assign(n_ids, 0);
+    }
+    size_t image_at = 0, ids_at = 0;
     struct Item { int32_t node, entry, step; };
     std::vector<Item> work;
-    out->cost = 0.0;
     for (size_t si = 0; si < out->segments.size(); ++si) {
       TreeletSegmentPlan &sp = out->segments[si];
       sp.first_chunk = (int)out->chunks.size();
       sp.n_chunks = (int)all[si].size() - 1;
-      out->cost += kTreeletColClk * (double)sp.cols.size();
       for (size_t ci = 0; ci + 1 < all[si].size(); ++ci) {
         const int a = all[si][ci], b = all[si][ci + 1];
         TreeletChunk h;
         int steps, entries, values;
         const size_t bytes = chunk_size(a, b, &steps, &entries, &values);
         const int n = (b - a + kTreeletUnit - 1) / kTreeletUnit * kTreeletUnit;
-        h.byte_off = (uint32_t)out->image.size();
+        h.byte_off = (uint32_t)image_at;
         h.bytes = (uint32_t)bytes;
         h.n_trees = (uint32_t)n;
         h.first_tree = (uint32_t)a;
         h.n_real = (uint32_t)(b - a);
         h.val_off = (uint32_t)entries * 8u;
         h.steps = (uint32_t)steps;
-        h.id_off = (uint32_t)out->ids.size();
-        out->image.resize(out->image.size() + bytes, 0);
-        out->ids.resize(out->ids.size() + (size_t)values, 0);
+        h.id_off = (uint32_t)ids_at;
+        image_at += bytes;
+        ids_at += (size_t)values;
         uint32_t *ent = (uint32_t *)(out->image.data() + h.byte_off);
         uint32_t *valtab = ent + 2 * (size_t)entries;
         uint16_t *ids = out->ids.data() + h.id_off;
@@ -489,7 +539,6 @@ bool build_treelets(int n_features, int n_trees, const int32_t *tree_off, const 
         largest = std::max(largest, bytes);
         out->max_trees = std::max(out->max_trees, n);
         out->chunks.push_back(h);
-        out->cost += kTreeletStepClk * (double)n * steps + kTreeletChunkClk;
       }
     }
     out->buf_bytes = (int)largest;
