@@ -728,22 +728,54 @@ extern "C" int fs_model_create(fs_model **out, int32_t n_features, int32_t n_tre
         m->n_nodes = n_nodes;
         m->bias = bias;
 
+        // perfect trees that the rank walk takes; measured: it pays from depth 8 on (3 KB per tree in the
+        // 8-byte-node format)
+        const bool ranks_pay = n_features <= 511 && tune(FS_TUNE_RANK) != 0 && perfect_depth <= 12 &&
+                               perfect_depth >= (tune(FS_TUNE_RANK) == 1 ? 1 : 8);
+
         // ---- byte-rank treelets ----
         TreeletPlan tl;
+        std::vector<uint32_t> rk_nodes;
+        std::vector<uint16_t> rk_ids;
+        std::vector<float> cuts;
         {
             // overrides of the other forms ask for those forms
             const bool others = tune(FS_TUNE_LDS_TILES) >= 0 || tune(FS_TUNE_LDS_MODE) >= 0 ||
                                 tune(FS_TUNE_LDS_GROUPS) >= 0 || tune(FS_TUNE_RANK) == 1;
             const int want = tune(FS_TUNE_TREELET);
-            // What the LDS kernel takes for a tile: about 13.5 clocks per level it walks and 3 per feature
-            // of the tile (measured on ensembles of 40 to 400 trees).  Models whose chunks do not fit half
-            // a compute unit's LDS only take treelets where there is no other LDS form.
-            const double most = want == 1 || n_features > 255
-                                    ? HUGE_VAL
-                                    : 13.5 * (double)n_trees * (double)shapes.max_depth() + 3.0 * (double)n_features;
-            if (want != 0 && (want == 1 || (!others && n_trees >= kTreeletMinTrees)))
-                m->tl_ok = build_treelets(n_features, n_trees, shapes, tree_off, split_feature, threshold, left,
-                                          right, value, want == 1, want != 1 && n_features <= 255, most, &tl);
+            TreeletLimits limits;
+            if (want != 1) {
+                limits.any_size = false;
+                // What the LDS kernel takes for a tile: about 13.5 clocks per level it walks and 3 per feature
+                // of the tile (measured on ensembles of 40 to 400 trees).  Models whose chunks do not fit half
+                // a compute unit's LDS only take treelets where there is no other LDS form.
+                if (n_features <= 255) {
+                    limits.pair_only = true;
+                    limits.cost = 13.5 * (double)n_trees * (double)shapes.max_depth() + 3.0 * (double)n_features;
+                }
+                // Every segment codes the rows anew, the rank walk codes them once.  Perfect trees of depth 8,
+                // 100 to 300 features, 64 to 500 trees, 5 to 6000 tiles in both layouts: with up to 376 columns
+                // in all treelets take 0.26 to 0.97 of the rank walk's time at every length, with 400 (two
+                // segments of 200) 0.85 to 1.09, with 460 to 492 0.77 to 1.25.
+                if (ranks_pay)
+                    limits.cols = kTreeletMostRankCols;
+            }
+            auto plan = [&] {
+                return build_treelets(n_features, n_trees, shapes, tree_off, split_feature, threshold, left, right,
+                                      value, limits, &tl);
+            };
+            const bool treelets = want != 0 && (want == 1 || (!others && n_trees >= kTreeletMinTrees));
+            if (treelets)
+                m->tl_ok = plan();
+            // ---- rank-coded format: deep perfect trees ----
+            if (ranks_pay && !m->tl_ok) {
+                build_rank_format(m, n_features, n_trees, perfect_depth, tree_off, split_feature, threshold, left,
+                                  right, value, &rk_nodes, &rk_ids, &cuts);
+                if (!m->rank_ok && limits.cols != INT_MAX && treelets) {
+                    limits.cols = INT_MAX;               // more thresholds of a feature than ranks of 16 bits
+                    m->tl_ok = plan();
+                }
+            }
             m->tl_pair = tl.pair_ok;
             m->tl_cols = tl.most_cols;
             if (m->tl_ok && tune(FS_TUNE_VERBOSE) > 0)
@@ -756,7 +788,7 @@ extern "C" int fs_model_create(fs_model **out, int32_t n_features, int32_t n_tre
         std::vector<uint8_t> image;
         std::vector<ChunkHdr> chunks;
         std::vector<uint16_t> slot_ids;
-        if (n_trees > 0 && n_features <= 255 && !m->tl_ok) {
+        if (n_trees > 0 && n_features <= 255 && !m->tl_ok && !m->rank_ok) {
             LdsPlan plan;
             if (plan_lds(n_features, n_trees, shapes, tree_off, split_feature, left, right, &plan)) {
                 m->lds_ok = true;
@@ -776,19 +808,6 @@ extern "C" int fs_model_create(fs_model **out, int32_t n_features, int32_t n_tre
                 m->image_bytes = image.size();
                 m->lds_tile0 = kLdsModeBytes[plan.mode] - plan.tiles * (n_features + 1) * 256;
             }
-        }
-
-        // ---- rank-coded format: deep perfect trees ----
-        std::vector<uint32_t> rk_nodes;
-        std::vector<uint16_t> rk_ids;
-        std::vector<float> cuts;
-        {
-            const int want = tune(FS_TUNE_RANK);   // -1 automatic, 0 never, 1 whenever possible
-            // measured: pays from depth 8 on (3 KB per tree in the 8-byte-node format)
-            if (n_features <= 511 && want != 0 && !m->tl_ok && perfect_depth >= (want == 1 ? 1 : 8) &&
-                perfect_depth <= 12)
-                build_rank_format(m, n_features, n_trees, perfect_depth, tree_off, split_feature, threshold,
-                                  left, right, value, &rk_nodes, &rk_ids, &cuts);
         }
 
         // ---- flat format: what the global-memory kernel walks, for models without another form ----

@@ -44,6 +44,7 @@ constexpr int kTreeletMaxSegments = 16;
 // a chunk's barriers.
 constexpr double kTreeletColClk = 18.0, kTreeletStepClk = 11.0, kTreeletChunkClk = 60.0;
 constexpr int kTreeletFewTrees = 12;          // a chunk should hold at least about this many
+constexpr int kTreeletMostRankCols = 399;     // of all segments, where the model could be rank-coded instead
 constexpr int kTreeletMinTrees = 32;          // the coder's work needs trees to pay
 constexpr int kTreeletUnit = 4;               // trees of a chunk come in units of four
 // Trees of a chunk at most: two wavefronts of two rounds of twelve walks.  Chunks of the first kind

@@ -2,6 +2,8 @@
 #ifndef FS_TREELET_PACK_H
 #define FS_TREELET_PACK_H
 
+#include <limits.h>
+#include <math.h>
 #include <algorithm>
 #include <vector>
 
@@ -81,13 +83,19 @@ struct TreeletPlan {
     double cost = 0.0;            // clocks of a compute unit per 64-row tile, estimated
 };
 
+// What a plan may not exceed, found out as early as possible.
+struct TreeletLimits {
+    bool any_size = true;         // also trees so large that the other forms are as good
+    bool pair_only = false;       // only if two workgroups fit a compute unit
+    double cost = HUGE_VAL;       // clocks, as TreeletPlan::cost
+    int cols = INT_MAX;           // columns of all segments together
+};
+
 // False if the model does not fit the format (more columns than a byte names, a node graph that
-// is not a tree, trees too large for a chunk -- or, unless `any_size`, so large that the other forms are
-// as good; or with `pair_only`, where no two workgroups fit a compute unit; or a cost above `most_cost`,
-// which is found out before most of the work).
+// is not a tree, trees too large for a chunk) or exceeds a limit.
 bool build_treelets(int n_features, int n_trees, const TreeShapes &shape, const int32_t *tree_off,
                     const int32_t *sf, const float *thr, const int32_t *left, const int32_t *right, const float *val,
-                    bool any_size, bool pair_only, double most_cost, TreeletPlan *out);
+                    const TreeletLimits &limits, TreeletPlan *out);
 
 }  // namespace fs
 #endif

@@ -250,7 +250,7 @@ bool segment_cuts(int n_features, int32_t node0, int32_t node1, const int32_t *s
 
 bool build_treelets(int n_features, int n_trees, const TreeShapes &shape, const int32_t *tree_off,
                     const int32_t *sf, const float *thr, const int32_t *left, const int32_t *right, const float *val,
-                    bool any_size, bool pair_only, double most_cost, TreeletPlan *out)
+                    const TreeletLimits &limits, TreeletPlan *out)
 {
     if (n_trees < 1)
         return false;
@@ -280,7 +280,7 @@ bool build_treelets(int n_features, int n_trees, const TreeShapes &shape, const 
     };
     int s_, e_, v_;
     // Trees so large that a chunk holds a handful walk no faster here than in the other forms.
-    if (!any_size && chunk_size(0, n_trees, &s_, &e_, &v_) / (size_t)n_trees * kTreeletFewTrees > (size_t)kTreeletPairBuf)
+    if (!limits.any_size && chunk_size(0, n_trees, &s_, &e_, &v_) / (size_t)n_trees * kTreeletFewTrees > (size_t)kTreeletPairBuf)
         return false;
 
     // ---- segments: as few as their columns allow, equally long ----
@@ -299,7 +299,7 @@ bool build_treelets(int n_features, int n_trees, const TreeShapes &shape, const 
             least += n ? kTreeletColClk : 0.0;
         for (uint8_t n : tree_steps)
             least += kTreeletStepClk * n;
-        if (least > most_cost)
+        if (least > limits.cost)
             return false;
         int m = 1;
         for (;; ++m) {                               // assumes that half of the splits are distinct
@@ -338,6 +338,11 @@ bool build_treelets(int n_features, int n_trees, const TreeShapes &shape, const 
     out->most_cols = 0;
     for (const SegmentCuts &c : seg_cuts)
         out->most_cols = std::max(out->most_cols, (int)c.pieces.size());
+    int all_cols = 0;
+    for (const SegmentCuts &c : seg_cuts)
+        all_cols += (int)c.pieces.size();
+    if (all_cols > limits.cols)
+        return false;
 
     // ---- bounds of the chunks ----
     // Bounds of the chunks of trees [t0, t1) in buffers of `buf` bytes.  Two wavefronts take a chunk's
@@ -386,9 +391,9 @@ bool build_treelets(int n_features, int n_trees, const TreeShapes &shape, const 
     std::vector<std::vector<int>> all;
     const long room = (long)kTreeletLds - kTreeletSumBytes - (long)out->most_cols * 256;
     out->pair_ok = plan_all(std::min((size_t)room / 1024 * 1024, (size_t)kTreeletPairBuf), &all);
-    if (pair_only && !out->pair_ok)
+    if (limits.pair_only && !out->pair_ok)
         return false;
-    if (out->pair_ok && cost_of(all) > most_cost)
+    if (out->pair_ok && cost_of(all) > limits.cost)
         return false;
 
     // ---- columns ----
@@ -419,7 +424,7 @@ bool build_treelets(int n_features, int n_trees, const TreeShapes &shape, const 
         }
         if (fits) {
             ++i;
-        } else if (pair_only) {
+        } else if (limits.pair_only) {
             return false;
         } else if (pair_coder) {                     // give the two-per-compute-unit form up and start over
             pair_coder = false;
@@ -434,7 +439,7 @@ bool build_treelets(int n_features, int n_trees, const TreeShapes &shape, const 
     if (!out->pair_ok && !plan_all(kTreeletWholeBuf, &all))
         return false;
     out->cost = cost_of(all);
-    if (out->cost > most_cost)
+    if (out->cost > limits.cost)
         return false;
     size_t largest = 0;
     out->max_trees = 0;
