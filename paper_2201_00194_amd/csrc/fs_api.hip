@@ -7,6 +7,7 @@
 #include <new>
 #include <vector>
 
+#include "fs_forms.h"
 #include "fs_internal.h"
 
 namespace fs {
@@ -347,35 +348,85 @@ static int lds_groups_wanted(int64_t groups_in_launch, double group_us, int n_co
     return g;
 }
 
-// Form of the treelet kernel for a call: long launches take two 4-tile workgroups per compute unit;
-// when that leaves compute units idle, fewer tiles per workgroup whose wavefronts share the trees.
-static int treelet_form(int n_families, const fs_family *fams, int n_compute_units)
+// A family that a call can walk either way.
+static bool has_both(const fs_model *m) { return m->tl_ok && m->lds_ok; }
+
+// Row-major families with both walks are re-tiled for the LDS walk in calls of up to this many tiles of theirs:
+// longer ones would need more scratch for it than the walk is worth (treelets win long row-major calls).
+constexpr int64_t kRetileTiles = 2048;
+
+static int64_t tiles_of(const fs_family &a) { return (a.n_rows + 63) / 64; }
+
+static bool needs_retile(const fs_family &a)
 {
-    const int forced = tune(FS_TUNE_TREELET_FORM);
-    if (forced >= 0 && forced < kTreeletForms)
-        return forced;
-    int64_t tiles = 0;
-    for (int f = 0; f < n_families; ++f)
-        if (fams[f].model->tl_ok)
-            tiles += (fams[f].n_rows + 63) / 64;
-    if (tiles <= n_compute_units)
-        return kTreeletSpread1;
-    if (tiles <= 2 * n_compute_units)
-        return kTreeletSpread2;
-    if (tiles <= 4 * n_compute_units)
-        return kTreeletSpread4;
-    return kTreeletPair;
+    return has_both(a.model) && a.layout == FS_ROWMAJOR && !lds_reads_rowmajor(a.model);
 }
 
-// Row-major input needs no pass of its own where the first kernel to touch the features can
-// read it: the rank-coding kernel always can; the LDS kernel transposes tiles on their way
-// into LDS (through the still unused chunk region) when rows are whole 16-byte pieces and at
-// least 8 padded rows fit below the tiles.  Other row-major families are re-tiled into scratch.
-static bool rowmajor_in_kernel(const fs_model *m)
+// Which families of a call walk treelets.
+struct Walks {
+    bool lds_for_both = false;       // families with both walks take the LDS walk
+    bool retiled_too = false;        // also those that are re-tiled for it
+    int form = kTreeletPair;         // of the treelet kernel
+
+    bool treelets(const fs_family &a) const
+    {
+        return a.model->tl_ok && !(a.model->lds_ok && lds_for_both && (retiled_too || !needs_retile(a)));
+    }
+};
+
+static Walks choose_walks(int n_families, const fs_family *fams, int n_compute_units)
 {
-    if (m->tl_ok || m->rank_ok)
-        return true;
-    return m->lds_ok && m->n_features % 4 == 0 && m->lds_tile0 >= 8 * (m->n_features + 1) * 4;
+    Walks w;
+    const int forced = tune(FS_TUNE_TREELET_FORM);
+    int64_t tiles = 0, retiled = 0;
+    for (int f = 0; f < n_families; ++f) {
+        tiles += fams[f].model->tl_ok ? tiles_of(fams[f]) : 0;
+        retiled += needs_retile(fams[f]) ? tiles_of(fams[f]) : 0;
+    }
+    w.form = treelet_form(tiles, n_compute_units);
+    w.retiled_too = retiled <= kRetileTiles;
+    if (forced >= 0 && forced < kTreeletForms) {
+        w.form = forced;
+        return w;
+    }
+    // the families with both walks, as one launch of either kind
+    double n = 0.0, wgs = 0.0, round_us = 0.0, groups = 0.0, group_us = 0.0, fetches = 0.0,
+           group_features = 0.0, rowmajor = 0.0, retile_features = 0.0;
+    for (int f = 0; f < n_families; ++f) {
+        const fs_family &a = fams[f];
+        const fs_model *m = a.model;
+        const double t = (double)tiles_of(a);
+        if (!has_both(m) || t == 0.0 || (needs_retile(a) && !w.retiled_too))
+            continue;
+        const bool rows = a.layout == FS_ROWMAJOR;
+        n += t;
+        wgs += ceil(t / kTreeletFormTiles[w.form]);
+        round_us += t * m->tl_us[rows][w.form];
+        groups += ceil(t / m->lds_tiles);
+        group_us += t * m->lds_group_us;
+        fetches += t * lds_fetches(m, rows && !needs_retile(a));
+        group_features += t * m->n_features * m->lds_tiles;
+        if (needs_retile(a))
+            retile_features += t * m->n_features;
+        else if (rows)
+            rowmajor += t;
+    }
+    if (n > 0.0) {
+        const double lds = lds_call_us(w.form, 2.0 * rowmajor > n, group_us / n, fetches / n, group_features / n,
+                                       groups, n_compute_units) +
+                           (retile_features > 0.0 ? retile_us(retile_features) : 0.0);
+        const double tl = treelet_call_us(w.form, round_us / n, wgs, n_compute_units);
+        w.lds_for_both = lds < tl;
+        if (tune(FS_TUNE_VERBOSE) > 0)
+            fprintf(stderr, "fs_score_families: %.0f tiles, treelets about %.0f us, LDS walk %.0f\n", n, tl, lds);
+    }
+    if (w.lds_for_both) {                            // the others' launch
+        tiles = 0;
+        for (int f = 0; f < n_families; ++f)
+            tiles += w.treelets(fams[f]) ? tiles_of(fams[f]) : 0;
+        w.form = treelet_form(tiles, n_compute_units);
+    }
+    return w;
 }
 
 // Validates the family descriptors (everything that does not need the device) and adds up the
@@ -384,6 +435,8 @@ static int score_scratch_floats(const char *who, int32_t n_families, const fs_fa
                                 size_t *out)
 {
     size_t scratch_floats = 0;
+    int64_t both_tiles = 0;                                  // of families with both walks that may be re-tiled
+    int32_t both_features = 0;
     for (int f = 0; f < n_families; ++f) {
         const fs_family &a = fams[f];
         if (!a.model)
@@ -413,10 +466,17 @@ static int score_scratch_floats(const char *who, int32_t n_families, const fs_fa
             scratch_floats += (size_t)a.n_rows;
         if (a.model->rank_ok)                                // u16 rank tiles, in float units
             scratch_floats += (size_t)((a.n_rows + 63) / 64) * 32 * (size_t)rank_tile_cols(a.model->n_features) + 4;
-        if ((a.model->tl_ok || a.model->rank_ok || a.model->lds_ok) && a.layout == FS_ROWMAJOR &&
-            !rowmajor_in_kernel(a.model))                                         // re-tiled copy
+        if (!a.model->tl_ok && !a.model->rank_ok && a.model->lds_ok && a.layout == FS_ROWMAJOR &&
+            !lds_reads_rowmajor(a.model))                                         // re-tiled copy
             scratch_floats += (size_t)((a.n_rows + 63) / 64) * 64 * (size_t)a.model->n_features + 4;
+        if (needs_retile(a)) {
+            both_tiles += tiles_of(a);
+            both_features = a.model->n_features > both_features ? a.model->n_features : both_features;
+            scratch_floats += 4;
+        }
     }
+    // (whether or not this call re-tiles them: a shorter call of what was reserved may)
+    scratch_floats += (size_t)(both_tiles < kRetileTiles ? both_tiles : kRetileTiles) * 64 * (size_t)both_features;
     *out = scratch_floats;
     return FS_OK;
 }
@@ -492,8 +552,16 @@ extern "C" int fs_score_families(int32_t n_families, const fs_family *fams, void
     int64_t trav_blocks = 0, seg_blocks = 0, lds_blocks[kLdsModes] = {0, 0};
     int64_t rk_blocks = 0, bin_blocks = 0, retile_blocks = 0, tl_blocks[2] = {0, 0};
     bool rk_dump = false, tl_dump[2] = {false, false};
+    const Walks walks = choose_walks(n_families, fams, ctx->n_compute_units);
+    if (tune(FS_TUNE_VERBOSE) > 0) {
+        int n_tl = 0;
+        for (int f = 0; f < n_families; ++f)
+            n_tl += walks.treelets(fams[f]) ? 1 : 0;
+        if (n_tl > 0)
+            fprintf(stderr, "fs_score_families: %d of %d families walk treelets, form %d\n", n_tl, n_families, walks.form);
+    }
     // treelet launches: 0 takes the form of the call, 1 the models that cannot take that
-    const int tl_form[2] = {treelet_form(n_families, fams, ctx->n_compute_units), kTreeletSpread4};
+    const int tl_form[2] = {walks.form, kTreeletSpread4};
     bool dump[kLdsModes] = {false, false};
     // tile groups the LDS kernel will see, per workgroup shape (row-major families included:
     // they count towards the length of the launch, though their workgroups take one group each)
@@ -501,7 +569,7 @@ extern "C" int fs_score_families(int32_t n_families, const fs_family *fams, void
     double lds_us[kLdsModes] = {0.0, 0.0};           // all groups of the launch, by the planner's estimate
     for (int f = 0; f < n_families; ++f) {
         const fs_model *m = fams[f].model;
-        if (!m->tl_ok && !m->rank_ok && m->lds_ok) {
+        if (!walks.treelets(fams[f]) && !m->rank_ok && m->lds_ok) {
             const int64_t g = ((fams[f].n_rows + 63) / 64 + m->lds_tiles - 1) / m->lds_tiles;
             lds_groups[m->lds_mode] += g;
             lds_us[m->lds_mode] += (double)g * (double)m->lds_group_us;
@@ -554,8 +622,9 @@ extern "C" int fs_score_families(int32_t n_families, const fs_family *fams, void
         d.rowmajor_src = nullptr;
         d.retile_block0 = (int32_t)retile_blocks;
         d.retile_colblocks = 0;
-        const bool fast = a.model->tl_ok || a.model->rank_ok || a.model->lds_ok;
-        const bool in_kernel = a.layout == FS_ROWMAJOR && rowmajor_in_kernel(a.model);
+        const bool treelets = walks.treelets(a);
+        const bool fast = treelets || a.model->rank_ok || a.model->lds_ok;
+        const bool in_kernel = a.layout == FS_ROWMAJOR && (treelets || a.model->rank_ok || lds_reads_rowmajor(a.model));
         if (fast && a.layout == FS_ROWMAJOR && a.n_rows > 0 && !in_kernel) {
             const int64_t tiles = (a.n_rows + 63) / 64;
             scratch_pos = (scratch_pos + 3) & ~(size_t)3;
@@ -588,7 +657,7 @@ extern "C" int fs_score_families(int32_t n_families, const fs_family *fams, void
         // Column-blocked features: deep perfect-tree models are rank-coded first and walked by
         // the rank kernel, other models that fit the LDS format take the LDS kernel; everything
         // else is walked from global memory.
-        if (a.model->tl_ok) {
+        if (treelets) {
             const int64_t tiles = (a.n_rows + 63) / 64;
             const int which = tl_form[0] == kTreeletPair && !a.model->tl_pair ? 1 : 0;
             const int per_wg = kTreeletFormTiles[tl_form[which]];

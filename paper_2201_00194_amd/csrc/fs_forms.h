@@ -1,0 +1,93 @@
+// Host-side estimates of a scoring call's time, by which a call chooses between the two walks of a model
+// that is prepared for both: byte-rank treelets and the LDS-staged format.
+//
+// Neither is the better one for a model.  Treelets pay for the coding of the rows (a latency that a short
+// launch shows in full) and every walk of a chunk takes the steps of its deepest tree; the LDS walk pays
+// for every level and for eight times the LDS reads.  Which one wins depends on layout and length of the call.
+// Fitted to 597 models of 32 to 500 irregular or perfect trees of depth 4 to 12 on 24 to 250 features, 5 to
+// 16 000 tiles, both layouts; the estimates are off by 3 to 8 % (rms).  Over 5200 calls of other models (36 to
+// 420 trees, 40 to 240 features, 8 to 5000 tiles) treelets alone are slower than the LDS walk by more than 10 % in
+// 804, by up to 2.97 times; the walk chosen here in 10, by up to 1.21, and it is slower than treelets by
+// more than 10 % in 38, by up to 1.24.
+#ifndef FS_FORMS_H
+#define FS_FORMS_H
+
+#include <math.h>
+
+#include "fs_internal.h"
+
+namespace fs {
+
+// Row-major input needs no pass of its own where the first kernel to touch the features can
+// read it: the rank-coding and treelet kernels always can; the LDS kernel transposes tiles on their way
+// into LDS (through the still unused chunk region) when rows are whole 16-byte pieces and at
+// least 8 padded rows fit below the tiles.  Other row-major families are re-tiled into scratch.
+inline bool lds_reads_rowmajor(const fs_model *m)
+{
+    return m->n_features % 4 == 0 && m->lds_tile0 >= 8 * (m->n_features + 1) * 4;
+}
+
+// Form of the treelet kernel for a launch of so many tiles: long launches take two 4-tile workgroups per
+// compute unit; when that leaves compute units idle, fewer tiles per workgroup whose wavefronts share the trees.
+inline int treelet_form(int64_t tiles, int n_compute_units)
+{
+    if (tiles <= n_compute_units)
+        return kTreeletSpread1;
+    if (tiles <= 2 * n_compute_units)
+        return kTreeletSpread2;
+    if (tiles <= 4 * n_compute_units)
+        return kTreeletSpread4;
+    return kTreeletPair;
+}
+
+// Times the workgroups of a launch follow one another on a compute unit.  Of two that share a compute unit
+// one alone is the quicker: a last round of up to half the workgroups takes about 0.6 of a full one.
+inline double launch_rounds(double workgroups, int n_compute_units, int side_by_side)
+{
+    const double r = workgroups / ((double)n_compute_units * side_by_side), whole = floor(r);
+    if (r > 3.0)
+        return r + 0.5;
+    if (side_by_side == 2 && whole > 0.0 && r > whole && r <= whole + 0.5)
+        return whole + 0.6;
+    return ceil(r);
+}
+
+// us of a call whose workgroups take `round_us` each (fs_model::tl_us, averaged over the families).
+inline double treelet_call_us(int form, double round_us, double workgroups, int n_compute_units)
+{
+    if (form != kTreeletPair)
+        return round_us;                             // such launches fit the chip
+    return 11.0 + round_us * launch_rounds(workgroups, n_compute_units, 2);
+}
+
+// Fetches of a tile group in the LDS walk: one per tile; row-major a part of a tile's rows at a time, as many as
+// the kernel's staging area below the tiles takes.
+inline double lds_fetches(const fs_model *m, bool rowmajor)
+{
+    const int rows = rowmajor ? m->lds_tile0 / (4 * (m->n_features + 1)) : 64;
+    return m->lds_tiles * ceil(64.0 / (rows < 64 ? rows : 64));
+}
+
+// The same for the LDS walk: `group_us` = fs_model::lds_group_us, `fetches` as above, `group_features` = tiles x
+// features of a group, all averaged; `form` is what the treelets would take, as a measure of the launch's length.
+inline double lds_call_us(int form, bool rowmajor, double group_us, double fetches,
+                          double group_features, double groups, int n_compute_units)
+{
+    struct Term { double call, fetch, feature; };
+    static const Term terms[2][kTreeletForms] = {
+        {{8.4, 0.22, 0.0077}, {5.7, 0.58, 0.0066}, {7.8, 0.0, 0.0029}, {7.2, 0.0, 0.0025}},
+        {{7.0, 1.46, 0.0109}, {6.2, 1.58, 0.01}, {6.8, 1.4, 0.0079}, {5.8, 1.46, 0.0079}}};
+    const Term &t = terms[rowmajor][form];
+    return t.call + launch_rounds(groups, n_compute_units, 1) *
+                        (0.84 * group_us + t.fetch * fetches + t.feature * group_features);
+}
+
+// Rows of an odd number of features are re-tiled before the LDS walk reads them: a launch, latency up to some
+// hundred tiles, then a rate.
+inline double retile_us(double tile_features)
+{
+    return fmin(5.0 + 2.4e-4 * tile_features, 20.0 + 6e-5 * tile_features);
+}
+
+}  // namespace fs
+#endif

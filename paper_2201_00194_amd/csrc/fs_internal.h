@@ -85,6 +85,11 @@ constexpr int kMaxChunkBytes = 65536 - 16;
 constexpr int kMaxChunkTrees = 96;
 constexpr int kPrefetchRegs = 6;        // 16-byte registers per thread for the next chunk
 
+// Forms of the treelet traversal: two 4-tile workgroups per compute unit, or one workgroup of 12
+// wavefronts that share 4, 2 or 1 tiles.
+enum { kTreeletPair = 0, kTreeletSpread4 = 1, kTreeletSpread2 = 2, kTreeletSpread1 = 3, kTreeletForms = 4 };
+constexpr int kTreeletFormTiles[kTreeletForms] = {4, 4, 2, 1};
+
 }  // namespace fs
 
 // The opaque model: host copy of what validation needs plus device arrays.
@@ -125,6 +130,9 @@ struct fs_model {
     bool tl_ok;
     bool tl_pair;              // two chunk buffers fit half a compute unit's LDS
     int32_t tl_cols;
+    // a round of workgroups, estimated, us (spread forms: the whole call); [row-major input][form].  A model
+    // with tl_ok and lds_ok has both walks, and the call chooses (fs_forms.h)
+    float tl_us[2][fs::kTreeletForms];
     void *d_tl_data;           // everything of this format, one allocation
     fs::TreeletModel *d_tl;    // inside it
 };
@@ -244,10 +252,6 @@ __host__ __device__ inline int lds_groups_per_wg(int layout, int n_features, int
 int launch_rank_code(const FamDesc *d_desc, int n_families, int total_blocks, hipStream_t stream);
 int launch_traverse_rank(const FamDesc *d_desc, int n_families, int total_blocks, bool dump,
                          hipStream_t stream);
-// Forms of the treelet traversal: two 4-tile workgroups per compute unit, or one workgroup of 12
-// wavefronts that share 4, 2 or 1 tiles.
-enum { kTreeletPair = 0, kTreeletSpread4 = 1, kTreeletSpread2 = 2, kTreeletSpread1 = 3, kTreeletForms = 4 };
-constexpr int kTreeletFormTiles[kTreeletForms] = {4, 4, 2, 1};
 // `launch`: which of FamDesc::tl_block0 numbers the blocks (a call makes up to two launches: models whose
 // chunks only fit a whole compute unit's LDS cannot take the first form).
 int launch_treelet(const FamDesc *d_desc, int n_families, int launch, int form, int total_blocks, bool dump,

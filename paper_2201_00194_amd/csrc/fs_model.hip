@@ -1,5 +1,5 @@
 // fs_model_create / fs_model_destroy: validation of the caller's ensemble and packing into
-// the two device formats (flat global-memory nodes; LDS-staged chunk images).
+// the device formats.
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
@@ -9,6 +9,7 @@
 #include <utility>
 #include <vector>
 
+#include "fs_forms.h"
 #include "fs_internal.h"
 #include "fs_treelet_pack.h"
 
@@ -567,9 +568,7 @@ void free_device(fs_model *m)
 {
     if (m->d_nodes) (void)hipFree(m->d_nodes);
     if (m->d_tree_off) (void)hipFree(m->d_tree_off);
-    if (m->d_image) (void)hipFree(m->d_image);
-    if (m->d_chunks) (void)hipFree(m->d_chunks);
-    if (m->d_slot_ids) (void)hipFree(m->d_slot_ids);
+    if (m->d_image) (void)hipFree(m->d_image);               // (the chunks and ids lie behind)
     if (m->d_rk_nodes) (void)hipFree(m->d_rk_nodes);
     if (m->d_rk_ids) (void)hipFree(m->d_rk_ids);
     if (m->d_cuts) (void)hipFree(m->d_cuts);
@@ -586,6 +585,21 @@ hipError_t upload(T **dst, const std::vector<T> &src)
     if (e != hipSuccess)
         return e;
     return hipMemcpy(*dst, src.data(), src.size() * sizeof(T), hipMemcpyHostToDevice);
+}
+
+// One allocation and one copy: [images][chunks][ids].
+hipError_t upload_lds(fs_model *m, std::vector<uint8_t> &image, const std::vector<ChunkHdr> &chunks,
+                      const std::vector<uint16_t> &slot_ids)
+{
+    const size_t chunk_at = (image.size() + 255) & ~(size_t)255, chunk_bytes = chunks.size() * sizeof(ChunkHdr);
+    const size_t ids_at = (chunk_at + chunk_bytes + 255) & ~(size_t)255, ids_bytes = slot_ids.size() * sizeof(uint16_t);
+    image.resize(ids_at + ids_bytes, 0);
+    memcpy(&image[chunk_at], chunks.data(), chunk_bytes);
+    memcpy(&image[ids_at], slot_ids.data(), ids_bytes);
+    const hipError_t e = upload(&m->d_image, image);
+    m->d_chunks = (ChunkHdr *)(m->d_image + chunk_at);
+    m->d_slot_ids = (uint16_t *)(m->d_image + ids_at);
+    return e;
 }
 
 // One allocation and one copy: [model][segments][chunks][image][ids][columns and tables per segment],
@@ -642,6 +656,26 @@ hipError_t upload_treelets(const TreeletPlan &tl, void **d_data, TreeletModel **
     }
     *d_model = (TreeletModel *)(base + model_at);
     return hipMemcpy(base, host.data(), total, hipMemcpyHostToDevice);
+}
+
+enum Wins { kNever, kSometimes, kAlways };
+
+// Whether treelets win the calls that a model prepared for both walks may get, by the estimates.
+Wins treelet_wins(const fs_model *m)
+{
+    constexpr int kUnits = 256;
+    const double lengths[] = {1, 256, 257, 512, 513, 1024, 1025, 1536, 2048, 4096, 16384};
+    double least = HUGE_VAL, most = 0.0;
+    for (int rowmajor = 0; rowmajor < (lds_reads_rowmajor(m) ? 2 : 1); ++rowmajor)
+        for (double tiles : lengths) {
+            const int form = treelet_form((int64_t)tiles, kUnits);
+            const double tl = treelet_call_us(form, m->tl_us[rowmajor][form], ceil(tiles / 4), kUnits);
+            const double lds = lds_call_us(form, rowmajor != 0, m->lds_group_us, lds_fetches(m, rowmajor != 0),
+                                           (double)m->n_features * m->lds_tiles, ceil(tiles / m->lds_tiles), kUnits);
+            least = std::min(least, tl / lds);
+            most = std::max(most, tl / lds);
+        }
+    return least > 1.0 ? kNever : most < 0.95 ? kAlways : kSometimes;
 }
 
 }  // namespace
@@ -746,9 +780,10 @@ extern "C" int fs_model_create(fs_model **out, int32_t n_features, int32_t n_tre
             TreeletLimits limits;
             if (want != 1) {
                 limits.any_size = false;
-                // What the LDS kernel takes for a tile: about 13.5 clocks per level it walks and 3 per feature
-                // of the tile (measured on ensembles of 40 to 400 trees).  Models whose chunks do not fit half
-                // a compute unit's LDS only take treelets where there is no other LDS form.
+                // A model is worth a second form if a treelet launch costs no more clocks than 13.5 per level
+                // of the trees and 3 per feature, which is about what the LDS walk takes for full trees; the
+                // call decides between the two.  Models whose chunks do not fit half a compute unit's LDS only
+                // take treelets where there is no other LDS form.
                 if (n_features <= 255) {
                     limits.pair_only = true;
                     limits.cost = 13.5 * (double)n_trees * (double)shapes.max_depth() + 3.0 * (double)n_features;
@@ -778,6 +813,7 @@ extern "C" int fs_model_create(fs_model **out, int32_t n_features, int32_t n_tre
             }
             m->tl_pair = tl.pair_ok;
             m->tl_cols = tl.most_cols;
+            memcpy(m->tl_us, tl.us, sizeof(m->tl_us));
             if (m->tl_ok && tune(FS_TUNE_VERBOSE) > 0)
                 fprintf(stderr, "fs_model_create: treelets, %zu segments of up to %d columns, %zu chunks of at most %d "
                         "trees and %d bytes%s, about %.0f clocks per tile\n", tl.segments.size(), m->tl_cols,
@@ -788,14 +824,25 @@ extern "C" int fs_model_create(fs_model **out, int32_t n_features, int32_t n_tre
         std::vector<uint8_t> image;
         std::vector<ChunkHdr> chunks;
         std::vector<uint16_t> slot_ids;
-        if (n_trees > 0 && n_features <= 255 && !m->tl_ok && !m->rank_ok) {
+        // beside treelets unless they win (or lose) every call; not where treelets were asked for, nor beside
+        // those of perfect trees that the rank walk would take, which win
+        if (n_trees > 0 && n_features <= 255 && !m->rank_ok &&
+            !(m->tl_ok && (tune(FS_TUNE_TREELET) == 1 || ranks_pay))) {
             LdsPlan plan;
-            if (plan_lds(n_features, n_trees, shapes, tree_off, split_feature, left, right, &plan)) {
-                m->lds_ok = true;
+            m->lds_ok = plan_lds(n_features, n_trees, shapes, tree_off, split_feature, left, right, &plan);
+            if (m->lds_ok) {
                 m->compact = plan.compact;
                 m->lds_tiles = plan.tiles;
                 m->lds_mode = plan.mode;
                 m->lds_group_us = plan.group_us;
+                m->lds_tile0 = kLdsModeBytes[plan.mode] - plan.tiles * (n_features + 1) * 256;
+                if (m->tl_ok) {
+                    const Wins wins = treelet_wins(m);
+                    m->lds_ok = wins != kAlways;
+                    m->tl_ok = wins != kNever;
+                }
+            }
+            if (m->lds_ok) {
                 write_lds(plan, n_features, tree_off, split_feature, threshold, left, right, value, &image, &chunks,
                           &slot_ids);
                 if (tune(FS_TUNE_VERBOSE) > 0) {
@@ -806,7 +853,6 @@ extern "C" int fs_model_create(fs_model **out, int32_t n_features, int32_t n_tre
                 }
                 m->n_chunks = (int32_t)chunks.size();
                 m->image_bytes = image.size();
-                m->lds_tile0 = kLdsModeBytes[plan.mode] - plan.tiles * (n_features + 1) * 256;
             }
         }
 
@@ -838,9 +884,8 @@ extern "C" int fs_model_create(fs_model **out, int32_t n_features, int32_t n_tre
             e = upload(&m->d_tree_off, toff);
         }
         if (e == hipSuccess) e = upload(&m->d_nodes, nodes);
-        if (e == hipSuccess) e = upload(&m->d_image, image);
-        if (e == hipSuccess) e = upload(&m->d_chunks, chunks);
-        if (e == hipSuccess) e = upload(&m->d_slot_ids, slot_ids);
+        if (e == hipSuccess && m->lds_ok)
+            e = upload_lds(m, image, chunks, slot_ids);
         if (e == hipSuccess && m->rank_ok) {
             e = upload(&m->d_rk_nodes, rk_nodes);
             if (e == hipSuccess) e = upload(&m->d_rk_ids, rk_ids);

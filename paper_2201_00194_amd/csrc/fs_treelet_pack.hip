@@ -158,8 +158,8 @@ uint64_t *sort_keys(uint64_t *keys, uint64_t *spare, int n)
     if (fullest > 16)
         for (int b = 0; b < buckets; ++b) {          // at[b] is where bucket b ends now
             const uint32_t from = b ? at[b - 1] : 0;
-            if (at[b] - from > 16)
-                std::sort(spare + from, spare + at[b]);
+            if (at[b] - from > 16 && !std::is_sorted(spare + from, spare + at[b]))
+                std::sort(spare + from, spare + at[b]);   // (equal thresholds arrive in order)
         }
     for (int i = 1; i < n; ++i) {                    // what is left to move stays inside its bucket
         const uint64_t k = spare[i];
@@ -244,6 +244,56 @@ bool segment_cuts(int n_features, int32_t node0, int32_t node1, const int32_t *s
     if (out->pieces.empty())                         // single leaves only: one column nobody asks
         out->pieces.push_back({0, 0, 0});
     return true;
+}
+
+// Times of a round of workgroups in each form (fs_forms.h says what they were fitted to): per segment
+// (launch and barriers), column, batch of columns that a wavefront codes, chunk, step of a chunk's deepest
+// walk, and step of all its trees.
+void estimate_rounds(int n_features, TreeletPlan *p)
+{
+    struct Spread { int tiles; double call, segment, col, wide, narrow, chunk, step, tree_step; };
+    static const Spread spread[2][kTreeletForms] = {
+        {{0, 0, 0, 0, 0, 0, 0, 0, 0},
+         {4, 3.8, 4.55, 0.057, 0.1, 0.21, 0.76, 0.053, 0.0185},
+         {2, 4.9, 3.8, 0.0217, 0.4, 0.27, 0.544, 0.12, 0.0067},
+         {1, 5.3, 2.85, 0.0105, 1.35, 0.49, 0.31, 0.206, 0.0026}},
+        {{0, 0, 0, 0, 0, 0, 0, 0, 0},
+         {4, 3.0, 5.05, 0.091, 0.0, 0.6, 0.74, 0.056, 0.019},
+         {2, 5.2, 3.7, 0.024, 0.4, 0.52, 0.54, 0.123, 0.0068},
+         {1, 5.3, 2.85, 0.0105, 1.35, 0.52, 0.31, 0.206, 0.0026}}};
+    // the pair form: a column by how many a wavefront codes at a time (4, 2, 1); row-major more the longer a
+    // row is, as fewer of its lines are still in a cache when the next batch asks for them
+    static const double pair_col[2][3] = {{0.0862, 0.0861, 0.106}, {0.097, 0.207, 0.236}};
+    static const double pair_feature[2][3] = {{0.0, 0.0, 0.0}, {2.2e-4, 5.5e-4, 5.5e-4}};
+    static const double pair_chunk[2] = {1.13, 1.09}, pair_tree_step[2] = {0.0317, 0.0284};
+    auto kb = [](long bytes) { return (bytes + 1023) / 1024 * 1024; };
+    double steps = 0.0, tree_steps = 0.0;
+    for (const TreeletChunk &c : p->chunks) {
+        steps += c.steps;
+        tree_steps += (double)c.n_trees * c.steps;
+    }
+    const double n_chunks = (double)p->chunks.size();
+    const long columns = (long)p->most_cols * 256;
+    for (int rowmajor = 0; rowmajor < 2; ++rowmajor) {
+        double pair = pair_chunk[rowmajor] * n_chunks + pair_tree_step[rowmajor] * tree_steps;
+        for (const TreeletSegmentPlan &sp : p->segments) {
+            const long room = (long)kTreeletLds - kTreeletSumBytes - columns;
+            const int batch = 16 * kb(4L * sp.table_stride) <= room ? 0 : 16 * kb(2L * sp.table_stride) <= room ? 1 : 2;
+            pair += (pair_col[rowmajor][batch] + pair_feature[rowmajor][batch] * n_features) * (double)sp.cols.size();
+        }
+        p->us[rowmajor][kTreeletPair] = (float)pair;
+        for (int form = kTreeletSpread4; form < kTreeletForms; ++form) {
+            const Spread &e = spread[rowmajor][form];
+            double us = e.call + e.chunk * n_chunks + e.step * steps + e.tree_step * tree_steps;
+            for (const TreeletSegmentPlan &sp : p->segments) {
+                const int wide = 16 / e.tiles, narrow = 4 / e.tiles;
+                const bool fits = 12 * kb((long)wide * sp.table_stride) + p->buf_bytes <= (long)kTreeletLdsWhole - columns;
+                const int cols = (int)sp.cols.size(), at_once = 12 * (fits ? wide : narrow);
+                us += e.segment + e.col * cols + (fits ? e.wide : e.narrow) * ((cols + at_once - 1) / at_once);
+            }
+            p->us[rowmajor][form] = (float)us;
+        }
+    }
 }
 
 }  // namespace
@@ -547,6 +597,7 @@ bool build_treelets(int n_features, int n_trees, const TreeShapes &shape, const 
       }
     }
     out->buf_bytes = (int)largest;
+    estimate_rounds(n_features, out);
     return true;
 }
 

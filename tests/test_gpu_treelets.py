@@ -82,3 +82,57 @@ def test_treelets_random_shapes(api, oracle, tune, seed):
     devs = run_families(api, fams, int(rng.integers(0, 2)))
     for f, d in zip(fams, devs):
         check_family(oracle, f, d)
+
+
+# A model with both walks, the layout, the rows of a call that belongs to the LDS walk and of one that
+# belongs to treelets: the coding shows in short calls; row-major input takes the coder longer in long ones.
+# 230 features row-major are re-tiled for the LDS walk, 24 and 164 are not.
+CHOICES = [
+    (dict(n_trees=100, depth=10, q=0.3, n_features=230), 1, 300, 150000),
+    (dict(n_trees=32, depth=8, q=0.35, n_features=24), 1, 64, 400000),
+    (dict(n_trees=160, depth=12, q=0.35, n_features=230), 0, 300, 40000),
+    (dict(n_trees=100, depth=7, q=0.0, n_features=164), 0, 126000, None),
+    (dict(n_trees=100, depth=6, q=0.2, n_features=164), 0, None, 257),
+]
+
+
+@pytest.mark.parametrize("shape,layout,lds_rows,treelet_rows", CHOICES)
+def test_the_call_chooses_between_the_walks(api, oracle, tune, capfd, shape, layout, lds_rows, treelet_rows):
+    tune(api.FS_TUNE_VERBOSE, 1)
+    sizes = {}
+    for rows, treelets in ((lds_rows, False), (treelet_rows, True)):
+        if rows is None:
+            continue
+        fam = family(8100, 3000, (1, 1), special=True, **shape)
+        if rows > 3000:
+            fam.features = np.random.default_rng(3).random((rows, shape["n_features"]), dtype=np.float32)
+            fam.prog_off = np.arange(0, rows + 1, 4, dtype=np.int32)
+        else:
+            fam.features, fam.prog_off = fam.features[:rows], fam.prog_off[:rows + 1]
+        fam.k = 50
+        capfd.readouterr()
+        dev, = run_families(api, [fam], layout, want_rows=rows <= 100000, want_leaves=rows <= 50000)
+        plan = capfd.readouterr().err
+        assert "treelets," in plan                   # the model has them
+        assert ("1 of 1 families walk treelets" in plan) == treelets and ("LDS shape" in plan) == (not treelets)
+        check_family(oracle, fam, dev)
+        sizes[rows] = api.fs_workspace_bytes([dev.family()])
+    # scratch reserved for the long call serves the short one, whichever walk it takes
+    assert sizes[min(sizes)] <= sizes[max(sizes)]
+
+
+@pytest.mark.parametrize("layout", [0, 1])
+def test_one_call_with_every_walk(api, oracle, layout):
+    """Families whose models have both walks beside some that have one: 230 features (re-tiled where row-major),
+    24 (not), perfect trees that stay treelets, ranked ones, and a model that only the global walk takes."""
+    fams = [family(8200 + i, n, (1, 3), special=True, **c) for i, (n, c) in enumerate([
+        (90, dict(n_trees=45, depth=12, q=0.35, n_features=230)),
+        (70, dict(n_trees=32, depth=8, q=0.35, n_features=24)),
+        (1, dict(n_trees=100, depth=12, q=0.35, n_features=230)),
+        (120, dict(n_trees=60, depth=8, q=0.0, n_features=64)),
+        (65, dict(n_trees=20, depth=9, q=0.0, n_features=64)),
+        (40, dict(n_trees=5, depth=6, q=0.2, n_features=300)),
+        (33, dict(n_trees=20, depth=5, q=0.2, n_features=131))])]
+    devs = run_families(api, fams, layout)
+    for f, d in zip(fams, devs):
+        check_family(oracle, f, d)

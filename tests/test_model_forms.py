@@ -52,3 +52,23 @@ def test_treelets_take_what_ranks_of_16_bits_cannot(capfd, tune):
     send the model to the walk from global memory."""
     plan = plan_of(capfd, tune, perfect_model(300, 6, 410, 8, zeros=0.0))
     assert "treelets" in plan and "rank-coded" not in plan
+
+
+@pytest.mark.parametrize("n_features,n_trees,depth,early_leaf,both", [
+    (230, 45, 12, 0.35, True),     # short calls belong to the LDS walk, long ones to treelets
+    (164, 64, 7, 0.0, True),       # an odd depth: the last treelet step takes two levels for one
+    (164, 200, 8, 0.2, True),
+    (131, 100, 4, 0.0, True),
+    (164, 300, 8, 0.0, False),     # the rank walk's, but for treelets
+])
+def test_a_model_has_both_walks_where_calls_differ(capfd, tune, n_features, n_trees, depth, early_leaf, both):
+    if early_leaf == 0.0:
+        model = perfect_model(n_features, n_features, n_trees, depth)
+    else:
+        rng = np.random.default_rng([n_features, n_trees])
+        model = W.draw_model(rng, rng.random((4000, n_features), dtype=np.float32), n_trees, depth,
+                             early_leaf_q=early_leaf)
+    plan = plan_of(capfd, tune, model)
+    assert "treelets" in plan
+    assert ("trees per chunk:" in plan) == both
+    assert "rank-coded" not in plan
