@@ -274,7 +274,7 @@ int fs_gather_programs(int32_t n_features, int32_t n_sources, const fs_gather_sr
  * that tests can drive every kernel form on small inputs and so that tile / chunk shapes can
  * be swept; results never depend on them (every form is exact).  value < 0 restores the
  * automatic choice.  The model options are read by fs_model_create (models already built keep
- * their plan), the training options by fs_train_boost.  Nothing else -- no environment
+ * their plan), the training options by fs_trainer_create and fs_train_boost.  Nothing else -- no environment
  * variable -- changes which kernel a model or trainer takes.
  */
 enum {
@@ -291,7 +291,9 @@ enum {
     FS_TUNE_TREELET = 9,          /* 0: never walk byte-rank treelets, 1: whenever the model fits them */
     FS_TUNE_TREELET_FORM = 10,    /* 0: two 4-tile workgroups per compute unit, 1 / 2 / 3: 4 / 2 / 1
                                      tiles shared by 12 wavefronts (read by fs_score_families)     */
-    FS_TUNE_OPTIONS = 11
+    FS_TUNE_TRAIN_WORK_MB = 11,   /* 1..: histogram memory a batch may take before it is trained in
+                                     parts, MB (automatic: 16 384)                                 */
+    FS_TUNE_OPTIONS = 12
 };
 int fs_tune_set(int32_t option, int32_t value);
 int32_t fs_tune_get(int32_t option);   /* current override, -1 = automatic */

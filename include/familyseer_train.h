@@ -63,6 +63,11 @@ typedef struct fs_train_params {
  * binning kernels run there, then the length of the longest program is read back (it sizes
  * the curvature sums of the histograms); the small host arrays are copied with plain
  * (synchronising) copies.  Create trainers outside latency-critical sections.
+ * All trainers of a device share one buffer for histograms.  This call grows it, where need be, to
+ * what any batch of the trainers alive takes, and then waits for all work on the device.  It is at
+ * most 16 GB, or what the largest trainer takes by itself.  With 256-bin features a trainer of depth d
+ * takes 4 KB x 2^(d-1) x n_features, and a batch up to 4 KB x n_features for each 512 rows,
+ * 192 times and once more per trainer at most.
  * Errors: FS_EINVAL, FS_EUNSUPPORTED (limits), FS_ENOMEM, FS_EDEVICE.
  */
 int fs_trainer_create(fs_trainer **out, int32_t n_features, const float *features /* DEVICE */,
@@ -72,16 +77,24 @@ int fs_trainer_create(fs_trainer **out, int32_t n_features, const float *feature
                       const int32_t *cut_off /* HOST, n_features+1 */, const float *cuts /* HOST */,
                       float bias, int32_t max_depth, int32_t max_trees, void *stream);
 
-/* Free a trainer (NULL allowed).  Synchronise its streams first. */
+/*
+ * Free a trainer (NULL allowed).  Synchronise its streams first.  With a device's last trainer the
+ * histograms' buffer goes too, unless it is of at most 512 MB: then it stays for the next trainer.
+ */
 void fs_trainer_destroy(fs_trainer *t);
 
 /*
  * n_rounds boosting rounds for every trainer of the batch (families train independently; one
- * batched submission per step, no host synchronisation).  All trainers use `params`.
+ * batched submission per step, no host synchronisation).  All trainers use `params`.  A batch whose
+ * histograms would take more than 16 GB is trained in parts, one after the other on `stream`.
+ * The call allocates and waits for the device only for a batch of more trainers than any before (its
+ * descriptors; the first allocation is for 16), or under an FS_TUNE_TRAIN_* override that was not set when
+ * the trainers were created.
  * Calls that involve the same trainer, and all training calls on one device, must be issued
  * on one stream (or be ordered by the caller): the batch descriptors and each trainer's
  * state are shared between calls.
- * Errors: FS_EINVAL, FS_EUNSUPPORTED (a trainer's max_depth / max_trees would be exceeded).
+ * Errors: FS_EINVAL, FS_EUNSUPPORTED (a trainer's max_depth / max_trees would be exceeded), FS_ENOMEM
+ * (in the cases above); after any of these no trainer of the batch has got a round.  FS_EDEVICE.
  */
 int fs_train_boost(int32_t n_trainers, fs_trainer *const *trainers /* HOST */, int32_t n_rounds,
                    const fs_train_params *params /* HOST */, void *stream);

@@ -86,8 +86,8 @@ _lib.fs_tune_get.restype = ctypes.c_int32
 _lib.fs_tune_get.argtypes = [ctypes.c_int32]
 (FS_TUNE_LDS_TILES, FS_TUNE_LDS_MODE, FS_TUNE_RANK, FS_TUNE_RANK_TILES, FS_TUNE_VERBOSE,
  FS_TUNE_TRAIN_SLAB_ROWS, FS_TUNE_TRAIN_SORT, FS_TUNE_TRAIN_PACKED, FS_TUNE_LDS_GROUPS,
- FS_TUNE_TREELET, FS_TUNE_TREELET_FORM) = range(11)
-FS_TUNE_OPTIONS = 11
+ FS_TUNE_TREELET, FS_TUNE_TREELET_FORM, FS_TUNE_TRAIN_WORK_MB) = range(12)
+FS_TUNE_OPTIONS = 12
 
 _lib.fs_profile_begin.restype = ctypes.c_int
 _lib.fs_profile_begin.argtypes = [ctypes.c_int32]

@@ -208,7 +208,7 @@ static int finish_desc(const DescBuf &db, hipStream_t stream)
 
 // ---- test and tuning overrides -----------------------------------------------------------------
 static std::mutex g_tune_mu;
-static int g_tune[FS_TUNE_OPTIONS] = {-1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1};
+static int g_tune[FS_TUNE_OPTIONS] = {-1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1};
 
 int tune(int option)
 {

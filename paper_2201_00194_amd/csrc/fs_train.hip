@@ -1270,7 +1270,6 @@ struct fs_trainer {
     int max_depth, max_trees;
     int trees_enqueued;
     int max_len;              // rows of the longest program
-    bool counted;             // among the device's trainers
     void *memory;             // everything the descriptor points to
 };
 
@@ -1281,29 +1280,37 @@ struct BatchBuf {
     TrainDesc *d_desc = nullptr;
     TrainDesc *h_desc = nullptr;   // pinned
     int cap = 0;
-    void *work = nullptr;          // histograms of the batch in work
+    void *work = nullptr;          // histograms of the batch in work: room for any batch of `alive`
     size_t work_bytes = 0;
-    int trainers = 0;              // alive; without any `work` is kept up to kKeptWork
+    std::vector<const fs_trainer *> alive;   // without any `work` is kept up to kKeptWork
+    size_t needed = 0, needed_before = 0;    // of `work`, since there was no trainer; and until then
     hipEvent_t copied = nullptr;
     bool pending = false;
 };
-static BatchBuf g_batch[16];
+static BatchBuf *const g_batch = new BatchBuf[16];   // never freed: trainers may outlive static objects
 
 // The histograms' buffer stays between the trainers of one tuning step and the next up to this size:
 // mapping and freeing it for every retraining took 0.7 to 1.3 ms of 6.5 to 17 (what a batch needs beyond
-// goes with the device's last trainer, all of it where device memory runs out for a new one).
+// goes with the device's last trainer, all of it where device memory runs out for something else).
 constexpr size_t kKeptWork = (size_t)512 << 20;
 
 // Frees the histograms' buffer of a device without trainers (g_train_mu held).
-static bool give_back(int dev)
+static bool give_back(BatchBuf &b)
 {
-    BatchBuf &b = g_batch[dev];
-    if (b.trainers != 0 || !b.work)
+    if (!b.alive.empty() || !b.work)
         return false;
     (void)hipFree(b.work);
     b.work = nullptr;
     b.work_bytes = 0;
     return true;
+}
+
+static bool give_back_training_memory(int device)
+{
+    if (device < 0 || device >= 16)
+        return false;
+    std::lock_guard<std::mutex> lock(g_train_mu);
+    return give_back(g_batch[device]);
 }
 
 // The arrays of a trainer lie in one device allocation: noted first, placed when all are known.
@@ -1341,6 +1348,119 @@ static int check_launch(const char *what)
     return FS_OK;
 }
 
+// ---- the histograms' buffer --------------------------------------------------------------------
+// Histograms live for one fs_train_boost only, and training calls on one device are ordered by the
+// caller, as its descriptors need already: all trainers share a buffer of the device (fresh memory of
+// 20 MB for each of eight trainers took 5 ms of a job's retraining).  fs_trainer_create, which waits for
+// the device anyway, grows it to what any batch of the trainers alive may need, so that fs_train_boost
+// neither allocates nor waits.  A batch that needs more than kMostWork is trained in parts, one after the other.
+constexpr size_t kMostWork = (size_t)16 << 30;
+
+static size_t most_work()
+{
+    const int mb = tune(FS_TUNE_TRAIN_WORK_MB);                  // test override
+    return mb >= 1 ? (size_t)mb << 20 : kMostWork;
+}
+
+// Bits that hold any curvature sum of a batch (rows x longest program bounds it).  The packed form of the
+// histograms needs room for the gradient sums beside them; beyond 31 bits the wide form is
+// taken right away (0).
+static int packed_bits(int max_len, int max_rows)
+{
+    int hb = 1;
+    while (hb < 63 && ((long long)1 << hb) <= (long long)max_len * (long long)max_rows)
+        ++hb;
+    return hb > 31 || tune(FS_TUNE_TRAIN_PACKED) == 0 ? 0 : hb;  // override: wide form only
+}
+
+// Planes of a trainer's histograms (the wide form takes the second).
+static int hist_planes(const fs_trainer *, int) { return 2; }
+
+// Words of the histograms that trees of `depth` levels keep, and of the parts of nodes of several items, in
+// a plane; returns the bytes of all planes.
+static size_t hist_bytes(const fs_trainer *t, int depth, int shift, int hb, size_t *hist, size_t *part)
+{
+    const size_t row = (size_t)t->h.n_features * kBins;
+    const int64_t rows = t->h.n_rows;
+    *hist = (depth > 0 ? (size_t)1 << (depth - 1) : 1) * row;
+    *part = rows >> shift ? ((size_t)((2 * rows) >> shift) + 1) * row : 0;
+    return (*hist + *part) * hist_planes(t, hb) * sizeof(unsigned long long);
+}
+
+// What a batch of any of these trainers takes at most.  With items of 2^shift rows the batch's parts are 2 R >> shift
+// and one more per trainer; shift is kChunkShiftMin or such that R are at most kChunkPieces items.
+static size_t any_batch_bytes(const std::vector<const fs_trainer *> &trainers)
+{
+    int max_len = 0, max_rows = 0;
+    for (const fs_trainer *t : trainers) {
+        max_len = std::max(max_len, t->max_len);
+        max_rows = std::max(max_rows, t->h.n_rows);
+    }
+    const int hb = packed_bits(max_len, max_rows);
+    size_t hists = 0, parts = 0, largest_row = 0, single = 0;
+    for (const fs_trainer *t : trainers) {
+        size_t hist, part;
+        (void)hist_bytes(t, t->max_depth, kChunkShiftMin, hb, &hist, &part);
+        const size_t words = (size_t)t->h.n_features * kBins, plane = sizeof(unsigned long long) * hist_planes(t, hb);
+        hists += hist * plane;
+        parts += part / words;
+        largest_row = std::max(largest_row, words * plane);
+        single = std::max(single, (hist + std::min(part, (2 * kChunkPieces + 1) * words)) * plane);
+    }
+    const size_t all = hists + std::min(parts, 2 * kChunkPieces + trainers.size()) * largest_row;
+    return std::max(single, std::min(all, most_work()));
+}
+
+// The buffer grows to `bytes`, or `wish` if that is to be had (g_train_mu held).  Where neither is, it is
+// what it was.
+static int grow_work(BatchBuf &b, size_t bytes, size_t wish)
+{
+    FS_HIP(hipDeviceSynchronize());                              // earlier batches may still be at work in it
+    const size_t had = b.work_bytes;
+    if (b.work)
+        (void)hipFree(b.work);
+    b.work = nullptr;
+    b.work_bytes = 0;
+    hipError_t e = hipErrorOutOfMemory;
+    for (const size_t size : {wish, bytes, had}) {
+        if (size == 0)
+            continue;
+        const hipError_t err = hipMalloc(&b.work, size);
+        if (err == hipSuccess) {
+            b.work_bytes = size;
+            break;
+        }
+        e = err;
+        b.work = nullptr;
+        (void)hipGetLastError();                                 // not the next launch's error
+    }
+    if (b.work_bytes >= bytes)
+        return FS_OK;
+    return e == hipErrorOutOfMemory ? fail(FS_ENOMEM, "hipMalloc of %zu bytes for histograms failed", bytes)
+                                    : fail_hip(e, "hipMalloc");
+}
+
+// Counts the trainer among its device's and makes room for it.
+static int reserve_work(const fs_trainer *t)
+{
+    if (t->device < 0 || t->device >= 16)
+        return FS_OK;                                            // fs_train_boost turns it down
+    std::lock_guard<std::mutex> lock(g_train_mu);
+    BatchBuf &b = g_batch[t->device];
+    try {
+        b.alive.push_back(t);
+    } catch (const std::bad_alloc &) {
+        return fail(FS_ENOMEM, "out of host memory");
+    }
+    const size_t need = any_batch_bytes(b.alive);
+    b.needed = std::max(b.needed, need);
+    if (b.work_bytes >= need)
+        return FS_OK;
+    // The trainers of a job are created one after the other: at once what the job before needed, else in
+    // steps.  (Eight trainers of depth 10, 1.5 GB: 4 ms in steps, 0.3 at once.)
+    return grow_work(b, need, std::max({need, b.needed_before, std::min(2 * b.work_bytes, b.work_bytes + kKeptWork)}));
+}
+
 }  // namespace fs
 
 using namespace fs;
@@ -1351,10 +1471,19 @@ extern "C" void fs_trainer_destroy(fs_trainer *t)
         return;
     if (t->memory)
         (void)hipFree(t->memory);
-    if (t->counted) {
+    if (t->device >= 0 && t->device < 16) {
         std::lock_guard<std::mutex> lock(g_train_mu);
-        if (--g_batch[t->device].trainers == 0 && g_batch[t->device].work_bytes > kKeptWork)
-            give_back(t->device);
+        BatchBuf &b = g_batch[t->device];
+        const auto it = std::find(b.alive.begin(), b.alive.end(), t);
+        if (it != b.alive.end()) {
+            b.alive.erase(it);
+            if (b.alive.empty()) {
+                b.needed_before = b.needed;
+                b.needed = 0;
+                if (b.work_bytes > kKeptWork)
+                    give_back(b);
+            }
+        }
     }
     delete t;
 }
@@ -1457,13 +1586,8 @@ extern "C" int fs_trainer_create(fs_trainer **out, int32_t n_features, const flo
     arena.add(&h.m_thr, (size_t)node_cap);
     arena.add(&h.m_val, (size_t)node_cap);
     rc = arena.place(&t->memory);
-    if (rc == FS_ENOMEM && t->device < 16) {
-        std::unique_lock<std::mutex> lock(g_train_mu);
-        const bool freed = give_back(t->device);
-        lock.unlock();
-        if (freed)
-            rc = arena.place(&t->memory);
-    }
+    if (rc == FS_ENOMEM && give_back_training_memory(t->device))
+        rc = arena.place(&t->memory);
     if (rc != FS_OK) {
         fs_trainer_destroy(t);
         return rc;
@@ -1528,72 +1652,18 @@ extern "C" int fs_trainer_create(fs_trainer **out, int32_t n_features, const flo
                 rc = fail_hip(e, "fs_trainer_create: reading the longest program");
         }
     }
+    if (rc == FS_OK)
+        rc = reserve_work(t);
     if (rc != FS_OK) {
         fs_trainer_destroy(t);
         return rc;
-    }
-    if (t->device < 16) {
-        std::lock_guard<std::mutex> lock(g_train_mu);
-        ++g_batch[t->device].trainers;
-        t->counted = true;
     }
     *out = t;
     return FS_OK;
 }
 
-// Histograms live for one fs_train_boost only, and training calls on one device are ordered by the
-// caller, as its descriptors need already: all trainers share a buffer of the device (fresh memory of
-// 20 MB for each of eight trainers took 5 ms of a job's retraining).  A batch that needs more than this is trained in parts, one after the other.
-constexpr size_t kMostWork = (size_t)16 << 30;
-
-// Bytes for the histograms that trees of `depth` levels keep and for the parts of nodes of several items.
-static size_t hist_bytes(const fs_trainer *t, int depth, int shift, size_t *hist, size_t *part)
-{
-    const size_t row = (size_t)t->h.n_features * kBins;
-    const int64_t rows = t->h.n_rows;
-    *hist = (depth > 0 ? (size_t)1 << (depth - 1) : 1) * row;
-    *part = rows >> shift ? ((size_t)((2 * rows) >> shift) + 1) * row : 0;
-    return (*hist + *part) * 2 * sizeof(unsigned long long);
-}
-
-// Gives every trainer its place in the device's buffer, which grows to `all` bytes.
-static int place_hist(int n, fs_trainer *const *trainers, int depth, int shift, size_t all)
-{
-    int dev = 0;
-    FS_HIP(hipGetDevice(&dev));
-    if (dev < 0 || dev >= 16)
-        return fail(FS_EUNSUPPORTED, "device ordinal %d not supported", dev);
-    BatchBuf &b = g_batch[dev];
-    if (b.work_bytes < all) {
-        FS_HIP(hipDeviceSynchronize());                          // earlier batches may still be at work in it
-        if (b.work)
-            (void)hipFree(b.work);
-        b.work_bytes = 0;
-        const hipError_t e = hipMalloc(&b.work, all);
-        if (e != hipSuccess) {
-            b.work = nullptr;
-            (void)hipGetLastError();
-            return e == hipErrorOutOfMemory ? fail(FS_ENOMEM, "hipMalloc of %zu bytes failed", all)
-                                            : fail_hip(e, "hipMalloc");
-        }
-        b.work_bytes = all;
-    }
-    char *at = (char *)b.work;
-    for (int i = 0; i < n; ++i) {
-        TrainDesc &h = trainers[i]->h;
-        size_t hist, part;
-        const size_t bytes = hist_bytes(trainers[i], depth, shift, &hist, &part);
-        h.hist = (unsigned long long *)at;
-        h.hist_plane = (int64_t)hist;
-        h.part = h.hist + 2 * hist;
-        h.part_plane = (int64_t)part;
-        at += bytes;
-    }
-    return FS_OK;
-}
-
-// Uploads the batch's descriptors; returns the device array.
-static int upload_batch(int n, fs_trainer *const *trainers, hipStream_t stream, const TrainDesc **d_out)
+// Uploads descriptors; returns the device array.
+static int upload_batch(int n, const fs_trainer *const *trainers, hipStream_t stream, const TrainDesc **d_out)
 {
     int dev = 0;
     FS_HIP(hipGetDevice(&dev));
@@ -1620,21 +1690,8 @@ static int upload_batch(int n, fs_trainer *const *trainers, hipStream_t stream, 
         FS_HIP(hipHostMalloc((void **)&b.h_desc, sizeof(TrainDesc) * (size_t)cap, hipHostMallocDefault));
         b.cap = cap;
     }
-    // Largest families first: the histogram launches have a workgroup per (family, four
-    // features), a little more than one per compute unit, and those dispatched last should be
-    // the short ones.  (The order of the descriptors is internal; kernels index by block.)
-    std::vector<int> order;
-    try {
-        order.resize((size_t)n);
-    } catch (...) {
-        return fail(FS_ENOMEM, "out of host memory");
-    }
     for (int i = 0; i < n; ++i)
-        order[(size_t)i] = i;
-    std::stable_sort(order.begin(), order.end(),
-                     [&](int a, int c) { return trainers[a]->h.n_rows > trainers[c]->h.n_rows; });
-    for (int i = 0; i < n; ++i)
-        b.h_desc[i] = trainers[order[(size_t)i]]->h;
+        b.h_desc[i] = trainers[i]->h;
     FS_HIP(hipMemcpyAsync(b.d_desc, b.h_desc, sizeof(TrainDesc) * (size_t)n, hipMemcpyHostToDevice, stream));
     FS_HIP(hipEventRecord(b.copied, stream));
     b.pending = true;
@@ -1663,96 +1720,56 @@ static int check_batch(const char *who, int n, fs_trainer *const *trainers)
     return FS_OK;
 }
 
-extern "C" int fs_train_boost(int32_t n_trainers, fs_trainer *const *trainers, int32_t n_rounds,
-                              const fs_train_params *p, void *stream_)
+namespace {
+
+// Trainers [first, first + n) of a call, trained side by side.
+struct Part {
+    int first, n;
+    int shift, hb;                   // rows of a histogram workgroup (log2); packed_bits
+    int max_rows, max_prog, max_feat;
+    size_t bytes;                    // of histograms
+};
+
+Part make_part(const fs_trainer *const *trainers, int first, int n, int depth)
 {
-    hipStream_t stream = (hipStream_t)stream_;
-    int rc = check_batch("fs_train_boost", n_trainers, trainers);
-    if (rc != FS_OK)
-        return rc;
-    if (!p)
-        return fail(FS_EINVAL, "fs_train_boost: params is NULL");
-    if (n_rounds < 0)
-        return fail(FS_EINVAL, "fs_train_boost: n_rounds %d is negative", n_rounds);
-    if (p->max_depth < 0 || p->max_depth > FS_TRAIN_MAX_DEPTH)
-        return fail(FS_EUNSUPPORTED, "fs_train_boost: max_depth=%d outside 0..%d", p->max_depth,
-                    FS_TRAIN_MAX_DEPTH);
-    if (!(p->eta > 0.0f) || !(p->lambda >= 0.0f) || !(p->grad_scale > 0.0f) || isinf(p->grad_scale) ||
-        isnan(p->min_gain) || isnan(p->min_child_weight))
-        return fail(FS_EINVAL, "fs_train_boost: eta > 0, lambda >= 0, grad_scale > 0 required");
-    int exp2 = 0;
-    if (frexpf(p->grad_scale, &exp2) != 0.5f)
-        return fail(FS_EINVAL, "fs_train_boost: grad_scale must be a power of two");
-    if (n_trainers == 0 || n_rounds == 0)
-        return FS_OK;
-    int max_rows = 0, max_prog = 0, max_feat = 0, max_len = 0;
+    Part pt = {first, n, kChunkShiftMin, 0, 0, 0, 0, 0};
+    int max_len = 0;
     int64_t total_rows = 0;
-    for (int i = 0; i < n_trainers; ++i) {
+    for (int i = first; i < first + n; ++i) {
         const fs_trainer *t = trainers[i];
-        if (p->max_depth > t->max_depth)
-            return fail(FS_EUNSUPPORTED, "fs_train_boost: trainer %d was created for max_depth %d", i, t->max_depth);
-        if (t->trees_enqueued + n_rounds > t->max_trees)
-            return fail(FS_EUNSUPPORTED, "fs_train_boost: trainer %d holds %d trees of at most %d", i,
-                        t->trees_enqueued, t->max_trees);
         total_rows += t->h.n_rows;
-        if (t->h.n_rows > max_rows) max_rows = t->h.n_rows;
-        if (t->h.n_programs > max_prog) max_prog = t->h.n_programs;
-        if (t->h.n_features > max_feat) max_feat = t->h.n_features;
-        if (t->max_len > max_len) max_len = t->max_len;
+        pt.max_rows = std::max(pt.max_rows, t->h.n_rows);
+        pt.max_prog = std::max(pt.max_prog, t->h.n_programs);
+        pt.max_feat = std::max(pt.max_feat, t->h.n_features);
+        max_len = std::max(max_len, t->max_len);
     }
     // A histogram workgroup takes up to 2^shift rows of a node: 48 to 96 pieces of all the batch's rows
     // at the root, which with ten feature groups are two to four workgroups per compute unit.
-    int shift = kChunkShiftMin;
-    while (shift < 30 && ((int64_t)1 << shift) * kChunkPieces < total_rows)
-        ++shift;
-    {
-        const int v = tune(FS_TUNE_TRAIN_SLAB_ROWS);             // test / tuning override
-        if (v >= 64 && v <= 65536)
-            for (shift = 6; (1 << shift) < v;)
-                ++shift;
-    }
-    size_t work = 0, hist = 0, part = 0;
-    for (int i = 0; i < n_trainers; ++i)
-        work += hist_bytes(trainers[i], p->max_depth, shift, &hist, &part);
-    if (work > kMostWork && n_trainers > 1) {                    // (all trainers were found good above)
-        rc = fs_train_boost(n_trainers / 2, trainers, n_rounds, p, stream_);
-        return rc != FS_OK ? rc
-                           : fs_train_boost(n_trainers - n_trainers / 2, trainers + n_trainers / 2, n_rounds, p, stream_);
-    }
-    std::lock_guard<std::mutex> lock(g_train_mu);
-    rc = place_hist(n_trainers, trainers, p->max_depth, shift, work);
-    if (rc != FS_OK)
-        return rc;
-    const TrainDesc *d = nullptr;
-    rc = upload_batch(n_trainers, trainers, stream, &d);
-    if (rc != FS_OK)
-        return rc;
-    Params prm;
-    prm.eta = (double)p->eta;
-    prm.lambda = (double)p->lambda;
-    prm.min_gain = (double)p->min_gain;
-    prm.inv_scale = 1.0 / (double)p->grad_scale;
-    double mcw = ceil((double)p->min_child_weight);
-    prm.mcw = mcw < 1.0 ? 1 : (mcw > 9e18 ? (long long)9e18 : (long long)mcw);
-    prm.grad_scale = p->grad_scale;
-    prm.max_depth = p->max_depth;
+    while (pt.shift < 30 && ((int64_t)1 << pt.shift) * kChunkPieces < total_rows)
+        ++pt.shift;
+    const int v = tune(FS_TUNE_TRAIN_SLAB_ROWS);                 // test / tuning override
+    if (v >= 64 && v <= 65536)
+        for (pt.shift = 6; (1 << pt.shift) < v;)
+            ++pt.shift;
+    pt.hb = packed_bits(max_len, pt.max_rows);
+    size_t hist, part;
+    for (int i = first; i < first + n; ++i)
+        pt.bytes += hist_bytes(trainers[i], depth, pt.shift, pt.hb, &hist, &part);
+    return pt;
+}
 
-    const unsigned nt = (unsigned)n_trainers;
-    const unsigned groups = (unsigned)((max_feat + kHistFeats - 1) / kHistFeats);
-    // Bits that hold any curvature sum (rows x longest program bounds it).  The packed form of the
-    // histograms needs room for the gradient sums beside them; beyond 31 bits the wide form is
-    // taken right away.
-    int hb = 1;
-    while (hb < 63 && ((long long)1 << hb) <= (long long)max_len * (long long)max_rows)
-        ++hb;
-    if (hb > 31 || tune(FS_TUNE_TRAIN_PACKED) == 0)              // override: wide form only
-        hb = 0;
+// Enqueues the rounds of a part whose descriptors are at d.
+int train_part(const TrainDesc *d, const Part &pt, int n_rounds, const Params &prm, hipStream_t stream)
+{
+    const unsigned nt = (unsigned)pt.n;
+    const unsigned groups = (unsigned)((pt.max_feat + kHistFeats - 1) / kHistFeats);
+    const int max_rows = pt.max_rows, shift = pt.shift, hb = pt.hb;
     prof_start(kKernTrainOther, stream);
     hipLaunchKernelGGL(train_begin_kernel, dim3(nt), dim3(512), 0, stream, d);
     prof_stop(stream);
     for (int round = 0; round < n_rounds; ++round) {
         prof_start(kKernTrainOther, stream);
-        hipLaunchKernelGGL(train_grad_kernel, dim3((unsigned)((max_prog + (int64_t)kGradThreads - 1) / kGradThreads), nt), dim3(kGradThreads), 0,
+        hipLaunchKernelGGL(train_grad_kernel, dim3((unsigned)((pt.max_prog + (int64_t)kGradThreads - 1) / kGradThreads), nt), dim3(kGradThreads), 0,
                            stream, d, prm.grad_scale, 1);
         prof_stop(stream);
         for (int level = 0; level < std::max(1, prm.max_depth); ++level) {
@@ -1767,7 +1784,7 @@ extern "C" int fs_train_boost(int32_t n_trainers, fs_trainer *const *trainers, i
                 prof_stop(stream);
                 prof_start(kKernTrainSplit, stream);
                 const unsigned waves = n_counted <= 4 ? kSplitWaves : 2;
-                hipLaunchKernelGGL(train_split_kernel, dim3((unsigned)max_feat, (unsigned)n_counted, nt),
+                hipLaunchKernelGGL(train_split_kernel, dim3((unsigned)pt.max_feat, (unsigned)n_counted, nt),
                                    dim3(64 * waves), 2 * waves * kBins * 8,
                                    stream, d, level, shift, hb, prm);
             } else {
@@ -1790,13 +1807,112 @@ extern "C" int fs_train_boost(int32_t n_trainers, fs_trainer *const *trainers, i
                                stream, d, level, prm.max_depth, row_blocks);
             prof_stop(stream);
         }
-        rc = check_launch("training kernels launch");
+        const int rc = check_launch("training kernels launch");
         if (rc != FS_OK)
             return rc;
     }
-    for (int i = 0; i < n_trainers; ++i)
-        trainers[i]->trees_enqueued += n_rounds;
     return FS_OK;
+}
+
+}  // namespace
+
+extern "C" int fs_train_boost(int32_t n_trainers, fs_trainer *const *trainers, int32_t n_rounds,
+                              const fs_train_params *p, void *stream_)
+{
+    hipStream_t stream = (hipStream_t)stream_;
+    int rc = check_batch("fs_train_boost", n_trainers, trainers);
+    if (rc != FS_OK)
+        return rc;
+    if (!p)
+        return fail(FS_EINVAL, "fs_train_boost: params is NULL");
+    if (n_rounds < 0)
+        return fail(FS_EINVAL, "fs_train_boost: n_rounds %d is negative", n_rounds);
+    if (p->max_depth < 0 || p->max_depth > FS_TRAIN_MAX_DEPTH)
+        return fail(FS_EUNSUPPORTED, "fs_train_boost: max_depth=%d outside 0..%d", p->max_depth,
+                    FS_TRAIN_MAX_DEPTH);
+    if (!(p->eta > 0.0f) || !(p->lambda >= 0.0f) || !(p->grad_scale > 0.0f) || isinf(p->grad_scale) ||
+        isnan(p->min_gain) || isnan(p->min_child_weight))
+        return fail(FS_EINVAL, "fs_train_boost: eta > 0, lambda >= 0, grad_scale > 0 required");
+    int exp2 = 0;
+    if (frexpf(p->grad_scale, &exp2) != 0.5f)
+        return fail(FS_EINVAL, "fs_train_boost: grad_scale must be a power of two");
+    if (n_trainers == 0 || n_rounds == 0)
+        return FS_OK;
+    for (int i = 0; i < n_trainers; ++i) {
+        const fs_trainer *t = trainers[i];
+        if (p->max_depth > t->max_depth)
+            return fail(FS_EUNSUPPORTED, "fs_train_boost: trainer %d was created for max_depth %d", i, t->max_depth);
+        if (t->trees_enqueued + n_rounds > t->max_trees)
+            return fail(FS_EUNSUPPORTED, "fs_train_boost: trainer %d holds %d trees of at most %d", i,
+                        t->trees_enqueued, t->max_trees);
+    }
+    Params prm;
+    prm.eta = (double)p->eta;
+    prm.lambda = (double)p->lambda;
+    prm.min_gain = (double)p->min_gain;
+    prm.inv_scale = 1.0 / (double)p->grad_scale;
+    double mcw = ceil((double)p->min_child_weight);
+    prm.mcw = mcw < 1.0 ? 1 : (mcw > 9e18 ? (long long)9e18 : (long long)mcw);
+    prm.grad_scale = p->grad_scale;
+    prm.max_depth = p->max_depth;
+    try {
+        // Largest families first in every launch: the last workgroups to be dispatched should be the short
+        // ones.  (The order of the descriptors is internal; kernels index by block.)
+        std::vector<fs_trainer *> order(trainers, trainers + n_trainers);
+        std::vector<Part> parts, todo(1, make_part(order.data(), 0, n_trainers, p->max_depth));
+        size_t need = 0;
+        while (!todo.empty()) {                                  // halves of what is too much at a time
+            const Part pt = todo.back();
+            todo.pop_back();
+            if (pt.n > 1 && pt.bytes > most_work()) {
+                todo.push_back(make_part(order.data(), pt.first + pt.n / 2, pt.n - pt.n / 2, p->max_depth));
+                todo.push_back(make_part(order.data(), pt.first, pt.n / 2, p->max_depth));
+                continue;
+            }
+            need = std::max(need, pt.bytes);
+            parts.push_back(pt);
+            std::stable_sort(order.begin() + pt.first, order.begin() + pt.first + pt.n,
+                             [](const fs_trainer *x, const fs_trainer *y) { return x->h.n_rows > y->h.n_rows; });
+        }
+
+        int dev = 0;
+        FS_HIP(hipGetDevice(&dev));
+        if (dev < 0 || dev >= 16)
+            return fail(FS_EUNSUPPORTED, "device ordinal %d not supported", dev);
+        // Everything that can fail for want of memory comes before the first launch: either all trainers
+        // get their rounds or none.
+        std::lock_guard<std::mutex> lock(g_train_mu);
+        BatchBuf &b = g_batch[dev];
+        if (b.work_bytes < need) {                               // an override asks for more than was reserved
+            rc = grow_work(b, need, need);
+            if (rc != FS_OK)
+                return rc;
+        }
+        for (const Part &pt : parts) {
+            char *at = (char *)b.work;
+            for (int i = pt.first; i < pt.first + pt.n; ++i) {
+                TrainDesc &h = order[(size_t)i]->h;
+                size_t hist, part;
+                const size_t bytes = hist_bytes(order[(size_t)i], p->max_depth, pt.shift, pt.hb, &hist, &part);
+                const int planes = hist_planes(order[(size_t)i], pt.hb);
+                h.hist = (unsigned long long *)at;
+                h.hist_plane = (int64_t)hist;
+                h.part = h.hist + planes * hist;
+                h.part_plane = (int64_t)part;
+                at += bytes;
+            }
+        }
+        const TrainDesc *d = nullptr;
+        rc = upload_batch(n_trainers, order.data(), stream, &d);
+        for (size_t i = 0; i < parts.size() && rc == FS_OK; ++i) {
+            rc = train_part(d + parts[i].first, parts[i], n_rounds, prm, stream);
+            for (int k = 0; k < parts[i].n && rc == FS_OK; ++k)
+                order[(size_t)(parts[i].first + k)]->trees_enqueued += n_rounds;
+        }
+        return rc;
+    } catch (const std::bad_alloc &) {
+        return fail(FS_ENOMEM, "out of host memory");
+    }
 }
 
 extern "C" int fs_trainer_size(const fs_trainer *t, int32_t *n_trees, int64_t *n_nodes, void *stream_)
@@ -1846,7 +1962,7 @@ extern "C" int fs_trainer_predictions(const fs_trainer *t, float *row_pred, floa
     std::lock_guard<std::mutex> lock(g_train_mu);
     if (prog_pred) {
         const TrainDesc *d = nullptr;
-        rc = upload_batch(1, &tt, stream, &d);
+        rc = upload_batch(1, &t, stream, &d);
         if (rc != FS_OK)
             return rc;
         hipLaunchKernelGGL(train_grad_kernel, dim3((unsigned)((t->h.n_programs + (int64_t)kGradThreads - 1) / kGradThreads), 1u), dim3(kGradThreads), 0,

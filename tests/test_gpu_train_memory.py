@@ -1,0 +1,82 @@
+"""Memory of training: what the calls allocate and wait for, batches trained in parts, and what is given back."""
+import numpy as np
+import pytest
+
+from paper_2201_00194_amd import workloads as W
+from test_gpu_train import check, same_trees
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def api():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    from paper_2201_00194_amd import api as A
+    return A
+
+
+@pytest.fixture(scope="module")
+def T():
+    from oracle import train_oracle
+    train_oracle.build()
+    return train_oracle
+
+
+def free_bytes():
+    import torch
+    torch.cuda.synchronize()
+    return torch.cuda.mem_get_info()[0]
+
+
+def sets_of(n, n_programs=400, n_features=164, max_cuts=20):
+    return [W.make_train_set(60 + i, n_programs + 37 * i, stmts=(1, 6), n_features=n_features, max_cuts=max_cuts)
+            for i in range(n)]
+
+
+def test_boosting_neither_allocates_nor_waits(api):
+    """Six trainers of depth 10 need more histograms than are kept between jobs; fs_trainer_create makes room for
+    them, so that fs_train_boost only enqueues."""
+    import torch
+    sets = sets_of(6)
+    params = api.train_params(max_depth=10, eta=0.5, lam=1.0)
+    warm = api.fs_trainer.from_train_set(W.make_train_set(1, 50, n_features=5, max_cuts=3), max_depth=2, max_trees=1)
+    api.fs_train_boost([warm], 1, api.train_params(max_depth=2, eta=0.5, lam=1.0))   # kernels and descriptors are there
+    trs = [api.fs_trainer.from_train_set(ts, max_depth=10, max_trees=3) for ts in sets]
+    a = torch.randn(8192, 8192, device="cuda", dtype=torch.bfloat16)
+    b = torch.mm(a, a)
+    side = torch.cuda.Stream()
+    before = free_bytes()
+    busy = torch.cuda.Event()
+    for _ in range(200):                             # 0.1 s of work on the default stream
+        torch.mm(a, a, out=b)
+    busy.record()
+    api.fs_train_boost(trs, 2, params, stream=side)
+    waited = busy.query()
+    assert not waited, "fs_train_boost waited for another stream"
+    torch.cuda.synchronize()
+    assert before - free_bytes() < 16 << 20
+
+
+def test_a_batch_in_parts_trains_like_one(api, T, tune):
+    """Histograms of three trainers at a time at most: eight are trained in four parts, in two calls."""
+    sets = sets_of(8, 300, 33)
+    params = api.train_params(max_depth=6, eta=0.4, lam=1.0)
+    tune(api.FS_TUNE_TRAIN_WORK_MB, 7)
+    trs = [api.fs_trainer.from_train_set(ts, max_depth=6, max_trees=4) for ts in sets]
+    api.fs_train_boost(trs, 2, params)
+    api.fs_train_boost(trs[::-1], 1, params)
+    for ts, tr in zip(sets, trs):
+        exp = T.train(ts.features, ts.prog_off, ts.target, ts.cut_off, ts.cuts, n_rounds=3, max_depth=6, eta=0.4,
+                      lam=1.0)
+        same_trees(tr.export(), exp)
+        assert tr.size()[0] == 3
+
+
+def test_an_override_may_need_more_than_was_reserved(api, T, tune):
+    ts = sets_of(1, 2500, 17, 63)[0]
+    tr = api.fs_trainer.from_train_set(ts, max_depth=5, max_trees=2)
+    tune(api.FS_TUNE_TRAIN_SLAB_ROWS, 64)
+    api.fs_train_boost([tr], 2, api.train_params(max_depth=5, eta=0.4, lam=1.0))
+    exp = T.train(ts.features, ts.prog_off, ts.target, ts.cut_off, ts.cuts, n_rounds=2, max_depth=5, eta=0.4, lam=1.0)
+    same_trees(tr.export(), exp)
