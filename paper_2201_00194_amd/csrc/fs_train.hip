@@ -1373,8 +1373,12 @@ static int packed_bits(int max_len, int max_rows)
     return hb > 31 || tune(FS_TUNE_TRAIN_PACKED) == 0 ? 0 : hb;  // override: wide form only
 }
 
-// Planes of a trainer's histograms (the wide form takes the second).
-static int hist_planes(const fs_trainer *, int) { return 2; }
+// Planes of a trainer's histograms: one where the packed form can never give way to the wide one, as no
+// gradient exceeds 31 bits (quantize).
+static int hist_planes(const fs_trainer *t, int hb)
+{
+    return hb > 0 && hb <= 32 && t->h.n_rows <= (int64_t)1 << (32 - hb) ? 1 : 2;
+}
 
 // Words of the histograms that trees of `depth` levels keep, and of the parts of nodes of several items, in
 // a plane; returns the bytes of all planes.

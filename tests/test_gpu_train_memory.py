@@ -80,3 +80,29 @@ def test_an_override_may_need_more_than_was_reserved(api, T, tune):
     api.fs_train_boost([tr], 2, api.train_params(max_depth=5, eta=0.4, lam=1.0))
     exp = T.train(ts.features, ts.prog_off, ts.target, ts.cut_off, ts.cuts, n_rounds=2, max_depth=5, eta=0.4, lam=1.0)
     same_trees(tr.export(), exp)
+
+
+def test_one_plane_of_histograms_where_the_packed_form_cannot_overflow(api):
+    """Six small families of depth 10 on 164 features: 512 nodes x 164 x 256 bins of eight bytes each."""
+    sets = sets_of(6)
+    before = free_bytes()
+    trs = [api.fs_trainer.from_train_set(ts, max_depth=10, max_trees=1) for ts in sets]
+    assert before - free_bytes() < 1_400_000_000     # 1.03 GB and what the buffer's steps add; two planes: 2.06 GB
+    del trs
+
+
+@pytest.mark.parametrize("packed", [-1, 0])
+@pytest.mark.parametrize("n", [65_535, 65_536])
+def test_both_sides_of_the_second_plane_with_saturated_gradients(api, T, tune, n, packed):
+    """65 535 rows of programs of one row: curvature sums take 16 bits, and gradients at the fixed point's limit
+    add up to just less than the 47 that are left.  With one row more the curvature takes 17 and the wide form
+    may have to step in (here it does).  packed = 0: the wide form, which a trainer was not made for."""
+    ts = W.make_train_set(9, n, stmts=(1, 1), n_features=5, max_cuts=31)
+    ts.target[:] = np.where(ts.features[:, 2] < 0.5, 1e9, np.where(ts.features[:, 0] < 0.3, -1e9, 9e8)).astype(np.float32)
+    params = api.train_params(max_depth=3, eta=0.5, lam=1.0)
+    tr = api.fs_trainer.from_train_set(ts, max_depth=3, max_trees=2)
+    tune(api.FS_TUNE_TRAIN_PACKED, packed)
+    api.fs_train_boost([tr], 2, params)
+    exp = T.train(ts.features, ts.prog_off, ts.target, ts.cut_off, ts.cuts, n_rounds=2, max_depth=3, eta=0.5, lam=1.0,
+                  grad_scale=params.grad_scale)
+    same_trees(tr.export(), exp)
