@@ -79,7 +79,8 @@ int fs_trainer_create(fs_trainer **out, int32_t n_features, const float *feature
 
 /*
  * Free a trainer (NULL allowed).  Synchronise its streams first.  With a device's last trainer the
- * histograms' buffer goes too, unless it is of at most 512 MB: then it stays for the next trainer.
+ * histograms' buffer goes too, unless it is of at most 512 MB: then it stays for the next trainer, or
+ * until a call of this library that creates a model or a trainer or grows scratch runs out of memory.
  */
 void fs_trainer_destroy(fs_trainer *t);
 

@@ -32,6 +32,17 @@ int fail_hip(hipError_t e, const char *what)
     return fail(FS_EDEVICE, "%s: %s", what, hipGetErrorString(e));
 }
 
+hipError_t device_malloc(void **p, size_t bytes)
+{
+    hipError_t e = hipMalloc(p, bytes);
+    int dev = 0;
+    if (e == hipErrorOutOfMemory && hipGetDevice(&dev) == hipSuccess && give_back_training_memory(dev)) {
+        (void)hipGetLastError();
+        e = hipMalloc(p, bytes);
+    }
+    return e;
+}
+
 // ---- per-device state: descriptor ring and scratch ---------------------------------------------
 constexpr int kSlots = 8;
 constexpr int kMaxDevices = 16;
@@ -120,7 +131,7 @@ static int acquire_slot(DeviceCtx *ctx, size_t bytes, Slot **out)
             FS_HIP(hipHostFree(s->h_buf));
         s->d_buf = s->h_buf = nullptr;
         s->cap = 0;
-        FS_HIP(hipMalloc(&s->d_buf, cap));
+        FS_HIP(device_malloc(&s->d_buf, cap));
         FS_HIP(hipHostMalloc(&s->h_buf, cap, hipHostMallocDefault));
         s->cap = cap;
     }
@@ -141,7 +152,7 @@ static int ensure_scratch(DeviceCtx *ctx, int which, size_t floats, bool exact =
     ctx->scratch[which] = nullptr;
     ctx->scratch_floats[which] = 0;
     size_t want = exact ? floats : floats + floats / 4 + 1024;
-    FS_HIP(hipMalloc((void **)&ctx->scratch[which], want * sizeof(float)));
+    FS_HIP(device_malloc((void **)&ctx->scratch[which], want * sizeof(float)));
     ctx->scratch_floats[which] = want;
     return FS_OK;
 }

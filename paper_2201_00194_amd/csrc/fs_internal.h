@@ -309,6 +309,12 @@ int launch_retile(const FamDesc *d_desc, int n_families, int total_blocks, hipSt
 int launch_pack_colblock64(const float *in, int64_t n_rows, int32_t n_features, float *out,
                            hipStream_t stream);
 
+// Frees what training keeps on a device without trainers, for a caller that ran out of device memory; true
+// if there was something (fs_train.hip).
+bool give_back_training_memory(int device);
+// hipMalloc on the current device that does so before it gives up.
+hipError_t device_malloc(void **p, size_t bytes);
+
 // ---- optional per-kernel timing (fs_profile_begin / fs_profile_end) ----------------------------
 enum KernelClass { kKernTraverse = 0, kKernSegsum = 1, kKernTopk = 2, kKernPack = 3,
                    kKernTraverseGlobal = 4, kKernRankCode = 5, kKernTraverseRank = 6,

@@ -581,7 +581,7 @@ hipError_t upload(T **dst, const std::vector<T> &src)
     *dst = nullptr;
     if (src.empty())
         return hipSuccess;
-    hipError_t e = hipMalloc((void **)dst, src.size() * sizeof(T));
+    hipError_t e = device_malloc((void **)dst, src.size() * sizeof(T));
     if (e != hipSuccess)
         return e;
     return hipMemcpy(*dst, src.data(), src.size() * sizeof(T), hipMemcpyHostToDevice);
@@ -620,7 +620,7 @@ hipError_t upload_treelets(const TreeletPlan &tl, void **d_data, TreeletModel **
         cols_at.push_back(room(sp.cols.size() * sizeof(TreeletCol)));
         tables_at.push_back(room(sp.tables.size()));
     }
-    hipError_t e = hipMalloc(d_data, total);
+    hipError_t e = device_malloc(d_data, total);
     if (e != hipSuccess)
         return e;
     uint8_t *base = (uint8_t *)*d_data;

@@ -1305,7 +1305,7 @@ static bool give_back(BatchBuf &b)
     return true;
 }
 
-static bool give_back_training_memory(int device)
+bool give_back_training_memory(int device)
 {
     if (device < 0 || device >= 16)
         return false;

@@ -106,3 +106,36 @@ def test_both_sides_of_the_second_plane_with_saturated_gradients(api, T, tune, n
     exp = T.train(ts.features, ts.prog_off, ts.target, ts.cut_off, ts.cuts, n_rounds=2, max_depth=3, eta=0.5, lam=1.0,
                   grad_scale=params.grad_scale)
     same_trees(tr.export(), exp)
+
+
+def test_what_is_kept_is_given_back_where_memory_runs_out(api):
+    """After the last trainer up to 512 MB stay.  A trainer, a scratch reservation or a model that is refused for
+    want of memory has first taken them."""
+    ts = W.make_train_set(3, 300, stmts=(1, 4), n_features=164, max_cuts=15)
+
+    def keep():
+        tr = api.fs_trainer.from_train_set(ts, max_depth=10, max_trees=1)
+        api.fs_train_boost([tr], 1, api.train_params(max_depth=10, eta=0.5, lam=1.0))
+        free_bytes()
+        tr.destroy()
+        return free_bytes()
+
+    def refused(call):
+        with pytest.raises(api.FsError) as e:
+            call()
+        assert e.value.code == api.FS_ENOMEM
+
+    huge = 1 << 45                                   # 32 TB
+    refused(lambda: api.fs_workspace_reserve(huge, 0))           # (the scratch of before is gone now)
+    for call in (lambda: api.fs_trainer.from_train_set(ts, max_depth=10, max_trees=1 << 30),
+                 lambda: api.fs_workspace_reserve(huge, 0)):
+        kept = keep()
+        refused(call)
+        assert free_bytes() - kept > 150 << 20
+    # a trainer alive keeps its buffer
+    tr = api.fs_trainer.from_train_set(ts, max_depth=10, max_trees=2)
+    alive = free_bytes()
+    refused(lambda: api.fs_workspace_reserve(huge, 0))
+    assert free_bytes() - alive < 16 << 20
+    api.fs_train_boost([tr], 2, api.train_params(max_depth=10, eta=0.5, lam=1.0))
+    assert tr.size()[0] == 2
