@@ -911,8 +911,12 @@ train_hist_kernel(const TrainDesc *__restrict__ descs, int level, int shift, int
 
 // One workgroup per (counted node, feature): the wavefronts add up the node's parts if it has several,
 // then one searches the node's cuts and another its sibling's, whose histogram takes the parent's place.
-// Four wavefronts where a node may have many parts, else two.
+// Two wavefronts; four where the launch has so few workgroups, of nodes near the root with many parts each, that
+// the adding up is a latency: a round of 65 000 rows of depth 6 takes 164.8 us against 166.4, of 255 000 239.6
+// against 242.0.  In batches they only hold others up: eight families of 30 000 rows 299.7 against 295.7, five of
+// 25 000 to 100 000 268.5 against 266.3.
 constexpr int kSplitWaves = 4;
+constexpr int kSplitWideNodes = 4;
 
 template <bool PACKED>
 __device__ __forceinline__ void split_run(const TrainDesc &d, const Params &prm, unsigned long long *lds,
@@ -1162,7 +1166,11 @@ __device__ __forceinline__ void emit_tree(const TrainDesc &d)
 //
 // A workgroup counts its rows up in the node's segment with one atomic where all are of one node, as
 // near the root; those of 1000 workgroups on one address are a chain.  Workgroups of 512 for up to
-// 65536 rows (25 500 rows: 4.7 us against 5.4 with 1024), of 1024 above (255 000 rows: 7.4 against 8.5).
+// 65536 rows, of 1024 above, by the largest family of a batch, which its launches wait for.  A round of
+// depth 6 and 9 in us, 512 against 1024: 8000 rows 135.8 / 258.8 against 137.9 / 260.9, 25 000 146.0 / 272.7
+// against 147.3 / 276.7, 65 000 167.8 / 305.6 against 168.3 / 306.7, 100 000 176.8 / 322.8 against 174.8 / 321.0,
+// 255 000 260.8 / 425.8 against 251.4 / 417.4; eight families of 30 000 302.6 / 1047 against 301.2 / 1049, of
+// 8000 and one of 200 000 318.2 / 1018 against 309.4 / 1013.
 constexpr int kPartThreads = 1024;
 constexpr int kPartRowsSmall = 65536;
 
@@ -1787,7 +1795,7 @@ int train_part(const TrainDesc *d, const Part &pt, int n_rounds, const Params &p
                                    stream, d, level, shift, hb, (int)groups);
                 prof_stop(stream);
                 prof_start(kKernTrainSplit, stream);
-                const unsigned waves = n_counted <= 4 ? kSplitWaves : 2;
+                const unsigned waves = n_counted * nt <= kSplitWideNodes ? kSplitWaves : 2;
                 hipLaunchKernelGGL(train_split_kernel, dim3((unsigned)pt.max_feat, (unsigned)n_counted, nt),
                                    dim3(64 * waves), 2 * waves * kBins * 8,
                                    stream, d, level, shift, hb, prm);
