@@ -81,8 +81,9 @@ static double split_gain(int64_t GL, int64_t HL, int64_t G, int64_t H, double in
 /*
  * Train n_rounds trees.  X is row-major n_rows x n_features.  cuts of feature f are
  * cuts[cut_off[f] .. cut_off[f+1]).  Outputs: the trees in the flat arrays the scoring
- * oracle reads (tree_off has n_rounds+1 entries; node arrays hold up to node_cap nodes),
- * the final row outputs and program sums, and the loss before every round and after the
+ * oracle reads (tree_off has n_rounds+1 entries; node arrays hold up to node_cap nodes).
+ * Row outputs start at `bias`, or at start[] (those of trees trained before) if it is not NULL.  Further
+ * outputs: the final row outputs and program sums, and the loss before every round and after the
  * last (n_rounds+1 doubles).  Returns 0, or -1 on bad arguments / too small node_cap /
  * allocation failure.
  */
@@ -91,7 +92,7 @@ int fso_train(int32_t n_features, int64_t n_rows, const float *X, const int32_t 
               const float *cuts, float bias, int32_t n_rounds, int32_t max_depth, float eta,
               float lambda, float min_gain, float min_child_weight, float grad_scale,
               int32_t *tree_off, int32_t *split_feature, float *threshold, int32_t *left,
-              int32_t *right, float *value, int64_t node_cap, float *row_pred,
+              int32_t *right, float *value, int64_t node_cap, const float *start, float *row_pred,
               float *prog_pred, double *loss)
 {
     if (n_rows < 1 || n_programs < 1 || n_features < 1 || max_depth < 0 || n_rounds < 0)
@@ -122,7 +123,7 @@ int fso_train(int32_t n_features, int64_t n_rows, const float *X, const int32_t 
         return -1;
 
     for (int64_t r = 0; r < n_rows; ++r)
-        row_pred[r] = bias;
+        row_pred[r] = start ? start[r] : bias;
     for (int32_t p = 0; p < n_programs; ++p)
         for (int64_t r = prog_off[p]; r < prog_off[p + 1]; ++r)
             h_row[r] = prog_off[p + 1] - prog_off[p];

@@ -40,7 +40,7 @@ def _load():
                                   i32p, f32p, ctypes.c_float, ctypes.c_int32, ctypes.c_int32,
                                   ctypes.c_float, ctypes.c_float, ctypes.c_float, ctypes.c_float,
                                   ctypes.c_float, i32p, i32p, f32p, i32p, i32p, f32p,
-                                  ctypes.c_int64, f32p, f32p, f64p]
+                                  ctypes.c_int64, f32p, f32p, f32p, f64p]
         lib.fso_train.restype = ctypes.c_int
         lib.fso_bins.argtypes = [ctypes.c_int32, ctypes.c_int64, f32p, i32p, f32p, i32p]
         lib.fso_bins.restype = None
@@ -66,7 +66,8 @@ class Trained:
 
 
 def train(X, prog_off, target, cut_off, cuts, *, bias=0.0, n_rounds=1, max_depth=6, eta=0.3,
-          lam=1.0, min_gain=0.0, min_child_weight=1.0, grad_scale=float(1 << 20)) -> Trained:
+          lam=1.0, min_gain=0.0, min_child_weight=1.0, grad_scale=float(1 << 20), start=None) -> Trained:
+    """`start`: row outputs of the trees trained before (instead of `bias`); only the new trees are returned."""
     lib = _load()
     X = np.ascontiguousarray(X, dtype=np.float32)
     n_rows, n_features = X.shape
@@ -84,6 +85,9 @@ def train(X, prog_off, target, cut_off, cuts, *, bias=0.0, n_rounds=1, max_depth
     le = np.zeros(cap, np.int32)
     ri = np.zeros(cap, np.int32)
     va = np.zeros(cap, np.float32)
+    if start is not None:
+        start = np.ascontiguousarray(start, dtype=np.float32)
+        assert start.shape == (n_rows,)
     row_pred = np.zeros(n_rows, np.float32)
     prog_pred = np.zeros(n_programs, np.float32)
     loss = np.zeros(n_rounds + 1, np.float64)
@@ -93,7 +97,7 @@ def train(X, prog_off, target, cut_off, cuts, *, bias=0.0, n_rounds=1, max_depth
                        min_child_weight, grad_scale, _p(tree_off, ctypes.c_int32),
                        _p(sf, ctypes.c_int32), _p(th, ctypes.c_float), _p(le, ctypes.c_int32),
                        _p(ri, ctypes.c_int32), _p(va, ctypes.c_float), cap,
-                       _p(row_pred, ctypes.c_float), _p(prog_pred, ctypes.c_float),
+                       None if start is None else _p(start, ctypes.c_float), _p(row_pred, ctypes.c_float), _p(prog_pred, ctypes.c_float),
                        _p(loss, ctypes.c_double))
     if rc != 0:
         raise ValueError("fso_train rejected its arguments")

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 from paper_2201_00194_amd import workloads as W
-from test_gpu_train import check
+from test_gpu_train import check, same_trees
 
 pytestmark = pytest.mark.gpu
 
@@ -60,7 +60,11 @@ def test_second_boost_goes_deeper_and_a_family_without_a_split(api, T):
         n = int(first.tree_off[1])
         assert int(got[0][1]) == n and np.array_equal(got[1][:n], first.split_feature)
         assert np.array_equal(got[5][:n].view(np.uint32), first.value.view(np.uint32))
-        # the later trees through the outputs they leave: the rows' walk of all trees, in their order
+        then = T.train(s.features, s.prog_off, s.target, s.cut_off, s.cuts, n_rounds=2, max_depth=10, eta=0.4, lam=0.0,
+                       start=first.row_pred)
+        later = [a[n:] for a in got[1:]]
+        same_trees([got[0][1:] - n] + later, then)
+        # and through the outputs they leave: the rows' walk of all trees, in their order
         to, sf, th, le, ri, va = got
         out = np.zeros(s.n_rows, np.float32)
         for t in range(len(to) - 1):

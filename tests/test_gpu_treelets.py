@@ -124,7 +124,8 @@ def test_the_call_chooses_between_the_walks(api, oracle, tune, capfd, shape, lay
 @pytest.mark.parametrize("layout", [0, 1])
 def test_one_call_with_every_walk(api, oracle, layout):
     """Families whose models have both walks beside some that have one: 230 features (re-tiled where row-major),
-    24 (not), perfect trees that stay treelets, ranked ones, and a model that only the global walk takes."""
+    24 (not), perfect trees that stay treelets, ranked ones, more than 255 features by treelets and, with few trees,
+    from global memory."""
     fams = [family(8200 + i, n, (1, 3), special=True, **c) for i, (n, c) in enumerate([
         (90, dict(n_trees=45, depth=12, q=0.35, n_features=230)),
         (70, dict(n_trees=32, depth=8, q=0.35, n_features=24)),
@@ -132,6 +133,7 @@ def test_one_call_with_every_walk(api, oracle, layout):
         (120, dict(n_trees=60, depth=8, q=0.0, n_features=64)),
         (65, dict(n_trees=20, depth=9, q=0.0, n_features=64)),
         (40, dict(n_trees=5, depth=6, q=0.2, n_features=300)),
+        (130, dict(n_trees=32, depth=4, q=0.0, n_features=300)),
         (33, dict(n_trees=20, depth=5, q=0.2, n_features=131))])]
     devs = run_families(api, fams, layout)
     for f, d in zip(fams, devs):

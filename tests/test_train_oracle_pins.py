@@ -128,6 +128,20 @@ def test_loss_never_increases_with_multi_statement_programs(T):
     assert r.loss[-1] < 0.2 * r.loss[0]
 
 
+def test_training_on_from_the_outputs_so_far_is_training_on(T):
+    ts = W.make_train_set(7, 200, stmts=(1, 6), n_features=9, max_cuts=15)
+    args = (ts.features, ts.prog_off, ts.target, ts.cut_off, ts.cuts)
+    kw = dict(max_depth=4, eta=0.5, lam=1.0)
+    whole = T.train(*args, n_rounds=5, bias=0.25, **kw)
+    two = T.train(*args, n_rounds=2, bias=0.25, **kw)
+    rest = T.train(*args, n_rounds=3, start=two.row_pred, **kw)
+    n = int(two.tree_off[-1])
+    assert np.array_equal(whole.tree_off[2:] - n, rest.tree_off)
+    assert np.array_equal(whole.split_feature[n:], rest.split_feature)
+    assert np.array_equal(whole.value[n:].view(np.uint32), rest.value.view(np.uint32))
+    assert np.array_equal(whole.row_pred.view(np.uint32), rest.row_pred.view(np.uint32))
+
+
 def test_exported_trees_score_like_the_trainer_itself(T, oracle):
     """The scoring oracle walking the exported arrays (x < threshold) must land every row where
     the trainer put it (bin < cut): two independent code paths, bit-identical sums."""
