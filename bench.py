@@ -74,8 +74,8 @@ def parse():
     return ap.parse_args()
 
 
-TRAVERSAL_SOURCES = ("fs_internal.h", "fs_lds.h", "fs_model.hip", "fs_rank.hip", "fs_treelet.h",
-                     "fs_treelet.hip", "fs_treelet_pack.hip", "fs_traverse_lds.hip")
+TRAVERSAL_SOURCES = ("fs_forms.h", "fs_internal.h", "fs_lds.h", "fs_model.hip", "fs_rank.hip", "fs_treelet.h",
+                     "fs_treelet.hip", "fs_treelet_pack.h", "fs_treelet_pack.hip", "fs_traverse_lds.hip")
 
 
 def source_digest() -> str:

@@ -38,8 +38,8 @@
  *     synchronised, the old buffer freed and a larger one allocated.  A caller that has
  *     reserved enough (fs_workspace_bytes, fs_topk_workspace_bytes, fs_workspace_reserve)
  *     never gets here;
- *   - the call's descriptors (280 bytes per family, 56 per top-k workgroup) exceed 20 KB
- *     (about 70 families or 360 top-k workgroups).  Up to that size they travel as kernel
+ *   - the call's descriptors (248 bytes per family, 56 per top-k workgroup) exceed 20 KB
+ *     (82 families or 365 top-k workgroups).  Up to that size they travel as kernel
  *     arguments; beyond it they are staged through a ring of 8 pinned slots per device: a
  *     slot grows when it is too small, and the ninth such submission waits until the first
  *     has finished on the device.
@@ -76,9 +76,10 @@ enum {
 enum {
     FS_ROWMAJOR = 0,   /* x[r][j] at r*n_features + j.  Accepted everywhere.  The kernels that
                           first touch the features read it themselves where they can (rank-coded
-                          models always; other LDS-staged models when n_features is a multiple
-                          of 4): 10-20 % slower than FS_COLBLOCK64.  Otherwise the library
-                          re-tiles the matrix into its scratch first (one extra pass)           */
+                          and treelet walks always; the LDS-staged walk when n_features is a
+                          multiple of 4).  Otherwise the library re-tiles the matrix into its
+                          scratch first (one extra pass).  Most calls take 0-80 % longer than
+                          with FS_COLBLOCK64                                                    */
     FS_COLBLOCK64 = 1  /* tiles of 64 rows, feature-major inside a tile:
                           x[r][j] at (r/64)*n_features*64 + j*64 + (r%64);
                           the last tile is padded to 64 rows (padding content is ignored);
@@ -155,7 +156,8 @@ typedef struct fs_family {
  * FS_EDEVICE (scratch growth, launch failure).
  * The library keeps one scoring scratch buffer per device (row scores of families that pass
  * row_score == NULL, rank tiles of models it rank-codes, re-tiled copies of row-major
- * input) which all fs_score_families calls on the device share: two such calls must not
+ * input -- counted for up to 2048 tiles where a shorter call of the same models may take the walk
+ * that needs them) which all fs_score_families calls on the device share: two such calls must not
  * overlap in time on different streams.  fs_topk has a scratch region of its own, so a
  * scoring call and a top-k call on unrelated data may overlap.
  */
@@ -282,7 +284,7 @@ enum {
     FS_TUNE_LDS_MODE = 1,         /* 1: half-LDS workgroups (two per compute unit), 2: full         */
     FS_TUNE_RANK = 2,             /* 0: never rank-code a model, 1: whenever its trees allow        */
     FS_TUNE_RANK_TILES = 3,       /* 1, 2, 3, 4 or 6: tiles per workgroup of the rank traversal     */
-    FS_TUNE_VERBOSE = 4,          /* 1: fs_model_create reports its plan on stderr                  */
+    FS_TUNE_VERBOSE = 4,          /* 1: fs_model_create and fs_score_families report on stderr      */
     FS_TUNE_TRAIN_SLAB_ROWS = 5,  /* 64..65536: rows per histogram workgroup, up to a power of two  */
     FS_TUNE_TRAIN_SORT = 6,       /* accepted, no effect: rows are always grouped by node           */
     FS_TUNE_TRAIN_PACKED = 7,     /* 0: separate 64-bit gradient / curvature sums only              */
@@ -290,7 +292,8 @@ enum {
                                      row (automatic: 1..4 by the length of the launch)             */
     FS_TUNE_TREELET = 9,          /* 0: never walk byte-rank treelets, 1: whenever the model fits them */
     FS_TUNE_TREELET_FORM = 10,    /* 0: two 4-tile workgroups per compute unit, 1 / 2 / 3: 4 / 2 / 1
-                                     tiles shared by 12 wavefronts (read by fs_score_families)     */
+                                     tiles shared by 12 wavefronts (read by fs_score_families; models
+                                     that have the LDS-staged walk too then walk treelets)         */
     FS_TUNE_TRAIN_WORK_MB = 11,   /* 1..: histogram memory a batch may take before it is trained in
                                      parts, MB (automatic: 16 384)                                 */
     FS_TUNE_OPTIONS = 12
@@ -301,7 +304,7 @@ int32_t fs_tune_get(int32_t option);   /* current override, -1 = automatic */
 /* ---- per-kernel timing (measurement aid) ----------------------------------------------------- */
 
 /* Kernel classes reported by fs_profile_end. */
-enum { FS_KERNEL_TRAVERSE = 0,        /* LDS-staged traversal (the hot kernel)               */
+enum { FS_KERNEL_TRAVERSE = 0,        /* treelet and LDS-staged traversals (the hot kernels)   */
        FS_KERNEL_SEGSUM = 1, FS_KERNEL_TOPK = 2, FS_KERNEL_PACK = 3,
        FS_KERNEL_TRAVERSE_GLOBAL = 4, /* traversal from global memory (models/layouts that
                                          the LDS kernel does not take)                       */

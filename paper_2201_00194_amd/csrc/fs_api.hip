@@ -340,8 +340,8 @@ extern "C" int64_t fs_colblock64_floats(int64_t n_rows, int32_t n_features)
 // 1 us of fetch latency per group; the price is a coarser tail at the end of the launch, half a
 // workgroup's time on average.  With R rounds of groups per compute unit and t us per group,
 // G groups per workgroup save R (1 - 1/G) us and cost G t / 2 us: best at G = sqrt(2 R / t).
-// Measured (traversal of configs[3] at full / half / quarter size, configs[4], the foresee
-// step; best G and what it gains): 4 (-3.3 %), 4-6 (-1.6 %), 2-3 (-0.7 %), 1 (any G > 1 loses,
+// Measured (traversal of thirty families of power-law size at full / half / quarter size, 64 families of
+// deep trees, the foresee step; best G and what it gains): 4 (-3.3 %), 4-6 (-1.6 %), 2-3 (-0.7 %), 1 (any G > 1 loses,
 // 51 us per group), 6 (-2.6 %; 4: -1.8 %).
 constexpr int kLdsMaxGroupsPerWg = 4;
 

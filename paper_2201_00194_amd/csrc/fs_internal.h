@@ -114,7 +114,7 @@ struct fs_model {
     uint16_t *d_slot_ids;  // caller's local node id per 4-byte slot (leaves only meaningful)
     size_t image_bytes;
     // Rank-coded format (deep perfect trees): features become 16-bit ranks among the model's
-    // own thresholds of that feature, nodes shrink to 4 bytes (see fs_traverse_rank.hip)
+    // own thresholds of that feature, nodes shrink to 4 bytes (see fs_rank.hip)
     bool rank_ok;
     int32_t rk_depth;          // common depth of the trees
     int32_t rk_tiles;          // 64-row tiles per workgroup

@@ -675,7 +675,8 @@ Wins treelet_wins(const fs_model *m)
             least = std::min(least, tl / lds);
             most = std::max(most, tl / lds);
         }
-    return least > 1.0 ? kNever : most < 0.95 ? kAlways : kSometimes;
+    // (row-major rows of an odd number of features, not looked at here, are mostly the treelets')
+    return least > 1.0 && lds_reads_rowmajor(m) ? kNever : most < 0.95 ? kAlways : kSometimes;
 }
 
 }  // namespace

@@ -38,7 +38,9 @@ constexpr int kTreeletMaxCols = 255;
 constexpr uint32_t kTreeletNanRank = 254;     // >= every threshold's rank: NaN goes right
 constexpr int kTreeletLds = 80 * 1024;        // two workgroups per compute unit
 constexpr int kTreeletLdsWhole = 160 * 1024;
-constexpr int kTreeletTablePad = 16384;       // the coder moves tables of up to eight columns in whole KB
+// The coder moves the tables of a batch, up to 16 columns, in whole KB: what it reads behind the last column's.
+// Twelve such batches have to fit the LDS of a compute unit, or the coder takes narrower ones.
+constexpr int kTreeletTablePad = 16384;
 constexpr int kTreeletMaxSegments = 16;
 // Estimated clocks of a compute unit, per 64-row tile: coding a column, a step (two levels) of a tree,
 // a chunk's barriers.
@@ -55,6 +57,7 @@ constexpr int kTreeletMaxTrees = 4 * kTreeletRound;
 constexpr int kTreeletPairBuf = 40 * 1024;
 constexpr int kTreeletSumBytes = 2048;
 constexpr int kTreeletWholeBuf = 48 * 1024;
+static_assert(kTreeletLdsWhole / 12 + 1024 <= kTreeletTablePad, "a batch of tables that starts at the last column");
 static_assert(kTreeletLdsWhole - kTreeletMaxCols * 256 >= kTreeletWholeBuf + kTreeletMaxTrees * 1024,
               "a chunk and its value rows fit beside the widest columns");
 

@@ -3,17 +3,17 @@
 // One kernel does both halves of the work on a workgroup's 64-row tiles:
 //   1. coding: every column's fp32 values -> ranks among the model's own thresholds, one byte
 //      each, into LDS;
-//   2. the walk: every lane owns a row and walks eight trees side by side, two levels per step,
-//      through treelets that stream through LDS in chunks; the leaf values are added in tree
+//   2. the walk: every lane owns a row and walks four to twelve trees side by side, two levels per
+//      step, through treelets that stream through LDS in chunks; the leaf values are added in tree
 //      order, so the row score has the bits of a plain sequential sum.
 //
 // Why this form.  The walk over fp32 tiles and 8-byte nodes (fs_traverse_lds.hip) is bound by LDS
 // instructions, two per level, and its tiles leave room for two per compute unit, so that the
 // leaf values of a chunk have to be parked and summed behind a barrier.  With one byte per value
-// four tiles take the room of one, a wavefront has a tile to itself and adds its values from
-// registers; a treelet entry covers two levels in the eight bytes of one node: three LDS and about
-// eight vector instructions per two levels instead of four and eight, conflict-free feature reads,
-// and a chunk holds four times the trees.
+// four tiles take the room of one; in long launches two wavefronts share a tile, each with half of a
+// chunk's trees, and add their values from registers in turn.  A treelet entry covers two levels in
+// the eight bytes of one node: three LDS and about eight vector instructions per two levels instead
+// of four and eight, conflict-free feature reads, and a chunk holds four times the trees.
 #include "fs_internal.h"
 #include "fs_lds.h"
 #include "fs_treelet.h"
@@ -465,13 +465,15 @@ static __device__ __forceinline__ void fetch_chunk(const TreeletModel &m, const 
 
 // Long launches: four tiles and eight wavefronts; two workgroups share a compute unit, so that one
 // walks while the other codes or waits at a barrier.  Two wavefronts share a tile: the first walks
-// the front half of a chunk's trees, the second the back half (at most kPairWalks each, side by
+// the front half of a chunk's trees, the second the back half (in rounds of kTreeletRound, side by
 // side).  The row's running sum goes to and fro between them through LDS: the first adds its values
 // before the barrier that ends the walks, the second behind it, while the next chunk, which waits
 // in registers, is being stored; a second barrier publishes both.  (One wavefront per tile needs no
-// hand-over, but eight wavefronts per compute unit leave the vector units half idle: 3.15 ms on
-// configs[3] against 2.30 ms; the float-threshold kernel took 3.62 ms there.  Vector issue bounds this
-// kernel now: about four fifths of its clocks, a quarter of them for the coding.)
+// hand-over, but eight wavefronts per compute unit leave the vector units half idle: 3.15 ms on thirty
+// families of power-law size, 200 irregular trees of depth 8, against 2.30 ms; the float-threshold kernel took
+// 3.62 ms there.)  Vector issue bounds this kernel: there it issues 1.05e9 vector instructions, which at four
+// clocks are 77 % of the SIMDs' clocks, and 3.2e8 LDS instructions, which with their bank conflicts keep the
+// LDS busy for 32 % of them.
 // LDS: [columns][chunk][running sums of the tiles, by hand-over]; the coder's tables are where the
 // chunks will be.
 constexpr int kPairTiles = 4;

@@ -82,7 +82,7 @@ struct TreeletPlan {
     int most_cols = 0, buf_bytes = 0, max_trees = 0;
     bool pair_ok = false;         // a chunk buffer fits beside the columns in half a compute unit's LDS
     double cost = 0.0;            // clocks of a compute unit per 64-row tile, estimated
-    float us[2][kTreeletForms];   // a round of a launch, estimated: fs_model::tl_us
+    float us[2][kTreeletForms] = {};   // a round of a launch, estimated: fs_model::tl_us
 };
 
 // What a plan may not exceed, found out as early as possible.
