@@ -5,10 +5,11 @@
 // launch shows in full) and every walk of a chunk takes the steps of its deepest tree; the LDS walk pays
 // for every level and for eight times the LDS reads.  Which one wins depends on layout and length of the call.
 // Fitted to 597 models of 32 to 500 irregular or perfect trees of depth 4 to 12 on 24 to 250 features, 5 to
-// 16 000 tiles, both layouts; the estimates are off by 3 to 8 % (rms).  Over 5200 calls of other models (36 to
-// 420 trees, 40 to 240 features, 8 to 5000 tiles) treelets alone are slower than the LDS walk by more than 10 % in
-// 804, by up to 2.97 times; the walk chosen here in 10, by up to 1.21, and it is slower than treelets by
-// more than 10 % in 38, by up to 1.24.
+// 16 000 tiles, both layouts; the estimates are off by 3 to 8 % (rms).  Over 9042 calls of other models (36 to
+// 420 trees, 40 to 240 features, 8 to 9000 tiles) treelets alone are slower than the LDS walk by more than 10 % in
+// 1403, by up to 2.86 times; the walk chosen here in 66, by up to 1.27, and it is slower than treelets by
+// more than 10 % in 39, by up to 1.46 (long row-major calls on 240 features).  All calls together take 0.4 % more
+// than with the better walk each time, with treelets alone 4.5 %.
 #ifndef FS_FORMS_H
 #define FS_FORMS_H
 
@@ -40,16 +41,22 @@ inline int treelet_form(int64_t tiles, int n_compute_units)
     return kTreeletPair;
 }
 
-// Times the workgroups of a launch follow one another on a compute unit.  Of two that share a compute unit
-// one alone is the quicker: a last round of up to half the workgroups takes about 0.6 of a full one.
-inline double launch_rounds(double workgroups, int n_compute_units, int side_by_side)
+// Times the workgroups of a launch follow one another on a compute unit, one at a time: they keep in step for
+// some rounds, then they spread.
+inline double launch_rounds(double workgroups, int n_compute_units)
 {
-    const double r = workgroups / ((double)n_compute_units * side_by_side), whole = floor(r);
+    const double r = workgroups / n_compute_units;
+    return r <= 10.0 ? ceil(r) : r + 0.5;
+}
+
+// The same for two at a time.  One alone is the quicker: a last round of up to half the workgroups takes about
+// 0.6 of a full one.
+inline double launch_rounds_of_two(double workgroups, int n_compute_units)
+{
+    const double r = workgroups / (2.0 * n_compute_units), whole = floor(r);
     if (r > 3.0)
         return r + 0.5;
-    if (side_by_side == 2 && whole > 0.0 && r > whole && r <= whole + 0.5)
-        return whole + 0.6;
-    return ceil(r);
+    return whole > 0.0 && r > whole && r <= whole + 0.5 ? whole + 0.6 : ceil(r);
 }
 
 // us of a call whose workgroups take `round_us` each (fs_model::tl_us, averaged over the families).
@@ -57,7 +64,7 @@ inline double treelet_call_us(int form, double round_us, double workgroups, int 
 {
     if (form != kTreeletPair)
         return round_us;                             // such launches fit the chip
-    return 11.0 + round_us * launch_rounds(workgroups, n_compute_units, 2);
+    return 11.0 + round_us * launch_rounds_of_two(workgroups, n_compute_units);
 }
 
 // Fetches of a tile group in the LDS walk: one per tile; row-major a part of a tile's rows at a time, as many as
@@ -75,10 +82,10 @@ inline double lds_call_us(int form, bool rowmajor, double group_us, double fetch
 {
     struct Term { double call, fetch, feature; };
     static const Term terms[2][kTreeletForms] = {
-        {{8.4, 0.22, 0.0077}, {5.7, 0.58, 0.0066}, {7.8, 0.0, 0.0029}, {7.2, 0.0, 0.0025}},
+        {{8.3, 0.2, 0.0079}, {5.7, 0.58, 0.0066}, {7.8, 0.0, 0.0029}, {7.2, 0.0, 0.0025}},
         {{7.0, 1.46, 0.0109}, {6.2, 1.58, 0.01}, {6.8, 1.4, 0.0079}, {5.8, 1.46, 0.0079}}};
     const Term &t = terms[rowmajor][form];
-    return t.call + launch_rounds(groups, n_compute_units, 1) *
+    return t.call + launch_rounds(groups, n_compute_units) *
                         (0.84 * group_us + t.fetch * fetches + t.feature * group_features);
 }
 

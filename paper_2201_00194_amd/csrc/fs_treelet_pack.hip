@@ -254,11 +254,11 @@ void estimate_rounds(int n_features, TreeletPlan *p)
     struct Spread { int tiles; double call, segment, col, wide, narrow, chunk, step, tree_step; };
     static const Spread spread[2][kTreeletForms] = {
         {{0, 0, 0, 0, 0, 0, 0, 0, 0},
-         {4, 3.8, 4.55, 0.057, 0.1, 0.21, 0.76, 0.053, 0.0185},
+         {4, 3.6, 4.3, 0.054, 0.1, 0.2, 0.72, 0.05, 0.0177},
          {2, 4.9, 3.8, 0.0217, 0.4, 0.27, 0.544, 0.12, 0.0067},
          {1, 5.3, 2.85, 0.0105, 1.35, 0.49, 0.31, 0.206, 0.0026}},
         {{0, 0, 0, 0, 0, 0, 0, 0, 0},
-         {4, 3.0, 5.05, 0.091, 0.0, 0.6, 0.74, 0.056, 0.019},
+         {4, 2.8, 4.6, 0.083, 0.0, 0.55, 0.67, 0.051, 0.0173},
          {2, 5.2, 3.7, 0.024, 0.4, 0.52, 0.54, 0.123, 0.0068},
          {1, 5.3, 2.85, 0.0105, 1.35, 0.52, 0.31, 0.206, 0.0026}}};
     // the pair form: a column by how many a wavefront codes at a time (4, 2, 1); row-major more the longer a
