@@ -472,8 +472,8 @@ static __device__ __forceinline__ void fetch_chunk(const TreeletModel &m, const 
 // hand-over, but eight wavefronts per compute unit leave the vector units half idle: 3.15 ms on thirty
 // families of power-law size, 200 irregular trees of depth 8, against 2.30 ms; the float-threshold kernel took
 // 3.62 ms there.)  Vector issue bounds this kernel: there it issues 1.05e9 vector instructions, which at four
-// clocks are 77 % of the SIMDs' clocks, and 3.2e8 LDS instructions, which with their bank conflicts keep the
-// LDS busy for 32 % of them.
+// clocks are 77 % of the SIMDs' clocks, and a compute unit an LDS instruction every 4.3 clocks, where
+// conflict-free ones take 2.4.
 // LDS: [columns][chunk][running sums of the tiles, by hand-over]; the coder's tables are where the
 // chunks will be.
 constexpr int kPairTiles = 4;
