@@ -5,11 +5,12 @@
 // launch shows in full) and every walk of a chunk takes the steps of its deepest tree; the LDS walk pays
 // for every level and for eight times the LDS reads.  Which one wins depends on layout and length of the call.
 // Fitted to 597 models of 32 to 500 irregular or perfect trees of depth 4 to 12 on 24 to 250 features, 5 to
-// 16 000 tiles, both layouts; the estimates are off by 3 to 8 % (rms).  Over 9042 calls of other models (36 to
-// 420 trees, 40 to 240 features, 8 to 9000 tiles) treelets alone are slower than the LDS walk by more than 10 % in
-// 1403, by up to 2.86 times; the walk chosen here in 66, by up to 1.27, and it is slower than treelets by
-// more than 10 % in 39, by up to 1.46 (long row-major calls on 240 features).  All calls together take 0.4 % more
-// than with the better walk each time, with treelets alone 4.5 %.
+// 16 000 tiles, both layouts; the estimates are off by 3 to 8 % (rms).  Timed on 379 models
+// that neither the fit nor a look at its errors used (40 to 350 trees, 32 to 248 features, 12 to 8500 tiles; 8338
+// calls): treelets alone are slower than the LDS walk by more than 10 % in 1694, by up to 2.80 times; the walk
+// chosen here in 27, by up to 1.22, and it is slower than treelets by more than 10 % in 34, by up to 1.18.  The
+// geometric mean over all calls is 0.2 % above the better walk's each time, with treelets alone 6.1 %, with the
+// LDS walk alone 18 %.
 #ifndef FS_FORMS_H
 #define FS_FORMS_H
 

@@ -789,10 +789,11 @@ extern "C" int fs_model_create(fs_model **out, int32_t n_features, int32_t n_tre
                     limits.pair_only = true;
                     limits.cost = 13.5 * (double)n_trees * (double)shapes.max_depth() + 3.0 * (double)n_features;
                 }
-                // Every segment codes the rows anew, the rank walk codes them once.  Perfect trees of depth 8,
-                // 100 to 300 features, 64 to 500 trees, 5 to 6000 tiles in both layouts: with up to 376 columns
-                // in all treelets take 0.26 to 0.97 of the rank walk's time at every length, with 400 (two
-                // segments of 200) 0.85 to 1.09, with 460 to 492 0.77 to 1.25.
+                // Every segment codes the rows anew, the rank walk codes them once.  Time of treelets over the rank
+                // walk's, perfect trees of depth 8, 5 to 16 000 tiles, both layouts, models that the other limits
+                // take: below 400 columns in all 0.20 to 0.98 on 100 to 300 features (32 models, 650 calls); on 24
+                // to 64 features 0.34 to 1.30 (17 models; 11 of 340 calls lose more than 2 %, ten of them of
+                // 24 features); from 400 columns 0.58 to 1.37 (6 models; 33 of 130 calls lose more than 2 %).
                 if (ranks_pay)
                     limits.cols = kTreeletMostRankCols;
             }
