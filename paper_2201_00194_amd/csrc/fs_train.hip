@@ -11,14 +11,16 @@
 // host between rounds):
 //   grad         per program: s_p (row order), g_p, q_p; its rows' records (row, q_p, rows of p)
 //                go back to the root; the root's (G, H) are added up on the way
-//   per level:   hist (LDS histograms of the smaller child of every split node, sixteen features
-//                per workgroup; the larger child is the parent minus the smaller, exactly; a
-//                feature's most frequent bin is never counted, it is the node's total minus the
-//                rest), split (adds up the parts of nodes whose rows were dealt to several workgroups,
-//                subtracts, searches the cuts of both children), pick (per node: best
-//                feature, split or leaf, child ids in breadth-first order), part (records of split
-//                nodes move to their child's segment, rows of leaves take the leaf's value)
-//                (after the last level: heap -> flat model arrays, heap cleared for the next tree)
+//   hist, split  histograms and best cuts of the root
+//   per level:   move (every workgroup decides its node for itself: best feature, split or leaf; the node's
+//                records go to its children's segments, rows of leaves take the leaf's value), hist (LDS
+//                histograms of the child with the smaller curvature, sixteen features per workgroup; the
+//                other child is the parent minus that one, exactly; a feature's most frequent bin is
+//                never counted, it is the node's total minus the rest) or, for few rows, both in one launch
+//                (grow); split (adds up the parts of nodes whose rows were dealt to several workgroups,
+//                subtracts, searches the cuts of both children)
+//   last level:  finish (decides its nodes; rows take the leaves' values)
+//   (one more workgroup of the next round's first hist: heap -> flat model arrays, heap cleared)
 #include <math.h>
 #include <stdlib.h>
 #include <string.h>
@@ -40,23 +42,27 @@ constexpr int kHistFeats = 16;          // features per workgroup: 16 bytes of b
 constexpr int kHistWords = kHistFeats * kBins;
 constexpr int kChunkShiftMin = 10;      // at least 1024 rows to a histogram workgroup: zeroing and storing its LDS
                                         // costs as much as 256 rows
+constexpr int kChunkSmallRows = 12288;  // 2048 in batches of more rows than this: a round of depth 6 of 8500 / 12 700 /
+                                        // 25 500 rows takes 93.9 / 99.8 / 115.0 us with 1024, 95.3 / 98.7 / 107.7 with 2048
 constexpr int kChunkPieces = 96;
 
-// heap node states
-enum { kAbsent = 0, kOpen = 1, kInternal = 2, kLeaf = 3 };
+// heap node states (undecided or not in the tree: absent)
+enum { kAbsent = 0, kInternal = 2, kLeaf = 3 };
 
 // A (node, feature)'s best cut; cut 0 = none is admissible.
 struct __align__(32) Best {
     double gain;
+    int32_t cut;
+    int32_t count_left;        // the left child is the counted one, see counts_left
     long long GL, HL;
-    int32_t cut, pad;
 };
 
-// Best feature of a node, and its cut.
-struct Winner {
-    double gain;
-    long long GL, HL;
-    int32_t feature, cut;     // feature -1: no candidate
+// Sums over all rows of a round.
+struct RootSums {
+    // (lines of their own: every wavefront of the launch adds to each)
+    __align__(128) long long G;
+    __align__(128) long long H;
+    __align__(128) unsigned long long abs_q;   // sum of |gradient| (fixed point)
 };
 
 struct TrainDesc {
@@ -72,7 +78,7 @@ struct TrainDesc {
                                // (it is the node's total minus the other bins)
     float *row_pred;
     float *prog_pred;
-    int4 *rec[2];              // {row, gradient in fixed point, curvature, node} of every row, grouped
+    int4 *rec[2];              // {row, gradient in fixed point, curvature, output so far (bits)} of every row, grouped
                                // by the node of a level; levels alternate between the two
     int4 *seg;                 // per split node of the heap: {rows gone left, rows gone right, first
                                // position, end}; zero if the node is not split.  The left child's
@@ -81,15 +87,13 @@ struct TrainDesc {
     unsigned long long *hist;  // [slot][feature][bin]: complete histograms, what the next level subtracts from
     unsigned long long *part;  // the same of parts of a node, see part_slot
     int64_t hist_plane, part_plane;   // words to the curvature sums (wide form)
-    int32_t *h_state, *h_id;
-    float *h_val;
+    float *h_val;              // leaves of the deepest level
     long long *h_G, *h_H;
     double *h_own;             // the node's own term of the gain
     Best *best;                // [node of the level][feature]
-    int4 *decision;            // per node of the heap: {state, feature, cut, leaf value (bits)}
-    int32_t *counters;         // [0] next node id of the tree in work, [1] trees, [2] nodes
-    unsigned long long *abs_q; // sum over the rows of |gradient| (fixed point) of the round in work
-    Winner *winner;            // per node of a level (levels with many nodes)
+    int4 *decision;            // per node of the heap: {state, feature, -, threshold or leaf value (bits)}
+    int32_t *counters;         // [1] trees, [2] nodes, [3] rows of the longest program
+    RootSums *root;            // two, rounds take them in turn: one is cleared while the other is in use
     int32_t *m_tree_off, *m_feat, *m_left, *m_right;
     float *m_thr, *m_val;
     int64_t r_pad;
@@ -249,26 +253,27 @@ __global__ void train_clear_kernel(uint32_t *count, int n, int32_t *counters, in
 
 // ---- per-round kernels -------------------------------------------------------------------
 
-// The heap of the tree to grow (one workgroup per trainer).  What belongs to a node below the root is
-// written when its parent is split.
-__device__ __forceinline__ void begin_tree(const TrainDesc &d)
+// The heap of the tree to grow and the sums of the round to come (one workgroup per trainer).  What belongs
+// to a node below the root is written when its parent is split.
+__device__ __forceinline__ void begin_tree(const TrainDesc &d, int turn)
 {
-    for (int i = threadIdx.x; i < kHeapNodes; i += blockDim.x)
-        d.h_state[i] = i == 0 ? kOpen : kAbsent;
+    for (int i = threadIdx.x; i < kHeapNodes; i += blockDim.x) {
+        d.decision[i] = make_int4(kAbsent, 0, 0, 0);
+        d.seg[i] = make_int4(0, 0, 0, i == 0 ? d.n_rows : 0);
+    }
     if (threadIdx.x == 0) {
-        d.h_G[0] = 0;
-        d.h_H[0] = 0;
-        d.h_id[0] = 0;
-        d.counters[0] = 1;
         d.h_slot[0] = 0;
-        *d.abs_q = 0ull;
+        d.root[turn] = {0, 0, 0ull};
     }
 }
 
 __global__ void __launch_bounds__(512)
 train_begin_kernel(const TrainDesc *__restrict__ descs)
 {
-    begin_tree(descs[blockIdx.x]);
+    const TrainDesc &d = descs[blockIdx.x];
+    begin_tree(d, 0);
+    if (threadIdx.x == 0)
+        d.root[1] = {0, 0, 0ull};
 }
 
 __device__ __forceinline__ int quantize(float g, float grad_scale)
@@ -284,7 +289,7 @@ __device__ __forceinline__ int quantize(float g, float grad_scale)
 constexpr int kGradThreads = 64;
 
 __global__ void __launch_bounds__(kGradThreads)
-train_grad_kernel(const TrainDesc *__restrict__ descs, float grad_scale, int with_grad)
+train_grad_kernel(const TrainDesc *__restrict__ descs, float grad_scale, int with_grad, int turn)
 {
     const TrainDesc &d = descs[blockIdx.y];
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
@@ -307,7 +312,7 @@ train_grad_kernel(const TrainDesc *__restrict__ descs, float grad_scale, int wit
             const int q = quantize(s - d.target[p], grad_scale);
             const int len = e - b;
             for (int r = b; r < e; ++r)
-                d.rec[0][r] = make_int4(r, q, len, 0);
+                d.rec[0][r] = make_int4(r, q, len, __float_as_int(d.row_pred[r]));
             G = (long long)q * len;
             H = (long long)len * len;
             A = (unsigned long long)(G < 0 ? -G : G);
@@ -322,9 +327,10 @@ train_grad_kernel(const TrainDesc *__restrict__ descs, float grad_scale, int wit
         A += __shfl_down(A, off);
     }
     if ((threadIdx.x & 63) == 0 && H != 0) {
-        atomicAdd((unsigned long long *)&d.h_G[0], (unsigned long long)G);
-        atomicAdd((unsigned long long *)&d.h_H[0], (unsigned long long)H);
-        atomicAdd(d.abs_q, A);
+        RootSums *sums = d.root + turn;
+        atomicAdd((unsigned long long *)&sums->G, (unsigned long long)G);
+        atomicAdd((unsigned long long *)&sums->H, (unsigned long long)H);
+        atomicAdd(&sums->abs_q, A);
     }
 }
 
@@ -400,6 +406,16 @@ __device__ __forceinline__ void best_step(double &best, int &best_cut)
     }
 }
 
+// The counted child of a split node: less curvature, the left one on ties.
+__device__ __forceinline__ int counts_left(long long HL, long long HR) { return HL <= HR ? 1 : 0; }
+
+// Totals of a node; `turn` says which of the root's sums the round uses.
+__device__ __forceinline__ void node_sums(const TrainDesc &d, int node, int turn, long long &G, long long &H)
+{
+    G = node == 0 ? d.root[turn].G : d.h_G[node];
+    H = node == 0 ? d.root[turn].H : d.h_H[node];
+}
+
 // Best cut of feature f for the open node `node`, by one wavefront: lane l holds bins 4l..4l+3
 // (g, h; the feature's most frequent bin holds 0 and is rebuilt here from the node's totals)
 // and forms the left sums of the cuts 4l+1..4l+4.  Lane 0 writes the result for
@@ -413,11 +429,12 @@ __device__ __forceinline__ void best_step(double &best, int &best_cut)
 // round of double-precision divisions instead of four.
 constexpr int kCutScratchBytes = 64 * (8 + 8 + 4);
 
-__device__ __forceinline__ void wave_best_cut(const TrainDesc &d, const Params &prm, int node, int f,
+__device__ __forceinline__ void wave_best_cut(const TrainDesc &d, const Params &prm, int node, int turn, int f,
                                               int pair, int lane, long long (&g)[4], long long (&h)[4],
                                               unsigned char *scratch)
 {
-    const long long G = d.h_G[node], H = d.h_H[node];
+    long long G, H;
+    node_sums(d, node, turn, G, H);
     const int hot = d.hot_bin[f];
     // inclusive prefix sums over the 256 bins, the hot bin still at 0
     const long long lane_g = g[0] + g[1] + g[2] + g[3], lane_h = h[0] + h[1] + h[2] + h[3];
@@ -523,7 +540,7 @@ __device__ __forceinline__ void wave_best_cut(const TrainDesc &d, const Params &
         if (lane == 0)
             d.best[pair].cut = 0;
     } else if (cut == best_cut) {                                // exactly one lane holds the winner
-        d.best[pair] = {gain, bGL, bHL, cut, 0};
+        d.best[pair] = {gain, cut, counts_left(bHL, H - bHL), bGL, bHL};
     }
 }
 
@@ -551,10 +568,11 @@ __device__ __forceinline__ float wave_max_f(float v)
 //    all are evaluated).  The gain itself is that sum minus a term that is the same for all cuts
 //    and at most twice the sum, so a cut that wins after the rounding of double arithmetic is
 //    within 2^-50 of the largest and never dropped.
-__device__ __forceinline__ void wave_best_cut_packed(const TrainDesc &d, const Params &prm, int node, int f,
-                                                     int pair, int lane, unsigned long long (&v)[4], int hb)
+__device__ __forceinline__ void wave_best_cut_packed(const TrainDesc &d, const Params &prm, int node, int turn,
+                                                     int f, int pair, int lane, unsigned long long (&v)[4], int hb)
 {
-    const long long G = d.h_G[node], H = d.h_H[node];
+    long long G, H;
+    node_sums(d, node, turn, G, H);
     const int hot = d.hot_bin[f];
     const int m = d.cut_off[f + 1] - d.cut_off[f];
     const unsigned mask = (1u << hb) - 1u;
@@ -635,46 +653,51 @@ __device__ __forceinline__ void wave_best_cut_packed(const TrainDesc &d, const P
         best_cut = __builtin_amdgcn_readlane(best_cut, 63);
     }
     if (cut != 0 && cut == best_cut)                             // exactly one lane holds the winner
-        d.best[pair] = {gain, bGL, bHL, cut, 0};
+        d.best[pair] = {gain, cut, counts_left(bHL, H - bHL), bGL, bHL};
 }
 
 // Histograms of one level.
 //
-// Of two siblings only the one with fewer rows is counted; the other is the parent's histogram
-// minus it.  All sums are integer sums, so that is exact.  A work item is up to 2^shift rows of
-// one such node; a workgroup takes one item and sixteen features, walks the item's records (grouped by
-// node) and gathers each row's bins, 16 bytes at a time.  Over a tree of depth 8 rows are visited 4.5
-// times instead of 8 and no level streams the rows of other nodes.
+// Of two siblings only the one with less curvature (about the fewer rows) is counted; the other is the
+// parent's histogram minus it.  All sums are integer sums, so that is exact.  A work item is up to 2^shift
+// rows; a workgroup takes one item and sixteen features, walks the item's records and gathers each row's
+// bins, 16 bytes at a time.
 //
-// A node of a single item leaves its histogram in its place of `hist`; the items of larger nodes write
-// their part and train_split_kernel adds the parts up.  (Parts are stored and not added atomically:
+// Two ways.  After train_move_kernel the items are the counted nodes' own records (ALL).  In train_grow_kernel
+// they are the parents', moved by other workgroups of the same launch: every workgroup decides its parent
+// and adds the rows that go to the counted child (a byte gathered from the split feature's column says
+// which).  That saves a launch of dependent loads a level, 5 to 6 us, and visits twice the rows with half of
+// the lanes idle: a round of depth 6 of 2500 / 8500 / 25 500 / 51 000 / 60 500 rows takes 83 / 94 / 108 /
+// 129 / 153 us grown and 99 / 108 / 118 / 129 / 150 moved first (kGrowRows), 255 000 rows 240 and 203.  (Compacting
+// the rows through a queue in LDS instead of leaving lanes idle: 117 us at 25 500 rows, 223 at 255 000.)
+//
+// A node of a single item leaves its histogram in its place of `hist`; the items of larger ones
+// write their part and train_split_kernel adds the parts up.  (Parts are stored and not added atomically:
 // nothing has to be cleared, and the memory-side atomics of eight XCDs are slower than the extra
 // read.)  The cut search is a kernel of its own: in here it held the row loop to 6 wavefronts a
 // SIMD and a node's sixteen features to eight wavefronts; depth 6, 25 500 rows: 15 us for the
 // histograms and cuts of 8 nodes.
 //
 // Bound by the LDS: 64-bit adds of 64 lanes on 32 bank pairs at random take about 20 clocks a wavefront.
-// 255 000 rows of 164 features, per level: 28 us at the root, 14 to 18 below; the former kernel, four
-// features and sixteen nodes of all rows per workgroup, took 145 on average (30 at the root).
 //
 // Two forms of a bin.  Packed: one 64-bit word G * 2^hb + H, fed by one atomic per (row, feature);
 // hb bits hold any curvature sum (the host knows rows x longest program) and the rest holds G as
-// long as the sum of |gradient| over the trainer's rows, which train_grad_kernel leaves in abs_q,
+// long as the sum of |gradient| over the trainer's rows, which train_grad_kernel leaves in `root`,
 // stays below 2^(63-hb).  Wide: G and H in 64 bits each, always safe, eight features at a time in
 // the same LDS; H has a plane of its own in the buffers.  Every kernel of a round decides alike.
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 constexpr int kHistThreads = 512;
+constexpr int64_t kGrowRows = 49152;    // of a batch
 static_assert(kBins * 8 >= kCutScratchBytes, "room for the cut search's scratch");
 
-__device__ __forceinline__ bool is_packed(const TrainDesc &d, int hb)
+__device__ __forceinline__ bool is_packed(const TrainDesc &d, int turn, int hb)
 {
-    return hb > 0 && *d.abs_q < (1ull << (63 - hb));
+    return hb > 0 && d.root[turn].abs_q < (1ull << (63 - hb));
 }
 
-// A node to count (`small`), its sibling, and the part of the node's records an item covers.
-struct Item {
-    int small, large;         // heap indices; large < 0 at the root
-    int pair;                 // number of the parent within its level
+// Records of a node (heap index) and which of its pieces of 2^shift rows a workgroup takes.
+struct Piece {
+    int node;
     int first, count;         // records of the whole node
     int piece;
 };
@@ -690,54 +713,91 @@ __device__ __forceinline__ int wave_prefix_i(int v)
     return v;
 }
 
-// The counted node of a pair, given the parent's segment.
-__device__ __forceinline__ Item counted_node(int parent, int pair, const int4 &s)
+__device__ __forceinline__ int pieces_of(int count, int shift)
 {
-    const int left = 2 * parent + 1;
-    if (s.x <= s.y)
-        return {left, left + 1, pair, s.z, s.x, 0};
-    return {left + 1, left, pair, s.z + s.x, s.y, 0};
+    return (int)(((int64_t)count + (1ll << shift) - 1) >> shift);
 }
 
-// Item number `index` of the level (every wavefront finds it for itself: one 16-byte load per parent
-// and a scan).
-__device__ __forceinline__ bool find_item(const TrainDesc &d, int level, int shift, int index, int lane, Item &it)
+// Piece number `index` of the level's nodes (every wavefront finds it for itself: one 16-byte load per
+// parent and a scan).
+__device__ __forceinline__ bool find_piece(const TrainDesc &d, int level, int shift, int index, int lane, Piece &it)
 {
     if (level == 0) {
-        it = {0, -1, 0, 0, d.n_rows, index};
-        return index < (int)(((int64_t)d.n_rows + (1ll << shift) - 1) >> shift);
+        it = {0, 0, d.n_rows, index};
+        return index < pieces_of(d.n_rows, shift);
     }
     constexpr int kMost = (1 << (FS_TRAIN_MAX_DEPTH - 2)) / 64;   // parents per lane
-    const int n_pairs = 1 << (level - 1);
-    const int per = n_pairs > 64 ? n_pairs / 64 : 1;
-    int items[kMost], sum = 0;
+    const int n_parents = 1 << (level - 1);
+    const int per = n_parents > 64 ? n_parents / 64 : 1;
+    int4 s[kMost];
+    int sum = 0;
 #pragma unroll
     for (int i = 0; i < kMost; ++i) {
-        items[i] = 0;
-        const int pair = lane * per + i;
-        if (i < per && pair < n_pairs) {
-            const int4 s = d.seg[n_pairs - 1 + pair];
-            items[i] = (int)(((int64_t)min(s.x, s.y) + (1ll << shift) - 1) >> shift);
-        }
-        sum += items[i];
+        const int p = lane * per + i;
+        s[i] = i < per && p < n_parents ? d.seg[n_parents - 1 + p] : make_int4(0, 0, 0, 0);
+        sum += pieces_of(s[i].x, shift) + pieces_of(s[i].y, shift);
     }
     const int incl = wave_prefix_i(sum);
     const unsigned long long past = __ballot(incl > index);
     if (past == 0)
         return false;
     const int owner = __builtin_amdgcn_readfirstlane(__ffsll((long long)past) - 1);
-    int rest = index - (incl - sum), pick = -1, piece = 0;
+    int rest = index - (incl - sum);
+    Piece mine = {-1, 0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < kMost; ++i)
+#pragma unroll
+        for (int right = 0; right < 2; ++right) {
+            const int count = right ? s[i].y : s[i].x, n = pieces_of(count, shift);
+            if (mine.node < 0 && rest < n)
+                mine = {2 * (n_parents - 1 + lane * per + i) + 1 + right, s[i].z + (right ? s[i].x : 0), count, rest};
+            rest -= n;
+        }
+    it.node = __builtin_amdgcn_readlane(mine.node, owner);
+    it.first = __builtin_amdgcn_readlane(mine.first, owner);
+    it.count = __builtin_amdgcn_readlane(mine.count, owner);
+    it.piece = __builtin_amdgcn_readlane(mine.piece, owner);
+    return true;
+}
+
+// The same over the counted children of the level.
+__device__ __forceinline__ bool find_counted(const TrainDesc &d, int level, int shift, int index, int lane, Piece &it)
+{
+    if (level == 0) {
+        it = {0, 0, d.n_rows, index};
+        return index < pieces_of(d.n_rows, shift);
+    }
+    constexpr int kMost = (1 << (FS_TRAIN_MAX_DEPTH - 2)) / 64;   // parents per lane
+    const int n_parents = 1 << (level - 1);
+    const int per = n_parents > 64 ? n_parents / 64 : 1;
+    int first[kMost], count[kMost], left[kMost], sum = 0;
 #pragma unroll
     for (int i = 0; i < kMost; ++i) {
-        if (pick < 0 && rest < items[i]) {
-            pick = lane * per + i;
-            piece = rest;
-        }
-        rest -= items[i];
+        const int p = lane * per + i, node = n_parents - 1 + (i < per && p < n_parents ? p : 0);
+        const int4 s = d.seg[node];
+        left[i] = counts_left(d.h_H[2 * node + 1], d.h_H[2 * node + 2]);
+        first[i] = left[i] ? s.z : s.z + s.x;
+        count[i] = i < per && p < n_parents ? (left[i] ? s.x : s.y) : 0;
+        sum += pieces_of(count[i], shift);
     }
-    const int pair = __builtin_amdgcn_readlane(pick, owner);
-    it = counted_node(n_pairs - 1 + pair, pair, d.seg[n_pairs - 1 + pair]);
-    it.piece = __builtin_amdgcn_readlane(piece, owner);
+    const int incl = wave_prefix_i(sum);
+    const unsigned long long past = __ballot(incl > index);
+    if (past == 0)
+        return false;
+    const int owner = __builtin_amdgcn_readfirstlane(__ffsll((long long)past) - 1);
+    int rest = index - (incl - sum);
+    Piece mine = {-1, 0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < kMost; ++i) {
+        const int n = pieces_of(count[i], shift);
+        if (mine.node < 0 && rest < n)
+            mine = {2 * (n_parents - 1 + lane * per + i) + 2 - left[i], first[i], count[i], rest};
+        rest -= n;
+    }
+    it.node = __builtin_amdgcn_readlane(mine.node, owner);
+    it.first = __builtin_amdgcn_readlane(mine.first, owner);
+    it.count = __builtin_amdgcn_readlane(mine.count, owner);
+    it.piece = __builtin_amdgcn_readlane(mine.piece, owner);
     return true;
 }
 
@@ -784,22 +844,29 @@ struct Bins4 {                // four consecutive bins of a lane
 };
 
 // Words of a node's histogram of feature f; at the root and for counted children a place of their own,
-// for the larger child its parent's.
-__device__ __forceinline__ int64_t hist_at(const TrainDesc &d, int level, const Item &it, int which, int f)
+// for the other child its parent's.  `pair`: number of the parent within its level.
+__device__ __forceinline__ int64_t hist_at(const TrainDesc &d, int level, int pair, int which, int f)
 {
     const int n_pairs = level > 0 ? 1 << (level - 1) : 0;
-    const int slot = level == 0 ? 0 : which ? d.h_slot[n_pairs - 1 + it.pair] : n_pairs + it.pair;
+    const int slot = level == 0 ? 0 : which ? d.h_slot[n_pairs - 1 + pair] : n_pairs + pair;
     return ((int64_t)slot * d.n_features + f) * kBins;
 }
 
+// Two siblings: the counted one and the other (-1 at the root).
+struct Pair {
+    int small, large;
+    int pair;                 // number of the parent within its level
+    int first, count;         // records that were dealt out in pieces
+};
+
 // Cuts of one child: `which` = 0 the counted node, 1 its sibling; `own`: the counted node's bins.
 template <bool PACKED>
-__device__ __forceinline__ void search_child(const TrainDesc &d, const Params &prm, int level, const Item &it,
+__device__ __forceinline__ void search_child(const TrainDesc &d, const Params &prm, int level, int turn, const Pair &it,
                                              int which, bool store, int f, int lane, Bins4<PACKED> &own, int hb,
                                              unsigned char *scratch)
 {
     const int node = which ? it.large : it.small;
-    unsigned long long *place = d.hist + hist_at(d, level, it, which, f) + 4 * lane;
+    unsigned long long *place = d.hist + hist_at(d, level, it.pair, which, f) + 4 * lane;
     if (which) {
         Bins4<PACKED> parent;
         parent.load(place, d.hist_plane);
@@ -810,39 +877,217 @@ __device__ __forceinline__ void search_child(const TrainDesc &d, const Params &p
     const int pair = (node - ((1 << level) - 1)) * d.n_features + f;
     if constexpr (PACKED) {
         unsigned long long v[4] = {own.a[0], own.a[1], own.a[2], own.a[3]};
-        wave_best_cut_packed(d, prm, node, f, pair, lane, v, hb);
+        wave_best_cut_packed(d, prm, node, turn, f, pair, lane, v, hb);
     } else {
         long long g[4] = {(long long)own.a[0], (long long)own.a[1], (long long)own.a[2], (long long)own.a[3]};
         long long h[4] = {(long long)own.b[0], (long long)own.b[1], (long long)own.b[2], (long long)own.b[3]};
-        wave_best_cut(d, prm, node, f, pair, lane, g, h, scratch);
+        wave_best_cut(d, prm, node, turn, f, pair, lane, g, h, scratch);
     }
 }
 
-// The children's places in `hist`, for the next level.
-__device__ __forceinline__ void note_slots(const TrainDesc &d, int level, const Item &it)
+// What the next level needs of two siblings: their places in `hist` and their segments, nothing moved yet.
+__device__ __forceinline__ void open_children(const TrainDesc &d, int level, const Pair &it)
 {
-    const int n_pairs = 1 << (level - 1);
-    d.h_slot[it.small] = n_pairs + it.pair;
-    d.h_slot[it.large] = d.h_slot[n_pairs - 1 + it.pair];
+    const int parent = (1 << (level - 1)) - 1 + it.pair, left = 2 * parent + 1;
+    const int4 s = d.seg[parent];
+    d.h_slot[it.small] = (1 << (level - 1)) + it.pair;
+    d.h_slot[it.large] = d.h_slot[parent];
+    d.seg[left] = make_int4(0, 0, s.z, s.z + s.x);
+    d.seg[left + 1] = make_int4(0, 0, s.z + s.x, s.w);
 }
 
-// Features f0 + base .. + NF of the item.
-template <bool PACKED>
-__device__ __forceinline__ void hist_run(const TrainDesc &d, unsigned long long *lds, const Item &it, int level, int shift, int group, int base, int hb)
+// One node's outcome, the same in every workgroup that works on it.
+struct Decision {
+    int split;                // else a leaf
+    int feature, cut;
+    int count_left;           // the left child is the counted one
+    float left, right;        // values of the children that become leaves; of the node itself in `left`
+};
+
+__device__ __forceinline__ float leaf_value(long long G, long long H, const Params &prm)
+{
+    const double g = (double)G * prm.inv_scale;
+    return (float)(-prm.eta * g / ((double)H + prm.lambda));
+}
+
+// Decides node `node` of the level, by one wavefront (lanes over the features): largest gain, lowest
+// feature on ties.  Everybody waits for this, so it reads and reduces no more than that.
+__device__ __forceinline__ Decision wave_decide(const TrainDesc &d, int level, const Params &prm, int node, int lane)
+{
+    double gain = 0.0;
+    int feature = -1, cut = 0;                                   // cut * 2 + count_left
+    if (level < prm.max_depth) {
+        typedef int i32x4 __attribute__((ext_vector_type(4)));
+        auto best = FS_GLOBAL(const i32x4, d.best + (int64_t)(node - ((1 << level) - 1)) * d.n_features);
+        constexpr int kPerLane = 3;                              // loads at a time: this is a chain of latencies
+        for (int f0 = lane; f0 < d.n_features; f0 += 64 * kPerLane) {
+            i32x4 o[kPerLane];                                   // a record's first half
+#pragma unroll
+            for (int i = 0; i < kPerLane; ++i)
+                o[i] = best[2 * min(f0 + 64 * i, d.n_features - 1)];
+#pragma unroll
+            for (int i = 0; i < kPerLane; ++i) {                 // ascending: first of equals stays
+                const int f = f0 + 64 * i;
+                const double g = __longlong_as_double((long long)((unsigned long long)(unsigned)o[i].y << 32 | (unsigned)o[i].x));
+                if (f < d.n_features && o[i].z != 0 && (feature < 0 || g > gain)) {
+                    gain = g;
+                    feature = f;
+                    cut = 2 * o[i].z + o[i].w;
+                }
+            }
+        }
+    }
+    const double mine = gain;
+    int id = feature + 1;                                        // as in the cut search: 0 = nothing
+    best_step<0x111, 0xf>(gain, id);
+    best_step<0x112, 0xf>(gain, id);
+    best_step<0x114, 0xf>(gain, id);
+    best_step<0x118, 0xf>(gain, id);
+    best_step<0x142, 0xa>(gain, id);
+    best_step<0x143, 0xc>(gain, id);
+    id = __builtin_amdgcn_readlane(id, 63);
+    const unsigned long long who = __ballot(feature + 1 == id && mine > prm.min_gain);
+    Decision r = {};
+    if (id != 0 && who != 0) {
+        cut = __builtin_amdgcn_readlane(cut, __ffsll((long long)who) - 1);
+        r.split = 1;
+        r.feature = id - 1;
+        r.cut = cut >> 1;
+        r.count_left = cut & 1;
+    }
+    return r;
+}
+
+// Values of the leaves that a decision makes.
+__device__ __forceinline__ void leaf_values(const TrainDesc &d, int level, int turn, const Params &prm, int node,
+                                            Decision &r)
+{
+    if (r.split && level + 1 < prm.max_depth)
+        return;
+    long long G, H;
+    node_sums(d, node, turn, G, H);
+    if (!r.split) {
+        r.left = leaf_value(G, H, prm);
+        return;
+    }
+    const Best b = d.best[(int64_t)(node - ((1 << level) - 1)) * d.n_features + r.feature];
+    r.left = leaf_value(b.GL, b.HL, prm);
+    r.right = leaf_value(G - b.GL, H - b.HL, prm);
+}
+
+// What later launches read of a decided node (one lane of one of its workgroups).
+__device__ __forceinline__ void note_decision(const TrainDesc &d, int level, int turn, const Params &prm, int node,
+                                              const Decision &r)
+{
+    if (!r.split) {
+        d.decision[node] = make_int4(kLeaf, 0, 0, __float_as_int(r.left));
+        return;
+    }
+    const int lc = 2 * node + 1, rc = lc + 1;
+    d.decision[node] = make_int4(kInternal, r.feature, 0, __float_as_int(d.cuts[d.cut_off[r.feature] + r.cut - 1]));
+    if (level + 1 >= prm.max_depth) {
+        d.h_val[lc] = r.left;
+        d.h_val[rc] = r.right;
+        return;
+    }
+    long long G, H;
+    node_sums(d, node, turn, G, H);
+    const Best b = d.best[(int64_t)(node - ((1 << level) - 1)) * d.n_features + r.feature];
+    d.h_G[lc] = b.GL;
+    d.h_H[lc] = b.HL;
+    d.h_G[rc] = G - b.GL;
+    d.h_H[rc] = H - b.HL;
+    d.h_own[lc] = parent_term(b.GL, b.HL, prm.inv_scale, prm.lambda);
+    d.h_own[rc] = parent_term(G - b.GL, H - b.HL, prm.inv_scale, prm.lambda);
+}
+
+// Heap -> flat arrays, appended to the model; then the heap is the next tree's (one workgroup of
+// kHistThreads).  Ids are local to the tree in breadth-first order, which is the heap's order.  `ids`: LDS.
+__device__ __forceinline__ void emit_tree(const TrainDesc &d, int max_depth, int turn, int *ids)
+{
+    constexpr int kPer = (kHeapNodes + kHistThreads) / kHistThreads;
+    __shared__ int s_sum[kHistThreads / 64];
+    const int n_trees = d.counters[1], base = d.counters[2];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_heap = (2 << max_depth) - 1;
+    int4 c[kPer];
+    int sum = 0;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const int i = threadIdx.x * kPer + k;
+        const bool deepest = i >= (1 << max_depth) - 1;
+        c[k] = make_int4(kAbsent, 0, 0, 0);
+        if (i < n_heap) {
+            c[k] = d.decision[deepest && max_depth > 0 ? (i - 1) >> 1 : i];
+            const float v = d.h_val[i];
+            if (deepest && max_depth > 0)
+                c[k] = make_int4(c[k].x == kInternal ? kLeaf : kAbsent, 0, 0, __float_as_int(v));
+        }
+        sum += c[k].x != kAbsent;
+    }
+    const int incl = wave_prefix_i(sum);
+    if (lane == 63)
+        s_sum[wave] = incl;
+    __syncthreads();
+    int id = incl - sum, total = 0;
+    for (int w = 0; w < kHistThreads / 64; ++w) {
+        id += w < wave ? s_sum[w] : 0;
+        total += s_sum[w];
+    }
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const int i = threadIdx.x * kPer + k;
+        if (i < n_heap)
+            ids[i] = id;
+        id += c[k].x != kAbsent;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const int i = threadIdx.x * kPer + k;
+        if (c[k].x == kAbsent)
+            continue;
+        const int at = base + ids[i];
+        const bool inner = c[k].x == kInternal;
+        d.m_feat[at] = inner ? c[k].y : -1;
+        d.m_thr[at] = inner ? __int_as_float(c[k].w) : 0.0f;
+        d.m_left[at] = inner ? ids[2 * i + 1] : -1;
+        d.m_right[at] = inner ? ids[2 * i + 2] : -1;
+        d.m_val[at] = inner ? 0.0f : __int_as_float(c[k].w);
+    }
+    if (threadIdx.x == 0) {
+        d.counters[1] = n_trees + 1;
+        d.counters[2] = base + total;
+        d.m_tree_off[n_trees + 1] = base + total;
+    }
+    begin_tree(d, turn);
+}
+
+__global__ void __launch_bounds__(kHistThreads)
+train_emit_kernel(const TrainDesc *__restrict__ descs, int max_depth, int turn)
+{
+    __shared__ int ids[kHeapNodes];
+    emit_tree(descs[blockIdx.x], max_depth, turn, ids);
+}
+
+struct HistLds {
+    unsigned long long bins[kHistWords];
+    Decision dec;
+};
+
+// The histogram of a counted node of level `child` (number `pair` of its parents): features f0 + base .. + NF of the
+// piece's rows, ALL of them (the piece is the node's) or those that go to it (the piece is its parent's, which
+// is decided here, while the first rows and their bins are on their way).
+template <bool PACKED, bool ALL>
+__device__ __forceinline__ void hist_run(const TrainDesc &d, HistLds &s, const Piece &it, int child, int pair, int shift,
+                                         int group, int base, int hb, const Params &prm)
 {
     constexpr int NF = PACKED ? kHistFeats : kHistFeats / 2;
     constexpr int NW = NF / 4;
     const int f0 = group * kHistFeats + base;
     const int nf = min(NF, d.n_features - f0);
-    for (int i = threadIdx.x; i < kHistWords; i += kHistThreads)
-        lds[i] = 0ull;
-    int hot[NF];
-#pragma unroll
-    for (int k = 0; k < NF; ++k)
-        hot[k] = k < nf ? d.hot_bin[f0 + k] : 256;               // 256: no bin, nothing is skipped
-    __syncthreads();
+    unsigned long long *lds = s.bins;
     const int n = min(it.count - (int)((int64_t)it.piece << shift), 1 << shift);
-    auto recs = FS_GLOBAL(const i32x4, d.rec[level & 1] + it.first + ((int64_t)it.piece << shift));
+    auto recs = FS_GLOBAL(const i32x4, d.rec[ALL ? child & 1 : (child - 1) & 1] + it.first + ((int64_t)it.piece << shift));
     typedef uint32_t words __attribute__((ext_vector_type(NW)));
     auto bins = FS_GLOBAL(const uint8_t, d.bins + f0);
     const int64_t row_bytes = d.row_bytes;
@@ -850,36 +1095,65 @@ __device__ __forceinline__ void hist_run(const TrainDesc &d, unsigned long long 
     // (the records of a group are read in order, its bins gathered: the loads of the next step are
     // issued before the atomics of this one)
     int i = threadIdx.x;
+    i32x4 r = {}, r_next = {};
+    words w = {};
     if (i < n) {
-        i32x4 r = recs[i];
-        words w = *(words_at)(bins + r.x * row_bytes);
-        i32x4 r_next = recs[min(i + kHistThreads, n - 1)];
-        for (; i < n; i += kHistThreads) {
-            const words w_next = *(words_at)(bins + r_next.x * row_bytes);
-            const i32x4 r_after = recs[min(i + 2 * kHistThreads, n - 1)];
-            const unsigned long long both =
-                (unsigned long long)((long long)r.y * ((long long)1 << hb) + (long long)r.z);
+        r = recs[i];
+        r_next = recs[min(i + kHistThreads, n - 1)];
+    }
+    for (int j = threadIdx.x; j < kHistWords; j += kHistThreads)
+        lds[j] = 0ull;
+    int hot[NF];
+#pragma unroll
+    for (int k = 0; k < NF; ++k)
+        hot[k] = k < nf ? d.hot_bin[f0 + k] : 256;               // 256: no bin, nothing is skipped
+    if (i < n)
+        w = *(words_at)(bins + r.x * row_bytes);
+    if (!ALL && threadIdx.x < 64) {
+        const Decision mine = wave_decide(d, child - 1, prm, it.node, threadIdx.x);
+        if (threadIdx.x == 0)
+            s.dec = mine;
+    }
+    __syncthreads();
+    int cut = 0, count_left = 0;
+    auto col = FS_GLOBAL(const uint8_t, d.cols);
+    int b = 0;
+    if (!ALL) {
+        if (!s.dec.split)
+            return;
+        cut = s.dec.cut;
+        count_left = s.dec.count_left;
+        col = FS_GLOBAL(const uint8_t, d.cols + s.dec.feature * d.r_pad);
+        b = i < n ? col[(uint32_t)r.x] : 0;
+    }
+    for (; i < n; i += kHistThreads) {
+        const words w_next = *(words_at)(bins + r_next.x * row_bytes);
+        const int b_next = ALL ? 0 : col[(uint32_t)r_next.x];
+        const i32x4 r_after = recs[min(i + 2 * kHistThreads, n - 1)];
+        if (ALL || (b < cut) == (count_left != 0)) {
+            const unsigned long long both = (unsigned long long)((long long)r.y * ((long long)1 << hb) + (long long)r.z);
 #pragma unroll
             for (int k = 0; k < NF; ++k) {
                 if ((k & 3) == 0 && k >= nf)
                     break;
-                const int b = (w[k >> 2] >> (8 * (k & 3))) & 255;
-                if (b != hot[k]) {
-                    atomicAdd(&lds[k * kBins + b], PACKED ? both : (unsigned long long)(long long)r.y);
+                const int bin = (w[k >> 2] >> (8 * (k & 3))) & 255;
+                if (bin != hot[k]) {
+                    atomicAdd(&lds[k * kBins + bin], PACKED ? both : (unsigned long long)(long long)r.y);
                     if (!PACKED)
-                        atomicAdd(&lds[kHistWords / 2 + k * kBins + b], (unsigned long long)r.z);
+                        atomicAdd(&lds[kHistWords / 2 + k * kBins + bin], (unsigned long long)r.z);
                 }
             }
-            r = r_next;
-            w = w_next;
-            r_next = r_after;
         }
+        r = r_next;
+        w = w_next;
+        b = b_next;
+        r_next = r_after;
     }
     __syncthreads();
     const bool whole = it.count <= 1 << shift;
     const int64_t plane = whole ? d.hist_plane : d.part_plane;
     unsigned long long *out =
-        whole ? d.hist + hist_at(d, level, it, 0, f0)
+        whole ? d.hist + hist_at(d, child, pair, 0, f0)
               : d.part + ((part_slot(it.first, shift) + it.piece) * d.n_features + f0) * kBins;
     for (int j = 2 * threadIdx.x; j < nf * kBins; j += 2 * kHistThreads) {
         *(ulonglong2 *)(out + j) = *(ulonglong2 *)(lds + j);
@@ -889,24 +1163,174 @@ __device__ __forceinline__ void hist_run(const TrainDesc &d, unsigned long long 
     __syncthreads();                                             // LDS may be reused by the next run
 }
 
-// blockIdx = (item and feature group, -, trainer)
+template <bool ALL>
+__device__ __forceinline__ void hist_both(const TrainDesc &d, HistLds &s, const Piece &it, int child, int pair, int turn,
+                                          int shift, int group, int hb, const Params &prm)
+{
+    if (is_packed(d, turn, hb)) {
+        hist_run<true, ALL>(d, s, it, child, pair, shift, group, 0, hb, prm);
+    } else {
+        hist_run<false, ALL>(d, s, it, child, pair, shift, group, 0, 0, prm);
+        if (group * kHistFeats + kHistFeats / 2 < d.n_features)
+            hist_run<false, ALL>(d, s, it, child, pair, shift, group, kHistFeats / 2, 0, prm);
+    }
+}
+
+// Histograms of the level's counted nodes, whose records are in place (of its LDS hist_run uses the bins only).
+// blockIdx = (item and feature group, -, trainer); the last workgroup of a trainer puts the tree of the round
+// before into the model (`emit`).
 __global__ void __launch_bounds__(kHistThreads)
-train_hist_kernel(const TrainDesc *__restrict__ descs, int level, int shift, int hb, int groups)
+train_hist_kernel(const TrainDesc *__restrict__ descs, int level, int turn, int shift, int hb, int groups, int emit,
+                  int max_depth)
 {
     __shared__ __align__(16) unsigned long long lds[kHistWords];
+    HistLds &s = *(HistLds *)lds;
     const TrainDesc &d = descs[blockIdx.z];
-    Item it;
+    if (emit && blockIdx.x == gridDim.x - 1) {
+        emit_tree(d, max_depth, turn ^ 1, (int *)lds);
+        return;
+    }
+    Piece it;
     int item, group;
     xcd_piece(blockIdx.x, groups, blockIdx.z, item, group);
-    if (group * kHistFeats >= d.n_features || !find_item(d, level, shift, item, threadIdx.x & 63, it))
+    if (group * kHistFeats >= d.n_features || !find_counted(d, level, shift, item, threadIdx.x & 63, it))
         return;
-    if (is_packed(d, hb)) {
-        hist_run<true>(d, lds, it, level, shift, group, 0, hb);
-    } else {
-        hist_run<false>(d, lds, it, level, shift, group, 0, 0);
-        if (group * kHistFeats + kHistFeats / 2 < d.n_features)
-            hist_run<false>(d, lds, it, level, shift, group, kHistFeats / 2, 0);
+    hist_both<true>(d, s, it, level, level ? ((it.node - 1) >> 1) - ((1 << (level - 1)) - 1) : 0, turn, shift, group, hb,
+                    Params());
+}
+
+// Records of a node that is split move to its children's segments in the other buffer: the left child's
+// fill the node's segment from its front, the right one's from its back (the order inside a segment is
+// free: all sums over rows are integer sums).  Rows of leaves take the leaf's value.
+// A workgroup takes kMoveRows rows of one node and counts them up with one atomic; bound by its chain of
+// three barriers and six loads.  Two rows a thread: one takes 212 us for a round of depth 6 of 255 000 rows (as
+// many atomics again on one address near the root), two 203, four 201, and 218 / 217 / 220 for depth 8
+// of 102 000.  On the last level nothing moves.
+constexpr int kMovePer = 2;
+constexpr int kMoveRows = kMovePer * kHistThreads;
+constexpr int kMoveShift = 10;
+static_assert(kMoveRows == 1 << kMoveShift, "rows of a moving workgroup");
+
+template <bool LAST>
+__device__ __forceinline__ void move_rows(const TrainDesc &d, Decision &s_dec, const Piece &it, int level, int turn,
+                                          const Params &prm)
+{
+    __shared__ int s_left[kHistThreads / 64], s_right[kHistThreads / 64];
+    __shared__ unsigned long long s_base;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int n = min(it.count - it.piece * kMoveRows, kMoveRows);
+    auto recs = FS_GLOBAL(const i32x4, d.rec[level & 1] + it.first + it.piece * kMoveRows);
+    i32x4 r[kMovePer];
+#pragma unroll
+    for (int k = 0; k < kMovePer; ++k)
+        r[k] = recs[min((int)threadIdx.x + k * kHistThreads, n - 1)];
+    if (wave == 0) {
+        Decision mine = wave_decide(d, level, prm, it.node, lane);
+        leaf_values(d, level, turn, prm, it.node, mine);
+        if (lane == 0)
+            s_dec = mine;
     }
+    __syncthreads();
+    const Decision dec = s_dec;
+    if (it.piece == 0 && threadIdx.x == kHistThreads - 1)
+        note_decision(d, level, turn, prm, it.node, dec);
+    if (!dec.split || LAST) {
+        int b[kMovePer];
+#pragma unroll
+        for (int k = 0; k < kMovePer; ++k)
+            b[k] = dec.split ? d.cols[dec.feature * d.r_pad + r[k].x] : 0;
+#pragma unroll
+        for (int k = 0; k < kMovePer; ++k)
+            if ((int)threadIdx.x + k * kHistThreads < n)
+                d.row_pred[r[k].x] = __int_as_float(r[k].w) + (!dec.split || b[k] < dec.cut ? dec.left : dec.right);
+        return;
+    }
+    int b[kMovePer];
+    unsigned long long lm[kMovePer], rm[kMovePer];
+#pragma unroll
+    for (int k = 0; k < kMovePer; ++k)
+        b[k] = d.cols[dec.feature * d.r_pad + r[k].x];
+    int wl = 0, wr = 0;
+#pragma unroll
+    for (int k = 0; k < kMovePer; ++k) {
+        const bool in = (int)threadIdx.x + k * kHistThreads < n;
+        lm[k] = __ballot(in && b[k] < dec.cut);
+        rm[k] = __ballot(in && !(b[k] < dec.cut));
+        wl += __popcll(lm[k]);
+        wr += __popcll(rm[k]);
+    }
+    if (lane == 0) {
+        s_left[wave] = wl;
+        s_right[wave] = wr;
+    }
+    __syncthreads();
+    int l = 0, rt = 0, l_all = 0, r_all = 0;
+#pragma unroll
+    for (int w = 0; w < kHistThreads / 64; ++w) {
+        l += w < wave ? s_left[w] : 0;
+        rt += w < wave ? s_right[w] : 0;
+        l_all += s_left[w];
+        r_all += s_right[w];
+    }
+    if (threadIdx.x == 0)
+        s_base = atomicAdd((unsigned long long *)&d.seg[it.node],
+                           (unsigned long long)(unsigned)l_all | (unsigned long long)(unsigned)r_all << 32);
+    __syncthreads();
+    const unsigned long long start = s_base, below = (1ull << lane) - 1ull;
+    l += it.first + (int)(unsigned)start;
+    rt += (int)(start >> 32);
+    auto out = FS_GLOBAL(i32x4, d.rec[(level + 1) & 1]);
+#pragma unroll
+    for (int k = 0; k < kMovePer; ++k) {
+        if ((int)threadIdx.x + k * kHistThreads < n)
+            out[b[k] < dec.cut ? l + __popcll(lm[k] & below) : it.first + it.count - 1 - (rt + __popcll(rm[k] & below))] = r[k];
+        l += __popcll(lm[k]);
+        rt += __popcll(rm[k]);
+    }
+}
+
+// One level: decides its nodes, moves their records, counts the smaller children.
+// blockIdx = (moving workgroups, then item and feature group, -, trainer)
+__global__ void __launch_bounds__(kHistThreads)
+train_grow_kernel(const TrainDesc *__restrict__ descs, int level, int turn, int shift, int hb, int groups, int movers,
+                  Params prm)
+{
+    __shared__ __align__(16) HistLds s;
+    const TrainDesc &d = descs[blockIdx.z];
+    const int lane = threadIdx.x & 63;
+    Piece it;
+    if ((int)blockIdx.x < movers) {
+        if (find_piece(d, level, kMoveShift, blockIdx.x, lane, it))
+            move_rows<false>(d, s.dec, it, level, turn, prm);
+        return;
+    }
+    int item, group;
+    xcd_piece(blockIdx.x - movers, groups, blockIdx.z, item, group);
+    if (group * kHistFeats >= d.n_features || !find_piece(d, level, shift, item, lane, it))
+        return;
+    hist_both<false>(d, s, it, level + 1, it.node - ((1 << level) - 1), turn, shift, group, hb, prm);
+}
+
+// The first half of a level by itself, where train_hist_kernel is to count the moved records.
+__global__ void __launch_bounds__(kHistThreads)
+train_move_kernel(const TrainDesc *__restrict__ descs, int level, int turn, Params prm)
+{
+    __shared__ Decision dec;
+    const TrainDesc &d = descs[blockIdx.y];
+    Piece it;
+    if (find_piece(d, level, kMoveShift, blockIdx.x, threadIdx.x & 63, it))
+        move_rows<false>(d, dec, it, level, turn, prm);
+}
+
+// The last level: decides its nodes, rows take the values of the leaves.  blockIdx = (workgroup, trainer)
+__global__ void __launch_bounds__(kHistThreads)
+train_finish_kernel(const TrainDesc *__restrict__ descs, int level, int turn, Params prm)
+{
+    __shared__ Decision dec;
+    const TrainDesc &d = descs[blockIdx.y];
+    Piece it;
+    if (find_piece(d, level, kMoveShift, blockIdx.x, threadIdx.x & 63, it))
+        move_rows<true>(d, dec, it, level, turn, prm);
 }
 
 // One workgroup per (counted node, feature): the wavefronts add up the node's parts if it has several,
@@ -920,11 +1344,11 @@ constexpr int kSplitWideNodes = 4;
 
 template <bool PACKED>
 __device__ __forceinline__ void split_run(const TrainDesc &d, const Params &prm, unsigned long long *lds,
-                                          const Item &it, int level, int shift, int f, int hb)
+                                          const Pair &it, int level, int turn, int shift, int f, int hb)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
     const int children = level > 0 ? 2 : 1;
-    const int pieces = (int)(((int64_t)it.count + (1ll << shift) - 1) >> shift);
+    const int pieces = pieces_of(it.count, shift);
     Bins4<PACKED> own = {};
     if (pieces > 1) {
         const unsigned long long *part = d.part + (part_slot(it.first, shift) * d.n_features + f) * kBins + 4 * lane;
@@ -949,323 +1373,39 @@ __device__ __forceinline__ void split_run(const TrainDesc &d, const Params &prm,
     } else {
         if (wave >= children)
             return;
-        own.load(d.hist + hist_at(d, level, it, 0, f) + 4 * lane, d.hist_plane);
+        own.load(d.hist + hist_at(d, level, it.pair, 0, f) + 4 * lane, d.hist_plane);
     }
-    search_child<PACKED>(d, prm, level, it, wave, wave || pieces > 1, f, lane, own, hb,
+    search_child<PACKED>(d, prm, level, turn, it, wave, wave || pieces > 1, f, lane, own, hb,
                          (unsigned char *)(lds + wave * kBins));
     if (f == 0 && wave == 0 && lane == 0 && level > 0 && level + 1 < prm.max_depth)
-        note_slots(d, level, it);
+        open_children(d, level, it);
 }
 
 __global__ void __launch_bounds__(64 * kSplitWaves, 6)
-train_split_kernel(const TrainDesc *__restrict__ descs, int level, int shift, int hb, Params prm)
+train_split_kernel(const TrainDesc *__restrict__ descs, int level, int turn, int shift, int hb, int grown, Params prm)
 {
     extern __shared__ __align__(16) unsigned long long lds[];
     const TrainDesc &d = descs[blockIdx.z];
     const int f = blockIdx.x, pair = blockIdx.y;
     if (f >= d.n_features)
         return;
-    Item it = {0, -1, 0, 0, d.n_rows, 0};
+    Pair it = {0, -1, 0, 0, d.n_rows};
     if (level > 0) {
-        const int parent = (1 << (level - 1)) - 1 + pair;
+        const int parent = (1 << (level - 1)) - 1 + pair, left = 2 * parent + 1;
         const int4 s = d.seg[parent];
+        const bool count_left = counts_left(d.h_H[left], d.h_H[left + 1]);
         if (s.x == 0)                                            // not split
             return;
-        it = counted_node(parent, pair, s);
+        it = {count_left ? left : left + 1, count_left ? left + 1 : left, pair, s.z, s.x + s.y};
+        if (!grown) {                                            // the pieces are the counted node's
+            it.first = count_left ? s.z : s.z + s.x;
+            it.count = count_left ? s.x : s.y;
+        }
     }
-    if (is_packed(d, hb))
-        split_run<true>(d, prm, lds, it, level, shift, f, hb);
+    if (is_packed(d, turn, hb))
+        split_run<true>(d, prm, lds, it, level, turn, shift, f, hb);
     else
-        split_run<false>(d, prm, lds, it, level, shift, f, 0);
-}
-
-// Per open node of the level: best feature, split or leaf; children get consecutive ids in
-// slot order (breadth-first numbering).  One workgroup per trainer: first every wavefront
-// finds the best feature of some of the nodes (lanes over features), then one thread per node
-// decides.
-constexpr int kPickThreads = 1024;
-constexpr int kMaxSlots = 1 << FS_TRAIN_MAX_DEPTH;
-static_assert(kMaxSlots <= kPickThreads, "one thread per node of the deepest level");
-constexpr int kPickSpreadSlots = 64;     // levels with at least this many nodes reduce in a kernel of their own
-
-// Best feature of node number `sl` of the level, by one wavefront (lanes over the features):
-// largest gain, lowest feature on ties.  `out` is written by the lane that holds it.
-__device__ __forceinline__ void wave_best_feature(const TrainDesc &d, int level, const Params &prm, int sl,
-                                                  int lane, Winner *out)
-{
-    const int n_slots = 1 << level;
-    Winner mine = {0.0, 0, 0, -1, 0};
-    if (level < prm.max_depth && d.h_state[n_slots - 1 + sl] == kOpen) {
-        constexpr int kPerLane = 3;                              // loads at a time: this is a chain of latencies
-        for (int f0 = lane; f0 < d.n_features; f0 += 64 * kPerLane) {
-            Best o[kPerLane];
-#pragma unroll
-            for (int i = 0; i < kPerLane; ++i)
-                o[i] = d.best[(int64_t)sl * d.n_features + min(f0 + 64 * i, d.n_features - 1)];
-#pragma unroll
-            for (int i = 0; i < kPerLane; ++i) {                 // ascending: first of equals stays
-                const int f = f0 + 64 * i;
-                if (f < d.n_features && o[i].cut != 0 && (mine.feature < 0 || o[i].gain > mine.gain)) {
-                    mine.gain = o[i].gain;
-                    mine.GL = o[i].GL;
-                    mine.HL = o[i].HL;
-                    mine.feature = f;
-                    mine.cut = o[i].cut;
-                }
-            }
-        }
-    }
-    double best = mine.gain;
-    int id = mine.feature + 1;                                   // as in the cut search: 0 = nothing
-    best_step<0x111, 0xf>(best, id);
-    best_step<0x112, 0xf>(best, id);
-    best_step<0x114, 0xf>(best, id);
-    best_step<0x118, 0xf>(best, id);
-    best_step<0x142, 0xa>(best, id);
-    best_step<0x143, 0xc>(best, id);
-    id = __builtin_amdgcn_readlane(id, 63);
-    if (id == 0 ? lane == 0 : mine.feature + 1 == id)
-        *out = mine;
-}
-
-// Levels with many nodes: the best feature of every node, one wavefront each, over the whole
-// chip (train_pick_kernel, one workgroup per trainer, then only decides).
-__global__ void __launch_bounds__(kPickThreads)
-train_pick_reduce_kernel(const TrainDesc *__restrict__ descs, int level, Params prm)
-{
-    const TrainDesc &d = descs[blockIdx.y];
-    const int sl = blockIdx.x * (kPickThreads / 64) + (threadIdx.x >> 6);
-    if (sl < (1 << level))
-        wave_best_feature(d, level, prm, sl, threadIdx.x & 63, &d.winner[sl]);
-}
-
-__device__ __forceinline__ float leaf_value(long long G, long long H, const Params &prm)
-{
-    const double g = (double)G * prm.inv_scale;
-    return (float)(-prm.eta * g / ((double)H + prm.lambda));
-}
-
-__global__ void __launch_bounds__(kPickThreads)
-train_pick_kernel(const TrainDesc *__restrict__ descs, int level, int reduced, Params prm)
-{
-    __shared__ int s_count[kPickThreads / 64];
-    __shared__ Winner s_win[kPickSpreadSlots];
-    const TrainDesc &d = descs[blockIdx.x];
-    const int n_slots = 1 << level;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int slot = threadIdx.x;
-    const int node = n_slots - 1 + slot;
-    const bool open = slot < n_slots && d.h_state[node] == kOpen;
-    // (what the decision needs is loaded before the barrier)
-    const long long G = open ? d.h_G[node] : 0, H = open ? d.h_H[node] : 0;
-    const int4 up = open && level > 0 ? d.seg[(node - 1) >> 1] : make_int4(0, 0, 0, 0);
-    const int next_id = d.counters[0];
-    if (!reduced) {
-        for (int sl = wave; sl < n_slots; sl += kPickThreads / 64)
-            wave_best_feature(d, level, prm, sl, lane, &s_win[sl]);
-        __syncthreads();
-    }
-    Winner win = {0.0, 0, 0, -1, 0};
-    if (open)
-        win = reduced ? d.winner[slot] : s_win[slot];
-    const int bf = win.feature, bc = win.cut;
-    const bool split = open && bf >= 0 && win.gain > prm.min_gain;
-    const unsigned long long votes = __ballot(split);
-    if (lane == 0)
-        s_count[wave] = __popcll(votes);
-    __syncthreads();
-    int before = __popcll(votes & ((1ull << lane) - 1ull)), total = 0;
-    for (int w = 0; w < kPickThreads / 64; ++w) {
-        before += w < wave ? s_count[w] : 0;
-        total += s_count[w];
-    }
-    if (slot < n_slots) {
-        int4 own = make_int4(0, 0, 0, 0);
-        if (split) {
-            own.w = d.n_rows;
-            if (level > 0) {
-                own.z = up.z + (node & 1 ? 0 : up.x);
-                own.w = node & 1 ? up.z + up.x : up.w;
-            }
-        }
-        d.seg[node] = own;
-        if (!open)
-            d.decision[node] = make_int4(kAbsent, 0, 0, 0);
-    }
-    if (open) {
-        if (split) {
-            const long long GL = win.GL, HL = win.HL;
-            const int lc = 2 * node + 1, rc = lc + 1;
-            d.h_state[node] = kInternal;
-            d.decision[node] = make_int4(kInternal, bf, bc, 0);
-            const bool deepest = level + 1 == prm.max_depth;     // what is left becomes leaves
-            d.h_state[lc] = deepest ? kLeaf : kOpen;
-            d.h_state[rc] = deepest ? kLeaf : kOpen;
-            if (deepest) {
-                d.h_val[lc] = leaf_value(GL, HL, prm);
-                d.h_val[rc] = leaf_value(G - GL, H - HL, prm);
-            }
-            d.h_G[lc] = GL;
-            d.h_H[lc] = HL;
-            d.h_G[rc] = G - GL;
-            d.h_H[rc] = H - HL;
-            d.h_own[lc] = parent_term(GL, HL, prm.inv_scale, prm.lambda);
-            d.h_own[rc] = parent_term(G - GL, H - HL, prm.inv_scale, prm.lambda);
-            d.h_id[lc] = next_id + 2 * before;
-            d.h_id[rc] = next_id + 2 * before + 1;
-        } else {
-            d.h_state[node] = kLeaf;
-            d.h_val[node] = leaf_value(G, H, prm);
-            d.decision[node] = make_int4(kLeaf, 0, 0, __float_as_int(leaf_value(G, H, prm)));
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x == 0)
-        d.counters[0] = next_id + 2 * total;
-}
-
-// Heap -> flat arrays, appended to the model; then the heap is the next tree's (one workgroup).
-__device__ __forceinline__ void emit_tree(const TrainDesc &d)
-{
-    const int n_trees = d.counters[1], base = d.counters[2], n_new = d.counters[0];
-    for (int i = threadIdx.x; i < kHeapNodes; i += blockDim.x) {
-        const int st = d.h_state[i];
-        if (st != kInternal && st != kLeaf)
-            continue;
-        const int at = base + d.h_id[i];
-        if (st == kInternal) {
-            const int4 c = d.decision[i];
-            d.m_feat[at] = c.y;
-            d.m_thr[at] = d.cuts[d.cut_off[c.y] + c.z - 1];
-            d.m_left[at] = d.h_id[2 * i + 1];
-            d.m_right[at] = d.h_id[2 * i + 2];
-            d.m_val[at] = 0.0f;
-        } else {
-            d.m_feat[at] = -1;
-            d.m_thr[at] = 0.0f;
-            d.m_left[at] = -1;
-            d.m_right[at] = -1;
-            d.m_val[at] = d.h_val[i];
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        d.counters[1] = n_trees + 1;
-        d.counters[2] = base + n_new;
-        d.m_tree_off[n_trees + 1] = base + n_new;
-    }
-    __syncthreads();
-    begin_tree(d);
-}
-
-// Records of the nodes that were split move to their child's segment in the other buffer (the order
-// inside a segment is free: all sums over rows are integer sums); rows of leaves take the leaf's
-// value.  A record of an earlier level that was not overwritten since belongs to a node above the
-// level and is passed over.  (At level 1 every position is fresh: either all rows moved there, or
-// the tree is one leaf and no node of the heap is open or split.)
-//
-// A workgroup counts its rows up in the node's segment with one atomic where all are of one node, as
-// near the root; those of 1000 workgroups on one address are a chain.  Workgroups of 512 for up to
-// 65536 rows, of 1024 above, by the largest family of a batch, which its launches wait for.  A round of
-// depth 6 and 9 in us, 512 against 1024: 8000 rows 135.8 / 258.8 against 137.9 / 260.9, 25 000 146.0 / 272.7
-// against 147.3 / 276.7, 65 000 167.8 / 305.6 against 168.3 / 306.7, 100 000 176.8 / 322.8 against 174.8 / 321.0,
-// 255 000 260.8 / 425.8 against 251.4 / 417.4; eight families of 30 000 302.6 / 1047 against 301.2 / 1049, of
-// 8000 and one of 200 000 318.2 / 1018 against 309.4 / 1013.
-constexpr int kPartThreads = 1024;
-constexpr int kPartRowsSmall = 65536;
-
-__global__ void __launch_bounds__(kPartThreads)
-train_part_kernel(const TrainDesc *__restrict__ descs, int level, int max_depth, int row_blocks)
-{
-    __shared__ int s_left[kPartThreads / 64], s_right[kPartThreads / 64];
-    __shared__ unsigned long long s_base;
-    const TrainDesc &d = descs[blockIdx.y];
-    if ((int)blockIdx.x == row_blocks) {                         // last level only; clears nothing that the rows read
-        emit_tree(d);
-        return;
-    }
-    const int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (blockIdx.x * (int64_t)blockDim.x >= d.n_rows)
-        return;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int4 r = make_int4(0, 0, 0, -1), todo_of = make_int4(kAbsent, 0, 0, 0);
-    int2 ends = make_int2(0, 0);
-    if (p < d.n_rows) {
-        r = d.rec[level & 1][p];
-        if (r.w >= (1 << level) - 1 && r.w < (2 << level) - 1) {
-            todo_of = d.decision[r.w];
-            ends = ((const int2 *)&d.seg[r.w])[1];               // (the other half is being counted up)
-        }
-    }
-    const int state = todo_of.x;
-    bool left = false;
-    if (state == kInternal) {
-        const int f = todo_of.y;
-        const int b = d.cols[f * d.r_pad + r.x];
-        left = b < todo_of.z;
-        if (level + 1 == max_depth) {
-            const float v = d.h_val[2 * r.w + (left ? 1 : 2)];
-            d.row_pred[r.x] = d.row_pred[r.x] + v;
-        }
-    } else if (state == kLeaf) {
-        d.row_pred[r.x] = d.row_pred[r.x] + __int_as_float(todo_of.w);
-    }
-    if (level + 1 >= max_depth)
-        return;
-    const bool moves = state == kInternal;
-    const unsigned long long below = (1ull << lane) - 1ull;
-    int at = 0;
-    // One node holds most positions of a workgroup high up in the tree: one atomic for all of them.
-    const int node0 = __builtin_amdgcn_readfirstlane(r.w);
-    __shared__ int s_node;
-    if (threadIdx.x == 0)
-        s_node = r.w;
-    __syncthreads();
-    if (__syncthreads_and(!moves ? p >= d.n_rows : r.w == s_node)) {
-        const unsigned long long lm = __ballot(moves && left), rm = __ballot(moves && !left);
-        if (lane == 0) {
-            s_left[wave] = __popcll(lm);
-            s_right[wave] = __popcll(rm);
-        }
-        __syncthreads();
-        int l = 0, rt = 0, l_all = 0, r_all = 0;
-        for (int w = 0; w < (int)blockDim.x / 64; ++w) {
-            if (w == wave) {
-                l = l_all;
-                rt = r_all;
-            }
-            l_all += s_left[w];
-            r_all += s_right[w];
-        }
-        if (threadIdx.x == 0)
-            s_base = atomicAdd((unsigned long long *)&d.seg[s_node],
-                               (unsigned long long)(unsigned)l_all | (unsigned long long)(unsigned)r_all << 32);
-        __syncthreads();
-        const unsigned long long base = s_base;
-        at = left ? (int)(unsigned)base + l + __popcll(lm & below) : (int)(base >> 32) + rt + __popcll(rm & below);
-    } else {
-        unsigned long long todo = __ballot(moves);
-        int node = node0;
-        while (todo) {
-            const int lead = __ffsll((long long)todo) - 1;
-            node = __builtin_amdgcn_readlane(r.w, lead);
-            const bool mine = moves && r.w == node;
-            const unsigned long long lm = __ballot(mine && left), rm = __ballot(mine && !left);
-            unsigned long long base = 0;
-            if (lane == lead)
-                base = atomicAdd((unsigned long long *)&d.seg[node],
-                                 (unsigned long long)__popcll(lm) | (unsigned long long)__popcll(rm) << 32);
-            const int bl = __builtin_amdgcn_readlane((int)(unsigned)base, lead);
-            const int br = __builtin_amdgcn_readlane((int)(base >> 32), lead);
-            if (mine)
-                at = left ? bl + __popcll(lm & below) : br + __popcll(rm & below);
-            todo &= ~(lm | rm);
-        }
-    }
-    if (moves) {
-        const int to = left ? ends.x + at : ends.y - 1 - at;
-        d.rec[(level + 1) & 1][to] = make_int4(r.x, r.y, r.z, 2 * r.w + (left ? 1 : 2));
-    }
+        split_run<false>(d, prm, lds, it, level, turn, shift, f, 0);
 }
 
 }  // namespace fs
@@ -1580,17 +1720,14 @@ extern "C" int fs_trainer_create(fs_trainer **out, int32_t n_features, const flo
     arena.add(&h.rec[1], (size_t)n_rows);
     arena.add(&h.seg, (size_t)kHeapNodes);
     arena.add(&h.h_slot, (size_t)kHeapNodes);
-    arena.add(&h.h_state, (size_t)kHeapNodes);
     arena.add(&h.h_own, (size_t)kHeapNodes);
-    arena.add(&h.h_id, (size_t)kHeapNodes);
     arena.add(&h.h_val, (size_t)kHeapNodes);
     arena.add(&h.h_G, (size_t)kHeapNodes);
     arena.add(&h.h_H, (size_t)kHeapNodes);
     arena.add(&h.best, (size_t)hist_slots * n_features);
     arena.add(&h.decision, (size_t)kHeapNodes);
     arena.add(&h.counters, (size_t)4);
-    arena.add(&h.abs_q, (size_t)1);
-    arena.add(&h.winner, (size_t)kMaxSlots);
+    arena.add(&h.root, (size_t)2);
     arena.add(&h.m_tree_off, (size_t)max_trees + 1);
     arena.add(&h.m_feat, (size_t)node_cap);
     arena.add(&h.m_left, (size_t)node_cap);
@@ -1738,13 +1875,14 @@ namespace {
 struct Part {
     int first, n;
     int shift, hb;                   // rows of a histogram workgroup (log2); packed_bits
+    bool grown;                      // the levels' records are moved and counted by one launch
     int max_rows, max_prog, max_feat;
     size_t bytes;                    // of histograms
 };
 
 Part make_part(const fs_trainer *const *trainers, int first, int n, int depth)
 {
-    Part pt = {first, n, kChunkShiftMin, 0, 0, 0, 0, 0};
+    Part pt = {first, n, kChunkShiftMin, 0, false, 0, 0, 0, 0};
     int max_len = 0;
     int64_t total_rows = 0;
     for (int i = first; i < first + n; ++i) {
@@ -1757,6 +1895,9 @@ Part make_part(const fs_trainer *const *trainers, int first, int n, int depth)
     }
     // A histogram workgroup takes up to 2^shift rows of a node: 48 to 96 pieces of all the batch's rows
     // at the root, which with ten feature groups are two to four workgroups per compute unit.
+    if (total_rows > kChunkSmallRows)
+        ++pt.shift;
+    pt.grown = total_rows <= kGrowRows;
     while (pt.shift < 30 && ((int64_t)1 << pt.shift) * kChunkPieces < total_rows)
         ++pt.shift;
     const int v = tune(FS_TUNE_TRAIN_SLAB_ROWS);                 // test / tuning override
@@ -1776,49 +1917,52 @@ int train_part(const TrainDesc *d, const Part &pt, int n_rounds, const Params &p
     const unsigned nt = (unsigned)pt.n;
     const unsigned groups = (unsigned)((pt.max_feat + kHistFeats - 1) / kHistFeats);
     const int max_rows = pt.max_rows, shift = pt.shift, hb = pt.hb;
+    const bool grown = pt.grown;
     prof_start(kKernTrainOther, stream);
     hipLaunchKernelGGL(train_begin_kernel, dim3(nt), dim3(512), 0, stream, d);
     prof_stop(stream);
     for (int round = 0; round < n_rounds; ++round) {
+        const int turn = round & 1;
         prof_start(kKernTrainOther, stream);
         hipLaunchKernelGGL(train_grad_kernel, dim3((unsigned)((pt.max_prog + (int64_t)kGradThreads - 1) / kGradThreads), nt), dim3(kGradThreads), 0,
-                           stream, d, prm.grad_scale, 1);
+                           stream, d, prm.grad_scale, 1, turn);
         prof_stop(stream);
-        for (int level = 0; level < std::max(1, prm.max_depth); ++level) {
-            const int n_slots = 1 << level;
-            if (level < prm.max_depth) {
-                // at most this many items: the counted children hold at most half the rows, each at least one
-                const int64_t rows = level ? max_rows / 2 : max_rows, n_counted = level ? n_slots / 2 : 1;
-                const int64_t items = std::max<int64_t>(1, std::min(rows, (rows >> shift) + n_counted));
-                prof_start(kKernTrainHist, stream);
-                hipLaunchKernelGGL(train_hist_kernel, dim3(xcd_grid(items, groups), 1u, nt), dim3(kHistThreads), 0,
-                                   stream, d, level, shift, hb, (int)groups);
+        for (int level = 0; level < prm.max_depth; ++level) {    // histograms and cuts of the level's nodes
+            const int64_t parents = level ? (int64_t)1 << (level - 1) : 1;
+            // at most this many pieces of 2^s rows of so many nodes of r rows in all
+            auto most = [&](int64_t r, int s) { return std::max<int64_t>(1, std::min<int64_t>(r, (r >> s) + parents)); };
+            if (level && !grown) {
+                prof_start(kKernTrainOther, stream);
+                hipLaunchKernelGGL(train_move_kernel, dim3((unsigned)most(max_rows, kMoveShift), nt), dim3(kHistThreads), 0,
+                                   stream, d, level - 1, turn, prm);
                 prof_stop(stream);
-                prof_start(kKernTrainSplit, stream);
-                const unsigned waves = n_counted * nt <= kSplitWideNodes ? kSplitWaves : 2;
-                hipLaunchKernelGGL(train_split_kernel, dim3((unsigned)pt.max_feat, (unsigned)n_counted, nt),
-                                   dim3(64 * waves), 2 * waves * kBins * 8,
-                                   stream, d, level, shift, hb, prm);
-            } else {
-                prof_start(kKernTrainSplit, stream);
             }
-            // from 64 nodes on the per-node reduction over the features gets the whole chip
-            const int reduced = n_slots >= kPickSpreadSlots ? 1 : 0;
-            if (reduced)
-                hipLaunchKernelGGL(train_pick_reduce_kernel,
-                                   dim3((unsigned)(n_slots / (kPickThreads / 64)), nt), dim3(kPickThreads), 0,
-                                   stream, d, level, prm);
-            hipLaunchKernelGGL(train_pick_kernel, dim3(nt), dim3(kPickThreads), 0, stream, d, level, reduced,
-                               prm);
+            prof_start(kKernTrainHist, stream);
+            if (level == 0 || !grown) {
+                const unsigned emit = level == 0 && round > 0 ? 1u : 0u;
+                hipLaunchKernelGGL(train_hist_kernel, dim3(xcd_grid(most(max_rows, shift), groups) + emit, 1u, nt),
+                                   dim3(kHistThreads), 0, stream, d, level, turn, shift, hb, (int)groups, (int)emit, prm.max_depth);
+            } else {
+                const unsigned movers = (unsigned)((most(max_rows, kMoveShift) + 7) / 8 * 8);
+                hipLaunchKernelGGL(train_grow_kernel, dim3(movers + xcd_grid(most(max_rows, shift), groups), 1u, nt),
+                                   dim3(kHistThreads), 0, stream, d, level - 1, turn, shift, hb, (int)groups, (int)movers, prm);
+            }
             prof_stop(stream);
-            prof_start(kKernTrainOther, stream);
-            const int part_threads = max_rows <= kPartRowsSmall ? kPartThreads / 2 : kPartThreads;
-            const int row_blocks = (int)((max_rows + (int64_t)part_threads - 1) / part_threads);
-            const int last = level + 1 >= prm.max_depth ? 1 : 0;   // one more workgroup puts the tree into the model
-            hipLaunchKernelGGL(train_part_kernel, dim3((unsigned)(row_blocks + last), nt), dim3(part_threads), 0,
-                               stream, d, level, prm.max_depth, row_blocks);
+            prof_start(kKernTrainSplit, stream);
+            const unsigned waves = parents * nt <= kSplitWideNodes ? kSplitWaves : 2;
+            hipLaunchKernelGGL(train_split_kernel, dim3((unsigned)pt.max_feat, (unsigned)parents, nt),
+                               dim3(64 * waves), 2 * waves * kBins * 8,
+                               stream, d, level, turn, shift, hb, grown ? 1 : 0, prm);
             prof_stop(stream);
         }
+        const int last = std::max(0, prm.max_depth - 1);
+        const int64_t finishers = std::min<int64_t>(max_rows, (max_rows >> kMoveShift) + ((int64_t)1 << last));
+        prof_start(kKernTrainOther, stream);
+        hipLaunchKernelGGL(train_finish_kernel, dim3((unsigned)finishers, nt), dim3(kHistThreads), 0, stream, d, last,
+                           turn, prm);
+        if (round + 1 == n_rounds || prm.max_depth == 0)         // else with the next round's histograms
+            hipLaunchKernelGGL(train_emit_kernel, dim3(nt), dim3(kHistThreads), 0, stream, d, prm.max_depth, turn ^ 1);
+        prof_stop(stream);
         const int rc = check_launch("training kernels launch");
         if (rc != FS_OK)
             return rc;
@@ -1978,7 +2122,7 @@ extern "C" int fs_trainer_predictions(const fs_trainer *t, float *row_pred, floa
         if (rc != FS_OK)
             return rc;
         hipLaunchKernelGGL(train_grad_kernel, dim3((unsigned)((t->h.n_programs + (int64_t)kGradThreads - 1) / kGradThreads), 1u), dim3(kGradThreads), 0,
-                           stream, d, 1.0f, 0);
+                           stream, d, 1.0f, 0, 0);
         rc = check_launch("train_grad_kernel launch");
         if (rc != FS_OK)
             return rc;

@@ -45,6 +45,23 @@ def test_both_sides_of_the_partition_workgroup(api, T, n):
     check(api, T, rows_set(7, n, 5, 31), rounds=2, max_depth=3, eta=0.5, lam=1.0)
 
 
+@pytest.mark.parametrize("n,depth,rounds", [(12_288, 10, 2), (12_289, 2, 3), (49_152, 10, 1), (49_153, 10, 1), (49_153, 1, 3)])
+def test_levels_grown_in_one_launch_and_moved_first(api, T, n, depth, rounds):
+    """Both sides of the lines between the sizes of work items (12 288 rows) and between moving records in
+    a launch of their own or with the histograms (49 152)."""
+    check(api, T, rows_set(n, n, 5, 31), rounds=rounds, max_depth=depth, eta=0.5, lam=1.0)
+
+
+@pytest.mark.parametrize("programs,slab,packed", [(900, 64, -1), (900, 64, 0), (9000, 128, -1), (9000, 128, 0)])
+def test_counted_children_of_uneven_programs(api, T, tune, programs, slab, packed):
+    """Programs of 1..12 rows: the child of less curvature may hold more rows; nodes of many pieces."""
+    ts = W.make_train_set(programs, programs, stmts=(1, 12), n_features=19, max_cuts=63)
+    assert (ts.n_rows > 49_152) == (programs == 9000)
+    tune(api.FS_TUNE_TRAIN_SLAB_ROWS, slab)
+    tune(api.FS_TUNE_TRAIN_PACKED, packed)
+    check(api, T, ts, rounds=2, max_depth=7, eta=0.5, lam=1.0)
+
+
 def test_second_boost_goes_deeper_and_a_family_without_a_split(api, T):
     import torch
     sets = [rows_set(3, 3000, 20), rows_set(4, 1, 3), W.make_train_set(5, 700, stmts=(1, 9), n_features=164, max_cuts=63)]
