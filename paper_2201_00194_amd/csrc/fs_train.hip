@@ -44,7 +44,9 @@ constexpr int kChunkShiftMin = 10;      // at least 1024 rows to a histogram wor
                                         // costs as much as 256 rows
 constexpr int kChunkSmallRows = 12288;  // 2048 in batches of more rows than this: a round of depth 6 of 8500 / 12 700 /
                                         // 25 500 rows takes 93.9 / 99.8 / 115.0 us with 1024, 95.3 / 98.7 / 107.7 with 2048
-constexpr int kChunkPieces = 96;
+constexpr int kMostGroups = 1024;       // items of so many rows as a batch has, times the feature groups of a workgroup
+                                        // each: four fit a compute unit.  213 000 rows of five groups: 170 us a round with
+                                        // 2048 rows, 175 with 4096; 308 000 of eleven: 286 with 2048, 280 with 4096, 297 with 8192
 
 // heap node states (undecided or not in the tree: absent)
 enum { kAbsent = 0, kInternal = 2, kLeaf = 3 };
@@ -111,20 +113,19 @@ struct Params {
 
 // ---- set-up kernels ----------------------------------------------------------------------
 
-// Workgroups go to the eight XCDs in turn: takes the workgroups of piece i of a launch, one per
-// feature group, to one XCD, one after the other, so that they share its L2.  `turn` (a trainer's number)
-// moves the first piece to another XCD: families of five pieces would leave three XCDs idle.
-__device__ __forceinline__ void xcd_piece(unsigned w, unsigned groups, unsigned turn, int &piece, int &group)
+// Workgroups go to the eight XCDs in turn, and on an XCD to its compute units in turn.  A grid of
+// (8 x feature groups, trainers, pieces / 8) takes the workgroups of a piece, one per feature group, to one XCD, one
+// after the other, so that they share its L2.  The trainers' first eight pieces come first, then their next
+// eight and so on: what a launch has too many of, being sized for the most pieces a trainer may have, ends up
+// last.  (One trainer after the other left gaps between them, and compute units without work beside others
+// with twice as much: two families of 34 000 rows of 250 features 190 us a round, so 180.)  A trainer's
+// number moves its first piece to another XCD: families of five pieces would leave three XCDs idle.
+__device__ __forceinline__ int xcd_piece(unsigned x, unsigned trainer, unsigned layer)
 {
-    const unsigned k = w >> 3, q = k / groups;
-    group = (int)(k - q * groups);
-    piece = (int)(q * 8 + ((w + 5 * turn) & 7));
+    return (int)(layer * 8 + ((x + 5 * trainer) & 7));
 }
 
-static unsigned xcd_grid(int64_t pieces, unsigned groups)
-{
-    return (unsigned)((pieces + 7) / 8 * 8) * groups;
-}
+constexpr int64_t kMostPieces = 8 * 65535;     // of a trainer in one grid
 
 // bin = number of cuts <= x; NaN takes the last bin.  A workgroup takes 256 rows of sixteen features,
 // whose cut lists fit LDS together, so that a row's sixteen bins leave in one store.
@@ -135,9 +136,10 @@ train_bin_kernel(const float *__restrict__ x, int layout, int n_features, int n_
                  uint8_t *__restrict__ cols)
 {
     __shared__ float c[kHistFeats][kBins];
-    int block, group;
-    xcd_piece(blockIdx.x, (n_features + kHistFeats - 1) / kHistFeats, 0, block, group);
-    if (block * (int64_t)blockDim.x >= n_rows)
+    const int groups = (n_features + kHistFeats - 1) / kHistFeats;      // a piece's to one XCD, as in xcd_piece
+    const int layer = (int)(blockIdx.x >> 3) / groups, group = (int)(blockIdx.x >> 3) - layer * groups;
+    const int64_t block = xcd_piece(blockIdx.x, 0, layer);
+    if (block * blockDim.x >= n_rows)
         return;
     const int f0 = group * kHistFeats;
     const int nf = min(kHistFeats, n_features - f0);
@@ -406,8 +408,8 @@ __device__ __forceinline__ void best_step(double &best, int &best_cut)
     }
 }
 
-// The counted child of a split node: less curvature, the left one on ties.
-__device__ __forceinline__ int counts_left(long long HL, long long HR) { return HL <= HR ? 1 : 0; }
+// The counted child of a split node: less curvature, or fewer rows where they are known; the left one on ties.
+__device__ __forceinline__ int counts_left(long long l, long long r) { return l <= r ? 1 : 0; }
 
 // Totals of a node; `turn` says which of the root's sums the round uses.
 __device__ __forceinline__ void node_sums(const TrainDesc &d, int node, int turn, long long &G, long long &H)
@@ -658,8 +660,8 @@ __device__ __forceinline__ void wave_best_cut_packed(const TrainDesc &d, const P
 
 // Histograms of one level.
 //
-// Of two siblings only the one with less curvature (about the fewer rows) is counted; the other is the
-// parent's histogram minus it.  All sums are integer sums, so that is exact.  A work item is up to 2^shift
+// Of two siblings only one is counted, the one with fewer rows or, before they are known, less curvature; the
+// other is the parent's histogram minus it.  All sums are integer sums, so that is exact.  A work item is up to 2^shift
 // rows; a workgroup takes one item and sixteen features, walks the item's records and gathers each row's
 // bins, 16 bytes at a time.
 //
@@ -775,7 +777,7 @@ __device__ __forceinline__ bool find_counted(const TrainDesc &d, int level, int 
     for (int i = 0; i < kMost; ++i) {
         const int p = lane * per + i, node = n_parents - 1 + (i < per && p < n_parents ? p : 0);
         const int4 s = d.seg[node];
-        left[i] = counts_left(d.h_H[2 * node + 1], d.h_H[2 * node + 2]);
+        left[i] = counts_left(s.x, s.y);
         first[i] = left[i] ? s.z : s.z + s.x;
         count[i] = i < per && p < n_parents ? (left[i] ? s.x : s.y) : 0;
         sum += pieces_of(count[i], shift);
@@ -1177,22 +1179,20 @@ __device__ __forceinline__ void hist_both(const TrainDesc &d, HistLds &s, const 
 }
 
 // Histograms of the level's counted nodes, whose records are in place (of its LDS hist_run uses the bins only).
-// blockIdx = (item and feature group, -, trainer); the last workgroup of a trainer puts the tree of the round
-// before into the model (`emit`).
+// Behind them, in layer `emit`, one workgroup per trainer puts the tree of the round before into the model.
 __global__ void __launch_bounds__(kHistThreads)
-train_hist_kernel(const TrainDesc *__restrict__ descs, int level, int turn, int shift, int hb, int groups, int emit,
-                  int max_depth)
+train_hist_kernel(const TrainDesc *__restrict__ descs, int level, int turn, int shift, int hb, int emit, int max_depth)
 {
     __shared__ __align__(16) unsigned long long lds[kHistWords];
     HistLds &s = *(HistLds *)lds;
-    const TrainDesc &d = descs[blockIdx.z];
-    if (emit && blockIdx.x == gridDim.x - 1) {
-        emit_tree(d, max_depth, turn ^ 1, (int *)lds);
+    const TrainDesc &d = descs[blockIdx.y];
+    if ((int)blockIdx.z == emit) {
+        if (blockIdx.x == 0)
+            emit_tree(d, max_depth, turn ^ 1, (int *)lds);
         return;
     }
     Piece it;
-    int item, group;
-    xcd_piece(blockIdx.x, groups, blockIdx.z, item, group);
+    const int item = xcd_piece(blockIdx.x, blockIdx.y, blockIdx.z), group = (int)blockIdx.x >> 3;
     if (group * kHistFeats >= d.n_features || !find_counted(d, level, shift, item, threadIdx.x & 63, it))
         return;
     hist_both<true>(d, s, it, level, level ? ((it.node - 1) >> 1) - ((1 << (level - 1)) - 1) : 0, turn, shift, group, hb,
@@ -1290,22 +1290,22 @@ __device__ __forceinline__ void move_rows(const TrainDesc &d, Decision &s_dec, c
 }
 
 // One level: decides its nodes, moves their records, counts the smaller children.
-// blockIdx = (moving workgroups, then item and feature group, -, trainer)
+// The first `layers` of the grid move.
 __global__ void __launch_bounds__(kHistThreads)
-train_grow_kernel(const TrainDesc *__restrict__ descs, int level, int turn, int shift, int hb, int groups, int movers,
+train_grow_kernel(const TrainDesc *__restrict__ descs, int level, int turn, int shift, int hb, int layers, int movers,
                   Params prm)
 {
     __shared__ __align__(16) HistLds s;
-    const TrainDesc &d = descs[blockIdx.z];
     const int lane = threadIdx.x & 63;
     Piece it;
-    if ((int)blockIdx.x < movers) {
-        if (find_piece(d, level, kMoveShift, blockIdx.x, lane, it))
+    const TrainDesc &d = descs[blockIdx.y];
+    if ((int)blockIdx.z < layers) {
+        const int index = (int)(blockIdx.z * gridDim.x + blockIdx.x);
+        if (index < movers && find_piece(d, level, kMoveShift, index, lane, it))
             move_rows<false>(d, s.dec, it, level, turn, prm);
         return;
     }
-    int item, group;
-    xcd_piece(blockIdx.x - movers, groups, blockIdx.z, item, group);
+    const int item = xcd_piece(blockIdx.x, blockIdx.y, blockIdx.z - layers), group = (int)blockIdx.x >> 3;
     if (group * kHistFeats >= d.n_features || !find_piece(d, level, shift, item, lane, it))
         return;
     hist_both<false>(d, s, it, level + 1, it.node - ((1 << level) - 1), turn, shift, group, hb, prm);
@@ -1393,9 +1393,9 @@ train_split_kernel(const TrainDesc *__restrict__ descs, int level, int turn, int
     if (level > 0) {
         const int parent = (1 << (level - 1)) - 1 + pair, left = 2 * parent + 1;
         const int4 s = d.seg[parent];
-        const bool count_left = counts_left(d.h_H[left], d.h_H[left + 1]);
         if (s.x == 0)                                            // not split
             return;
+        const bool count_left = grown ? counts_left(d.h_H[left], d.h_H[left + 1]) : counts_left(s.x, s.y);
         it = {count_left ? left : left + 1, count_left ? left + 1 : left, pair, s.z, s.x + s.y};
         if (!grown) {                                            // the pieces are the counted node's
             it.first = count_left ? s.z : s.z + s.x;
@@ -1540,7 +1540,7 @@ static size_t hist_bytes(const fs_trainer *t, int depth, int shift, int hb, size
 }
 
 // What a batch of any of these trainers takes at most.  With items of 2^shift rows the batch's parts are 2 R >> shift
-// and one more per trainer; shift is kChunkShiftMin or such that R are at most kChunkPieces items.
+// and one more per trainer; shift is kChunkShiftMin or such that R are at most kMostGroups items of all features.
 static size_t any_batch_bytes(const std::vector<const fs_trainer *> &trainers)
 {
     int max_len = 0, max_rows = 0;
@@ -1549,7 +1549,9 @@ static size_t any_batch_bytes(const std::vector<const fs_trainer *> &trainers)
         max_rows = std::max(max_rows, t->h.n_rows);
     }
     const int hb = packed_bits(max_len, max_rows);
-    size_t hists = 0, parts = 0, largest_row = 0, single = 0;
+    // words of the parts of that many items: groups of features are whole ones at most
+    const size_t most = (size_t)2 * kMostGroups * kHistWords;
+    size_t hists = 0, parts = 0, largest_row = 0, largest_plane = 0, single = 0;
     for (const fs_trainer *t : trainers) {
         size_t hist, part;
         (void)hist_bytes(t, t->max_depth, kChunkShiftMin, hb, &hist, &part);
@@ -1557,9 +1559,10 @@ static size_t any_batch_bytes(const std::vector<const fs_trainer *> &trainers)
         hists += hist * plane;
         parts += part / words;
         largest_row = std::max(largest_row, words * plane);
-        single = std::max(single, (hist + std::min(part, (2 * kChunkPieces + 1) * words)) * plane);
+        largest_plane = std::max(largest_plane, plane);
+        single = std::max(single, (hist + std::min(part, most + words)) * plane);
     }
-    const size_t all = hists + std::min(parts, 2 * kChunkPieces + trainers.size()) * largest_row;
+    const size_t all = hists + std::min(parts * largest_row, most * largest_plane + trainers.size() * largest_row);
     return std::max(single, std::min(all, most_work()));
 }
 
@@ -1772,7 +1775,7 @@ extern "C" int fs_trainer_create(fs_trainer **out, int32_t n_features, const flo
         return fail_hip(e, "fs_trainer_create: copies");
     }
     hipLaunchKernelGGL(train_bin_kernel,
-                       dim3(xcd_grid((n_rows + 255) / 256, (unsigned)((n_features + kHistFeats - 1) / kHistFeats))),
+                       dim3((unsigned)((n_rows + 2047) / 2048 * 8 * ((n_features + kHistFeats - 1) / kHistFeats))),
                        dim3(256), 0, stream, features, layout, n_features, (int)n_rows, h.r_pad,
                        (const int32_t *)d_cut_off, (const float *)d_cuts, bins, h.row_bytes, cols);
     rc = check_launch("train_bin_kernel launch");
@@ -1893,17 +1896,19 @@ Part make_part(const fs_trainer *const *trainers, int first, int n, int depth)
         pt.max_feat = std::max(pt.max_feat, t->h.n_features);
         max_len = std::max(max_len, t->max_len);
     }
-    // A histogram workgroup takes up to 2^shift rows of a node: 48 to 96 pieces of all the batch's rows
-    // at the root, which with ten feature groups are two to four workgroups per compute unit.
+    // A histogram workgroup takes up to 2^shift rows of a node.
+    const int64_t groups = (pt.max_feat + kHistFeats - 1) / kHistFeats;
     if (total_rows > kChunkSmallRows)
         ++pt.shift;
     pt.grown = total_rows <= kGrowRows;
-    while (pt.shift < 30 && ((int64_t)1 << pt.shift) * kChunkPieces < total_rows)
+    while (pt.shift < 30 && total_rows * groups > (int64_t)kMostGroups << pt.shift)
         ++pt.shift;
     const int v = tune(FS_TUNE_TRAIN_SLAB_ROWS);                 // test / tuning override
     if (v >= 64 && v <= 65536)
         for (pt.shift = 6; (1 << pt.shift) < v;)
             ++pt.shift;
+    while (((int64_t)pt.max_rows >> pt.shift) + (1 << FS_TRAIN_MAX_DEPTH) > kMostPieces)
+        ++pt.shift;
     pt.hb = packed_bits(max_len, pt.max_rows);
     size_t hist, part;
     for (int i = first; i < first + n; ++i)
@@ -1939,13 +1944,16 @@ int train_part(const TrainDesc *d, const Part &pt, int n_rounds, const Params &p
             }
             prof_start(kKernTrainHist, stream);
             if (level == 0 || !grown) {
+                // (below the root the children with fewer rows)
+                const unsigned layers = (unsigned)((most(level ? max_rows / 2 : max_rows, shift) + 7) / 8);
                 const unsigned emit = level == 0 && round > 0 ? 1u : 0u;
-                hipLaunchKernelGGL(train_hist_kernel, dim3(xcd_grid(most(max_rows, shift), groups) + emit, 1u, nt),
-                                   dim3(kHistThreads), 0, stream, d, level, turn, shift, hb, (int)groups, (int)emit, prm.max_depth);
+                hipLaunchKernelGGL(train_hist_kernel, dim3(8 * groups, nt, layers + emit), dim3(kHistThreads), 0, stream, d,
+                                   level, turn, shift, hb, (int)layers, prm.max_depth);
             } else {
-                const unsigned movers = (unsigned)((most(max_rows, kMoveShift) + 7) / 8 * 8);
-                hipLaunchKernelGGL(train_grow_kernel, dim3(movers + xcd_grid(most(max_rows, shift), groups), 1u, nt),
-                                   dim3(kHistThreads), 0, stream, d, level - 1, turn, shift, hb, (int)groups, (int)movers, prm);
+                const unsigned movers = (unsigned)most(max_rows, kMoveShift);
+                const unsigned layers = (movers + 8 * groups - 1) / (8 * groups);
+                hipLaunchKernelGGL(train_grow_kernel, dim3(8 * groups, nt, layers + (unsigned)((most(max_rows, shift) + 7) / 8)),
+                                   dim3(kHistThreads), 0, stream, d, level - 1, turn, shift, hb, (int)layers, (int)movers, prm);
             }
             prof_stop(stream);
             prof_start(kKernTrainSplit, stream);
