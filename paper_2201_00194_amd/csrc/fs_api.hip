@@ -59,7 +59,8 @@ struct Slot {
 // Two scratch regions per device, so that a scoring call and a top-k call never share bytes.
 enum { kScratchScore = 0, kScratchTopk = 1, kScratchRegions = 2 };
 
-// Descriptors of up to kInlineBytes travel as kernel arguments: a small kernel stores them into
+// A few descriptors travel as an argument of the kernels that read them (Descs, fs_internal.h); more of
+// them, up to kInlineBytes, as kernel arguments too: a small kernel stores them into
 // a fixed device buffer (one per kind of call), in stream order in front of the kernels that read
 // them.  No pinned staging, no copy, no event and nothing to wait for, so such a call can also be
 // recorded into a HIP graph.  Longer descriptor arrays go through the ring of pinned slots.
@@ -714,10 +715,17 @@ extern "C" int fs_score_families(int32_t n_families, const fs_family *fams, void
         retile_blocks >= ((int64_t)1 << 31))
         return fail(FS_EUNSUPPORTED, "fs_score_families: too much work for one submission");
 
-    rc = commit_desc(db, sizeof(FamDesc) * (size_t)n_families, stream);
-    if (rc != FS_OK)
-        return rc;
+    // by value where every kernel of the call takes them so (not that of long treelet launches: with a pointer that
+    // may be either its coder compiles to 2 % more time, and such a call gains 1 us)
+    const bool near = n_families <= kNearFams && retile_blocks + bin_blocks + rk_blocks + trav_blocks == 0 &&
+                      (tl_blocks[0] == 0 || tl_form[0] != kTreeletPair);
+    if (!near) {
+        rc = commit_desc(db, sizeof(FamDesc) * (size_t)n_families, stream);
+        if (rc != FS_OK)
+            return rc;
+    }
     const FamDesc *d_desc = (const FamDesc *)db.dev;
+    const Descs<FamDesc> descs = {near ? nullptr : d_desc, h, n_families};
     if (retile_blocks > 0) {
         prof_start(kKernPack, stream);
         rc = launch_retile(d_desc, n_families, (int)retile_blocks, stream);
@@ -727,10 +735,10 @@ extern "C" int fs_score_families(int32_t n_families, const fs_family *fams, void
         prof_start(kKernTraverse, stream);
         for (int i = 0; i < 2 && rc == FS_OK; ++i)
             if (tl_blocks[i] > 0)
-                rc = launch_treelet(d_desc, n_families, i, tl_form[i], (int)tl_blocks[i], tl_dump[i], stream);
+                rc = launch_treelet(descs, i, tl_form[i], (int)tl_blocks[i], tl_dump[i], stream);
         for (int md = 0; md < kLdsModes && rc == FS_OK; ++md)
             if (lds_blocks[md] > 0)
-                rc = launch_traverse_lds(d_desc, n_families, md, (int)lds_blocks[md], groups_per_wg[md],
+                rc = launch_traverse_lds(descs, md, (int)lds_blocks[md], groups_per_wg[md],
                                          dump[md], stream);
         prof_stop(stream);
     }
@@ -751,7 +759,7 @@ extern "C" int fs_score_families(int32_t n_families, const fs_family *fams, void
     }
     if (rc == FS_OK && seg_blocks > 0) {
         prof_start(kKernSegsum, stream);
-        rc = launch_segsum(d_desc, n_families, (int)seg_blocks, stream);
+        rc = launch_segsum(descs, (int)seg_blocks, stream);
         prof_stop(stream);
     }
     const int rc2 = finish_desc(db, stream);
@@ -972,17 +980,21 @@ extern "C" int fs_topk(int32_t n_requests, const fs_topk_req *reqs, void *stream
     }
     if ((size_t)(comp - (unsigned long long *)ctx->scratch[kScratchTopk]) > comp_total || b != n_blocks || m != n_merge)
         return fail(FS_EDEVICE, "fs_topk: internal plan mismatch");
-    rc = commit_desc(db, total_bytes, stream);
-    if (rc != FS_OK)
-        return rc;
+    const bool near = n_blocks <= kNearTopk && n_merge <= kNearMerge && level_pairs[0] <= kNearPairs;
+    if (!near) {
+        rc = commit_desc(db, total_bytes, stream);
+        if (rc != FS_OK)
+            return rc;
+    }
+    const char *dev = (const char *)db.dev;
     prof_start(kKernTopk, stream);
-    rc = launch_topk((const TopkDesc *)db.dev, (int)n_blocks, max_k, stream);
+    rc = launch_topk({near ? nullptr : (const TopkDesc *)dev, h, (int)n_blocks}, max_k, stream);
     if (rc == FS_OK && n_merge)
-        rc = launch_topk_merge((const TopkMergeDesc *)((const char *)db.dev + merge_off),
-                               (int)n_merge, max_comp, stream);
+        rc = launch_topk_merge({near ? nullptr : (const TopkMergeDesc *)(dev + merge_off), hm, (int)n_merge},
+                               max_comp, stream);
     for (int lv = 0; lv < n_levels && rc == FS_OK; ++lv)
-        rc = launch_topk_pairs((const TopkPairDesc *)((const char *)db.dev + path_off) + level_at[lv],
-                               (int)level_pairs[lv], level_entries[lv], stream);
+        rc = launch_topk_pairs({near ? nullptr : (const TopkPairDesc *)(dev + path_off) + level_at[lv], hp + level_at[lv],
+                                (int)level_pairs[lv]}, level_entries[lv], stream);
     prof_stop(stream);
     const int rc2 = finish_desc(db, stream);
     return rc != FS_OK ? rc : rc2;

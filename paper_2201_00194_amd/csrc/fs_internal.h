@@ -186,6 +186,60 @@ struct FamDesc {
     int32_t tl_block0[2];            // first block of this family in the two treelet launches
 };
 
+// Descriptors reach a kernel by value, as its last argument, where a call has few of them: a call of two or three
+// short kernels otherwise pays for another launch that only stores them (scoring and cutting 320 / 4096
+// programs 30.6 / 35.5 us, so 27.8 / 31.9).  More of them lie in device memory at `far`.
+constexpr int kNearFams = 14;
+struct NearFams {
+    FamDesc d[kNearFams];
+};
+struct FamArgs1 {              // arguments of kernels with one, two and three numbers
+    const FamDesc *far;
+    int a;
+    NearFams near;
+};
+struct FamArgs2 {
+    const FamDesc *far;
+    int a, b;
+    NearFams near;
+};
+struct FamArgs3 {
+    const FamDesc *far;
+    int a, b, c;
+    NearFams near;
+};
+static_assert(sizeof(NearFams) <= 3600, "kernel arguments are 4 KB at most, hidden ones among them");
+
+// What the launchers take: descriptors in device memory or, where far is null, n of them at `host`.
+template <class T>
+struct Descs {
+    const T *far;
+    const T *host;
+    int n;
+};
+// In a kernel: the descriptors, read-only memory either way so that they come through scalar loads; `at`: where the
+// by-value ones lie among the kernel's arguments, which are laid out like a struct.
+template <class T>
+__device__ __forceinline__ const T *where_descs(const T *far, uint32_t at)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    const uintptr_t near = (uintptr_t)__builtin_amdgcn_kernarg_segment_ptr() + at;
+    return (const T *)(__attribute__((address_space(4))) const T *)(far ? (uintptr_t)far : near);
+#else
+    (void)at;
+    return far;
+#endif
+}
+template <class Near, class T>
+Near near_descs(const Descs<T> &from)
+{
+    Near near;
+    if (!from.far)
+        for (int i = 0; i < from.n; ++i)
+            near.d[i] = from.host[i];
+    return near;
+}
+
 // One workgroup of the first top-k stage: the whole request, or one slice of a large one.
 struct TopkDesc {
     const float *score;
@@ -232,10 +286,21 @@ struct TopkPairDesc {
 __host__ __device__ inline int rank_tile_cols(int n_features) { return (n_features + 1) & ~1; }
 __host__ __device__ inline uint32_t rank_feature_offset(int f) { return (uint32_t)(f >> 1) * 256u + (uint32_t)(f & 1) * 2u; }
 
+constexpr int kNearTopk = 48, kNearMerge = 48, kNearPairs = 32;
+struct NearTopk {
+    TopkDesc d[kNearTopk];
+};
+struct NearMerge {
+    TopkMergeDesc d[kNearMerge];
+};
+struct NearPairs {
+    TopkPairDesc d[kNearPairs];
+};
+
 // ---- launchers (each returns FS_OK or records an error) ---------------------------------------
 int launch_traverse_global(const FamDesc *d_desc, int n_families, int total_blocks,
                            hipStream_t stream);
-int launch_traverse_lds(const FamDesc *d_desc, int n_families, int mode, int total_blocks,
+int launch_traverse_lds(const Descs<FamDesc> &descs, int mode, int total_blocks,
                         int groups_per_wg, bool dump, hipStream_t stream);
 // Tile groups one workgroup of the LDS traversal takes in a row; host (workgroup counts) and
 // kernel agree on it through this function.  From its second group on a workgroup receives the
@@ -254,12 +319,12 @@ int launch_traverse_rank(const FamDesc *d_desc, int n_families, int total_blocks
                          hipStream_t stream);
 // `launch`: which of FamDesc::tl_block0 numbers the blocks (a call makes up to two launches: models whose
 // chunks only fit a whole compute unit's LDS cannot take the first form).
-int launch_treelet(const FamDesc *d_desc, int n_families, int launch, int form, int total_blocks, bool dump,
+int launch_treelet(const Descs<FamDesc> &descs, int launch, int form, int total_blocks, bool dump,
                    hipStream_t stream);
-int launch_segsum(const FamDesc *d_desc, int n_families, int total_blocks, hipStream_t stream);
-int launch_topk(const TopkDesc *d_desc, int n_blocks, int max_k, hipStream_t stream);
+int launch_segsum(const Descs<FamDesc> &descs, int total_blocks, hipStream_t stream);
+int launch_topk(const Descs<TopkDesc> &descs, int max_k, hipStream_t stream);
 // max_padded: largest (slices * k rounded up to a power of two) over the requests
-int launch_topk_merge(const TopkMergeDesc *d_desc, int n_requests, int max_padded, hipStream_t stream);
+int launch_topk_merge(const Descs<TopkMergeDesc> &descs, int max_padded, hipStream_t stream);
 constexpr int kTopkSliceMin = 8192;      // requests at least this long are split into slices
 constexpr int kTopkSliceEntries = 2048;  // of at least this many entries
 constexpr int kTopkMaxSlices = 16;
@@ -304,7 +369,7 @@ inline TopkPlan topk_plan(int n, int k)
     }
     return p;
 }
-int launch_topk_pairs(const TopkPairDesc *d_desc, int n_pairs, int max_entries, hipStream_t stream);
+int launch_topk_pairs(const Descs<TopkPairDesc> &descs, int max_entries, hipStream_t stream);
 int launch_retile(const FamDesc *d_desc, int n_families, int total_blocks, hipStream_t stream);
 int launch_pack_colblock64(const float *in, int64_t n_rows, int32_t n_features, float *out,
                            hipStream_t stream);

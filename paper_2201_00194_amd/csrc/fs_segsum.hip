@@ -14,8 +14,9 @@
 namespace fs {
 
 __global__ void __launch_bounds__(kSegProgsPerBlock)
-segsum_kernel(const FamDesc *__restrict__ descs, int n_families)
+segsum_kernel(const FamDesc *__restrict__ far, int n_families, NearFams)
 {
+    const FamDesc *descs = where_descs(far, offsetof(FamArgs1, near));
     int lo = 0, hi = n_families - 1;
     while (lo < hi) {
         int mid = (lo + hi + 1) >> 1;
@@ -81,10 +82,10 @@ segsum_kernel(const FamDesc *__restrict__ descs, int n_families)
         d.prog_score[p] = acc;
 }
 
-int launch_segsum(const FamDesc *d_desc, int n_families, int total_blocks, hipStream_t stream)
+int launch_segsum(const Descs<FamDesc> &descs, int total_blocks, hipStream_t stream)
 {
     hipLaunchKernelGGL(segsum_kernel, dim3(total_blocks), dim3(kSegProgsPerBlock), 0, stream,
-                       d_desc, n_families);
+                       descs.far, descs.n, near_descs<NearFams>(descs));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return fail_hip(e, "segsum_kernel launch");

@@ -55,10 +55,10 @@ __device__ __forceinline__ void load_keys(const float *__restrict__ score, int b
 }
 
 __global__ void __launch_bounds__(kTopkThreads)
-topk_kernel(const TopkDesc *__restrict__ descs)
+topk_kernel(const TopkDesc *__restrict__ far, NearTopk)
 {
     extern __shared__ unsigned long long cand[];   // [kpow2] then small scratch
-    const TopkDesc d = descs[blockIdx.x];
+    const TopkDesc d = where_descs(far, sizeof(far))[blockIdx.x];
     const int n = d.sub_end - d.sub_begin, k = d.k;   // this workgroup's entries
     const int kk = min(n, k);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -246,10 +246,10 @@ topk_kernel(const TopkDesc *__restrict__ descs)
 // max(A[i], B[kp-1-i]) holds the best kp of two descending lists as a bitonic sequence, and
 // q compare-exchange rounds sort it.  What is left in list 0 is the answer.
 __global__ void __launch_bounds__(kTopkThreads)
-topk_merge_kernel(const TopkMergeDesc *__restrict__ descs)
+topk_merge_kernel(const TopkMergeDesc *__restrict__ far, NearMerge)
 {
     extern __shared__ unsigned long long cand[];
-    const TopkMergeDesc d = descs[blockIdx.x];
+    const TopkMergeDesc d = where_descs(far, sizeof(far))[blockIdx.x];
     const int tid = threadIdx.x;
     const int k = d.k, lists = d.n_comp / k;
     int q = 0;
@@ -309,9 +309,9 @@ topk_merge_kernel(const TopkMergeDesc *__restrict__ descs)
 // finds that count by bisection and stores the entry if its place is among the best `lo`.
 // blockIdx.y names the pair, blockIdx.x a run of kTopkThreads entries of (a then b).
 __global__ void __launch_bounds__(kTopkThreads)
-topk_pair_kernel(const TopkPairDesc *__restrict__ descs)
+topk_pair_kernel(const TopkPairDesc *__restrict__ far, NearPairs)
 {
-    const TopkPairDesc d = descs[blockIdx.y];
+    const TopkPairDesc d = where_descs(far, sizeof(far))[blockIdx.y];
     const int e = blockIdx.x * kTopkThreads + threadIdx.x;
     if (e < d.la + d.lb) {
         const bool in_a = e < d.la;
@@ -351,13 +351,15 @@ topk_pair_kernel(const TopkPairDesc *__restrict__ descs)
     }
 }
 
-int launch_topk_pairs(const TopkPairDesc *d_desc, int n_pairs, int max_entries, hipStream_t stream)
+int launch_topk_pairs(const Descs<TopkPairDesc> &descs, int max_entries, hipStream_t stream)
 {
     const int runs = max_entries > 0 ? (max_entries + kTopkThreads - 1) / kTopkThreads : 1;
     constexpr int kMaxY = 32768;             // pairs per launch (grid.y)
-    for (int at = 0; at < n_pairs; at += kMaxY) {
-        const int cnt = n_pairs - at < kMaxY ? n_pairs - at : kMaxY;
-        hipLaunchKernelGGL(topk_pair_kernel, dim3(runs, cnt), dim3(kTopkThreads), 0, stream, d_desc + at);
+    const NearPairs near = near_descs<NearPairs>(descs);
+    for (int at = 0; at < descs.n; at += kMaxY) {
+        const int cnt = descs.n - at < kMaxY ? descs.n - at : kMaxY;
+        hipLaunchKernelGGL(topk_pair_kernel, dim3(runs, cnt), dim3(kTopkThreads), 0, stream,
+                           descs.far ? descs.far + at : nullptr, near);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess)
             return fail_hip(e, "topk_pair_kernel launch");
@@ -365,7 +367,7 @@ int launch_topk_pairs(const TopkPairDesc *d_desc, int n_pairs, int max_entries, 
     return FS_OK;
 }
 
-int launch_topk_merge(const TopkMergeDesc *d_desc, int n_requests, int max_padded, hipStream_t stream)
+int launch_topk_merge(const Descs<TopkMergeDesc> &descs, int max_padded, hipStream_t stream)
 {
     if (max_padded > kTopkMergeCap)
         return fail(FS_EUNSUPPORTED, "top-k merge of %d candidates exceeds %d", max_padded, kTopkMergeCap);
@@ -379,14 +381,14 @@ int launch_topk_merge(const TopkMergeDesc *d_desc, int n_requests, int max_padde
         if (dev >= 0 && dev < 16)
             configured[dev] = lds;
     }
-    hipLaunchKernelGGL(topk_merge_kernel, dim3(n_requests), dim3(kTopkThreads), lds, stream, d_desc);
+    hipLaunchKernelGGL(topk_merge_kernel, dim3(descs.n), dim3(kTopkThreads), lds, stream, descs.far, near_descs<NearMerge>(descs));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return fail_hip(e, "topk_merge_kernel launch");
     return FS_OK;
 }
 
-int launch_topk(const TopkDesc *d_desc, int n_requests, int max_k, hipStream_t stream)
+int launch_topk(const Descs<TopkDesc> &descs, int max_k, hipStream_t stream)
 {
     int kpow2 = 2;
     while (kpow2 < max_k)
@@ -401,7 +403,7 @@ int launch_topk(const TopkDesc *d_desc, int n_requests, int max_k, hipStream_t s
         if (dev >= 0 && dev < 16)
             configured[dev] = lds;
     }
-    hipLaunchKernelGGL(topk_kernel, dim3(n_requests), dim3(kTopkThreads), lds, stream, d_desc);
+    hipLaunchKernelGGL(topk_kernel, dim3(descs.n), dim3(kTopkThreads), lds, stream, descs.far, near_descs<NearTopk>(descs));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return fail_hip(e, "topk_kernel launch");
@@ -542,9 +544,9 @@ extern "C" int fs_topk_noalloc(int32_t n_requests, const fs_topk_req *reqs, void
     if (e != hipSuccess)
         return fail_hip(e, "topk_store_desc_kernel launch");
     prof_start(kKernTopk, stream);
-    int rc = launch_topk((const TopkDesc *)base, (int)n_blocks, max_k, stream);
+    int rc = launch_topk({(const TopkDesc *)base, nullptr, (int)n_blocks}, max_k, stream);
     if (rc == FS_OK && n_merge)
-        rc = launch_topk_merge((const TopkMergeDesc *)(base + merge_off), (int)n_merge, max_comp, stream);
+        rc = launch_topk_merge({(const TopkMergeDesc *)(base + merge_off), nullptr, (int)n_merge}, max_comp, stream);
     prof_stop(stream);
     return rc;
 }

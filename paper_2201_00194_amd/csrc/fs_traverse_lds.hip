@@ -132,8 +132,9 @@ __device__ __forceinline__ ChunkView load_chunk(const ChunkHdr *hdr_)
 
 template <bool DUMP, bool MULTI>
 __global__ void __launch_bounds__(64 * kLdsMaxWaves)
-traverse_lds_kernel(const FamDesc *__restrict__ descs, int n_families, int mode, int groups_per_wg)
+traverse_lds_kernel(const FamDesc *__restrict__ far, int n_families, int mode, int groups_per_wg, NearFams)
 {
+    const FamDesc *descs = where_descs(far, offsetof(FamArgs3, near));
     const int kLdsThreads = blockDim.x;
     const int kLdsWaves = kLdsThreads >> 6;
     int lo = 0, hi = n_families - 1;
@@ -411,7 +412,7 @@ traverse_lds_kernel(const FamDesc *__restrict__ descs, int n_families, int mode,
     }   // tile groups of this workgroup
 }
 
-int launch_traverse_lds(const FamDesc *d_desc, int n_families, int mode, int total_blocks,
+int launch_traverse_lds(const Descs<FamDesc> &descs, int mode, int total_blocks,
                         int groups_per_wg, bool dump, hipStream_t stream)
 {
     const int kLdsBytes = kLdsModeBytes[mode];
@@ -436,8 +437,8 @@ int launch_traverse_lds(const FamDesc *d_desc, int n_families, int mode, int tot
         if (dev >= 0 && dev < 16)
             configured[dev][form] = true;
     }
-    hipLaunchKernelGGL(kernel, dim3(total_blocks), dim3(kLdsThreads), kLdsBytes, stream, d_desc,
-                       n_families, mode, groups_per_wg);
+    hipLaunchKernelGGL(kernel, dim3(total_blocks), dim3(kLdsThreads), kLdsBytes, stream, descs.far,
+                       descs.n, mode, groups_per_wg, near_descs<NearFams>(descs));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return fail_hip(e, "traverse_lds_kernel launch");

@@ -621,8 +621,9 @@ treelet_pair_kernel(const FamDesc *__restrict__ descs, int n_families, int launc
 // over what follows the first buffer.
 template <int T, int S, bool DUMP>
 __global__ void __launch_bounds__(64 * T * S)
-treelet_spread_kernel(const FamDesc *__restrict__ descs, int n_families, int launch)
+treelet_spread_kernel(const FamDesc *__restrict__ far, int n_families, int launch, NearFams)
 {
+    const FamDesc *descs = where_descs(far, offsetof(FamArgs2, near));
     constexpr int kWaves = T * S;
     const FamDesc &d = descs[treelet_family(descs, n_families, launch)];
     const TreeletModel m = load_model(d.tl);
@@ -717,9 +718,10 @@ treelet_spread_kernel(const FamDesc *__restrict__ descs, int n_families, int lau
         FS_GLOBAL(float, d.row_score)[r] = acc;
 }
 
-template <class Kernel>
-static int launch_form(Kernel kernel, int form, int threads, int lds, const FamDesc *d_desc, int n_families,
-                       int launch, int total_blocks, hipStream_t stream)
+// `near`: the descriptors by value, for kernels that take them so.
+template <class Kernel, class... Near>
+static int launch_form(Kernel kernel, int form, int threads, int lds, const Descs<FamDesc> &descs,
+                       int launch, int total_blocks, hipStream_t stream, Near... near)
 {
     static bool configured[16][kTreeletForms * 2] = {};
     int dev = 0;
@@ -735,34 +737,35 @@ static int launch_form(Kernel kernel, int form, int threads, int lds, const FamD
         if (dev >= 0 && dev < 16)
             configured[dev][form] = true;
     }
-    hipLaunchKernelGGL(kernel, dim3(total_blocks), dim3(threads), lds, stream, d_desc, n_families, launch);
+    hipLaunchKernelGGL(kernel, dim3(total_blocks), dim3(threads), lds, stream, descs.far, descs.n, launch, near...);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return fail_hip(e, "treelet kernel launch");
     return FS_OK;
 }
 
-int launch_treelet(const FamDesc *d_desc, int n_families, int launch, int form, int total_blocks, bool dump,
+int launch_treelet(const Descs<FamDesc> &descs, int launch, int form, int total_blocks, bool dump,
                    hipStream_t stream)
 {
+    const NearFams near = near_descs<NearFams>(descs);
     const int id = 2 * form + (dump ? 1 : 0);
     switch (id) {
     case 2 * kTreeletPair:
-        return launch_form(treelet_pair_kernel<false>, id, 64 * kPairWaves, kTreeletLds, d_desc, n_families, launch, total_blocks, stream);
+        return launch_form(treelet_pair_kernel<false>, id, 64 * kPairWaves, kTreeletLds, descs, launch, total_blocks, stream);
     case 2 * kTreeletPair + 1:
-        return launch_form(treelet_pair_kernel<true>, id, 64 * kPairWaves, kTreeletLds, d_desc, n_families, launch, total_blocks, stream);
+        return launch_form(treelet_pair_kernel<true>, id, 64 * kPairWaves, kTreeletLds, descs, launch, total_blocks, stream);
     case 2 * kTreeletSpread4:
-        return launch_form(treelet_spread_kernel<4, 3, false>, id, 768, kTreeletLdsWhole, d_desc, n_families, launch, total_blocks, stream);
+        return launch_form(treelet_spread_kernel<4, 3, false>, id, 768, kTreeletLdsWhole, descs, launch, total_blocks, stream, near);
     case 2 * kTreeletSpread4 + 1:
-        return launch_form(treelet_spread_kernel<4, 3, true>, id, 768, kTreeletLdsWhole, d_desc, n_families, launch, total_blocks, stream);
+        return launch_form(treelet_spread_kernel<4, 3, true>, id, 768, kTreeletLdsWhole, descs, launch, total_blocks, stream, near);
     case 2 * kTreeletSpread2:
-        return launch_form(treelet_spread_kernel<2, 6, false>, id, 768, kTreeletLdsWhole, d_desc, n_families, launch, total_blocks, stream);
+        return launch_form(treelet_spread_kernel<2, 6, false>, id, 768, kTreeletLdsWhole, descs, launch, total_blocks, stream, near);
     case 2 * kTreeletSpread2 + 1:
-        return launch_form(treelet_spread_kernel<2, 6, true>, id, 768, kTreeletLdsWhole, d_desc, n_families, launch, total_blocks, stream);
+        return launch_form(treelet_spread_kernel<2, 6, true>, id, 768, kTreeletLdsWhole, descs, launch, total_blocks, stream, near);
     case 2 * kTreeletSpread1:
-        return launch_form(treelet_spread_kernel<1, 12, false>, id, 768, kTreeletLdsWhole, d_desc, n_families, launch, total_blocks, stream);
+        return launch_form(treelet_spread_kernel<1, 12, false>, id, 768, kTreeletLdsWhole, descs, launch, total_blocks, stream, near);
     case 2 * kTreeletSpread1 + 1:
-        return launch_form(treelet_spread_kernel<1, 12, true>, id, 768, kTreeletLdsWhole, d_desc, n_families, launch, total_blocks, stream);
+        return launch_form(treelet_spread_kernel<1, 12, true>, id, 768, kTreeletLdsWhole, descs, launch, total_blocks, stream, near);
     default:
         return fail(FS_EUNSUPPORTED, "unknown treelet form %d", form);
     }

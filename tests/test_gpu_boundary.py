@@ -156,3 +156,35 @@ def test_small_calls_replay_from_a_hip_graph(api, oracle):
         api.fs_topk(other_req)
         torch.cuda.synchronize()
         assert np.array_equal(o_idx.cpu().numpy(), oracle.topk(other.cpu().numpy(), 100)[0])
+
+
+@pytest.mark.parametrize("n_fams,trees", [(14, 36), (15, 36), (14, 8), (15, 8)])
+def test_descriptors_by_value_and_in_memory(api, oracle, n_fams, trees):
+    """Up to 14 families travel inside the kernels' arguments (both the treelet walk and the LDS walk), 48
+    top-k workgroups and merges; calls of other families queue up behind each other unsynchronised."""
+    import torch
+    fams = [W.make_small_family(seed=400 + i, n_programs=40 + 7 * i, stmts=(1, 5), n_trees=trees, depth=5,
+                                early_leaf_q=0.1, k=9) for i in range(n_fams)]
+    devs = [api.DeviceFamily(f) for f in fams]
+    torch.cuda.synchronize()
+    for part in (slice(0, n_fams), slice(0, 1), slice(3, n_fams)):
+        api.fs_score_families([d.family() for d in devs[part]])
+        api.fs_topk([d.topk_request() for d in devs[part]])
+    torch.cuda.synchronize()
+    for f, d in zip(fams, devs):
+        same(d, f, *expect(oracle, f))
+
+
+@pytest.mark.parametrize("n_req,n,k", [(48, 300, 5), (49, 300, 5), (6, 17_000, 40), (7, 17_000, 40), (1, 65_536, 9000),
+                                       (2, 65_536, 9000), (3, 65_536, 9000)])
+def test_topk_descriptors_by_value_and_in_memory(api, oracle, n_req, n, k):
+    import torch
+    rng = np.random.default_rng(n_req)
+    scores = [rng.integers(0, 5000, n).astype(np.float32) for _ in range(n_req)]
+    dev = [torch.from_numpy(s).cuda() for s in scores]
+    idx = torch.zeros(n_req * k, dtype=torch.int32, device="cuda")
+    api.fs_topk([api.TopkRequest(d, n, k, idx[i * k:(i + 1) * k]) for i, d in enumerate(dev)])
+    torch.cuda.synchronize()
+    got = idx.cpu().numpy().reshape(n_req, k)
+    for i, s in enumerate(scores):
+        assert np.array_equal(got[i], oracle.topk(s, k)[0])
