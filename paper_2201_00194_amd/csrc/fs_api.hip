@@ -1,4 +1,5 @@
 // Host side of the C ABI: argument validation, model packing, descriptor upload, launches.
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -563,6 +564,7 @@ extern "C" int fs_score_families(int32_t n_families, const fs_family *fams, void
     FamDesc *h = (FamDesc *)db.host;
     int64_t trav_blocks = 0, seg_blocks = 0, lds_blocks[kLdsModes] = {0, 0};
     int64_t rk_blocks = 0, bin_blocks = 0, retile_blocks = 0, tl_blocks[2] = {0, 0};
+    int rk_regs = 0;
     bool rk_dump = false, tl_dump[2] = {false, false};
     const Walks walks = choose_walks(n_families, fams, ctx->n_compute_units);
     if (tune(FS_TUNE_VERBOSE) > 0) {
@@ -654,7 +656,8 @@ extern "C" int fs_score_families(int32_t n_families, const fs_family *fams, void
         d.ranks = nullptr;
         d.rk_depth = a.model->rk_depth;
         d.rk_tiles = a.model->rk_tiles;
-        d.rk_trees_per_chunk = a.model->rk_trees_per_chunk;
+        d.rk_slots = a.model->rk_slots;
+        d.rk_trees_per_slot = a.model->rk_trees_per_slot;
         d.rk_tree_bytes = a.model->rk_tree_bytes;
         d.rk_tile0 = a.model->rk_tile0;
         d.rk_block0 = (int32_t)rk_blocks;
@@ -693,6 +696,8 @@ extern "C" int fs_score_families(int32_t n_families, const fs_family *fams, void
             d.bin_tiles_per_block = (int32_t)tpb;
             bin_blocks += (int64_t)d.bin_groups * ((tiles + tpb - 1) / tpb);
             rk_blocks += (tiles + a.model->rk_tiles - 1) / a.model->rk_tiles;
+            const int slot_bytes = a.model->rk_trees_per_slot * a.model->rk_tree_bytes, at_once = a.model->rk_tiles * 64 * 16;
+            rk_regs = std::max(rk_regs, (slot_bytes + at_once - 1) / at_once);
             if (a.leaf_idx && a.n_rows > 0)
                 rk_dump = true;
         } else if (a.model->lds_ok && (colblock || in_kernel)) {
@@ -749,7 +754,7 @@ extern "C" int fs_score_families(int32_t n_families, const fs_family *fams, void
     }
     if (rc == FS_OK && rk_blocks > 0) {
         prof_start(kKernTraverseRank, stream);
-        rc = launch_traverse_rank(d_desc, n_families, (int)rk_blocks, rk_dump, stream);
+        rc = launch_traverse_rank(d_desc, n_families, (int)rk_blocks, rk_regs, rk_dump, stream);
         prof_stop(stream);
     }
     if (rc == FS_OK && trav_blocks > 0) {

@@ -118,7 +118,8 @@ struct fs_model {
     bool rank_ok;
     int32_t rk_depth;          // common depth of the trees
     int32_t rk_tiles;          // 64-row tiles per workgroup
-    int32_t rk_trees_per_chunk;
+    int32_t rk_slots;          // wavefronts of a tile that have trees
+    int32_t rk_trees_per_slot;
     int32_t rk_tree_bytes;     // 4 * 2^(depth+1): heap words 1 .. 2^(depth+1)-1, word 0 unused
     int32_t rk_tile0;          // LDS byte offset of the first (u16) feature tile
     uint32_t *d_rk_nodes;      // [n_trees][2^(depth+1)] 1-based heap order: splits then leaf values
@@ -170,7 +171,7 @@ struct FamDesc {
     const uint16_t *rk_ids;
     const float *cuts;
     uint16_t *ranks;                 // scratch: rank-coded feature tiles [tile][feature][64]
-    int32_t rk_depth, rk_tiles, rk_trees_per_chunk, rk_tree_bytes, rk_tile0;
+    int32_t rk_depth, rk_tiles, rk_slots, rk_trees_per_slot, rk_tree_bytes, rk_tile0;
     int32_t rk_block0;               // first block of the rank traversal grid
     int32_t bin_block0;              // first block of the rank-coding grid
     int32_t bin_groups;              // feature groups of this family in the rank-coding grid
@@ -181,7 +182,6 @@ struct FamDesc {
     int32_t retile_block0;           // first block of the re-tiling grid
     int32_t retile_colblocks;        // column blocks per tile (0: family not re-tiled)
     int32_t cut_bits;                // threshold tables are padded to 2^cut_bits entries
-    int32_t pad;
     const TreeletModel *tl;          // byte-rank treelets
     int32_t tl_block0[2];            // first block of this family in the two treelet launches
 };
@@ -315,7 +315,8 @@ __host__ __device__ inline int lds_groups_per_wg(int layout, int n_features, int
     return want < 1 ? 1 : want;
 }
 int launch_rank_code(const FamDesc *d_desc, int n_families, int total_blocks, hipStream_t stream);
-int launch_traverse_rank(const FamDesc *d_desc, int n_families, int total_blocks, bool dump,
+// `regs`: most 16-byte pieces of a slot's trees that a thread copies.
+int launch_traverse_rank(const FamDesc *d_desc, int n_families, int total_blocks, int regs, bool dump,
                          hipStream_t stream);
 // `launch`: which of FamDesc::tl_block0 numbers the blocks (a call makes up to two launches: models whose
 // chunks only fit a whole compute unit's LDS cannot take the first form).
@@ -395,7 +396,7 @@ constexpr int kBinTilesPerBlock = 256;
 constexpr int kBinTableBytes = 64 * 1024;
 constexpr int kRankWaves = 12;
 constexpr int kRankLdsBytes = 160 * 1024;
-constexpr int kRankPrefetchRegs = 6;     // 16-byte registers per thread for the next chunk
+constexpr int kRankMostTrees = 8;        // of a slot
 
 constexpr int kTravRowsPerBlock = 256;   // rows per block of the global-memory traversal
 constexpr int kSegProgsPerBlock = 256;   // programs per block of the segmented sum

@@ -525,43 +525,44 @@ void build_rank_format(fs_model *m, int n_features, int n_trees, int depth, cons
         }
     }
 
-    // tiles per workgroup (must divide the wavefront count): most (tiles x trees per chunk)
+    // tiles per workgroup (must divide the wavefront count): most walks side by side, up to eight trees a slot; of
+    // equals the most tiles, as every workgroup reads the whole model
     const size_t tree_bytes = words * 4, tile_bytes = (size_t)rank_tile_cols(n_features) * 128;
-    const size_t reg_limit = (size_t)kRankPrefetchRegs * 64 * kRankWaves * 16;
-    int best_t = 0, best_per = 0, best_score = -1;
+    int best_t = 0, best_slots = 0, best_per = 0, best_score = 0;
     const int forced = tune(FS_TUNE_RANK_TILES);
     const int choices[] = {6, 4, 3, 2, 1};
     for (int nt : choices) {
         if (forced > 0 && nt != forced)
             continue;
-        const long avail = (long)kRankLdsBytes - (long)nt * (long)tile_bytes - 64;
-        if (avail < (long)(tree_bytes + (size_t)nt * 256))
-            continue;
-        size_t per_c = (size_t)avail / (tree_bytes + (size_t)nt * 256);
-        if (per_c > reg_limit / tree_bytes) per_c = reg_limit / tree_bytes;
-        if (per_c > (size_t)kMaxChunkTrees) per_c = kMaxChunkTrees;
-        if (per_c < 1)
-            continue;
-        int score = nt * (int)per_c;
-        if (score > 64) score = 64;
-        if (score > best_score) {
-            best_score = score;
-            best_t = nt;
-            best_per = (int)per_c;
+        const long avail = (long)kRankLdsBytes - (long)nt * (long)(tile_bytes + 256) - 128;
+        const int fit = avail < 0 ? 0 : (int)std::min<size_t>((size_t)avail / tree_bytes, 1024);
+        for (int slots = std::min(kRankWaves / nt, fit); slots >= 1; --slots) {
+            const int per = std::min(fit / slots, kRankMostTrees);
+            const int score = std::min(nt * slots * per, 64);
+            if (score > best_score) {
+                best_score = score;
+                best_t = nt;
+                best_slots = slots;
+                best_per = per;
+            }
         }
     }
     if (best_t == 0)
         return;
+    // as many trees in every turn as the number of turns needs
+    const int rounds = std::max(1, (n_trees + best_slots * best_per - 1) / (best_slots * best_per));
+    best_per = std::max(1, (n_trees + best_slots * rounds - 1) / (best_slots * rounds));
     m->rank_ok = true;
     m->rk_depth = depth;
     m->rk_tiles = best_t;
-    m->rk_trees_per_chunk = chunk_tree_target(n_trees, best_per, kRankWaves / best_t);
+    m->rk_slots = best_slots;
+    m->rk_trees_per_slot = best_per;
     m->rk_tree_bytes = (int32_t)tree_bytes;
     m->rk_tile0 = kRankLdsBytes - best_t * (int32_t)tile_bytes;
     m->cut_bits = bits;
     if (tune(FS_TUNE_VERBOSE) > 0)
-        fprintf(stderr, "fs_model_create: rank-coded depth=%d tiles=%d trees/chunk=%d max_cuts=%zu\n",
-                depth, best_t, best_per, max_cuts);
+        fprintf(stderr, "fs_model_create: rank-coded depth=%d tiles=%d slots=%d of %d trees max_cuts=%zu\n",
+                depth, best_t, best_slots, best_per, max_cuts);
 }
 
 void free_device(fs_model *m)

@@ -16,8 +16,8 @@
 //                        threshold tables, one feature group per workgroup)
 //   traverse_rank_kernel the LDS-staged walk over rank tiles; trees in heap order without
 //                        child pointers (node i has children 2i, 2i+1, 1-based), leaves are the
-//                        last level; tile-sharing wavefronts, parked leaf values and the
-//                        ordered per-row sum as in the fp32 kernel
+//                        last level; the wavefronts that share a tile walk trees of their own and
+//                        pass the row's sum on in tree order
 #include "fs_internal.h"
 #include "fs_lds.h"
 
@@ -181,10 +181,17 @@ int launch_rank_code(const FamDesc *d_desc, int n_families, int total_blocks, hi
 // ------------------------------------------------------------------------------------------------
 // traversal over rank tiles
 // ------------------------------------------------------------------------------------------------
-// LDS map:  [0, trees*tree_bytes)               current chunk: trees back to back, each
-//                                               2^(depth+1) words: [unused][splits in heap
+// A workgroup has T tiles and 12 / T wavefronts per tile, its slots.  The trees in LDS are dealt to the slots, and
+// the T wavefronts of a slot (one per tile) walk the slot's trees, wait for each other, put the slot's next
+// trees in their place and wait again, on their own: while one slot copies others walk.  A row's running sum
+// goes from slot to slot in tree order, through LDS with a counter that says whose turn it is.
+// (One chunk of trees for all wavefronts and barriers around walks, sums and copy: a chunk of eight
+// trees of depth 10 took 5500 clocks, 3300 of them walks, the rest copying 64 KB into LDS and
+// adding up while nothing else ran.  2.1 M rows, 500 such trees: 4.63 ms, so 3.85.)
+//
+// LDS map:  [0, slots * per_slot * tree_bytes)  the slots' trees, each 2^(depth+1) words: [unused][splits in heap
 //                                               order, 1-based][leaf values]
-//           [tile0 - trees*T*256, tile0)        leaf values parked per [tree][tile][lane]
+//           [tile0 - T*256 - 128, ...)          running sums [tile][lane], then the counters
 //           [tile0 + t*Fc*128, ...)             tile t: features 2i, 2i+1 of row l in the word at
 //                                               i*256 + 4*l (Fc = F rounded up to even)
 // A split word is rank(thr) << 16 | offset of the feature in a tile (i*256 + 2*(f & 1)).
@@ -192,6 +199,8 @@ int launch_rank_code(const FamDesc *d_desc, int n_families, int total_blocks, hi
 // K trees at once for this lane's row.  base[k] = LDS address of tree k; the 1-based heap
 // index i lives at A = base + 4*i, and the step i' = 2i + c is taken on the address itself:
 // A' = 2A + (4c - base)   (one select between two per-tree constants and one shift-add).
+// (Reading both children of a split together with its feature halves the chain of LDS latencies, but two words cost
+// the LDS more bank conflicts than one: 4.67 ms instead of 4.51 for 2.1 M rows under 500 trees of depth 10.)
 template <int K>
 __device__ __forceinline__ void rank_walk(const uint32_t (&base)[K], int depth, uint32_t lane_base,
                                           uint32_t (&idx)[K], float (&v)[K])
@@ -225,57 +234,46 @@ __device__ __forceinline__ void rank_walk(const uint32_t (&base)[K], int depth, 
     }
 }
 
-template <int K, bool DUMP>
-__device__ __forceinline__ void rank_walk_k(int g, int depth, uint32_t tree_bytes,
-                                            uint32_t lane_base, uint32_t val_addr,
-                                            uint32_t val_stride, const uint16_t *ids_,
-                                            uint16_t *leaf_out_)
-{
-    uint32_t base[K], idx[K];
-    float v[K];
-#pragma unroll
-    for (int k = 0; k < K; ++k)
-        base[k] = (uint32_t)(g + k) * tree_bytes;
-    rank_walk<K>(base, depth, lane_base, idx, v);
-#pragma unroll
-    for (int k = 0; k < K; ++k)
-        lds_store_f(val_addr + (uint32_t)(g + k) * val_stride, v[k]);
-    if (DUMP) {
-        if (leaf_out_) {
-            auto ids = FS_GLOBAL(const uint16_t, ids_);
-            auto leaf_out = FS_GLOBAL(uint16_t, leaf_out_);
-            const uint32_t per_tree = tree_bytes >> 2;
-#pragma unroll
-            for (int k = 0; k < K; ++k)
-                leaf_out[g + k] = ids[(uint32_t)(g + k) * per_tree + idx[k]];
-        }
-    }
-}
-
-template <bool DUMP>
-__device__ __forceinline__ void rank_walk_n(int count, int g, int depth, uint32_t tree_bytes,
-                                            uint32_t lane_base, uint32_t val_addr,
-                                            uint32_t val_stride, const uint16_t *ids,
-                                            uint16_t *leaf_out)
-{
-    switch (count) {
-    case 8: rank_walk_k<8, DUMP>(g, depth, tree_bytes, lane_base, val_addr, val_stride, ids, leaf_out); break;
-    case 7: rank_walk_k<7, DUMP>(g, depth, tree_bytes, lane_base, val_addr, val_stride, ids, leaf_out); break;
-    case 6: rank_walk_k<6, DUMP>(g, depth, tree_bytes, lane_base, val_addr, val_stride, ids, leaf_out); break;
-    case 5: rank_walk_k<5, DUMP>(g, depth, tree_bytes, lane_base, val_addr, val_stride, ids, leaf_out); break;
-    case 4: rank_walk_k<4, DUMP>(g, depth, tree_bytes, lane_base, val_addr, val_stride, ids, leaf_out); break;
-    case 3: rank_walk_k<3, DUMP>(g, depth, tree_bytes, lane_base, val_addr, val_stride, ids, leaf_out); break;
-    case 2: rank_walk_k<2, DUMP>(g, depth, tree_bytes, lane_base, val_addr, val_stride, ids, leaf_out); break;
-    case 1: rank_walk_k<1, DUMP>(g, depth, tree_bytes, lane_base, val_addr, val_stride, ids, leaf_out); break;
-    default: break;
-    }
-}
-
 constexpr int kRankThreads = 64 * kRankWaves;
 constexpr int kRankTileBatch = 11;   // 16-byte loads in flight per thread while tiles are fetched
                                      // (six 164-feature rank tiles are 10.25 pieces per thread)
 
-template <bool DUMP>
+// Counters in LDS that only grow.  Everything in LDS that the wavefront did before count_up() is visible to who
+// saw the count: LDS operations of a wavefront are carried out in order, and what it read has arrived.
+static __device__ __forceinline__ void count_up(uint32_t counter, int lane)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    if (lane == 0)
+        asm volatile("ds_add_u32 %0, %1" ::"v"(counter), "v"(1u) : "memory");
+#else
+    (void)counter; (void)lane;
+#endif
+}
+
+// Until the counter has reached `count`.  (Ends: the wavefronts of a workgroup are all on the compute unit, and
+// each counts up as often as it is waited for, see rank_slot.)
+static __device__ __forceinline__ void wait_for(uint32_t counter, uint32_t count)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    for (;;) {
+        uint32_t now;
+        asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(now) : "v"(counter) : "memory");
+        if ((uint32_t)uniform((int)now) >= count)
+            break;
+        __builtin_amdgcn_s_sleep(1);
+    }
+#else
+    (void)counter; (void)count;
+#endif
+}
+
+template <int N> struct RankInt { static constexpr int value = N; };
+
+// REGS: 16-byte registers per thread for a slot's next trees.  (No more than they take: a load of a register too
+// many costs as much as one that is needed, eleven for six 25 % of the kernel's time; loads under a
+// condition had waits put in front of them, 40 %.)
+template <int REGS, bool DUMP>
 __global__ void __launch_bounds__(kRankThreads)
 traverse_rank_kernel(const FamDesc *__restrict__ descs, int n_families)
 {
@@ -291,34 +289,30 @@ traverse_rank_kernel(const FamDesc *__restrict__ descs, int n_families)
     const int tid = threadIdx.x;
     const int wave = uniform(tid >> 6), lane = tid & 63;
     const int T = d.rk_tiles;                   // tiles per workgroup (divides 12)
-    const int S = kRankWaves / T;               // wavefronts sharing a tile
-    const int my_tile = wave % T, my_slot = wave / T;
+    const int n_slots = d.rk_slots;             // 12 / T or fewer
+    const int my_slot = wave / T, my_tile = wave - my_slot * T;
     const int n_tiles = (d.n_rows + 63) >> 6;
     const int tile_first = (blockIdx.x - d.rk_block0) * T;
     const int tiles_here = min(T, n_tiles - tile_first);
-    const bool active = my_tile < tiles_here;
-    const int F = d.n_features;
-    const int Fc = rank_tile_cols(F);
+    const int Fc = rank_tile_cols(d.n_features);
     const uint32_t tile_bytes = (uint32_t)Fc * 128u;
     const uint32_t tile0 = (uint32_t)d.rk_tile0;
     const uint32_t lane_base = tile0 + (uint32_t)my_tile * tile_bytes + 4u * (uint32_t)lane;
     const uint32_t tree_bytes = (uint32_t)d.rk_tree_bytes;
-    const int per_chunk = d.rk_trees_per_chunk;
-    const int n_trees = d.n_trees;
-    const int depth = d.rk_depth;
-    const int n_chunks = (n_trees + per_chunk - 1) / per_chunk;
-    // tree_bytes = 2^(depth+3) is a multiple of 16, so every chunk starts 16-byte aligned
-
-    // ---- first chunk: global -> registers ----
-    u32x4 pf[kRankPrefetchRegs];
+    const int per_slot = d.rk_trees_per_slot;
+    const int n_trees = d.n_trees, depth = d.rk_depth;
+    const int n_turns = (n_trees + per_slot - 1) / per_slot;     // turn q: trees [q, q + 1) * per_slot, slot q % n_slots
+    const uint32_t sums = tile0 - (uint32_t)T * 256u - 128u, counters = tile0 - 128u;
+    const uint32_t my_sum = sums + 256u * (uint32_t)my_tile + 4u * (uint32_t)lane;
+    const uint32_t turn_at = counters + 4u * (uint32_t)my_tile;            // turns whose values the sum holds
+    const uint32_t slot_at = counters + 64u + 4u * (uint32_t)my_slot;      // how often wavefronts of the slot came by
+    // tree_bytes = 2^(depth+3) is a multiple of 16, so every tree starts 16-byte aligned
     auto image = FS_GLOBAL(const u32x4, d.rk_nodes);
     const int tree16 = (int)(tree_bytes >> 4);
-    // The first chunk and the tiles go straight from memory to LDS, 1 KB per wavefront-wide
+    // The first trees and the tiles go straight from memory to LDS, 1 KB per wavefront-wide
     // load; what is left of each (fewer than 64 pieces) goes through registers.
-    const int first16 = min(per_chunk, n_trees) * tree16;
+    const int first16 = min(n_slots * per_slot, n_trees) * tree16;
     const int first_rest = lds_fill_direct(image, 0u, first16, wave, kRankWaves, lane) + tid;
-    if (first_rest < first16)
-        pf[0] = image[first_rest];
     // ---- rank tiles: consecutive tiles are one contiguous run ----
     {
         auto src = FS_GLOBAL(const u32x4, d.ranks + (int64_t)tile_first * Fc * 64);
@@ -339,104 +333,135 @@ traverse_rank_kernel(const FamDesc *__restrict__ descs, int n_families)
         }
     }
     if (first_rest < first16)
-        lds_store_u4(16u * (uint32_t)first_rest, pf[0]);
+        lds_store_u4(16u * (uint32_t)first_rest, image[first_rest]);
+    if (my_slot == 0)
+        lds_store_f(my_sum, d.bias);
+    if (tid < 32)
+        lds_store_f(counters + 4u * (uint32_t)tid, 0.0f);  // (the bits of zero)
     lds_direct_wait();
     __syncthreads();
+    if (my_slot >= n_slots)
+        return;
 
     const int r = (tile_first + my_tile) * 64 + lane;
-    float acc = d.bias;
+    const bool active = my_tile < tiles_here;
+    const uint32_t region = (uint32_t)my_slot * (uint32_t)per_slot * tree_bytes;
+    const int in_slot = my_tile * 64 + lane, slot_threads = T * 64;
     uint16_t *leaf_row = nullptr;
     if (DUMP) {
         if (active && d.leaf_idx && r < d.n_rows)
             leaf_row = d.leaf_idx + (int64_t)r * n_trees;
     }
-    const uint32_t val_stride = (uint32_t)T * 256u;
-
-    // Wavefronts 0..T-1 do the ordered sums.  When the others can carry a whole chunk in their
-    // prefetch registers they copy it alone, so a sum and the copy run side by side.
-    const int n_copiers = kRankThreads - 64 * T;
-    for (int c = 0; c < n_chunks; ++c) {
-        const int first = c * per_chunk;
-        const int n = uniform(min(per_chunk, n_trees - first));
-        int n_next = 0, cp_id = tid, cp_n = kRankThreads;
-        if (c + 1 < n_chunks) {                            // next chunk: global -> registers
-            n_next = min(per_chunk, n_trees - first - per_chunk);
-            const int n16 = n_next * tree16;
-            auto src = image + (int64_t)(first + per_chunk) * tree16;
-            if (n16 <= kRankPrefetchRegs * n_copiers) {
-                cp_n = n_copiers;
-                cp_id = tid - 64 * T;                      // negative in the summing wavefronts
-            }
-            if (cp_id >= 0) {
+    uint32_t passed = 0;                                   // what the slot's counter has to reach
+    for (int q = my_slot; q < n_turns; q += n_slots) {
+        const int n = min(per_slot, n_trees - q * per_slot);
+        // the slot's next trees: global -> registers
+        const int q_next = q + n_slots;
+        const int n16 = q_next < n_turns ? min(per_slot, n_trees - q_next * per_slot) * tree16 : 0;
+        auto src = image + (int64_t)q_next * per_slot * tree16;
+        u32x4 pf[REGS];
+        if (n16 > 0) {
 #pragma unroll
-                for (int j = 0; j < kRankPrefetchRegs; ++j)
-                    pf[j] = src[min(cp_id + j * cp_n, n16 - 1)];
-            }
+            for (int j = 0; j < REGS; ++j)
+                pf[j] = src[min(in_slot + j * slot_threads, n16 - 1)];
         }
-        const uint32_t val0 = tile0 - (uint32_t)per_chunk * val_stride;   // fixed: above any image
-        if (active) {
-            const uint32_t val_addr = val0 + (uint32_t)my_tile * 256u + 4u * (uint32_t)lane;
-            const uint16_t *ids = d.rk_ids + (int64_t)first * (tree_bytes >> 2);
-            uint16_t *leaf_out = leaf_row ? leaf_row + first : nullptr;
-            const int n_groups = S * ((n + 8 * S - 1) / (8 * S));
-            const int base = n / n_groups, rem = n - base * n_groups;
-            for (int j = my_slot; j < n_groups; j += S) {
-                const int g = j * base + min(j, rem);
-                const int count = base + (j < rem ? 1 : 0);
-                rank_walk_n<DUMP>(count, g, depth, tree_bytes, lane_base, val_addr, val_stride, ids,
-                                  leaf_out);
-            }
-        }
-        __syncthreads();       // every walk of this chunk is done and its values are parked
-        if (active && my_slot == 0) {
-            const uint32_t va = val0 + (uint32_t)my_tile * 256u + 4u * (uint32_t)lane;
-            ordered_add_n(acc, va, val_stride, n);
-        }
-        if (c + 1 < n_chunks) {
-            const int n16 = n_next * tree16;
-            if (cp_id >= 0) {
+        auto turn = [&](auto trees) {
+            constexpr int K = decltype(trees)::value;
+            uint32_t base[K], idx[K];
+            float v[K];
 #pragma unroll
-                for (int j = 0; j < kRankPrefetchRegs; ++j) {
-                    const int i = cp_id + j * cp_n;
-                    if (i < n16)
-                        lds_store_u4(16u * (uint32_t)i, pf[j]);
+            for (int k = 0; k < K; ++k)
+                base[k] = region + (uint32_t)k * tree_bytes;
+            rank_walk<K>(base, depth, lane_base, idx, v);
+            if (DUMP) {
+                if (leaf_row) {
+                    auto ids = FS_GLOBAL(const uint16_t, d.rk_ids + (int64_t)q * per_slot * (tree_bytes >> 2));
+                    auto out = FS_GLOBAL(uint16_t, leaf_row + q * per_slot);
+#pragma unroll
+                    for (int k = 0; k < K; ++k)
+                        out[k] = ids[(uint32_t)k * (tree_bytes >> 2) + idx[k]];
                 }
             }
-            __syncthreads();
+            if (n16 > 0)
+                count_up(slot_at, lane);                   // the trees have been read
+            wait_for(turn_at, (uint32_t)q);
+            float acc = lds_f(my_sum);
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                acc = acc + v[k];
+            if (q + 1 < n_turns) {
+                lds_store_f(my_sum, acc);
+                count_up(turn_at, lane);
+            } else if (r < d.n_rows) {
+                FS_GLOBAL(float, d.row_score)[r] = acc;
+            }
+        };
+        if (active) {
+            switch (n) {
+            case 8: turn(RankInt<8>()); break;
+            case 7: turn(RankInt<7>()); break;
+            case 6: turn(RankInt<6>()); break;
+            case 5: turn(RankInt<5>()); break;
+            case 4: turn(RankInt<4>()); break;
+            case 3: turn(RankInt<3>()); break;
+            case 2: turn(RankInt<2>()); break;
+            default: turn(RankInt<1>());
+            }
+        } else if (n16 > 0) {
+            count_up(slot_at, lane);
+        }
+        if (n16 > 0) {
+            passed += (uint32_t)T;
+            wait_for(slot_at, passed);
+#pragma unroll
+            for (int j = 0; j < REGS; ++j) {
+                const int i = in_slot + j * slot_threads;
+                if (i < n16)
+                    lds_store_u4(region + 16u * (uint32_t)i, pf[j]);
+            }
+            for (int i = in_slot + REGS * slot_threads; i < n16; i += slot_threads)   // trees larger than that
+                lds_store_u4(region + 16u * (uint32_t)i, src[i]);
+            count_up(slot_at, lane);
+            passed += (uint32_t)T;
+            wait_for(slot_at, passed);
         }
     }
-    if (active && my_slot == 0 && r < d.n_rows)
-        FS_GLOBAL(float, d.row_score)[r] = acc;
+    // (no trees: the row's score is the bias)
+    if (n_turns == 0 && my_slot == 0 && active && r < d.n_rows)
+        FS_GLOBAL(float, d.row_score)[r] = d.bias;
 }
 
-int launch_traverse_rank(const FamDesc *d_desc, int n_families, int total_blocks, bool dump,
-                         hipStream_t stream)
+template <int REGS>
+static int launch_rank_regs(const FamDesc *d_desc, int n_families, int total_blocks, bool dump, hipStream_t stream)
 {
     static bool configured[16][2] = {};
     int dev = 0;
     FS_HIP(hipGetDevice(&dev));
-    const void *fn = dump ? (const void *)traverse_rank_kernel<true>
-                          : (const void *)traverse_rank_kernel<false>;
+    auto kernel = dump ? traverse_rank_kernel<REGS, true> : traverse_rank_kernel<REGS, false>;
     if (dev < 0 || dev >= 16 || !configured[dev][dump ? 1 : 0]) {
         hipFuncAttributes attr;
-        FS_HIP(hipFuncGetAttributes(&attr, fn));
+        FS_HIP(hipFuncGetAttributes(&attr, (const void *)kernel));
         if (attr.sharedSizeBytes != 0)
             return fail(FS_EDEVICE, "traverse_rank_kernel was built with %zu bytes of static LDS",
                         (size_t)attr.sharedSizeBytes);
-        FS_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kRankLdsBytes));
+        FS_HIP(hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kRankLdsBytes));
         if (dev >= 0 && dev < 16)
             configured[dev][dump ? 1 : 0] = true;
     }
-    if (dump)
-        hipLaunchKernelGGL(traverse_rank_kernel<true>, dim3(total_blocks), dim3(kRankThreads),
-                           kRankLdsBytes, stream, d_desc, n_families);
-    else
-        hipLaunchKernelGGL(traverse_rank_kernel<false>, dim3(total_blocks), dim3(kRankThreads),
-                           kRankLdsBytes, stream, d_desc, n_families);
+    hipLaunchKernelGGL(kernel, dim3(total_blocks), dim3(kRankThreads), kRankLdsBytes, stream, d_desc, n_families);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return fail_hip(e, "traverse_rank_kernel launch");
     return FS_OK;
+}
+
+int launch_traverse_rank(const FamDesc *d_desc, int n_families, int total_blocks, int regs, bool dump, hipStream_t stream)
+{
+    if (regs <= 3)
+        return launch_rank_regs<3>(d_desc, n_families, total_blocks, dump, stream);
+    if (regs <= 6)
+        return launch_rank_regs<6>(d_desc, n_families, total_blocks, dump, stream);
+    return launch_rank_regs<11>(d_desc, n_families, total_blocks, dump, stream);
 }
 
 }  // namespace fs
