@@ -403,7 +403,7 @@ static Walks choose_walks(int n_families, const fs_family *fams, int n_compute_u
         return w;
     }
     // the families with both walks, as one launch of either kind
-    double n = 0.0, wgs = 0.0, round_us = 0.0, groups = 0.0, group_us = 0.0, fetches = 0.0,
+    double n = 0.0, wgs = 0.0, round_us = 0.0, once_us = 0.0, groups = 0.0, group_us = 0.0, fetches = 0.0,
            group_features = 0.0, rowmajor = 0.0, retile_features = 0.0;
     for (int f = 0; f < n_families; ++f) {
         const fs_family &a = fams[f];
@@ -415,6 +415,7 @@ static Walks choose_walks(int n_families, const fs_family *fams, int n_compute_u
         n += t;
         wgs += ceil(t / kTreeletFormTiles[w.form]);
         round_us += t * m->tl_us[rows][w.form];
+        once_us += t * m->tl_once_us;
         groups += ceil(t / m->lds_tiles);
         group_us += t * m->lds_group_us;
         fetches += t * lds_fetches(m, rows && !needs_retile(a));
@@ -428,7 +429,7 @@ static Walks choose_walks(int n_families, const fs_family *fams, int n_compute_u
         const double lds = lds_call_us(w.form, 2.0 * rowmajor > n, group_us / n, fetches / n, group_features / n,
                                        groups, n_compute_units) +
                            (retile_features > 0.0 ? retile_us(retile_features) : 0.0);
-        const double tl = treelet_call_us(w.form, round_us / n, wgs, n_compute_units);
+        const double tl = treelet_call_us(w.form, round_us / n, once_us / n, wgs, n_compute_units);
         w.lds_for_both = lds < tl;
         if (tune(FS_TUNE_VERBOSE) > 0)
             fprintf(stderr, "fs_score_families: %.0f tiles, treelets about %.0f us, LDS walk %.0f\n", n, tl, lds);

@@ -60,12 +60,13 @@ inline double launch_rounds_of_two(double workgroups, int n_compute_units)
     return whole > 0.0 && r > whole && r <= whole + 0.5 ? whole + 0.6 : ceil(r);
 }
 
-// us of a call whose workgroups take `round_us` each (fs_model::tl_us, averaged over the families).
-inline double treelet_call_us(int form, double round_us, double workgroups, int n_compute_units)
+// us of a call whose workgroups take `round_us` each (fs_model::tl_us, averaged over the families, as `once_us`:
+// fs_model::tl_once_us).
+inline double treelet_call_us(int form, double round_us, double once_us, double workgroups, int n_compute_units)
 {
     if (form != kTreeletPair)
         return round_us;                             // such launches fit the chip
-    return 11.0 + round_us * launch_rounds_of_two(workgroups, n_compute_units);
+    return 11.0 + once_us + round_us * launch_rounds_of_two(workgroups, n_compute_units);
 }
 
 // Fetches of a tile group in the LDS walk: one per tile; row-major a part of a tile's rows at a time, as many as

@@ -134,6 +134,7 @@ struct fs_model {
     // a round of workgroups, estimated, us (spread forms: the whole call); [row-major input][form].  A model
     // with tl_ok and lds_ok has both walks, and the call chooses (fs_forms.h)
     float tl_us[2][fs::kTreeletForms];
+    float tl_once_us;          // and once per call of the pair form
     void *d_tl_data;           // everything of this format, one allocation
     fs::TreeletModel *d_tl;    // inside it
 };

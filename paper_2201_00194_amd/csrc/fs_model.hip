@@ -5,7 +5,10 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <future>
+#include <memory>
 #include <new>
+#include <system_error>
 #include <utility>
 #include <vector>
 
@@ -608,9 +611,11 @@ hipError_t upload_lds(fs_model *m, std::vector<uint8_t> &image, const std::vecto
 hipError_t upload_treelets(const TreeletPlan &tl, void **d_data, TreeletModel **d_model)
 {
     size_t total = 0;
+    std::vector<std::pair<size_t, size_t>> gaps;     // between the parts
     auto room = [&](size_t bytes) {
         const size_t at = total;
         total = (total + bytes + 255) & ~(size_t)255;
+        gaps.push_back({at + bytes, total});
         return at;
     };
     const size_t model_at = room(sizeof(TreeletModel)), seg_at = room(tl.segments.size() * sizeof(TreeletSegment)),
@@ -625,7 +630,9 @@ hipError_t upload_treelets(const TreeletPlan &tl, void **d_data, TreeletModel **
     if (e != hipSuccess)
         return e;
     uint8_t *base = (uint8_t *)*d_data;
-    std::vector<uint8_t> host(total, 0);
+    std::unique_ptr<uint8_t[]> host(new uint8_t[total]);
+    for (const auto &g : gaps)
+        memset(&host[g.first], 0, g.second - g.first);
     TreeletModel tm;
     memset(&tm, 0, sizeof(tm));
     tm.image = base + image_at;
@@ -656,7 +663,7 @@ hipError_t upload_treelets(const TreeletPlan &tl, void **d_data, TreeletModel **
         memcpy(&host[tables_at[i]], sp.tables.data(), sp.tables.size());
     }
     *d_model = (TreeletModel *)(base + model_at);
-    return hipMemcpy(base, host.data(), total, hipMemcpyHostToDevice);
+    return hipMemcpy(base, host.get(), total, hipMemcpyHostToDevice);
 }
 
 enum Wins { kNever, kSometimes, kAlways };
@@ -670,7 +677,7 @@ Wins treelet_wins(const fs_model *m)
     for (int rowmajor = 0; rowmajor < (lds_reads_rowmajor(m) ? 2 : 1); ++rowmajor)
         for (double tiles : lengths) {
             const int form = treelet_form((int64_t)tiles, kUnits);
-            const double tl = treelet_call_us(form, m->tl_us[rowmajor][form], ceil(tiles / 4), kUnits);
+            const double tl = treelet_call_us(form, m->tl_us[rowmajor][form], m->tl_once_us, ceil(tiles / 4), kUnits);
             const double lds = lds_call_us(form, rowmajor != 0, m->lds_group_us, lds_fetches(m, rowmajor != 0),
                                            (double)m->n_features * m->lds_tiles, ceil(tiles / m->lds_tiles), kUnits);
             least = std::min(least, tl / lds);
@@ -769,6 +776,39 @@ extern "C" int fs_model_create(fs_model **out, int32_t n_features, int32_t n_tre
         const bool ranks_pay = n_features <= 511 && tune(FS_TUNE_RANK) != 0 && perfect_depth <= 12 &&
                                perfect_depth >= (tune(FS_TUNE_RANK) == 1 ? 1 : 8);
 
+        // ---- LDS-staged format, of a large model on a thread of its own beside the treelets ----
+        // (Models that may take either walk need both: 400 irregular trees of depth 12, 112 000 nodes, take 2256 us one
+        // after the other and 1957 side by side; below 50 000 nodes there is less to gain than a thread costs.)
+        constexpr int64_t kLdsAheadNodes = 50000;
+        struct LdsBuild {
+            LdsPlan plan;
+            bool ok = false, written = false;
+            std::vector<uint8_t> image;
+            std::vector<ChunkHdr> chunks;
+            std::vector<uint16_t> slot_ids;
+        };
+        const auto plan_format = [&](LdsBuild *b) {
+            b->ok = plan_lds(n_features, n_trees, shapes, tree_off, split_feature, left, right, &b->plan);
+        };
+        const auto write_format = [&](LdsBuild *b) {
+            if (b->ok && !b->written)
+                write_lds(b->plan, n_features, tree_off, split_feature, threshold, left, right, value, &b->image,
+                          &b->chunks, &b->slot_ids);
+            b->written = true;
+        };
+        LdsBuild lds;
+        std::future<void> lds_ahead;                     // (waits in its destructor)
+        if (n_features <= 255 && n_trees >= kTreeletMinTrees && n_nodes >= kLdsAheadNodes && !ranks_pay &&
+            tune(FS_TUNE_TREELET) < 0) {
+            try {
+                lds_ahead = std::async(std::launch::async, [&] {
+                    plan_format(&lds);
+                    write_format(&lds);
+                });
+            } catch (const std::system_error &) {        // no thread to be had
+            }
+        }
+
         // ---- byte-rank treelets ----
         TreeletPlan tl;
         std::vector<uint32_t> rk_nodes;
@@ -817,28 +857,30 @@ extern "C" int fs_model_create(fs_model **out, int32_t n_features, int32_t n_tre
             m->tl_pair = tl.pair_ok;
             m->tl_cols = tl.most_cols;
             memcpy(m->tl_us, tl.us, sizeof(m->tl_us));
+            m->tl_once_us = tl.once_us;
             if (m->tl_ok && tune(FS_TUNE_VERBOSE) > 0)
                 fprintf(stderr, "fs_model_create: treelets, %zu segments of up to %d columns, %zu chunks of at most %d "
                         "trees and %d bytes%s, about %.0f clocks per tile\n", tl.segments.size(), m->tl_cols,
                         tl.chunks.size(), tl.max_trees, tl.buf_bytes, tl.pair_ok ? "" : " (whole LDS)", tl.cost);
         }
 
-        // ---- LDS-staged format ----
-        std::vector<uint8_t> image;
-        std::vector<ChunkHdr> chunks;
-        std::vector<uint16_t> slot_ids;
+        // ---- the LDS-staged format, if it is needed ----
         // beside treelets unless they win (or lose) every call; not where treelets were asked for, nor beside
         // those of perfect trees that the rank walk would take, which win
+        const bool planned = lds_ahead.valid();
+        if (planned)
+            lds_ahead.get();
         if (n_trees > 0 && n_features <= 255 && !m->rank_ok &&
             !(m->tl_ok && (tune(FS_TUNE_TREELET) == 1 || ranks_pay))) {
-            LdsPlan plan;
-            m->lds_ok = plan_lds(n_features, n_trees, shapes, tree_off, split_feature, left, right, &plan);
+            if (!planned)
+                plan_format(&lds);
+            m->lds_ok = lds.ok;
             if (m->lds_ok) {
-                m->compact = plan.compact;
-                m->lds_tiles = plan.tiles;
-                m->lds_mode = plan.mode;
-                m->lds_group_us = plan.group_us;
-                m->lds_tile0 = kLdsModeBytes[plan.mode] - plan.tiles * (n_features + 1) * 256;
+                m->compact = lds.plan.compact;
+                m->lds_tiles = lds.plan.tiles;
+                m->lds_mode = lds.plan.mode;
+                m->lds_group_us = lds.plan.group_us;
+                m->lds_tile0 = kLdsModeBytes[lds.plan.mode] - lds.plan.tiles * (n_features + 1) * 256;
                 if (m->tl_ok) {
                     const Wins wins = treelet_wins(m);
                     m->lds_ok = wins != kAlways;
@@ -846,16 +888,15 @@ extern "C" int fs_model_create(fs_model **out, int32_t n_features, int32_t n_tre
                 }
             }
             if (m->lds_ok) {
-                write_lds(plan, n_features, tree_off, split_feature, threshold, left, right, value, &image, &chunks,
-                          &slot_ids);
+                write_format(&lds);
                 if (tune(FS_TUNE_VERBOSE) > 0) {
-                    fprintf(stderr, "fs_model_create: %zu chunks, trees per chunk:", chunks.size());
-                    for (const ChunkHdr &c : chunks)
+                    fprintf(stderr, "fs_model_create: %zu chunks, trees per chunk:", lds.chunks.size());
+                    for (const ChunkHdr &c : lds.chunks)
                         fprintf(stderr, " %u", c.n_trees);
                     fprintf(stderr, "\n");
                 }
-                m->n_chunks = (int32_t)chunks.size();
-                m->image_bytes = image.size();
+                m->n_chunks = (int32_t)lds.chunks.size();
+                m->image_bytes = lds.image.size();
             }
         }
 
@@ -888,7 +929,7 @@ extern "C" int fs_model_create(fs_model **out, int32_t n_features, int32_t n_tre
         }
         if (e == hipSuccess) e = upload(&m->d_nodes, nodes);
         if (e == hipSuccess && m->lds_ok)
-            e = upload_lds(m, image, chunks, slot_ids);
+            e = upload_lds(m, lds.image, lds.chunks, lds.slot_ids);
         if (e == hipSuccess && m->rank_ok) {
             e = upload(&m->d_rk_nodes, rk_nodes);
             if (e == hipSuccess) e = upload(&m->d_rk_ids, rk_ids);

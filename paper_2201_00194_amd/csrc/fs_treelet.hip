@@ -514,8 +514,10 @@ treelet_pair_kernel(const FamDesc *__restrict__ descs, int n_families, int launc
             code_columns<kPairTiles, 4>(d, g, tile_first, n_tiles, wave, kPairWaves, lane, buf + 2u * half4 * (uint32_t)wave, half4, 2);
         else if (kHalves * half2 <= room)
             code_columns<kPairTiles, 2>(d, g, tile_first, n_tiles, wave, kPairWaves, lane, buf + 2u * half2 * (uint32_t)wave, half2, 2);
-        else                                         // the packer sees to it that this fits
-            code_columns<kPairTiles, 1>(d, g, tile_first, n_tiles, wave, kPairWaves, lane, buf + 2u * half1 * (uint32_t)wave, half1, 2);
+        else {                                       // the packer sees to it that one buffer fits
+            const uint32_t halves = kHalves * half1 <= room ? 2u : 1u;
+            code_columns<kPairTiles, 1>(d, g, tile_first, n_tiles, wave, kPairWaves, lane, buf + halves * half1 * (uint32_t)wave, half1, (int)halves);
+        }
         if (si == 0)
             lds_store_f(sum_at + kBack, acc);        // (both wavefronts of a tile, the same value)
         __syncthreads();                             // columns coded, tables free

@@ -83,6 +83,7 @@ struct TreeletPlan {
     bool pair_ok = false;         // a chunk buffer fits beside the columns in half a compute unit's LDS
     double cost = 0.0;            // clocks of a compute unit per 64-row tile, estimated
     float us[2][kTreeletForms] = {};   // a round of a launch, estimated: fs_model::tl_us
+    float once_us = 0.0f;              // fs_model::tl_once_us
 };
 
 // What a plan may not exceed, found out as early as possible.

@@ -171,30 +171,19 @@ uint64_t *sort_keys(uint64_t *keys, uint64_t *spare, int n)
     return spare;
 }
 
-// Sorts the thresholds of nodes [node0, node1) by feature, lists the columns and sets word[node] = column << 8 |
+// Sorts the thresholds of n_splits nodes, so many of each feature, by feature, lists the columns and sets word[node] = column << 8 |
 // rank of every split (rank 0 for a NaN threshold: it sends nothing left).  False if the trees need more
 // columns than a byte names.
-bool segment_cuts(int n_features, int32_t node0, int32_t node1, const int32_t *sf, const float *thr,
-                  std::vector<uint64_t> &keys, uint16_t *word, SegmentCuts *out)
+bool segment_cuts(int n_features, const int32_t *nodes, size_t n_splits, const std::vector<int32_t> &of_feature,
+                  const int32_t *sf, const float *thr, std::vector<uint64_t> &keys, uint16_t *word, SegmentCuts *out)
 {
-    // The splits, and how many each feature has (at [feature + 2]; leaves count at [1]: no branch that a leaf
-    // would upset), then where its keys start.
-    std::vector<int32_t> at((size_t)n_features + 2, 0), fill((size_t)n_features, 0), nan_nodes;
-    std::vector<int32_t> nodes((size_t)(node1 - node0));
-    size_t n_splits = 0;
-    for (int32_t g = node0; g < node1; ++g) {
-        nodes[n_splits] = g;
-        n_splits += sf[g] >= 0;
-        ++at[(size_t)(std::max(sf[g], -1) + 2)];
-    }
-    at[1] = 0;
+    std::vector<int32_t> at((size_t)n_features + 1, 0), fill((size_t)n_features, 0), nan_nodes;
     int32_t most = 0;
-    for (int f = 0; f < n_features; ++f) {
-        most = std::max(most, at[(size_t)f + 2]);
-        at[(size_t)f + 2] += at[(size_t)f + 1];
-        fill[(size_t)f] = at[(size_t)f + 1];
+    for (int f = 0; f < n_features; ++f) {           // feature f's keys are [at[f], at[f + 1])
+        most = std::max(most, of_feature[(size_t)f]);
+        at[(size_t)f + 1] = at[(size_t)f] + of_feature[(size_t)f];
+        fill[(size_t)f] = at[(size_t)f];
     }
-    at.erase(at.begin());                            // feature f's keys are [at[f], at[f + 1])
     keys.resize(n_splits + (size_t)most);
     for (size_t i = 0; i < n_splits; ++i) {
         const int32_t g = nodes[i];
@@ -272,6 +261,11 @@ void estimate_rounds(int n_features, TreeletPlan *p)
         steps += c.steps;
         tree_steps += (double)c.n_trees * c.steps;
     }
+    // Tables of single columns without a second buffer, where the columns leave no room for one: 0.15 us a column
+    // more in launches of a round or two (164 features, 200 columns, 3000 tiles: estimated 269, measured
+    // 300 us; row-major 323 and 359), nothing in long ones, whose workgroups are out of step (40 000
+    // tiles 2845 and 2730, 3579 and 3387).
+    double once = 0.0;
     const double n_chunks = (double)p->chunks.size();
     const long columns = (long)p->most_cols * 256;
     for (int rowmajor = 0; rowmajor < 2; ++rowmajor) {
@@ -279,6 +273,8 @@ void estimate_rounds(int n_features, TreeletPlan *p)
         for (const TreeletSegmentPlan &sp : p->segments) {
             const long room = (long)kTreeletLds - kTreeletSumBytes - columns;
             const int batch = 16 * kb(4L * sp.table_stride) <= room ? 0 : 16 * kb(2L * sp.table_stride) <= room ? 1 : 2;
+            if (rowmajor == 0 && 16 * kb(sp.table_stride) > room)
+                once += 0.15 * (double)sp.cols.size();
             pair += (pair_col[rowmajor][batch] + pair_feature[rowmajor][batch] * n_features) * (double)sp.cols.size();
         }
         p->us[rowmajor][kTreeletPair] = (float)pair;
@@ -294,6 +290,7 @@ void estimate_rounds(int n_features, TreeletPlan *p)
             p->us[rowmajor][form] = (float)us;
         }
     }
+    p->once_us = (float)once;
 }
 
 }  // namespace
@@ -339,10 +336,16 @@ bool build_treelets(int n_features, int n_trees, const TreeShapes &shape, const 
     {
         // (an ensemble whose splits are many times what the columns hold starts with several segments: no
         // sort of a million thresholds only to see that)
-        std::vector<int32_t> n_splits((size_t)n_features, 0);
-        for (int32_t g = 0; g < tree_off[n_trees]; ++g)
-            if (sf[g] >= 0)
-                ++n_splits[(size_t)sf[g]];
+        // The splits, and how many each feature has (at [feature + 1]; leaves count at [0]: no branch that a leaf
+        // would upset).
+        std::vector<int32_t> nodes((size_t)tree_off[n_trees]), n_splits((size_t)n_features + 1, 0);
+        size_t all_splits = 0;
+        for (int32_t g = 0; g < tree_off[n_trees]; ++g) {
+            nodes[all_splits] = g;
+            all_splits += sf[g] >= 0;
+            ++n_splits[(size_t)(std::max(sf[g], -1) + 1)];
+        }
+        n_splits.erase(n_splits.begin());
         // what the walk costs at least: every used feature one column, every tree its own steps
         double least = 0.0;
         for (int32_t n : n_splits)
@@ -370,14 +373,24 @@ bool build_treelets(int n_features, int n_trees, const TreeShapes &shape, const 
             out->segments.clear();
             seg_cuts.clear();
             bool ok = true;
-            for (int t = 0; t < n_trees && ok; t += per) {
+            size_t from = 0, to;                         // splits of the segment
+            std::vector<int32_t> mine;
+            for (int t = 0; t < n_trees && ok; t += per, from = to) {
                 out->segments.emplace_back();
                 seg_cuts.emplace_back();
                 TreeletSegmentPlan &sp = out->segments.back();
                 sp.first_tree = t;
                 sp.n_trees = std::min(per, n_trees - t);
-                ok = segment_cuts(n_features, tree_off[t], tree_off[t + sp.n_trees], sf, thr, keys, word.data(),
-                                  &seg_cuts.back());
+                to = all_splits;
+                if (per < n_trees) {
+                    to = (size_t)(std::lower_bound(nodes.begin() + (long)from, nodes.begin() + (long)all_splits,
+                                                   tree_off[t + sp.n_trees]) - nodes.begin());
+                    mine.assign((size_t)n_features, 0);
+                    for (size_t i = from; i < to; ++i)
+                        ++mine[(size_t)sf[nodes[i]]];
+                }
+                ok = segment_cuts(n_features, nodes.data() + from, to - from, per < n_trees ? mine : n_splits, sf, thr,
+                                  keys, word.data(), &seg_cuts.back());
             }
             if (ok)
                 break;
@@ -452,9 +465,9 @@ bool build_treelets(int n_features, int n_trees, const TreeShapes &shape, const 
     // wavefronts would not fit beside the columns.
     const long beside = (long)out->most_cols * 256;
     auto kb = [](long bytes) { return (bytes + 1023) / 1024 * 1024; };
-    // (the coder's layouts in fs_treelet.hip: a double-buffered table for each of 8 wavefronts; four
-    // tables for each of 12)
-    auto pair_fits = [&](int stride) { return 16 * kb(stride) <= (long)kTreeletLds - kTreeletSumBytes - beside; };
+    // (the coder's layouts in fs_treelet.hip: a double-buffered table for each of 8 wavefronts, or a single one
+    // beside more columns; four tables for each of 12)
+    auto pair_fits = [&](int stride, int halves) { return 8 * halves * kb(stride) <= (long)kTreeletLds - kTreeletSumBytes - beside; };
     auto spread_fits = [&](int stride) { return 12 * kb(4 * stride) <= (long)kTreeletLdsWhole - beside; };
     bool pair_coder = true;
     for (size_t i = 0; i < out->segments.size();) {
@@ -465,13 +478,14 @@ bool build_treelets(int n_features, int n_trees, const TreeShapes &shape, const 
         while (want < 5 * most_cuts && want < 1024)
             want *= 2;
         bool fits = false;
-        for (int B = want; B >= 64 && !fits; B /= 2) {
-            const int least = B + 4 * ((most_cuts + 1 + 3) / 4 * 4);   // of what build_columns makes the stride
-            if (!spread_fits(least) || (pair_coder && !pair_fits(least)))
-                continue;
-            build_columns(seg_cuts[i].pieces, seg_cuts[i].cuts, seg_cuts[i].cut_at, B, sp);
-            fits = spread_fits(sp->table_stride) && (pair_fits(sp->table_stride) || !pair_coder);
-        }
+        for (int halves = 2; halves >= 1 && !fits; --halves)
+            for (int B = want; B >= 64 && !fits; B /= 2) {
+                const int least = B + 4 * ((most_cuts + 1 + 3) / 4 * 4);   // of what build_columns makes the stride
+                if (!spread_fits(least) || (pair_coder && !pair_fits(least, halves)))
+                    continue;
+                build_columns(seg_cuts[i].pieces, seg_cuts[i].cuts, seg_cuts[i].cut_at, B, sp);
+                fits = spread_fits(sp->table_stride) && (pair_fits(sp->table_stride, halves) || !pair_coder);
+            }
         if (fits) {
             ++i;
         } else if (limits.pair_only) {

@@ -138,3 +138,22 @@ def test_one_call_with_every_walk(api, oracle, layout):
     devs = run_families(api, fams, layout)
     for f, d in zip(fams, devs):
         check_family(oracle, f, d)
+
+
+@pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("n_features,n_trees,depth,q", [(250, 60, 8, 0.2), (255, 48, 7, 0.1), (236, 45, 9, 0.25), (110, 300, 9, 0.2)])
+def test_columns_that_leave_room_for_one_table_a_wavefront(api, oracle, tune, layout, n_features, n_trees, depth, q):
+    """Many columns in half a compute unit's LDS: the coder's tables have no second buffer."""
+    tune(api.FS_TUNE_TREELET, 1)
+    tune(api.FS_TUNE_TREELET_FORM, 0)
+    fam = family(n_features, 560, (2, 5), n_trees, depth, q, n_features=n_features, special=True)
+    check_family(oracle, fam, run_families(api, [fam], layout)[0])
+
+
+def test_a_large_model_with_both_walks(api, oracle):
+    """112 000 nodes: the two formats are built side by side; calls on both sides of the choice."""
+    fam = family(5, 200, (1, 2), 400, 12, 0.3)
+    big = family(6, 3000, (16, 16), 150, 12, 0.3, n_features=200)
+    for f, dev in zip([fam, big], run_families(api, [fam, big], 0, want_leaves=False)):
+        check_family(oracle, f, dev, check_leaves=False)
+    check_family(oracle, fam, run_families(api, [fam], 1)[0])
