@@ -835,8 +835,10 @@ extern "C" int fs_model_create(fs_model **out, int32_t n_features, int32_t n_tre
                 // take: below 400 columns in all 0.20 to 0.98 on 100 to 300 features (32 models, 650 calls); on 24
                 // to 64 features 0.34 to 1.30 (17 models; 11 of 340 calls lose more than 2 %, ten of them of
                 // 24 features); from 400 columns 0.58 to 1.37 (6 models; 33 of 130 calls lose more than 2 %).
-                if (ranks_pay)
+                if (ranks_pay) {
                     limits.cols = kTreeletMostRankCols;
+                    limits.ranks = true;
+                }
             }
             auto plan = [&] {
                 return build_treelets(n_features, n_trees, shapes, tree_off, split_feature, threshold, left, right,
@@ -851,6 +853,7 @@ extern "C" int fs_model_create(fs_model **out, int32_t n_features, int32_t n_tre
                                   right, value, &rk_nodes, &rk_ids, &cuts);
                 if (!m->rank_ok && limits.cols != INT_MAX && treelets) {
                     limits.cols = INT_MAX;               // more thresholds of a feature than ranks of 16 bits
+                    limits.ranks = false;
                     m->tl_ok = plan();
                 }
             }

@@ -92,6 +92,7 @@ struct TreeletLimits {
     bool pair_only = false;       // only if two workgroups fit a compute unit
     double cost = HUGE_VAL;       // clocks, as TreeletPlan::cost
     int cols = INT_MAX;           // columns of all segments together
+    bool ranks = false;           // the rank walk could take the model
 };
 
 // False if the model does not fit the format (more columns than a byte names, a node graph that

@@ -331,6 +331,7 @@ bool build_treelets(int n_features, int n_trees, const TreeShapes &shape, const 
         return false;
 
     // ---- segments: as few as their columns allow, equally long ----
+    int n_used = 0;                                                  // features
     std::vector<SegmentCuts> seg_cuts;
     std::vector<uint16_t> word((size_t)tree_off[n_trees]);           // column << 8 | rank of the splits
     {
@@ -346,6 +347,8 @@ bool build_treelets(int n_features, int n_trees, const TreeShapes &shape, const 
             ++n_splits[(size_t)(std::max(sf[g], -1) + 1)];
         }
         n_splits.erase(n_splits.begin());
+        for (int32_t n : n_splits)
+            n_used += n != 0;
         // what the walk costs at least: every used feature one column, every tree its own steps
         double least = 0.0;
         for (int32_t n : n_splits)
@@ -470,6 +473,16 @@ bool build_treelets(int n_features, int n_trees, const TreeShapes &shape, const 
     auto pair_fits = [&](int stride, int halves) { return 8 * halves * kb(stride) <= (long)kTreeletLds - kTreeletSumBytes - beside; };
     auto spread_fits = [&](int stride) { return 12 * kb(4 * stride) <= (long)kTreeletLdsWhole - beside; };
     bool pair_coder = true;
+    // Where the rank walk could take the model, single tables only with chunks of eight trees and about one column a
+    // feature.  Treelets / rank walk, perfect trees of depth 8, 2400 to 960 000 rows: 190 to 220 features,
+    // 180 to 200 trees 0.67 to 0.84; 250 features, room for four trees a chunk, 200 and 250 trees 0.87 to 1.15; 110 and
+    // 120 features of two columns each, 220 and 200 trees 0.77 to 1.07.
+    bool single = true;
+    if (limits.ranks && out->pair_ok) {
+        single = 4 * all_cols <= 5 * n_used;
+        for (const std::vector<int> &b : all)
+            single = single && b[1] - b[0] >= std::min(8, b.back() - b[0]);
+    }
     for (size_t i = 0; i < out->segments.size();) {
         TreeletSegmentPlan *sp = &out->segments[i];
         int most_cuts = 0, want = 64;
@@ -478,7 +491,7 @@ bool build_treelets(int n_features, int n_trees, const TreeShapes &shape, const 
         while (want < 5 * most_cuts && want < 1024)
             want *= 2;
         bool fits = false;
-        for (int halves = 2; halves >= 1 && !fits; --halves)
+        for (int halves = 2; halves >= (single ? 1 : 2) && !fits; --halves)
             for (int B = want; B >= 64 && !fits; B /= 2) {
                 const int least = B + 4 * ((most_cuts + 1 + 3) / 4 * 4);   // of what build_columns makes the stride
                 if (!spread_fits(least) || (pair_coder && !pair_fits(least, halves)))
