@@ -50,8 +50,8 @@ constexpr int kTreeletMostRankCols = 399;     // of all segments, where the mode
 constexpr int kTreeletMinTrees = 32;          // the coder's work needs trees to pay
 constexpr int kTreeletUnit = 4;               // trees of a chunk come in units of four
 // Trees of a chunk at most: two wavefronts of two rounds of twelve walks.  Chunks of the first kind
-// fit one buffer beside the columns in half a compute unit's LDS (and the registers it is prefetched
-// into); models with larger trees have chunks of the second kind and run one workgroup per compute unit.
+// fit one buffer beside the columns in half a compute unit's LDS; models with larger trees have chunks of
+// the second kind and run one workgroup per compute unit.  (56 KB for models of few columns: -1 to +2 %.)
 constexpr int kTreeletRound = 12;             // walks of a wavefront side by side
 constexpr int kTreeletMaxTrees = 4 * kTreeletRound;
 constexpr int kTreeletPairBuf = 40 * 1024;

@@ -467,8 +467,10 @@ static __device__ __forceinline__ void fetch_chunk(const TreeletModel &m, const 
 // walks while the other codes or waits at a barrier.  Two wavefronts share a tile: the first walks
 // the front half of a chunk's trees, the second the back half (in rounds of kTreeletRound, side by
 // side).  The row's running sum goes to and fro between them through LDS: the first adds its values
-// before the barrier that ends the walks, the second behind it, while the next chunk, which waits
-// in registers, is being stored; a second barrier publishes both.  (One wavefront per tile needs no
+// before the barrier that ends the walks, the second behind it, while the next chunk travels from memory to
+// LDS; a second barrier publishes both.  (The latency of that is the other workgroup's time: the LDS is what
+// is short, and a chunk that waits in registers and is stored from there takes more of it: eight families of 300
+// perfect trees of depth 8 1024 us instead of 1000, 64 of deep irregular trees 2211 instead of 2161.)  (One wavefront per tile needs no
 // hand-over, but eight wavefronts per compute unit leave the vector units half idle: 3.15 ms on thirty
 // families of power-law size, 200 irregular trees of depth 8, against 2.30 ms; the float-threshold kernel took
 // 3.62 ms there.)  Vector issue bounds this kernel: there it issues 1.05e9 vector instructions, which at four
@@ -478,7 +480,6 @@ static __device__ __forceinline__ void fetch_chunk(const TreeletModel &m, const 
 // chunks will be.
 constexpr int kPairTiles = 4;
 constexpr int kPairWaves = 2 * kPairTiles;
-constexpr int kPairPrefetch = kTreeletPairBuf / (64 * kPairWaves * 16);   // 16-byte registers per thread
 
 template <bool DUMP>
 __global__ void __launch_bounds__(64 * kPairWaves, 4)
@@ -529,14 +530,6 @@ treelet_pair_kernel(const FamDesc *__restrict__ descs, int n_families, int launc
 
         for (int c = 0; c < g.n_chunks; ++c) {
             const bool more = c + 1 < g.n_chunks;
-            u32x4 pf[kPairPrefetch];
-            if (more) {                              // next chunk: global -> registers
-                auto src = FS_GLOBAL(const u32x4, m.image + hn.byte_off);
-#pragma unroll
-                for (int j = 0; j < kPairPrefetch; ++j)
-                    if (1024u * (uint32_t)(wave + j * kPairWaves) < hn.bytes)
-                        pf[j] = src[(int)threadIdx.x + j * 64 * kPairWaves];
-            }
             const uint32_t val = buf + h.val_off;
             const int units = (int)h.n_trees / kTreeletUnit, front = (units + 1) / 2;
             int j0 = back ? front * kTreeletUnit : 0;
@@ -589,6 +582,8 @@ treelet_pair_kernel(const FamDesc *__restrict__ descs, int n_families, int launc
                 lds_store_f(sum_at, acc);
             }
             __syncthreads();
+            if (more)                                // every walk of this chunk is done
+                fetch_chunk(m, hn, buf, wave, kPairWaves, lane);
             if (back) {
                 acc = lds_f(sum_at);
 #pragma unroll
@@ -600,10 +595,7 @@ treelet_pair_kernel(const FamDesc *__restrict__ descs, int n_families, int launc
                 lds_store_f(sum_at + kBack, acc);
             }
             if (more) {
-#pragma unroll
-                for (int j = 0; j < kPairPrefetch; ++j)
-                    if (1024u * (uint32_t)(wave + j * kPairWaves) < hn.bytes)
-                        lds_store_u4(buf + 16u * (uint32_t)((int)threadIdx.x + j * 64 * kPairWaves), pf[j]);
+                dma_wait();
                 __syncthreads();
             }
             h = hn;
