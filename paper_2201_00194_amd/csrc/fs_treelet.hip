@@ -177,8 +177,7 @@ __device__ __forceinline__ void code_columns(const FamDesc &d, const TreeletSegm
             for (int t = 0; t < T; ++t)
                 r[j * T + t] = lds_u8(lut + min(to_u32(__builtin_fmaf(x[j * T + t], scale, offset)), last_bucket));
         }
-        for (int s = steps - 1; s >= 0; --s) {
-            float key[kChains];
+        auto probe = [&](int s, float (&key)[kChains]) {
             const uint32_t step = 1u << s;
 #pragma unroll
             for (int j = 0; j < NC; ++j) {
@@ -188,15 +187,19 @@ __device__ __forceinline__ void code_columns(const FamDesc &d, const TreeletSegm
                 for (int t = 0; t < T; ++t)
                     key[j * T + t] = lds_f(keys + 4u * r[j * T + t]);
             }
-            if (s == 0) {
+        };
+        float key[kChains];
+        for (int s = steps - 1; s > 0; --s) {
+            probe(s, key);
 #pragma unroll
-                for (int k = 0; k < kChains; k += 4)
-                    count_below(key + k, x + k, r + k);
-            } else {
+            for (int k = 0; k < kChains; ++k)
+                r[k] += key[k] <= x[k] ? 1u << s : 0u;
+        }
+        if (steps > 0) {                             // (inside the loop this cost a register move per search, 1 % of a call)
+            probe(0, key);
 #pragma unroll
-                for (int k = 0; k < kChains; ++k)
-                    r[k] += key[k] <= x[k] ? step : 0u;
-            }
+            for (int k = 0; k < kChains; k += 4)
+                count_below(key + k, x + k, r + k);
         }
         bool nan = false;
 #pragma unroll
