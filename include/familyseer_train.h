@@ -59,15 +59,14 @@ typedef struct fs_train_params {
  * may be asked for later (they size the buffers).  n_rows >= 1, n_programs >= 1.
  * The content of prog_off (DEVICE) is not validated: it must start at 0, be non-decreasing
  * and end at n_rows, as for fs_score_families; a malformed array gives undefined results.
- * The cut lists (HOST) are validated.  The call BLOCKS until its work on `stream` is done: the
- * binning kernels run there, then the length of the longest program is read back (it sizes
- * the curvature sums of the histograms); the small host arrays are copied with plain
- * (synchronising) copies.  Create trainers outside latency-critical sections.
+ * The cut lists (HOST) are validated.  The call first waits for all work on the device (its memory may
+ * be a destroyed trainer's) and BLOCKS until its own on `stream` is done: the binning kernels run there,
+ * and the length of the longest program is read back (it sizes the curvature sums of the histograms).
+ * Create trainers outside latency-critical sections.
  * All trainers of a device share one buffer for histograms.  This call grows it, where need be, to
- * what any batch of the trainers alive takes, and then waits for all work on the device.  It is at
- * most 16 GB, or what the largest trainer takes by itself.  With 256-bin features a trainer of depth d
- * takes 4 KB x 2^(d-1) x n_features, and a batch up to 4 KB x n_features for each 512 rows,
- * 192 times and once more per trainer at most.
+ * what any batch of the trainers alive takes.  It is at most 16 GB, or what the largest trainer takes by
+ * itself.  With 256-bin features a trainer of depth d takes 4 KB x 2^(d-1) x n_features, and a batch up to
+ * 4 KB x n_features for each 512 rows, but not more than 128 MB and once 4 KB x n_features per trainer.
  * Errors: FS_EINVAL, FS_EUNSUPPORTED (limits), FS_ENOMEM, FS_EDEVICE.
  */
 int fs_trainer_create(fs_trainer **out, int32_t n_features, const float *features /* DEVICE */,
@@ -78,9 +77,10 @@ int fs_trainer_create(fs_trainer **out, int32_t n_features, const float *feature
                       float bias, int32_t max_depth, int32_t max_trees, void *stream);
 
 /*
- * Free a trainer (NULL allowed).  Synchronise its streams first.  With a device's last trainer the
- * histograms' buffer goes too, unless it is of at most 512 MB: then it stays for the next trainer, or
- * until a call of this library that creates a model or a trainer or grows scratch runs out of memory.
+ * Free a trainer (NULL allowed).  Synchronise its streams first.  Its memory stays for trainers created
+ * later, up to 256 MB and 64 trainers a device.  With a device's last trainer the histograms' buffer goes
+ * too, unless it is of at most 512 MB: then it stays as well.  Both are given back where a call of this
+ * library that creates a model or a trainer or grows scratch runs out of memory.
  */
 void fs_trainer_destroy(fs_trainer *t);
 

@@ -199,13 +199,68 @@ train_count_kernel(const uint8_t *__restrict__ cols, int n_rows, int64_t r_pad, 
         atomicAdd(&count[f * kBins + t], all);
 }
 
-// The most frequent bin of every feature over the whole training set (lowest on ties).
+// Largest of a workgroup's values, in thread 0.
+__device__ int largest_of(int m)
+{
+    __shared__ int part[kBins / 64];
+    for (int off = 32; off > 0; off >>= 1)
+        m = max(m, __shfl_down(m, off));
+    if ((threadIdx.x & 63) == 0)
+        part[threadIdx.x >> 6] = m;
+    __syncthreads();
+    for (int w = 0; w < kBins / 64; ++w)
+        m = max(m, part[w]);
+    return m;
+}
+
+// What a new trainer starts with: the cut lists, if they are in pinned host memory (`staged`, n_words of them), no
+// rows counted, no trees, every row's output the bias.  Each workgroup leaves the longest of its programs in `longest`.
 __global__ void __launch_bounds__(kBins)
-train_hot_bin_kernel(const uint32_t *__restrict__ count, int32_t *__restrict__ hot_bin)
+train_clear_kernel(const int32_t *__restrict__ staged, int n_words, int32_t *__restrict__ cut_off, uint32_t *count, int n_count,
+                   int32_t *counters, int32_t *tree_off, float *row_pred, int64_t n_rows, float bias,
+                   const int32_t *__restrict__ prog_off, int n_programs, int32_t *longest)
+{
+    const int64_t at = blockIdx.x * (int64_t)kBins + threadIdx.x, step = (int64_t)gridDim.x * kBins;
+    if (staged)
+        for (int64_t i = at; i < n_words; i += step)
+            cut_off[i] = staged[i];
+    for (int64_t i = at; i < n_count; i += step)
+        count[i] = 0u;
+    for (int64_t i = at; i < n_rows; i += step)
+        row_pred[i] = bias;
+    if (blockIdx.x == 0 && threadIdx.x < 3)
+        counters[threadIdx.x] = 0;
+    if (blockIdx.x == 0 && threadIdx.x == 3)
+        tree_off[0] = 0;
+    int m = 0;
+    for (int64_t p = at; p < n_programs; p += step)
+        m = max(m, prog_off[p + 1] - prog_off[p]);
+    m = largest_of(m);
+    if (threadIdx.x == 0)
+        longest[blockIdx.x] = m;
+}
+
+// The most frequent bin of every feature over the whole training set (lowest on ties).  A workgroup behind the last
+// feature's finds the longest program (it sizes the curvature sums), also for the host (pinned memory, or null).
+__global__ void __launch_bounds__(kBins)
+train_hot_bin_kernel(const uint32_t *__restrict__ count, int n_features, int32_t *__restrict__ hot_bin,
+                     const int32_t *__restrict__ longest, int n_longest, int32_t *__restrict__ max_len, int32_t *host_max_len)
 {
     __shared__ unsigned int s_best[kBins];
     __shared__ int s_arg[kBins];
     const int f = blockIdx.x, t = threadIdx.x;
+    if (f == n_features) {
+        int m = 0;
+        for (int i = t; i < n_longest; i += kBins)
+            m = max(m, longest[i]);
+        m = largest_of(m);
+        if (t == 0) {
+            *max_len = m;
+            if (host_max_len)
+                *host_max_len = m;
+        }
+        return;
+    }
     s_best[t] = count[f * kBins + t];
     s_arg[t] = t;
     __syncthreads();
@@ -223,34 +278,32 @@ train_hot_bin_kernel(const uint32_t *__restrict__ count, int32_t *__restrict__ h
         hot_bin[f] = s_arg[0];
 }
 
-// Rows of the longest program (sizes the curvature sums).
+// The model for the host, in pinned memory of `cap` words: trees, nodes, 1; the trees' offsets; the nodes' features,
+// thresholds, children and values.  Without room for them the third word is 0.
 __global__ void __launch_bounds__(256)
-train_max_len_kernel(const int32_t *__restrict__ prog_off, int n_programs, int32_t *__restrict__ out)
+train_export_kernel(const TrainDesc d, int32_t *out, int64_t cap)
 {
-    int m = 0;
-    for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < n_programs; p += gridDim.x * blockDim.x)
-        m = max(m, prog_off[p + 1] - prog_off[p]);
-    for (int off = 32; off > 0; off >>= 1)
-        m = max(m, __shfl_down(m, off));
-    if ((threadIdx.x & 63) == 0)
-        atomicMax(out, m);
-}
-
-__global__ void train_fill_kernel(float *p, int64_t n, float v)
-{
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = v;
-}
-
-__global__ void train_clear_kernel(uint32_t *count, int n, int32_t *counters, int32_t *tree_off)
-{
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
-        count[i] = 0u;
-    if (blockIdx.x == 0 && threadIdx.x < 4)
-        counters[threadIdx.x] = 0;
-    if (blockIdx.x == 0 && threadIdx.x == 4)
-        tree_off[0] = 0;
+    const int64_t trees = d.counters[1], nodes = d.counters[2];
+    const bool fits = 4 + trees + 1 + 5 * nodes <= cap;
+    const int64_t at = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+    if (at == 0) {
+        out[0] = (int32_t)trees;
+        out[1] = (int32_t)nodes;
+        out[2] = fits ? 1 : 0;
+    }
+    if (!fits)
+        return;
+    out += 4;
+    for (int64_t i = at; i <= trees; i += step)
+        out[i] = d.m_tree_off[i];
+    out += trees + 1;
+    for (int64_t i = at; i < nodes; i += step) {
+        out[i] = d.m_feat[i];
+        out[nodes + i] = __float_as_int(d.m_thr[i]);
+        out[2 * nodes + i] = d.m_left[i];
+        out[3 * nodes + i] = d.m_right[i];
+        out[4 * nodes + i] = __float_as_int(d.m_val[i]);
+    }
 }
 
 // ---- per-round kernels -------------------------------------------------------------------
@@ -1419,6 +1472,7 @@ struct fs_trainer {
     int trees_enqueued;
     int max_len;              // rows of the longest program
     void *memory;             // everything the descriptor points to
+    size_t memory_bytes;
 };
 
 namespace fs {
@@ -1431,6 +1485,10 @@ struct BatchBuf {
     void *work = nullptr;          // histograms of the batch in work: room for any batch of `alive`
     size_t work_bytes = 0;
     std::vector<const fs_trainer *> alive;   // without any `work` is kept up to kKeptWork
+    struct Block { void *p; size_t bytes; };
+    std::vector<Block> kept;       // memory of destroyed trainers, for the next
+    size_t kept_bytes = 0;
+    void *staging[4] = {};         // pinned memory that no call uses
     size_t needed = 0, needed_before = 0;    // of `work`, since there was no trainer; and until then
     hipEvent_t copied = nullptr;
     bool pending = false;
@@ -1442,16 +1500,119 @@ static BatchBuf *const g_batch = new BatchBuf[16];   // never freed: trainers ma
 // goes with the device's last trainer, all of it where device memory runs out for something else).
 constexpr size_t kKeptWork = (size_t)512 << 20;
 
-// Frees the histograms' buffer of a device without trainers (g_train_mu held).
+// Memory of destroyed trainers stays for the next ones up to this: allocating and freeing it cost 210 us a trainer
+// (eight retrained families: 1.7 of 15 ms).
+constexpr size_t kKeptBlocks = (size_t)256 << 20;
+constexpr size_t kMostKept = 64;
+
+// Small host arrays go through pinned memory that kernels read and write: a plain copy waits 14 to 36 us.
+constexpr size_t kStagingBytes = (size_t)512 << 10;
+
+// Frees the kept blocks (g_train_mu held).
+static bool free_kept(BatchBuf &b)
+{
+    const bool any = !b.kept.empty();
+    for (const BatchBuf::Block &k : b.kept)
+        (void)hipFree(k.p);
+    b.kept.clear();
+    b.kept_bytes = 0;
+    return any;
+}
+
+// Frees the kept blocks and the histograms' buffer of a device without trainers (g_train_mu held).
 static bool give_back(BatchBuf &b)
 {
+    const bool any = free_kept(b);
     if (!b.alive.empty() || !b.work)
-        return false;
+        return any;
     (void)hipFree(b.work);
     b.work = nullptr;
     b.work_bytes = 0;
     return true;
 }
+
+// Keeps a destroyed trainer's memory, or frees it.  Kernels may still be at work in it: take_block's caller waits.
+static void keep_block(BatchBuf &b, void *p, size_t bytes)
+{
+    if (bytes > kKeptBlocks) {
+        (void)hipFree(p);
+        return;
+    }
+    while (!b.kept.empty() && (b.kept_bytes + bytes > kKeptBlocks || b.kept.size() >= kMostKept)) {   // the oldest first
+        (void)hipFree(b.kept.front().p);
+        b.kept_bytes -= b.kept.front().bytes;
+        b.kept.erase(b.kept.begin());
+    }
+    try {
+        b.kept.push_back({p, bytes});
+        b.kept_bytes += bytes;
+    } catch (const std::bad_alloc &) {
+        (void)hipFree(p);
+    }
+}
+
+// A kept block for `bytes`, not more than twice as large; null if there is none.
+static void *take_block(int device, size_t bytes, size_t *size)
+{
+    if (device < 0 || device >= 16)
+        return nullptr;
+    std::lock_guard<std::mutex> lock(g_train_mu);
+    BatchBuf &b = g_batch[device];
+    size_t best = b.kept.size();
+    for (size_t i = 0; i < b.kept.size(); ++i)
+        if (b.kept[i].bytes >= bytes && b.kept[i].bytes / 2 <= bytes && (best == b.kept.size() || b.kept[i].bytes < b.kept[best].bytes))
+            best = i;
+    if (best == b.kept.size())
+        return nullptr;
+    void *p = b.kept[best].p;
+    *size = b.kept[best].bytes;
+    b.kept_bytes -= *size;
+    b.kept.erase(b.kept.begin() + (long)best);
+    return p;
+}
+
+// kStagingBytes of pinned memory for a call that waits for what it starts, or null.
+class Staging {
+public:
+    Staging(int device, size_t bytes) : device_(device)
+    {
+        if (device < 0 || device >= 16 || bytes > kStagingBytes)
+            return;
+        {
+            std::lock_guard<std::mutex> lock(g_train_mu);
+            for (void *&s : g_batch[device].staging)
+                if (s) {
+                    p = s;
+                    s = nullptr;
+                    return;
+                }
+        }
+        if (hipHostMalloc(&p, kStagingBytes, hipHostMallocDefault) != hipSuccess) {
+            p = nullptr;
+            (void)hipGetLastError();
+        }
+    }
+    ~Staging()
+    {
+        if (!p)
+            return;
+        {
+            std::lock_guard<std::mutex> lock(g_train_mu);
+            for (void *&s : g_batch[device_].staging)
+                if (!s) {
+                    s = p;
+                    return;
+                }
+        }
+        (void)hipHostFree(p);
+    }
+    Staging(const Staging &) = delete;
+    Staging &operator=(const Staging &) = delete;
+    void *p = nullptr;
+
+private:
+    int device_;
+};
 
 bool give_back_training_memory(int device)
 {
@@ -1473,9 +1634,10 @@ struct Arena {
         part[n++] = {(void **)out, bytes};
         bytes += ((count ? count : 1) * sizeof(T) + 255) & ~(size_t)255;
     }
-    int place(void **base)
+    int place(void **base, size_t *size, int device)
     {
-        const hipError_t e = hipMalloc(base, bytes);
+        *base = take_block(device, bytes, size);
+        const hipError_t e = *base ? hipSuccess : hipMalloc(base, *size = bytes);
         if (e != hipSuccess) {
             *base = nullptr;
             (void)hipGetLastError();                             // not the next launch's error
@@ -1580,7 +1742,11 @@ static int grow_work(BatchBuf &b, size_t bytes, size_t wish)
     for (const size_t size : {wish, bytes, had}) {
         if (size == 0)
             continue;
-        const hipError_t err = hipMalloc(&b.work, size);
+        hipError_t err = hipMalloc(&b.work, size);
+        if (err == hipErrorOutOfMemory && free_kept(b)) {
+            (void)hipGetLastError();
+            err = hipMalloc(&b.work, size);
+        }
         if (err == hipSuccess) {
             b.work_bytes = size;
             break;
@@ -1624,19 +1790,24 @@ extern "C" void fs_trainer_destroy(fs_trainer *t)
 {
     if (!t)
         return;
-    if (t->memory)
+    if (t->memory && (t->device < 0 || t->device >= 16))
         (void)hipFree(t->memory);
     if (t->device >= 0 && t->device < 16) {
         std::lock_guard<std::mutex> lock(g_train_mu);
         BatchBuf &b = g_batch[t->device];
+        if (t->memory)
+            keep_block(b, t->memory, t->memory_bytes);
         const auto it = std::find(b.alive.begin(), b.alive.end(), t);
         if (it != b.alive.end()) {
             b.alive.erase(it);
             if (b.alive.empty()) {
                 b.needed_before = b.needed;
                 b.needed = 0;
-                if (b.work_bytes > kKeptWork)
-                    give_back(b);
+                if (b.work_bytes > kKeptWork) {
+                    (void)hipFree(b.work);
+                    b.work = nullptr;
+                    b.work_bytes = 0;
+                }
             }
         }
     }
@@ -1706,6 +1877,8 @@ extern "C" int fs_trainer_create(fs_trainer **out, int32_t n_features, const flo
     float *d_target = nullptr, *d_cuts = nullptr;
     int32_t *d_hot = nullptr;
     uint32_t *d_count = nullptr;
+    int32_t *d_longest = nullptr;
+    const int clear_blocks = (int)std::min<int64_t>(1024, std::max<int64_t>(32, n_rows / 1024));
     Arena arena;
     // whole pieces of a row, and of a 64-byte sector from four pieces on
     h.row_bytes = (n_features + kHistFeats - 1) / kHistFeats * kHistFeats;
@@ -1717,6 +1890,7 @@ extern "C" int fs_trainer_create(fs_trainer **out, int32_t n_features, const flo
     arena.add(&d_cut_off, (size_t)n_features + 1 + (size_t)n_cuts);   // the cuts lie behind
     arena.add(&d_hot, (size_t)n_features);
     arena.add(&d_count, (size_t)n_features * kBins);
+    arena.add(&d_longest, (size_t)clear_blocks);
     arena.add(&h.row_pred, (size_t)n_rows);
     arena.add(&h.prog_pred, (size_t)n_programs);
     arena.add(&h.rec[0], (size_t)n_rows);
@@ -1737,9 +1911,9 @@ extern "C" int fs_trainer_create(fs_trainer **out, int32_t n_features, const flo
     arena.add(&h.m_right, (size_t)node_cap);
     arena.add(&h.m_thr, (size_t)node_cap);
     arena.add(&h.m_val, (size_t)node_cap);
-    rc = arena.place(&t->memory);
+    rc = arena.place(&t->memory, &t->memory_bytes, t->device);
     if (rc == FS_ENOMEM && give_back_training_memory(t->device))
-        rc = arena.place(&t->memory);
+        rc = arena.place(&t->memory, &t->memory_bytes, t->device);
     if (rc != FS_OK) {
         fs_trainer_destroy(t);
         return rc;
@@ -1752,57 +1926,58 @@ extern "C" int fs_trainer_create(fs_trainer **out, int32_t n_features, const flo
     h.cut_off = d_cut_off;
     h.cuts = d_cuts;
     h.hot_bin = d_hot;
-    e = hipMemcpyAsync(d_prog_off, prog_off, sizeof(int32_t) * ((size_t)n_programs + 1),
-                       hipMemcpyDeviceToDevice, stream);
+    // A kept block may still be in use by what its trainer had started, on whichever stream.
+    e = hipDeviceSynchronize();
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(d_prog_off, prog_off, sizeof(int32_t) * ((size_t)n_programs + 1),
+                           hipMemcpyDeviceToDevice, stream);
     if (e == hipSuccess)
         e = hipMemcpyAsync(d_target, target, sizeof(float) * (size_t)n_programs,
                            hipMemcpyDeviceToDevice, stream);
-    // the small host arrays in one plain copy (it waits for the device)
+    // the small host arrays, staged [longest program, cut_off, cuts] or, if too long for that, in one plain copy
+    const size_t head = (size_t)n_features + 1, n_words = head + (size_t)n_cuts;
+    const Staging staging(t->device, sizeof(int32_t) * (n_words + 1));
+    int32_t *const staged = (int32_t *)staging.p;
     if (e == hipSuccess) {
-        const size_t head = (size_t)n_features + 1;
-        std::unique_ptr<int32_t[]> both(new (std::nothrow) int32_t[head + (size_t)n_cuts]);
-        if (!both) {
+        std::unique_ptr<int32_t[]> both(staged ? nullptr : new (std::nothrow) int32_t[n_words]);
+        int32_t *const words = staged ? staged + 1 : both.get();
+        if (!words) {
             fs_trainer_destroy(t);
             return fail(FS_ENOMEM, "out of host memory");
         }
-        memcpy(both.get(), cut_off, sizeof(int32_t) * head);
+        memcpy(words, cut_off, sizeof(int32_t) * head);
         if (n_cuts > 0)
-            memcpy(both.get() + head, cuts, sizeof(float) * (size_t)n_cuts);
-        e = hipMemcpy(d_cut_off, both.get(), sizeof(int32_t) * (head + (size_t)n_cuts), hipMemcpyHostToDevice);
+            memcpy(words + head, cuts, sizeof(float) * (size_t)n_cuts);
+        if (!staged)
+            e = hipMemcpy(d_cut_off, words, sizeof(int32_t) * n_words, hipMemcpyHostToDevice);
     }
     if (e != hipSuccess) {
         fs_trainer_destroy(t);
         return fail_hip(e, "fs_trainer_create: copies");
     }
+    hipLaunchKernelGGL(train_clear_kernel, dim3((unsigned)clear_blocks), dim3(kBins), 0, stream,
+                       (const int32_t *)(staged ? staged + 1 : nullptr), (int)n_words, d_cut_off, d_count, n_features * kBins,
+                       h.counters, h.m_tree_off, h.row_pred, (int64_t)n_rows, bias, (const int32_t *)d_prog_off, n_programs,
+                       d_longest);
     hipLaunchKernelGGL(train_bin_kernel,
                        dim3((unsigned)((n_rows + 2047) / 2048 * 8 * ((n_features + kHistFeats - 1) / kHistFeats))),
                        dim3(256), 0, stream, features, layout, n_features, (int)n_rows, h.r_pad,
                        (const int32_t *)d_cut_off, (const float *)d_cuts, bins, h.row_bytes, cols);
-    rc = check_launch("train_bin_kernel launch");
+    hipLaunchKernelGGL(train_count_kernel,
+                       dim3((unsigned)((n_rows + kCountRows - 1) / kCountRows), (unsigned)n_features), dim3(256),
+                       0, stream, (const uint8_t *)cols, (int)n_rows, h.r_pad, d_count);
+    hipLaunchKernelGGL(train_hot_bin_kernel, dim3((unsigned)n_features + 1), dim3(kBins), 0, stream,
+                       (const uint32_t *)d_count, n_features, d_hot, (const int32_t *)d_longest, clear_blocks, h.counters + 3,
+                       staged);
+    rc = check_launch("trainer set-up kernels launch");
+    e = hipStreamSynchronize(stream);                            // (whatever has been launched reads the staging memory)
     if (rc == FS_OK) {
-        hipLaunchKernelGGL(train_clear_kernel, dim3(64), dim3(256), 0, stream, d_count, n_features * kBins,
-                           h.counters, h.m_tree_off);
-        hipLaunchKernelGGL(train_count_kernel,
-                           dim3((unsigned)((n_rows + kCountRows - 1) / kCountRows), (unsigned)n_features), dim3(256),
-                           0, stream, (const uint8_t *)cols, (int)n_rows, h.r_pad, d_count);
-        hipLaunchKernelGGL(train_hot_bin_kernel, dim3((unsigned)n_features), dim3(kBins), 0, stream,
-                           (const uint32_t *)d_count, d_hot);
-        hipLaunchKernelGGL(train_fill_kernel, dim3(1024), dim3(256), 0, stream, h.row_pred,
-                           (int64_t)n_rows, bias);
-        rc = check_launch("trainer set-up kernels launch");
-    }
-    if (rc == FS_OK) {
-        // counters[3] is free until training starts: longest program, read back here
-        hipLaunchKernelGGL(train_max_len_kernel, dim3((unsigned)std::min(256, (n_programs + 255) / 256)), dim3(256), 0, stream,
-                           (const int32_t *)d_prog_off, n_programs, h.counters + 3);
-        rc = check_launch("train_max_len_kernel launch");
-        if (rc == FS_OK) {
-            e = hipStreamSynchronize(stream);
-            if (e == hipSuccess)
-                e = hipMemcpy(&t->max_len, h.counters + 3, sizeof(int32_t), hipMemcpyDeviceToHost);
-            if (e != hipSuccess)
-                rc = fail_hip(e, "fs_trainer_create: reading the longest program");
-        }
+        if (staged)
+            t->max_len = staged[0];
+        else if (e == hipSuccess)
+            e = hipMemcpy(&t->max_len, h.counters + 3, sizeof(int32_t), hipMemcpyDeviceToHost);
+        if (e != hipSuccess)
+            rc = fail_hip(e, "fs_trainer_create: reading the longest program");
     }
     if (rc == FS_OK)
         rc = reserve_work(t);
@@ -2100,6 +2275,30 @@ extern "C" int fs_trainer_export(const fs_trainer *t, int32_t *tree_off, int32_t
     if (!t || !tree_off || !split_feature || !threshold || !left || !right || !value)
         return fail(FS_EINVAL, "fs_trainer_export: NULL argument");
     FS_HIP(hipStreamSynchronize((hipStream_t)stream_));
+    int dev = -1;
+    if (hipGetDevice(&dev) == hipSuccess && dev == t->device) {  // at once, if it is small (six plain copies took 95 us)
+        const Staging staging(dev, 0);
+        const int32_t *at = (const int32_t *)staging.p;
+        if (at) {
+            hipLaunchKernelGGL(train_export_kernel, dim3(32), dim3(256), 0, nullptr, t->h, (int32_t *)staging.p,
+                               (int64_t)(kStagingBytes / sizeof(int32_t)));
+            const int rc = check_launch("train_export_kernel launch");
+            FS_HIP(hipStreamSynchronize(nullptr));
+            if (rc != FS_OK)
+                return rc;
+            if (at[2] != 0) {
+                const size_t offs = (size_t)at[0] + 1, n = (size_t)at[1];
+                at += 4;
+                memcpy(tree_off, at, sizeof(int32_t) * offs);
+                at += offs;
+                for (void *out : {(void *)split_feature, (void *)threshold, (void *)left, (void *)right, (void *)value}) {
+                    memcpy(out, at, sizeof(int32_t) * n);
+                    at += n;
+                }
+                return FS_OK;
+            }
+        }
+    }
     int32_t c[4];
     FS_HIP(hipMemcpy(c, t->h.counters, sizeof(c), hipMemcpyDeviceToHost));
     const size_t n = (size_t)c[2];

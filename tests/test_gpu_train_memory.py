@@ -139,3 +139,23 @@ def test_what_is_kept_is_given_back_where_memory_runs_out(api):
     assert free_bytes() - alive < 16 << 20
     api.fs_train_boost([tr], 2, api.train_params(max_depth=10, eta=0.5, lam=1.0))
     assert tr.size()[0] == 2
+
+
+@pytest.mark.parametrize("n_programs,n_features,max_cuts,depth,rounds", [
+    (40, 5, 15, 3, 2),
+    (300, 700, 255, 2, 2),                           # 0.7 MB of cut lists: more than is staged at once
+    (6000, 17, 63, 10, 20),                          # 0.6 MB of trees
+])
+def test_a_destroyed_trainers_memory_serves_the_next(api, T, n_programs, n_features, max_cuts, depth, rounds):
+    params = api.train_params(max_depth=depth, eta=0.4, lam=0.1)
+    held = None
+    for n in (n_programs, n_programs * 9 // 10):
+        ts = W.make_train_set(n, n, stmts=(1, 6), n_features=n_features, max_cuts=max_cuts)
+        tr = api.fs_trainer.from_train_set(ts, max_depth=depth, max_trees=rounds)
+        api.fs_train_boost([tr], rounds, params)
+        exp = T.train(ts.features, ts.prog_off, ts.target, ts.cut_off, ts.cuts, n_rounds=rounds, max_depth=depth,
+                      eta=0.4, lam=0.1)
+        same_trees(tr.export(), exp)
+        tr.destroy()
+        held = held or free_bytes()
+        assert held - free_bytes() < 1 << 20         # the second one took no more
