@@ -441,6 +441,25 @@ __device__ __forceinline__ long long wave_prefix_ll(long long v)
     return v;
 }
 
+// The same as 32-bit adds whose operand comes through DPP; a lane without a source is not written.  (A DPP operand may
+// not have been written by the last two instructions.)
+__device__ __forceinline__ unsigned long long wave_prefix_u64(unsigned long long v)
+{
+    uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
+#define FS_PREFIX_STEP(how) \
+    "v_add_co_u32_dpp %0, vcc, %0, %0 " how " bank_mask:0xf\n\t" \
+    "v_addc_co_u32_dpp %1, vcc, %1, %1, vcc " how " bank_mask:0xf\n\t"
+    asm("s_nop 1\n\t" FS_PREFIX_STEP("row_shr:1 row_mask:0xf") "s_nop 0\n\t" FS_PREFIX_STEP("row_shr:2 row_mask:0xf")
+        "s_nop 0\n\t" FS_PREFIX_STEP("row_shr:4 row_mask:0xf") "s_nop 0\n\t" FS_PREFIX_STEP("row_shr:8 row_mask:0xf")
+        "s_nop 0\n\t" FS_PREFIX_STEP("row_bcast:15 row_mask:0xa") "s_nop 0\n\t" FS_PREFIX_STEP("row_bcast:31 row_mask:0xc")
+        "s_nop 1"
+        : "+v"(lo), "+v"(hi)
+        :
+        : "vcc");
+#undef FS_PREFIX_STEP
+    return (unsigned long long)hi << 32 | lo;
+}
+
 __device__ __forceinline__ long long lane63_ll(long long v)
 {
     const int lo = __builtin_amdgcn_readlane((int)v, 63), hi = __builtin_amdgcn_readlane((int)(v >> 32), 63);
@@ -464,11 +483,17 @@ __device__ __forceinline__ void best_step(double &best, int &best_cut)
 // The counted child of a split node: less curvature, or fewer rows where they are known; the left one on ties.
 __device__ __forceinline__ int counts_left(long long l, long long r) { return l <= r ? 1 : 0; }
 
-// Totals of a node; `turn` says which of the root's sums the round uses.
+// Totals of a node; `turn` says which of the root's sums the round uses.  (No launch that calls this writes the totals
+// of the level's nodes: with a uniform node they are scalar loads.)
 __device__ __forceinline__ void node_sums(const TrainDesc &d, int node, int turn, long long &G, long long &H)
 {
-    G = node == 0 ? d.root[turn].G : d.h_G[node];
-    H = node == 0 ? d.root[turn].H : d.h_H[node];
+    if (node == 0) {
+        G = *FS_CONST(long long, &d.root[turn].G);
+        H = *FS_CONST(long long, &d.root[turn].H);
+    } else {
+        G = *FS_CONST(long long, d.h_G + node);
+        H = *FS_CONST(long long, d.h_H + node);
+    }
 }
 
 // Best cut of feature f for the open node `node`, by one wavefront: lane l holds bins 4l..4l+3
@@ -599,21 +624,23 @@ __device__ __forceinline__ void wave_best_cut(const TrainDesc &d, const Params &
     }
 }
 
-// Shared by the packed search below: largest value of a non-negative float over the wavefront.
+// Largest of a value over the wavefront, by the steps of the prefix sum.
 __device__ __forceinline__ float wave_max_f(float v)
 {
-    v = fmaxf(v, __int_as_float(dpp_i<0x111, 0xf>(__float_as_int(v))));
-    v = fmaxf(v, __int_as_float(dpp_i<0x112, 0xf>(__float_as_int(v))));
-    v = fmaxf(v, __int_as_float(dpp_i<0x114, 0xf>(__float_as_int(v))));
-    v = fmaxf(v, __int_as_float(dpp_i<0x118, 0xf>(__float_as_int(v))));
-    v = fmaxf(v, __int_as_float(dpp_i<0x142, 0xa>(__float_as_int(v))));
-    v = fmaxf(v, __int_as_float(dpp_i<0x143, 0xc>(__float_as_int(v))));
+#define FS_MAX_STEP(how) "s_nop 1\n\tv_max_f32_dpp %0, %0, %0 " how " bank_mask:0xf\n\t"
+    asm(FS_MAX_STEP("row_shr:1 row_mask:0xf") FS_MAX_STEP("row_shr:2 row_mask:0xf") FS_MAX_STEP("row_shr:4 row_mask:0xf")
+        FS_MAX_STEP("row_shr:8 row_mask:0xf") FS_MAX_STEP("row_bcast:15 row_mask:0xa") FS_MAX_STEP("row_bcast:31 row_mask:0xc")
+        "s_nop 1"
+        : "+v"(v));
+#undef FS_MAX_STEP
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
-// The same for packed bins (G * 2^hb + H, hb <= 31).  The search is bound by instruction issue, most
-// of it double-precision divisions, so:
+// The same for packed bins (G * 2^hb + H, hb <= 31).  Bound by instruction issue where a level has many nodes (42 000
+// searches of 164 features in 8 families: 25 us, 30 with the sums' steps and the nodes' values in vector code), by
+// its chain of loads elsewhere (one family of 4000 programs: 5.9 us, 6.7 so), so:
 //  - G and H go through one prefix sum, still packed.
+//  - what the level's nodes are and hold comes by scalar loads.
 //  - GL^2/(HL+lambda) + GR^2/(HR+lambda) is formed in float first, and only cuts within 2^-18 of
 //    the largest are evaluated as the definition says, usually one.  The float value is within
 //    10 * 2^-24 of the true one (G and GL times 2^hb are multiples of 2^hb below 2^63, and below
@@ -628,56 +655,69 @@ __device__ __forceinline__ void wave_best_cut_packed(const TrainDesc &d, const P
 {
     long long G, H;
     node_sums(d, node, turn, G, H);
-    const int hot = d.hot_bin[f];
-    const int m = d.cut_off[f + 1] - d.cut_off[f];
+    const int hot = *FS_CONST(int32_t, d.hot_bin + f);
     const unsigned mask = (1u << hb) - 1u;
     const unsigned long long total = (unsigned long long)(G * ((long long)1 << hb) + H);
     const unsigned long long mine = v[0] + v[1] + v[2] + v[3];
-    const unsigned long long incl = (unsigned long long)wave_prefix_ll((long long)mine);
+    const unsigned long long incl = wave_prefix_u64(mine);
     // what the counted bins lack of the node's totals sits in the hot bin
     const unsigned long long rest = total - (unsigned long long)lane63_ll((long long)incl);
-    unsigned long long before = incl - mine;
-    if ((hot >> 2) < lane)
-        before += rest;
-    if ((hot >> 2) == lane) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-            if ((hot & 3) == k)
-                v[k] = rest;
+    unsigned long long before = incl - mine + ((hot >> 2) < lane ? rest : 0ull);
+    const unsigned before_H = (unsigned)before & mask;
+    const unsigned long long here = (hot >> 2) == lane ? rest : 0ull;
+    switch (hot & 3) {
+    case 0: v[0] += here; break;
+    case 1: v[1] += here; break;
+    case 2: v[2] += here; break;
+    default: v[3] += here;
     }
     const int mcw = (int)min(prm.mcw, 0x7fffffffll), H_all = (int)H;
     const float lambda = (float)prm.lambda;
     const double G_all = (double)(long long)(total - (unsigned long long)H);
-    float t[4], most = 0.0f;
-    bool cand[4];
+    // (Cuts behind the feature's last one leave no curvature on the right, and mcw is at least 1.)
+    float t[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        before += v[k];
+        v[k] = before;                                           // left sums of cut 4 * lane + k + 1
+        const unsigned low = (unsigned)before;
+        const int HL = (int)(low & mask), HR = H_all - HL;
+        const double GL = __builtin_fma((double)(int)(before >> 32), 0x1p32, (double)(low & ~mask));   // times 2^hb
+        const float gl = (float)GL, gr = (float)(G_all - GL);
+        const float l = gl * __builtin_amdgcn_rcpf((float)HL + lambda), r = gr * __builtin_amdgcn_rcpf((float)HR + lambda);
+        t[k] = HL >= mcw && HR >= mcw ? __builtin_fmaf(gl, l, gr * r) : -1.0f;
+    }
+    const float most = wave_max_f(fmaxf(fmaxf(t[0], t[1]), fmaxf(t[2], t[3])));
+    const float least = most * (1.0f - 0x1p-18f);                // more than -1
+    unsigned long long votes[4];
     int n_cand = 0;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        const bool filled = ((unsigned)v[k] & mask) != 0u;
-        before += v[k];
-        v[k] = before;                                           // left sums of cut 4 * lane + k + 1
-        const int HL = (int)((unsigned)before & mask), HR = H_all - HL;
-        cand[k] = 4 * lane + k + 1 <= m && filled && HL >= mcw && HR >= mcw;
-        const double GL = (double)(long long)(before - (unsigned)HL);   // times 2^hb
-        const float gl = (float)GL, gr = (float)(G_all - GL);
-        const float l = gl * __builtin_amdgcn_rcpf((float)HL + lambda), r = gr * __builtin_amdgcn_rcpf((float)HR + lambda);
-        t[k] = gl * l + gr * r;
-        most = cand[k] ? fmaxf(most, t[k]) : most;
+        votes[k] = __builtin_amdgcn_ballot_w64(!(t[k] < least));
+        n_cand += __popcll(votes[k]);
     }
-    most = wave_max_f(most);
-    const float least = most * (1.0f - 0x1p-18f);
+    if (n_cand > 1) {                                            // less those behind an empty bin
+        n_cand = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            votes[k] &= __builtin_amdgcn_ballot_w64((((unsigned)v[k] & mask) != (k ? (unsigned)v[k ? k - 1 : 0] & mask : before_H)));
+            n_cand += __popcll(votes[k]);
+        }
+    }
+    if (n_cand == 0) {
+        if (lane == 0)
+            d.best[pair].cut = 0;
+        return;
+    }
     int cut = 0;
     double best = 0.0;
     long long bGL = 0, bHL = 0;
-    const double t3 = node == 0 ? parent_term(G, H, prm.inv_scale, prm.lambda) : d.h_own[node];
+    const double t3 = node == 0 ? parent_term(G, H, prm.inv_scale, prm.lambda) : *FS_CONST(double, d.h_own + node);
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        const bool eval = cand[k] && !(t[k] < least);
-        const unsigned long long votes = __ballot(eval);
-        if (votes == 0)
+        if (votes[k] == 0)
             continue;
-        n_cand += __popcll(votes);
-        if (eval) {
+        if (votes[k] >> lane & 1) {
             const long long HL = (long long)((unsigned)v[k] & mask);
             const long long GL = ((long long)v[k] - HL) >> hb;   // the difference is a multiple of 2^hb
             const double gn = split_gain(GL, HL, G, H, prm.inv_scale, prm.lambda, t3);
@@ -688,11 +728,6 @@ __device__ __forceinline__ void wave_best_cut_packed(const TrainDesc &d, const P
                 bHL = HL;
             }
         }
-    }
-    if (n_cand == 0) {
-        if (lane == 0)
-            d.best[pair].cut = 0;
-        return;
     }
     const double gain = best;
     int best_cut = cut;
@@ -747,7 +782,7 @@ static_assert(kBins * 8 >= kCutScratchBytes, "room for the cut search's scratch"
 
 __device__ __forceinline__ bool is_packed(const TrainDesc &d, int turn, int hb)
 {
-    return hb > 0 && d.root[turn].abs_q < (1ull << (63 - hb));
+    return hb > 0 && *FS_CONST(unsigned long long, &d.root[turn].abs_q) < (1ull << (63 - hb));
 }
 
 // Records of a node (heap index) and which of its pieces of 2^shift rows a workgroup takes.
@@ -903,7 +938,7 @@ struct Bins4 {                // four consecutive bins of a lane
 __device__ __forceinline__ int64_t hist_at(const TrainDesc &d, int level, int pair, int which, int f)
 {
     const int n_pairs = level > 0 ? 1 << (level - 1) : 0;
-    const int slot = level == 0 ? 0 : which ? d.h_slot[n_pairs - 1 + pair] : n_pairs + pair;
+    const int slot = level == 0 ? 0 : which ? *FS_CONST(int32_t, d.h_slot + n_pairs - 1 + pair) : n_pairs + pair;
     return ((int64_t)slot * d.n_features + f) * kBins;
 }
 
@@ -1399,7 +1434,7 @@ template <bool PACKED>
 __device__ __forceinline__ void split_run(const TrainDesc &d, const Params &prm, unsigned long long *lds,
                                           const Pair &it, int level, int turn, int shift, int f, int hb)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
     const int children = level > 0 ? 2 : 1;
     const int pieces = pieces_of(it.count, shift);
     Bins4<PACKED> own = {};
@@ -1445,10 +1480,11 @@ train_split_kernel(const TrainDesc *__restrict__ descs, int level, int turn, int
     Pair it = {0, -1, 0, 0, d.n_rows};
     if (level > 0) {
         const int parent = (1 << (level - 1)) - 1 + pair, left = 2 * parent + 1;
-        const int4 s = d.seg[parent];
+        const i32x4 s = *FS_CONST(i32x4, d.seg + parent);
         if (s.x == 0)                                            // not split
             return;
-        const bool count_left = grown ? counts_left(d.h_H[left], d.h_H[left + 1]) : counts_left(s.x, s.y);
+        const bool count_left = grown ? counts_left(*FS_CONST(long long, d.h_H + left), *FS_CONST(long long, d.h_H + left + 1))
+                                      : counts_left(s.x, s.y);
         it = {count_left ? left : left + 1, count_left ? left + 1 : left, pair, s.z, s.x + s.y};
         if (!grown) {                                            // the pieces are the counted node's
             it.first = count_left ? s.z : s.z + s.x;
