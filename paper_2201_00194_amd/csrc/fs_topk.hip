@@ -4,8 +4,10 @@
 //
 // Scores are mapped to unsigned keys whose integer order is the wanted order (-0 and +0
 // share a key, NaN gets the lowest key).  One workgroup serves one request:
-//   1. radix select (4 passes of 8 bits, histogram in LDS) finds the key of the k-th
-//      best entry and how many entries that tie with it still fit;
+//   1. radix select (passes of 11, 11 and 10 bits, histogram in LDS) finds the key of the k-th
+//      best entry and how many entries that tie with it still fit.  As soon as no more than
+//      kRankMost entries can be among the best, each of these counts those above it and so knows
+//      its place: steps 2 and 3 fall away (usually after the first pass);
 //   2. every wavefront owns a contiguous slice of the scores; it counts the entries above
 //      that key and the ties in its slice, the counts are scanned, and a second sweep places
 //      every entry above the key plus the lowest-index ties as 64-bit composites
@@ -40,18 +42,63 @@ __device__ __forceinline__ uint32_t score_key(float s)
 constexpr int kTopkWaves = kTopkThreads / 64;
 constexpr int kTopkUnroll = 8;     // loads in flight per thread
 
-// Keys of kTopkUnroll consecutive 64-element pieces starting at `base`, this lane's element of
+// Scores and keys of kTopkUnroll consecutive 64-element pieces starting at `base`, this lane's element of
 // each; pieces past `end` read a clamped address and are flagged invalid by the caller.
 __device__ __forceinline__ void load_keys(const float *__restrict__ score, int base, int end,
-                                          int lane, uint32_t (&key)[kTopkUnroll])
+                                          int lane, uint32_t (&key)[kTopkUnroll], float (&v)[kTopkUnroll])
 {
-    float v[kTopkUnroll];
 #pragma unroll
     for (int u = 0; u < kTopkUnroll; ++u)
         v[u] = score[min(base + u * 64 + lane, end - 1)];
 #pragma unroll
     for (int u = 0; u < kTopkUnroll; ++u)
         key[u] = score_key(v[u]);
+}
+
+constexpr int kDigitBits = 11;     // of a pass of the radix select
+constexpr int kBinsOf = 1 << kDigitBits;
+
+// Entries are placed by counting those above each, which takes c^2 comparisons, where that is faster than what it saves:
+//  - all of them, without a select, up to kRankAll: a cut of 256 entries 4.4 us, 4.7 with a select; of 320 5.4 and 4.8;
+//  - what a pass of the select leaves, up to kRankSome.  4096 entries, cut of 64: 6.7 us (sorted: 14.0), of 180: 8.4 (16.4);
+//  - up to kRankMost if another pass would leave nearly as many: cut of 300 9.6 us (10.6 always; sorted 19.2),
+//    of 450 12.0 (17.4 with kRankSome only; sorted 19.4).
+constexpr int kRankAll = 256, kRankSome = 320, kRankMost = 512;
+static_assert(kRankMost * 16 <= kBinsOf * 4, "the entries, their scores and places lie where the histogram was");
+
+__device__ __forceinline__ int wave_inclusive(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast:15
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);   // row_bcast:31
+    return v;
+}
+
+// The digit whose bin holds the need-th best entry, by one wavefront: sel = {digit, place in the bin, entries of it}.
+__device__ __forceinline__ void find_digit(const int *hist, int need, int lane, int *sel)
+{
+    constexpr int kPer = kBinsOf / 64;               // bins 32l .. 32l+31 of lane l, in an order that spreads over the banks
+    int total = 0;
+#pragma unroll
+    for (int j = 0; j < kPer / 4; ++j) {
+        const int4 c = *(const int4 *)&hist[kPer * lane + 4 * ((j + lane) & (kPer / 4 - 1))];
+        total += c.x + c.y + c.z + c.w;
+    }
+    const int incl = wave_inclusive(total);
+    const int above = __builtin_amdgcn_readlane(incl, 63) - incl;                 // entries in higher lanes' bins
+    const unsigned long long here = __builtin_amdgcn_ballot_w64(above < need && above + total >= need);
+    const int owner = __ffsll((long long)here) - 1;
+    const int rest = need - __builtin_amdgcn_readlane(above, owner);
+    const int digit = kPer * owner + kPer - 1 - (lane & (kPer - 1));              // downwards; both halves alike
+    const int count = hist[digit], upto = wave_inclusive(lane < kPer ? count : 0);
+    if (lane < kPer && upto >= rest && upto - count < rest) {
+        sel[0] = digit;
+        sel[1] = rest - (upto - count);
+        sel[2] = count;
+    }
 }
 
 __global__ void __launch_bounds__(kTopkThreads)
@@ -81,9 +128,9 @@ topk_kernel(const TopkDesc *__restrict__ far, NearTopk)
     int kpow2 = 2;                        // at least 2: keeps the histogram 16-byte aligned
     while (kpow2 < kk)
         kpow2 <<= 1;
-    int *hist = (int *)(cand + kpow2);    // 256 ints
-    int *wave_cnt = hist + 256;           // 2 x 16 ints: per-wavefront counts (above, equal)
-    int *sel = wave_cnt + 2 * kTopkWaves; // [0] digit, [1] remaining need
+    int *hist = (int *)(cand + kpow2);    // kBinsOf ints
+    int *wave_cnt = hist + kBinsOf;       // 2 x 16 ints: per-wavefront counts (above, equal)
+    int *sel = wave_cnt + 2 * kTopkWaves; // [0] digit, [1] remaining need, [2] entries of the digit, [3] entries collected
 
     // Every wavefront owns a contiguous, 64-aligned slice of the scores: slices in wavefront
     // order are the scores in index order.
@@ -94,26 +141,30 @@ topk_kernel(const TopkDesc *__restrict__ far, NearTopk)
     // fetches its keys once and keeps them in registers for all six sweeps below.
     const bool cached = per_wave <= 64 * kTopkUnroll;
     uint32_t key[kTopkUnroll];
+    float v[kTopkUnroll];
     if (cached && w_begin < w_end)
-        load_keys(score, w_begin, w_end, lane, key);
+        load_keys(score, w_begin, w_end, lane, key, v);
 
     // ---- 1. key of the kk-th best entry ----
     uint32_t prefix = 0, mask = 0;
     int need = kk;
-    if (kk < n) {
-        for (int shift = 24; shift >= 0; shift -= 8) {
-            if (tid < 256)
-                hist[tid] = 0;
+    int few = n <= kRankAll ? n : 0;     // entries that may be among the best, once there are few enough
+    if (few == 0 && kk < n) {
+        if (tid == 0)
+            sel[3] = 0;
+        for (int shift = 32 - kDigitBits;; shift = max(shift - kDigitBits, 0)) {
+            for (int b = tid; b < kBinsOf; b += kTopkThreads)
+                hist[b] = 0;
             __syncthreads();
             int run_digit = -1, run = 0;
             for (int base = w_begin; base < w_end; base += 64 * kTopkUnroll) {
                 if (!cached)
-                    load_keys(score, base, w_end, lane, key);
+                    load_keys(score, base, w_end, lane, key, v);
 #pragma unroll
                 for (int u = 0; u < kTopkUnroll; ++u) {
                     const bool valid = base + u * 64 + lane < w_end;
                     if (valid && (key[u] & mask) == prefix) {
-                        const int dg = (key[u] >> shift) & 255;
+                        const int dg = (key[u] >> shift) & (kBinsOf - 1) & ~(mask >> shift);
                         if (dg != run_digit) {
                             if (run)
                                 atomicAdd(&hist[run_digit], run);
@@ -127,37 +178,84 @@ topk_kernel(const TopkDesc *__restrict__ far, NearTopk)
             if (run)
                 atomicAdd(&hist[run_digit], run);
             __syncthreads();
-            if (wave == 0) {
-                // The digit whose bin holds the need-th best entry: lane l owns bins 4l..4l+3,
-                // a suffix sum over the lanes gives the entries in higher bins.
-                const int4 c = *(const int4 *)&hist[4 * lane];
-                const int total = c.x + c.y + c.z + c.w;
-                int suffix = total;                       // inclusive: lanes >= this one
-#pragma unroll
-                for (int off = 1; off < 64; off <<= 1) {
-                    const int v = __shfl_down(suffix, off);
-                    if (lane + off < 64)
-                        suffix += v;
-                }
-                int above = suffix - total;
-                const int cnt[4] = {c.w, c.z, c.y, c.x};
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    if (above < need && above + cnt[j] >= need) {
-                        sel[0] = 4 * lane + 3 - j;
-                        sel[1] = need - above;
-                    }
-                    above += cnt[j];
-                }
-            }
+            if (wave == 0)
+                find_digit(hist, need, lane, sel);
             __syncthreads();
             prefix |= (uint32_t)sel[0] << shift;
-            mask |= 255u << shift;
+            mask = ~0u << shift;
             need = sel[1];
+            const int may = kk - need + sel[2];
+            if (cached && (may <= kRankSome || may <= min(kk + kk / 8, kRankMost))) {
+                few = may;
+                break;
+            }
+            if (shift == 0)
+                break;
             __syncthreads();
         }
     } else {
         need = n;   // take everything; every key is >= 0
+    }
+    if (few > 0) {                        // entries of keys >= prefix
+        unsigned long long *const all = (unsigned long long *)hist;
+        float *const value = (float *)(all + kRankMost);
+        int *const place = (int *)(value + kRankMost);
+        int at = w_begin;
+        if (n > kRankAll) {
+            int mine = 0;
+#pragma unroll
+            for (int u = 0; u < kTopkUnroll; ++u)
+                mine += __popcll(__builtin_amdgcn_ballot_w64(w_begin + u * 64 + lane < w_end && key[u] >= prefix));
+            if (mine && lane == 0)
+                at = atomicAdd(&sel[3], mine);
+            at = __builtin_amdgcn_readfirstlane(at);
+        }
+        const unsigned long long below = (1ull << lane) - 1ull;
+#pragma unroll
+        for (int u = 0; u < kTopkUnroll; ++u) {
+            const int i = w_begin + u * 64 + lane;
+            const bool take = i < w_end && key[u] >= prefix;
+            const unsigned long long who = __builtin_amdgcn_ballot_w64(take);
+            if (take) {
+                const int c = at + __popcll(who & below);
+                all[c] = ((unsigned long long)key[u] << 32) | (unsigned long long)(0xFFFFFFFFu - (idx0 + (uint32_t)i));
+                value[c] = v[u];
+                place[c] = 0;
+            }
+            at += __popcll(who);
+        }
+        if (tid == 0 && (few & 1))
+            all[few] = 0ull;              // (few < kRankMost then)
+        __syncthreads();
+        // 64 entries to a wavefront, and some of what each is compared with
+        const int groups = (few + 63) >> 6, parts = kTopkWaves / groups, part = wave / groups;
+        const int e = (wave - part * groups) * 64 + lane;
+        if (part < parts) {
+            const int per = ((few + parts - 1) / parts + 1) & ~1;
+            const int end = min(part * per + per, few);
+            const unsigned long long me = all[min(e, few - 1)];
+            int above = 0;
+#pragma unroll 8
+            for (int j = part * per; j < end; j += 2) {
+                const ulonglong2 o = *(const ulonglong2 *)&all[j];
+                above += o.x > me ? 1 : 0;
+                above += o.y > me ? 1 : 0;
+            }
+            if (e < few && above)
+                atomicAdd(&place[e], above);
+        }
+        __syncthreads();
+        if (tid < few && place[tid] < kk) {
+            const int j = place[tid];
+            if (d.comp_out) {
+                d.comp_out[j] = all[tid];
+            } else {
+                d.out_idx[j] = (int32_t)(0xFFFFFFFFu - (uint32_t)all[tid]);
+                if (d.out_score)
+                    d.out_score[j] = value[tid];
+            }
+        }
+        return;
     }
     const uint32_t tau = prefix;
     const int need_eq = need;
@@ -166,7 +264,7 @@ topk_kernel(const TopkDesc *__restrict__ far, NearTopk)
     int my_gt = 0, my_eq = 0;
     for (int base = w_begin; base < w_end; base += 64 * kTopkUnroll) {
         if (!cached)
-            load_keys(score, base, w_end, lane, key);
+            load_keys(score, base, w_end, lane, key, v);
 #pragma unroll
         for (int u = 0; u < kTopkUnroll; ++u) {
             const bool valid = base + u * 64 + lane < w_end;
@@ -187,7 +285,7 @@ topk_kernel(const TopkDesc *__restrict__ far, NearTopk)
     const unsigned long long below = (1ull << lane) - 1ull;
     for (int base = w_begin; base < w_end; base += 64 * kTopkUnroll) {
         if (!cached)
-            load_keys(score, base, w_end, lane, key);
+            load_keys(score, base, w_end, lane, key, v);
 #pragma unroll
         for (int u = 0; u < kTopkUnroll; ++u) {
             const int i = base + u * 64 + lane;
@@ -393,7 +491,7 @@ int launch_topk(const Descs<TopkDesc> &descs, int max_k, hipStream_t stream)
     int kpow2 = 2;
     while (kpow2 < max_k)
         kpow2 <<= 1;
-    const size_t lds = (size_t)kpow2 * 8 + (256 + 2 * (kTopkThreads / 64) + 2) * sizeof(int);
+    const size_t lds = (size_t)kpow2 * 8 + (kBinsOf + 2 * kTopkWaves + 4) * sizeof(int);
     static size_t configured[16] = {0};
     int dev = 0;
     FS_HIP(hipGetDevice(&dev));

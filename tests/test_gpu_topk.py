@@ -1,0 +1,36 @@
+"""Cuts at the sizes where their kernels change over, on scores with ties, zeros of both signs, infinities and NaN."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+SCORES = {
+    "random": lambda g, n: g.standard_normal(n),
+    "equal": lambda g, n: np.full(n, -0.25),
+    "few values": lambda g, n: g.integers(0, 5, n) / 4 - 0.5,
+    "close": lambda g, n: 1.0 + g.integers(0, 3000, n) * 2.0 ** -23,          # the first pass of the select tells none apart
+    "special": lambda g, n: g.choice([0.0, -0.0, np.inf, -np.inf, np.nan, 1e-45, -1e-45, 1.0], n),
+}
+
+
+@pytest.fixture(scope="module")
+def api():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    from paper_2201_00194_amd import api as A
+    return A
+
+
+@pytest.mark.parametrize("kind", SCORES)
+@pytest.mark.parametrize("n,k", [(1, 1), (63, 64), (255, 255), (256, 16), (257, 1), (257, 256), (321, 320), (321, 321),
+                                 (1025, 320), (1025, 456), (513, 512), (600, 513), (4096, 64), (8191, 321), (8192, 64), (9001, 2000), (200_000, 64)])
+def test_cut(api, oracle, kind, n, k):
+    import torch
+    score = SCORES[kind](np.random.default_rng([n, k]), n).astype(np.float32)
+    d = torch.from_numpy(score).cuda()
+    idx = torch.zeros(k, dtype=torch.int32, device="cuda")
+    best = torch.zeros(k, dtype=torch.float32, device="cuda")
+    api.fs_topk([api.TopkRequest(d, n, k, idx, best)])
+    e_idx, e_best = oracle.topk(score, k)
+    assert np.array_equal(idx.cpu().numpy(), e_idx)
+    assert np.array_equal(best.cpu().numpy().view(np.uint32), e_best.view(np.uint32))
