@@ -12,8 +12,8 @@
 //      that key and the ties in its slice, the counts are scanned, and a second sweep places
 //      every entry above the key plus the lowest-index ties as 64-bit composites
 //      (key, ~index) in LDS;
-//   3. a bitonic sort of the composites gives the final order; all composites differ, so
-//      the result is unique.
+//   3. the composites are sorted: runs of 64 by counting, then merges of two runs in which each
+//      entry finds its place by bisection; all composites differ, so the result is unique.
 // A long request (>= 8192 entries) is cut into up to 16 slices, one workgroup each, which
 // leave their best k composites in scratch, best first; a second kernel merges the slices'
 // lists pairwise in LDS, keeping the best k of every pair, and writes the answer.  The union
@@ -98,6 +98,102 @@ __device__ __forceinline__ void find_digit(const int *hist, int need, int lane, 
         sel[0] = digit;
         sel[1] = rest - (upto - count);
         sel[2] = count;
+    }
+}
+
+// Merges the runs of LEN entries of c[0 .. n) pairwise, then those of 2 * LEN and so on (n a power of two, at most
+// E * kTopkThreads; all entries differ).  An entry's place is its own in its run and that among the other run's
+// entries, by bisection; a thread holds its entries in registers meanwhile.  Bound by instruction issue: four a probe.
+template <int LEN, int E>
+__device__ __forceinline__ void merge_runs(unsigned long long *c, int n, int tid)
+{
+    if constexpr (LEN < E * kTopkThreads) {
+        if (LEN >= n)
+            return;
+        unsigned long long me[E];
+        const unsigned long long *sib[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int at = tid + e * kTopkThreads;
+            me[e] = c[at < n ? at : 0];
+            sib[e] = c + (at < n ? (at & ~(LEN - 1)) ^ LEN : 0);
+        }
+#pragma unroll
+        for (int step = LEN / 2; step > 0; step >>= 1) {
+            unsigned long long o[E];
+#pragma unroll
+            for (int e = 0; e < E; ++e)
+                o[e] = sib[e][step - 1];
+#pragma unroll
+            for (int e = 0; e < E; ++e)
+                sib[e] += o[e] > me[e] ? step : 0;
+        }
+        int to[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int at = tid + e * kTopkThreads;
+            const int above = (int)(sib[e] - c) - ((at & ~(LEN - 1)) ^ LEN) + (sib[e][0] > me[e] ? 1 : 0);
+            to[e] = (at & ~(2 * LEN - 1)) + (at & (LEN - 1)) + above;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+            if (tid + e * kTopkThreads < n)
+                c[to[e]] = me[e];
+        __syncthreads();
+        merge_runs<2 * LEN, E>(c, n, tid);
+    }
+}
+
+// Sorts c[0 .. n), largest first (n a power of two from 64 on, at most E * kTopkThreads; all entries differ).
+// A bitonic sort has 66 rounds with a barrier each for 2048 entries: the whole cut 25.1 us, so 12.3; of 4000 of 8000
+// entries 47 and 25, of 8000 78 and 37.
+template <int E>
+__device__ __forceinline__ void sort_descending(unsigned long long *c, int n, int tid)
+{
+    unsigned long long me[E];
+    int to[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {                    // runs of 64, by counting
+        const int at = tid + e * kTopkThreads, run = at < n ? at & ~63 : 0;
+        me[e] = c[at < n ? at : 0];
+        to[e] = run;
+#pragma unroll 8
+        for (int j = 0; j < 64; j += 2) {
+            const ulonglong2 o = *(const ulonglong2 *)&c[run + j];
+            to[e] += o.x > me[e] ? 1 : 0;
+            to[e] += o.y > me[e] ? 1 : 0;
+        }
+    }
+    // (a run is one wavefront's: nobody else reads or writes it)
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+        if (tid + e * kTopkThreads < n)
+            c[to[e]] = me[e];
+    __syncthreads();
+    merge_runs<64, E>(c, n, tid);
+}
+
+// The same for 16384 entries: sixteen a thread would not fit its registers.
+__device__ __forceinline__ void sort_bitonic(unsigned long long *c, int n, int tid)
+{
+    for (int size = 2; size <= n; size <<= 1) {
+        for (int stride = size >> 1; stride > 0; stride >>= 1) {
+            for (int t = tid; t < (n >> 1); t += kTopkThreads) {
+                const int lo = ((t & ~(stride - 1)) << 1) | (t & (stride - 1));
+                const int hi = lo | stride;
+                const bool desc = (lo & size) == 0;
+                const unsigned long long a = c[lo], b = c[hi];
+                if ((a < b) == desc) {
+                    c[lo] = b;
+                    c[hi] = a;
+                }
+            }
+            __syncthreads();
+        }
     }
 }
 
@@ -259,10 +355,12 @@ topk_kernel(const TopkDesc *__restrict__ far, NearTopk)
     }
     const uint32_t tau = prefix;
     const int need_eq = need;
+    const bool all = kk == n;
+    const int sorted = max(kpow2, 64);                      // (room: the histogram is done with)
 
     // ---- 2. collect, in index order: count per wavefront, scan, then place ----
     int my_gt = 0, my_eq = 0;
-    for (int base = w_begin; base < w_end; base += 64 * kTopkUnroll) {
+    for (int base = w_begin; base < w_end && !all; base += 64 * kTopkUnroll) {
         if (!cached)
             load_keys(score, base, w_end, lane, key, v);
 #pragma unroll
@@ -277,8 +375,8 @@ topk_kernel(const TopkDesc *__restrict__ far, NearTopk)
         wave_cnt[kTopkWaves + wave] = my_eq;
     }
     __syncthreads();
-    int gt_before = 0, eq_before = 0;
-    for (int w = 0; w < wave; ++w) {
+    int gt_before = all ? w_begin : 0, eq_before = 0;
+    for (int w = 0; w < wave && !all; ++w) {
         gt_before += wave_cnt[w];
         eq_before += wave_cnt[kTopkWaves + w];
     }
@@ -290,7 +388,7 @@ topk_kernel(const TopkDesc *__restrict__ far, NearTopk)
         for (int u = 0; u < kTopkUnroll; ++u) {
             const int i = base + u * 64 + lane;
             const bool valid = i < w_end;
-            const bool gt = valid && key[u] > tau, eq = valid && key[u] == tau;
+            const bool gt = valid && (all || key[u] > tau), eq = valid && !gt && key[u] == tau;
             const unsigned long long bg = __ballot(gt), be = __ballot(eq);
             const unsigned long long comp =
                 ((unsigned long long)key[u] << 32) |
@@ -306,26 +404,20 @@ topk_kernel(const TopkDesc *__restrict__ far, NearTopk)
             eq_before += __popcll(be);
         }
     }
-    for (int j = kk + tid; j < kpow2; j += kTopkThreads)
-        cand[j] = 0ull;                                     // below every real composite
+    // ---- 3. sort, descending ----
+    for (int j = kk + tid; j < sorted; j += kTopkThreads)
+        cand[j] = (unsigned long long)(sorted - j);         // below every real composite, and different
     __syncthreads();
-
-    // ---- 3. bitonic sort, descending ----
-    for (int size = 2; size <= kpow2; size <<= 1) {
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            for (int t = tid; t < (kpow2 >> 1); t += kTopkThreads) {
-                const int lo = ((t & ~(stride - 1)) << 1) | (t & (stride - 1));
-                const int hi = lo | stride;
-                const bool desc = (lo & size) == 0;
-                const unsigned long long a = cand[lo], b = cand[hi];
-                if ((a < b) == desc) {
-                    cand[lo] = b;
-                    cand[hi] = a;
-                }
-            }
-            __syncthreads();
-        }
-    }
+    if (sorted <= kTopkThreads)
+        sort_descending<1>(cand, sorted, tid);
+    else if (sorted <= 2 * kTopkThreads)
+        sort_descending<2>(cand, sorted, tid);
+    else if (sorted <= 4 * kTopkThreads)
+        sort_descending<4>(cand, sorted, tid);
+    else if (sorted <= 8 * kTopkThreads)
+        sort_descending<8>(cand, sorted, tid);
+    else
+        sort_bitonic(cand, sorted, tid);
     if (d.comp_out) {
         for (int j = tid; j < kk; j += kTopkThreads)
             d.comp_out[j] = cand[j];
