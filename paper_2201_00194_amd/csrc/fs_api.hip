@@ -773,8 +773,11 @@ extern "C" int fs_score_families(int32_t n_families, const fs_family *fams, void
 }
 
 // ---- top-k -------------------------------------------------------------------------------------
+// Merges of a level of a mode-2 request: groups of kTopkWays lists, a last list by itself needs none.
+static int topk_joins(int lists) { return lists / kTopkWays + (lists % kTopkWays > 1 ? 1 : 0); }
+
 struct TopkSizes {
-    size_t n_blocks = 0, n_merge = 0, comp_total = 0, n_pairs_total = 0;
+    size_t n_blocks = 0, n_merge = 0, comp_total = 0, n_joins_total = 0;
     int max_comp = 0, n_levels = 0, max_k = 0;
 };
 
@@ -815,11 +818,11 @@ static int topk_sizes(const char *who, int32_t n_requests, const fs_topk_req *re
             z.comp_total += every < capped ? every : capped;
             int lists = p.s, levels = 0;
             while (lists > 1) {
-                const int pairs = lists / 2;
-                z.n_pairs_total += (size_t)pairs;
-                if (lists > 2)
-                    z.comp_total += (size_t)pairs * (size_t)r.k;   // merged lists (the last level writes the answer)
-                lists = pairs + (lists & 1);
+                const int joins = topk_joins(lists);
+                z.n_joins_total += (size_t)joins;
+                if (lists > kTopkWays)
+                    z.comp_total += (size_t)joins * (size_t)r.k;   // merged lists (the last level writes the answer)
+                lists = (lists + kTopkWays - 1) / kTopkWays;
                 ++levels;
             }
             if (levels > z.n_levels)
@@ -868,7 +871,7 @@ extern "C" int fs_topk(int32_t n_requests, const fs_topk_req *reqs, void *stream
     auto plan_of = [](const fs_topk_req &r) { return topk_plan(r.n, r.k); };
     typedef TopkPlan Plan;
     const size_t n_blocks = z.n_blocks, n_merge = z.n_merge, comp_total = z.comp_total,
-                 n_pairs_total = z.n_pairs_total;
+                 n_joins_total = z.n_joins_total;
     const int max_comp = z.max_comp, n_levels = z.n_levels;
     if (comp_total) {
         rc = ensure_scratch(ctx, kScratchTopk, comp_total * 2);
@@ -878,31 +881,31 @@ extern "C" int fs_topk(int32_t n_requests, const fs_topk_req *reqs, void *stream
     const size_t desc_bytes = sizeof(TopkDesc) * n_blocks;
     const size_t merge_off = (desc_bytes + 15) & ~(size_t)15;
     const size_t path_off = (merge_off + sizeof(TopkMergeDesc) * n_merge + 15) & ~(size_t)15;
-    const size_t total_bytes = path_off + sizeof(TopkPairDesc) * n_pairs_total;
+    const size_t total_bytes = path_off + sizeof(TopkJoinDesc) * n_joins_total;
     DescBuf db;
     rc = acquire_desc(ctx, kDescTopk, total_bytes, &db);
     if (rc != FS_OK)
         return rc;
     TopkDesc *h = (TopkDesc *)db.host;
     TopkMergeDesc *hm = (TopkMergeDesc *)((char *)db.host + merge_off);
-    TopkPairDesc *hp = (TopkPairDesc *)((char *)db.host + path_off);
+    TopkJoinDesc *hj = (TopkJoinDesc *)((char *)db.host + path_off);
     unsigned long long *comp = (unsigned long long *)ctx->scratch[kScratchTopk];
-    // merge-path descriptors are stored level by level: first count the pairs of every level
+    // merge-path descriptors are stored level by level: first count the merges of every level
     constexpr int kMaxLevels = 8;
-    size_t level_pairs[kMaxLevels] = {0}, level_at[kMaxLevels] = {0};
-    int level_entries[kMaxLevels] = {0};        // longest la + lb of the level: sizes its grid
+    size_t level_joins[kMaxLevels] = {0}, level_at[kMaxLevels] = {0};
+    int level_entries[kMaxLevels] = {0};        // most entries of a merge of the level: sizes its grid
     for (int i = 0; i < n_requests; ++i) {
         const Plan p = plan_of(reqs[i]);
         if (p.mode != 2)
             continue;
         int lists = p.s, lv = 0;
         while (lists > 1) {
-            level_pairs[lv++] += (size_t)(lists / 2);
-            lists = lists / 2 + (lists & 1);
+            level_joins[lv++] += (size_t)topk_joins(lists);
+            lists = (lists + kTopkWays - 1) / kTopkWays;
         }
     }
     for (int lv = 1; lv < kMaxLevels; ++lv)
-        level_at[lv] = level_at[lv - 1] + level_pairs[lv - 1];
+        level_at[lv] = level_at[lv - 1] + level_joins[lv - 1];
     size_t level_fill[kMaxLevels];
     for (int lv = 0; lv < kMaxLevels; ++lv)
         level_fill[lv] = level_at[lv];
@@ -951,22 +954,30 @@ extern "C" int fs_topk(int32_t n_requests, const fs_topk_req *reqs, void *stream
         } else if (p.mode == 2) {
             int lists = p.s, lv = 0;
             while (lists > 1) {
-                const int pairs = lists / 2;
-                for (int q = 0; q < pairs; ++q) {
-                    TopkPairDesc &t = hp[level_fill[lv]++];
-                    t.a = list_ptr[2 * q];
-                    t.b = list_ptr[2 * q + 1];
-                    t.la = list_len[2 * q];
-                    t.lb = list_len[2 * q + 1];
-                    const long long both = (long long)t.la + t.lb;
-                    if (both > level_entries[lv])
-                        level_entries[lv] = (int)both;
-                    t.lo = (int32_t)(both < r.k ? both : r.k);
+                const int joins = topk_joins(lists);
+                for (int q = 0; q < joins; ++q) {
+                    TopkJoinDesc &t = hj[level_fill[lv]++];
+                    int all = 0;
+                    t.longest = 0;
+                    t.n = lists - kTopkWays * q < kTopkWays ? lists - kTopkWays * q : kTopkWays;
+                    for (int w = 0; w < kTopkWays; ++w) {
+                        const int l = kTopkWays * q + w;
+                        t.list[w] = list_ptr[l < lists ? l : kTopkWays * q];
+                        t.len[w] = l < lists ? list_len[l] : 0;
+                        if (t.len[w] == 0)
+                            t.list[w] = first;                // (readable)
+                        if (t.len[w] > t.longest)
+                            t.longest = t.len[w];
+                        all += t.len[w];
+                    }
+                    if (all > level_entries[lv])
+                        level_entries[lv] = all;
+                    t.lo = all < r.k ? all : r.k;
                     t.k = r.k;
                     t.score = r.score;
                     t.out_idx = r.out_idx;
                     t.out_score = r.out_score;
-                    if (lists == 2) {
+                    if (lists <= kTopkWays) {
                         t.out = nullptr;                      // last level: the answer itself
                     } else {
                         t.out = comp;
@@ -975,18 +986,18 @@ extern "C" int fs_topk(int32_t n_requests, const fs_topk_req *reqs, void *stream
                     list_ptr[q] = t.out;
                     list_len[q] = t.lo;
                 }
-                if (lists & 1) {                              // odd one out moves up as it is
-                    list_ptr[pairs] = list_ptr[lists - 1];
-                    list_len[pairs] = list_len[lists - 1];
+                if (lists % kTopkWays == 1) {                 // odd one out moves up as it is
+                    list_ptr[joins] = list_ptr[lists - 1];
+                    list_len[joins] = list_len[lists - 1];
                 }
-                lists = pairs + (lists & 1);
+                lists = (lists + kTopkWays - 1) / kTopkWays;
                 ++lv;
             }
         }
     }
     if ((size_t)(comp - (unsigned long long *)ctx->scratch[kScratchTopk]) > comp_total || b != n_blocks || m != n_merge)
         return fail(FS_EDEVICE, "fs_topk: internal plan mismatch");
-    const bool near = n_blocks <= kNearTopk && n_merge <= kNearMerge && level_pairs[0] <= kNearPairs;
+    const bool near = n_blocks <= kNearTopk && n_merge <= kNearMerge && level_joins[0] <= kNearJoins;
     if (!near) {
         rc = commit_desc(db, total_bytes, stream);
         if (rc != FS_OK)
@@ -999,8 +1010,8 @@ extern "C" int fs_topk(int32_t n_requests, const fs_topk_req *reqs, void *stream
         rc = launch_topk_merge({near ? nullptr : (const TopkMergeDesc *)(dev + merge_off), hm, (int)n_merge},
                                max_comp, stream);
     for (int lv = 0; lv < n_levels && rc == FS_OK; ++lv)
-        rc = launch_topk_pairs({near ? nullptr : (const TopkPairDesc *)(dev + path_off) + level_at[lv], hp + level_at[lv],
-                                (int)level_pairs[lv]}, level_entries[lv], stream);
+        rc = launch_topk_joins({near ? nullptr : (const TopkJoinDesc *)(dev + path_off) + level_at[lv], hj + level_at[lv],
+                                (int)level_joins[lv]}, level_entries[lv], stream);
     prof_stop(stream);
     const int rc2 = finish_desc(db, stream);
     return rc != FS_OK ? rc : rc2;

@@ -268,16 +268,18 @@ struct TopkMergeDesc {
 };
 
 
-// One merge of two lists of composites (each best first) in global memory: the best `lo` of
+// One merge of up to kTopkWays lists of composites (each best first) in global memory: the best `lo` of
 // their union go to `out` (composites), or, at the last level of a request, to its
 // out_idx / out_score (then `lo` = min(n, k) and entries up to k are padded with -1 / -inf).
-struct TopkPairDesc {
-    const unsigned long long *a, *b;
+constexpr int kTopkWays = 8;
+struct TopkJoinDesc {
+    const unsigned long long *list[kTopkWays];   // readable also where `len` is 0
     unsigned long long *out;       // NULL at the last level
     const float *score;
     int32_t *out_idx;
     float *out_score;              // may be NULL
-    int32_t la, lb, lo, k;
+    int32_t len[kTopkWays];
+    int32_t n, longest, lo, k;     // lists, entries of the longest
 };
 
 // u16 rank tiles keep the features of a row in pairs: features 2i and 2i+1 of row l share the
@@ -287,15 +289,15 @@ struct TopkPairDesc {
 __host__ __device__ inline int rank_tile_cols(int n_features) { return (n_features + 1) & ~1; }
 __host__ __device__ inline uint32_t rank_feature_offset(int f) { return (uint32_t)(f >> 1) * 256u + (uint32_t)(f & 1) * 2u; }
 
-constexpr int kNearTopk = 48, kNearMerge = 48, kNearPairs = 32;
+constexpr int kNearTopk = 48, kNearMerge = 48, kNearJoins = 16;
 struct NearTopk {
     TopkDesc d[kNearTopk];
 };
 struct NearMerge {
     TopkMergeDesc d[kNearMerge];
 };
-struct NearPairs {
-    TopkPairDesc d[kNearPairs];
+struct NearJoins {
+    TopkJoinDesc d[kNearJoins];
 };
 
 // ---- launchers (each returns FS_OK or records an error) ---------------------------------------
@@ -338,7 +340,7 @@ constexpr int kTopkWideMaxSlices = 128;
 //   mode 1  long request, k <= 4096: `s` slices of `per` entries (one workgroup each) leave their
 //           best k in scratch and one workgroup merges them in LDS;
 //   mode 2  long request with a wider cut: slices of about kTopkWideSlice entries leave their best
-//           min(k, length) sorted, then pairwise merges in global memory, level by level.
+//           min(k, length) sorted, then merges of kTopkWays lists in global memory, level by level.
 struct TopkPlan { int mode, s, per; };
 inline TopkPlan topk_plan(int n, int k)
 {
@@ -371,7 +373,7 @@ inline TopkPlan topk_plan(int n, int k)
     }
     return p;
 }
-int launch_topk_pairs(const Descs<TopkPairDesc> &descs, int max_entries, hipStream_t stream);
+int launch_topk_joins(const Descs<TopkJoinDesc> &descs, int max_entries, hipStream_t stream);
 int launch_retile(const FamDesc *d_desc, int n_families, int total_blocks, hipStream_t stream);
 int launch_pack_colblock64(const float *in, int64_t n_rows, int32_t n_features, float *out,
                            hipStream_t stream);

@@ -20,7 +20,7 @@
 // of the slices' best k holds the request's best k, and composites order the same way
 // everywhere, so nothing changes in the result.  Cuts wider than 4096 do not fit that merge:
 // they are cut into slices of about 2048 entries (up to 128) whose sorted lists are merged
-// pairwise in global memory, level by level, each merge keeping the best k.
+// eight at a time in global memory, level by level, each merge keeping the best k.
 #include <cstring>
 #include <mutex>
 
@@ -493,47 +493,76 @@ topk_merge_kernel(const TopkMergeDesc *__restrict__ far, NearMerge)
     }
 }
 
-// Merge of two descending lists of composites that live in global memory, for cuts too wide
+// Merge of up to kTopkWays descending lists of composites that live in global memory, for cuts too wide
 // for the LDS merge.  All composites differ, so an entry's place in the merged list is its own
-// position plus the number of entries of the other list that exceed it: one thread per entry
-// finds that count by bisection and stores the entry if its place is among the best `lo`.
-// blockIdx.y names the pair, blockIdx.x a run of kTopkThreads entries of (a then b).
-__global__ void __launch_bounds__(kTopkThreads)
-topk_pair_kernel(const TopkPairDesc *__restrict__ far, NearPairs)
+// position plus the number of entries of the other lists that exceed it: one thread per entry
+// finds these counts by bisection, side by side, and stores the entry if its place is among the best `lo`.
+// blockIdx.y names the merge, blockIdx.x a run of kJoinThreads entries of its lists, one after the other.
+// A chain of 12 to 16 loads from the L2 beside a launch's start and end, and bound by the lines that a compute unit's
+// loads touch where its workgroup is large.  32 lists of 2048 entries, cut of 16384: 26.1 us two at a time, five
+// launches of 1024 threads a workgroup; 18.2 four at a time with 256 (26.0 with 1024); 13.8 so.
+constexpr int kJoinThreads = 256;
+
+// Entries of the first W lists above v, of which `me` entries of list `mine` are known.
+template <int W>
+__device__ __forceinline__ int entries_above(const TopkJoinDesc &d, unsigned long long v, int mine, int me)
 {
-    const TopkPairDesc d = where_descs(far, sizeof(far))[blockIdx.y];
-    const int e = blockIdx.x * kTopkThreads + threadIdx.x;
-    if (e < d.la + d.lb) {
-        const bool in_a = e < d.la;
-        const unsigned long long *__restrict__ self = in_a ? d.a : d.b;
-        const unsigned long long *__restrict__ other = in_a ? d.b : d.a;
-        const int me = in_a ? e : e - d.la;
-        if (me < d.lo) {
-            const unsigned long long v = self[me];
-            // entries of `other` above v, counted no further than would push v out of the cut
-            int lo = 0, hi = min(in_a ? d.lb : d.la, d.lo - me);
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (other[mid] > v)
-                    lo = mid + 1;
-                else
-                    hi = mid;
-            }
-            const int p = me + lo;
-            if (p < d.lo) {
-                if (d.out) {
-                    d.out[p] = v;
-                } else {
-                    const uint32_t idx = 0xFFFFFFFFu - (uint32_t)(v & 0xFFFFFFFFull);
-                    d.out_idx[p] = (int32_t)idx;
-                    if (d.out_score)
-                        d.out_score[p] = d.score[idx];
-                }
+    int above[W], most[W], top = 1;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {                        // counted no further than would push v out of the cut
+        above[w] = 0;
+        most[w] = w == mine ? 0 : min(d.len[w], d.lo - me);
+    }
+    while (2 * top <= d.longest)
+        top <<= 1;
+    for (int step = top; step > 0; step >>= 1) {
+        unsigned long long o[W];
+#pragma unroll
+        for (int w = 0; w < W; ++w)
+            o[w] = d.list[w][max(min(above[w] + step, most[w]), 1) - 1];
+#pragma unroll
+        for (int w = 0; w < W; ++w)
+            above[w] += above[w] + step <= most[w] && o[w] > v ? step : 0;
+    }
+    int all = me;
+#pragma unroll
+    for (int w = 0; w < W; ++w)
+        all += above[w];
+    return all;
+}
+
+__global__ void __launch_bounds__(kJoinThreads)
+topk_join_kernel(const TopkJoinDesc *__restrict__ far, NearJoins)
+{
+    const TopkJoinDesc d = where_descs(far, sizeof(far))[blockIdx.y];
+    int me = blockIdx.x * kJoinThreads + threadIdx.x, mine = -1;
+    const unsigned long long *self = nullptr;
+#pragma unroll
+    for (int w = 0; w < kTopkWays; ++w) {
+        if (mine < 0 && me < d.len[w]) {
+            mine = w;
+            self = d.list[w];
+        }
+        me -= mine < 0 ? d.len[w] : 0;
+    }
+    if (mine >= 0 && me < d.lo) {
+        const unsigned long long v = self[me];
+        const int p = d.n <= 2   ? entries_above<2>(d, v, mine, me)
+                      : d.n <= 4 ? entries_above<4>(d, v, mine, me)
+                                 : entries_above<kTopkWays>(d, v, mine, me);
+        if (p < d.lo) {
+            if (d.out) {
+                d.out[p] = v;
+            } else {
+                const uint32_t idx = 0xFFFFFFFFu - (uint32_t)(v & 0xFFFFFFFFull);
+                d.out_idx[p] = (int32_t)idx;
+                if (d.out_score)
+                    d.out_score[p] = d.score[idx];
             }
         }
     }
     if (!d.out && blockIdx.x == 0) {
-        for (int p = d.lo + threadIdx.x; p < d.k; p += kTopkThreads) {
+        for (int p = d.lo + threadIdx.x; p < d.k; p += kJoinThreads) {
             d.out_idx[p] = -1;
             if (d.out_score)
                 d.out_score[p] = -__builtin_inff();
@@ -541,18 +570,18 @@ topk_pair_kernel(const TopkPairDesc *__restrict__ far, NearPairs)
     }
 }
 
-int launch_topk_pairs(const Descs<TopkPairDesc> &descs, int max_entries, hipStream_t stream)
+int launch_topk_joins(const Descs<TopkJoinDesc> &descs, int max_entries, hipStream_t stream)
 {
-    const int runs = max_entries > 0 ? (max_entries + kTopkThreads - 1) / kTopkThreads : 1;
-    constexpr int kMaxY = 32768;             // pairs per launch (grid.y)
-    const NearPairs near = near_descs<NearPairs>(descs);
+    const int runs = max_entries > 0 ? (max_entries + kJoinThreads - 1) / kJoinThreads : 1;
+    constexpr int kMaxY = 32768;             // merges per launch (grid.y)
+    const NearJoins near = near_descs<NearJoins>(descs);
     for (int at = 0; at < descs.n; at += kMaxY) {
         const int cnt = descs.n - at < kMaxY ? descs.n - at : kMaxY;
-        hipLaunchKernelGGL(topk_pair_kernel, dim3(runs, cnt), dim3(kTopkThreads), 0, stream,
+        hipLaunchKernelGGL(topk_join_kernel, dim3(runs, cnt), dim3(kJoinThreads), 0, stream,
                            descs.far ? descs.far + at : nullptr, near);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess)
-            return fail_hip(e, "topk_pair_kernel launch");
+            return fail_hip(e, "topk_join_kernel launch");
     }
     return FS_OK;
 }

@@ -25,7 +25,7 @@ def api():
 @pytest.mark.parametrize("n,k", [(1, 1), (63, 64), (255, 255), (256, 16), (257, 1), (257, 256), (321, 320), (321, 321),
                                  (1025, 320), (1025, 456), (513, 512), (600, 513), (4096, 64), (8191, 321), (8192, 64), (9001, 2000), (200_000, 64), (1024, 1024), (1500, 1025),
                                  (2048, 2048), (3000, 2500), (4097, 4096), (8191, 8191), (8000, 4097), (20_000, 16_384),
-                                 (1_100_000, 16_384)])
+                                 (1_100_000, 16_384), (8200, 5000), (18_000, 6000), (34_000, 5000), (262_200, 4097)])
 def test_cut(api, oracle, kind, n, k):
     import torch
     score = SCORES[kind](np.random.default_rng([n, k]), n).astype(np.float32)
