@@ -120,6 +120,26 @@ def test_gather_with_very_uneven_program_lengths(api, oracle, order):
     assert np.array_equal(got.view(np.uint32), ex.view(np.uint32))
 
 
+@pytest.mark.parametrize("at", [0, 1, 3])
+@pytest.mark.parametrize("n_keep", [1, 3, 15, 16, 17, 1023, 1024, 16_383, 16_384])
+def test_offsets_of_any_count_at_any_place(api, n_keep, at):
+    """out_prog_off is read and written four entries at a time and need not be aligned for that."""
+    import torch
+    fam = W.make_small_family(seed=76, n_programs=90, stmts=(0, 9), n_trees=1, depth=1, k=1)
+    dev = api.upload_case(W.Case("one", 0, [fam]))[0]
+    lens = np.diff(fam.prog_off)
+    keep = np.random.default_rng(n_keep).integers(-1, 90, n_keep).astype(np.int32)
+    off = torch.full((at + n_keep + 5,), -9, dtype=torch.int32, device="cuda")
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    exp = np.concatenate(([0], np.cumsum(np.where(keep < 0, 0, lens[keep]))))
+    out_x = torch.zeros((int(exp[-1]) + 63) // 64 * 164 * 64 + 1, dtype=torch.float32, device="cuda")
+    api.fs_gather_programs(164, [(dev.features, dev.prog_off, None, 90)], torch.from_numpy(keep).cuda(), n_keep, out_x,
+                           int(exp[-1]), off[at:at + n_keep + 1], None, status)
+    got = off.cpu().numpy()
+    assert int(status.item()) == 0 and np.array_equal(got[at:at + n_keep + 1], exp)
+    assert np.all(got[:at] == -9) and np.all(got[at + n_keep + 1:] == -9)
+
+
 def test_generations_with_a_resident_population_match_rescoring_everything(api, oracle):
     """Three generations of: score only the new candidates, cut (old scores + new scores) to the
     population size, gather the survivors from (population, new) into the next population --
