@@ -120,10 +120,11 @@ struct fs_model {
     int32_t rk_tiles;          // 64-row tiles per workgroup
     int32_t rk_slots;          // wavefronts of a tile that have trees
     int32_t rk_trees_per_slot;
-    int32_t rk_tree_bytes;     // 4 * 2^(depth+1): heap words 1 .. 2^(depth+1)-1, word 0 unused
+    int32_t rk_tree_bytes;     // of a tree in LDS: heap words 1 .. 2^depth - 1, word 0 unused, and the leaves if they are
+                               // held there (then 8 << depth, else 4 << depth)
     int32_t rk_tile0;          // LDS byte offset of the first (u16) feature tile
-    uint32_t *d_rk_nodes;      // [n_trees][2^(depth+1)] 1-based heap order: splits then leaf values
-    uint16_t *d_rk_ids;        // same shape: caller's local node id
+    uint32_t *d_rk_nodes;      // [n_trees][rk_tree_bytes], then, if they are not held, [n_trees][2^depth] leaf values
+    uint16_t *d_rk_ids;        // [n_trees][2^(depth+1)] 1-based heap order: caller's local node id
     float *d_cuts;             // [n_features][2^cut_bits]: the feature's sorted distinct
                                // thresholds, NaN-padded, as a breadth-first search tree
     int32_t cut_bits;

@@ -460,8 +460,9 @@ void write_lds(const LdsPlan &plan, int n_features, const int32_t *tree_off, con
 }
 
 // Rank-coded image of a model of perfect trees of one depth (see fs_rank.hip): per feature the
-// sorted distinct thresholds; per tree 2^(depth+1) words, word i = heap node i (1-based),
-// splits as rank << 16 | offset of the feature in a rank tile, leaves as value bits; plus the caller's node id per word.
+// sorted distinct thresholds; per tree the splits, word i = heap node i (1-based) as
+// rank << 16 | offset of the feature in a rank tile, then its leaf values or, if they are not held in LDS, behind
+// the splits of all trees 2^depth of each; plus the caller's node id per heap node.
 void build_rank_format(fs_model *m, int n_features, int n_trees, int depth, const int32_t *tree_off,
                        const int32_t *sf, const float *thr, const int32_t *left,
                        const int32_t *right, const float *val, std::vector<uint32_t> *nodes,
@@ -500,16 +501,55 @@ void build_rank_format(fs_model *m, int n_features, int n_trees, int depth, cons
             }
     }
 
-    const size_t words = (size_t)2 << depth;              // per tree, word 0 unused
-    nodes->assign(words * (size_t)n_trees, 0u);
+    // tiles per workgroup (must divide the wavefront count): most walks side by side, up to eight trees a slot; of
+    // equals the most tiles, as every workgroup reads the whole model.  Leaf values are held in LDS only where that
+    // leaves room for the most walks on the most tiles: 164 features, 500 trees of depth 8 2.19 ms held and 2.40 not
+    // (1.6 M rows), of depth 9 0.86 and 0.79 (0.5 M), of depth 10 4.50 and 3.92 (2.1 M), 200 of depth 11 0.41 and 0.27.
+    const size_t tile_bytes = (size_t)rank_tile_cols(n_features) * 128;
+    size_t tree_bytes = (size_t)8 << depth;
+    int best_t = 0, best_slots = 0, best_per = 0;
+    const int forced = tune(FS_TUNE_RANK_TILES);
+    const int choices[] = {6, 4, 3, 2, 1};
+    constexpr int kMostWalks = 64;
+    auto choose = [&]() {
+        int best_score = 0;
+        for (int nt : choices) {
+            if (forced > 0 && nt != forced)
+                continue;
+            const long avail = (long)kRankLdsBytes - (long)nt * (long)(tile_bytes + 256) - 128;
+            const int fit = avail < 0 ? 0 : (int)std::min<size_t>((size_t)avail / tree_bytes, 1024);
+            for (int slots = std::min(kRankWaves / nt, fit); slots >= 1; --slots) {
+                const int per = std::min(fit / slots, kRankMostTrees);
+                const int score = std::min(nt * slots * per, kMostWalks);
+                if (score > best_score) {
+                    best_score = score;
+                    best_t = nt;
+                    best_slots = slots;
+                    best_per = per;
+                }
+            }
+        }
+        return best_score;
+    };
+    const int score = choose();
+    if (score == 0)
+        return;                                           // (one such tree takes longer to bring in than to walk)
+    const bool held = depth < 2 || (score == kMostWalks && (forced > 0 || best_t == choices[0]));
+    if (!held) {                                          // (depth 2 and more: whole 16-byte pieces)
+        tree_bytes /= 2;
+        choose();
+    }
+    const size_t words = (size_t)2 << depth, n_leaves = words / 2, stride = tree_bytes / 4;   // per tree, word 0 unused
+    nodes->assign((stride + (held ? 0 : n_leaves)) * (size_t)n_trees, 0u);
     ids->assign(words * (size_t)n_trees, 0);
     std::vector<int32_t> at(words);                       // caller's node at heap position i
     for (int t = 0; t < n_trees; ++t) {
         const int32_t o = tree_off[t];
+        uint32_t *const splits = nodes->data() + (size_t)t * stride;
+        uint32_t *const leaves = held ? splits + n_leaves : nodes->data() + stride * (size_t)n_trees + (size_t)t * n_leaves;
         at[1] = 0;
         for (size_t i = 1; i < words; ++i) {
             const int32_t n = at[i];
-            uint32_t w;
             if (sf[o + n] >= 0) {
                 at[2 * i] = left[o + n];
                 at[2 * i + 1] = right[o + n];
@@ -519,39 +559,13 @@ void build_rank_format(fs_model *m, int n_features, int n_trees, int depth, cons
                     const std::vector<float> &v = per[(size_t)sf[o + n]];
                     rank = 1u + (uint32_t)(std::lower_bound(v.begin(), v.end(), th + 0.0f) - v.begin());
                 }
-                w = (rank << 16) | rank_feature_offset(sf[o + n]);
+                splits[i] = (rank << 16) | rank_feature_offset(sf[o + n]);
             } else {
-                memcpy(&w, &val[o + n], 4);
+                memcpy(&leaves[i - n_leaves], &val[o + n], 4);
             }
-            (*nodes)[(size_t)t * words + i] = w;
             (*ids)[(size_t)t * words + i] = (uint16_t)n;
         }
     }
-
-    // tiles per workgroup (must divide the wavefront count): most walks side by side, up to eight trees a slot; of
-    // equals the most tiles, as every workgroup reads the whole model
-    const size_t tree_bytes = words * 4, tile_bytes = (size_t)rank_tile_cols(n_features) * 128;
-    int best_t = 0, best_slots = 0, best_per = 0, best_score = 0;
-    const int forced = tune(FS_TUNE_RANK_TILES);
-    const int choices[] = {6, 4, 3, 2, 1};
-    for (int nt : choices) {
-        if (forced > 0 && nt != forced)
-            continue;
-        const long avail = (long)kRankLdsBytes - (long)nt * (long)(tile_bytes + 256) - 128;
-        const int fit = avail < 0 ? 0 : (int)std::min<size_t>((size_t)avail / tree_bytes, 1024);
-        for (int slots = std::min(kRankWaves / nt, fit); slots >= 1; --slots) {
-            const int per = std::min(fit / slots, kRankMostTrees);
-            const int score = std::min(nt * slots * per, 64);
-            if (score > best_score) {
-                best_score = score;
-                best_t = nt;
-                best_slots = slots;
-                best_per = per;
-            }
-        }
-    }
-    if (best_t == 0)
-        return;
     // as many trees in every turn as the number of turns needs
     const int rounds = std::max(1, (n_trees + best_slots * best_per - 1) / (best_slots * best_per));
     best_per = std::max(1, (n_trees + best_slots * rounds - 1) / (best_slots * rounds));

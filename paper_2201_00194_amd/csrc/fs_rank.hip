@@ -189,23 +189,26 @@ int launch_rank_code(const FamDesc *d_desc, int n_families, int total_blocks, hi
 // trees of depth 10 took 5500 clocks, 3300 of them walks, the rest copying 64 KB into LDS and
 // adding up while nothing else ran.  2.1 M rows, 500 such trees: 4.63 ms, so 3.85.)
 //
-// LDS map:  [0, slots * per_slot * tree_bytes)  the slots' trees, each 2^(depth+1) words: [unused][splits in heap
-//                                               order, 1-based][leaf values]
+// The leaf values stay in memory where they, half of a tree, would cost walks side by side: a slot asks for its
+// values, replaces its trees and then adds the values up.  (2.1 M rows, 500 trees of depth 10: 4.50 ms with three
+// trees a slot and their leaves, 3.92 with six without.)  Each way has its own loop: one for both took 6 % more.
+//
+// LDS map:  [0, slots * per_slot * tree_bytes)  the slots' trees, each [unused][splits in heap order, 1-based]
+//                                               and, if held, [leaf values]
 //           [tile0 - T*256 - 128, ...)          running sums [tile][lane], then the counters
 //           [tile0 + t*Fc*128, ...)             tile t: features 2i, 2i+1 of row l in the word at
 //                                               i*256 + 4*l (Fc = F rounded up to even)
 // A split word is rank(thr) << 16 | offset of the feature in a tile (i*256 + 2*(f & 1)).
 
-// K trees at once for this lane's row.  base[k] = LDS address of tree k; the 1-based heap
+// K trees at once for this lane's row, down to the leaves' places A[k].  base[k] = LDS address of tree k; the 1-based heap
 // index i lives at A = base + 4*i, and the step i' = 2i + c is taken on the address itself:
 // A' = 2A + (4c - base)   (one select between two per-tree constants and one shift-add).
 // (Reading both children of a split together with its feature halves the chain of LDS latencies, but two words cost
 // the LDS more bank conflicts than one: 4.67 ms instead of 4.51 for 2.1 M rows under 500 trees of depth 10.)
 template <int K>
-__device__ __forceinline__ void rank_walk(const uint32_t (&base)[K], int depth, uint32_t lane_base,
-                                          uint32_t (&idx)[K], float (&v)[K])
+__device__ __forceinline__ void rank_walk(const uint32_t (&base)[K], int depth, uint32_t lane_base, uint32_t (&A)[K])
 {
-    uint32_t A[K], left[K], right[K];
+    uint32_t left[K], right[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         A[k] = base[k] + 4u;
@@ -226,11 +229,6 @@ __device__ __forceinline__ void rank_walk(const uint32_t (&base)[K], int depth, 
 #pragma unroll
         for (int k = 0; k < K; ++k)
             A[k] = (A[k] << 1) + ((x[k] < (nd[k] >> 16)) ? left[k] : right[k]);
-    }
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        v[k] = lds_f(A[k]);
-        idx[k] = (A[k] - base[k]) >> 2;
     }
 }
 
@@ -306,8 +304,10 @@ traverse_rank_kernel(const FamDesc *__restrict__ descs, int n_families)
     const uint32_t my_sum = sums + 256u * (uint32_t)my_tile + 4u * (uint32_t)lane;
     const uint32_t turn_at = counters + 4u * (uint32_t)my_tile;            // turns whose values the sum holds
     const uint32_t slot_at = counters + 64u + 4u * (uint32_t)my_slot;      // how often wavefronts of the slot came by
-    // tree_bytes = 2^(depth+3) is a multiple of 16, so every tree starts 16-byte aligned
+    // tree_bytes is a multiple of 16, so every tree starts 16-byte aligned
     auto image = FS_GLOBAL(const u32x4, d.rk_nodes);
+    // (the values of a tree, by heap index)
+    auto leaves = FS_GLOBAL(const float, d.rk_nodes) + (int64_t)n_trees * (tree_bytes >> 2) - ((int64_t)1 << depth);
     const int tree16 = (int)(tree_bytes >> 4);
     // The first trees and the tiles go straight from memory to LDS, 1 KB per wavefront-wide
     // load; what is left of each (fewer than 64 pieces) goes through registers.
@@ -353,79 +353,104 @@ traverse_rank_kernel(const FamDesc *__restrict__ descs, int n_families)
             leaf_row = d.leaf_idx + (int64_t)r * n_trees;
     }
     uint32_t passed = 0;                                   // what the slot's counter has to reach
-    for (int q = my_slot; q < n_turns; q += n_slots) {
-        const int n = min(per_slot, n_trees - q * per_slot);
-        // the slot's next trees: global -> registers
-        const int q_next = q + n_slots;
-        const int n16 = q_next < n_turns ? min(per_slot, n_trees - q_next * per_slot) * tree16 : 0;
-        auto src = image + (int64_t)q_next * per_slot * tree16;
-        u32x4 pf[REGS];
-        if (n16 > 0) {
+    auto turns = [&](auto held_) {
+        constexpr bool HELD = decltype(held_)::value != 0;
+        for (int q = my_slot; q < n_turns; q += n_slots) {
+            const int n = min(per_slot, n_trees - q * per_slot);
+            // the slot's next trees: global -> registers
+            const int q_next = q + n_slots;
+            const int n16 = q_next < n_turns ? min(per_slot, n_trees - q_next * per_slot) * tree16 : 0;
+            auto src = image + (int64_t)q_next * per_slot * tree16;
+            u32x4 pf[REGS];
+            if (n16 > 0) {
 #pragma unroll
-            for (int j = 0; j < REGS; ++j)
-                pf[j] = src[min(in_slot + j * slot_threads, n16 - 1)];
-        }
-        auto turn = [&](auto trees) {
-            constexpr int K = decltype(trees)::value;
-            uint32_t base[K], idx[K];
-            float v[K];
+                for (int j = 0; j < REGS; ++j)
+                    pf[j] = src[min(in_slot + j * slot_threads, n16 - 1)];
+            }
+            float kept[kRankMostTrees];                    // values from memory
+            auto add_up = [&](auto trees, const float *v) {
+                wait_for(turn_at, (uint32_t)q);
+                float acc = lds_f(my_sum);
 #pragma unroll
-            for (int k = 0; k < K; ++k)
-                base[k] = region + (uint32_t)k * tree_bytes;
-            rank_walk<K>(base, depth, lane_base, idx, v);
-            if (DUMP) {
-                if (leaf_row) {
-                    auto ids = FS_GLOBAL(const uint16_t, d.rk_ids + (int64_t)q * per_slot * (tree_bytes >> 2));
-                    auto out = FS_GLOBAL(uint16_t, leaf_row + q * per_slot);
+                for (int k = 0; k < decltype(trees)::value; ++k)
+                    acc = acc + v[k];
+                if (q + 1 < n_turns) {
+                    lds_store_f(my_sum, acc);
+                    count_up(turn_at, lane);
+                } else if (r < d.n_rows) {
+                    FS_GLOBAL(float, d.row_score)[r] = acc;
+                }
+            };
+            auto walk = [&](auto trees) {
+                constexpr int K = decltype(trees)::value;
+                uint32_t base[K], at[K];
+#pragma unroll
+                for (int k = 0; k < K; ++k)
+                    base[k] = region + (uint32_t)k * tree_bytes;
+                rank_walk<K>(base, depth, lane_base, at);
+                float v[K];
+#pragma unroll
+                for (int k = 0; k < K; ++k)
+                    v[k] = HELD ? lds_f(at[k]) : (leaves + ((int64_t)(q * per_slot + k) << depth))[(at[k] - base[k]) >> 2];
+                if (DUMP) {
+                    if (leaf_row) {
+                        auto ids = FS_GLOBAL(const uint16_t, d.rk_ids + ((int64_t)q * per_slot << (depth + 1)));
+                        auto out = FS_GLOBAL(uint16_t, leaf_row + q * per_slot);
+#pragma unroll
+                        for (int k = 0; k < K; ++k)
+                            out[k] = ids[((uint32_t)k << (depth + 1)) + ((at[k] - base[k]) >> 2)];
+                    }
+                }
+                if (n16 > 0)
+                    count_up(slot_at, lane);               // the trees have been read
+                if (HELD) {
+                    add_up(trees, v);
+                } else {
 #pragma unroll
                     for (int k = 0; k < K; ++k)
-                        out[k] = ids[(uint32_t)k * (tree_bytes >> 2) + idx[k]];
+                        kept[k] = v[k];
                 }
+            };
+            auto for_trees = [&](auto what) {
+                switch (n) {
+                case 8: what(RankInt<8>()); break;
+                case 7: what(RankInt<7>()); break;
+                case 6: what(RankInt<6>()); break;
+                case 5: what(RankInt<5>()); break;
+                case 4: what(RankInt<4>()); break;
+                case 3: what(RankInt<3>()); break;
+                case 2: what(RankInt<2>()); break;
+                default: what(RankInt<1>());
+                }
+            };
+            if (active)
+                for_trees(walk);
+            else if (n16 > 0)
+                count_up(slot_at, lane);
+            if (n16 > 0) {
+                passed += (uint32_t)T;
+                wait_for(slot_at, passed);
+#pragma unroll
+                for (int j = 0; j < REGS; ++j) {
+                    const int i = in_slot + j * slot_threads;
+                    if (i < n16)
+                        lds_store_u4(region + 16u * (uint32_t)i, pf[j]);
+                }
+                for (int i = in_slot + REGS * slot_threads; i < n16; i += slot_threads)   // trees larger than that
+                    lds_store_u4(region + 16u * (uint32_t)i, src[i]);
+                count_up(slot_at, lane);
+                passed += (uint32_t)T;
             }
+            if (!HELD && active)
+                for_trees([&](auto trees) { add_up(trees, kept); });
             if (n16 > 0)
-                count_up(slot_at, lane);                   // the trees have been read
-            wait_for(turn_at, (uint32_t)q);
-            float acc = lds_f(my_sum);
-#pragma unroll
-            for (int k = 0; k < K; ++k)
-                acc = acc + v[k];
-            if (q + 1 < n_turns) {
-                lds_store_f(my_sum, acc);
-                count_up(turn_at, lane);
-            } else if (r < d.n_rows) {
-                FS_GLOBAL(float, d.row_score)[r] = acc;
-            }
-        };
-        if (active) {
-            switch (n) {
-            case 8: turn(RankInt<8>()); break;
-            case 7: turn(RankInt<7>()); break;
-            case 6: turn(RankInt<6>()); break;
-            case 5: turn(RankInt<5>()); break;
-            case 4: turn(RankInt<4>()); break;
-            case 3: turn(RankInt<3>()); break;
-            case 2: turn(RankInt<2>()); break;
-            default: turn(RankInt<1>());
-            }
-        } else if (n16 > 0) {
-            count_up(slot_at, lane);
+                wait_for(slot_at, passed);                 // the next trees are there
         }
-        if (n16 > 0) {
-            passed += (uint32_t)T;
-            wait_for(slot_at, passed);
-#pragma unroll
-            for (int j = 0; j < REGS; ++j) {
-                const int i = in_slot + j * slot_threads;
-                if (i < n16)
-                    lds_store_u4(region + 16u * (uint32_t)i, pf[j]);
-            }
-            for (int i = in_slot + REGS * slot_threads; i < n16; i += slot_threads)   // trees larger than that
-                lds_store_u4(region + 16u * (uint32_t)i, src[i]);
-            count_up(slot_at, lane);
-            passed += (uint32_t)T;
-            wait_for(slot_at, passed);
-        }
-    }
+    };
+    if (tree_bytes == 8u << depth)                         // leaf values in LDS
+        turns(RankInt<1>());
+    else
+        turns(RankInt<0>());
     // (no trees: the row's score is the bias)
     if (n_turns == 0 && my_slot == 0 && active && r < d.n_rows)
         FS_GLOBAL(float, d.row_score)[r] = d.bias;

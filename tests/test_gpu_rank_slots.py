@@ -28,3 +28,12 @@ def test_models_of_different_trees_in_one_launch(api, oracle, tune):  # noqa: F8
             for d in (12, 4, 8, 10)]
     for f, dev in zip(fams, run_families(api, fams, api.FS_COLBLOCK64)):
         check_family(oracle, f, dev)
+
+
+@pytest.mark.parametrize("depth,features", [(8, 164), (8, 180), (8, 251), (9, 100), (9, 164), (2, 600), (1, 630), (0, 9)])
+def test_leaf_values_in_lds_or_in_memory(api, oracle, tune, depth, features):  # noqa: F811
+    """They are held where that leaves room for 64 trees walked at a time on six tiles, and always in shallow trees."""
+    tune(api.FS_TUNE_RANK, 1)
+    fam = W.make_small_family(seed=depth + features, n_programs=64 * 9 + 7, stmts=(1, 1), n_trees=53, depth=depth, k=5,
+                              n_features=features, bias=-0.5)
+    check_family(oracle, fam, run_families(api, [fam], api.FS_COLBLOCK64)[0])
