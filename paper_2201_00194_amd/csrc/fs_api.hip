@@ -685,10 +685,8 @@ extern "C" int fs_score_families(int32_t n_families, const fs_family *fams, void
             scratch_pos = (scratch_pos + 3) & ~(size_t)3;            // 16-byte aligned tiles
             d.ranks = (uint16_t *)(ctx->scratch[kScratchScore] + scratch_pos);
             scratch_pos += (size_t)tiles * 32 * (size_t)rank_tile_cols(a.model->n_features);
-            const int len = 1 << a.model->cut_bits;
-            int per_group = kBinTableBytes / 4 / len;
-            if (per_group > a.model->n_features) per_group = a.model->n_features;
-            d.bin_feats_per_group = per_group;                      // >= 1 by model packing
+            const int per_group = a.model->bin_group;
+            d.bin_feats_per_group = per_group;
             d.bin_groups = (a.model->n_features + per_group - 1) / per_group;
             // enough workgroups to fill the chip even for a small family
             int64_t tpb = tiles * d.bin_groups / 512;

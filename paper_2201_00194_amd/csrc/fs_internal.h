@@ -127,7 +127,8 @@ struct fs_model {
     uint16_t *d_rk_ids;        // [n_trees][2^(depth+1)] 1-based heap order: caller's local node id
     float *d_cuts;             // [n_features][2^cut_bits]: the feature's sorted distinct
                                // thresholds, NaN-padded, as a breadth-first search tree
-    int32_t cut_bits;
+    int32_t cut_bits;          // or RankColumn tables of -cut_bits bytes each
+    int32_t bin_group;         // features whose tables a workgroup of the coder holds
     // Byte-rank treelets (fs_treelet.h); null if the model does not fit that format
     bool tl_ok;
     bool tl_pair;              // two chunk buffers fit half a compute unit's LDS
@@ -183,7 +184,8 @@ struct FamDesc {
     const float *rowmajor_src;
     int32_t retile_block0;           // first block of the re-tiling grid
     int32_t retile_colblocks;        // column blocks per tile (0: family not re-tiled)
-    int32_t cut_bits;                // threshold tables are padded to 2^cut_bits entries
+    int32_t cut_bits;                // threshold tables are padded to 2^cut_bits entries; negative: RankColumn tables of
+                                     // so many bytes
     const TreeletModel *tl;          // byte-rank treelets
     int32_t tl_block0[2];            // first block of this family in the two treelet launches
 };
@@ -397,7 +399,15 @@ void prof_stop(hipStream_t stream);
 
 // rank-coding kernel: most tiles handled by one workgroup, LDS bytes for threshold tables
 constexpr int kBinTilesPerBlock = 256;
-constexpr int kBinTableBytes = 64 * 1024;
+constexpr int kBinTableBytes = 80 * 1024;    // two workgroups fit a compute unit
+constexpr int kBinTreeBytes = 64 * 1024;     // of search trees
+// Head of a feature's table, if values are coded by buckets: then 16-bit numbers of the thresholds in lower buckets
+// for each bucket, then the sorted thresholds, NaN behind.  The bucket of x is x * scale + offset (one rounding),
+// truncated and clamped, which never decreases with x; up to 2^steps - 1 thresholds share one.
+struct RankColumn {
+    float scale, offset;
+    int32_t buckets, steps;
+};
 constexpr int kRankWaves = 12;
 constexpr int kRankLdsBytes = 160 * 1024;
 constexpr int kRankMostTrees = 8;        // of a slot

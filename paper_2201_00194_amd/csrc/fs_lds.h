@@ -26,6 +26,16 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 #define FS_GLOBAL(T, p) ((T *)(uintptr_t)(p))
 #define FS_CONST(T, p) ((const T *)(uintptr_t)(p))
 #endif
+// Truncation that saturates (negative and NaN: 0), which a C conversion does not promise.
+static __device__ __forceinline__ uint32_t to_u32(float v)
+{
+    uint32_t r = 0;
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm("v_cvt_u32_f32 %0, %1" : "=v"(r) : "v"(v));
+#endif
+    return r;
+}
+
 static __device__ __forceinline__ u32x2 lds_u2(uint32_t a) { return *FS_LDS_PTR(const u32x2, a); }
 static __device__ __forceinline__ float lds_f(uint32_t a) { return *FS_LDS_PTR(const float, a); }
 static __device__ __forceinline__ uint32_t lds_u(uint32_t a) { return *FS_LDS_PTR(const uint32_t, a); }

@@ -12,7 +12,7 @@
 // only a handful of trees per chunk and the model has to stream through LDS once per 128 rows.
 //
 // Two kernels:
-//   rank_code_kernel     fp32 feature tiles -> u16 rank tiles (binary search in LDS-resident
+//   rank_code_kernel     fp32 feature tiles -> u16 rank tiles (searches in LDS-resident
 //                        threshold tables, one feature group per workgroup)
 //   traverse_rank_kernel the LDS-staged walk over rank tiles; trees in heap order without
 //                        child pointers (node i has children 2i, 2i+1, 1-based), leaves are the
@@ -36,6 +36,11 @@ constexpr int kBinThreads = 1024;
 // the lanes' reads spread over the LDS banks, whereas the probes of a bisection of the sorted
 // array are a power-of-two stride apart and all fall into the same bank.  Four searches run
 // interleaved per wavefront.
+//
+// Where the thresholds are spread well enough (bucket_tables), the tree's upper levels give way to a bucket table: a
+// multiply-add finds the bucket, the table the thresholds below it, and a bisection of at most 5 steps the bucket's own.
+// (With q = 12 steps of four instructions vector issue took 95 % of the clocks, now memory bounds it: 2.1 M rows of
+// 164 features, 3100 thresholds each, 2.1 GB: 611 us, so 490.)
 constexpr int kBinChains = 4;
 
 __global__ void __launch_bounds__(kBinThreads, 8)     // two workgroups per compute unit
@@ -61,7 +66,8 @@ rank_code_kernel(const FamDesc *__restrict__ descs, int n_families)
     const int nt = min(tpb, n_tiles - t0);
     const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
     const int q = d.cut_bits;                       // table stride 2^q entries
-    const int len = 1 << q;
+    const bool bucketed = q < 0;
+    const int len = bucketed ? -q / 4 : 1 << q;     // words of a feature's table
 
     // this group's padded threshold tables: one contiguous, 16-byte aligned run, straight from
     // memory to LDS (what is left below 64 pieces goes through a register)
@@ -101,12 +107,11 @@ rank_code_kernel(const FamDesc *__restrict__ descs, int n_families)
         const int j0 = jg * kBinChains;
         const int64_t base = (int64_t)(t0 + t) * rank_tile_cols(F) * 64 + 2 * lane;   // u16 units
         float x[kBinChains];
-        uint32_t pos[kBinChains], tab[kBinChains];
+        uint32_t r[kBinChains], tab[kBinChains];
 #pragma unroll
         for (int k = 0; k < kBinChains; ++k) {
             x[k] = xn[k];
             tab[k] = 4u * (uint32_t)(min(j0 + k, gf - 1) * len);
-            pos[k] = 1u;                             // node of the implicit search tree
         }
         // next round
         int tn = t, jn = jg + 1;
@@ -119,19 +124,46 @@ rank_code_kernel(const FamDesc *__restrict__ descs, int n_families)
             for (int k = 0; k < kBinChains; ++k)
                 xn[k] = X[x_at(t0 + tn, min(jn * kBinChains + k, gf - 1))];
         }
-        for (int s = 0; s < q; ++s) {
-            float c[kBinChains];
+        if (bucketed) {
+            int steps = 0;
+            uint32_t keys[kBinChains];
+#pragma unroll
+            for (int k = 0; k < kBinChains; ++k) {
+                auto col = FS_CONST(RankColumn, d.cuts + (int64_t)(f0 + min(j0 + k, gf - 1)) * len);
+                const uint32_t bucket = to_u32(__builtin_fmaf(x[k], col->scale, col->offset));
+                r[k] = lds_u16(tab[k] + 16u + 2u * min(bucket, (uint32_t)col->buckets - 1u));
+                keys[k] = tab[k] + 16u + 2u * (uint32_t)col->buckets;
+                steps = col->steps;                  // the same for all features
+            }
+            for (int s = steps - 1; s >= 0; --s) {
+                float c[kBinChains];
+#pragma unroll
+                for (int k = 0; k < kBinChains; ++k)
+                    c[k] = lds_f(keys[k] + 4u * r[k] + (4u << s) - 4u);
+#pragma unroll
+                for (int k = 0; k < kBinChains; ++k)
+                    r[k] += c[k] <= x[k] ? 1u << s : 0u;
+            }
+        } else {
 #pragma unroll
             for (int k = 0; k < kBinChains; ++k)
-                c[k] = lds_f(tab[k] + 4u * pos[k]);
+                r[k] = 1u;                           // node of the implicit search tree
+            for (int s = 0; s < q; ++s) {
+                float c[kBinChains];
+#pragma unroll
+                for (int k = 0; k < kBinChains; ++k)
+                    c[k] = lds_f(tab[k] + 4u * r[k]);
+#pragma unroll
+                for (int k = 0; k < kBinChains; ++k)
+                    r[k] = 2u * r[k] + ((c[k] <= x[k]) ? 1u : 0u);
+            }
 #pragma unroll
             for (int k = 0; k < kBinChains; ++k)
-                pos[k] = 2u * pos[k] + ((c[k] <= x[k]) ? 1u : 0u);
+                r[k] -= (uint32_t)len;
         }
-        uint32_t r[kBinChains];
 #pragma unroll
         for (int k = 0; k < kBinChains; ++k)
-            r[k] = (x[k] != x[k]) ? 65535u : (pos[k] - (uint32_t)len);
+            r[k] = x[k] != x[k] ? 65535u : r[k];
         if ((f0 & 1) == 0) {
             // chains 2i and 2i+1 hold the two features of one word of the tile
             auto R2 = FS_GLOBAL(uint32_t, d.ranks);

@@ -82,16 +82,6 @@ static __device__ __forceinline__ void count_below(const float *key, const float
 #endif
 }
 
-// Truncation that saturates (negative and NaN: 0), which a C conversion does not promise.
-static __device__ __forceinline__ uint32_t to_u32(float v)
-{
-    uint32_t r = 0;
-#if defined(__HIP_DEVICE_COMPILE__)
-    asm("v_cvt_u32_f32 %0, %1" : "=v"(r) : "v"(v));
-#endif
-    return r;
-}
-
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
 // One wavefront codes columns in batches of NC columns x T tiles (batch wave, wave + n_waves, ...),

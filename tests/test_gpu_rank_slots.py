@@ -37,3 +37,30 @@ def test_leaf_values_in_lds_or_in_memory(api, oracle, tune, depth, features):  #
     fam = W.make_small_family(seed=depth + features, n_programs=64 * 9 + 7, stmts=(1, 1), n_trees=53, depth=depth, k=5,
                               n_features=features, bias=-0.5)
     check_family(oracle, fam, run_families(api, [fam], api.FS_COLBLOCK64)[0])
+
+
+@pytest.mark.parametrize("kind", ["spread", "one value", "crowded", "decades", "with infinities"])
+@pytest.mark.parametrize("layout", ["colblock", "rowmajor"])
+def test_thresholds_in_buckets_or_search_trees(api, oracle, tune, kind, layout):  # noqa: F811
+    """The coder's tables follow how a feature's thresholds are spread; values are on, beside and far off them."""
+    tune(api.FS_TUNE_RANK, 1)
+    fam = W.make_small_family(seed=31, n_programs=700, stmts=(1, 2), n_trees=40, depth=6, k=5, n_features=13)
+    rng = np.random.default_rng(8)
+    m, x = fam.model, fam.features
+    split = np.flatnonzero(np.asarray(m.split_feature) >= 0)
+    n = split.shape[0]
+    thr = np.array(m.threshold, np.float32)
+    if kind == "one value":
+        thr[split] = 0.25
+    elif kind == "crowded":
+        thr[split] = np.where(rng.random(n) < 0.9, 1.0 + rng.integers(0, 200, n) * 2.0 ** -23, rng.random(n) * 1e6)
+    elif kind == "decades":
+        thr[split] = 10.0 ** rng.uniform(-38, 38, n) * rng.choice([-1, 1], n)
+    elif kind == "with infinities":
+        thr[split] = np.where(rng.random(n) < 0.1, rng.choice([np.inf, -np.inf, 0.0, -0.0, np.nan], n), rng.random(n))
+    m.threshold[:] = thr
+    pick = rng.random(x.shape)
+    near = thr[split][rng.integers(0, n, x.shape)]
+    x[:] = np.where(pick < 0.4, near, np.where(pick < 0.6, np.nextafter(near, np.float32(np.inf)),
+                    np.where(pick < 0.7, rng.choice([np.inf, -np.inf, np.nan, 0.0, -0.0, 1e-45], x.shape), x)))
+    check_family(oracle, fam, run_families(api, [fam], getattr(api, "FS_" + layout.upper() + ("64" if layout == "colblock" else "")))[0])
