@@ -126,8 +126,9 @@ struct fs_model {
     uint32_t *d_rk_nodes;      // [n_trees][rk_tree_bytes], then, if they are not held, [n_trees][2^depth] leaf values
     uint16_t *d_rk_ids;        // [n_trees][2^(depth+1)] 1-based heap order: caller's local node id
     float *d_cuts;             // [n_features][2^cut_bits]: the feature's sorted distinct
-                               // thresholds, NaN-padded, as a breadth-first search tree
-    int32_t cut_bits;          // or RankColumn tables of -cut_bits bytes each
+                               // thresholds, NaN-padded, as a breadth-first search tree; or, with
+                               // cut_bits negative, [n_features][-cut_bits bytes]: RankColumn tables
+    int32_t cut_bits;
     int32_t bin_group;         // features whose tables a workgroup of the coder holds
     // Byte-rank treelets (fs_treelet.h); null if the model does not fit that format
     bool tl_ok;

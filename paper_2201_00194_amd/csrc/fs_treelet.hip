@@ -465,10 +465,10 @@ static __device__ __forceinline__ void fetch_chunk(const TreeletModel &m, const 
 // is short, and a chunk that waits in registers and is stored from there takes more of it: eight families of 300
 // perfect trees of depth 8 1024 us instead of 1000, 64 of deep irregular trees 2211 instead of 2161.)  (One wavefront per tile needs no
 // hand-over, but eight wavefronts per compute unit leave the vector units half idle: 3.15 ms on thirty
-// families of power-law size, 200 irregular trees of depth 8, against 2.30 ms; the float-threshold kernel took
-// 3.62 ms there.)  Vector issue bounds this kernel: there it issues 1.05e9 vector instructions, which at four
-// clocks are 77 % of the SIMDs' clocks, and a compute unit an LDS instruction every 4.3 clocks, where
-// conflict-free ones take 2.4.
+// families of power-law size, 200 irregular trees of depth 8, against 2.30 ms then; the float-threshold kernel took
+// 3.62 ms there.)  Vector issue and the LDS bound this kernel alike: there it issues 1.02e9 vector instructions, which
+// at four clocks are 78 % of the SIMDs' clocks, and a compute unit an LDS instruction every 4.2 clocks, where
+// conflict-free ones take 2.4.  (Leaf values read from memory instead of the LDS: 2.36 ms, 2.26 so.)
 // LDS: [columns][chunk][running sums of the tiles, by hand-over]; the coder's tables are where the
 // chunks will be.
 constexpr int kPairTiles = 4;
