@@ -459,6 +459,23 @@ void write_lds(const LdsPlan &plan, int n_features, const int32_t *tree_off, con
     }
 }
 
+// The bucket of x as the device rounds, truncates and clamps: x * scale is exact in double, so the sum in double rounded
+// to float is the fused result unless the rounding to double has made it a tie between two floats, which is noted in
+// `tie` or, without that, settled.
+inline int rank_bucket(float x, const RankColumn &c, bool *tie)
+{
+    const double sum = (double)x * (double)c.scale + (double)c.offset;
+    uint64_t sum_bits;
+    memcpy(&sum_bits, &sum, 8);
+    float t = (float)sum;
+    const bool is_tie = (sum_bits & 0x1FFFFFFFu) == 0x10000000u;
+    if (tie)
+        *tie |= is_tie;
+    else if (is_tie)
+        t = std::fmaf(x, c.scale, c.offset);
+    return (int)std::min(t > 0.0f ? t : 0.0f, (float)(c.buckets - 1));
+}
+
 // Tables of RankColumn for the rank coder; false where they do not fit or thresholds crowd into few buckets (32 or more
 // in one): the bucket and its steps would come near the search tree's, whose reads spread better over the LDS banks.
 // A call's time, tree / buckets (2 to 4 steps): 500 trees of depth 10, 2.1 M rows 3.91 / 3.82 ms; of depth 9, 0.5 M rows
@@ -476,18 +493,17 @@ bool bucket_tables(fs_model *m, int n_features, int max_cuts, const std::vector<
     const int B = std::min((kBinTableBytes / group - 16 - 4 * keys) / 2, std::max(4 * max_cuts, 64)) & ~7;
     if (B < std::max(64, max_cuts / 2) || B > 65536)
         return false;
-    // As the device rounds, truncates and clamps: x * scale is exact in double, so the sum in double rounded
-    // to float is the fused result unless the rounding to double has made it a tie between two floats.
-    auto bucket_of = [B](float x, const RankColumn &c) -> int {
-        const double sum = (double)x * (double)c.scale + (double)c.offset;
-        uint64_t sum_bits;
-        memcpy(&sum_bits, &sum, 8);
-        float t = (float)sum;
-        if ((sum_bits & 0x1FFFFFFFu) == 0x10000000u)
-            t = std::fmaf(x, c.scale, c.offset);
-        return t >= (float)(B - 1) ? B - 1 : (t > 0.0f ? (int)t : 0);
+    auto find_buckets = [&](const std::vector<float> &v, const RankColumn &c, std::vector<int> &out) {
+        out.resize(v.size());
+        bool ties = false;
+        for (size_t i = 0; i < v.size(); ++i)
+            out[i] = rank_bucket(v[i], c, &ties);
+        for (size_t i = 0; i < v.size() && ties; ++i)
+            out[i] = rank_bucket(v[i], c, nullptr);
     };
     std::vector<RankColumn> cols((size_t)n_features);
+    std::vector<std::vector<int>> bucket((size_t)n_features);
+    std::vector<int> tried;
     int most_load = 0;
     for (int f = 0; f < n_features; ++f) {
         const std::vector<float> &v = per[(size_t)f];
@@ -495,6 +511,7 @@ bool bucket_tables(fs_model *m, int n_features, int max_cuts, const std::vector<
         while (lo < hi && std::isinf(v[(size_t)lo])) ++lo;
         while (hi > lo && std::isinf(v[(size_t)hi])) --hi;
         RankColumn best = {0.0f, 0.0f, B, 0};             // one bucket for all
+        bucket[(size_t)f].assign(v.size(), 0);
         // the buckets cover all finite thresholds, or all but the lowest (an exact zero far below the rest) or highest
         for (int trial = 0; trial < 4 && best_load > 7; ++trial) {
             const int a = std::min(lo + (trial & 1), hi), b = std::max(hi - (trial >> 1), a);
@@ -505,9 +522,9 @@ bool bucket_tables(fs_model *m, int n_features, int max_cuts, const std::vector<
             if (!(s < 3e38 && s > 1e-37 && std::fabs(o) < 3e38))
                 continue;
             const RankColumn c = {(float)s, (float)o, B, 0};
+            find_buckets(v, c, tried);
             int load = 0, run = 0, prev = -1;
-            for (size_t i = 0; i < v.size() && load < best_load; ++i) {
-                const int bk = bucket_of(v[i], c);
+            for (const int bk : tried) {
                 run = bk == prev ? run + 1 : 1;
                 prev = bk;
                 load = std::max(load, run);
@@ -515,6 +532,7 @@ bool bucket_tables(fs_model *m, int n_features, int max_cuts, const std::vector<
             if (load < best_load) {
                 best_load = load;
                 best = c;
+                bucket[(size_t)f].swap(tried);
             }
         }
         most_load = std::max(most_load, best_load);
@@ -535,7 +553,7 @@ bool bucket_tables(fs_model *m, int n_features, int max_cuts, const std::vector<
         uint16_t *const below = (uint16_t *)(tab + 16);
         int b = 0;
         for (size_t i = 0; i <= v.size(); ++i) {
-            const int end = i < v.size() ? bucket_of(v[i], cols[(size_t)f]) + 1 : B;
+            const int end = i < v.size() ? bucket[(size_t)f][i] + 1 : B;
             for (; b < end; ++b)
                 below[b] = (uint16_t)i;
         }
@@ -650,7 +668,18 @@ void build_rank_format(fs_model *m, int n_features, int n_trees, int depth, cons
                 uint32_t rank = 0;
                 if (th == th) {
                     const std::vector<float> &v = per[(size_t)sf[o + n]];
-                    rank = 1u + (uint32_t)(std::lower_bound(v.begin(), v.end(), th + 0.0f) - v.begin());
+                    auto from = v.begin();
+                    if (m->cut_bits < 0) {                // not in a lower bucket
+                        const char *tab = (const char *)cuts->data() + (int64_t)-m->cut_bits * sf[o + n];
+                        RankColumn c;
+                        memcpy(&c, tab, sizeof(c));
+                        from += ((const uint16_t *)(tab + sizeof(c)))[rank_bucket(th + 0.0f, c, nullptr)];
+                        while (*from < th)
+                            ++from;
+                    } else {
+                        from = std::lower_bound(from, v.end(), th + 0.0f);
+                    }
+                    rank = 1u + (uint32_t)(from - v.begin());
                 }
                 splits[i] = (rank << 16) | rank_feature_offset(sf[o + n]);
             } else {
