@@ -38,8 +38,8 @@
  *     synchronised, the old buffer freed and a larger one allocated.  A caller that has
  *     reserved enough (fs_workspace_bytes, fs_topk_workspace_bytes, fs_workspace_reserve)
  *     never gets here;
- *   - the call's descriptors (248 bytes per family, 56 per top-k workgroup) exceed 20 KB
- *     (82 families or 365 top-k workgroups).  Up to that size they travel as kernel
+ *   - the call's descriptors (256 bytes per family, 56 per top-k workgroup) exceed 21 KB
+ *     (84 families or 384 top-k workgroups).  Up to that size they travel as kernel
  *     arguments; beyond it they are staged through a ring of 8 pinned slots per device: a
  *     slot grows when it is too small, and the ninth such submission waits until the first
  *     has finished on the device.

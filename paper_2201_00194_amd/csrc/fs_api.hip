@@ -65,7 +65,7 @@ enum { kScratchScore = 0, kScratchTopk = 1, kScratchRegions = 2 };
 // a fixed device buffer (one per kind of call), in stream order in front of the kernels that read
 // them.  No pinned staging, no copy, no event and nothing to wait for, so such a call can also be
 // recorded into a HIP graph.  Longer descriptor arrays go through the ring of pinned slots.
-constexpr size_t kInlineBytes = 20480;
+constexpr size_t kInlineBytes = 21504;
 constexpr size_t kBlobBytes = 3968;               // one kernel argument (the limit is 4 KB)
 enum { kDescScore = 0, kDescTopk = 1, kDescKinds = 2 };
 
