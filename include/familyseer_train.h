@@ -59,14 +59,15 @@ typedef struct fs_train_params {
  * may be asked for later (they size the buffers).  n_rows >= 1, n_programs >= 1.
  * The content of prog_off (DEVICE) is not validated: it must start at 0, be non-decreasing
  * and end at n_rows, as for fs_score_families; a malformed array gives undefined results.
- * The cut lists (HOST) are validated.  The call first waits for all work on the device (its memory may
- * be a destroyed trainer's) and BLOCKS until its own on `stream` is done: the binning kernels run there,
- * and the length of the longest program is read back (it sizes the curvature sums of the histograms).
- * Create trainers outside latency-critical sections.
+ * The cut lists (HOST) are validated.  The call BLOCKS until its work on `stream` is done: the binning
+ * kernels run there, and the length of the longest program is read back (it sizes the curvature sums of the
+ * histograms).  Where its memory was a destroyed trainer's, it also waits for what that trainer's calls had
+ * started.  Create trainers outside latency-critical sections.
  * All trainers of a device share one buffer for histograms.  This call grows it, where need be, to
- * what any batch of the trainers alive takes.  It is at most 16 GB, or what the largest trainer takes by
- * itself.  With 256-bin features a trainer of depth d takes 4 KB x 2^(d-1) x n_features, and a batch up to
- * 4 KB x n_features for each 512 rows, but not more than 128 MB and once 4 KB x n_features per trainer.
+ * what any batch of the trainers alive takes, and then waits for all work on the device.  It is at most
+ * 16 GB, or what the largest trainer takes by itself.  With 256-bin features a trainer of depth d takes
+ * 4 KB x 2^(d-1) x n_features, and a batch up to 4 KB x n_features for each 512 rows, but not more than
+ * 128 MB and once 4 KB x n_features per trainer.
  * Errors: FS_EINVAL, FS_EUNSUPPORTED (limits), FS_ENOMEM, FS_EDEVICE.
  */
 int fs_trainer_create(fs_trainer **out, int32_t n_features, const float *features /* DEVICE */,

@@ -1501,6 +1501,20 @@ train_split_kernel(const TrainDesc *__restrict__ descs, int level, int turn, int
 
 // ---- host side ----------------------------------------------------------------------------
 
+namespace fs {
+
+// A call's work on the device: done where the event is.
+struct Work {
+    hipEvent_t done = nullptr;
+    ~Work()
+    {
+        if (done)
+            (void)hipEventDestroy(done);
+    }
+};
+
+}  // namespace fs
+
 struct fs_trainer {
     fs::TrainDesc h;          // host copy of the descriptor (device pointers inside)
     int device;
@@ -1509,6 +1523,8 @@ struct fs_trainer {
     int max_len;              // rows of the longest program
     void *memory;             // everything the descriptor points to
     size_t memory_bytes;
+    std::shared_ptr<fs::Work> last;   // of the calls that work in the memory; none: nothing is at work
+    bool untracked;           // something may be that `last` does not tell
 };
 
 namespace fs {
@@ -1521,13 +1537,14 @@ struct BatchBuf {
     void *work = nullptr;          // histograms of the batch in work: room for any batch of `alive`
     size_t work_bytes = 0;
     std::vector<const fs_trainer *> alive;   // without any `work` is kept up to kKeptWork
-    struct Block { void *p; size_t bytes; };
+    struct Block { void *p; size_t bytes; std::shared_ptr<Work> last; };
     std::vector<Block> kept;       // memory of destroyed trainers, for the next
     size_t kept_bytes = 0;
     void *staging[4] = {};         // pinned memory that no call uses
     size_t needed = 0, needed_before = 0;    // of `work`, since there was no trainer; and until then
     hipEvent_t copied = nullptr;
     bool pending = false;
+    std::shared_ptr<Work> last;    // of fs_train_boost and fs_trainer_predictions, each of which waits for it first
 };
 static BatchBuf *const g_batch = new BatchBuf[16];   // never freed: trainers may outlive static objects
 
@@ -1567,8 +1584,9 @@ static bool give_back(BatchBuf &b)
     return true;
 }
 
-// Keeps a destroyed trainer's memory, or frees it.  Kernels may still be at work in it: take_block's caller waits.
-static void keep_block(BatchBuf &b, void *p, size_t bytes)
+// Keeps a destroyed trainer's memory, or frees it, which waits for the device.  `last` may still be at work in it:
+// take_block's caller waits for that.
+static void keep_block(BatchBuf &b, void *p, size_t bytes, const std::shared_ptr<Work> &last)
 {
     if (bytes > kKeptBlocks) {
         (void)hipFree(p);
@@ -1580,7 +1598,7 @@ static void keep_block(BatchBuf &b, void *p, size_t bytes)
         b.kept.erase(b.kept.begin());
     }
     try {
-        b.kept.push_back({p, bytes});
+        b.kept.push_back({p, bytes, last});
         b.kept_bytes += bytes;
     } catch (const std::bad_alloc &) {
         (void)hipFree(p);
@@ -1588,7 +1606,7 @@ static void keep_block(BatchBuf &b, void *p, size_t bytes)
 }
 
 // A kept block for `bytes`, not more than twice as large; null if there is none.
-static void *take_block(int device, size_t bytes, size_t *size)
+static void *take_block(int device, size_t bytes, size_t *size, std::shared_ptr<Work> *last)
 {
     if (device < 0 || device >= 16)
         return nullptr;
@@ -1602,6 +1620,7 @@ static void *take_block(int device, size_t bytes, size_t *size)
         return nullptr;
     void *p = b.kept[best].p;
     *size = b.kept[best].bytes;
+    *last = b.kept[best].last;
     b.kept_bytes -= *size;
     b.kept.erase(b.kept.begin() + (long)best);
     return p;
@@ -1672,7 +1691,16 @@ struct Arena {
     }
     int place(void **base, size_t *size, int device)
     {
-        *base = take_block(device, bytes, size);
+        std::shared_ptr<Work> last;
+        *base = take_block(device, bytes, size, &last);
+        if (last) {                                              // not for whatever else the device does
+            const hipError_t e = hipEventSynchronize(last->done);
+            if (e != hipSuccess) {
+                (void)hipFree(*base);
+                *base = nullptr;
+                return fail_hip(e, "waiting for a destroyed trainer");
+            }
+        }
         const hipError_t e = *base ? hipSuccess : hipMalloc(base, *size = bytes);
         if (e != hipSuccess) {
             *base = nullptr;
@@ -1697,8 +1725,8 @@ static int check_launch(const char *what)
 // ---- the histograms' buffer --------------------------------------------------------------------
 // Histograms live for one fs_train_boost only, and training calls on one device are ordered by the
 // caller, as its descriptors need already: all trainers share a buffer of the device (fresh memory of
-// 20 MB for each of eight trainers took 5 ms of a job's retraining).  fs_trainer_create, which waits for
-// the device anyway, grows it to what any batch of the trainers alive may need, so that fs_train_boost
+// 20 MB for each of eight trainers took 5 ms of a job's retraining).  fs_trainer_create
+// grows it to what any batch of the trainers alive may need, so that fs_train_boost
 // neither allocates nor waits.  A batch that needs more than kMostWork is trained in parts, one after the other.
 constexpr size_t kMostWork = (size_t)16 << 30;
 
@@ -1826,13 +1854,14 @@ extern "C" void fs_trainer_destroy(fs_trainer *t)
 {
     if (!t)
         return;
-    if (t->memory && (t->device < 0 || t->device >= 16))
+    const bool keeps = !t->untracked && t->device >= 0 && t->device < 16;
+    if (t->memory && !keeps)
         (void)hipFree(t->memory);
     if (t->device >= 0 && t->device < 16) {
         std::lock_guard<std::mutex> lock(g_train_mu);
         BatchBuf &b = g_batch[t->device];
-        if (t->memory)
-            keep_block(b, t->memory, t->memory_bytes);
+        if (t->memory && keeps)
+            keep_block(b, t->memory, t->memory_bytes, t->last);
         const auto it = std::find(b.alive.begin(), b.alive.end(), t);
         if (it != b.alive.end()) {
             b.alive.erase(it);
@@ -1899,6 +1928,7 @@ extern "C" int fs_trainer_create(fs_trainer **out, int32_t n_features, const flo
     t->max_depth = max_depth;
     t->max_trees = max_trees;
     t->trees_enqueued = 0;
+    t->untracked = true;                                         // until this call's work is done
     TrainDesc &h = t->h;
     h.n_features = n_features;
     h.n_rows = (int32_t)n_rows;
@@ -1962,11 +1992,8 @@ extern "C" int fs_trainer_create(fs_trainer **out, int32_t n_features, const flo
     h.cut_off = d_cut_off;
     h.cuts = d_cuts;
     h.hot_bin = d_hot;
-    // A kept block may still be in use by what its trainer had started, on whichever stream.
-    e = hipDeviceSynchronize();
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(d_prog_off, prog_off, sizeof(int32_t) * ((size_t)n_programs + 1),
-                           hipMemcpyDeviceToDevice, stream);
+    e = hipMemcpyAsync(d_prog_off, prog_off, sizeof(int32_t) * ((size_t)n_programs + 1),
+                       hipMemcpyDeviceToDevice, stream);
     if (e == hipSuccess)
         e = hipMemcpyAsync(d_target, target, sizeof(float) * (size_t)n_programs,
                            hipMemcpyDeviceToDevice, stream);
@@ -2007,6 +2034,7 @@ extern "C" int fs_trainer_create(fs_trainer **out, int32_t n_features, const flo
                        staged);
     rc = check_launch("trainer set-up kernels launch");
     e = hipStreamSynchronize(stream);                            // (whatever has been launched reads the staging memory)
+    t->untracked = e != hipSuccess;
     if (rc == FS_OK) {
         if (staged)
             t->max_len = staged[0];
@@ -2023,6 +2051,48 @@ extern "C" int fs_trainer_create(fs_trainer **out, int32_t n_features, const flo
     }
     *out = t;
     return FS_OK;
+}
+
+// Work that trainers' memory, the descriptors and the histograms' buffer are in, between begin_work and end_work
+// (g_train_mu held): behind that of the call before, on whichever stream, and noted for the next call and for who
+// takes a trainer's memory over.  (One event for all trainers of a call; on one stream the wait costs nothing.)
+// Not while the stream is captured: the work runs with the graph, and the trainers' memory is not kept.
+static bool captured(hipStream_t stream)
+{
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &s) == hipSuccess)
+        return s != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
+static int begin_work(BatchBuf &b, hipStream_t stream)
+{
+    if (b.last && !captured(stream))
+        FS_HIP(hipStreamWaitEvent(stream, b.last->done, 0));
+    return FS_OK;
+}
+
+static void end_work(BatchBuf &b, fs_trainer *const *trainers, int n, hipStream_t stream)
+{
+    std::shared_ptr<Work> work;
+    try {
+        work = std::make_shared<Work>();
+    } catch (const std::bad_alloc &) {
+    }
+    const bool noted = work && !captured(stream) &&
+                       hipEventCreateWithFlags(&work->done, hipEventDisableTiming) == hipSuccess &&
+                       hipEventRecord(work->done, stream) == hipSuccess;
+    for (int i = 0; i < n; ++i) {
+        if (noted)
+            trainers[i]->last = work;
+        else
+            trainers[i]->untracked = true;
+    }
+    if (noted)
+        b.last = work;
+    else
+        (void)hipGetLastError();                                 // not the next launch's error
 }
 
 // Uploads descriptors; returns the device array.
@@ -2278,12 +2348,15 @@ extern "C" int fs_train_boost(int32_t n_trainers, fs_trainer *const *trainers, i
             }
         }
         const TrainDesc *d = nullptr;
-        rc = upload_batch(n_trainers, order.data(), stream, &d);
+        rc = begin_work(b, stream);
+        if (rc == FS_OK)
+            rc = upload_batch(n_trainers, order.data(), stream, &d);
         for (size_t i = 0; i < parts.size() && rc == FS_OK; ++i) {
             rc = train_part(d + parts[i].first, parts[i], n_rounds, prm, stream);
             for (int k = 0; k < parts[i].n && rc == FS_OK; ++k)
                 order[(size_t)(parts[i].first + k)]->trees_enqueued += n_rounds;
         }
+        end_work(b, order.data(), n_trainers, stream);
         return rc;
     } catch (const std::bad_alloc &) {
         return fail(FS_ENOMEM, "out of host memory");
@@ -2349,19 +2422,11 @@ extern "C" int fs_trainer_export(const fs_trainer *t, int32_t *tree_off, int32_t
     return FS_OK;
 }
 
-extern "C" int fs_trainer_predictions(const fs_trainer *t, float *row_pred, float *prog_pred, void *stream_)
+static int read_predictions(const fs_trainer *t, float *row_pred, float *prog_pred, hipStream_t stream)
 {
-    hipStream_t stream = (hipStream_t)stream_;
-    if (!t)
-        return fail(FS_EINVAL, "fs_trainer_predictions: trainer is NULL");
-    fs_trainer *tt = const_cast<fs_trainer *>(t);
-    int rc = check_batch("fs_trainer_predictions", 1, &tt);
-    if (rc != FS_OK)
-        return rc;
-    std::lock_guard<std::mutex> lock(g_train_mu);
     if (prog_pred) {
         const TrainDesc *d = nullptr;
-        rc = upload_batch(1, &t, stream, &d);
+        int rc = upload_batch(1, &t, stream, &d);
         if (rc != FS_OK)
             return rc;
         hipLaunchKernelGGL(train_grad_kernel, dim3((unsigned)((t->h.n_programs + (int64_t)kGradThreads - 1) / kGradThreads), 1u), dim3(kGradThreads), 0,
@@ -2376,4 +2441,24 @@ extern "C" int fs_trainer_predictions(const fs_trainer *t, float *row_pred, floa
         FS_HIP(hipMemcpyAsync(row_pred, t->h.row_pred, sizeof(float) * (size_t)t->h.n_rows,
                               hipMemcpyDeviceToDevice, stream));
     return FS_OK;
+}
+
+extern "C" int fs_trainer_predictions(const fs_trainer *t, float *row_pred, float *prog_pred, void *stream_)
+{
+    hipStream_t stream = (hipStream_t)stream_;
+    if (!t)
+        return fail(FS_EINVAL, "fs_trainer_predictions: trainer is NULL");
+    fs_trainer *tt = const_cast<fs_trainer *>(t);
+    int rc = check_batch("fs_trainer_predictions", 1, &tt);
+    if (rc != FS_OK)
+        return rc;
+    std::lock_guard<std::mutex> lock(g_train_mu);
+    if (t->device < 0 || t->device >= 16)                        // (its memory is never kept)
+        return read_predictions(t, row_pred, prog_pred, stream);
+    BatchBuf &b = g_batch[t->device];
+    rc = begin_work(b, stream);
+    if (rc == FS_OK)
+        rc = read_predictions(t, row_pred, prog_pred, stream);
+    end_work(b, &tt, 1, stream);
+    return rc;
 }

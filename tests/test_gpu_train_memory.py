@@ -29,6 +29,11 @@ def free_bytes():
     return torch.cuda.mem_get_info()[0]
 
 
+def free_now():
+    import torch
+    return torch.cuda.mem_get_info()[0]
+
+
 def sets_of(n, n_programs=400, n_features=164, max_cuts=20):
     return [W.make_train_set(60 + i, n_programs + 37 * i, stmts=(1, 6), n_features=n_features, max_cuts=max_cuts)
             for i in range(n)]
@@ -159,3 +164,121 @@ def test_a_destroyed_trainers_memory_serves_the_next(api, T, n_programs, n_featu
         tr.destroy()
         held = held or free_bytes()
         assert held - free_bytes() < 1 << 20         # the second one took no more
+
+
+def keep_busy(stream, seconds=0.1):
+    """An event on `stream` behind about so much work."""
+    import torch
+    a = torch.ones(8192, 8192, device="cuda", dtype=torch.bfloat16)
+    b = torch.mm(a, a)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        for _ in range(int(seconds * 2000)):
+            torch.mm(a, a, out=b)
+        busy = torch.cuda.Event()
+        busy.record()
+    return busy, (a, b)                              # (to be kept until the stream is done)
+
+
+def stream_of_its_own():
+    """A stream whose work the default stream's does not queue up behind (streams share hardware queues)."""
+    import torch
+    one = torch.ones(64, device="cuda")
+    for _ in range(8):
+        side = torch.cuda.Stream()
+        busy, held = keep_busy(side, 0.05)
+        one.add_(1)
+        torch.cuda.current_stream().synchronize()
+        free = not busy.query()
+        torch.cuda.synchronize()
+        if free:
+            return side
+    pytest.skip("every stream tried shares a hardware queue with the default stream")
+
+
+def maker(api, ts, **kw):
+    """Creates trainers from inputs that are on the device already."""
+    import torch
+    n = ts.features.shape[1]
+    x = api.fs_pack_colblock64(torch.from_numpy(ts.features).cuda(), ts.n_rows, n)
+    off, y = torch.from_numpy(ts.prog_off.astype(np.int32)).cuda(), torch.from_numpy(ts.target.astype(np.float32)).cuda()
+    torch.cuda.synchronize()
+    return lambda max_trees: api.fs_trainer(n, x, api.FS_COLBLOCK64, ts.n_rows, off, ts.n_programs, y, ts.cut_off,
+                                            ts.cuts, max_trees=max_trees, **kw)
+
+
+@pytest.mark.parametrize("memory", ["fresh", "kept"])
+def test_creating_a_trainer_waits_for_no_other_stream(api, memory):
+    import torch
+    create = maker(api, sets_of(1, 300, 17)[0], max_depth=4)
+    side = stream_of_its_own()
+    params = api.train_params(max_depth=4, eta=0.5, lam=1.0)
+    first, other = create(50_000), create(50_000)    # 31 MB each (both alive: the histograms' buffer is large enough)
+    api.fs_train_boost([first, other], 2, params)
+    exported = other.export()
+    torch.cuda.synchronize()
+    first.destroy()
+    busy, held = keep_busy(side)
+    here = free_now()
+    again = create(50_000 if memory == "kept" else 100_000)
+    waited = busy.query()
+    assert not waited, "fs_trainer_create waited for another stream"
+    assert (here - free_now() < 16 << 20) == (memory == "kept")
+    api.fs_train_boost([again], 2, params)
+    for a, b in zip(again.export(), exported):
+        assert np.array_equal(a.view(np.uint32), b.view(np.uint32))
+    torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("call", ["boost", "predictions"])
+def test_what_a_destroyed_trainer_had_queued_is_waited_for(api, T, call):
+    """Destroyed with work queued on another stream, behind more that is still running; its memory goes to the next."""
+    import torch
+    params = api.train_params(max_depth=6, eta=0.4, lam=0.1)
+    sets = sets_of(2, 500, 23, 63)
+    create_next, create_first = (maker(api, ts, max_depth=6) for ts in sets)
+    side = stream_of_its_own()
+    first = create_first(12_000)                     # 30 MB
+    api.fs_train_boost([first], 1, params)
+    torch.cuda.synchronize()
+    busy, held = keep_busy(side)
+    here = free_now()
+    if call == "boost":
+        api.fs_train_boost([first], 19, params, stream=side)
+    else:
+        with torch.cuda.stream(side):
+            rows, progs = first.predictions(stream=side)
+    assert not busy.query()
+    first.destroy()
+    following = create_next(12_000)
+    assert here - free_now() < 16 << 20
+    api.fs_train_boost([following], 3, params)
+    ts = sets[0]
+    same_trees(following.export(), T.train(ts.features, ts.prog_off, ts.target, ts.cut_off, ts.cuts, n_rounds=3,
+                                           max_depth=6, eta=0.4, lam=0.1))
+    torch.cuda.synchronize()
+    if call == "predictions":
+        ts = sets[1]
+        exp = T.train(ts.features, ts.prog_off, ts.target, ts.cut_off, ts.cuts, n_rounds=1, max_depth=6, eta=0.4, lam=0.1)
+        assert np.array_equal(rows.cpu().numpy().view(np.uint32), exp.row_pred.view(np.uint32))
+        assert np.array_equal(progs.cpu().numpy().view(np.uint32), exp.prog_pred.view(np.uint32))
+
+
+@pytest.mark.parametrize("order", ["bins first", "trees first"])
+def test_whatever_kept_memory_holds(api, T, order):
+    """One trainer's memory is nearly all random bins, the other's nearly all trees, most of which are never
+    written: each finds what the other left where it expects to have cleared or written."""
+    bins = W.make_train_set(71, 9000, stmts=(1, 4), n_features=40, max_cuts=255)
+    trees = W.make_train_set(72, 200, stmts=(1, 3), n_features=6, max_cuts=40)
+    shapes = [(bins, 3, 2), (trees, 10, 70)]         # 3.3 and 3.1 MB
+    if order == "trees first":
+        shapes = [(trees, 10, 78), (bins, 3, 2)]     # 3.4 and 3.3 MB
+    held = None
+    for ts, depth, most in shapes + shapes:
+        tr = api.fs_trainer.from_train_set(ts, max_depth=depth, max_trees=most)
+        api.fs_train_boost([tr], 2, api.train_params(max_depth=depth, eta=0.5, lam=1.0))
+        exp = T.train(ts.features, ts.prog_off, ts.target, ts.cut_off, ts.cuts, n_rounds=2, max_depth=depth, eta=0.5, lam=1.0)
+        same_trees(tr.export(), exp)
+        tr.destroy()
+        held = held or free_bytes()
+        assert held - free_bytes() < 1 << 20         # one trainer's memory serves them all
