@@ -81,7 +81,7 @@ int fs_trainer_create(fs_trainer **out, int32_t n_features, const float *feature
  * Free a trainer (NULL allowed).  Synchronise its streams first.  Its memory stays for trainers created
  * later, up to 256 MB and 64 trainers a device.  With a device's last trainer the histograms' buffer goes
  * too, unless it is of at most 512 MB: then it stays as well.  Both are given back where a call of this
- * library that creates a model or a trainer or grows scratch runs out of memory.
+ * library would run out of device memory otherwise (the buffer only while there is no trainer).
  */
 void fs_trainer_destroy(fs_trainer *t);
 

@@ -162,7 +162,7 @@ static int ensure_scratch(DeviceCtx *ctx, int which, size_t floats, bool exact =
 static int ensure_inline(DeviceCtx *ctx, int kind)
 {
     if (!ctx->inline_dev[kind])
-        FS_HIP(hipMalloc(&ctx->inline_dev[kind], kInlineBytes));
+        FS_HIP(device_malloc(&ctx->inline_dev[kind], kInlineBytes));
     if (!ctx->inline_host[kind]) {
         ctx->inline_host[kind] = malloc(kInlineBytes);
         if (!ctx->inline_host[kind])
@@ -525,7 +525,7 @@ extern "C" int fs_workspace_reserve(size_t score_bytes, size_t topk_bytes)
         if (!s->done)
             FS_HIP(hipEventCreateWithFlags(&s->done, hipEventDisableTiming));
         if (s->cap == 0) {
-            FS_HIP(hipMalloc(&s->d_buf, kSlotBytes));
+            FS_HIP(device_malloc(&s->d_buf, kSlotBytes));
             FS_HIP(hipHostMalloc(&s->h_buf, kSlotBytes, hipHostMallocDefault));
             s->cap = kSlotBytes;
         }

@@ -1554,7 +1554,9 @@ static BatchBuf *const g_batch = new BatchBuf[16];   // never freed: trainers ma
 constexpr size_t kKeptWork = (size_t)512 << 20;
 
 // Memory of destroyed trainers stays for the next ones up to this: allocating and freeing it cost 210 us a trainer
-// (eight retrained families: 1.7 of 15 ms).
+// (eight retrained families: 1.7 of 15 ms).  Room for two jobs of the largest kind: a model of 255 000 rows of 164
+// features takes 101 MB, eight of 34 000 rows 108; and for one of more families than the paper's networks have (38).
+// Every allocation of the library takes it back before it fails.
 constexpr size_t kKeptBlocks = (size_t)256 << 20;
 constexpr size_t kMostKept = 64;
 
@@ -1582,6 +1584,17 @@ static bool give_back(BatchBuf &b)
     b.work = nullptr;
     b.work_bytes = 0;
     return true;
+}
+
+// device_malloc for who holds g_train_mu.
+static hipError_t malloc_or_give_back(BatchBuf &b, void **p, size_t bytes)
+{
+    hipError_t e = hipMalloc(p, bytes);
+    if (e == hipErrorOutOfMemory && give_back(b)) {
+        (void)hipGetLastError();
+        e = hipMalloc(p, bytes);
+    }
+    return e;
 }
 
 // Keeps a destroyed trainer's memory, or frees it, which waits for the device.  `last` may still be at work in it:
@@ -1806,11 +1819,7 @@ static int grow_work(BatchBuf &b, size_t bytes, size_t wish)
     for (const size_t size : {wish, bytes, had}) {
         if (size == 0)
             continue;
-        hipError_t err = hipMalloc(&b.work, size);
-        if (err == hipErrorOutOfMemory && free_kept(b)) {
-            (void)hipGetLastError();
-            err = hipMalloc(&b.work, size);
-        }
+        const hipError_t err = malloc_or_give_back(b, &b.work, size);
         if (err == hipSuccess) {
             b.work_bytes = size;
             break;
@@ -2119,7 +2128,7 @@ static int upload_batch(int n, const fs_trainer *const *trainers, hipStream_t st
         b.d_desc = b.h_desc = nullptr;
         b.cap = 0;
         const int cap = n < 16 ? 16 : 2 * n;
-        FS_HIP(hipMalloc((void **)&b.d_desc, sizeof(TrainDesc) * (size_t)cap));
+        FS_HIP(malloc_or_give_back(b, (void **)&b.d_desc, sizeof(TrainDesc) * (size_t)cap));
         FS_HIP(hipHostMalloc((void **)&b.h_desc, sizeof(TrainDesc) * (size_t)cap, hipHostMallocDefault));
         b.cap = cap;
     }
