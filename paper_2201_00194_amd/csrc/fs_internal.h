@@ -193,8 +193,13 @@ struct FamDesc {
 
 // Descriptors reach a kernel by value, as its last argument, where a call has few of them: a call of two or three
 // short kernels otherwise pays for another launch that only stores them (scoring and cutting 320 / 4096
-// programs 30.6 / 35.5 us, so 27.8 / 31.9).  More of them lie in device memory at `far`.
-constexpr int kNearFams = 14;
+// programs 30.6 / 35.5 us, so 27.8 / 31.9).  As many as fit do: the arguments of a kernel take 4 KB, of which 256 bytes
+// are hidden ones and some are for pointers and numbers (64 cuts of 320 entries in a call, one after the other: 4.9 us,
+// 7.2 from memory; 16 of them 4.8).  More descriptors lie in device memory at `far`.
+constexpr size_t kNearBytes = 3600;
+template <class T>
+constexpr int kNear = (int)(kNearBytes / sizeof(T));
+constexpr int kNearFams = kNear<FamDesc>;
 struct NearFams {
     FamDesc d[kNearFams];
 };
@@ -213,7 +218,7 @@ struct FamArgs3 {
     int a, b, c;
     NearFams near;
 };
-static_assert(sizeof(NearFams) <= 3600, "kernel arguments are 4 KB at most, hidden ones among them");
+static_assert(sizeof(FamArgs3) + 256 <= 4096, "kernel arguments are 4 KB at most, hidden ones among them");
 
 // What the launchers take: descriptors in device memory or, where far is null, n of them at `host`.
 template <class T>
@@ -293,7 +298,8 @@ struct TopkJoinDesc {
 __host__ __device__ inline int rank_tile_cols(int n_features) { return (n_features + 1) & ~1; }
 __host__ __device__ inline uint32_t rank_feature_offset(int f) { return (uint32_t)(f >> 1) * 256u + (uint32_t)(f & 1) * 2u; }
 
-constexpr int kNearTopk = 48, kNearMerge = 48, kNearJoins = 16;
+// (64 workgroups, 75 merges, 25 joins)
+constexpr int kNearTopk = kNear<TopkDesc>, kNearMerge = kNear<TopkMergeDesc>, kNearJoins = kNear<TopkJoinDesc>;
 struct NearTopk {
     TopkDesc d[kNearTopk];
 };

@@ -160,8 +160,8 @@ def test_small_calls_replay_from_a_hip_graph(api, oracle):
 
 @pytest.mark.parametrize("n_fams,trees", [(14, 36), (15, 36), (14, 8), (15, 8)])
 def test_descriptors_by_value_and_in_memory(api, oracle, n_fams, trees):
-    """Up to 14 families travel inside the kernels' arguments (both the treelet walk and the LDS walk), 48
-    top-k workgroups and merges; calls of other families queue up behind each other unsynchronised."""
+    """Up to 14 families travel inside the kernels' arguments (both the treelet walk and the LDS walk); calls of
+    other families queue up behind each other unsynchronised."""
     import torch
     fams = [W.make_small_family(seed=400 + i, n_programs=40 + 7 * i, stmts=(1, 5), n_trees=trees, depth=5,
                                 early_leaf_q=0.1, k=9) for i in range(n_fams)]
@@ -188,3 +188,10 @@ def test_topk_descriptors_by_value_and_in_memory(api, oracle, n_req, n, k):
     got = idx.cpu().numpy().reshape(n_req, k)
     for i, s in enumerate(scores):
         assert np.array_equal(got[i], oracle.topk(s, k)[0])
+
+
+@pytest.mark.parametrize("n_req,n,k", [(64, 300, 5), (65, 300, 5), (8, 17_000, 40), (9, 17_000, 40), (2, 65_536, 9000),
+                                       (3, 65_536, 9000), (16, 8192, 5000), (17, 8192, 5000)])
+def test_as_many_topk_descriptors_by_value_as_a_kernel_takes(api, oracle, n_req, n, k):
+    """64 workgroups of the first stage: of 64 requests, of 8 in eight slices, of 2 in 32, of 16 in four."""
+    test_topk_descriptors_by_value_and_in_memory(api, oracle, n_req, n, k)
