@@ -476,14 +476,15 @@ inline int rank_bucket(float x, const RankColumn &c, bool *tie)
     return (int)std::min(t > 0.0f ? t : 0.0f, (float)(c.buckets - 1));
 }
 
-// Tables of RankColumn for the rank coder; false where they do not fit or thresholds crowd into few buckets (32 or more
+// Tables of RankColumn for the rank coder; false where they do not fit or thresholds crowd into few buckets (16 or more
 // in one): the bucket and its steps would come near the search tree's, whose reads spread better over the LDS banks.
-// A call's time, tree / buckets (2 to 4 steps): 500 trees of depth 10, 2.1 M rows 3.91 / 3.82 ms; of depth 9, 0.5 M rows
-// 0.80 / 0.78; of depth 8, 1.6 M rows 2.19 / 2.16.
+// The coder's time over 0.5 M rows of 164 features, tree / buckets, us: thresholds of 500 trees of depth 10 175 / 143
+// (3 steps), 178 / 150 (4); of 250 of depth 9 154 / 139 (3), 156 / 149 (4), 154 / 155 (5); of 500 of depth 8
+// 151 / 138 (3), 155 / 146 (4), 151 / 153 (5).  A call on 2.1 M rows, 500 trees of depth 10: 3.91 / 3.82 ms.
 bool bucket_tables(fs_model *m, int n_features, int max_cuts, const std::vector<std::vector<float>> &per,
                    std::vector<float> *tables)
 {
-    constexpr int kMostSteps = 5, kPast = 1 << (kMostSteps - 1);
+    constexpr int kMostSteps = 4, kPast = 1 << (kMostSteps - 1);
     // two buckets a threshold if whole fours of features fit then (the coder searches four at a time), else what is left
     const int keys = (max_cuts + kPast + 3) & ~3;
     int group = kBinTableBytes / (16 + 4 * keys + 4 * max_cuts) & ~3;

@@ -64,3 +64,25 @@ def test_thresholds_in_buckets_or_search_trees(api, oracle, tune, kind, layout):
     x[:] = np.where(pick < 0.4, near, np.where(pick < 0.6, np.nextafter(near, np.float32(np.inf)),
                     np.where(pick < 0.7, rng.choice([np.inf, -np.inf, np.nan, 0.0, -0.0, 1e-45], x.shape), x)))
     check_family(oracle, fam, run_families(api, [fam], getattr(api, "FS_" + layout.upper() + ("64" if layout == "colblock" else "")))[0])
+
+
+@pytest.mark.parametrize("crowd", [6, 7, 8, 14, 15, 16, 17, 40])
+def test_buckets_of_as_many_thresholds_as_the_steps_find(api, oracle, tune, crowd):  # noqa: F811
+    """So many thresholds of one feature lie closer together than buckets are wide, the others far apart: 2^steps - 1 of
+    them are the most that buckets serve (15; beyond that the search tree)."""
+    tune(api.FS_TUNE_RANK, 1)
+    fam = W.make_small_family(seed=90 + crowd, n_programs=500, stmts=(1, 2), n_trees=6, depth=5, k=5, n_features=3)
+    rng = np.random.default_rng(crowd)
+    m, x = fam.model, fam.features
+    thr = np.array(m.threshold, np.float32)
+    for f in range(3):
+        of = rng.permutation(np.flatnonzero(np.asarray(m.split_feature) == f))
+        assert of.shape[0] > crowd + 5
+        thr[of] = np.linspace(0, 1, of.shape[0])
+        if f == 1:
+            thr[of[:crowd]] = 0.503 + np.arange(crowd) * 1e-6
+    m.threshold[:] = thr
+    near = thr[rng.integers(0, thr.shape[0], x.shape)]
+    x[:] = np.where(rng.random(x.shape) < 0.5, np.where(rng.random(x.shape) < 0.5, near, np.nextafter(near, np.float32(-1))),
+                    0.503 + rng.integers(-3, 45, x.shape) * 1e-6)
+    check_family(oracle, fam, run_families(api, [fam], api.FS_COLBLOCK64)[0])
