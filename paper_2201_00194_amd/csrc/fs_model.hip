@@ -967,10 +967,11 @@ extern "C" int fs_model_create(fs_model **out, int32_t n_features, int32_t n_tre
                     limits.cost = 13.5 * (double)n_trees * (double)shapes.max_depth() + 3.0 * (double)n_features;
                 }
                 // Every segment codes the rows anew, the rank walk codes them once.  Time of treelets over the rank
-                // walk's, perfect trees of depth 8, 5 to 16 000 tiles, both layouts, models that the other limits
-                // take: below 400 columns in all 0.20 to 0.98 on 100 to 300 features (32 models, 650 calls); on 24
-                // to 64 features 0.34 to 1.30 (17 models; 11 of 340 calls lose more than 2 %, ten of them of
-                // 24 features); from 400 columns 0.58 to 1.37 (6 models; 33 of 130 calls lose more than 2 %).
+                // walk's, perfect trees of depth 8, 36 to 500 of them, 24 to 250 features, 5 to 16 000 tiles, both
+                // layouts, models that the other limits take: below 400 columns in all 0.20 to 1.41, geometric mean
+                // 0.58 (61 models; 65 of 1098 calls lose more than 2 %, 51 of them of 1000 to 2500 tiles, 51 of 24 to
+                // 64 features); from 400 columns 0.53 to 1.76, mean 1.01 (16 models; 135 of 288 calls lose more than
+                // 2 %; three models of three segments with double-buffered tables 0.53 to 1.25, mean 0.78).
                 if (ranks_pay) {
                     limits.cols = kTreeletMostRankCols;
                     limits.ranks = true;

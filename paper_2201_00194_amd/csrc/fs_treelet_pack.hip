@@ -474,9 +474,10 @@ bool build_treelets(int n_features, int n_trees, const TreeShapes &shape, const 
     auto spread_fits = [&](int stride) { return 12 * kb(4 * stride) <= (long)kTreeletLdsWhole - beside; };
     bool pair_coder = true;
     // Where the rank walk could take the model, single tables only with chunks of eight trees and about one column a
-    // feature.  Treelets / rank walk, perfect trees of depth 8, 2400 to 960 000 rows: 190 to 220 features,
-    // 180 to 200 trees 0.67 to 0.84; 250 features, room for four trees a chunk, 200 and 250 trees 0.87 to 1.15; 110 and
-    // 120 features of two columns each, 220 and 200 trees 0.77 to 1.07.
+    // feature.  Treelets / rank walk, perfect trees of depth 8, 3800 to 1 M rows: 200 and 220 features, 160 and
+    // 230 trees 0.53 to 0.87, mean 0.69; 250 features, room for four trees a chunk, 100 to 230 trees 0.48 to 1.32, mean
+    // 0.85; 80 and 100 features of two to three columns each, 160 to 300 trees 0.71 to 1.35, mean 0.92; 24 to 64 features
+    // of three and more, 230 and 300 trees 0.78 to 1.60, mean 1.02.
     bool single = true;
     if (limits.ranks && out->pair_ok) {
         single = 4 * all_cols <= 5 * n_used;
