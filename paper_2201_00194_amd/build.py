@@ -18,8 +18,8 @@ FLAGS = [
     "-ffp-contract=off",                     # sums must stay plain sequential adds
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     # A launch's first arguments arrive in scalar registers instead of through a load: most launches here are
-    # chains of latencies of 2 to 8 us (one training iteration of one family 6.19 -> 5.98 ms, the scoring of 320
-    # programs 32.0 -> 30.6 us).
+    # chains of latencies of 2 to 8 us (a tuning iteration of one family, 40 rounds among it, 6.19 -> 5.98 ms, the
+    # scoring of 320 programs 32.0 -> 30.6 us).
     "-mllvm", "-amdgpu-kernarg-preload-count=16",
     "-mllvm", "-disable-promote-alloca-to-lds",   # the traversal kernel owns LDS from address 0
     "-Wall", "-Wno-unused-command-line-argument",

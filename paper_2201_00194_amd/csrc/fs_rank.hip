@@ -282,7 +282,7 @@ static __device__ __forceinline__ void count_up(uint32_t counter, int lane)
 }
 
 // Until the counter has reached `count`.  (Ends: the wavefronts of a workgroup are all on the compute unit, and
-// each counts up as often as it is waited for, see rank_slot.)
+// each counts up as often as it is waited for: see the turns of traverse_rank_kernel.)
 static __device__ __forceinline__ void wait_for(uint32_t counter, uint32_t count)
 {
 #if defined(__HIP_DEVICE_COMPILE__)

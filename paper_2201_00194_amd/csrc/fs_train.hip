@@ -14,10 +14,11 @@
 //   hist, split  histograms and best cuts of the root
 //   per level:   move (every workgroup decides its node for itself: best feature, split or leaf; the node's
 //                records go to its children's segments, rows of leaves take the leaf's value), hist (LDS
-//                histograms of the child with the smaller curvature, sixteen features per workgroup; the
+//                histograms of the child with fewer rows, sixteen features per workgroup; the
 //                other child is the parent minus that one, exactly; a feature's most frequent bin is
 //                never counted, it is the node's total minus the rest) or, for few rows, both in one launch
-//                (grow); split (adds up the parts of nodes whose rows were dealt to several workgroups,
+//                (grow: from the parent's records, of the child with the smaller curvature, as the children's
+//                rows are not counted yet); split (adds up the parts of nodes whose rows were dealt to several workgroups,
 //                subtracts, searches the cuts of both children)
 //   last level:  finish (decides its nodes; rows take the leaves' values)
 //   (one more workgroup of the next round's first hist: heap -> flat model arrays, heap cleared)
@@ -82,8 +83,8 @@ struct TrainDesc {
     float *prog_pred;
     int4 *rec[2];              // {row, gradient in fixed point, curvature, output so far (bits)} of every row, grouped
                                // by the node of a level; levels alternate between the two
-    int4 *seg;                 // per split node of the heap: {rows gone left, rows gone right, first
-                               // position, end}; zero if the node is not split.  The left child's
+    int4 *seg;                 // per node of the heap: {rows gone left, rows gone right, first position, end}; no rows
+                               // gone while the node is not split, no segment where there is no node.  The left child's
                                // records fill the segment from its front, the right child's from its back
     int32_t *h_slot;           // where in `hist` the node's histograms are
     unsigned long long *hist;  // [slot][feature][bin]: complete histograms, what the next level subtracts from

@@ -41,7 +41,8 @@ def test_edges_of_rows_and_feature_groups(api, T, tune, packed, n, n_features):
 
 
 @pytest.mark.parametrize("n", [65_536, 65_537])
-def test_both_sides_of_the_partition_workgroup(api, T, n):
+def test_whole_moving_workgroups_and_a_row_more(api, T, n):
+    """64 workgroups of 1024 rows move the root's records."""
     check(api, T, rows_set(7, n, 5, 31), rounds=2, max_depth=3, eta=0.5, lam=1.0)
 
 
