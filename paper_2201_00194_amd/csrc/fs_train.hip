@@ -105,6 +105,15 @@ struct TrainDesc {
     float bias;
 };
 
+// A trainer's descriptor as kernels read it: what a launch finds in constant memory are pointers to global memory, so that
+// everything behind them is read by global and scalar loads.  (Through a plain pointer those were flat loads, which count as
+// LDS reads too: waits for all of both kinds, one after the other, in launches that are chains of latencies.)
+#if defined(__HIP_DEVICE_COMPILE__)
+typedef __attribute__((address_space(4))) const TrainDesc Desc;
+#else
+typedef const TrainDesc Desc;
+#endif
+
 struct Params {
     double eta, lambda, min_gain, inv_scale;
     long long mcw;
@@ -311,7 +320,7 @@ train_export_kernel(const TrainDesc d, int32_t *out, int64_t cap)
 
 // The heap of the tree to grow and the sums of the round to come (one workgroup per trainer).  What belongs
 // to a node below the root is written when its parent is split.
-__device__ __forceinline__ void begin_tree(const TrainDesc &d, int turn)
+__device__ __forceinline__ void begin_tree(Desc &d, int turn)
 {
     for (int i = threadIdx.x; i < kHeapNodes; i += blockDim.x) {
         d.decision[i] = make_int4(kAbsent, 0, 0, 0);
@@ -326,7 +335,7 @@ __device__ __forceinline__ void begin_tree(const TrainDesc &d, int turn)
 __global__ void __launch_bounds__(512)
 train_begin_kernel(const TrainDesc *__restrict__ descs)
 {
-    const TrainDesc &d = descs[blockIdx.x];
+    Desc &d = FS_CONST(TrainDesc, descs)[blockIdx.x];
     begin_tree(d, 0);
     if (threadIdx.x == 0)
         d.root[1] = {0, 0, 0ull};
@@ -347,7 +356,7 @@ constexpr int kGradThreads = 64;
 __global__ void __launch_bounds__(kGradThreads)
 train_grad_kernel(const TrainDesc *__restrict__ descs, float grad_scale, int with_grad, int turn)
 {
-    const TrainDesc &d = descs[blockIdx.y];
+    Desc &d = FS_CONST(TrainDesc, descs)[blockIdx.y];
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     long long G = 0, H = 0;
     unsigned long long A = 0;                        // |gradient| x rows: bounds every histogram sum
@@ -486,7 +495,7 @@ __device__ __forceinline__ int counts_left(long long l, long long r) { return l 
 
 // Totals of a node; `turn` says which of the root's sums the round uses.  (No launch that calls this writes the totals
 // of the level's nodes: with a uniform node they are scalar loads.)
-__device__ __forceinline__ void node_sums(const TrainDesc &d, int node, int turn, long long &G, long long &H)
+__device__ __forceinline__ void node_sums(Desc &d, int node, int turn, long long &G, long long &H)
 {
     if (node == 0) {
         G = *FS_CONST(long long, &d.root[turn].G);
@@ -510,7 +519,7 @@ __device__ __forceinline__ void node_sums(const TrainDesc &d, int node, int turn
 // round of double-precision divisions instead of four.
 constexpr int kCutScratchBytes = 64 * (8 + 8 + 4);
 
-__device__ __forceinline__ void wave_best_cut(const TrainDesc &d, const Params &prm, int node, int turn, int f,
+__device__ __forceinline__ void wave_best_cut(Desc &d, const Params &prm, int node, int turn, int f,
                                               int pair, int lane, long long (&g)[4], long long (&h)[4],
                                               unsigned char *scratch)
 {
@@ -651,7 +660,7 @@ __device__ __forceinline__ float wave_max_f(float v)
 //    all are evaluated).  The gain itself is that sum minus a term that is the same for all cuts
 //    and at most twice the sum, so a cut that wins after the rounding of double arithmetic is
 //    within 2^-50 of the largest and never dropped.
-__device__ __forceinline__ void wave_best_cut_packed(const TrainDesc &d, const Params &prm, int node, int turn,
+__device__ __forceinline__ void wave_best_cut_packed(Desc &d, const Params &prm, int node, int turn,
                                                      int f, int pair, int lane, unsigned long long (&v)[4], int hb)
 {
     long long G, H;
@@ -781,7 +790,7 @@ constexpr int kHistThreads = 512;
 constexpr int64_t kGrowRows = 49152;    // of a batch
 static_assert(kBins * 8 >= kCutScratchBytes, "room for the cut search's scratch");
 
-__device__ __forceinline__ bool is_packed(const TrainDesc &d, int turn, int hb)
+__device__ __forceinline__ bool is_packed(Desc &d, int turn, int hb)
 {
     return hb > 0 && *FS_CONST(unsigned long long, &d.root[turn].abs_q) < (1ull << (63 - hb));
 }
@@ -811,7 +820,7 @@ __device__ __forceinline__ int pieces_of(int count, int shift)
 
 // Piece number `index` of the level's nodes (every wavefront finds it for itself: one 16-byte load per
 // parent and a scan).
-__device__ __forceinline__ bool find_piece(const TrainDesc &d, int level, int shift, int index, int lane, Piece &it)
+__device__ __forceinline__ bool find_piece(Desc &d, int level, int shift, int index, int lane, Piece &it)
 {
     if (level == 0) {
         it = {0, 0, d.n_rows, index};
@@ -852,7 +861,7 @@ __device__ __forceinline__ bool find_piece(const TrainDesc &d, int level, int sh
 }
 
 // The same over the counted children of the level.
-__device__ __forceinline__ bool find_counted(const TrainDesc &d, int level, int shift, int index, int lane, Piece &it)
+__device__ __forceinline__ bool find_counted(Desc &d, int level, int shift, int index, int lane, Piece &it)
 {
     if (level == 0) {
         it = {0, 0, d.n_rows, index};
@@ -936,7 +945,7 @@ struct Bins4 {                // four consecutive bins of a lane
 
 // Words of a node's histogram of feature f; at the root and for counted children a place of their own,
 // for the other child its parent's.  `pair`: number of the parent within its level.
-__device__ __forceinline__ int64_t hist_at(const TrainDesc &d, int level, int pair, int which, int f)
+__device__ __forceinline__ int64_t hist_at(Desc &d, int level, int pair, int which, int f)
 {
     const int n_pairs = level > 0 ? 1 << (level - 1) : 0;
     const int slot = level == 0 ? 0 : which ? *FS_CONST(int32_t, d.h_slot + n_pairs - 1 + pair) : n_pairs + pair;
@@ -952,7 +961,7 @@ struct Pair {
 
 // Cuts of one child: `which` = 0 the counted node, 1 its sibling; `own`: the counted node's bins.
 template <bool PACKED>
-__device__ __forceinline__ void search_child(const TrainDesc &d, const Params &prm, int level, int turn, const Pair &it,
+__device__ __forceinline__ void search_child(Desc &d, const Params &prm, int level, int turn, const Pair &it,
                                              int which, bool store, int f, int lane, Bins4<PACKED> &own, int hb,
                                              unsigned char *scratch)
 {
@@ -977,7 +986,7 @@ __device__ __forceinline__ void search_child(const TrainDesc &d, const Params &p
 }
 
 // What the next level needs of two siblings: their places in `hist` and their segments, nothing moved yet.
-__device__ __forceinline__ void open_children(const TrainDesc &d, int level, const Pair &it)
+__device__ __forceinline__ void open_children(Desc &d, int level, const Pair &it)
 {
     const int parent = (1 << (level - 1)) - 1 + it.pair, left = 2 * parent + 1;
     const int4 s = d.seg[parent];
@@ -1003,7 +1012,7 @@ __device__ __forceinline__ float leaf_value(long long G, long long H, const Para
 
 // Decides node `node` of the level, by one wavefront (lanes over the features): largest gain, lowest
 // feature on ties.  Everybody waits for this, so it reads and reduces no more than that.
-__device__ __forceinline__ Decision wave_decide(const TrainDesc &d, int level, const Params &prm, int node, int lane)
+__device__ __forceinline__ Decision wave_decide(Desc &d, int level, const Params &prm, int node, int lane)
 {
     double gain = 0.0;
     int feature = -1, cut = 0;                                   // cut * 2 + count_left
@@ -1050,7 +1059,7 @@ __device__ __forceinline__ Decision wave_decide(const TrainDesc &d, int level, c
 }
 
 // Values of the leaves that a decision makes.
-__device__ __forceinline__ void leaf_values(const TrainDesc &d, int level, int turn, const Params &prm, int node,
+__device__ __forceinline__ void leaf_values(Desc &d, int level, int turn, const Params &prm, int node,
                                             Decision &r)
 {
     if (r.split && level + 1 < prm.max_depth)
@@ -1067,7 +1076,7 @@ __device__ __forceinline__ void leaf_values(const TrainDesc &d, int level, int t
 }
 
 // What later launches read of a decided node (one lane of one of its workgroups).
-__device__ __forceinline__ void note_decision(const TrainDesc &d, int level, int turn, const Params &prm, int node,
+__device__ __forceinline__ void note_decision(Desc &d, int level, int turn, const Params &prm, int node,
                                               const Decision &r)
 {
     if (!r.split) {
@@ -1094,7 +1103,7 @@ __device__ __forceinline__ void note_decision(const TrainDesc &d, int level, int
 
 // Heap -> flat arrays, appended to the model; then the heap is the next tree's (one workgroup of
 // kHistThreads).  Ids are local to the tree in breadth-first order, which is the heap's order.  `ids`: LDS.
-__device__ __forceinline__ void emit_tree(const TrainDesc &d, int max_depth, int turn, int *ids)
+__device__ __forceinline__ void emit_tree(Desc &d, int max_depth, int turn, int *ids)
 {
     constexpr int kPer = (kHeapNodes + kHistThreads) / kHistThreads;
     __shared__ int s_sum[kHistThreads / 64];
@@ -1157,7 +1166,7 @@ __global__ void __launch_bounds__(kHistThreads)
 train_emit_kernel(const TrainDesc *__restrict__ descs, int max_depth, int turn)
 {
     __shared__ int ids[kHeapNodes];
-    emit_tree(descs[blockIdx.x], max_depth, turn, ids);
+    emit_tree(FS_CONST(TrainDesc, descs)[blockIdx.x], max_depth, turn, ids);
 }
 
 struct HistLds {
@@ -1169,7 +1178,7 @@ struct HistLds {
 // piece's rows, ALL of them (the piece is the node's) or those that go to it (the piece is its parent's, which
 // is decided here, while the first rows and their bins are on their way).
 template <bool PACKED, bool ALL>
-__device__ __forceinline__ void hist_run(const TrainDesc &d, HistLds &s, const Piece &it, int child, int pair, int shift,
+__device__ __forceinline__ void hist_run(Desc &d, HistLds &s, const Piece &it, int child, int pair, int shift,
                                          int group, int base, int hb, const Params &prm)
 {
     constexpr int NF = PACKED ? kHistFeats : kHistFeats / 2;
@@ -1194,10 +1203,13 @@ __device__ __forceinline__ void hist_run(const TrainDesc &d, HistLds &s, const P
     }
     for (int j = threadIdx.x; j < kHistWords; j += kHistThreads)
         lds[j] = 0ull;
+    auto hots = FS_CONST(int32_t, d.hot_bin + f0);
     int hot[NF];
 #pragma unroll
-    for (int k = 0; k < NF; ++k)
-        hot[k] = k < nf ? d.hot_bin[f0 + k] : 256;               // 256: no bin, nothing is skipped
+    for (int k = 0; k < NF; ++k) {
+        hot[k] = hots[min(k, nf - 1)];                           // (no branch: sixteen scalar loads at once)
+        hot[k] = k < nf ? hot[k] : 256;                          // 256: no bin, nothing is skipped
+    }
     if (i < n)
         w = *(words_at)(bins + r.x * row_bytes);
     if (!ALL && threadIdx.x < 64) {
@@ -1255,7 +1267,7 @@ __device__ __forceinline__ void hist_run(const TrainDesc &d, HistLds &s, const P
 }
 
 template <bool ALL>
-__device__ __forceinline__ void hist_both(const TrainDesc &d, HistLds &s, const Piece &it, int child, int pair, int turn,
+__device__ __forceinline__ void hist_both(Desc &d, HistLds &s, const Piece &it, int child, int pair, int turn,
                                           int shift, int group, int hb, const Params &prm)
 {
     if (is_packed(d, turn, hb)) {
@@ -1274,7 +1286,7 @@ train_hist_kernel(const TrainDesc *__restrict__ descs, int level, int turn, int 
 {
     __shared__ __align__(16) unsigned long long lds[kHistWords];
     HistLds &s = *(HistLds *)lds;
-    const TrainDesc &d = descs[blockIdx.y];
+    Desc &d = FS_CONST(TrainDesc, descs)[blockIdx.y];
     if ((int)blockIdx.z == emit) {
         if (blockIdx.x == 0)
             emit_tree(d, max_depth, turn ^ 1, (int *)lds);
@@ -1301,7 +1313,7 @@ constexpr int kMoveShift = 10;
 static_assert(kMoveRows == 1 << kMoveShift, "rows of a moving workgroup");
 
 template <bool LAST>
-__device__ __forceinline__ void move_rows(const TrainDesc &d, Decision &s_dec, const Piece &it, int level, int turn,
+__device__ __forceinline__ void move_rows(Desc &d, Decision &s_dec, const Piece &it, int level, int turn,
                                           const Params &prm)
 {
     __shared__ int s_left[kHistThreads / 64], s_right[kHistThreads / 64];
@@ -1387,7 +1399,7 @@ train_grow_kernel(const TrainDesc *__restrict__ descs, int level, int turn, int 
     __shared__ __align__(16) HistLds s;
     const int lane = threadIdx.x & 63;
     Piece it;
-    const TrainDesc &d = descs[blockIdx.y];
+    Desc &d = FS_CONST(TrainDesc, descs)[blockIdx.y];
     if ((int)blockIdx.z < layers) {
         const int index = (int)(blockIdx.z * gridDim.x + blockIdx.x);
         if (index < movers && find_piece(d, level, kMoveShift, index, lane, it))
@@ -1405,7 +1417,7 @@ __global__ void __launch_bounds__(kHistThreads)
 train_move_kernel(const TrainDesc *__restrict__ descs, int level, int turn, Params prm)
 {
     __shared__ Decision dec;
-    const TrainDesc &d = descs[blockIdx.y];
+    Desc &d = FS_CONST(TrainDesc, descs)[blockIdx.y];
     Piece it;
     if (find_piece(d, level, kMoveShift, blockIdx.x, threadIdx.x & 63, it))
         move_rows<false>(d, dec, it, level, turn, prm);
@@ -1416,7 +1428,7 @@ __global__ void __launch_bounds__(kHistThreads)
 train_finish_kernel(const TrainDesc *__restrict__ descs, int level, int turn, Params prm)
 {
     __shared__ Decision dec;
-    const TrainDesc &d = descs[blockIdx.y];
+    Desc &d = FS_CONST(TrainDesc, descs)[blockIdx.y];
     Piece it;
     if (find_piece(d, level, kMoveShift, blockIdx.x, threadIdx.x & 63, it))
         move_rows<true>(d, dec, it, level, turn, prm);
@@ -1432,7 +1444,7 @@ constexpr int kSplitWaves = 4;
 constexpr int kSplitWideNodes = 4;
 
 template <bool PACKED>
-__device__ __forceinline__ void split_run(const TrainDesc &d, const Params &prm, unsigned long long *lds,
+__device__ __forceinline__ void split_run(Desc &d, const Params &prm, unsigned long long *lds,
                                           const Pair &it, int level, int turn, int shift, int f, int hb)
 {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
@@ -1474,7 +1486,7 @@ __global__ void __launch_bounds__(64 * kSplitWaves, 6)
 train_split_kernel(const TrainDesc *__restrict__ descs, int level, int turn, int shift, int hb, int grown, Params prm)
 {
     extern __shared__ __align__(16) unsigned long long lds[];
-    const TrainDesc &d = descs[blockIdx.z];
+    Desc &d = FS_CONST(TrainDesc, descs)[blockIdx.z];
     const int f = blockIdx.x, pair = blockIdx.y;
     if (f >= d.n_features)
         return;
