@@ -49,10 +49,14 @@ static __device__ __forceinline__ void keep_order()
 #endif
 }
 
+// All loads are there.  (The builtin, so that the compiler knows it too: behind a wait of inline assembly it put waits of
+// its own in front of a batch's searches, which were waits for the values of the next batch as well.)
 static __device__ __forceinline__ void dma_wait()
 {
 #if defined(__HIP_DEVICE_COMPILE__)
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0)
+    asm volatile("" ::: "memory");
 #endif
 }
 
