@@ -1,11 +1,12 @@
 // Byte-rank treelet format: what fs_treelet.hip walks and fs_treelet_pack.hip builds.
 //
 // A split "x[f] < thr" only asks how x[f] orders against the thresholds the model itself uses on
-// feature f.  With a feature's distinct thresholds sorted, rank(x) = number of them <= x and
-// rank(thr) = 1 + position of thr,  x < thr  <=>  rank(x) < rank(thr)  exactly.  Up to
+// feature f.  With a feature's distinct thresholds sorted downwards, rank(x) = number of them > x and
+// rank(thr) = 1 + position of thr,  x < thr  <=>  rank(x) >= rank(thr)  exactly; a NaN is below nothing,
+// as it has rank 0 (counted upwards it would need a test of its own).  Up to
 // kTreeletMaxCuts thresholds a rank fits a byte; a feature with more is split into several
 // columns, each with its own piece of the sorted thresholds (x is below threshold p of a piece iff
-// its rank inside that piece is below p + 1, whatever the other pieces say).  Features the model
+// its rank inside that piece is above p, whatever the other pieces say).  Features the model
 // does not use have no column.
 //
 // Columns in LDS: column c of four 64-row tiles is the 256 bytes at c*256, row l of tile t in byte
@@ -14,11 +15,11 @@
 //
 // A treelet entry is 8 bytes {w0, w1}: a split node and its two children.
 //     w0 = threshold rank (bits 0-7) | column (8-15) | block of the four outcomes (16-31)
-//     w1 = left child: rank (0-7), column (8-15); right child: rank (16-23), column (24-31)
-// A row goes right where its rank >= the threshold's; with b0, b1 the two decisions the walk goes
+//     w1 = right child: rank (0-7), column (8-15); left child: rank (16-23), column (24-31)
+// A row goes left where its rank >= the threshold's; with b0, b1 the two decisions (1 = left) the walk goes
 // on at entry 4*block + 2*b0 + b1 of the chunk.  Every walk of a chunk takes the chunk's `steps`
 // steps (two levels each); what the last one yields indexes the chunk's value table.  A leaf above
-// that level is an entry that steps onto itself: rank 0 (always right) or 255 (never: ranks stay
+// that level is an entry that steps onto itself: rank 0 (always left) or 255 (never: ranks stay
 // below) force both decisions to its own position in its block, and the value table holds its
 // value at its entry index.  Where a treelet's child is a leaf its own decision is forced too.
 //
@@ -35,7 +36,6 @@ namespace fs {
 
 constexpr int kTreeletMaxCuts = 254;          // ranks 0..254; 255 is above every rank
 constexpr int kTreeletMaxCols = 255;
-constexpr uint32_t kTreeletNanRank = 254;     // >= every threshold's rank: NaN goes right
 constexpr int kTreeletLds = 80 * 1024;        // two workgroups per compute unit
 constexpr int kTreeletLdsWhole = 160 * 1024;
 // The coder moves the tables of a batch, up to 16 columns, in whole KB: what it reads behind the last column's.
@@ -72,11 +72,11 @@ struct TreeletChunk {
     uint32_t id_off;        // into the id map: caller's node id of value index v at [id_off + v]
 };
 
-// A column and how its ranks are found.  bucket(x) = clamp((uint32)(x * scale + offset)), one fused
-// multiply-add, truncated, never decreases with x; the column's table gives for every bucket the
-// number of thresholds in lower buckets (all <= x) and `steps` bisection steps count those of x's own
-// bucket (2^steps - 1 of them at most; thresholds of higher buckets are above x, so a probe past the
-// bucket's end counts nothing).  Table: `buckets` bytes, then the sorted thresholds, NaN behind.
+// A column and how its ranks are found.  bucket(x) = x * scale + offset (one fused multiply-add, scale below 0) clamped
+// to [0, 1], NaN to 0, times the number of buckets less one, rounded to the nearest integer: it never increases with x.
+// The column's table gives for every bucket the number of thresholds in lower buckets (all > x) and `steps` bisection
+// steps count those of x's own bucket (2^steps - 1 of them at most; thresholds of higher buckets are not above x, so a
+// probe past the bucket's end counts nothing).  Table: `buckets` bytes, then the thresholds downwards, NaN behind.
 struct TreeletCol {
     int32_t feature;
     float scale, offset;

@@ -63,15 +63,15 @@ static __device__ __forceinline__ void dma_wait()
 template <int N> struct Int { static constexpr int value = N; };
 
 // ---- coding ------------------------------------------------------------------------------------
-// The last step of four searches: r[k] += (key[k] <= x[k]).
-static __device__ __forceinline__ void count_below(const float *key, const float *x, uint32_t *r)
+// The last step of four searches, r[k] += (key[k] > x[k]).
+static __device__ __forceinline__ void count_above(const float *key, const float *x, uint32_t *r)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     uint64_t m0, m1, m2, m3;
-    asm("v_cmp_le_f32_e64 %[m0], %[k0], %[x0]\n\t"
-        "v_cmp_le_f32_e64 %[m1], %[k1], %[x1]\n\t"
-        "v_cmp_le_f32_e64 %[m2], %[k2], %[x2]\n\t"
-        "v_cmp_le_f32_e64 %[m3], %[k3], %[x3]\n\t"
+    asm("v_cmp_gt_f32_e64 %[m0], %[k0], %[x0]\n\t"
+        "v_cmp_gt_f32_e64 %[m1], %[k1], %[x1]\n\t"
+        "v_cmp_gt_f32_e64 %[m2], %[k2], %[x2]\n\t"
+        "v_cmp_gt_f32_e64 %[m3], %[k3], %[x3]\n\t"
         "v_addc_co_u32_e64 %[r0], vcc, %[r0], 0, %[m0]\n\t"
         "v_addc_co_u32_e64 %[r1], vcc, %[r1], 0, %[m1]\n\t"
         "v_addc_co_u32_e64 %[r2], vcc, %[r2], 0, %[m2]\n\t"
@@ -86,6 +86,57 @@ static __device__ __forceinline__ void count_below(const float *key, const float
 #endif
 }
 
+// The same of the four tiles of a column: the ranks as the bytes of a word, written there by the additions themselves.
+static __device__ __forceinline__ uint32_t count_above_bytes(const float *key, const float *x, const uint32_t *r, uint32_t zero)
+{
+    uint32_t word = 0;
+#if defined(__HIP_DEVICE_COMPILE__)
+    uint64_t m1, m2, m3;
+    asm("v_cmp_gt_f32_e32 vcc, %[k0], %[x0]\n\t"
+        "v_cmp_gt_f32_e64 %[m1], %[k1], %[x1]\n\t"
+        "v_cmp_gt_f32_e64 %[m2], %[k2], %[x2]\n\t"
+        "v_cmp_gt_f32_e64 %[m3], %[k3], %[x3]\n\t"
+        "v_addc_co_u32_sdwa %[w], vcc, %[r0], %[z], vcc dst_sel:BYTE_0 dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:DWORD\n\t"
+        "s_mov_b64 vcc, %[m1]\n\t"
+        "s_nop 0\n\t"
+        "v_addc_co_u32_sdwa %[w], vcc, %[r1], %[z], vcc dst_sel:BYTE_1 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:DWORD\n\t"
+        "s_mov_b64 vcc, %[m2]\n\t"
+        "s_nop 0\n\t"
+        "v_addc_co_u32_sdwa %[w], vcc, %[r2], %[z], vcc dst_sel:BYTE_2 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:DWORD\n\t"
+        "s_mov_b64 vcc, %[m3]\n\t"
+        "s_nop 0\n\t"
+        "v_addc_co_u32_sdwa %[w], vcc, %[r3], %[z], vcc dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:DWORD\n\t"
+        "s_nop 1"
+        : [w] "=&v"(word), [m1] "=&s"(m1), [m2] "=&s"(m2), [m3] "=&s"(m3)
+        : [k0] "v"(key[0]), [k1] "v"(key[1]), [k2] "v"(key[2]), [k3] "v"(key[3]), [x0] "v"(x[0]), [x1] "v"(x[1]),
+          [x2] "v"(x[2]), [x3] "v"(x[3]), [r0] "v"(r[0]), [r1] "v"(r[1]), [r2] "v"(r[2]), [r3] "v"(r[3]), [z] "v"(zero)
+        : "vcc");
+#else
+    (void)key; (void)x; (void)r; (void)zero;
+#endif
+    return word;
+}
+
+// A lane's offset as it is at this point: what the compiler widens to 64 bits ahead of a loop costs every load behind a
+// scalar base an addition.
+static __device__ __forceinline__ uint32_t here(uint32_t v)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+v"(v));
+#endif
+    return v;
+}
+
+// x * scale + offset, clamped to [0, 1], NaN to 0.
+static __device__ __forceinline__ float fma_clamped(float x, float scale, float offset)
+{
+    float u = 0.0f;
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm("v_fma_f32 %0, %1, %2, %3 clamp" : "=v"(u) : "v"(x), "s"(scale), "v"(offset));
+#endif
+    return u;
+}
+
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
 // One wavefront codes columns in batches of NC columns x T tiles (batch wave, wave + n_waves, ...),
@@ -93,6 +144,11 @@ typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 // bisection of the bucket's few.  `slot` is LDS of this wavefront only: the tables of the batch in
 // work and, where `halves` is 2, of the next one, `half_bytes` each.  The next batch's values (and tables)
 // are on their way while a batch is searched.
+//
+// Vector issue is what a search costs the walks of the other workgroup, so it takes nine instructions where it took
+// sixteen, and of the cheap ones (and, add, multiply-add with vector operands: 3 clocks, all others 4.5 to 5) where it can:
+// LDS addresses are multiply-adds of denormal floats, which carry integers as they are; the clamp is a modifier; NaN needs no
+// test; ranks are added up in their bytes; loads have a scalar base.
 template <int T, int NC>
 __device__ __forceinline__ void code_columns(const FamDesc &d, const TreeletSegment &m, int tile_first,
                                              int n_tiles, int wave, int n_waves, int lane, uint32_t slot,
@@ -101,19 +157,38 @@ __device__ __forceinline__ void code_columns(const FamDesc &d, const TreeletSegm
     constexpr int kChains = T * NC;
     static_assert(kChains % 4 == 0, "searches go in fours");
     const int C = m.n_cols, F = d.n_features;
-    const uint32_t stride = (uint32_t)m.table_stride, last_bucket = (uint32_t)m.buckets - 1u;
+    const uint32_t stride = (uint32_t)m.table_stride, buckets = (uint32_t)m.buckets;
     auto cols = FS_CONST(TreeletCol, m.cols);
-    auto X = FS_GLOBAL(const float, d.features);
     const int n_batches = (C + NC - 1) / NC;
     const bool rowmajor = d.layout == FS_ROWMAJOR;
-    // this lane's rows (row-major input); the last tile's missing rows repeat the last row
-    int64_t row_at[T];
-    if (rowmajor) {
+    // Tiles of both layouts start 64 * F values apart.  What is left of an address is a scalar offset of the feature and
+    // these of the lane's rows (row-major: the last tile's missing rows repeat the last row).
+    auto X = FS_GLOBAL(const uint8_t, d.features) + (int64_t)tile_first * F * 256;
+    const uint32_t feature_bytes = rowmajor ? 4u : 256u;
+    uint32_t row_at[T];
 #pragma unroll
-        for (int t = 0; t < T; ++t)
-            row_at[t] = (int64_t)min((tile_first + t) * 64 + lane, d.n_rows - 1) * F;
-    }
+    for (int t = 0; t < T; ++t)
+        row_at[t] = rowmajor ? (uint32_t)min(64 * t + lane, d.n_rows - 1 - 64 * tile_first) * 4u * (uint32_t)F
+                             : (uint32_t)min(t, n_tiles - 1 - tile_first) * 256u * (uint32_t)F + 4u * (uint32_t)lane;
     auto col_of = [&](int b, int j) { return min(b * NC + j, C - 1); };   // past the last: it again
+    // What a batch's searches need, asked for at once and before the wait for its values.
+    struct Batch { float scale[NC], offset[NC]; int steps[NC]; };
+    auto read_batch = [&](int b) {
+        Batch q;
+#pragma unroll
+        for (int j = 0; j < NC; ++j) {
+            const int c = col_of(b, j);
+            q.scale[j] = cols[c].scale;
+            q.offset[j] = cols[c].offset;
+            q.steps[j] = cols[c].steps;
+        }
+#if defined(__HIP_DEVICE_COMPILE__)
+#pragma unroll
+        for (int j = 0; j < NC; ++j)
+            asm volatile("" : "+s"(q.scale[j]), "+s"(q.offset[j]), "+s"(q.steps[j]));
+#endif
+        return q;
+    };
     auto fetch_values = [&](int b, float (&x)[kChains]) {
         if (rowmajor) {
             // four neighbouring features of a row are one load
@@ -124,33 +199,26 @@ __device__ __forceinline__ void code_columns(const FamDesc &d, const TreeletSegm
                                   cols[col_of(b, j + 1)].feature == cols[col_of(b, j)].feature + 1);
             if (quads) {
 #pragma unroll
-                for (int j = 0; j + 3 < NC; j += 4)
+                for (int j = 0; j + 3 < NC; j += 4) {
+                    auto at = X + (uint32_t)cols[col_of(b, j)].feature * 4u;
 #pragma unroll
                     for (int t = 0; t < T; ++t) {
-                        const f32x4u v =
-                            *(__attribute__((address_space(1))) const f32x4u *)(X + row_at[t] + cols[col_of(b, j)].feature);
+                        const f32x4u v = *(__attribute__((address_space(1))) const f32x4u *)(at + here(row_at[t]));
                         x[j * T + t] = v.x;
                         x[(j + 1) * T + t] = v.y;
                         x[(j + 2) * T + t] = v.z;
                         x[(j + 3) * T + t] = v.w;
                     }
+                }
                 return;
             }
-#pragma unroll
-            for (int j = 0; j < NC; ++j)
-#pragma unroll
-                for (int t = 0; t < T; ++t)
-                    x[j * T + t] = X[row_at[t] + cols[col_of(b, j)].feature];
-            return;
         }
 #pragma unroll
         for (int j = 0; j < NC; ++j) {
-            const int f = cols[col_of(b, j)].feature;
+            auto at = X + (uint32_t)cols[col_of(b, j)].feature * feature_bytes;
 #pragma unroll
-            for (int t = 0; t < T; ++t) {
-                auto column = X + ((int64_t)min(tile_first + t, n_tiles - 1) * F + f) * 64;
-                x[j * T + t] = column[(uint32_t)lane];
-            }
+            for (int t = 0; t < T; ++t)
+                x[j * T + t] = *(__attribute__((address_space(1))) const float *)(at + here(row_at[t]));
         }
     };
     auto fetch_tables = [&](int b, uint32_t to) {    // whole KB; the tables are padded behind the last one
@@ -158,51 +226,63 @@ __device__ __forceinline__ void code_columns(const FamDesc &d, const TreeletSegm
         for (uint32_t at = 0; at < bytes; at += 1024u)
             dma_1k(m.tables + (size_t)b * bytes + at, to + at, lane);
     };
-    auto search = [&](int b, const float (&x)[kChains], uint32_t tab) {
+    float last_bucket = __uint_as_float(buckets - 1u), four = 4.0f;
+    uint32_t zero = 0u;
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm("" : "+v"(last_bucket), "+v"(four), "+v"(zero));             // vector registers: the fast forms
+#endif
+    auto search = [&](int b, const Batch &q, const float (&x)[kChains], uint32_t tab) {
         uint32_t r[kChains];
+        float keys[NC], key[kChains];                // LDS addresses of the thresholds, as floats
         int steps = 0;
 #pragma unroll
         for (int j = 0; j < NC; ++j) {
             const int c = col_of(b, j);
-            const float scale = cols[c].scale, offset = cols[c].offset;
             const uint32_t lut = tab + (uint32_t)(c - b * NC) * stride;
-            steps = max(steps, cols[c].steps);
+            steps = max(steps, q.steps[j]);
+            float lut_f = __uint_as_float(lut), offset = q.offset[j];
+            keys[j] = __uint_as_float(lut + buckets);
+#if defined(__HIP_DEVICE_COMPILE__)
+            asm("" : "+v"(lut_f), "+v"(keys[j]), "+v"(offset));
+#endif
 #pragma unroll
             for (int t = 0; t < T; ++t)
-                r[j * T + t] = lds_u8(lut + min(to_u32(__builtin_fmaf(x[j * T + t], scale, offset)), last_bucket));
+                r[j * T + t] = lds_u8(__float_as_uint(__builtin_fmaf(fma_clamped(x[j * T + t], q.scale[j], offset), last_bucket, lut_f)));
         }
-        auto probe = [&](int s, float (&key)[kChains]) {
-            const uint32_t step = 1u << s;
+        // threshold r + 2^s - 1 of the column; those past the last are NaN and never counted
+        auto probe = [&](int s) {
 #pragma unroll
-            for (int j = 0; j < NC; ++j) {
-                // key r + 2^s - 1 of the column; keys past the last are NaN and never counted
-                const uint32_t keys = tab + (uint32_t)(col_of(b, j) - b * NC) * stride + last_bucket + 1u + 4u * (step - 1u);
+            for (int j = 0; j < NC; ++j)
 #pragma unroll
                 for (int t = 0; t < T; ++t)
-                    key[j * T + t] = lds_f(keys + 4u * r[j * T + t]);
-            }
+                    key[j * T + t] = lds_f(__float_as_uint(__builtin_fmaf(__uint_as_float(r[j * T + t]), four, keys[j])) + (4u << s) - 4u);
         };
-        float key[kChains];
-        for (int s = steps - 1; s > 0; --s) {
-            probe(s, key);
+        auto step = [&](int s) {
 #pragma unroll
             for (int k = 0; k < kChains; ++k)
-                r[k] += key[k] <= x[k] ? 1u << s : 0u;
+                r[k] += key[k] > x[k] ? 1u << s : 0u;
+        };
+        for (int s = steps - 1; s > 1; --s) {
+            probe(s);
+            step(s);
         }
-        if (steps > 0) {                             // (inside the loop this cost a register move per search, 1 % of a call)
-            probe(0, key);
+        if (steps > 1) {
+            probe(1);
+            step(1);
+        }
+        if (T == 4 && steps > 0) {
+            probe(0);
+#pragma unroll
+            for (int j = 0; j < NC; ++j)
+                lds_store_u((uint32_t)col_of(b, j) * 256u + 4u * (uint32_t)lane,
+                            count_above_bytes(key + 4 * j, x + 4 * j, r + 4 * j, zero));
+            return;
+        }
+        if (steps > 0) {
+            probe(0);
 #pragma unroll
             for (int k = 0; k < kChains; k += 4)
-                count_below(key + k, x + k, r + k);
-        }
-        bool nan = false;
-#pragma unroll
-        for (int k = 0; k < kChains; k += 2)
-            nan = nan || __builtin_isunordered(x[k], x[k + 1]);
-        if (__any(nan)) {
-#pragma unroll
-            for (int k = 0; k < kChains; ++k)
-                r[k] = x[k] != x[k] ? kTreeletNanRank : r[k];
+                count_above(key + k, x + k, r + k);
         }
 #pragma unroll
         for (int j = 0; j < NC; ++j) {
@@ -221,24 +301,26 @@ __device__ __forceinline__ void code_columns(const FamDesc &d, const TreeletSegm
     }
     for (int b = wave; b < n_batches; b += 2 * n_waves) {
         const int b1 = b + n_waves, b2 = b1 + n_waves;
+        const Batch q = read_batch(b);
         dma_wait();
         if (b1 < n_batches) {
             if (halves == 2)
                 fetch_tables(b1, slot1);
             fetch_values(b1, xb);
         }
-        search(b, xa, slot);
+        search(b, q, xa, slot);
         if (b1 >= n_batches)
             break;
         if (halves != 2)
             fetch_tables(b1, slot1);
+        const Batch q1 = read_batch(b1);
         dma_wait();
         if (b2 < n_batches) {
             if (halves == 2)
                 fetch_tables(b2, slot);
             fetch_values(b2, xa);
         }
-        search(b1, xb, slot1);
+        search(b1, q1, xb, slot1);
         if (halves != 2 && b2 < n_batches)
             fetch_tables(b2, slot);
     }

@@ -19,16 +19,19 @@ void build_columns(const std::vector<Piece> &pieces, const std::vector<float> &c
                    const std::vector<int32_t> &cut_at, int B, TreeletSegmentPlan *out)
 {
     auto values = [&](const Piece &pc) { return cuts.data() + cut_at[(size_t)pc.feature] + pc.at; };
-    // As the device rounds, truncates and clamps.  x * scale is exact in double, so the sum in double rounded
-    // to float is the fused result unless the rounding to double has made it a tie between two floats.
+    // As the device computes it: one rounding of x * scale + offset, clamped to [0, 1], times B - 1, rounded to the
+    // nearest integer (ties to even).  x * scale is exact in double, so the sum in double rounded to float is the
+    // fused result unless the rounding to double has made it a tie between two floats; the second product is exact too.
     auto bucket_of = [B](float x, const TreeletCol &c) -> int {
         const double sum = (double)x * (double)c.scale + (double)c.offset;
         uint64_t bits;
         memcpy(&bits, &sum, 8);
-        float t = (float)sum;
+        float u = (float)sum;
         if ((bits & 0x1FFFFFFFu) == 0x10000000u)
-            t = std::fmaf(x, c.scale, c.offset);
-        return t >= (float)(B - 1) ? B - 1 : (t > 0.0f ? (int)t : 0);
+            u = std::fmaf(x, c.scale, c.offset);
+        u = u > 0.0f ? std::min(u, 1.0f) : 0.0f;
+        constexpr double kToInt = 6755399441055744.0;        // 1.5 * 2^52: adding it rounds
+        return (int)(((double)u * (double)(B - 1) + kToInt) - kToInt);
     };
     out->cols.clear();
     int most_cuts = 0, most_steps = 0;
@@ -36,7 +39,7 @@ void build_columns(const std::vector<Piece> &pieces, const std::vector<float> &c
     uint16_t tried[kTreeletMaxCuts];
     for (const Piece &pc : pieces) {
         const float *v = values(pc);
-        // The range the buckets cover: all finite thresholds, or all but the lowest or the highest (an
+        // The range the buckets cover, downwards: all finite thresholds, or all but the highest or the lowest (an
         // exact zero far below the rest), a little wider or narrower; the fullest bucket decides.
         int lo = 0, hi = pc.n - 1;
         while (lo < hi && std::isinf(v[lo])) ++lo;
@@ -44,12 +47,12 @@ void build_columns(const std::vector<Piece> &pieces, const std::vector<float> &c
         TreeletCol best = {pc.feature, 0.0f, 0.0f, 0};
         int best_load = pc.n;                        // one bucket for all
         for (int trial = 0; trial < 8 && best_load > 3; ++trial) {
-            const int a = std::min(lo + (trial & 1), hi), b = std::max(hi - ((trial >> 1) & 1), a);
-            const double span = (double)v[b] - (double)v[a];
+            const int a = std::min(lo + ((trial >> 1) & 1), hi), b = std::max(hi - (trial & 1), a);
+            const double span = (double)v[a] - (double)v[b];
             if (!(span > 0.0))
                 continue;
-            const double s = (B - 2.0) * (1.0 - 0.07 * (trial >> 2)) / span, o = 1.0 - (double)v[a] * s;
-            if (!(s < 3e38 && s > 1e-37 && std::fabs(o) < 3e38))
+            const double s = -(B - 2.0) / (B - 1.0) * (1.0 - 0.07 * (trial >> 2)) / span, o = 1.0 / (B - 1.0) - (double)v[a] * s;
+            if (!(s > -3e38 && s < -1e-37 && std::fabs(o) < 3e38))
                 continue;
             const TreeletCol c = {pc.feature, (float)s, (float)o, 0};
             int load = 0, run = 0, prev = -1;
@@ -81,7 +84,7 @@ void build_columns(const std::vector<Piece> &pieces, const std::vector<float> &c
         const float *v = values(pieces[c]);
         const uint16_t *bucket = &buckets[c * (size_t)kTreeletMaxCuts];
         uint8_t *tab = out->tables.data() + c * (size_t)out->table_stride;
-        // thresholds in lower buckets, for every bucket: eight at a time (the last writes run into the keys'
+        // (higher) thresholds in lower buckets, for every bucket: eight at a time (the last writes run into the keys'
         // place, or the next column's, which are written after)
         int b = 0;
         for (int i = 0; i <= pieces[c].n; ++i) {
@@ -99,7 +102,7 @@ void build_columns(const std::vector<Piece> &pieces, const std::vector<float> &c
 
 // Thresholds and columns of a segment's trees.
 struct SegmentCuts {
-    std::vector<float> cuts;                         // sorted and distinct, per feature
+    std::vector<float> cuts;                         // distinct, the highest first, per feature
     std::vector<int32_t> cut_at;
     std::vector<Piece> pieces;
 };
@@ -172,7 +175,7 @@ uint64_t *sort_keys(uint64_t *keys, uint64_t *spare, int n)
 }
 
 // Sorts the thresholds of n_splits nodes, so many of each feature, by feature, lists the columns and sets word[node] = column << 8 |
-// rank of every split (rank 0 for a NaN threshold: it sends nothing left).  False if the trees need more
+// rank of every split (rank 255 for a NaN threshold: it sends nothing left).  False if the trees need more
 // columns than a byte names.
 bool segment_cuts(int n_features, const int32_t *nodes, size_t n_splits, const std::vector<int32_t> &of_feature,
                   const int32_t *sf, const float *thr, std::vector<uint64_t> &keys, uint16_t *word, SegmentCuts *out)
@@ -207,12 +210,12 @@ bool segment_cuts(int n_features, const int32_t *nodes, size_t n_splits, const s
         float *v = out->cuts.data() + at[(size_t)f];
         int n = 0, rank = 0;                         // rank inside the piece
         uint32_t piece = (uint32_t)first - 1, last = 0;
-        for (int i = 0; i < m; ++i) {
+        for (int i = m - 1; i >= 0; --i) {
             const uint32_t key = (uint32_t)(k[i] >> 32);
-            if (i == 0 || key != last) {
+            if (i == m - 1 || key != last) {
                 last = key;
                 v[n++] = unordered(key);
-                if (++rank > kTreeletMaxCuts || i == 0) {
+                if (++rank > kTreeletMaxCuts || i == m - 1) {
                     rank = 1;
                     ++piece;
                 }
@@ -229,7 +232,7 @@ bool segment_cuts(int n_features, const int32_t *nodes, size_t n_splits, const s
             return false;
     }
     for (int32_t g : nan_nodes)
-        word[g] = (uint16_t)(first_col[(size_t)sf[g]] << 8);
+        word[g] = (uint16_t)(first_col[(size_t)sf[g]] << 8 | 255);
     if (out->pieces.empty())                         // single leaves only: one column nobody asks
         out->pieces.push_back({0, 0, 0});
     return true;
@@ -590,7 +593,7 @@ bool build_treelets(int n_features, int n_trees, const TreeShapes &shape, const 
                 const int32_t block = next;
                 next += 4;
                 uint32_t half[2];
-                const int32_t child[2] = {left[g], right[g]};
+                const int32_t child[2] = {right[g], left[g]};
                 for (int c = 0; c < 2; ++c) {
                     const int64_t gc = (int64_t)o + child[c];
                     int32_t to[2];                   // node of outcome (c, 0) and (c, 1), -1: never reached
@@ -600,8 +603,8 @@ bool build_treelets(int n_features, int n_trees, const TreeShapes &shape, const 
                         to[1] = child[c];
                     } else {
                         half[c] = word[(size_t)gc];
-                        to[0] = left[gc];
-                        to[1] = right[gc];
+                        to[0] = right[gc];
+                        to[1] = left[gc];
                     }
                     for (int k = 0; k < 2; ++k) {
                         if (to[k] < 0)
