@@ -283,7 +283,7 @@ enum {
     FS_TUNE_LDS_TILES = 0,        /* 1..3: 64-row tiles per workgroup of the LDS-staged traversal  */
     FS_TUNE_LDS_MODE = 1,         /* 1: half-LDS workgroups (two per compute unit), 2: full         */
     FS_TUNE_RANK = 2,             /* 0: never rank-code a model, 1: whenever its trees allow        */
-    FS_TUNE_RANK_TILES = 3,       /* 1, 2, 3, 4 or 6: tiles per workgroup of the rank traversal     */
+    FS_TUNE_RANK_TILES = 3,       /* 1..6 or 8: tiles per workgroup of the rank traversal           */
     FS_TUNE_VERBOSE = 4,          /* 1: fs_model_create and fs_score_families report on stderr      */
     FS_TUNE_TRAIN_SLAB_ROWS = 5,  /* 64..65536: rows per histogram workgroup, up to a power of two  */
     FS_TUNE_TRAIN_SORT = 6,       /* accepted, no effect: rows are always grouped by node           */

@@ -582,8 +582,11 @@ extern "C" int fs_score_families(int32_t n_families, const fs_family *fams, void
     // they count towards the length of the launch, though their workgroups take one group each)
     int64_t lds_groups[kLdsModes] = {0, 0};
     double lds_us[kLdsModes] = {0.0, 0.0};           // all groups of the launch, by the planner's estimate
+    int64_t rk_tiles = 0;
     for (int f = 0; f < n_families; ++f) {
         const fs_model *m = fams[f].model;
+        if (!walks.treelets(fams[f]) && m->rank_ok)
+            rk_tiles += (fams[f].n_rows + 63) / 64;
         if (!walks.treelets(fams[f]) && !m->rank_ok && m->lds_ok) {
             const int64_t g = ((fams[f].n_rows + 63) / 64 + m->lds_tiles - 1) / m->lds_tiles;
             lds_groups[m->lds_mode] += g;
@@ -656,11 +659,7 @@ extern "C" int fs_score_families(int32_t n_families, const fs_family *fams, void
         d.cuts = a.model->d_cuts;
         d.ranks = nullptr;
         d.rk_depth = a.model->rk_depth;
-        d.rk_tiles = a.model->rk_tiles;
-        d.rk_slots = a.model->rk_slots;
-        d.rk_trees_per_slot = a.model->rk_trees_per_slot;
         d.rk_tree_bytes = a.model->rk_tree_bytes;
-        d.rk_tile0 = a.model->rk_tile0;
         d.rk_block0 = (int32_t)rk_blocks;
         d.bin_block0 = (int32_t)bin_blocks;
         d.bin_groups = 1;
@@ -694,8 +693,10 @@ extern "C" int fs_score_families(int32_t n_families, const fs_family *fams, void
             if (tpb > kBinTilesPerBlock) tpb = kBinTilesPerBlock;
             d.bin_tiles_per_block = (int32_t)tpb;
             bin_blocks += (int64_t)d.bin_groups * ((tiles + tpb - 1) / tpb);
-            rk_blocks += (tiles + a.model->rk_tiles - 1) / a.model->rk_tiles;
-            const int slot_bytes = a.model->rk_trees_per_slot * a.model->rk_tree_bytes, at_once = a.model->rk_tiles * 64 * 16;
+            d.rk = rank_shape(a.model->n_features, a.model->n_trees, a.model->rk_tree_bytes, tiles, rk_tiles,
+                              a.model->rk_forced_tiles);
+            rk_blocks += (tiles + d.rk.tiles - 1) / d.rk.tiles;
+            const int slot_bytes = d.rk.per_slot * a.model->rk_tree_bytes, at_once = d.rk.tiles * 64 * 16;
             rk_regs = std::max(rk_regs, (slot_bytes + at_once - 1) / at_once);
             if (a.leaf_idx && a.n_rows > 0)
                 rk_dump = true;

@@ -117,13 +117,9 @@ struct fs_model {
     // own thresholds of that feature, nodes shrink to 4 bytes (see fs_rank.hip)
     bool rank_ok;
     int32_t rk_depth;          // common depth of the trees
-    int32_t rk_tiles;          // 64-row tiles per workgroup
-    int32_t rk_slots;          // wavefronts of a tile that have trees
-    int32_t rk_trees_per_slot;
-    int32_t rk_tree_bytes;     // of a tree in LDS: heap words 1 .. 2^depth - 1, word 0 unused, and the leaves if they are
-                               // held there (then 8 << depth, else 4 << depth)
-    int32_t rk_tile0;          // LDS byte offset of the first (u16) feature tile
-    uint32_t *d_rk_nodes;      // [n_trees][rk_tree_bytes], then, if they are not held, [n_trees][2^depth] leaf values
+    int32_t rk_tree_bytes;     // of a tree in LDS: heap words 1 .. 2^(depth - 1) - 1, word 0 unused, whole 16 bytes
+    int32_t rk_forced_tiles;   // tiles per workgroup as overridden, or 0
+    uint32_t *d_rk_nodes;      // [n_trees][rk_tree_bytes], then [n_trees][2^(depth - 1)] RankLast
     uint16_t *d_rk_ids;        // [n_trees][2^(depth+1)] 1-based heap order: caller's local node id
     float *d_cuts;             // [n_features][2^cut_bits]: the feature's sorted distinct
                                // thresholds, NaN-padded, as a breadth-first search tree; or, with
@@ -143,6 +139,12 @@ struct fs_model {
 };
 
 namespace fs {
+
+struct RankShape {                       // a workgroup of the rank walk
+    int32_t tiles;                       // of 64 rows
+    int32_t slots, per_slot;             // wavefronts of a tile that have trees, and how many at a time
+    int32_t tile0;                       // LDS byte offset of the first (u16) tile
+};
 
 // ---- per-family descriptor as the kernels see it --------------------------------------------
 struct FamDesc {
@@ -175,7 +177,8 @@ struct FamDesc {
     const uint16_t *rk_ids;
     const float *cuts;
     uint16_t *ranks;                 // scratch: rank-coded feature tiles [tile][feature][64]
-    int32_t rk_depth, rk_tiles, rk_slots, rk_trees_per_slot, rk_tree_bytes, rk_tile0;
+    RankShape rk;
+    int32_t rk_depth, rk_tree_bytes;
     int32_t rk_block0;               // first block of the rank traversal grid
     int32_t bin_block0;              // first block of the rank-coding grid
     int32_t bin_groups;              // feature groups of this family in the rank-coding grid
@@ -415,9 +418,15 @@ struct RankColumn {
     float scale, offset;
     int32_t buckets, steps;
 };
-constexpr int kRankWaves = 12;
+constexpr int kRankWaves = 16;
 constexpr int kRankLdsBytes = 160 * 1024;
 constexpr int kRankMostTrees = 8;        // of a slot
+struct RankLast {                        // a split of a tree's last level, as in LDS, and its leaves' values
+    uint32_t split;
+    float left, right;
+};
+// For a family of own_tiles in a launch of all_tiles; no tiles where a tree does not fit beside one.
+RankShape rank_shape(int n_features, int n_trees, int tree_bytes, int64_t own_tiles, int64_t all_tiles, int forced_tiles);
 
 constexpr int kTravRowsPerBlock = 256;   // rows per block of the global-memory traversal
 constexpr int kSegProgsPerBlock = 256;   // programs per block of the segmented sum

@@ -567,10 +567,51 @@ bool bucket_tables(fs_model *m, int n_features, int max_cuts, const std::vector<
     return true;
 }
 
+}  // namespace
+
+// Workgroups of the walk: what is walked side by side decides (neither the LDS nor vector issue is busy), up to eight
+// trees a slot, and how full the last round of workgroups is.  0.5 M rows of 164 features, 500 trees of depth 10, us by tiles
+// a workgroup: 849 with 4 (128 walks), 896 with 5 (120), 897 with 3 (120), 946 with 6 (96), 963 with 2 (112); 4800 rows: 213
+// with 8, 136 with 6, 90 with 4, 59 with 2, 48 with 1.  40 000 rows of 60 features, 300 trees of depth 8: 63, 63, 50, 57, 68,
+// 82 and 93 us with 1, 2, 3, 4, 5, 6 and 8: 14 us of coding, and a workgroup takes 3.8 us for all its trees' turns and 7.4 more.
+RankShape fs::rank_shape(int n_features, int n_trees, int tree_bytes, int64_t own_tiles, int64_t all_tiles, int forced)
+{
+    const long tile_bytes = (long)rank_tile_cols(n_features) * 128;
+    RankShape best = {0, 0, 0, 0};
+    double least = 0.0;
+    for (const int nt : {8, 6, 5, 4, 3, 2, 1}) {
+        if (forced > 0 ? nt != forced : nt > std::max<int64_t>(own_tiles, 1))
+            continue;
+        const long avail = (long)kRankLdsBytes - nt * (tile_bytes + 256) - 128;
+        const int fit = avail < 0 ? 0 : (int)std::min<long>(avail / tree_bytes, 1024);
+        RankShape shape = {0, 0, 0, 0};
+        for (int slots = std::min(kRankWaves / nt, fit); slots >= 1; --slots) {
+            const int per = std::min(fit / slots, kRankMostTrees);
+            if (slots * per > shape.slots * shape.per_slot)
+                shape = {nt, slots, per, kRankLdsBytes - nt * (int)tile_bytes};
+        }
+        if (shape.tiles == 0)
+            continue;
+        const int at_once = std::max(1, std::min(shape.slots * shape.per_slot, n_trees));
+        const int64_t rounds = ((all_tiles + nt - 1) / nt + 255) / 256;
+        const double time = (double)rounds * (2.0 + (double)n_trees / at_once);
+        if (best.tiles > 0 && time >= least)
+            continue;
+        least = time;
+        // as many trees in every turn as the number of turns needs
+        const int turns = std::max(1, (n_trees + shape.slots * shape.per_slot - 1) / (shape.slots * shape.per_slot));
+        shape.per_slot = std::max(1, (n_trees + shape.slots * turns - 1) / (shape.slots * turns));
+        best = shape;
+    }
+    return best;
+}
+
+namespace {
+
 // Rank-coded image of a model of perfect trees of one depth (see fs_rank.hip): per feature the
 // sorted distinct thresholds; per tree the splits, word i = heap node i (1-based) as
-// rank << 16 | offset of the feature in a rank tile, then its leaf values or, if they are not held in LDS, behind
-// the splits of all trees 2^depth of each; plus the caller's node id per heap node.
+// rank << 16 | offset of the feature in a rank tile, without the last level; behind those of all trees the last level's
+// splits with their leaves' values (RankLast); plus the caller's node id per heap node.
 void build_rank_format(fs_model *m, int n_features, int n_trees, int depth, const int32_t *tree_off,
                        const int32_t *sf, const float *thr, const int32_t *left,
                        const int32_t *right, const float *val, std::vector<uint32_t> *nodes,
@@ -613,52 +654,19 @@ void build_rank_format(fs_model *m, int n_features, int n_trees, int depth, cons
         }
     }
 
-    // tiles per workgroup (must divide the wavefront count): most walks side by side, up to eight trees a slot; of
-    // equals the most tiles, as every workgroup reads the whole model.  Leaf values are held in LDS only where that
-    // leaves room for the most walks on the most tiles: 164 features, 500 trees of depth 8 2.19 ms held and 2.40 not
-    // (1.6 M rows), of depth 9 0.86 and 0.79 (0.5 M), of depth 10 4.50 and 3.92 (2.1 M), 200 of depth 11 0.41 and 0.27.
-    const size_t tile_bytes = (size_t)rank_tile_cols(n_features) * 128;
-    size_t tree_bytes = (size_t)8 << depth;
-    int best_t = 0, best_slots = 0, best_per = 0;
-    const int forced = tune(FS_TUNE_RANK_TILES);
-    const int choices[] = {6, 4, 3, 2, 1};
-    constexpr int kMostWalks = 64;
-    auto choose = [&]() {
-        int best_score = 0;
-        for (int nt : choices) {
-            if (forced > 0 && nt != forced)
-                continue;
-            const long avail = (long)kRankLdsBytes - (long)nt * (long)(tile_bytes + 256) - 128;
-            const int fit = avail < 0 ? 0 : (int)std::min<size_t>((size_t)avail / tree_bytes, 1024);
-            for (int slots = std::min(kRankWaves / nt, fit); slots >= 1; --slots) {
-                const int per = std::min(fit / slots, kRankMostTrees);
-                const int score = std::min(nt * slots * per, kMostWalks);
-                if (score > best_score) {
-                    best_score = score;
-                    best_t = nt;
-                    best_slots = slots;
-                    best_per = per;
-                }
-            }
-        }
-        return best_score;
-    };
-    const int score = choose();
-    if (score == 0)
+    const size_t tree_bytes = std::max<size_t>(16, (size_t)2 << depth);   // (whole 16-byte pieces)
+    m->rk_forced_tiles = tune(FS_TUNE_RANK_TILES);
+    if (rank_shape(n_features, n_trees, (int)tree_bytes, 1, 1, m->rk_forced_tiles).tiles == 0)
         return;                                           // (too large: other walks take them)
-    const bool held = depth < 2 || (score == kMostWalks && (forced > 0 || best_t == choices[0]));
-    if (!held) {                                          // (depth 2 and more: whole 16-byte pieces)
-        tree_bytes /= 2;
-        choose();
-    }
     const size_t words = (size_t)2 << depth, n_leaves = words / 2, stride = tree_bytes / 4;   // per tree, word 0 unused
-    nodes->assign((stride + (held ? 0 : n_leaves)) * (size_t)n_trees, 0u);
+    const size_t n_last = n_leaves / 2, last_words = 3;
+    nodes->assign((stride + n_last * last_words) * (size_t)n_trees, 0u);
     ids->assign(words * (size_t)n_trees, 0);
     std::vector<int32_t> at(words);                       // caller's node at heap position i
     for (int t = 0; t < n_trees; ++t) {
         const int32_t o = tree_off[t];
         uint32_t *const splits = nodes->data() + (size_t)t * stride;
-        uint32_t *const leaves = held ? splits + n_leaves : nodes->data() + stride * (size_t)n_trees + (size_t)t * n_leaves;
+        uint32_t *const last = nodes->data() + stride * (size_t)n_trees + (size_t)t * n_last * last_words;
         at[1] = 0;
         for (size_t i = 1; i < words; ++i) {
             const int32_t n = at[i];
@@ -682,26 +690,18 @@ void build_rank_format(fs_model *m, int n_features, int n_trees, int depth, cons
                     }
                     rank = 1u + (uint32_t)(from - v.begin());
                 }
-                splits[i] = (rank << 16) | rank_feature_offset(sf[o + n]);
+                (i < n_last ? splits[i] : last[(i - n_last) * last_words]) = (rank << 16) | rank_feature_offset(sf[o + n]);
             } else {
-                memcpy(&leaves[i - n_leaves], &val[o + n], 4);
+                memcpy(&last[(i / 2 - n_last) * last_words + 1 + (i & 1)], &val[o + n], 4);
             }
             (*ids)[(size_t)t * words + i] = (uint16_t)n;
         }
     }
-    // as many trees in every turn as the number of turns needs
-    const int rounds = std::max(1, (n_trees + best_slots * best_per - 1) / (best_slots * best_per));
-    best_per = std::max(1, (n_trees + best_slots * rounds - 1) / (best_slots * rounds));
     m->rank_ok = true;
     m->rk_depth = depth;
-    m->rk_tiles = best_t;
-    m->rk_slots = best_slots;
-    m->rk_trees_per_slot = best_per;
     m->rk_tree_bytes = (int32_t)tree_bytes;
-    m->rk_tile0 = kRankLdsBytes - best_t * (int32_t)tile_bytes;
     if (tune(FS_TUNE_VERBOSE) > 0)
-        fprintf(stderr, "fs_model_create: rank-coded depth=%d tiles=%d slots=%d of %d trees max_cuts=%zu\n",
-                depth, best_t, best_slots, best_per, max_cuts);
+        fprintf(stderr, "fs_model_create: rank-coded depth=%d max_cuts=%zu\n", depth, max_cuts);
 }
 
 void free_device(fs_model *m)

@@ -15,9 +15,9 @@
 //   rank_code_kernel     fp32 feature tiles -> u16 rank tiles (searches in LDS-resident
 //                        threshold tables, one feature group per workgroup)
 //   traverse_rank_kernel the LDS-staged walk over rank tiles; trees in heap order without
-//                        child pointers (node i has children 2i, 2i+1, 1-based), leaves are the
-//                        last level; the wavefronts that share a tile walk trees of their own and
-//                        pass the row's sum on in tree order
+//                        child pointers (node i has children 2i, 2i+1, 1-based), the last level of
+//                        splits and the leaves in memory; the wavefronts that share a tile walk
+//                        trees of their own and pass the row's sum on in tree order
 #include "fs_internal.h"
 #include "fs_lds.h"
 
@@ -213,7 +213,7 @@ int launch_rank_code(const FamDesc *d_desc, int n_families, int total_blocks, hi
 // ------------------------------------------------------------------------------------------------
 // traversal over rank tiles
 // ------------------------------------------------------------------------------------------------
-// A workgroup has T tiles and 12 / T wavefronts per tile, its slots.  The trees in LDS are dealt to the slots, and
+// A workgroup has T tiles and 16 / T wavefronts per tile, its slots.  The trees in LDS are dealt to the slots, and
 // the T wavefronts of a slot (one per tile) walk the slot's trees, wait for each other, put the slot's next
 // trees in their place and wait again, on their own: while one slot copies others walk.  A row's running sum
 // goes from slot to slot in tree order, through LDS with a counter that says whose turn it is.
@@ -221,18 +221,22 @@ int launch_rank_code(const FamDesc *d_desc, int n_families, int total_blocks, hi
 // trees of depth 10 took 5500 clocks, 3300 of them walks, the rest copying 64 KB into LDS and
 // adding up while nothing else ran.  2.1 M rows, 500 such trees: 4.63 ms, so 3.85.)
 //
-// The leaf values stay in memory where they, half of a tree, would cost walks side by side: a slot asks for its
-// values, replaces its trees and then adds the values up.  (2.1 M rows, 500 trees of depth 10: 4.50 ms with three
-// trees a slot and their leaves, 3.92 with six without.)  Each way has its own loop: one for both took 6 % more.
+// Bound by the latency of two LDS reads a level at the walks that fit side by side (vector issue 47 % and LDS 55 % at 72
+// of them), and what they need is room: half of a tree's splits are its last level and half of its words the
+// leaves, each read once a walk.  So both stay in memory, a split and its two values in one record: a slot asks for
+// its walks' records, replaces its trees, and then takes the last decisions and adds the values up.  A tree of depth
+// 10 is 2 KB in LDS then and four tiles have 16 wavefronts of eight walks.  (2.1 M rows of 164 features, 500 trees of
+// depth 10, the call: 3.82 ms with splits of all levels in LDS, 12 wavefronts of six walks, so 3.01; half a million rows,
+// 300 trees of depth 8 541 us and 476, of depth 9 627 and 527, 200 of depth 11 353 and 272, 100 of depth 12 in 131 072
+// rows 198 and 121.  With the leaves in LDS too, as for depth 8 before, 480 instead of 476, and never less.)
 //
 // LDS map:  [0, slots * per_slot * tree_bytes)  the slots' trees, each [unused][splits in heap order, 1-based]
-//                                               and, if held, [leaf values]
 //           [tile0 - T*256 - 128, ...)          running sums [tile][lane], then the counters
 //           [tile0 + t*Fc*128, ...)             tile t: features 2i, 2i+1 of row l in the word at
 //                                               i*256 + 4*l (Fc = F rounded up to even)
 // A split word is rank(thr) << 16 | offset of the feature in a tile (i*256 + 2*(f & 1)).
 
-// K trees at once for this lane's row, down to the leaves' places A[k].  base[k] = LDS address of tree k; the 1-based heap
+// K trees at once for this lane's row, `depth` levels down to the places A[k].  base[k] = LDS address of tree k; the 1-based heap
 // index i lives at A = base + 4*i, and the step i' = 2i + c is taken on the address itself:
 // A' = 2A + (4c - base)   (one select between two per-tree constants and one shift-add).
 // (Reading both children of a split together with its feature halves the chain of LDS latencies, but two words cost
@@ -318,18 +322,18 @@ traverse_rank_kernel(const FamDesc *__restrict__ descs, int n_families)
     const FamDesc &d = descs[lo];
     const int tid = threadIdx.x;
     const int wave = uniform(tid >> 6), lane = tid & 63;
-    const int T = d.rk_tiles;                   // tiles per workgroup (divides 12)
-    const int n_slots = d.rk_slots;             // 12 / T or fewer
+    const int T = d.rk.tiles;                   // tiles per workgroup
+    const int n_slots = d.rk.slots;             // kRankWaves / T or fewer
     const int my_slot = wave / T, my_tile = wave - my_slot * T;
     const int n_tiles = (d.n_rows + 63) >> 6;
     const int tile_first = (blockIdx.x - d.rk_block0) * T;
     const int tiles_here = min(T, n_tiles - tile_first);
     const int Fc = rank_tile_cols(d.n_features);
     const uint32_t tile_bytes = (uint32_t)Fc * 128u;
-    const uint32_t tile0 = (uint32_t)d.rk_tile0;
+    const uint32_t tile0 = (uint32_t)d.rk.tile0;
     const uint32_t lane_base = tile0 + (uint32_t)my_tile * tile_bytes + 4u * (uint32_t)lane;
     const uint32_t tree_bytes = (uint32_t)d.rk_tree_bytes;
-    const int per_slot = d.rk_trees_per_slot;
+    const int per_slot = d.rk.per_slot;
     const int n_trees = d.n_trees, depth = d.rk_depth;
     const int n_turns = (n_trees + per_slot - 1) / per_slot;     // turn q: trees [q, q + 1) * per_slot, slot q % n_slots
     const uint32_t sums = tile0 - (uint32_t)T * 256u - 128u, counters = tile0 - 128u;
@@ -338,8 +342,9 @@ traverse_rank_kernel(const FamDesc *__restrict__ descs, int n_families)
     const uint32_t slot_at = counters + 64u + 4u * (uint32_t)my_slot;      // how often wavefronts of the slot came by
     // tree_bytes is a multiple of 16, so every tree starts 16-byte aligned
     auto image = FS_GLOBAL(const u32x4, d.rk_nodes);
-    // (the values of a tree, by heap index)
-    auto leaves = FS_GLOBAL(const float, d.rk_nodes) + (int64_t)n_trees * (tree_bytes >> 2) - ((int64_t)1 << depth);
+    // (the records of a tree's last splits, by heap index)
+    const int last_bytes = (int)sizeof(RankLast) << (depth - 1);    // of a tree
+    auto last_splits = FS_GLOBAL(const uint8_t, d.rk_nodes) + (int64_t)n_trees * tree_bytes - last_bytes;
     const int tree16 = (int)(tree_bytes >> 4);
     // The first trees and the tiles go straight from memory to LDS, 1 KB per wavefront-wide
     // load; what is left of each (fewer than 64 pieces) goes through registers.
@@ -385,104 +390,109 @@ traverse_rank_kernel(const FamDesc *__restrict__ descs, int n_families)
             leaf_row = d.leaf_idx + (int64_t)r * n_trees;
     }
     uint32_t passed = 0;                                   // what the slot's counter has to reach
-    auto turns = [&](auto held_) {
-        constexpr bool HELD = decltype(held_)::value != 0;
-        for (int q = my_slot; q < n_turns; q += n_slots) {
-            const int n = min(per_slot, n_trees - q * per_slot);
-            // the slot's next trees: global -> registers
-            const int q_next = q + n_slots;
-            const int n16 = q_next < n_turns ? min(per_slot, n_trees - q_next * per_slot) * tree16 : 0;
-            auto src = image + (int64_t)q_next * per_slot * tree16;
-            u32x4 pf[REGS];
-            if (n16 > 0) {
+    for (int q = my_slot; q < n_turns; q += n_slots) {
+        const int n = min(per_slot, n_trees - q * per_slot);
+        // the slot's next trees: global -> registers
+        const int q_next = q + n_slots;
+        const int n16 = q_next < n_turns ? min(per_slot, n_trees - q_next * per_slot) * tree16 : 0;
+        auto src = image + (int64_t)q_next * per_slot * tree16;
+        u32x4 pf[REGS];
+        if (n16 > 0) {
 #pragma unroll
-                for (int j = 0; j < REGS; ++j)
-                    pf[j] = src[min(in_slot + j * slot_threads, n16 - 1)];
-            }
-            float kept[kRankMostTrees];                    // values from memory
-            auto add_up = [&](auto trees, const float *v) {
-                wait_for(turn_at, (uint32_t)q);
-                float acc = lds_f(my_sum);
-#pragma unroll
-                for (int k = 0; k < decltype(trees)::value; ++k)
-                    acc = acc + v[k];
-                if (q + 1 < n_turns) {
-                    lds_store_f(my_sum, acc);
-                    count_up(turn_at, lane);
-                } else if (r < d.n_rows) {
-                    FS_GLOBAL(float, d.row_score)[r] = acc;
-                }
-            };
-            auto walk = [&](auto trees) {
-                constexpr int K = decltype(trees)::value;
-                uint32_t base[K], at[K];
-#pragma unroll
-                for (int k = 0; k < K; ++k)
-                    base[k] = region + (uint32_t)k * tree_bytes;
-                rank_walk<K>(base, depth, lane_base, at);
-                float v[K];
-#pragma unroll
-                for (int k = 0; k < K; ++k)
-                    v[k] = HELD ? lds_f(at[k]) : (leaves + ((int64_t)(q * per_slot + k) << depth))[(at[k] - base[k]) >> 2];
-                if (DUMP) {
-                    if (leaf_row) {
-                        auto ids = FS_GLOBAL(const uint16_t, d.rk_ids + ((int64_t)q * per_slot << (depth + 1)));
-                        auto out = FS_GLOBAL(uint16_t, leaf_row + q * per_slot);
-#pragma unroll
-                        for (int k = 0; k < K; ++k)
-                            out[k] = ids[((uint32_t)k << (depth + 1)) + ((at[k] - base[k]) >> 2)];
-                    }
-                }
-                if (n16 > 0)
-                    count_up(slot_at, lane);               // the trees have been read
-                if (HELD) {
-                    add_up(trees, v);
-                } else {
-#pragma unroll
-                    for (int k = 0; k < K; ++k)
-                        kept[k] = v[k];
-                }
-            };
-            auto for_trees = [&](auto what) {
-                switch (n) {
-                case 8: what(RankInt<8>()); break;
-                case 7: what(RankInt<7>()); break;
-                case 6: what(RankInt<6>()); break;
-                case 5: what(RankInt<5>()); break;
-                case 4: what(RankInt<4>()); break;
-                case 3: what(RankInt<3>()); break;
-                case 2: what(RankInt<2>()); break;
-                default: what(RankInt<1>());
-                }
-            };
-            if (active)
-                for_trees(walk);
-            else if (n16 > 0)
-                count_up(slot_at, lane);
-            if (n16 > 0) {
-                passed += (uint32_t)T;
-                wait_for(slot_at, passed);
-#pragma unroll
-                for (int j = 0; j < REGS; ++j) {
-                    const int i = in_slot + j * slot_threads;
-                    if (i < n16)
-                        lds_store_u4(region + 16u * (uint32_t)i, pf[j]);
-                }
-                for (int i = in_slot + REGS * slot_threads; i < n16; i += slot_threads)   // trees larger than that
-                    lds_store_u4(region + 16u * (uint32_t)i, src[i]);
-                count_up(slot_at, lane);
-                passed += (uint32_t)T;
-            }
-            if (!HELD && active)
-                for_trees([&](auto trees) { add_up(trees, kept); });
-            if (n16 > 0)
-                wait_for(slot_at, passed);                 // the next trees are there
+            for (int j = 0; j < REGS; ++j)
+                pf[j] = src[min(in_slot + j * slot_threads, n16 - 1)];
         }
-    };
-    if (tree_bytes == 8u << depth)                         // leaf values in LDS
-        turns(RankInt<1>());
-    else
-        turns(RankInt<0>());
+        RankLast kept[kRankMostTrees];                     // last splits, from memory
+        uint32_t kept_at[DUMP ? kRankMostTrees : 1];
+        auto dump = [&](int k, uint32_t heap) {
+            if (DUMP && leaf_row) {
+                auto ids = FS_GLOBAL(const uint16_t, d.rk_ids + ((int64_t)q * per_slot << (depth + 1)));
+                FS_GLOBAL(uint16_t, leaf_row + q * per_slot)[k] = ids[((uint32_t)k << (depth + 1)) + heap];
+            }
+        };
+        auto add_up = [&](auto trees, const float *v) {
+            wait_for(turn_at, (uint32_t)q);
+            float acc = lds_f(my_sum);
+#pragma unroll
+            for (int k = 0; k < decltype(trees)::value; ++k)
+                acc = acc + v[k];
+            if (q + 1 < n_turns) {
+                lds_store_f(my_sum, acc);
+                count_up(turn_at, lane);
+            } else if (r < d.n_rows) {
+                FS_GLOBAL(float, d.row_score)[r] = acc;
+            }
+        };
+        auto walk = [&](auto trees) {
+            constexpr int K = decltype(trees)::value;
+            uint32_t base[K], at[K];
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                base[k] = region + (uint32_t)k * tree_bytes;
+            rank_walk<K>(base, depth - 1, lane_base, at);
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                auto tree = last_splits + (int64_t)(q * per_slot + k) * last_bytes;
+                auto from = FS_GLOBAL(const RankLast, tree + 3u * (at[k] - base[k]));
+                kept[k].split = from->split;
+                kept[k].left = from->left;
+                kept[k].right = from->right;
+                if (DUMP)
+                    kept_at[DUMP ? k : 0] = (at[k] - base[k]) >> 2;
+            }
+            if (n16 > 0)
+                count_up(slot_at, lane);                   // the trees have been read
+        };
+        auto finish = [&](auto trees) {                    // the last splits, then the sum
+            constexpr int K = decltype(trees)::value;
+            uint32_t x[K];
+            float v[K];
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                x[k] = lds_u16((kept[k].split & 0xFFFFu) + lane_base);
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const bool left = x[k] < (kept[k].split >> 16);
+                v[k] = left ? kept[k].left : kept[k].right;
+                dump(k, 2u * kept_at[DUMP ? k : 0] + (left ? 0u : 1u));
+            }
+            add_up(trees, v);
+        };
+        auto for_trees = [&](auto what) {
+            switch (n) {
+            case 8: what(RankInt<8>()); break;
+            case 7: what(RankInt<7>()); break;
+            case 6: what(RankInt<6>()); break;
+            case 5: what(RankInt<5>()); break;
+            case 4: what(RankInt<4>()); break;
+            case 3: what(RankInt<3>()); break;
+            case 2: what(RankInt<2>()); break;
+            default: what(RankInt<1>());
+            }
+        };
+        if (active)
+            for_trees(walk);
+        else if (n16 > 0)
+            count_up(slot_at, lane);
+        if (n16 > 0) {
+            passed += (uint32_t)T;
+            wait_for(slot_at, passed);
+#pragma unroll
+            for (int j = 0; j < REGS; ++j) {
+                const int i = in_slot + j * slot_threads;
+                if (i < n16)
+                    lds_store_u4(region + 16u * (uint32_t)i, pf[j]);
+            }
+            for (int i = in_slot + REGS * slot_threads; i < n16; i += slot_threads)   // trees larger than that
+                lds_store_u4(region + 16u * (uint32_t)i, src[i]);
+            count_up(slot_at, lane);
+            passed += (uint32_t)T;
+        }
+        if (active)
+            for_trees(finish);
+        if (n16 > 0)
+            wait_for(slot_at, passed);                 // the next trees are there
+    }
     // (no trees: the row's score is the bias)
     if (n_turns == 0 && my_slot == 0 && active && r < d.n_rows)
         FS_GLOBAL(float, d.row_score)[r] = d.bias;
@@ -516,9 +526,11 @@ int launch_traverse_rank(const FamDesc *d_desc, int n_families, int total_blocks
 {
     if (regs <= 3)
         return launch_rank_regs<3>(d_desc, n_families, total_blocks, dump, stream);
+    if (regs <= 4)
+        return launch_rank_regs<4>(d_desc, n_families, total_blocks, dump, stream);
     if (regs <= 6)
         return launch_rank_regs<6>(d_desc, n_families, total_blocks, dump, stream);
-    return launch_rank_regs<11>(d_desc, n_families, total_blocks, dump, stream);
+    return launch_rank_regs<8>(d_desc, n_families, total_blocks, dump, stream);
 }
 
 }  // namespace fs

@@ -22,6 +22,27 @@ def test_slots_at_their_edges(api, oracle, tune, tiles, depth, trees, rows):  # 
     check_family(oracle, fam, devs[0])
 
 
+@pytest.mark.parametrize("tiles", [5, 8])
+@pytest.mark.parametrize("depth,trees,features", [(1, 33, 20), (2, 9, 20), (9, 150, 70), (10, 41, 33), (12, 11, 40)])
+def test_more_tiles_than_four(api, oracle, tune, tiles, depth, trees, features):  # noqa: F811
+    tune(api.FS_TUNE_RANK, 1)
+    tune(api.FS_TUNE_RANK_TILES, tiles)
+    fam = W.make_small_family(seed=depth + trees, n_programs=64 * 11 + 3, stmts=(1, 1), n_trees=trees, depth=depth, k=5,
+                              n_features=features)
+    check_family(oracle, fam, run_families(api, [fam], api.FS_COLBLOCK64)[0])
+
+
+@pytest.mark.parametrize("tiles", [1, 7, 256, 257, 520, 900, 2100])
+def test_workgroups_follow_the_length_of_the_call(api, oracle, tune, tiles):  # noqa: F811
+    """So many tiles take one, two, three ... of them a workgroup; a family of a few rows beside them takes no more than it has."""
+    tune(api.FS_TUNE_RANK, 1)
+    fams = [W.make_small_family(seed=tiles, n_programs=64 * tiles - 5, stmts=(1, 1), n_trees=70, depth=8, k=5, n_features=24),
+            W.make_small_family(seed=tiles + 1, n_programs=90, stmts=(1, 1), n_trees=17, depth=9, k=5, n_features=164)]
+    for n in (1, 2):
+        for f, dev in zip(fams[:n], run_families(api, fams[:n], api.FS_COLBLOCK64)):
+            check_family(oracle, f, dev)
+
+
 def test_models_of_different_trees_in_one_launch(api, oracle, tune):  # noqa: F811
     tune(api.FS_TUNE_RANK, 1)
     fams = [W.make_small_family(seed=70 + d, n_programs=90 + 31 * d, stmts=(1, 4), n_trees=3 + 11 * (12 - d), depth=d, k=8)
@@ -32,7 +53,7 @@ def test_models_of_different_trees_in_one_launch(api, oracle, tune):  # noqa: F8
 
 @pytest.mark.parametrize("depth,features", [(8, 164), (8, 180), (8, 251), (9, 100), (9, 164), (2, 600), (1, 630), (0, 9)])
 def test_leaf_values_in_lds_or_in_memory(api, oracle, tune, depth, features):  # noqa: F811
-    """They are held where that leaves room for 64 trees walked at a time on six tiles, and always in shallow trees."""
+    """They are in memory with the last level's splits, whatever the depth and the room beside the tiles."""
     tune(api.FS_TUNE_RANK, 1)
     fam = W.make_small_family(seed=depth + features, n_programs=64 * 9 + 7, stmts=(1, 1), n_trees=53, depth=depth, k=5,
                               n_features=features, bias=-0.5)
