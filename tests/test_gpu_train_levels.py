@@ -63,6 +63,14 @@ def test_counted_children_of_uneven_programs(api, T, tune, programs, slab, packe
     check(api, T, ts, rounds=2, max_depth=7, eta=0.5, lam=1.0)
 
 
+@pytest.mark.parametrize("programs,stmts", [(65, (15, 17)), (64, (16, 16)), (300, (1, 50)), (16_384, (1, 3)), (16_385, (1, 3))])
+def test_gradients_of_long_programs_and_of_many(api, T, programs, stmts):
+    """Around the sixteen rows of a program that are held for its records, and on both sides of the line between
+    workgroups of one wavefront and of four."""
+    ts = W.make_train_set(programs + stmts[1], programs, stmts=stmts, n_features=5, max_cuts=31)
+    check(api, T, ts, rounds=3, max_depth=3, eta=0.5, lam=1.0)
+
+
 def test_second_boost_goes_deeper_and_a_family_without_a_split(api, T):
     import torch
     sets = [rows_set(3, 3000, 20), rows_set(4, 1, 3), W.make_train_set(5, 700, stmts=(1, 9), n_features=164, max_cuts=63)]
