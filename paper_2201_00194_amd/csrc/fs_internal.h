@@ -418,6 +418,7 @@ struct RankColumn {
     float scale, offset;
     int32_t buckets, steps;
 };
+constexpr int kRankMostSteps = 4;
 constexpr int kRankWaves = 16;
 constexpr int kRankLdsBytes = 160 * 1024;
 constexpr int kRankMostTrees = 8;        // of a slot

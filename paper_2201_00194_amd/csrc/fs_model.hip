@@ -484,7 +484,7 @@ inline int rank_bucket(float x, const RankColumn &c, bool *tie)
 bool bucket_tables(fs_model *m, int n_features, int max_cuts, const std::vector<std::vector<float>> &per,
                    std::vector<float> *tables)
 {
-    constexpr int kMostSteps = 4, kPast = 1 << (kMostSteps - 1);
+    constexpr int kMostSteps = kRankMostSteps, kPast = 1 << (kMostSteps - 1);
     // two buckets a threshold if whole fours of features fit then (the coder searches four at a time), else what is left
     const int keys = (max_cuts + kPast + 3) & ~3;
     int group = kBinTableBytes / (16 + 4 * keys + 4 * max_cuts) & ~3;

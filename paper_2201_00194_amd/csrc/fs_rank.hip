@@ -38,10 +38,89 @@ constexpr int kBinThreads = 1024;
 // interleaved per wavefront.
 //
 // Where the thresholds are spread well enough (bucket_tables), the tree's upper levels give way to a bucket table: a
-// multiply-add finds the bucket, the table the thresholds below it, and a bisection of at most 5 steps the bucket's own.
-// (With q = 12 steps of four instructions vector issue took 95 % of the clocks, now memory bounds it: 2.1 M rows of
-// 164 features, 3100 thresholds each, 2.1 GB: 611 us, so 490.)
+// multiply-add finds the bucket, the table the thresholds below it, and a bisection of at most 4 steps the bucket's own.
+// (With q = 12 steps of four instructions vector issue took 95 % of the clocks.  2.1 M rows of 164 features, 3100 thresholds
+// each, 2.1 GB: 611 us, by buckets 490, see below for what is left of that.)
 constexpr int kBinChains = 4;
+
+template <int N> struct RankInt { static constexpr int value = N; };
+
+// Column-blocked rows by buckets: a wavefront takes four features at a time over all its tiles, so that what the
+// features' tables say is read once and the loop is vector and LDS instructions.  (Feature by feature within a tile the
+// loop had 40 scalar instructions a search beside 26 vector ones, and scalar loads among its LDS reads:
+// 2.1 M rows of 164 features, 3100 thresholds each, 488 us, so 392; the bytes take 322.)
+template <int STEPS>
+__device__ __forceinline__ void code_by_buckets(const FamDesc &d, int f0, int gf, int len, int t0, int nt, int wave, int lane)
+{
+    constexpr int kWaves = kBinThreads / 64;
+    const int F = d.n_features;
+    const uint32_t tile_words = (uint32_t)rank_tile_cols(F) * 32u;            // of a tile of ranks
+    for (int j0 = 0; j0 < gf; j0 += kBinChains) {
+        float scale[kBinChains], offset[kBinChains];
+        uint32_t lut[kBinChains], keys[kBinChains], most = 0;
+        uint32_t from[kBinChains];
+#pragma unroll
+        for (int k = 0; k < kBinChains; ++k) {
+            const int j = min(j0 + k, gf - 1);
+            auto col = FS_CONST(RankColumn, d.cuts + (int64_t)(f0 + j) * len);
+            scale[k] = col->scale;
+            offset[k] = col->offset;
+            most = (uint32_t)col->buckets - 1u;                              // the same for all features
+            lut[k] = 4u * (uint32_t)(j * len) + 16u;
+            keys[k] = lut[k] + 2u * (most + 1u);
+            from[k] = 64u * (uint32_t)(f0 + j);
+        }
+        const int n = min(kBinChains, gf - j0);
+        auto X = FS_GLOBAL(const float, d.features) + (int64_t)t0 * F * 64 + lane;
+        auto R = FS_GLOBAL(uint16_t, d.ranks) + (int64_t)t0 * tile_words * 2 + 2 * lane;
+        float next[kBinChains] = {};
+        if (wave < nt)
+#pragma unroll
+            for (int k = 0; k < kBinChains; ++k)
+                next[k] = X[(int64_t)wave * F * 64 + from[k]];
+        for (int t = wave; t < nt; t += kWaves) {
+            float x[kBinChains];
+            uint32_t at[kBinChains], r[kBinChains];
+#pragma unroll
+            for (int k = 0; k < kBinChains; ++k)
+                x[k] = next[k];
+            const int64_t ahead = (int64_t)min(t + kWaves, nt - 1) * F * 64;
+#pragma unroll
+            for (int k = 0; k < kBinChains; ++k)
+                next[k] = X[ahead + from[k]];
+#pragma unroll
+            for (int k = 0; k < kBinChains; ++k)
+                at[k] = lds_u16(lut[k] + 2u * min(to_u32(__builtin_fmaf(x[k], scale[k], offset[k])), most));
+#pragma unroll
+            for (int k = 0; k < kBinChains; ++k)
+                at[k] = keys[k] + 4u * at[k];                                // the first threshold that is not known to be <= x
+#pragma unroll
+            for (int s = STEPS - 1; s >= 0; --s) {
+                float c[kBinChains];
+#pragma unroll
+                for (int k = 0; k < kBinChains; ++k)
+                    c[k] = lds_f(at[k] + (4u << s) - 4u);
+#pragma unroll
+                for (int k = 0; k < kBinChains; ++k)
+                    at[k] += c[k] <= x[k] ? 4u << s : 0u;
+            }
+#pragma unroll
+            for (int k = 0; k < kBinChains; ++k)
+                r[k] = x[k] != x[k] ? 65535u : (at[k] - keys[k]) >> 2;
+            const int64_t base = (int64_t)t * tile_words * 2;                 // u16 units
+            if (n == kBinChains) {                           // features 2i and 2i + 1 share a word of the tile (f0 is a multiple of 4)
+#pragma unroll
+                for (int k = 0; k < kBinChains; k += 2)
+                    *(__attribute__((address_space(1))) uint32_t *)(R + base + (rank_feature_offset(f0 + j0 + k) >> 1)) = r[k] | r[k + 1] << 16;
+            } else {
+#pragma unroll
+                for (int k = 0; k < kBinChains; ++k)
+                    if (k < n)
+                        R[base + (rank_feature_offset(f0 + j0 + k) >> 1)] = (uint16_t)r[k];
+            }
+        }
+    }
+}
 
 __global__ void __launch_bounds__(kBinThreads, 8)     // two workgroups per compute unit
 rank_code_kernel(const FamDesc *__restrict__ descs, int n_families)
@@ -80,6 +159,17 @@ rank_code_kernel(const FamDesc *__restrict__ descs, int n_families)
         lds_direct_wait();
     }
     __syncthreads();
+
+    if (bucketed && d.layout != FS_ROWMAJOR) {
+        switch (FS_CONST(RankColumn, d.cuts)->steps) {               // the same for all features
+        case 0: code_by_buckets<0>(d, f0, gf, len, t0, nt, wave, lane); break;
+        case 1: code_by_buckets<1>(d, f0, gf, len, t0, nt, wave, lane); break;
+        case 2: code_by_buckets<2>(d, f0, gf, len, t0, nt, wave, lane); break;
+        case 3: code_by_buckets<3>(d, f0, gf, len, t0, nt, wave, lane); break;
+        default: code_by_buckets<kRankMostSteps>(d, f0, gf, len, t0, nt, wave, lane);
+        }
+        return;
+    }
 
     auto X = FS_GLOBAL(const float, d.features);
     auto R = FS_GLOBAL(uint16_t, d.ranks);
@@ -301,8 +391,6 @@ static __device__ __forceinline__ void wait_for(uint32_t counter, uint32_t count
     (void)counter; (void)count;
 #endif
 }
-
-template <int N> struct RankInt { static constexpr int value = N; };
 
 // REGS: 16-byte registers per thread for a slot's next trees.  (No more than they take: a load of a register too
 // many costs as much as one that is needed, eleven for six 25 % of the kernel's time; loads under a
