@@ -778,13 +778,15 @@ static int topk_joins(int lists) { return lists / kTopkWays + (lists % kTopkWays
 struct TopkSizes {
     size_t n_blocks = 0, n_merge = 0, comp_total = 0, n_joins_total = 0;
     int max_comp = 0, n_levels = 0, max_k = 0;
+    bool whole = true;               // no request is cut into slices
 };
 
 // Validates the requests and sizes the submission: first-stage workgroups, LDS merges, pairwise
 // merges per level, scratch composites (8 bytes each).
-static int topk_sizes(const char *who, int32_t n_requests, const fs_topk_req *reqs, TopkSizes *out)
+static int topk_sizes(const char *who, int32_t n_requests, const fs_topk_req *reqs, bool may_be_whole, TopkSizes *out)
 {
     TopkSizes z;
+    z.whole = may_be_whole;
     for (int i = 0; i < n_requests; ++i) {
         const fs_topk_req &r = reqs[i];
         if (r.n < 0 || r.k < 0)
@@ -798,10 +800,11 @@ static int topk_sizes(const char *who, int32_t n_requests, const fs_topk_req *re
             return fail(FS_EINVAL, "%s: request %d: out_idx is NULL", who, i);
         if (r.k > z.max_k)
             z.max_k = r.k;
+        z.whole &= topk_whole(r.n, r.k);
     }
     for (int i = 0; i < n_requests; ++i) {
         const fs_topk_req &r = reqs[i];
-        const TopkPlan p = topk_plan(r.n, r.k);
+        const TopkPlan p = topk_plan(r.n, r.k, z.whole);
         z.n_blocks += (size_t)p.s;
         if (p.mode == 1) {
             ++z.n_merge;
@@ -840,7 +843,8 @@ extern "C" size_t fs_topk_workspace_bytes(int32_t n_requests, const fs_topk_req 
         return 0;
     }
     TopkSizes z;
-    if (topk_sizes("fs_topk_workspace_bytes", n_requests, reqs, &z) != FS_OK)
+    // (as if cut into slices, so that what is set aside for these requests also serves them beside longer ones)
+    if (topk_sizes("fs_topk_workspace_bytes", n_requests, reqs, false, &z) != FS_OK)
         return 0;
     return z.comp_total * sizeof(unsigned long long);
 }
@@ -855,7 +859,7 @@ extern "C" int fs_topk(int32_t n_requests, const fs_topk_req *reqs, void *stream
     if (!reqs)
         return fail(FS_EINVAL, "fs_topk: reqs is NULL");
     TopkSizes z;
-    int rc = topk_sizes("fs_topk", n_requests, reqs, &z);
+    int rc = topk_sizes("fs_topk", n_requests, reqs, true, &z);
     if (rc != FS_OK)
         return rc;
     const int max_k = z.max_k;
@@ -867,7 +871,7 @@ extern "C" int fs_topk(int32_t n_requests, const fs_topk_req *reqs, void *stream
     rc = current_ctx(&ctx);
     if (rc != FS_OK)
         return rc;
-    auto plan_of = [](const fs_topk_req &r) { return topk_plan(r.n, r.k); };
+    auto plan_of = [&z](const fs_topk_req &r) { return topk_plan(r.n, r.k, z.whole); };
     typedef TopkPlan Plan;
     const size_t n_blocks = z.n_blocks, n_merge = z.n_merge, comp_total = z.comp_total,
                  n_joins_total = z.n_joins_total;
@@ -1004,7 +1008,10 @@ extern "C" int fs_topk(int32_t n_requests, const fs_topk_req *reqs, void *stream
     }
     const char *dev = (const char *)db.dev;
     prof_start(kKernTopk, stream);
-    rc = launch_topk({near ? nullptr : (const TopkDesc *)dev, h, (int)n_blocks}, max_k, stream);
+    int max_entries = 0;
+    for (size_t i = 0; i < n_blocks; ++i)
+        max_entries = std::max(max_entries, h[i].sub_end - h[i].sub_begin);
+    rc = launch_topk({near ? nullptr : (const TopkDesc *)dev, h, (int)n_blocks}, max_k, max_entries, stream);
     if (rc == FS_OK && n_merge)
         rc = launch_topk_merge({near ? nullptr : (const TopkMergeDesc *)(dev + merge_off), hm, (int)n_merge},
                                max_comp, stream);

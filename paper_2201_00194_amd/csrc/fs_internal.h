@@ -339,10 +339,15 @@ int launch_traverse_rank(const FamDesc *d_desc, int n_families, int total_blocks
 int launch_treelet(const Descs<FamDesc> &descs, int launch, int form, int total_blocks, bool dump,
                    hipStream_t stream);
 int launch_segsum(const Descs<FamDesc> &descs, int total_blocks, hipStream_t stream);
-int launch_topk(const Descs<TopkDesc> &descs, int max_k, hipStream_t stream);
+// max_entries: of a workgroup
+int launch_topk(const Descs<TopkDesc> &descs, int max_k, int max_entries, hipStream_t stream);
 // max_padded: largest (slices * k rounded up to a power of two) over the requests
 int launch_topk_merge(const Descs<TopkMergeDesc> &descs, int max_padded, hipStream_t stream);
-constexpr int kTopkSliceMin = 8192;      // requests at least this long are split into slices
+constexpr int kTopkSliceMin = 8192;      // requests at least this long are split into slices,
+constexpr int kTopkAtOnce = 16384;       // but not up to this long with a small cut, in calls without longer ones: a workgroup
+constexpr int kTopkSmallCut = 256;       // holds so many keys, and there is no second kernel then.  Five cuts of 50 of 9001 12.1
+                                         // us in slices and 9.6 so, eight of 128 of 10 000 13.5 and 11.0, of 256 14.5 and
+                                         // 11.5, four of 256 of 16 384 17.5 and 12.4; beside one of 65 536 14.5 and 16.8
 constexpr int kTopkSliceEntries = 2048;  // of at least this many entries
 constexpr int kTopkMaxSlices = 16;
 constexpr int kTopkMergeCap = 16384;     // composites (lists padded to a power of two) the merge holds in LDS
@@ -355,10 +360,12 @@ constexpr int kTopkWideMaxSlices = 128;
 //   mode 2  long request with a wider cut: slices of about kTopkWideSlice entries leave their best
 //           min(k, length) sorted, then merges of kTopkWays lists in global memory, level by level.
 struct TopkPlan { int mode, s, per; };
-inline TopkPlan topk_plan(int n, int k)
+// `whole`: no request of the call needs slices whatever the others do (topk_whole).
+inline bool topk_whole(int n, int k) { return n < kTopkSliceMin || k == 0 || (n <= kTopkAtOnce && k <= kTopkSmallCut); }
+inline TopkPlan topk_plan(int n, int k, bool whole)
 {
     TopkPlan p = {0, 1, n};
-    if (n < kTopkSliceMin || k == 0)
+    if (whole || n < kTopkSliceMin || k == 0)
         return p;
     int kp = 1;
     while (kp < k)

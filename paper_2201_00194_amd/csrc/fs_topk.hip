@@ -14,13 +14,14 @@
 //      (key, ~index) in LDS;
 //   3. the composites are sorted: runs of 64 by counting, then merges of two runs in which each
 //      entry finds its place by bisection; all composites differ, so the result is unique.
-// A long request (>= 8192 entries) is cut into up to 16 slices, one workgroup each, which
+// A long request (8192 entries, with small cuts 16384) is cut into up to 16 slices, one workgroup each, which
 // leave their best k composites in scratch, best first; a second kernel merges the slices'
 // lists pairwise in LDS, keeping the best k of every pair, and writes the answer.  The union
 // of the slices' best k holds the request's best k, and composites order the same way
 // everywhere, so nothing changes in the result.  Cuts wider than 4096 do not fit that merge:
 // they are cut into slices of about 2048 entries (up to 128) whose sorted lists are merged
 // eight at a time in global memory, level by level, each merge keeping the best k.
+#include <algorithm>
 #include <cstring>
 #include <mutex>
 
@@ -40,18 +41,21 @@ __device__ __forceinline__ uint32_t score_key(float s)
 }
 
 constexpr int kTopkWaves = kTopkThreads / 64;
-constexpr int kTopkUnroll = 8;     // loads in flight per thread
+// Entries a thread holds, all loads in flight at once: 16 where a workgroup has more than 8192 entries, as their keys are
+// read once then (262 144 entries in 16 slices, cut of 64: 27.5 us with 8, so 17.5; cut of 1024 53.5 and 49.1), else 8.
+constexpr int kTopkFew = 8, kTopkMany = kTopkAtOnce / kTopkThreads;
 
-// Scores and keys of kTopkUnroll consecutive 64-element pieces starting at `base`, this lane's element of
+// Scores and keys of U consecutive 64-element pieces starting at `base`, this lane's element of
 // each; pieces past `end` read a clamped address and are flagged invalid by the caller.
+template <int U>
 __device__ __forceinline__ void load_keys(const float *__restrict__ score, int base, int end,
-                                          int lane, uint32_t (&key)[kTopkUnroll], float (&v)[kTopkUnroll])
+                                          int lane, uint32_t (&key)[U], float (&v)[U])
 {
 #pragma unroll
-    for (int u = 0; u < kTopkUnroll; ++u)
+    for (int u = 0; u < U; ++u)
         v[u] = score[min(base + u * 64 + lane, end - 1)];
 #pragma unroll
-    for (int u = 0; u < kTopkUnroll; ++u)
+    for (int u = 0; u < U; ++u)
         key[u] = score_key(v[u]);
 }
 
@@ -197,6 +201,7 @@ __device__ __forceinline__ void sort_bitonic(unsigned long long *c, int n, int t
     }
 }
 
+template <int U>
 __global__ void __launch_bounds__(kTopkThreads)
 topk_kernel(const TopkDesc *__restrict__ far, NearTopk)
 {
@@ -233,11 +238,11 @@ topk_kernel(const TopkDesc *__restrict__ far, NearTopk)
     const int per_wave = (((n + kTopkWaves - 1) / kTopkWaves) + 63) & ~63;
     const int w_begin = min(wave * per_wave, n), w_end = min(w_begin + per_wave, n);
 
-    // A wavefront whose slice is a single round of loads (requests of up to 8192 entries)
+    // A wavefront whose slice is a single round of loads (requests of up to 1024 * U entries)
     // fetches its keys once and keeps them in registers for all six sweeps below.
-    const bool cached = per_wave <= 64 * kTopkUnroll;
-    uint32_t key[kTopkUnroll];
-    float v[kTopkUnroll];
+    const bool cached = per_wave <= 64 * U;
+    uint32_t key[U];
+    float v[U];
     if (cached && w_begin < w_end)
         load_keys(score, w_begin, w_end, lane, key, v);
 
@@ -253,11 +258,11 @@ topk_kernel(const TopkDesc *__restrict__ far, NearTopk)
                 hist[b] = 0;
             __syncthreads();
             int run_digit = -1, run = 0;
-            for (int base = w_begin; base < w_end; base += 64 * kTopkUnroll) {
+            for (int base = w_begin; base < w_end; base += 64 * U) {
                 if (!cached)
                     load_keys(score, base, w_end, lane, key, v);
 #pragma unroll
-                for (int u = 0; u < kTopkUnroll; ++u) {
+                for (int u = 0; u < U; ++u) {
                     const bool valid = base + u * 64 + lane < w_end;
                     if (valid && (key[u] & mask) == prefix) {
                         const int dg = (key[u] >> shift) & (kBinsOf - 1) & ~(mask >> shift);
@@ -300,7 +305,7 @@ topk_kernel(const TopkDesc *__restrict__ far, NearTopk)
         if (n > kRankAll) {
             int mine = 0;
 #pragma unroll
-            for (int u = 0; u < kTopkUnroll; ++u)
+            for (int u = 0; u < U; ++u)
                 mine += __popcll(__builtin_amdgcn_ballot_w64(w_begin + u * 64 + lane < w_end && key[u] >= prefix));
             if (mine && lane == 0)
                 at = atomicAdd(&sel[3], mine);
@@ -308,7 +313,7 @@ topk_kernel(const TopkDesc *__restrict__ far, NearTopk)
         }
         const unsigned long long below = (1ull << lane) - 1ull;
 #pragma unroll
-        for (int u = 0; u < kTopkUnroll; ++u) {
+        for (int u = 0; u < U; ++u) {
             const int i = w_begin + u * 64 + lane;
             const bool take = i < w_end && key[u] >= prefix;
             const unsigned long long who = __builtin_amdgcn_ballot_w64(take);
@@ -360,11 +365,11 @@ topk_kernel(const TopkDesc *__restrict__ far, NearTopk)
 
     // ---- 2. collect, in index order: count per wavefront, scan, then place ----
     int my_gt = 0, my_eq = 0;
-    for (int base = w_begin; base < w_end && !all; base += 64 * kTopkUnroll) {
+    for (int base = w_begin; base < w_end && !all; base += 64 * U) {
         if (!cached)
             load_keys(score, base, w_end, lane, key, v);
 #pragma unroll
-        for (int u = 0; u < kTopkUnroll; ++u) {
+        for (int u = 0; u < U; ++u) {
             const bool valid = base + u * 64 + lane < w_end;
             my_gt += __popcll(__ballot(valid && key[u] > tau));
             my_eq += __popcll(__ballot(valid && key[u] == tau));
@@ -381,11 +386,11 @@ topk_kernel(const TopkDesc *__restrict__ far, NearTopk)
         eq_before += wave_cnt[kTopkWaves + w];
     }
     const unsigned long long below = (1ull << lane) - 1ull;
-    for (int base = w_begin; base < w_end; base += 64 * kTopkUnroll) {
+    for (int base = w_begin; base < w_end; base += 64 * U) {
         if (!cached)
             load_keys(score, base, w_end, lane, key, v);
 #pragma unroll
-        for (int u = 0; u < kTopkUnroll; ++u) {
+        for (int u = 0; u < U; ++u) {
             const int i = base + u * 64 + lane;
             const bool valid = i < w_end;
             const bool gt = valid && (all || key[u] > tau), eq = valid && !gt && key[u] == tau;
@@ -607,7 +612,8 @@ int launch_topk_merge(const Descs<TopkMergeDesc> &descs, int max_padded, hipStre
     return FS_OK;
 }
 
-int launch_topk(const Descs<TopkDesc> &descs, int max_k, hipStream_t stream)
+template <int U>
+static int launch_topk_form(const Descs<TopkDesc> &descs, int max_k, hipStream_t stream)
 {
     int kpow2 = 2;
     while (kpow2 < max_k)
@@ -617,16 +623,22 @@ int launch_topk(const Descs<TopkDesc> &descs, int max_k, hipStream_t stream)
     int dev = 0;
     FS_HIP(hipGetDevice(&dev));
     if (lds > 65536 && (dev < 0 || dev >= 16 || configured[dev] < lds)) {
-        FS_HIP(hipFuncSetAttribute((const void *)topk_kernel,
+        FS_HIP(hipFuncSetAttribute((const void *)topk_kernel<U>,
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         if (dev >= 0 && dev < 16)
             configured[dev] = lds;
     }
-    hipLaunchKernelGGL(topk_kernel, dim3(descs.n), dim3(kTopkThreads), lds, stream, descs.far, near_descs<NearTopk>(descs));
+    hipLaunchKernelGGL(topk_kernel<U>, dim3(descs.n), dim3(kTopkThreads), lds, stream, descs.far, near_descs<NearTopk>(descs));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return fail_hip(e, "topk_kernel launch");
     return FS_OK;
+}
+
+int launch_topk(const Descs<TopkDesc> &descs, int max_k, int max_entries, hipStream_t stream)
+{
+    return max_entries > kTopkFew * kTopkThreads ? launch_topk_form<kTopkMany>(descs, max_k, stream)
+                                                 : launch_topk_form<kTopkFew>(descs, max_k, stream);
 }
 
 // ---- fs_topk_noalloc: the same cut for callers that cannot allocate -----------------------------
@@ -665,6 +677,9 @@ extern "C" int fs_topk_noalloc(int32_t n_requests, const fs_topk_req *reqs, void
         return fail(FS_EINVAL, "fs_topk_noalloc: reqs is NULL");
     size_t n_blocks = 0, n_merge = 0, comp_total = 0;
     int max_k = 0, max_comp = 0;
+    bool whole = true;
+    for (int i = 0; i < n_requests; ++i)
+        whole &= topk_whole(reqs[i].n, reqs[i].k);
     for (int i = 0; i < n_requests; ++i) {
         const fs_topk_req &r = reqs[i];
         if (r.n < 0 || r.k < 0)
@@ -676,7 +691,7 @@ extern "C" int fs_topk_noalloc(int32_t n_requests, const fs_topk_req *reqs, void
             return fail(FS_EINVAL, "fs_topk_noalloc: request %d: score is NULL", i);
         if (r.k > 0 && !r.out_idx)
             return fail(FS_EINVAL, "fs_topk_noalloc: request %d: out_idx is NULL", i);
-        const TopkPlan p = topk_plan(r.n, r.k);
+        const TopkPlan p = topk_plan(r.n, r.k, whole);
         if (p.mode == 2)
             return fail(FS_EUNSUPPORTED, "fs_topk_noalloc: request %d: cuts wider than 4096 of %d or "
                         "more entries are not served without allocation (use fs_topk)", i, kTopkSliceMin);
@@ -728,7 +743,7 @@ extern "C" int fs_topk_noalloc(int32_t n_requests, const fs_topk_req *reqs, void
     size_t b = 0, m = 0;
     for (int i = 0; i < n_requests; ++i) {
         const fs_topk_req &r = reqs[i];
-        const TopkPlan p = topk_plan(r.n, r.k);
+        const TopkPlan p = topk_plan(r.n, r.k, whole);
         for (int j = 0; j < p.s; ++j, ++b) {
             h[b].score = r.score;
             h[b].out_idx = r.out_idx;
@@ -763,7 +778,10 @@ extern "C" int fs_topk_noalloc(int32_t n_requests, const fs_topk_req *reqs, void
     if (e != hipSuccess)
         return fail_hip(e, "topk_store_desc_kernel launch");
     prof_start(kKernTopk, stream);
-    int rc = launch_topk({(const TopkDesc *)base, nullptr, (int)n_blocks}, max_k, stream);
+    int max_entries = 0;
+    for (size_t i = 0; i < n_blocks; ++i)
+        max_entries = std::max(max_entries, h[i].sub_end - h[i].sub_begin);
+    int rc = launch_topk({(const TopkDesc *)base, nullptr, (int)n_blocks}, max_k, max_entries, stream);
     if (rc == FS_OK && n_merge)
         rc = launch_topk_merge({(const TopkMergeDesc *)(base + merge_off), nullptr, (int)n_merge}, max_comp, stream);
     prof_stop(stream);

@@ -36,3 +36,24 @@ def test_cut(api, oracle, kind, n, k):
     e_idx, e_best = oracle.topk(score, k)
     assert np.array_equal(idx.cpu().numpy(), e_idx)
     assert np.array_equal(best.cpu().numpy().view(np.uint32), e_best.view(np.uint32))
+
+
+@pytest.mark.parametrize("kind", ["random", "equal", "special"])
+@pytest.mark.parametrize("sizes", [[(8192, 256)], [(8193, 257)], [(16_383, 64), (9001, 50)], [(16_384, 256), (1, 1)], [(16_385, 64)],
+                                   [(12_000, 64), (16_385, 64)], [(12_000, 64), (8192, 300)], [(9000, 0), (9000, 1)],
+                                   [(262_144, 64), (300, 16)]])
+def test_whole_requests_and_slices(api, oracle, kind, sizes):
+    """Both sides of the lines between one workgroup and slices, which follow all requests of a call."""
+    import torch
+    g = np.random.default_rng(len(sizes) * sizes[0][0])
+    score = [SCORES[kind](g, n).astype(np.float32) for n, _ in sizes]
+    reqs, outs = [], []
+    for s, (n, k) in zip(score, sizes):
+        idx, best = torch.full((max(k, 1),), 7, dtype=torch.int32, device="cuda"), torch.zeros(max(k, 1), device="cuda")
+        reqs.append(api.TopkRequest(torch.from_numpy(s).cuda(), n, k, idx, best))
+        outs.append((idx, best))
+    api.fs_topk(reqs)
+    for s, (n, k), (idx, best) in zip(score, sizes, outs):
+        e_idx, e_best = oracle.topk(s, k)
+        assert np.array_equal(idx.cpu().numpy()[:k], e_idx)
+        assert np.array_equal(best.cpu().numpy()[:k].view(np.uint32), e_best.view(np.uint32))
