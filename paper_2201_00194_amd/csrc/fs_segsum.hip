@@ -2,16 +2,29 @@
 //
 // A candidate program's score is the sum of the model's outputs over its statement rows;
 // the additions are sequential fp32 in ascending row order starting from +0, so the
-// result is reproducible bit for bit.  One lane owns one program.  A wavefront streams
-// the contiguous row range of its 64 programs through registers 64 rows at a time
-// (coalesced loads) and every lane pulls the rows it owns out of the current window with
-// wavefront shuffles, one row per step, in order.  That suits very short programs (many
-// programs per 64-row window).  When the wavefront's programs average more than 4 rows (measured:
-// from 8 rows per program on the shuffles lose), every lane reads its own rows straight from
-// memory instead, four loads in flight, still adding them in ascending order.
+// result is reproducible bit for bit.  One lane owns one program.  A wavefront takes the contiguous rows of its 64
+// programs to LDS, 2048 at a time with coalesced loads that are all in flight at once, and every lane adds its own from
+// there, in order.  (Rows read from memory by each lane for itself, four at a time, were a chain of up to 16 latencies of
+// lines that 64 lanes share with nobody: 200 000 programs of 1 to 64 rows 32.5 us, sixteen at
+// a time 26.3, so 16.9; 80 000 of 16 rows 7.7 and 5.3.)
 #include "fs_internal.h"
+#include "fs_lds.h"
 
 namespace fs {
+
+constexpr int kSegWindow = 2048;         // rows in LDS of a wavefront; a word of padding every 16 keeps programs of 16, 32 ... rows
+                                         // off each other's banks
+constexpr int kSegLoads = 16;            // loads in flight per lane
+constexpr int kSegAdds = 8;              // LDS reads in flight per lane
+__device__ __forceinline__ int seg_word(int i) { return i + (i >> 4); }
+
+// What this wavefront has done in LDS is done.
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 __global__ void __launch_bounds__(kSegProgsPerBlock)
 segsum_kernel(const FamDesc *__restrict__ far, int n_families, NearFams)
@@ -36,7 +49,7 @@ segsum_kernel(const FamDesc *__restrict__ far, int n_families, NearFams)
     const int p = p_wave + lane;
     const int p_last = min(p_wave + 64, n_programs);
     const int n_rows = d.n_rows;
-    // Lanes past the family's last program own no rows but keep taking part in the shuffles.
+    // Lanes past the family's last program own no rows but load for the others.
     int begin = 0, end = 0;
     if (p < n_programs) {
         begin = min(max(off[p], 0), n_rows);
@@ -45,38 +58,33 @@ segsum_kernel(const FamDesc *__restrict__ far, int n_families, NearFams)
     const int w_begin = min(max(off[p_wave], 0), n_rows);
     const int w_end = min(max(off[p_last], w_begin), n_rows);
 
+    __shared__ float s_rows[kSegProgsPerBlock / 64][kSegWindow + kSegWindow / 16];
+    float *const mine = s_rows[threadIdx.x >> 6];
+    auto rows = FS_GLOBAL(const float, rs);
     float acc = 0.0f;
-    int cur = begin;
-    if (w_end - w_begin > 4 * (p_last - p_wave)) {         // longer programs: per-lane reads
-        while (__any(cur < end)) {
-            float v[4];
+    for (int base = w_begin; base < w_end; base += kSegWindow) {
+        const int n = min(kSegWindow, w_end - base);
+        for (int at = lane; at < n; at += 64 * kSegLoads) {
+            float v[kSegLoads];
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
-                v[u] = (cur + u < end) ? rs[cur + u] : 0.0f;
+            for (int u = 0; u < kSegLoads; ++u)
+                v[u] = rows[base + min(at + 64 * u, n - 1)];
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (cur + u < end)
-                    acc = acc + v[u];
-            cur += 4;
+            for (int u = 0; u < kSegLoads; ++u)
+                mine[seg_word(at + 64 * u)] = v[u];        // (at + 64 * u < kSegWindow)
         }
-        if (p < n_programs)
-            d.prog_score[p] = acc;
-        return;
-    }
-    for (int base = w_begin; base < w_end; base += 64) {
-        const int idx = base + lane;
-        const float v = (idx < w_end) ? rs[idx] : 0.0f;
-        const int win_end = min(base + 64, w_end);
-        while (true) {
-            const bool active = (cur < end) && (cur < win_end) && (cur >= base);
-            if (!__any(active))
-                break;
-            const float t = __shfl(v, active ? (cur - base) : 0, 64);
-            if (active) {
-                acc = acc + t;
-                ++cur;
-            }
+        wave_sync();
+        const int from = max(begin - base, 0), to = min(end - base, n);
+        for (int i = from; i < to; i += kSegAdds) {
+            float v[kSegAdds];
+#pragma unroll
+            for (int u = 0; u < kSegAdds; ++u)
+                v[u] = mine[seg_word(min(i + u, to - 1))];
+#pragma unroll
+            for (int u = 0; u < kSegAdds; ++u)
+                acc = i + u < to ? acc + v[u] : acc;
         }
+        wave_sync();                                       // read before the next window is written
     }
     if (p < n_programs)
         d.prog_score[p] = acc;
