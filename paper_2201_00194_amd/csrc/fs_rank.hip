@@ -311,8 +311,9 @@ int launch_rank_code(const FamDesc *d_desc, int n_families, int total_blocks, hi
 // trees of depth 10 took 5500 clocks, 3300 of them walks, the rest copying 64 KB into LDS and
 // adding up while nothing else ran.  2.1 M rows, 500 such trees: 4.63 ms, so 3.85.)
 //
-// Bound by the latency of two LDS reads a level at the walks that fit side by side (vector issue 47 % and LDS 55 % at 72
-// of them), and what they need is room: half of a tree's splits are its last level and half of its words the
+// Two LDS reads a level are a chain of latencies, so what decides is how many walks fit side by side (at 72 of them vector
+// issue was 47 % and LDS 55 %; at 128 it is 61 %, and an LDS instruction every 4.15 clocks, the mean of a feature's
+// conflict-free read, 2.4, and a node's at random, 5.8), and what they need is room: half of a tree's splits are its last level and half of its words the
 // leaves, each read once a walk.  So both stay in memory, a split and its two values in one record: a slot asks for
 // its walks' records, replaces its trees, and then takes the last decisions and adds the values up.  A tree of depth
 // 10 is 2 KB in LDS then and four tiles have 16 wavefronts of eight walks.  (2.1 M rows of 164 features, 500 trees of
