@@ -711,7 +711,7 @@ extern "C" int fs_score_families(int32_t n_families, const fs_family *fams, void
                 dump[md] = true;
         } else
         trav_blocks += (a.n_rows + kTravRowsPerBlock - 1) / kTravRowsPerBlock;
-        seg_blocks += (a.n_programs + kSegProgsPerBlock - 1) / kSegProgsPerBlock;
+        seg_blocks += ((int64_t)a.n_programs + kSegProgsPerBlock - 1) / kSegProgsPerBlock;
         h[f] = d;
     }
     if (trav_blocks >= ((int64_t)1 << 31) || seg_blocks >= ((int64_t)1 << 31) ||

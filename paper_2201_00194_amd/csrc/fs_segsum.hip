@@ -9,6 +9,7 @@
 // a time 26.3, so 16.9; 80 000 of 16 rows 7.7 and 5.3.)
 #include "fs_internal.h"
 #include "fs_lds.h"
+#include "fs_runs.h"
 
 namespace fs {
 
@@ -47,7 +48,7 @@ segsum_kernel(const FamDesc *__restrict__ far, int n_families, NearFams)
     if (p_wave >= n_programs)
         return;                                     // whole wavefront leaves together
     const int p = p_wave + lane;
-    const int p_last = min(p_wave + 64, n_programs);
+    const int p_last = p_wave + min(64, n_programs - p_wave);
     const int n_rows = d.n_rows;
     // Lanes past the family's last program own no rows but load for the others.
     int begin = 0, end = 0;
@@ -62,8 +63,8 @@ segsum_kernel(const FamDesc *__restrict__ far, int n_families, NearFams)
     float *const mine = s_rows[threadIdx.x >> 6];
     auto rows = FS_GLOBAL(const float, rs);
     float acc = 0.0f;
-    for (int base = w_begin; base < w_end; base += kSegWindow) {
-        const int n = min(kSegWindow, w_end - base);
+    in_runs<kSegWindow>(w_begin, w_end, [&](int base, int left) {
+        const int n = min(kSegWindow, left);
         for (int at = lane; at < n; at += 64 * kSegLoads) {
             float v[kSegLoads];
 #pragma unroll
@@ -85,7 +86,7 @@ segsum_kernel(const FamDesc *__restrict__ far, int n_families, NearFams)
                 acc = i + u < to ? acc + v[u] : acc;
         }
         wave_sync();                                       // read before the next window is written
-    }
+    });
     if (p < n_programs)
         d.prog_score[p] = acc;
 }
