@@ -34,6 +34,7 @@
 #include "familyseer_train.h"
 #include "fs_internal.h"
 #include "fs_lds.h"
+#include "fs_runs.h"
 
 namespace fs {
 
@@ -434,33 +435,33 @@ train_grad_kernel(const TrainDesc *__restrict__ descs, float grad_scale, int wit
         const int b = d.prog_off[p], e = d.prog_off[p + 1];
         const float target = with_grad ? d.target[p] : 0.0f;
         float first[kGradRows] = {}, s = 0.0f;
-        for (int r = b; r < e; r += kGradRows) {
+        in_runs<kGradRows>(b, e, [&](int r, int left) {
             float v[kGradRows];
 #pragma unroll
             for (int i = 0; i < kGradRows; ++i)
-                v[i] = preds[r < e - i ? r + i : e - 1];
+                v[i] = preds[i < left ? r + i : e - 1];
 #pragma unroll
             for (int i = 0; i < kGradRows; ++i) {
-                s = r + i < e ? s + v[i] : s;
+                s = i < left ? s + v[i] : s;
                 first[i] = r == b ? v[i] : first[i];
             }
-        }
+        });
         d.prog_pred[p] = s;
         if (with_grad) {
             const int q = quantize(s - target, grad_scale);
             const int len = e - b;
             auto recs = FS_GLOBAL(i32x4, d.rec[0]);
-            for (int r = b; r < e; r += kGradRows) {
+            in_runs<kGradRows>(b, e, [&](int r, int left) {
                 if (r > b) {
 #pragma unroll
                     for (int i = 0; i < kGradRows; ++i)
-                        first[i] = preds[r < e - i ? r + i : e - 1];
+                        first[i] = preds[i < left ? r + i : e - 1];
                 }
 #pragma unroll
                 for (int i = 0; i < kGradRows; ++i)
-                    if (r + i < e)
+                    if (i < left)
                         recs[r + i] = (i32x4){r + i, q, len, __float_as_int(first[i])};
-            }
+            });
             G = (long long)q * len;
             H = (long long)len * len;
             A = (unsigned long long)(G < 0 ? -G : G);
