@@ -436,6 +436,9 @@ struct RankLast {                        // a split of a tree's last level, as i
 // For a family of own_tiles in a launch of all_tiles; no tiles where a tree does not fit beside one.
 RankShape rank_shape(int n_features, int n_trees, int tree_bytes, int64_t own_tiles, int64_t all_tiles, int forced_tiles);
 
+// Tiles of up to 2^31 - 1 rows.
+__host__ __device__ inline int row_tiles(int n_rows) { return (int)(((uint32_t)n_rows + 63u) >> 6); }
+
 constexpr int kTravRowsPerBlock = 256;   // rows per block of the global-memory traversal
 constexpr int kSegProgsPerBlock = 256;   // programs per block of the segmented sum
 

@@ -139,7 +139,7 @@ rank_code_kernel(const FamDesc *__restrict__ descs, int n_families)
     const int F = d.n_features;
     const int f0 = group * d.bin_feats_per_group;
     const int gf = min(d.bin_feats_per_group, F - f0);
-    const int n_tiles = (d.n_rows + 63) >> 6;
+    const int n_tiles = row_tiles(d.n_rows);
     const int tpb = d.bin_tiles_per_block;
     const int t0 = tile_block * tpb;
     const int nt = min(tpb, n_tiles - t0);
@@ -414,7 +414,7 @@ traverse_rank_kernel(const FamDesc *__restrict__ descs, int n_families)
     const int T = d.rk.tiles;                   // tiles per workgroup
     const int n_slots = d.rk.slots;             // kRankWaves / T or fewer
     const int my_slot = wave / T, my_tile = wave - my_slot * T;
-    const int n_tiles = (d.n_rows + 63) >> 6;
+    const int n_tiles = row_tiles(d.n_rows);
     const int tile_first = (blockIdx.x - d.rk_block0) * T;
     const int tiles_here = min(T, n_tiles - tile_first);
     const int Fc = rank_tile_cols(d.n_features);

@@ -150,7 +150,7 @@ traverse_lds_kernel(const FamDesc *__restrict__ far, int n_families, int mode, i
     const int wave = uniform(tid >> 6), lane = tid & 63;
     const int T = d.lds_tiles;                  // tiles per workgroup
     const int my_tile = wave % T, my_slot = wave / T;
-    const int n_tiles = (d.n_rows + 63) >> 6;
+    const int n_tiles = row_tiles(d.n_rows);
     const int F = d.n_features;
     // A workgroup takes several consecutive tile groups when the next group's tiles can wait in
     // registers (column-blocked input whose tiles fit kLdsTileRegs pieces per thread): they are

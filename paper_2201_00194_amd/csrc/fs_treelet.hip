@@ -569,17 +569,17 @@ treelet_pair_kernel(const FamDesc *__restrict__ descs, int n_families, int launc
     const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6);
     const int my_tile = wave % kPairTiles;
     const bool back = wave >= kPairTiles;
-    const int n_tiles = (d.n_rows + 63) >> 6;
+    const int n_tiles = row_tiles(d.n_rows);
     const int tile_first = (blockIdx.x - d.tl_block0[launch]) * kPairTiles;
     const uint32_t buf = (uint32_t)m.most_cols * 256u;
     const uint32_t sum_at = (uint32_t)kTreeletLds - kTreeletSumBytes + 256u * (uint32_t)my_tile + 4u * (uint32_t)lane;
     constexpr uint32_t kBack = 256u * (uint32_t)kPairTiles;      // sums of the back half's wavefronts
-    const int r = (tile_first + my_tile) * 64 + lane;
+    const uint32_t r = (uint32_t)(tile_first + my_tile) * 64u + (uint32_t)lane;   // (past 2^31 in missing tiles)
     const uint32_t row = 4u * (uint32_t)lane + (uint32_t)my_tile;
     float acc = d.bias;
     uint16_t *leaf_row = nullptr;
     if (DUMP) {
-        if (d.leaf_idx && r < d.n_rows)
+        if (d.leaf_idx && r < (uint32_t)d.n_rows)
             leaf_row = d.leaf_idx + (int64_t)r * d.n_trees;
     }
 
@@ -681,7 +681,7 @@ treelet_pair_kernel(const FamDesc *__restrict__ descs, int n_families, int launc
             hn = hnn;
         }
     }
-    if (back && r < d.n_rows)
+    if (back && r < (uint32_t)d.n_rows)
         FS_GLOBAL(float, d.row_score)[r] = acc;
 }
 
@@ -702,7 +702,7 @@ treelet_spread_kernel(const FamDesc *__restrict__ far, int n_families, int launc
     const TreeletModel m = load_model(d.tl);
     const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6);
     const int my_tile = wave % T, my_slot = wave / T;
-    const int n_tiles = (d.n_rows + 63) >> 6;
+    const int n_tiles = row_tiles(d.n_rows);
     const int tile_first = (blockIdx.x - d.tl_block0[launch]) * T;
     const uint32_t area = (uint32_t)m.most_cols * 256u, chunk_bytes = (uint32_t)m.buf_bytes;
     constexpr uint32_t kValStride = 256u * (uint32_t)T;
@@ -710,12 +710,12 @@ treelet_spread_kernel(const FamDesc *__restrict__ far, int n_families, int launc
     const uint32_t room = (uint32_t)kTreeletLdsWhole - area;     // one buffer and its rows fit by packing
     const bool two = 2u * (chunk_bytes + row_bytes) <= room;
     const uint32_t val_rows = area + (two ? 2u : 1u) * chunk_bytes;
-    const int r = (tile_first + my_tile) * 64 + lane;
+    const uint32_t r = (uint32_t)(tile_first + my_tile) * 64u + (uint32_t)lane;   // (past 2^31 in missing tiles)
     const uint32_t row = 4u * (uint32_t)lane + (uint32_t)my_tile;
     float acc = d.bias;
     uint16_t *leaf_row = nullptr;
     if (DUMP) {
-        if (d.leaf_idx && r < d.n_rows)
+        if (d.leaf_idx && r < (uint32_t)d.n_rows)
             leaf_row = d.leaf_idx + (int64_t)r * d.n_trees;
     }
     for (int si = 0; si < m.n_segments; ++si) {
@@ -787,7 +787,7 @@ treelet_spread_kernel(const FamDesc *__restrict__ far, int n_families, int launc
         if (two && si + 1 < m.n_segments)
             __syncthreads();                         // the next segment's tables overwrite the last values
     }
-    if (my_slot == 0 && r < d.n_rows)
+    if (my_slot == 0 && r < (uint32_t)d.n_rows)
         FS_GLOBAL(float, d.row_score)[r] = acc;
 }
 

@@ -2,6 +2,8 @@
 import numpy as np
 import pytest
 
+from paper_2201_00194_amd import workloads as W
+
 pytestmark = pytest.mark.gpu
 MOST = (1 << 31) - 1
 
@@ -34,6 +36,37 @@ def test_programs_that_end_at_the_last_row(api, last):
     lengths = np.diff(off)
     sums = np.add.accumulate(np.full(lengths.max(), 0.1, np.float32))          # one after the other
     assert np.array_equal(score.cpu().numpy().view(np.uint32), sums[lengths - 1].view(np.uint32))
+
+
+@pytest.mark.parametrize("walk,rows", [("global", MOST), ("lds", MOST), ("treelet", MOST - 255), ("rank", MOST - 511)])
+def test_walks_end_at_the_last_row(api, oracle, tune, walk, rows):
+    """As many rows as the walk's launch takes (2^32 - 1 threads); a call with more is refused.  All rows but the last few are zeros."""
+    import torch
+    tune(api.FS_TUNE_TREELET, 1 if walk == "treelet" else 0)
+    tune(api.FS_TUNE_TREELET_FORM, 0)
+    tune(api.FS_TUNE_RANK, 1 if walk == "rank" else 0)
+    tune(api.FS_TUNE_RANK_TILES, 8)
+    m = W.make_small_family(seed=11, n_programs=300, stmts=(1, 1), n_trees=4, depth=2, k=1, n_features=1, bias=0.25).model
+    if walk == "global":
+        m = W.Model(n_features=1, tree_off=np.zeros(1, np.int32), split_feature=m.split_feature[:0], threshold=m.threshold[:0],
+                    left=m.left[:0], right=m.right[:0], value=m.value[:0], bias=0.25)
+    last = 1000
+    tail = np.random.default_rng(4).random((last, 1), np.float32)
+    zero, expected = (oracle.score_programs(m, x, np.arange(x.shape[0] + 1, dtype=np.int32)) for x in (np.zeros((1, 1), np.float32), tail))
+    x = torch.zeros(api.fs_colblock64_floats(MOST, 1), device="cuda")
+    x[rows - last:rows] = torch.from_numpy(tail[:, 0]).cuda()
+    off = torch.from_numpy(np.linspace(0, rows, 65_537).astype(np.int64).astype(np.int32)).cuda()
+    score, outputs = torch.zeros(65_536, device="cuda"), torch.full((MOST + 640,), 7.0, device="cuda")
+    model = api.fs_model.from_arrays(m)
+    api.fs_score_families([api.Family(model, x, api.FS_COLBLOCK64, rows, off, score, outputs)])
+    assert bool((outputs[:rows - last] == float(zero[0])).all())
+    assert bool((outputs[rows:] == 7.0).all())                                # none is written past the last
+    assert np.array_equal(outputs[rows - last:rows].cpu().numpy().view(np.uint32), expected.view(np.uint32))
+    if rows < MOST:
+        with pytest.raises(api.FsError) as e:
+            api.fs_score_families([api.Family(model, x, api.FS_COLBLOCK64, MOST, off, score, outputs)])
+        assert e.value.code == api.FS_EDEVICE
+    torch.cuda.synchronize()
 
 
 def test_as_many_programs_as_there_are_numbers(api):
