@@ -18,6 +18,8 @@
 //                        child pointers (node i has children 2i, 2i+1, 1-based), the last level of
 //                        splits and the leaves in memory; the wavefronts that share a tile walk
 //                        trees of their own and pass the row's sum on in tree order
+#include <algorithm>
+
 #include "fs_internal.h"
 #include "fs_lds.h"
 
@@ -398,12 +400,13 @@ static __device__ __forceinline__ void wait_for(uint32_t counter, uint32_t count
 // condition had waits put in front of them, 40 %.)
 template <int REGS, bool DUMP>
 __global__ void __launch_bounds__(kRankThreads)
-traverse_rank_kernel(const FamDesc *__restrict__ descs, int n_families)
+traverse_rank_kernel(const FamDesc *__restrict__ descs, int n_families, int first_block)
 {
+    const int block = first_block + (int)blockIdx.x;
     int lo = 0, hi = n_families - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        if (descs[mid].rk_block0 <= (int)blockIdx.x)
+        if (descs[mid].rk_block0 <= block)
             lo = mid;
         else
             hi = mid - 1;
@@ -415,7 +418,7 @@ traverse_rank_kernel(const FamDesc *__restrict__ descs, int n_families)
     const int n_slots = d.rk.slots;             // kRankWaves / T or fewer
     const int my_slot = wave / T, my_tile = wave - my_slot * T;
     const int n_tiles = row_tiles(d.n_rows);
-    const int tile_first = (blockIdx.x - d.rk_block0) * T;
+    const int tile_first = (block - d.rk_block0) * T;
     const int tiles_here = min(T, n_tiles - tile_first);
     const int Fc = rank_tile_cols(d.n_features);
     const uint32_t tile_bytes = (uint32_t)Fc * 128u;
@@ -604,10 +607,14 @@ static int launch_rank_regs(const FamDesc *d_desc, int n_families, int total_blo
         if (dev >= 0 && dev < 16)
             configured[dev][dump ? 1 : 0] = true;
     }
-    hipLaunchKernelGGL(kernel, dim3(total_blocks), dim3(kRankThreads), kRankLdsBytes, stream, d_desc, n_families);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess)
-        return fail_hip(e, "traverse_rank_kernel launch");
+    constexpr int kMostBlocks = (int)((((int64_t)1 << 32) - 1) / kRankThreads);      // of a launch
+    for (int first = 0; first < total_blocks; first += kMostBlocks) {
+        const int n = std::min(total_blocks - first, kMostBlocks);
+        hipLaunchKernelGGL(kernel, dim3(n), dim3(kRankThreads), kRankLdsBytes, stream, d_desc, n_families, first);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess)
+            return fail_hip(e, "traverse_rank_kernel launch");
+    }
     return FS_OK;
 }
 
