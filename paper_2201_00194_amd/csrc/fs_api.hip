@@ -563,6 +563,7 @@ extern "C" int fs_score_families(int32_t n_families, const fs_family *fams, void
     if (rc != FS_OK)
         return rc;
     FamDesc *h = (FamDesc *)db.host;
+    int64_t all_rows = 0, all_programs = 0;
     int64_t trav_blocks = 0, seg_blocks = 0, lds_blocks[kLdsModes] = {0, 0};
     int64_t rk_blocks = 0, bin_blocks = 0, retile_blocks = 0, tl_blocks[2] = {0, 0};
     int rk_regs = 0;
@@ -711,6 +712,8 @@ extern "C" int fs_score_families(int32_t n_families, const fs_family *fams, void
                 dump[md] = true;
         } else
         trav_blocks += (a.n_rows + kTravRowsPerBlock - 1) / kTravRowsPerBlock;
+        all_rows += a.n_rows;
+        all_programs += a.n_programs;
         seg_blocks += ((int64_t)a.n_programs + kSegProgsPerBlock - 1) / kSegProgsPerBlock;
         h[f] = d;
     }
@@ -764,7 +767,7 @@ extern "C" int fs_score_families(int32_t n_families, const fs_family *fams, void
     }
     if (rc == FS_OK && seg_blocks > 0) {
         prof_start(kKernSegsum, stream);
-        rc = launch_segsum(descs, (int)seg_blocks, stream);
+        rc = launch_segsum(descs, all_rows, all_programs, (int)seg_blocks, stream);
         prof_stop(stream);
     }
     const int rc2 = finish_desc(db, stream);

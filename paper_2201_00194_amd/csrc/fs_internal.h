@@ -338,7 +338,8 @@ int launch_traverse_rank(const FamDesc *d_desc, int n_families, int total_blocks
 // chunks only fit a whole compute unit's LDS cannot take the first form).
 int launch_treelet(const Descs<FamDesc> &descs, int launch, int form, int total_blocks, bool dump,
                    hipStream_t stream);
-int launch_segsum(const Descs<FamDesc> &descs, int total_blocks, hipStream_t stream);
+// rows, programs: of all families
+int launch_segsum(const Descs<FamDesc> &descs, int64_t rows, int64_t programs, int total_blocks, hipStream_t stream);
 // max_entries: of a workgroup
 int launch_topk(const Descs<TopkDesc> &descs, int max_k, int max_entries, hipStream_t stream);
 // max_padded: largest (slices * k rounded up to a power of two) over the requests
