@@ -566,7 +566,7 @@ extern "C" int fs_score_families(int32_t n_families, const fs_family *fams, void
     int64_t all_rows = 0, all_programs = 0;
     int64_t trav_blocks = 0, seg_blocks = 0, lds_blocks[kLdsModes] = {0, 0};
     int64_t rk_blocks = 0, bin_blocks = 0, retile_blocks = 0, tl_blocks[2] = {0, 0};
-    int rk_regs = 0;
+    int rk_regs = 0;                                 // a thread of the rank walk for its slot's next trees
     bool rk_dump = false, tl_dump[2] = {false, false};
     const Walks walks = choose_walks(n_families, fams, ctx->n_compute_units);
     if (tune(FS_TUNE_VERBOSE) > 0) {
@@ -583,11 +583,13 @@ extern "C" int fs_score_families(int32_t n_families, const fs_family *fams, void
     // they count towards the length of the launch, though their workgroups take one group each)
     int64_t lds_groups[kLdsModes] = {0, 0};
     double lds_us[kLdsModes] = {0.0, 0.0};           // all groups of the launch, by the planner's estimate
-    int64_t rk_tiles = 0;
+    int64_t rk_tiles = 0, rk_longest = 0;
     for (int f = 0; f < n_families; ++f) {
         const fs_model *m = fams[f].model;
-        if (!walks.treelets(fams[f]) && m->rank_ok)
-            rk_tiles += (fams[f].n_rows + 63) / 64;
+        if (!walks.treelets(fams[f]) && m->rank_ok) {
+            rk_tiles += tiles_of(fams[f]);
+            rk_longest = std::max(rk_longest, tiles_of(fams[f]));
+        }
         if (!walks.treelets(fams[f]) && !m->rank_ok && m->lds_ok) {
             const int64_t g = ((fams[f].n_rows + 63) / 64 + m->lds_tiles - 1) / m->lds_tiles;
             lds_groups[m->lds_mode] += g;
@@ -698,7 +700,10 @@ extern "C" int fs_score_families(int32_t n_families, const fs_family *fams, void
                               a.model->rk_forced_tiles);
             rk_blocks += (tiles + d.rk.tiles - 1) / d.rk.tiles;
             const int slot_bytes = d.rk.per_slot * a.model->rk_tree_bytes, at_once = d.rk.tiles * 64 * 16;
-            rk_regs = std::max(rk_regs, (slot_bytes + at_once - 1) / at_once);
+            // (a few rows of a family do not decide: beside one of half a million, 500 trees of depth 10, eight rows
+            // with a tile a workgroup and so twice the registers made 731 us 746, with 300 trees and 60 features 395 420)
+            if (tiles * kRankSay >= rk_longest)
+                rk_regs = std::max(rk_regs, (slot_bytes + at_once - 1) / at_once);
             if (a.leaf_idx && a.n_rows > 0)
                 rk_dump = true;
         } else if (a.model->lds_ok && (colblock || in_kernel)) {
@@ -756,6 +761,8 @@ extern "C" int fs_score_families(int32_t n_families, const fs_family *fams, void
         prof_stop(stream);
     }
     if (rc == FS_OK && rk_blocks > 0) {
+        if (tune(FS_TUNE_VERBOSE) > 0)
+            fprintf(stderr, "fs_score_families: rank walk of %lld workgroups, next trees take %d registers\n", (long long)rk_blocks, rk_regs);
         prof_start(kKernTraverseRank, stream);
         rc = launch_traverse_rank(d_desc, n_families, (int)rk_blocks, rk_regs, rk_dump, stream);
         prof_stop(stream);

@@ -430,6 +430,7 @@ constexpr int kRankMostSteps = 4;
 constexpr int kRankWaves = 16;
 constexpr int kRankLdsBytes = 160 * 1024;
 constexpr int kRankMostTrees = 8;        // of a slot
+constexpr int kRankSay = 16;             // families of at least a 16th of the longest's tiles decide about the kernel's registers
 struct RankLast {                        // a split of a tree's last level, as in LDS, and its leaves' values
     uint32_t split;
     float left, right;

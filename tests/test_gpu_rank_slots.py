@@ -43,6 +43,32 @@ def test_workgroups_follow_the_length_of_the_call(api, oracle, tune, tiles):  # 
             check_family(oracle, f, dev)
 
 
+@pytest.mark.parametrize("depth,trees", [(10, 150), (11, 100), (12, 41)])
+def test_more_registers_than_the_kernel_has(api, oracle, tune, depth, trees):  # noqa: F811
+    """One tile a workgroup and several turns of 10, 12 and 16 registers a thread: what eight do not hold is read later."""
+    tune(api.FS_TUNE_RANK, 1)
+    tune(api.FS_TUNE_RANK_TILES, 1)
+    features = 100 if depth == 12 else 164
+    fam = W.make_small_family(seed=depth, n_programs=64 * 3 + 5, stmts=(1, 1), n_trees=trees, depth=depth, k=5, n_features=features)
+    check_family(oracle, fam, run_families(api, [fam], api.FS_COLBLOCK64)[0])
+
+
+def test_a_few_rows_do_not_decide_the_registers(api, oracle, tune, capfd):  # noqa: F811
+    tune(api.FS_TUNE_RANK, 1)
+    fams = [W.make_small_family(seed=5, n_programs=64 * 2000, stmts=(1, 1), n_trees=300, depth=7, k=5, n_features=30),
+            W.make_small_family(seed=6, n_programs=60, stmts=(1, 1), n_trees=100, depth=11, k=5, n_features=164)]
+    tune(api.FS_TUNE_VERBOSE, 1)
+    said = []
+    for some in (fams[:1], fams[1:], fams):
+        capfd.readouterr()
+        devs = run_families(api, some, api.FS_COLBLOCK64)
+        said += [int(line.split()[-2]) for line in capfd.readouterr().err.splitlines() if "registers" in line]
+        for f, dev in zip(some, devs):
+            check_family(oracle, f, dev)
+    alone, few, both = said
+    assert few > 8 and both == alone < few
+
+
 def test_models_of_different_trees_in_one_launch(api, oracle, tune):  # noqa: F811
     tune(api.FS_TUNE_RANK, 1)
     fams = [W.make_small_family(seed=70 + d, n_programs=90 + 31 * d, stmts=(1, 4), n_trees=3 + 11 * (12 - d), depth=d, k=8)
