@@ -31,7 +31,7 @@ def same(dev, fam, ps, idx, val):
 
 def families():
     # an LDS-staged irregular model, a rank-coded deep one, and a cut long enough to be sliced
-    return [W.make_small_family(seed=61, n_programs=9000, stmts=(1, 3), n_trees=30, depth=8,
+    return [W.make_small_family(seed=61, n_programs=17_000, stmts=(1, 3), n_trees=30, depth=8,
                                 early_leaf_q=0.2, k=64),
             W.make_small_family(seed=62, n_programs=500, stmts=(2, 6), n_trees=20, depth=9, k=16),
             W.make_small_family(seed=63, n_programs=700, stmts=(1, 1), n_trees=12, depth=4, k=700)]
@@ -88,8 +88,8 @@ def test_workspace_sizes_and_reservation(api, oracle):
     rows = sum(f.n_rows for f in fams)
     rank_tiles = ((fams[1].n_rows + 63) // 64) * 64 * 164 * 2
     assert 4 * rows + rank_tiles <= need <= 4 * rows + rank_tiles + 64
-    # family 0's cut is sliced (9000 programs): slices x k composites of 8 bytes
-    assert api.fs_topk_workspace_bytes(reqs) == 4 * 64 * 8
+    # family 0's cut is sliced (17 000 programs): slices x k composites of 8 bytes
+    assert api.fs_topk_workspace_bytes(reqs) == 8 * 64 * 8
     # a family that brings its own row-score buffer and has no rank-coded model needs nothing
     own = api.DeviceFamily(fams[2], want_row_score=True)
     assert api.fs_workspace_bytes([own.family()]) == 0

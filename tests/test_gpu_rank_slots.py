@@ -77,9 +77,9 @@ def test_models_of_different_trees_in_one_launch(api, oracle, tune):  # noqa: F8
         check_family(oracle, f, dev)
 
 
-@pytest.mark.parametrize("depth,features", [(8, 164), (8, 180), (8, 251), (9, 100), (9, 164), (2, 600), (1, 630), (0, 9)])
-def test_leaf_values_in_lds_or_in_memory(api, oracle, tune, depth, features):  # noqa: F811
-    """They are in memory with the last level's splits, whatever the depth and the room beside the tiles."""
+@pytest.mark.parametrize("depth,features", [(8, 164), (8, 180), (8, 251), (9, 100), (9, 164), (2, 510), (1, 511), (2, 600), (0, 9)])
+def test_last_splits_and_leaf_values_in_memory(api, oracle, tune, depth, features):  # noqa: F811
+    """Whatever the depth and the room beside the tiles.  (More than 511 features and trees of one leaf take other walks.)"""
     tune(api.FS_TUNE_RANK, 1)
     fam = W.make_small_family(seed=depth + features, n_programs=64 * 9 + 7, stmts=(1, 1), n_trees=53, depth=depth, k=5,
                               n_features=features, bias=-0.5)

@@ -48,7 +48,7 @@ def test_noalloc_cut_equals_the_allocating_cut_twice_in_a_row(api, oracle):
     first = both_cuts(api, [big, tied, small], [1024, 64, 500])
     assert_same(*first)
     # second call, smaller input: fewer and shorter lists than the array still holds
-    mid = rng.standard_normal(9000).astype(np.float32)
+    mid = rng.standard_normal(17_000).astype(np.float32)
     tiny = rng.standard_normal(40).astype(np.float32)
     second = both_cuts(api, [mid, tiny], [33, 16])
     assert_same(*second)
@@ -57,6 +57,22 @@ def test_noalloc_cut_equals_the_allocating_cut_twice_in_a_row(api, oracle):
         idx, val = oracle.topk(s, k)
         assert np.array_equal(gi[:k], idx) and np.array_equal(gv[:k].view(np.uint32), val.view(np.uint32))
     for s, k, (gi, gv) in zip([mid, tiny], [33, 16], second[1]):
+        idx, val = oracle.topk(s, k)
+        assert np.array_equal(gi[:k], idx) and np.array_equal(gv[:k].view(np.uint32), val.view(np.uint32))
+
+
+@pytest.mark.parametrize("sizes", [[(9000, 33), (40, 16)], [(16_384, 256)], [(16_384, 257)], [(16_385, 256)], [(16_384, 64), (16_385, 64)],
+                                   [(8192, 4096), (12_000, 20)]])
+def test_noalloc_takes_requests_whole_where_the_allocating_cut_does(api, oracle, sizes):
+    """Up to 16 384 entries with cuts up to 256 are one workgroup's where all requests of the call are; both sides of the lines,
+    behind a call that left longer lists in the array."""
+    rng = np.random.default_rng(len(sizes) + sizes[0][0])
+    both_cuts(api, [rng.standard_normal(100_000).astype(np.float32)], [2048])
+    scores = [np.round(rng.standard_normal(n) * 50).astype(np.float32) for n, _ in sizes]
+    ks = [k for _, k in sizes]
+    cuts = both_cuts(api, scores, ks)
+    assert_same(*cuts)
+    for s, k, (gi, gv) in zip(scores, ks, cuts[1]):
         idx, val = oracle.topk(s, k)
         assert np.array_equal(gi[:k], idx) and np.array_equal(gv[:k].view(np.uint32), val.view(np.uint32))
 
