@@ -180,9 +180,10 @@ typedef struct fs_topk_req {
  * index ascending) (Section 3.2: candidates are sorted by the model's estimate and the
  * top k are kept; Algorithm 1: k = g, or g*p in the foresee step).  One batched
  * submission for all requests.  Errors: FS_EINVAL, FS_EUNSUPPORTED (k > FS_MAX_TOPK),
- * FS_ENOMEM, FS_EDEVICE.  Requests of 8192 entries and more use the device's top-k scratch
+ * FS_ENOMEM, FS_EDEVICE.  Requests of 8192 entries and more may use the device's top-k scratch
  * region, which all fs_topk calls on the device share: two such calls must not overlap in
- * time on different streams.
+ * time on different streams.  (They do not where every request of the call has fewer entries, or
+ * up to 16 384 and k <= 256, or k = 0.)
  */
 int fs_topk(int32_t n_requests, const fs_topk_req *reqs /* HOST */, void *stream);
 
@@ -191,9 +192,10 @@ int fs_topk(int32_t n_requests, const fs_topk_req *reqs /* HOST */, void *stream
  * serving loops, harnesses that forbid hipMalloc.  Same arguments, same result as fs_topk, but
  * the call allocates nothing and never waits: descriptors and the candidate lists of sliced
  * requests (8192 entries and more) live in a fixed 1 MiB array in device memory that the
- * library holds on every GPU it runs on until the process ends.  Limits (FS_EUNSUPPORTED
+ * library holds on every GPU it runs on until the process ends; where every request of a call has
+ * fewer than 8192 entries, or up to 16 384 and k <= 256, or k = 0, none is sliced.  Limits (FS_EUNSUPPORTED
  * beyond them, nothing is enqueued): descriptors of at most 3584 bytes -- 56 per workgroup,
- * one workgroup per request below 8192 entries, up to 16 per longer request, plus 48 per
+ * one workgroup per request that is not sliced, up to 16 per sliced one, plus 48 per
  * sliced request: about 60 workgroups; candidate lists (slices x k x 8 bytes per sliced
  * request) of at most 1 MiB - 3584 bytes; no cut wider than 4096 on a request of 8192 or more
  * entries.  All calls on a GPU share that GPU's array, which keeps the previous call's
@@ -207,9 +209,11 @@ int fs_topk_noalloc(int32_t n_requests, const fs_topk_req *reqs /* HOST */, void
 
 /*
  * Bytes of scoring scratch that fs_score_families(n_families, fams, ...) would use, and of
- * top-k scratch that fs_topk(n_requests, reqs, ...) would use.  Only sizes, layouts, models
- * and the NULL-ness of row_score are looked at; nothing is enqueued.  Return 0 for calls that
- * need none, and 0 with fs_last_error() set for descriptors the scoring / top-k call itself
+ * top-k scratch that is enough for fs_topk(n_requests, reqs, ...).  Requests of 8192 to 16 384
+ * entries count as sliced, though a call of nothing longer does without scratch: so the bytes of
+ * several sets of requests, added up, are enough for them in one call.  Only sizes, layouts,
+ * models and the NULL-ness of row_score are looked at; nothing is enqueued.  Return 0 for calls
+ * that need none, and 0 with fs_last_error() set for descriptors the scoring / top-k call itself
  * would reject.
  */
 size_t fs_workspace_bytes(int32_t n_families, const fs_family *fams /* HOST */);
