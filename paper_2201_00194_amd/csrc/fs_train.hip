@@ -413,7 +413,10 @@ __device__ __forceinline__ long long lane63_ll(long long v)
 // chip; of many programs four share the three atomics, which all go to the same addresses.  A round's launch: 4000 programs
 // of 8.5 rows 6.5 -> 4.0 us, eight families of them 6.9 -> 5.2, 30 000 in one family 11.3 -> 6.3.
 constexpr int kGradThreads = 64, kGradManyThreads = 256;
-constexpr int kGradMany = 16384;                     // programs of a family
+// Programs of a family from which on workgroups have four wavefronts: 8000 of 8.5 rows 4.6 us with one and 4.8 with four, of
+// 1.5 rows 4.2 and 4.2, 12 000 5.4 and 5.1, 5.0 and 4.1, 16 000 6.2 and 5.6, 5.9 and 4.1, four families of 30 000 18.4 and 14.7; 4000
+// 3.9 and 4.9, four families of them 4.4 and 5.4.
+constexpr int kGradMany = 10000;
 constexpr int kGradRows = 16;
 
 // Bits of the sum over the wavefront.
@@ -2156,12 +2159,12 @@ static void end_work(BatchBuf &b, fs_trainer *const *trainers, int n, hipStream_
 // `most`: programs of the largest of `n` trainers.
 static void launch_grad(const TrainDesc *d, int most, unsigned n, float grad_scale, int with_grad, int turn, hipStream_t stream)
 {
+    const int threads = most > kGradMany ? kGradManyThreads : kGradThreads;
+    const dim3 grid((unsigned)(((int64_t)most + threads - 1) / threads), n);
     if (most > kGradMany)
-        hipLaunchKernelGGL(train_grad_kernel<kGradManyThreads>, dim3((unsigned)(((int64_t)most + kGradManyThreads - 1) / kGradManyThreads), n),
-                           dim3(kGradManyThreads), 0, stream, d, grad_scale, with_grad, turn);
+        hipLaunchKernelGGL(train_grad_kernel<kGradManyThreads>, grid, dim3(threads), 0, stream, d, grad_scale, with_grad, turn);
     else
-        hipLaunchKernelGGL(train_grad_kernel<kGradThreads>, dim3((unsigned)((most + kGradThreads - 1) / kGradThreads), n),
-                           dim3(kGradThreads), 0, stream, d, grad_scale, with_grad, turn);
+        hipLaunchKernelGGL(train_grad_kernel<kGradThreads>, grid, dim3(threads), 0, stream, d, grad_scale, with_grad, turn);
 }
 
 // Uploads descriptors; returns the device array.

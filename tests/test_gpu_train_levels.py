@@ -63,7 +63,7 @@ def test_counted_children_of_uneven_programs(api, T, tune, programs, slab, packe
     check(api, T, ts, rounds=2, max_depth=7, eta=0.5, lam=1.0)
 
 
-@pytest.mark.parametrize("programs,stmts", [(65, (15, 17)), (64, (16, 16)), (300, (1, 50)), (16_384, (1, 3)), (16_385, (1, 3))])
+@pytest.mark.parametrize("programs,stmts", [(65, (15, 17)), (64, (16, 16)), (300, (1, 50)), (10_000, (1, 3)), (10_001, (1, 3))])
 def test_gradients_of_long_programs_and_of_many(api, T, programs, stmts):
     """Around the sixteen rows of a program that are held for its records, and on both sides of the line between
     workgroups of one wavefront and of four."""
