@@ -5,12 +5,11 @@
 // launch shows in full) and every walk of a chunk takes the steps of its deepest tree; the LDS walk pays
 // for every level and for eight times the LDS reads.  Which one wins depends on layout and length of the call.
 // Fitted to 597 models of 32 to 500 irregular or perfect trees of depth 4 to 12 on 24 to 250 features, 5 to
-// 16 000 tiles, both layouts; the estimates are off by 3 to 8 % (rms).  Timed on 379 models
-// that neither the fit nor a look at its errors used (40 to 350 trees, 32 to 248 features, 12 to 8500 tiles; 8338
-// calls): treelets alone are slower than the LDS walk by more than 10 % in 1694, by up to 2.80 times; the walk
-// chosen here in 27, by up to 1.22, and it is slower than treelets by more than 10 % in 34, by up to 1.18.  The
-// geometric mean over all calls is 0.2 % above the better walk's each time, with treelets alone 6.1 %, with the
-// LDS walk alone 18 %.
+// 16 000 tiles, both layouts, with walks that were slower than they are now, the treelets' coder most of all.  Timed since,
+// 80 models of 36 to 400 trees, depth 4 to 12 (perfect ones to 7), 1 to 8000 tiles, 1090 calls: the walk chosen takes 7.3 % more than
+// the better one on the geometric mean, treelets alone 5.0 %, the LDS walk alone 32 %; 177 calls lose more than 10 %.
+// (6.9 %, 5.9 % and 30 % with the coder before.)  Most of that are models of few trees with row-major or long calls, up to three
+// times as long, which have no treelets at all because of the limit on their cost in fs_model_create.
 #ifndef FS_FORMS_H
 #define FS_FORMS_H
 

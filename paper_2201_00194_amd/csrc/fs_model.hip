@@ -569,7 +569,7 @@ bool bucket_tables(fs_model *m, int n_features, int max_cuts, const std::vector<
 
 }  // namespace
 
-// Workgroups of the walk: what is walked side by side decides (neither the LDS nor vector issue is busy), up to eight
+// Workgroups of the walk: what is walked side by side decides (no unit is full), up to eight
 // trees a slot, and how full the last round of workgroups is.  0.5 M rows of 164 features, 500 trees of depth 10, us by tiles
 // a workgroup: 849 with 4 (128 walks), 896 with 5 (120), 897 with 3 (120), 946 with 6 (96), 963 with 2 (112); 4800 rows: 213
 // with 8, 136 with 6, 90 with 4, 59 with 2, 48 with 1.  40 000 rows of 60 features, 300 trees of depth 8: 63, 63, 50, 57, 68,
@@ -966,12 +966,14 @@ extern "C" int fs_model_create(fs_model **out, int32_t n_features, int32_t n_tre
                     limits.pair_only = true;
                     limits.cost = 13.5 * (double)n_trees * (double)shapes.max_depth() + 3.0 * (double)n_features;
                 }
-                // Every segment codes the rows anew, the rank walk codes them once.  Time of treelets over the rank
-                // walk's, perfect trees of depth 8, 36 to 500 of them, 24 to 250 features, 5 to 16 000 tiles, both
-                // layouts, models that the other limits take: below 400 columns in all 0.20 to 1.41, geometric mean
-                // 0.58 (61 models; 65 of 1098 calls lose more than 2 %, 51 of them of 1000 to 2500 tiles, 51 of 24 to
-                // 64 features); from 400 columns 0.53 to 1.76, mean 1.01 (16 models; 135 of 288 calls lose more than
-                // 2 %; three models of three segments with double-buffered tables 0.53 to 1.25, mean 0.78).
+                // Every segment codes the rows anew, the rank walk codes them once.  The line was drawn with an earlier
+                // form of either walk.  As they are now, time of treelets over the rank walk's, 90 models of 36 to 500
+                // perfect trees of depth 8, 24 to 250 features, 1 to 8000 tiles, both layouts: below 400 columns in all
+                // models that take treelets 0.22 to 1.94, geometric mean 0.65 (63 models; 176 of 862 calls lose more than
+                // 2 %, 163 of them of up to 1024 tiles, where the rank walk gained most since), models that the other
+                // limits turn down 0.13 to 2.61, mean 0.67 (25 models, 334 calls, 157 lose); from 400 columns 0.99 to
+                // 2.35, mean 1.69 (2 models, 26 calls, 24 lose).  No line on the model alone is right for both: long calls and
+                // few trees are the treelets', short calls of many trees the rank walk's.
                 if (ranks_pay) {
                     limits.cols = kTreeletMostRankCols;
                     limits.ranks = true;

@@ -313,15 +313,19 @@ int launch_rank_code(const FamDesc *d_desc, int n_families, int total_blocks, hi
 // trees of depth 10 took 5500 clocks, 3300 of them walks, the rest copying 64 KB into LDS and
 // adding up while nothing else ran.  2.1 M rows, 500 such trees: 4.63 ms, so 3.85.)
 //
-// Two LDS reads a level are a chain of latencies, so what decides is how many walks fit side by side (at 72 of them vector
-// issue was 47 % and LDS 55 %; at 128 it is 61 %, and an LDS instruction every 4.15 clocks, the mean of a feature's
-// conflict-free read, 2.4, and a node's at random, 5.8), and what they need is room: half of a tree's splits are its last level and half of its words the
+// Two LDS reads a level are a chain of latencies, so what decides is how many walks fit side by side, and what they need
+// is room: half of a tree's splits are its last level and half of its words the
 // leaves, each read once a walk.  So both stay in memory, a split and its two values in one record: a slot asks for
 // its walks' records, replaces its trees, and then takes the last decisions and adds the values up.  A tree of depth
 // 10 is 2 KB in LDS then and four tiles have 16 wavefronts of eight walks.  (2.1 M rows of 164 features, 500 trees of
 // depth 10, the call: 3.82 ms with splits of all levels in LDS, 12 wavefronts of six walks, so 3.01; half a million rows,
 // 300 trees of depth 8 541 us and 476, of depth 9 627 and 527, 200 of depth 11 353 and 272, 100 of depth 12 in 131 072
 // rows 198 and 121.  With the leaves in LDS too, as for depth 8 before, 480 instead of 476, and never less.)
+//
+// No unit is full then, there: vector issue 61 % of the clocks (47 at 72 walks); an LDS instruction every 4.15 clocks, where the
+// reads take 2.9 on the mean at the rates measured for them alone (a feature's 2.4; a node's 2.4 in the first six levels,
+// 4.2 to 6.7 in the next three); addresses of vector loads 45, their data 59, a cache access every 1.5 clocks.  The records
+// are not what it waits for: with those of all walks of a tree at one address the kernel takes 2.63 ms instead of 2.70.
 //
 // LDS map:  [0, slots * per_slot * tree_bytes)  the slots' trees, each [unused][splits in heap order, 1-based]
 //           [tile0 - T*256 - 128, ...)          running sums [tile][lane], then the counters

@@ -171,7 +171,8 @@ __device__ __forceinline__ void code_columns(const FamDesc &d, const TreeletSegm
         row_at[t] = rowmajor ? (uint32_t)min(64 * t + lane, d.n_rows - 1 - 64 * tile_first) * 4u * (uint32_t)F
                              : (uint32_t)min(t, n_tiles - 1 - tile_first) * 256u * (uint32_t)F + 4u * (uint32_t)lane;
     auto col_of = [&](int b, int j) { return min(b * NC + j, C - 1); };   // past the last: it again
-    // What a batch's searches need, asked for at once and before the wait for its values.
+    // What a batch's searches need, asked for at once and before the wait for its values.  (Sixteen columns' do not all fit the
+    // scalar registers: the forms of one and two tiles a workgroup spill 109 and 43 of them to vector registers.)
     struct Batch { float scale[NC], offset[NC]; int steps[NC]; };
     auto read_batch = [&](int b) {
         Batch q;
