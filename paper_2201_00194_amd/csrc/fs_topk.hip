@@ -43,10 +43,11 @@ __device__ __forceinline__ uint32_t score_key(float s)
 constexpr int kTopkWaves = kTopkThreads / 64;
 // Entries a thread holds, all loads in flight at once: 16 where a workgroup has more than 8192 entries, as their keys are
 // read once then (262 144 entries in 16 slices, cut of 64: 27.5 us with 8, so 17.5; cut of 1024 53.5 and 49.1), else 8.
-// (A request alone whose cut falls among equal scores is the one that slices served better: their histograms' hot digits
-// gather fewer entries each.  16 of 16 384: random scores 11.2 us in slices and 7.9 whole, a tenth ones
+// (A request alone whose cut falls among equal scores is the one that slices served better: all passes and sweeps over all
+// entries are one workgroup's then.  16 of 16 384: random scores 11.2 us in slices and 7.9 whole, a tenth ones
 // among zeros 12.1 and 18.6, seven values 16.1 and 19.9, all equal 17.8 and 18.2; 300 such requests of 64 79.6 and
-// 29.2, 99 and 52 for seven values.)
+// 29.2, 99 and 52 for seven values.  A wavefront's most frequent digit counted by ballots does not help: 18.6 -> 22.6,
+// random 7.9 -> 9.5.)
 constexpr int kTopkFew = 8, kTopkMany = kTopkAtOnce / kTopkThreads;
 
 // Scores and keys of U consecutive 64-element pieces starting at `base`, this lane's element of
